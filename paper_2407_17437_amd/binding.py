@@ -113,7 +113,9 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream or None
+        # the current stream's handle without a torch.cuda.Stream object around it: 0.2 against 2.8 us per call, which
+        # the calls that last 10 .. 20 us are bound by
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream or None
     return stream or None
@@ -407,7 +409,7 @@ class MLP:
         off = lay[1 + 4 * l + k] // 4
         L = self.layers[l]
         if kind in ("A", "dZ"):
-            return self.workspace[off: off + L.rows * ld].view(L.rows, ld)[:, :batch]
+            return self.workspace.as_strided((L.rows, batch), (ld, 1), self.workspace.storage_offset() + off)   # (one torch call: part of every forward())
         n = L.nnz if kind == "g" else L.rows
         return self.workspace[off: off + n]
 
