@@ -22,8 +22,8 @@
  * - Dense matrices hold one example per column (Appendix B listing: Xtrain[:, batch]).
  *   They are fp32, row-major (features, ld): element (i, c) is at base[i*ld + c], with
  *   ld >= batch.  Columns batch..ld-1 are padding: never written, and their contents
- *   never influence a result.  Calls are fastest when every ld is a multiple of 4 and
- *   every base pointer is 16-byte aligned; other values take a slower kernel.
+ *   never influence a result.  Any ld and any 4-byte aligned base take the same kernels; they
+ *   are fastest when every row starts on a 128-byte line (ld a multiple of 32).
  * - Biases are dense fp32 vectors of length rows (Section 3: biases are not sparsified).
  * - Every pointer is a DEVICE pointer owned by the caller unless the comment says
  *   "host".  The library owns only what *_create builds and frees it in *_destroy.

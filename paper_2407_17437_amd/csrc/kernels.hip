@@ -38,8 +38,35 @@ __device__ __forceinline__ float4 keep_where_positive(float4 x, float4 m)
 }
 __device__ __forceinline__ float keep_where_positive(float x, float m) { return m > 0.f ? x : 0.f; }
 
-__device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-__device__ __forceinline__ void st4(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
+// 16-byte accesses to global memory ask for 4-byte alignment only, which the hardware serves: matrices of any
+// leading dimension run on the kernels below (a first layer of 1501 x 3001 at batch 77 stored without padding:
+// forward 9.1 us and SDDMM 29.7 us on one-column-per-lane kernels, here 7.5 us, and 13.1 us for the SDDMMs of both
+// layers, which now share a grid).
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 ld4(const float *p)
+{
+    const v4f_any r = *reinterpret_cast<const v4f_any *>(p);
+    return make_float4(r.x, r.y, r.z, r.w);
+}
+__device__ __forceinline__ void st4(float *p, float4 v)
+{
+    v4f_any r = {v.x, v.y, v.z, v.w};
+    *reinterpret_cast<v4f_any *>(p) = r;
+}
+// First of the four columns that the lane at column `col` (a multiple of 4, below `batch`, batch >= 4) works on: where
+// fewer than four are left the access moves back to the row's last four columns, so that nothing beyond the batch is
+// read or written whatever the leading dimension.  The columns that it shares with its neighbour are computed by both,
+// in the same order, to the same bits.
+__device__ __forceinline__ int four_columns(int col, int batch) { return min(col, batch - 4); }
+// ... and the lane's share of a sum over columns: those of its four that the neighbour does not have
+__device__ __forceinline__ float4 drop_shared(float4 x, int col, int first)
+{
+    if (first < col) x.x = 0.f;
+    if (first + 1 < col) x.y = 0.f;
+    if (first + 2 < col) x.z = 0.f;
+    return x;
+}
 
 // Data-parallel-primitive move: lane l receives x from the lane that CTRL names; lanes in rows
 // not selected by ROW_MASK receive 0.
@@ -126,24 +153,11 @@ __device__ __forceinline__ gmem_ptr row_base(const void *base, int j, uint32_t l
     return reinterpret_cast<gmem_ptr>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 __device__ __forceinline__ gmem_ptr as_gmem(const void *p) { return reinterpret_cast<gmem_ptr>(reinterpret_cast<uint64_t>(p)); }
-typedef float v4f __attribute__((ext_vector_type(4)));
-template <typename V>
-__device__ __forceinline__ V gload(gmem_ptr row, uint32_t byte_offset);
-template <>
-__device__ __forceinline__ float4 gload<float4>(gmem_ptr row, uint32_t byte_offset)
+__device__ __forceinline__ float4 gload4(gmem_ptr row, uint32_t byte_offset)
 {
-    const v4f r = *reinterpret_cast<const __attribute__((address_space(1))) v4f *>(row + byte_offset);
+    const v4f_any r = *reinterpret_cast<const __attribute__((address_space(1))) v4f_any *>(row + byte_offset);
     return make_float4(r.x, r.y, r.z, r.w);
 }
-template <>
-__device__ __forceinline__ float gload<float>(gmem_ptr row, uint32_t byte_offset)
-{
-    return *reinterpret_cast<const __attribute__((address_space(1))) float *>(row + byte_offset);
-}
-
-template <int VEC> struct Pack;
-template <> struct Pack<4> { using type = float4; };
-template <> struct Pack<1> { using type = float; };
 
 __device__ __forceinline__ void fma_into(float (&acc)[4], float w, float4 x)
 {
@@ -152,15 +166,13 @@ __device__ __forceinline__ void fma_into(float (&acc)[4], float w, float4 x)
     acc[2] = fmaf(w, x.z, acc[2]);
     acc[3] = fmaf(w, x.w, acc[3]);
 }
-__device__ __forceinline__ void fma_into(float (&acc)[1], float w, float x) { acc[0] = fmaf(w, x, acc[0]); }
 
 // U consecutive stored entries starting at p: all index/weight fetches, then all gathers, then
 // the FMAs, so that U*NV reads are in flight per wave.
-template <int VEC, int NV, bool XMASK, int U>
+template <int NV, bool XMASK, int U>
 __device__ __forceinline__ void spmm_step(const SpmmArgs &a, int p, uint32_t ldxb, uint32_t ldmb,
-                                          const uint32_t (&off)[NV], float (&acc)[NV][VEC])
+                                          const uint32_t (&off)[NV], float (&acc)[NV][4])
 {
-    using V = typename Pack<VEC>::type;
     int j[U];
     float w[U];
 #pragma unroll
@@ -168,16 +180,16 @@ __device__ __forceinline__ void spmm_step(const SpmmArgs &a, int p, uint32_t ldx
         j[u] = a.indices[p + u];
         w[u] = a.values[p + u];
     }
-    V x[U][NV];
+    float4 x[U][NV];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const gmem_ptr xr = row_base(a.X, j[u], ldxb);
 #pragma unroll
-        for (int t = 0; t < NV; ++t) x[u][t] = gload<V>(xr, off[t]);
+        for (int t = 0; t < NV; ++t) x[u][t] = gload4(xr, off[t]);
         if constexpr (XMASK) {
             const gmem_ptr mr = row_base(a.XM, j[u], ldmb);
 #pragma unroll
-            for (int t = 0; t < NV; ++t) x[u][t] = keep_where_positive(x[u][t], gload<V>(mr, off[t]));
+            for (int t = 0; t < NV; ++t) x[u][t] = keep_where_positive(x[u][t], gload4(mr, off[t]));
         }
     }
 #pragma unroll
@@ -186,35 +198,48 @@ __device__ __forceinline__ void spmm_step(const SpmmArgs &a, int p, uint32_t ldx
         for (int t = 0; t < NV; ++t) fma_into(acc[t], w[u], x[u][t]);
 }
 
+// Bias, ReLU and the optional output mask on the four columns from `col` on of one row, and their store.
+__device__ __forceinline__ void spmm_store(const SpmmArgs &a, int row, int col, const float (&acc)[4])
+{
+    const float b = a.bias ? a.bias[row] : 0.f;
+    float y[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        y[k] = acc[k] + b;
+        if (a.relu) y[k] = y[k] > 0.f ? y[k] : 0.f;
+    }
+    float4 o = make_float4(y[0], y[1], y[2], y[3]);
+    if (a.YM) o = keep_where_positive(o, ld4(a.YM + static_cast<int64_t>(row) * a.ldym + col));
+    st4(a.Y + static_cast<int64_t>(row) * a.ldy + col, o);
+}
+
 // ---------------------------------------------------------------------------------------
-// SpMM.  VEC = floats per lane access (4: 16-byte accesses, needs leading dimensions that are
-// multiples of 4 and 16-byte aligned bases; 1: anything).  A wave covers 64*VEC*NV columns;
-// blockIdx.y walks over column tiles.
+// SpMM, 16-byte accesses.  A wave covers 64*4*NV columns; blockIdx.y walks over column tiles.
 // ---------------------------------------------------------------------------------------
-template <int VEC, int NV, bool XMASK>
+template <int NV, bool XMASK>
 __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, const int col_tile)
 {
     constexpr int U = NV >= 4 ? 2 : (NV == 2 ? 4 : 8);
-    __shared__ float red[kWavesPerBlock][NV][VEC][kWave];
+    __shared__ float red[kWavesPerBlock][NV][4][kWave];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = wave_in_block();
     const WaveTask task = wave_task(a.blocks, block);
-    const int col_base = col_tile * (kWave * VEC * NV);
+    const int col_base = col_tile * (kWave * 4 * NV);
 
     // Lanes whose columns lie beyond the batch re-read the tile's first columns and are never stored.
-    // A 4-wide access that starts below `batch` stays inside the row: ld is a multiple of 4 and >= batch.
     int col[NV];
     bool on[NV];
     uint32_t off[NV];
-    float acc[NV][VEC];
+    float acc[NV][4];
 #pragma unroll
     for (int t = 0; t < NV; ++t) {
-        col[t] = col_base + (t * kWave + lane) * VEC;
+        col[t] = col_base + (t * kWave + lane) * 4;
         on[t] = col[t] < a.batch;
-        off[t] = static_cast<uint32_t>(on[t] ? col[t] : col_base) * 4u;
+        col[t] = four_columns(on[t] ? col[t] : col_base, a.batch);
+        off[t] = static_cast<uint32_t>(col[t]) * 4u;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) acc[t][k] = 0.f;
+        for (int k = 0; k < 4; ++k) acc[t][k] = 0.f;
     }
 
     if (task.row >= 0) {
@@ -223,12 +248,12 @@ __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, co
         int p = task.s0;
         const int pe = task.s1;
         // only entries of this wave's share are gathered: the gather stream is what the kernel pays for
-        for (; p + U <= pe; p += U) spmm_step<VEC, NV, XMASK, U>(a, p, ldxb, ldmb, off, acc);
+        for (; p + U <= pe; p += U) spmm_step<NV, XMASK, U>(a, p, ldxb, ldmb, off, acc);
         if constexpr (U >= 8)
-            if (p + 4 <= pe) { spmm_step<VEC, NV, XMASK, 4>(a, p, ldxb, ldmb, off, acc); p += 4; }
+            if (p + 4 <= pe) { spmm_step<NV, XMASK, 4>(a, p, ldxb, ldmb, off, acc); p += 4; }
         if constexpr (U >= 4)
-            if (p + 2 <= pe) { spmm_step<VEC, NV, XMASK, 2>(a, p, ldxb, ldmb, off, acc); p += 2; }
-        if (p < pe) spmm_step<VEC, NV, XMASK, 1>(a, p, ldxb, ldmb, off, acc);
+            if (p + 2 <= pe) { spmm_step<NV, XMASK, 2>(a, p, ldxb, ldmb, off, acc); p += 2; }
+        if (p < pe) spmm_step<NV, XMASK, 1>(a, p, ldxb, ldmb, off, acc);
     }
 
     if (task.lg > 0) {  // uniform over the work-group
@@ -236,7 +261,7 @@ __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, co
 #pragma unroll
             for (int t = 0; t < NV; ++t)
 #pragma unroll
-                for (int k = 0; k < VEC; ++k) red[wv][t][k][lane] = acc[t][k];
+                for (int k = 0; k < 4; ++k) red[wv][t][k][lane] = acc[t][k];
         }
         __syncthreads();
         if (task.part == 0) {
@@ -244,7 +269,7 @@ __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, co
 #pragma unroll
                 for (int t = 0; t < NV; ++t)
 #pragma unroll
-                    for (int k = 0; k < VEC; ++k) acc[t][k] += red[wv + s][t][k][lane];
+                    for (int k = 0; k < 4; ++k) acc[t][k] += red[wv + s][t][k][lane];
         }
     }
     if (task.row < 0 || task.part != 0) return;
@@ -254,43 +279,12 @@ __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, co
         float *sr = a.scratch + static_cast<int64_t>(block) * a.scratch_ld;
 #pragma unroll
         for (int t = 0; t < NV; ++t)
-#pragma unroll
-            for (int k = 0; k < VEC; ++k)
-                if (col[t] + k < a.batch) sr[col[t] + k] = acc[t][k];
+            if (on[t]) st4(sr + col[t], make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]));
         return;
     }
-
-    const float b = a.bias ? a.bias[task.row] : 0.f;
-    float *yr = a.Y + static_cast<int64_t>(task.row) * a.ldy;
-    const float *ym = a.YM ? a.YM + static_cast<int64_t>(task.row) * a.ldym : nullptr;
 #pragma unroll
-    for (int t = 0; t < NV; ++t) {
-        if (!on[t]) continue;
-        float y[VEC];
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            y[k] = acc[t][k] + b;
-            if (a.relu) y[k] = y[k] > 0.f ? y[k] : 0.f;
-        }
-        if constexpr (VEC == 4) {
-            if (col[t] + 4 <= a.batch) {
-                float4 o = make_float4(y[0], y[1], y[2], y[3]);
-                if (ym) o = keep_where_positive(o, ld4(ym + col[t]));
-                st4(yr + col[t], o);
-            } else {
-                for (int k = 0; k < 4; ++k)
-                    if (col[t] + k < a.batch) {
-                        float o = y[k];
-                        if (ym) o = keep_where_positive(o, ym[col[t] + k]);
-                        yr[col[t] + k] = o;
-                    }
-            }
-        } else {
-            float o = y[0];
-            if (ym) o = keep_where_positive(o, ym[col[t]]);
-            yr[col[t]] = o;
-        }
-    }
+    for (int t = 0; t < NV; ++t)
+        if (on[t]) spmm_store(a, task.row, col[t], acc[t]);
 }
 
 // One pass of U gather instructions of the grouped SpMM: every index move, then every gather,
@@ -313,10 +307,10 @@ __device__ __forceinline__ void grouped_pass(gmem_ptr Xg, gmem_ptr Mg, int src, 
     }
     float4 x[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = gload<float4>(Xg, ro[u] + off);
+    for (int u = 0; u < U; ++u) x[u] = gload4(Xg, ro[u] + off);
     if constexpr (XMASK) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = keep_where_positive(x[u], gload<float4>(Mg, mo[u] + off));
+        for (int u = 0; u < U; ++u) x[u] = keep_where_positive(x[u], gload4(Mg, mo[u] + off));
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -346,9 +340,9 @@ __device__ __forceinline__ void spmm_body_grouped(const SpmmArgs &a, const int b
     const int grp = lane / GS;
     const int lig = lane % GS;
     const WaveTask task = wave_task(a.blocks, block);
-    const int col = col0 + lig * 4;
-    const bool on = col < a.batch;
-    const uint32_t off = static_cast<uint32_t>(on ? col : col0) * 4u;
+    const bool on = col0 + lig * 4 < a.batch;
+    const int col = four_columns(on ? col0 + lig * 4 : col0, a.batch);
+    const uint32_t off = static_cast<uint32_t>(col) * 4u;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 
     if (task.row >= 0) {
@@ -399,33 +393,10 @@ __device__ __forceinline__ void spmm_body_grouped(const SpmmArgs &a, const int b
     if (!on) return;
 
     if (task.huge) {
-        float *sr = a.scratch + static_cast<int64_t>(block) * a.scratch_ld;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (col + k < a.batch) sr[col + k] = acc[k];
+        st4(a.scratch + static_cast<int64_t>(block) * a.scratch_ld + col, make_float4(acc[0], acc[1], acc[2], acc[3]));
         return;
     }
-    const float b = a.bias ? a.bias[task.row] : 0.f;
-    float *yr = a.Y + static_cast<int64_t>(task.row) * a.ldy;
-    const float *ym = a.YM ? a.YM + static_cast<int64_t>(task.row) * a.ldym : nullptr;
-    float y[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        y[k] = acc[k] + b;
-        if (a.relu) y[k] = y[k] > 0.f ? y[k] : 0.f;
-    }
-    if (col + 4 <= a.batch) {
-        float4 o = make_float4(y[0], y[1], y[2], y[3]);
-        if (ym) o = keep_where_positive(o, ld4(ym + col));
-        st4(yr + col, o);
-    } else {
-        for (int k = 0; k < 4; ++k)
-            if (col + k < a.batch) {
-                float o = y[k];
-                if (ym) o = keep_where_positive(o, ym[col + k]);
-                yr[col + k] = o;
-            }
-    }
+    spmm_store(a, task.row, col, acc);
 }
 
 // Packed SpMM for short rows: each group of GS lanes owns one row, so a gather instruction
@@ -443,9 +414,9 @@ __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int bl
     const int wv = wave_in_block();
     const int grp = lane / GS;
     const int lig = lane % GS;
-    const int col = col0 + lig * 4;
-    const bool on = col < a.batch;
-    const uint32_t off = static_cast<uint32_t>(on ? col : col0) * 4u;
+    const bool on = col0 + lig * 4 < a.batch;
+    const int col = four_columns(on ? col0 + lig * 4 : col0, a.batch);
+    const uint32_t off = static_cast<uint32_t>(col) * 4u;
     const uint32_t ldxb = static_cast<uint32_t>(a.ldx) * 4u;
     const uint32_t ldmb = XMASK ? static_cast<uint32_t>(a.ldxm) * 4u : 0u;
     const gmem_ptr Xg = as_gmem(a.X);
@@ -511,27 +482,8 @@ __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int bl
         } while (base < maxlen);
         d = dn;
         if (row < 0 || !on) continue;
-        const float b = a.bias ? a.bias[row] : 0.f;
-        float *yr = a.Y + static_cast<int64_t>(row) * a.ldy;
-        const float *ym = a.YM ? a.YM + static_cast<int64_t>(row) * a.ldym : nullptr;
-        float y[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            y[k] = (len > 0 ? acc[k] : 0.f) + b;  // an empty row gathered (with weight 0) from entry 0 of the matrix
-            if (a.relu) y[k] = y[k] > 0.f ? y[k] : 0.f;
-        }
-        if (col + 4 <= a.batch) {
-            float4 o = make_float4(y[0], y[1], y[2], y[3]);
-            if (ym) o = keep_where_positive(o, ld4(ym + col));
-            st4(yr + col, o);
-        } else {
-            for (int k = 0; k < 4; ++k)
-                if (col + k < a.batch) {
-                    float o = y[k];
-                    if (ym) o = keep_where_positive(o, ym[col + k]);
-                    yr[col + k] = o;
-                }
-        }
+        if (len == 0) acc[0] = acc[1] = acc[2] = acc[3] = 0.f;  // an empty row gathered (with weight 0) from entry 0 of the matrix
+        spmm_store(a, row, col, acc);
     }
 }
 
@@ -590,10 +542,10 @@ __global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, co
     spmm_body_grouped<GS, XMASK>(a, rb, tile * GS * 4);
 }
 
-template <int VEC, int NV, bool XMASK>
+template <int NV, bool XMASK>
 __global__ __launch_bounds__(kBlock) void spmm_kernel(const SpmmArgs a)
 {
-    spmm_body<VEC, NV, XMASK>(a, blockIdx.x, blockIdx.y);
+    spmm_body<NV, XMASK>(a, blockIdx.x, blockIdx.y);
 }
 
 // SpMM for batches of at most 4 columns (inference on one or a few examples): there is no batch
@@ -666,9 +618,9 @@ __global__ __launch_bounds__(kFullWaves * kWave) void full_rows_kernel(const Spm
     const int wv = wave_in_block();
     const int K = a.x_rows;
     const int slice = blockIdx.x;
-    const int col = (blockIdx.y * kWave + lane) * 4;
-    const bool on = col < a.batch;
-    const int64_t xoff = on ? col : 0;
+    const bool on = static_cast<int>((blockIdx.y * kWave + lane) * 4) < a.batch;
+    const int col = on ? four_columns((blockIdx.y * kWave + lane) * 4, a.batch) : 0;
+    const int64_t xoff = col;
     constexpr int KW = kFullSlice / kFullWaves;  // operand rows per wave: all requested before the first use
     static_assert(KW <= 64 && (KW & (KW - 1)) == 0, "one weight per lane");
     const int k_begin = slice * kFullSlice + wv * KW;
@@ -955,8 +907,8 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = wave_in_block();
     const int lrow = lane >> 4, lig = lane & 15;
-    const int col = tile * kStageCols + lig * 4;
-    const bool col_on = col < a.batch;
+    const bool col_on = tile * kStageCols + lig * 4 < a.batch;
+    const int col = four_columns(tile * kStageCols + lig * 4, a.batch);
     const char *lds = reinterpret_cast<const char *>(stage) + lig * 16;
     if (threadIdx.x < kStageCols / 4) stage[kStageRows * kStageCols / 4 + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);  // (visible after the first barrier)
     const int n_cb = a.blocks.staged_cblocks;
@@ -1097,8 +1049,7 @@ __global__ __launch_bounds__(256) void spmm_finish_kernel(const SpmmArgs a)
 // columns per lane and tile, NV tiles: G*4*NV >= batch), reduced inside the group with DPP
 // moves.  Results of up to 64 consecutive entries are collected one per lane, so the store of
 // g -- or the fused momentum step on values/velocity -- is a coalesced access.
-// EXACT4: batch is a multiple of 4 (no column tail inside a 4-wide access).
-// Lanes whose columns lie beyond the batch hold dZ = 0 and re-read columns 0..3 of the row.
+// Lanes whose columns lie beyond the batch hold dZ = 0 and re-read the row's first columns.
 // ---------------------------------------------------------------------------------------
 // By-product carried by an SDDMM launch: the mean of the per-column losses the head kernel left.
 __device__ __forceinline__ void mean_loss_task(const SddmmArgs &a, int block)
@@ -1115,9 +1066,9 @@ __device__ __forceinline__ void mean_loss_task(const SddmmArgs &a, int block)
 // then the dot products and their reductions.  Straight-line, so that all U*NV gathers stay in
 // flight (see grouped_pass).  Group `grp` works on slot it*NG+grp of the chunk in iteration it;
 // that slot's row offset sits in lane grp*G+it, and its result is kept by the lane with lig == it.
-template <int G, int NV, bool EXACT4, int U>
+template <int G, int NV, int U>
 __device__ __forceinline__ void sddmm_pass(gmem_ptr Xg, int it0, int my_ro, const uint32_t (&off)[NV],
-                                           const float4 (&dz)[NV], int batch, float &res)
+                                           const float4 (&dz)[NV], float &res)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int lig = lane % G;
@@ -1133,20 +1084,12 @@ __device__ __forceinline__ void sddmm_pass(gmem_ptr Xg, int it0, int my_ro, cons
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int t = 0; t < NV; ++t) x[u][t] = gload<float4>(Xg, ro[u] + off[t]);
+        for (int t = 0; t < NV; ++t) x[u][t] = gload4(Xg, ro[u] + off[t]);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         float part = 0.f;
 #pragma unroll
         for (int t = 0; t < NV; ++t) {
-            if constexpr (!EXACT4) {
-                // padding columns inside the access may hold anything, also NaN: drop them
-                const int c = (t * G + lig) * 4;
-                if (c + 1 >= batch) x[u][t].y = 0.f;
-                if (c + 2 >= batch) x[u][t].z = 0.f;
-                if (c + 3 >= batch) x[u][t].w = 0.f;
-                if (c >= batch) x[u][t].x = 0.f;
-            }
             part = fmaf(dz[t].x, x[u][t].x, part);
             part = fmaf(dz[t].y, x[u][t].y, part);
             part = fmaf(dz[t].z, x[u][t].z, part);
@@ -1157,8 +1100,9 @@ __device__ __forceinline__ void sddmm_pass(gmem_ptr Xg, int it0, int my_ro, cons
     }
 }
 
-template <int G, int NV, bool EXACT4>
-__device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block)
+// col0: first column of the pass, which covers G*4*NV columns of the batch.
+template <int G, int NV>
+__device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, const int col0 = 0)
 {
     constexpr int NG = kWave / G;
     constexpr int UI = NV >= 4 ? 2 : (NV == 2 ? 4 : 8);   // 32 registers of gathered data: two 16-wave work-groups fit a compute unit
@@ -1170,26 +1114,29 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block)
     const int grp = lane / G;
     const int lig = lane % G;
 
+    // the row of dZ: all its loads together, whole waves (lanes beyond the batch re-read columns of the pass and are zeroed)
     float4 dz[NV];
     uint32_t off[NV];
     {
-        const float *zr = a.dZ + static_cast<int64_t>(row) * a.lddz;
-        const float *zm = a.ZM ? a.ZM + static_cast<int64_t>(row) * a.ldzm : nullptr;
+        const gmem_ptr zr = as_gmem(a.dZ + static_cast<int64_t>(row) * a.lddz);
 #pragma unroll
         for (int t = 0; t < NV; ++t) {
-            const int c = (t * G + lig) * 4;
-            dz[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-            off[t] = 0u;
-            if (c < a.batch) {
-                off[t] = static_cast<uint32_t>(c) * 4u;
-                dz[t] = ld4(zr + c);
-                if (zm) dz[t] = keep_where_positive(dz[t], ld4(zm + c));
-                if constexpr (!EXACT4) {
-                    if (c + 1 >= a.batch) dz[t].y = 0.f;
-                    if (c + 2 >= a.batch) dz[t].z = 0.f;
-                    if (c + 3 >= a.batch) dz[t].w = 0.f;
-                }
-            }
+            const int own = col0 + (t * G + lig) * 4;
+            off[t] = static_cast<uint32_t>(four_columns(own < a.batch ? own : col0, a.batch)) * 4u;
+            dz[t] = gload4(zr, off[t]);
+        }
+        if (a.ZM) {
+            const gmem_ptr zm = as_gmem(a.ZM + static_cast<int64_t>(row) * a.ldzm);
+            float4 m[NV];
+#pragma unroll
+            for (int t = 0; t < NV; ++t) m[t] = gload4(zm, off[t]);
+#pragma unroll
+            for (int t = 0; t < NV; ++t) dz[t] = keep_where_positive(dz[t], m[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int own = col0 + (t * G + lig) * 4;
+            dz[t] = own < a.batch ? drop_shared(dz[t], own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
 
@@ -1234,12 +1181,12 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block)
         const int iters = (n + NG - 1) / NG;
         float res = 0.f;
         int it = 0;
-        for (; it + UI <= iters; it += UI) sddmm_pass<G, NV, EXACT4, UI>(Xg, it, my_ro, off, dz, a.batch, res);
+        for (; it + UI <= iters; it += UI) sddmm_pass<G, NV, UI>(Xg, it, my_ro, off, dz, res);
         if constexpr (UI >= 8)
-            if (it + 4 <= iters) { sddmm_pass<G, NV, EXACT4, 4>(Xg, it, my_ro, off, dz, a.batch, res); it += 4; }
+            if (it + 4 <= iters) { sddmm_pass<G, NV, 4>(Xg, it, my_ro, off, dz, res); it += 4; }
         if constexpr (UI >= 4)
-            if (it + 2 <= iters) { sddmm_pass<G, NV, EXACT4, 2>(Xg, it, my_ro, off, dz, a.batch, res); it += 2; }
-        if (it < iters) sddmm_pass<G, NV, EXACT4, 1>(Xg, it, my_ro, off, dz, a.batch, res);
+            if (it + 2 <= iters) { sddmm_pass<G, NV, 2>(Xg, it, my_ro, off, dz, res); it += 2; }
+        if (it < iters) sddmm_pass<G, NV, 1>(Xg, it, my_ro, off, dz, res);
         if (mine) {
             if (a.g) a.g[p] = res;
             if (a.fused) {
@@ -1253,18 +1200,17 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block)
     }
 }
 
-template <int G, int NV, bool EXACT4>
+template <int G, int NV>
 __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 {
-    sddmm_body<G, NV, EXACT4>(a, blockIdx.x);
+    sddmm_body<G, NV>(a, blockIdx.x);
 }
 
 // Column-tiled SDDMM for operands X that no L2 holds: tile t covers columns [t*W, t*W + W), W =
-// G*4*NV; a work-group computes the partial products of its rows over one tile, as sddmm_body on
-// the sub-matrices that start at the tile's first column, and stores them (and the partial row
+// G*4*NV; a work-group computes the partial products of its rows over one tile and stores them (and the partial row
 // sums of dZ) in the tile's slice of the partial buffer.  Work-group ids are decoded XCD-first as
 // in spmm_tiled_kernel, so an operand tile stays in one L2 while every entry gathers from it.
-template <int G, int NV, bool EXACT4>
+template <int G, int NV>
 __global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const int spread)
 {
     const int nrb = a.blocks.n_blocks;
@@ -1278,17 +1224,12 @@ __global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, 
         rb = blockIdx.x % nrb;
     }
     if (tile >= n_tiles) return;
-    const int col0 = tile * (G * 4 * NV);
     SddmmArgs t = a;
-    t.dZ = a.dZ + col0;
-    t.X = a.X + col0;
-    if (a.ZM) t.ZM = a.ZM + col0;
-    t.batch = min(G * 4 * NV, a.batch - col0);
     t.fused = 0;
     t.g = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
     t.db = t.g + a.partial_db_at;
     if (tile != 0) t.loss_cols = nullptr;
-    sddmm_body<G, NV, EXACT4>(t, rb);
+    sddmm_body<G, NV>(t, rb, tile * (G * 4 * NV));
 }
 
 // ---- staged SDDMM --------------------------------------------------------------------------
@@ -1397,8 +1338,9 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = wave_in_block();
     const int lrow = lane >> 4, lig = lane & 15;
-    const int col = tile * kStageCols + lig * 4;
-    const bool col_on = col < a.batch;
+    const int own_col = tile * kStageCols + lig * 4;
+    const bool col_on = own_col < a.batch;
+    const int col = four_columns(own_col, a.batch);
     const char *lds = reinterpret_cast<const char *>(stage) + lig * 16;
     const int n_cb = a.blocks.staged_cblocks;
     const int my_slot = ((lig & (kStageJ - 1)) * kStageWaves + wv) * 4 + lrow;
@@ -1418,6 +1360,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
             if (row >= 0 && col_on) {
                 z[j] = ld4(a.dZ + static_cast<int64_t>(row) * a.lddz + col);
                 if (a.ZM) z[j] = keep_where_positive(z[j], ld4(a.ZM + static_cast<int64_t>(row) * a.ldzm + col));
+                z[j] = drop_shared(z[j], own_col, col);
             }
             const float sum = row16_sum((z[j].x + z[j].y) + (z[j].z + z[j].w));
             // (the four lane rows of a split row hold the same dZ: the first one reports it)
@@ -1509,8 +1452,10 @@ __global__ __launch_bounds__(kBlock) void full_sddmm_kernel(const SddmmArgs a, c
         const int i = idx / (n_chunks * kWave), c4 = idx % (n_chunks * kWave);
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (c4 * 4 < a.batch) {
-            v = ld4(a.dZ + static_cast<int64_t>(i) * a.lddz + c4 * 4);
-            if (a.ZM) v = keep_where_positive(v, ld4(a.ZM + static_cast<int64_t>(i) * a.ldzm + c4 * 4));
+            const int c = four_columns(c4 * 4, a.batch);
+            v = ld4(a.dZ + static_cast<int64_t>(i) * a.lddz + c);
+            if (a.ZM) v = keep_where_positive(v, ld4(a.ZM + static_cast<int64_t>(i) * a.ldzm + c));
+            v = drop_shared(v, c4 * 4, c);
         }
         dz_s[idx] = v;
     }
@@ -1543,8 +1488,9 @@ __global__ __launch_bounds__(kBlock) void full_sddmm_kernel(const SddmmArgs a, c
         if constexpr (WITH_T)
             if (lane < R) w_own = a.values[static_cast<int64_t>(lane) * K + j];
         for (int ch = 0; ch < n_chunks; ++ch) {
-            const int col = (ch * kWave + lane) * 4;
-            const float4 x = col < a.batch ? ld4(xr + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const int own = (ch * kWave + lane) * 4;
+            const int col = four_columns(own, a.batch);
+            const float4 x = own < a.batch ? ld4(xr + col) : make_float4(0.f, 0.f, 0.f, 0.f);
             float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int i = 0; i < kFullMaxRows; ++i) {
@@ -1562,7 +1508,7 @@ __global__ __launch_bounds__(kBlock) void full_sddmm_kernel(const SddmmArgs a, c
             }
             if constexpr (WITH_T) {
                 const float4 o = keep_where_positive(t, x);  // (columns beyond the batch: x = 0, so o = 0)
-                if (col < a.batch) st4(dX + static_cast<int64_t>(j) * lddx + col, o);  // (batch % 4 == 0)
+                if (own < a.batch) st4(dX + static_cast<int64_t>(j) * lddx + col, o);  // (batch % 4 == 0: no columns are shared)
                 below += (o.x + o.y) + (o.z + o.w);
             }
         }
@@ -1661,7 +1607,7 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, int src, int my_ro, float 
     }
     float4 x[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = gload<float4>(Zg, ro[u] + off);
+    for (int u = 0; u < U; ++u) x[u] = gload4(Zg, ro[u] + off);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         acc[0] = fmaf(w[u], x[u].x, acc[0]);
@@ -1694,9 +1640,10 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     const int wv = wave_in_block();
     const int grp = lane / GS;
     const int lig = lane % GS;
-    const int col = col0 + lig * 4;
-    const bool on = col < a.batch;  // (batch is a multiple of 4: a lane's four columns are all in or all out)
-    const uint32_t off = static_cast<uint32_t>(on ? col : col0) * 4u;
+    const int own_col = col0 + lig * 4;
+    const bool on = own_col < a.batch;
+    const int col = four_columns(on ? own_col : col0, a.batch);
+    const uint32_t off = static_cast<uint32_t>(col) * 4u;
     const uint32_t ldzb = static_cast<uint32_t>(a.lddz) * 4u;
     const gmem_ptr Zg = as_gmem(a.dZ);
     const int n_sets = (a.blocks.n_short + NE - 1) / NE;
@@ -1721,8 +1668,11 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
         const int maxlen = __builtin_amdgcn_readfirstlane(len);  // group 0 holds the set's longest row
         // the group's row of X: the second operand of its entries' products, and the mask of its result;
         // lanes beyond the batch hold zeros, so that the columns they re-read add nothing to a product
-        float4 ax = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row >= 0 && on) ax = ld4(a.X + static_cast<int64_t>(row) * a.ldx + col);
+        float4 ax = make_float4(0.f, 0.f, 0.f, 0.f), mask = ax;
+        if (row >= 0 && on) {
+            mask = ld4(a.X + static_cast<int64_t>(row) * a.ldx + col);
+            ax = drop_shared(mask, own_col, col);
+        }
         float acc[4] = {0.f, 0.f, 0.f, 0.f};
         int cur_j;
         float cur_w;
@@ -1752,7 +1702,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
         }
         if (row < 0 || !on) continue;
         float4 y = len > 0 ? make_float4(acc[0], acc[1], acc[2], acc[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
-        if (a.mask) y = keep_where_positive(y, ax);
+        if (a.mask) y = keep_where_positive(y, mask);
         st4(a.dX + static_cast<int64_t>(row) * a.lddx + col, y);
     }
 }
@@ -1794,7 +1744,8 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
         const float *zr = a.dZ + i * a.lddz;
         float s = 0.f;
         for (int c = lane * 4; c < a.batch; c += kWave * 4) {
-            const float4 z = ld4(zr + c);
+            const int first = four_columns(c, a.batch);
+            const float4 z = drop_shared(ld4(zr + first), c, first);
             s += (z.x + z.y) + (z.z + z.w);
         }
         s = group_sum<kWave>(s);
@@ -1812,29 +1763,29 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
 
 // Two independent launches of a training step in one grid: work-groups [0, na) run the first,
 // the rest the second.  Saves a launch (and its drain) on the step's critical path.
-template <int GS_S, int NV_S, int G, int NV_D, bool EXACT4>
+template <int GS_S, int NV_S, int G, int NV_D>
 __global__ __launch_bounds__(kBlock) void spmm_sddmm_pair_kernel(const SpmmArgs a, const SddmmArgs b, const int na)
 {
     if (static_cast<int>(blockIdx.x) < na) {
         if constexpr (GS_S < kWave)
             spmm_body_grouped<GS_S, false>(a, blockIdx.x);
         else
-            spmm_body<4, NV_S, false>(a, blockIdx.x, 0);
+            spmm_body<NV_S, false>(a, blockIdx.x, 0);
     } else {
-        sddmm_body<G, NV_D, EXACT4>(b, blockIdx.x - na);
+        sddmm_body<G, NV_D>(b, blockIdx.x - na);
     }
 }
-template <int G, int NV_D, bool EXACT4>
+template <int G, int NV_D>
 __global__ __launch_bounds__(kBlock) void sddmm_pair_kernel(const SddmmArgs a, const SddmmArgs b, const int na)
 {
     if (static_cast<int>(blockIdx.x) < na)
-        sddmm_body<G, NV_D, EXACT4>(a, blockIdx.x);
+        sddmm_body<G, NV_D>(a, blockIdx.x);
     else
-        sddmm_body<G, NV_D, EXACT4>(b, blockIdx.x - na);
+        sddmm_body<G, NV_D>(b, blockIdx.x - na);
 }
 
-// Any batch size, any leading dimension, any alignment: one column per lane and pass, both
-// operands re-read per stored entry.  The slow path behind sddmm_kernel.
+// Any batch size, operands of any span: one column per lane and pass, both operands re-read per stored
+// entry.  For batches below 4, untiled ones beyond 1024 and operands of 4 GiB or more.
 __global__ __launch_bounds__(kBlock) void sddmm_generic(const SddmmArgs a)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -2130,15 +2081,15 @@ inline int elementwise_blocks(int64_t work_items)
     return static_cast<int>(b);
 }
 
-template <int VEC, int NV>
+template <int NV>
 hipError_t spmm_go(const SpmmArgs &a, hipStream_t s)
 {
-    const int tile = kWave * VEC * NV;
+    const int tile = kWave * 4 * NV;
     dim3 grid(a.blocks.n_blocks, (a.batch + tile - 1) / tile);
     if (a.XM)
-        hipLaunchKernelGGL((spmm_kernel<VEC, NV, true>), grid, dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL((spmm_kernel<NV, true>), grid, dim3(kBlock), 0, s, a);
     else
-        hipLaunchKernelGGL((spmm_kernel<VEC, NV, false>), grid, dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL((spmm_kernel<NV, false>), grid, dim3(kBlock), 0, s, a);
     if (a.blocks.n_huge_rows > 0)
         hipLaunchKernelGGL(spmm_finish_kernel, dim3(a.blocks.n_huge_rows, (a.batch + 255) / 256), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -2224,17 +2175,12 @@ template <int G, int NV>
 hipError_t sddmm_go(const SddmmArgs &a, hipStream_t s)
 {
     dim3 grid(a.blocks.n_blocks);
-    if (a.batch % 4 == 0)
-        hipLaunchKernelGGL((sddmm_kernel<G, NV, true>), grid, dim3(kBlock), 0, s, a);
-    else
-        hipLaunchKernelGGL((sddmm_kernel<G, NV, false>), grid, dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL((sddmm_kernel<G, NV>), grid, dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
 
 // The grouped kernels address the gathered operand with 32-bit byte offsets from its base.
 inline bool spans_below_4gib(int64_t rows, int64_t ld) { return rows * ld * 4 < (1ll << 32); }
-
-bool spmm_vec_ok(const SpmmArgs &a);
 
 // The staged product pays where a work-group finds several stored entries per operand row it
 // copies into LDS, fills its column tiles, and has enough siblings to occupy the chip; where the
@@ -2244,7 +2190,7 @@ bool spmm_vec_ok(const SpmmArgs &a);
 // the chip's 256 LDS serve at about one entry and tile per 3.3 ns each.
 bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t long_segment)
 {
-    if (!blocks.staged_rows || batch < kStageMinBatch || batch % 4 != 0) return false;
+    if (!blocks.staged_rows || batch < kStageMinBatch) return false;
     // (an operand of a few rows is in cache wherever it is gathered from: config 4's 8192 x 10 mirror, 21 against 28 us)
     if (x_rows < kStageRows / 2 && !blocks.staged_preferred) return false;
     const int64_t rows = blocks.staged_row_count, nnz = blocks.staged_nnz;  // what the plan covers
@@ -2298,7 +2244,7 @@ int spmm_split_group(const SpmmArgs &a)
 
 bool spmm_staged_ok(const SpmmArgs &a)
 {
-    if (!spmm_vec_ok(a) || !staged_pays(a.blocks, a.x_rows, a.batch, kStageLongSegment)) return false;
+    if (!staged_pays(a.blocks, a.x_rows, a.batch, kStageLongSegment)) return false;
     return !a.blocks.staged_partial || a.blocks.n_rest_blocks > 0;  // (the rows the plan leaves out need a partition of their own)
 }
 
@@ -2308,20 +2254,20 @@ bool staged_rest_packed(const SpmmArgs &a, int tg)
     return a.blocks.n_short > 0 && tg != 0 && spmm_offsets_ok(a) && packed_grid(a, tg, false).ids <= kMaxGridIds;
 }
 
-bool sddmm_vec_ok(const SddmmArgs &a);
+bool sddmm_offsets_ok(const SddmmArgs &a);
 
 // a full matrix of few rows whose dZ fits in 64 KiB of LDS
 bool sddmm_full_ok(const SddmmArgs &a)
 {
     if (a.rows > kFullMaxRows || a.x_rows < 256 || static_cast<int64_t>(a.nnz) != static_cast<int64_t>(a.rows) * a.x_rows) return false;
-    if (a.batch < 64 || a.batch % 4 != 0 || a.skip_products || a.dense || a.loss_cols || !sddmm_vec_ok(a)) return false;
+    if (a.batch < 64 || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     return static_cast<int64_t>(a.rows) * ((a.batch + 255) / 256) <= 64;
 }
 
 // the staged SDDMM needs room for one slice of partial products per 64-column tile
 bool sddmm_staged_ok(const SddmmArgs &a)
 {
-    if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_vec_ok(a)) return false;
+    if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     if ((a.batch + kStageCols - 1) / kStageCols > a.partial_tiles) return false;
     return staged_pays(a.blocks, a.x_rows, a.batch, kStageLongSegmentSddmm) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
 }
@@ -2339,29 +2285,16 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
     const int spread = n_tiles >= 8;
     const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * a.blocks.n_blocks;
     dim3 grid(static_cast<unsigned>(ids));
-    if (a.batch % 4 == 0)
-        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, true>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
-    else
-        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, false>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
+    hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
     const int64_t work = a.nnz > a.rows ? a.nnz : a.rows;
     hipLaunchKernelGGL(sddmm_finish_kernel, dim3(elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles);
     return hipGetLastError();
 }
 
-bool spmm_vec_ok(const SpmmArgs &a)
+// what the SDDMM kernels but the generic one ask for: four columns, 32-bit offsets into X
+bool sddmm_offsets_ok(const SddmmArgs &a)
 {
-    bool vec = a.ldx % 4 == 0 && a.ldy % 4 == 0 && aligned16(a.X) && aligned16(a.Y);
-    if (a.XM) vec = vec && a.ldxm % 4 == 0 && aligned16(a.XM);
-    if (a.YM) vec = vec && a.ldym % 4 == 0 && aligned16(a.YM);
-    return vec;
-}
-
-bool sddmm_vec_ok(const SddmmArgs &a)
-{
-    bool vec = a.lddz % 4 == 0 && aligned16(a.dZ);
-    if (!a.skip_products) vec = vec && a.ldx % 4 == 0 && aligned16(a.X) && spans_below_4gib(a.x_rows, a.ldx);
-    if (a.ZM) vec = vec && a.ldzm % 4 == 0 && aligned16(a.ZM);
-    return vec;
+    return a.batch >= 4 && (a.skip_products || spans_below_4gib(a.x_rows, a.ldx));
 }
 
 template <int GS_S, int NV_S, int G, int NV_D>
@@ -2369,10 +2302,7 @@ hipError_t pair_go(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
 {
     const int na = a.blocks.n_blocks;
     dim3 grid(na + b.blocks.n_blocks);
-    if (a.batch % 4 == 0)
-        hipLaunchKernelGGL((spmm_sddmm_pair_kernel<GS_S, NV_S, G, NV_D, true>), grid, dim3(kBlock), 0, s, a, b, na);
-    else
-        hipLaunchKernelGGL((spmm_sddmm_pair_kernel<GS_S, NV_S, G, NV_D, false>), grid, dim3(kBlock), 0, s, a, b, na);
+    hipLaunchKernelGGL((spmm_sddmm_pair_kernel<GS_S, NV_S, G, NV_D>), grid, dim3(kBlock), 0, s, a, b, na);
     if (a.blocks.n_huge_rows > 0)
         hipLaunchKernelGGL(spmm_finish_kernel, dim3(a.blocks.n_huge_rows, (a.batch + 255) / 256), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -2383,10 +2313,7 @@ hipError_t sddmm_pair_go(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 {
     const int na = a.blocks.n_blocks;
     dim3 grid(na + b.blocks.n_blocks);
-    if (a.batch % 4 == 0)
-        hipLaunchKernelGGL((sddmm_pair_kernel<G, NV_D, true>), grid, dim3(kBlock), 0, s, a, b, na);
-    else
-        hipLaunchKernelGGL((sddmm_pair_kernel<G, NV_D, false>), grid, dim3(kBlock), 0, s, a, b, na);
+    hipLaunchKernelGGL((sddmm_pair_kernel<G, NV_D>), grid, dim3(kBlock), 0, s, a, b, na);
     return hipGetLastError();
 }
 
@@ -2440,15 +2367,15 @@ int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, float
 bool can_pair(const SpmmArgs &a, const SddmmArgs &b)
 {
     return a.batch == b.batch && a.batch > 4 && a.batch <= 1024 && !a.XM && a.rows > 0 && b.rows > 0 &&
-           a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && spmm_vec_ok(a) && spmm_offsets_ok(a) &&
-           sddmm_vec_ok(b) && spmm_tile_group(a) == 0 && !spmm_staged_ok(a) && sddmm_tile_columns(b) == 0 &&
+           a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && spmm_offsets_ok(a) &&
+           sddmm_offsets_ok(b) && spmm_tile_group(a) == 0 && !spmm_staged_ok(a) && sddmm_tile_columns(b) == 0 &&
            !sddmm_staged_ok(b) && !sddmm_full_ok(b);
 }
 
 bool can_pair(const SddmmArgs &a, const SddmmArgs &b)
 {
     return a.batch == b.batch && a.batch > 0 && a.batch <= 1024 && a.rows > 0 && b.rows > 0 &&
-           a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && sddmm_vec_ok(a) && sddmm_vec_ok(b) &&
+           a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && sddmm_offsets_ok(a) && sddmm_offsets_ok(b) &&
            sddmm_tile_columns(a) == 0 && sddmm_tile_columns(b) == 0 && !sddmm_staged_ok(a) && !sddmm_staged_ok(b) &&
            !sddmm_full_ok(a) && !sddmm_full_ok(b);
 }
@@ -2487,10 +2414,10 @@ static int backward_tile_group(const SpmmArgs &t)
 
 bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g)
 {
-    if (t.batch != g.batch || t.batch % 4 != 0 || t.XM || !t.YM || t.YM != g.X || t.ldym != g.ldx || t.X != g.dZ || t.ldx != g.lddz) return false;
+    if (t.batch != g.batch || t.batch < 4 || t.XM || !t.YM || t.YM != g.X || t.ldym != g.ldx || t.X != g.dZ || t.ldx != g.lddz) return false;
     if (t.rows != g.x_rows || t.x_rows != g.rows || t.nnz != g.nnz || t.nnz <= 0) return false;
     if (g.ZM || g.skip_products || g.dense || g.loss_cols || !g.partial || !g.perm) return false;
-    if (!spmm_vec_ok(t) || !spmm_offsets_ok(t) || !sddmm_vec_ok(g) || spmm_staged_ok(t)) return false;
+    if (!spmm_offsets_ok(t) || !sddmm_offsets_ok(g) || spmm_staged_ok(t)) return false;
     if (t.blocks.n_short != t.rows || t.blocks.n_long_blocks != 0) return false;  // every mirror row packed
     const int tg = backward_tile_group(t);
     if (tg != 16 && tg != 32) return false;  // (32-column tiles are only chosen for rows too long to be packed)
@@ -2506,10 +2433,9 @@ bool full_backward_ok(const SpmmArgs &t, const SddmmArgs &g)
 {
     SddmmArgs plain = g;
     plain.loss_cols = nullptr;  // (this launch can carry the mean of the losses, the plain one is not asked to)
-    if (!sddmm_full_ok(plain) || !g.fused || g.ZM || !g.values || !g.velocity) return false;
+    if (g.batch % 4 != 0 || !sddmm_full_ok(plain) || !g.fused || g.ZM || !g.values || !g.velocity) return false;
     if (t.batch != g.batch || t.XM || t.bias || t.relu || !t.YM || t.YM != g.X || t.ldym != g.ldx || t.X != g.dZ || t.ldx != g.lddz) return false;
-    if (t.rows != g.x_rows || t.x_rows != g.rows || t.nnz != g.nnz || !t.Y) return false;
-    return t.ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(t.Y) & 15u) == 0;
+    return t.rows == g.x_rows && t.x_rows == g.rows && t.nnz == g.nnz && t.Y;
 }
 
 hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream_t s)
@@ -2550,7 +2476,7 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, hipStrea
 // whether launch_spmm serves `a` by streaming (full matrix of few rows), where the softmax epilogue can ride along
 static bool spmm_full_rows_ok(const SpmmArgs &a)
 {
-    return a.batch > 4 && a.full_scratch && !a.XM && a.batch >= 64 && a.rows <= kFullMaxRows && spmm_vec_ok(a) && a.full_scratch_ld % 4 == 0;
+    return a.batch > 4 && a.full_scratch && !a.XM && a.batch >= 64 && a.rows <= kFullMaxRows;
 }
 bool spmm_softmax_epilogue_ok(const SpmmArgs &a)
 {
@@ -2608,60 +2534,55 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         }
         return hipGetLastError();
     }
-    if (spmm_vec_ok(a)) {
-        if (spmm_offsets_ok(a)) {
-            const int tg = spmm_tile_group(a);
-            const int sg = tg == 0 ? spmm_split_group(a) : 0;
-            if (sg != 0) {
-                // Long rows inside column tiles (their gathers are most of the traffic and then hit in the L2s),
-                // short rows outside (a pass over them per tile would cost more than their gathers): two launches.
-                SpmmArgs longs = a, rest = a;
-                longs.blocks.waves = a.blocks.long_waves;
-                longs.blocks.n_blocks = a.blocks.n_long_blocks;
-                longs.blocks.n_short = 0;
-                rest.blocks.waves = a.blocks.rest_waves;
-                rest.blocks.n_blocks = a.blocks.n_rest_blocks;
-                rest.blocks.n_huge_rows = 0;
-                rest.blocks.n_short = 0;
-                rest.blocks.n_long_blocks = 0;   // (nothing left to split off)
-                rest.blocks.staged_rows = nullptr;
-                const hipError_t e = launch_spmm(rest, s);
-                if (e != hipSuccess) return e;
-                switch (sg) {
-                    case 32: return spmm_tiled_go<32>(longs, s);
-                    case 16: return spmm_tiled_go<16>(longs, s);
-                    default: return spmm_tiled_go<8>(longs, s);
-                }
+    if (spmm_offsets_ok(a)) {
+        const int tg = spmm_tile_group(a);
+        const int sg = tg == 0 ? spmm_split_group(a) : 0;
+        if (sg != 0) {
+            // Long rows inside column tiles (their gathers are most of the traffic and then hit in the L2s),
+            // short rows outside (a pass over them per tile would cost more than their gathers): two launches.
+            SpmmArgs longs = a, rest = a;
+            longs.blocks.waves = a.blocks.long_waves;
+            longs.blocks.n_blocks = a.blocks.n_long_blocks;
+            longs.blocks.n_short = 0;
+            rest.blocks.waves = a.blocks.rest_waves;
+            rest.blocks.n_blocks = a.blocks.n_rest_blocks;
+            rest.blocks.n_huge_rows = 0;
+            rest.blocks.n_short = 0;
+            rest.blocks.n_long_blocks = 0;   // (nothing left to split off)
+            rest.blocks.staged_rows = nullptr;
+            const hipError_t e = launch_spmm(rest, s);
+            if (e != hipSuccess) return e;
+            switch (sg) {
+                case 32: return spmm_tiled_go<32>(longs, s);
+                case 16: return spmm_tiled_go<16>(longs, s);
+                default: return spmm_tiled_go<8>(longs, s);
             }
-            if (a.blocks.n_short > 0 && tg != 0 && packed_grid(a, tg, true).ids <= kMaxGridIds) {
-                switch (tg) {
-                    case 32: return spmm_packed_go<32>(a, s);
-                    case 16: return spmm_packed_go<16>(a, s);
-                    default: return spmm_packed_go<8>(a, s);
-                }
-            }
-            switch (tg) {
-                case 32: return spmm_tiled_go<32>(a, s);
-                case 16: return spmm_tiled_go<16>(a, s);
-                case 8: return spmm_tiled_go<8>(a, s);
-                default: break;
-            }
-            if (a.batch <= 64) return spmm_grouped_go<16>(a, s);
-            if (a.batch <= 128) return spmm_grouped_go<32>(a, s);
         }
-        if (a.batch <= 256) return spmm_go<4, 1>(a, s);
-        if (a.batch <= 512) return spmm_go<4, 2>(a, s);
-        return spmm_go<4, 4>(a, s);
+        if (a.blocks.n_short > 0 && tg != 0 && packed_grid(a, tg, true).ids <= kMaxGridIds) {
+            switch (tg) {
+                case 32: return spmm_packed_go<32>(a, s);
+                case 16: return spmm_packed_go<16>(a, s);
+                default: return spmm_packed_go<8>(a, s);
+            }
+        }
+        switch (tg) {
+            case 32: return spmm_tiled_go<32>(a, s);
+            case 16: return spmm_tiled_go<16>(a, s);
+            case 8: return spmm_tiled_go<8>(a, s);
+            default: break;
+        }
+        if (a.batch <= 64) return spmm_grouped_go<16>(a, s);
+        if (a.batch <= 128) return spmm_grouped_go<32>(a, s);
     }
-    if (a.batch <= 64) return spmm_go<1, 1>(a, s);
-    if (a.batch <= 128) return spmm_go<1, 2>(a, s);
-    return spmm_go<1, 4>(a, s);
+    if (a.batch <= 256) return spmm_go<1>(a, s);
+    if (a.batch <= 512) return spmm_go<2>(a, s);
+    return spmm_go<4>(a, s);
 }
 
 // Columns per tile of the column-tiled SDDMM, 0: one pass over the whole batch.
 int sddmm_tile_columns(const SddmmArgs &a)
 {
-    if (!a.partial || a.skip_products || a.dense || !sddmm_vec_ok(a)) return 0;  // (the finish pass does not know an entry's row)
+    if (!a.partial || a.skip_products || a.dense || !sddmm_offsets_ok(a)) return 0;  // (the finish pass does not know an entry's row)
     // the operand rows an entry gathers are named by its column index: the matrix's own partition
     // carries the share of the most referenced ones
     const int w = tile_columns(a.x_rows, a.batch, a.nnz, a.rows, a.blocks.hot_share, false, true);
@@ -2692,7 +2613,7 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
             const int spread = n_tiles >= 8;
             const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * rest.blocks.n_blocks;
-            hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1, true>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles, spread);
+            hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles, spread);
         }
         const int64_t work = a.nnz > a.rows ? a.nnz : a.rows;
         hipLaunchKernelGGL(sddmm_finish_kernel, dim3(elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles);
@@ -2704,7 +2625,7 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
         case 32: return sddmm_tiled_go<8, 1>(a, s);
         default: break;
     }
-    if (sddmm_vec_ok(a) && a.batch <= 1024) {
+    if (sddmm_offsets_ok(a) && a.batch <= 1024) {
         if (a.batch <= 64) return sddmm_go<16, 1>(a, s);
         if (a.batch <= 128) return sddmm_go<16, 2>(a, s);
         if (a.batch <= 256) return sddmm_go<16, 4>(a, s);
