@@ -1454,7 +1454,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         HeadArgs h{};
         h.indptr = last->indptr; h.indices = last->indices; h.values = last->values; h.bias = last->bias;
         h.indptr_t = last->indptr_t; h.indices_t = last->indices_t; h.values_t = last->values_t;
-        h.rows = last->rows; h.cols = last->cols; h.batch = batch;
+        h.rows = last->rows; h.cols = last->cols; h.batch = batch; h.nnz = last->nnz;
         h.X = A(n - 2); h.ldx = L.ld; h.Z = A(n - 1); h.ldz = L.ld; h.labels = labels;
         h.dZ = dZ(n - 1); h.lddz = L.ld; h.dX = dZ(n - 2); h.lddx = L.ld;
         h.loss_cols = mlp->head_scratch;  // their mean is taken by the launch that runs S_{n-1}

@@ -295,7 +295,7 @@ struct HeadArgs {
     const float *values, *bias;           // bias may be null
     const int32_t *indptr_t, *indices_t;  // its mirror: CSR of W^T
     const float *values_t;
-    int32_t rows, cols, batch;
+    int32_t rows, cols, batch, nnz;
     const float *X;                       // (cols, ldx)
     int64_t ldx;
     float *Z;                             // (rows, ldz)

@@ -1960,76 +1960,137 @@ __global__ __launch_bounds__(kSoftmaxBlock) void softmax_ce_kernel(const float *
     }
 }
 
-// Output-layer head (see HeadArgs).  Forward: wave w takes rows w, w+16, ..., lanes run across
-// the row's stored entries, DPP sum.  Softmax-CE: one wave per column, one class per lane.
-// Transposed product: one thread per row of W^T, dZ read from LDS.  Each column's loss goes to
-// loss_cols; their mean is taken by a later launch of the step (SddmmArgs::loss_cols).
+// Output-layer head (see HeadArgs).  A work-group first brings what its three phases gather from into LDS, in one
+// round of loads: its four columns of the layer's input (IN_LDS), every entry of the mirror (MIRROR_LDS), and, in
+// registers, the first chunks of every wave's row.  Forward: wave w takes rows w, w+16, ..., lanes run across the row's stored
+// entries, DPP sum.  Softmax-CE: one wave per column, one class per lane.  Transposed product: one thread per row of
+// W^T.  Each column's loss goes to loss_cols; their mean is taken by a later launch of the step (SddmmArgs::loss_cols).
+// What bounds it is the chain of dependent memory round trips, a few microseconds for a few thousand entries: with
+// gathers and mirror reads straight from memory, entry after entry, a full 10 x 777 layer took 15.1 us, now 8.2
+// (a layer with an entry or less per column has nothing to share: read directly, 4.8 us at 10 x 512 and 1 %).
 constexpr int kHeadCols = 4;
+constexpr int kHeadChunks = 8;              // chunks of 64 entries of a row whose loads travel together
+constexpr int kHeadMaxLds = 60 << 10;
 __device__ __forceinline__ float wave_max(float x)
 {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m, kWave));
     return x;
 }
+template <bool IN_LDS, bool MIRROR_LDS>
 __global__ __launch_bounds__(kBlock) void head_kernel(const HeadArgs a)
 {
-    __shared__ float z[kHeadMaxRows][kHeadCols];
+    extern __shared__ float4 head_lds[];    // [cols] input columns (IN_LDS), then the mirror's values and rows
+    __shared__ float4 z[kHeadMaxRows];
+    float4 *xs = head_lds;
+    float *wt = reinterpret_cast<float *>(head_lds + (IN_LDS ? a.cols : 0));
+    unsigned char *it = reinterpret_cast<unsigned char *>(wt + a.nnz);
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = wave_in_block();
-    const int c0 = blockIdx.x * kHeadCols;
-    const int nc = min(kHeadCols, a.batch - c0);
-    const bool vec = nc == kHeadCols && a.ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15u) == 0;
+    // (the last work-group's columns move back to the batch's last four; those it shares with its neighbour get the same bits)
+    const int nc = min(kHeadCols, a.batch);
+    const int c0 = a.batch >= kHeadCols ? four_columns(blockIdx.x * kHeadCols, a.batch) : 0;
+    auto four_of = [&](int j) {
+        const float *xr = a.X + static_cast<int64_t>(j) * a.ldx + c0;
+        if (nc == kHeadCols) return ld4(xr);
+        return make_float4(xr[0], nc > 1 ? xr[1] : 0.f, nc > 2 ? xr[2] : 0.f, 0.f);
+    };
 
-    // Operands of the last phase are requested first: their latency passes behind the forward product.
+    // One round of loads: first chunks of the wave's row, mirror row bounds, label, mirror, input columns.  No load
+    // hides behind a lane's condition (lanes without an entry repeat the last one): a branch would make the compiler
+    // wait for what is in flight.
     const int j0 = threadIdx.x;
-    int q0 = 0, q1 = 0;
-    float mask[kHeadCols] = {0.f, 0.f, 0.f, 0.f};
-    if (j0 < a.cols) {
-        q0 = a.indptr_t[j0];
-        q1 = a.indptr_t[j0 + 1];
-        const float *mr = a.X + static_cast<int64_t>(j0) * a.ldx + c0;
-        if (vec) {
-            const float4 m = ld4(mr);
-            mask[0] = m.x; mask[1] = m.y; mask[2] = m.z; mask[3] = m.w;
-        } else {
-#pragma unroll
-            for (int c = 0; c < kHeadCols; ++c)
-                if (c < nc) mask[c] = mr[c];
-        }
-    }
+    const int j_first = min(j0, a.cols - 1);
+    int q0 = a.indptr_t[j_first], q1 = a.indptr_t[j_first + 1];
+    float4 mask = four_of(j_first);
     const int label = wv < nc ? a.labels[c0 + wv] : 0;
+    int row_b = 0, row_e = 0, idx[kHeadChunks];
+    float w[kHeadChunks];
+    auto load_chunks = [&](int p0) {        // p0 < row_e
+        auto chunk = [&](int k) {
+            const int p = min(p0 + k * kWave + lane, row_e - 1);
+            idx[k] = a.indices[p];
+            w[k] = a.values[p];
+        };
+        chunk(0);
+        if (p0 + kWave < row_e)             // uniform
+#pragma unroll
+            for (int k = 1; k < kHeadChunks; ++k) chunk(k);
+    };
+    if (wv < a.rows && MIRROR_LDS) {
+        row_b = a.indptr[wv];
+        row_e = a.indptr[wv + 1];
+        if (row_b < row_e) load_chunks(row_b);
+    }
+    constexpr int kM = 8;                   // nnz <= 8 * 1024 (head_ok)
+    float mw[kM];
+    int mi[kM];
+    auto mirror_load = [&](int k) {
+        const int q = min(k * kBlock + static_cast<int>(threadIdx.x), a.nnz - 1);
+        mw[k] = a.values_t[q];
+        mi[k] = a.indices_t[q];
+    };
+    auto mirror_keep = [&](int k) {
+        const int q = k * kBlock + threadIdx.x;
+        if (q < a.nnz) {
+            wt[q] = mw[k];
+            it[q] = static_cast<unsigned char>(mi[k]);
+        }
+    };
+    if constexpr (MIRROR_LDS) {
+        if (a.nnz > 0) mirror_load(0);
+        if (a.nnz > kBlock)                 // uniform
+#pragma unroll
+            for (int k = 1; k < kM; ++k) mirror_load(k);
+    }
+    if constexpr (IN_LDS) {
+        if (j0 < a.cols) xs[j0] = mask;
+        for (int j = j0 + kBlock; j < a.cols; j += kBlock) xs[j] = four_of(j);
+    }
+    if constexpr (MIRROR_LDS) {
+        if (a.nnz > 0) mirror_keep(0);
+        if (a.nnz > kBlock)
+#pragma unroll
+            for (int k = 1; k < kM; ++k) mirror_keep(k);
+    }
+    if constexpr (IN_LDS || MIRROR_LDS) __syncthreads();
 
     for (int i = wv; i < a.rows; i += kWavesPerBlock) {
+        if (i != wv || !MIRROR_LDS) {
+            row_b = a.indptr[i];
+            row_e = a.indptr[i + 1];
+            if (row_b < row_e && MIRROR_LDS) load_chunks(row_b);
+        }
         float acc[kHeadCols] = {0.f, 0.f, 0.f, 0.f};
-        for (int p = a.indptr[i] + lane; p < a.indptr[i + 1]; p += kWave) {
-            const float w = a.values[p];
-            const float *xr = a.X + static_cast<int64_t>(a.indices[p]) * a.ldx + c0;
-            if (vec) {
-                const float4 x = ld4(xr);
-                acc[0] = fmaf(w, x.x, acc[0]);
-                acc[1] = fmaf(w, x.y, acc[1]);
-                acc[2] = fmaf(w, x.z, acc[2]);
-                acc[3] = fmaf(w, x.w, acc[3]);
-            } else {
+        if constexpr (!MIRROR_LDS)
+            for (int p = row_b + lane; p < row_e; p += kWave) fma_into(acc, a.values[p], four_of(a.indices[p]));
+        for (int p0 = MIRROR_LDS ? row_b : row_e; p0 < row_e; p0 += kHeadChunks * kWave) {
+            float4 x[kHeadChunks];
 #pragma unroll
-                for (int c = 0; c < kHeadCols; ++c)
-                    if (c < nc) acc[c] = fmaf(w, xr[c], acc[c]);
-            }
+            for (int k = 0; k < kHeadChunks; ++k)
+                if (p0 + k * kWave < row_e) x[k] = IN_LDS ? xs[idx[k]] : four_of(idx[k]);  // uniform
+            float wk[kHeadChunks];
+#pragma unroll
+            for (int k = 0; k < kHeadChunks; ++k) wk[k] = w[k];
+            if (p0 + kHeadChunks * kWave < row_e) load_chunks(p0 + kHeadChunks * kWave);  // travel while these are added
+#pragma unroll
+            for (int k = 0; k < kHeadChunks; ++k)
+                if (p0 + k * kWave + lane < row_e) fma_into(acc, wk[k], x[k]);
         }
 #pragma unroll
         for (int c = 0; c < kHeadCols; ++c) acc[c] = group_sum<kWave>(acc[c]);
         if (lane == 0) {
             const float b = a.bias ? a.bias[i] : 0.f;
-#pragma unroll
-            for (int c = 0; c < kHeadCols; ++c) z[i][c] = acc[c] + b;
+            z[i] = make_float4(acc[0] + b, acc[1] + b, acc[2] + b, acc[3] + b);
         }
     }
     __syncthreads();
 
     // softmax cross-entropy of column c0+wv by wave wv: one class per lane (rows <= 32)
     if (wv < nc) {
+        float *zc = reinterpret_cast<float *>(z) + wv;
         const bool live = lane < a.rows;
-        const float zi = live ? z[lane][wv] : -INFINITY;
+        const float zi = live ? zc[lane * kHeadCols] : -INFINITY;
         const float m = wave_max(zi);
         const float lse = m + logf(group_sum<kWave>(live ? expf(zi - m) : 0.f));
         const float zt = group_sum<kWave>(lane == label ? zi : 0.f);  // one non-zero term: exact
@@ -2037,7 +2098,7 @@ __global__ __launch_bounds__(kBlock) void head_kernel(const HeadArgs a)
         if (live) {
             a.Z[static_cast<int64_t>(lane) * a.ldz + c0 + wv] = zi;
             a.dZ[static_cast<int64_t>(lane) * a.lddz + c0 + wv] = d;
-            z[lane][wv] = d;
+            zc[lane * kHeadCols] = d;
         }
         if (lane == 0) a.loss_cols[c0 + wv] = lse - zt;
     }
@@ -2047,26 +2108,23 @@ __global__ __launch_bounds__(kBlock) void head_kernel(const HeadArgs a)
         if (j != j0) {
             q0 = a.indptr_t[j];
             q1 = a.indptr_t[j + 1];
-            const float *mr = a.X + static_cast<int64_t>(j) * a.ldx + c0;
-#pragma unroll
-            for (int c = 0; c < kHeadCols; ++c)
-                if (c < nc) mask[c] = mr[c];
+            mask = IN_LDS ? xs[j] : four_of(j);
         }
         float acc[kHeadCols] = {0.f, 0.f, 0.f, 0.f};
         for (int q = q0; q < q1; ++q) {
-            const float w = a.values_t[q];
-            const int i = a.indices_t[q];
-#pragma unroll
-            for (int c = 0; c < kHeadCols; ++c) acc[c] = fmaf(w, z[i][c], acc[c]);
+            if constexpr (MIRROR_LDS)
+                fma_into(acc, wt[q], z[it[q]]);
+            else
+                fma_into(acc, a.values_t[q], z[a.indices_t[q]]);
         }
+        const float4 o = keep_where_positive(make_float4(acc[0], acc[1], acc[2], acc[3]), mask);
         float *dr = a.dX + static_cast<int64_t>(j) * a.lddx + c0;
-        if (vec && a.lddx % 4 == 0 && (reinterpret_cast<uintptr_t>(a.dX) & 15u) == 0) {
-            st4(dr, make_float4(keep_where_positive(acc[0], mask[0]), keep_where_positive(acc[1], mask[1]),
-                                keep_where_positive(acc[2], mask[2]), keep_where_positive(acc[3], mask[3])));
+        if (nc == kHeadCols) {
+            st4(dr, o);
         } else {
-#pragma unroll
-            for (int c = 0; c < kHeadCols; ++c)
-                if (c < nc) dr[c] = keep_where_positive(acc[c], mask[c]);
+            dr[0] = o.x;
+            if (nc > 1) dr[1] = o.y;
+            if (nc > 2) dr[2] = o.z;
         }
     }
 }
@@ -2675,7 +2733,16 @@ bool head_ok(int32_t rows, int32_t cols, int32_t nnz)
 
 hipError_t launch_head(const HeadArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(head_kernel, dim3((a.batch + kHeadCols - 1) / kHeadCols), dim3(kBlock), 0, s, a);
+    const dim3 grid((a.batch + kHeadCols - 1) / kHeadCols);
+    const size_t mirror = static_cast<size_t>(a.nnz) * 5, input = static_cast<size_t>(a.cols) * sizeof(float4);
+    // Input columns and mirror come into LDS where the columns are gathered from more often than they are loaded (and
+    // fit): with an entry or less per column there is nothing to share and the detour costs 0.3 us.
+    if (a.nnz <= a.cols)
+        hipLaunchKernelGGL((head_kernel<false, false>), grid, dim3(kBlock), 0, s, a);
+    else if (mirror + input <= kHeadMaxLds)
+        hipLaunchKernelGGL((head_kernel<true, true>), grid, dim3(kBlock), mirror + input, s, a);
+    else
+        hipLaunchKernelGGL((head_kernel<false, true>), grid, dim3(kBlock), mirror, s, a);
     return hipGetLastError();
 }
 
