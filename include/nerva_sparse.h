@@ -152,10 +152,9 @@ int nerva_plan_staged_host(int32_t rows, int32_t cols, const int32_t *indptr_hos
  * indices ascending per column, values_t[nnz]) and the maps between CSR and mirror
  * positions.  The paper leaves A = S^T B to the vendor library (Section 4); the mirror
  * exists because the topology is static (Section 6).  The call checks the pattern on the
- * device (NERVA_ERR_CSR if not canonical; one status word comes back), builds the mirror there
- * (a stable counting sort by column: the same bits on every run), plans the row partitions on
- * the host from a copy of the row pointers (4 * (rows + cols) bytes), allocates device memory
- * and synchronises `stream`.  activation: NERVA_ACT_RELU for hidden layers, NERVA_ACT_NONE
+ * device (NERVA_ERR_CSR if not canonical), builds the mirror (the stable sort by column: the same
+ * bits on every run) and plans the row partitions there, allocates device memory (and a pinned
+ * struct of 300 bytes) and synchronises `stream` once.  activation: NERVA_ACT_RELU for hidden layers, NERVA_ACT_NONE
  * for the output layer (Section 5.1). `bias` may be NULL (no bias).  max_batch bounds the
  * batch of later calls on this layer (a later call with a larger batch returns
  * NERVA_ERR_SHAPE) and is the batch the static tables are laid out for: the scratch rows of
@@ -165,9 +164,9 @@ int nerva_plan_staged_host(int32_t rows, int32_t cols, const int32_t *indptr_hos
  * most 4 GiB (beyond that the SDDMM stays untiled).  Device memory owned by the layer besides
  * that buffer: 16 bytes per stored entry (mirror and position maps) and the partition tables (a
  * 16-byte record per wave of each partition; with a staged plan 4 bytes per row and block of 512
- * columns, for the matrix and for its mirror) -- twice that once the layer has been rebound (see
- * sparse_linear_rebind) -- and the counters of the mirror build (4 bytes per column and row tile,
- * at most 128 MiB).  */
+ * columns, for the matrix and for its mirror; room for any pattern of the same size) -- twice that
+ * once the layer has been rebound (see sparse_linear_rebind) -- and the scratch of the set-up
+ * (12 bytes per stored entry, 24 per row and column).  */
 int sparse_linear_create(nerva_layer **out, int32_t rows, int32_t cols, int32_t nnz,
                          const int32_t *indptr, const int32_t *indices,
                          float *values, float *bias, int32_t activation, int32_t max_batch,
@@ -179,7 +178,7 @@ void sparse_linear_destroy(nerva_layer *layer);
  * same rows x cols matrix -- entries pruned, others grown, nnz free to change -- as a canonical
  * CSR in device arrays indptr[rows+1], indices[nnz], values[nnz] (caller-owned; they replace the
  * arrays given at creation, which the layer no longer touches; bias, activation and max_batch
- * stay).  The call waits for the stream, checks the pattern as sparse_linear_create does, builds
+ * stay).  The call waits for the stream once, checks the pattern as sparse_linear_create does, builds
  * the mirror, the position maps and the partitions in a second set of buffers that the layer keeps
  * for this purpose, then switches over: repeated updates of about the same size allocate nothing.
  * On any error (bad CSR: NERVA_ERR_CSR, allocation: NERVA_ERR_HIP) the layer keeps its old pattern
@@ -187,10 +186,9 @@ void sparse_linear_destroy(nerva_layer *layer);
  * that belongs to an MLP, hand the MLP a velocity array of the new length, mapped to the new
  * entries as the method prescribes (zero for grown ones), with mlp_rebind_velocity, and ask
  * mlp_workspace_bytes / mlp_workspace_layout again: the workspace holds one float per stored
- * entry of every layer, so its size and offsets move with nnz.  Everything proportional
- * to nnz runs on the device; the host plans the partitions from the row lengths (measured on an
- * MI355X: 0.3 ms for a 1024 x 3072 layer with 315 k entries, 1.6 ms for a 16384 x 16384 matrix with
- * 2.7 M) -- cheap enough for a topology update every few hundred steps, not meant for every step. */
+ * entry of every layer, so its size and offsets move with nnz.  Everything runs on
+ * the device (measured on an MI355X: 0.06 ms for a 1024 x 3072 layer with 315 k entries, 0.3 ms for a
+ * 16384 x 16384 matrix with 2.7 M) -- cheap enough for a topology update every few dozen steps. */
 int sparse_linear_rebind(nerva_layer *layer, int32_t nnz, const int32_t *indptr,
                          const int32_t *indices, float *values, void *stream);
 

@@ -89,8 +89,8 @@ struct PatternBuffers {
     int32_t *indptr_t = nullptr;    // [cols + 1]
     int32_t *mirror_mem = nullptr;  // indices_t | perm | pos_t | values_t, round_up(nnz, 64) elements each
     size_t mirror_ints = 0;
-    int32_t *plan_mem = nullptr, *plan_t_mem = nullptr;
-    size_t plan_ints = 0, plan_t_ints = 0;
+    int32_t *plan_mem = nullptr;    // tables of both orientations
+    size_t plan_ints = 0;
 };
 
 struct nerva_layer {
@@ -107,12 +107,12 @@ struct nerva_layer {
     float *values_t = nullptr;     // [nnz]
     int32_t *perm = nullptr;       // [nnz] mirror position -> CSR position
     int32_t *pos_t = nullptr;      // [nnz] CSR position -> mirror position
-    // static work partitions of W (by rows) and of the mirror (by W's columns): views into cur.plan_mem / cur.plan_t_mem
+    // static work partitions of W (by rows) and of the mirror (by W's columns): views into cur.plan_mem
     RowBlocks plan{}, plan_t{};
-    // owned scratch of the set-up kernels: counters of the mirror build, then 4 status ints
+    // owned scratch of the set-up kernels, and what they report (pinned host memory)
     int32_t *build_work = nullptr;
     size_t build_work_ints = 0;
-    int32_t *status = nullptr;     // [4] result of the device-side CSR check
+    BindResult *bind_result = nullptr;
     // owned: partial rows of huge-row work-groups, shared by the forward and the transposed product
     float *scratch = nullptr;
     size_t scratch_floats = 0;
@@ -273,7 +273,7 @@ RowPlan plan_rows(int32_t rows, const int32_t *indptr, const RowsByLength &by_le
             for (int32_t q = 0; q < parts; ++q) {
                 const int64_t b = indptr[i] + q * share;
                 const int64_t e = b + share < indptr[i + 1] ? b + share : indptr[i + 1];
-                P.blocks.insert(P.blocks.end(), {kHugeFlag | q, i, static_cast<int32_t>(b), static_cast<int32_t>(e)});
+                P.blocks.insert(P.blocks.end(), {NERVA_HUGE_FLAG | q, i, static_cast<int32_t>(b), static_cast<int32_t>(e)});
             }
             P.huge_rows.insert(P.huge_rows.end(), {i, first, parts, 0});
             continue;
@@ -324,7 +324,7 @@ RowPlan plan_rows(int32_t rows, const int32_t *indptr, const RowsByLength &by_le
     int32_t *out = P.waves.data();
     for (int32_t b = 0; b < P.n_blocks(); ++b) {
         const int32_t info = P.blocks[4 * b], y = P.blocks[4 * b + 1];
-        const bool huge = (info & kHugeFlag) != 0;
+        const bool huge = (info & NERVA_HUGE_FLAG) != 0;
         const int lg = huge ? max_lg : (info & 0xff);
         for (int w = 0; w < kWavesPerBlock; ++w) {
             const int part = w & ((1 << lg) - 1);
@@ -333,7 +333,7 @@ RowPlan plan_rows(int32_t rows, const int32_t *indptr, const RowsByLength &by_le
             bool lead = false;
             if (huge) {
                 row = y; p0 = P.blocks[4 * b + 2]; p1 = P.blocks[4 * b + 3];
-                lead = w == 0 && (info & ~kHugeFlag) == 0;
+                lead = w == 0 && (info & ~NERVA_HUGE_FLAG) == 0;
             } else if ((w >> lg) < (info >> 8)) {
                 row = P.row_order[y + (w >> lg)];
                 p0 = indptr[row]; p1 = indptr[row + 1];
@@ -375,21 +375,6 @@ std::vector<int32_t> short_row_table(int32_t rows, const int32_t *indptr, const 
     return t;
 }
 
-// Share of the stored entries that gather one of the kHotRows most referenced operand rows;
-// `other` is the transposed orientation (its row lengths are the reference counts).
-float hot_row_share(int32_t other_rows, const int32_t *other_indptr, const RowsByLength &other_by_len)
-{
-    const int64_t nnz = other_indptr[other_rows];
-    if (nnz == 0) return 0.f;
-    if (other_rows <= kHotRows) return 1.f;
-    int64_t top = 0;
-    for (int32_t k = 0; k < kHotRows; ++k) {
-        const int32_t r = other_by_len.order[k];
-        top += other_indptr[r + 1] - other_indptr[r];
-    }
-    return static_cast<float>(static_cast<double>(top) / static_cast<double>(nnz));
-}
-
 // Row ranges and slot order of the staged product (RowBlocks::staged_*) for a matrix whose products
 // run at up to max_batch columns; empty when that product would never be chosen.  The segment
 // bounds (`ends`) depend on the column indices: the host API fills them here, a layer on the device.
@@ -417,22 +402,9 @@ StagedPlan plan_staged(int32_t all_rows, int32_t cols, const int32_t *indptr, co
             nnz += indptr[r + 1] - indptr[r];
         }
     const int32_t rows = static_cast<int32_t>(covered.size());  // from here on: rows of the plan, covered[k] their ids
-    const bool preferred = g_partition_mode.load() == NERVA_PARTITION_PREFER_STAGED;
-    if (g_partition_mode.load() == NERVA_PARTITION_ROW_SPLIT || max_batch < kStageMinBatch || nnz == 0) return H;
-    const int32_t n_tiles = (max_batch + kStageCols - 1) / kStageCols;
-    int32_t want = kStageTargetGroups / n_tiles;
-    if (want > rows / 64) want = rows / 64;
-    // (ranges cut by cost are not equally long: leave an eighth of the slots as slack)
-    const int32_t at_least = (rows + kStageRangeRows * 7 / 8 - 1) / (kStageRangeRows * 7 / 8);
-    if (want < at_least) want = at_least;
-    // one work-group fits a compute unit at a time: fill the last round of the grid as well
-    if (static_cast<int64_t>(want) * n_tiles > kStageTargetGroups) {
-        const int64_t rounds = (static_cast<int64_t>(want) * n_tiles + kStageTargetGroups - 1) / kStageTargetGroups;
-        want = static_cast<int32_t>(rounds * kStageTargetGroups / n_tiles);
-    }
-    if (!preferred && static_cast<double>(nnz) < static_cast<double>(kStageMinReuse) * want * cols) return H;
+    const int32_t want = staged_ranges_wanted(rows, nnz, cols, max_batch, g_partition_mode.load(), staged_range_bound(all_rows, cols, max_batch));
+    if (want == 0) return H;
     const int32_t cblocks = (cols + kStageRows - 1) / kStageRows;
-    if ((static_cast<int64_t>(want) + at_least) * (cblocks + 1) * kStageRangeRows > (1ll << 28)) return H;  // tables beyond 1 GiB
     // ranges of about equal cost: a stored entry costs one gather, a segment about two more
     auto cost = [&](int32_t r) {
         const int64_t len = indptr[r + 1] - indptr[r];
@@ -445,24 +417,23 @@ StagedPlan plan_staged(int32_t all_rows, int32_t cols, const int32_t *indptr, co
     // quarter of every segment ("quad": four slots, group-aligned).
     const int64_t quad_len = std::max<int64_t>(256, total / want / 32);
     auto slots_of = [&](int32_t r) { return indptr[r + 1] - indptr[r] >= quad_len ? 4 : 1; };
+    // a range begins where the row's share of the total cost does, and after every kStageRangeFill slots of a share
     std::vector<int32_t> range_of(all_rows, -1);
     int32_t ranges = 0;
     {
-        int32_t range = 0, in_range = 0;
+        int32_t last_cut = -1, last_part = 0, slots = 0;
         int64_t done = 0;
         for (int32_t k = 0; k < rows; ++k) {
-            const int32_t r = covered[k];
-            const bool next = range + 1 < want && done * want >= total * (range + 1);
-            if ((next || in_range + slots_of(r) > kStageRangeRows) && in_range > 0) {
-                ++ranges;
-                in_range = 0;
-            }
-            if (next) ++range;
+            const int32_t r = covered[k], cut = staged_cut(done, want, total);
+            if (cut != last_cut) slots = 0;
+            const int32_t part = slots / kStageRangeFill;
+            if (cut != last_cut || part != last_part) ++ranges;
+            last_cut = cut;
+            last_part = part;
             done += cost(r);
-            in_range += slots_of(r);
-            range_of[r] = ranges;
+            slots += slots_of(r);
+            range_of[r] = ranges - 1;
         }
-        ++ranges;
     }
     H.ranges = ranges;
     H.cblocks = cblocks;
@@ -506,92 +477,69 @@ void fill_staged_ends_host(StagedPlan &H, const int32_t *indptr, const int32_t *
     }
 }
 
-// All partitions of one orientation of a pattern, planned on the host from its row pointers, laid
-// out as they go to the device: `staging` is copied to the start of the plan's device memory, the
-// segment bounds of the staged plan (ends_ints ints, computed on the device) follow it.
-struct HostPlan {
-    std::vector<int32_t> staging;
-    size_t blocks_at = 0, huge_at = 0, waves_at = 0, staged_at = 0, long_at = 0, rest_at = 0, short_at = 0, order_at = 0, groups_at = 0;
-    size_t ends_ints = 0;
-    RowBlocks view{};   // counts and flags filled in; pointers are set once the device address is known
-    size_t total_ints() const { return staging.size() + ends_ints; }
+// Sizes of the tables of one orientation, from bounds that hold for every pattern with these row and entry counts:
+// the tables are laid out before the planner, which runs on the device, has counted anything.
+struct PlanRoom {
+    int64_t blocks, long_blocks, rest_blocks, huge_rows, short_rows;
+    int32_t ranges, cblocks;
+    PlanRoom(int32_t rows, int32_t other, int64_t nnz, int32_t max_batch)
+    {
+        const int64_t target = std::min<int64_t>(std::max<int64_t>(nnz / 4096, 8), 64);
+        const int64_t cap = std::min<int64_t>(std::max<int64_t>(nnz / 16384, 8), 64) * kWavesPerBlock;
+        // a row's waves number 1 or fewer than 2 * entries / target; a class ends in a work-group that may not be full
+        auto room = [&](int64_t n_rows, int64_t n) { return n_rows / kWavesPerBlock + n / (8 * target) + 8; };
+        huge_rows = nnz / (4 * cap) + 1;
+        const int64_t huge_blocks = nnz / (2 * cap) + huge_rows;
+        blocks = room(rows, nnz) + huge_blocks;
+        const bool packed = rows >= kPackMinRows;
+        long_blocks = packed ? room(std::min<int64_t>(rows, nnz / kPackMaxLen), nnz) + huge_blocks : 0;
+        rest_blocks = packed ? room(rows, std::min<int64_t>(nnz, static_cast<int64_t>(rows) * kPackMaxLen)) : 0;
+        short_rows = packed ? round_up(rows, 64) : 0;
+        ranges = staged_range_bound(rows, other, max_batch);
+        cblocks = (other + kStageRows - 1) / kStageRows;
+    }
+    size_t ints() const
+    {
+        return static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks + rest_blocks) + huge_rows + short_rows)) +
+               static_cast<size_t>(ranges) * (kStageRangeRows * (cblocks + 2) + 4);
+    }
+    // the tables at `mem` (16-byte records first)
+    PlanTables at(int32_t *mem) const
+    {
+        PlanTables t;
+        int4 *r = reinterpret_cast<int4 *>(mem);
+        t.waves = r; r += kWavesPerBlock * blocks;
+        t.long_waves = r; r += kWavesPerBlock * long_blocks;
+        t.rest_waves = r; r += kWavesPerBlock * rest_blocks;
+        t.huge_rows = r; r += huge_rows;
+        t.short_rows = r; r += short_rows;
+        int32_t *i = reinterpret_cast<int32_t *>(r);
+        t.staged_rows = i; i += static_cast<size_t>(ranges) * kStageRangeRows;
+        t.staged_ends = i; i += static_cast<size_t>(ranges) * kStageRangeRows * (cblocks + 1);
+        t.staged_groups = i;
+        return t;
+    }
 };
 
-HostPlan make_plan(int32_t rows, const int32_t *indptr_host, const RowsByLength &by_len, int32_t max_batch, int32_t other_rows,
-                   float hot_share)
+// RowBlocks of one orientation from what the planner reports of it; hot_nnz: entries of the most referenced operand rows
+RowBlocks plan_view(const PlanTables &t, const PlanCounts &c, int32_t other, int32_t nnz, int32_t other_hot_nnz, int32_t mode)
 {
-    HostPlan hp;
-    const RowPlan P = plan_rows(rows, indptr_host, by_len);
-    int32_t n_short = 0;
-    const std::vector<int32_t> short_rows = short_row_table(rows, indptr_host, by_len, &n_short);
-    const int32_t longest_row = by_len.longest;
-    // The staged product serves all rows, or, where the rows differ widely in length and the short
-    // ones have the packed path to go to, the rows beyond that path's length limit only.
-    StagedPlan H;
-    bool staged_partial = false;
-    if (n_short > 0 && n_short < rows && g_partition_mode.load() == NERVA_PARTITION_BALANCED &&
-        static_cast<int64_t>(longest_row) * rows > 4 * static_cast<int64_t>(indptr_host[rows])) {
-        H = plan_staged(rows, other_rows, indptr_host, by_len, max_batch, kPackMaxLen + 1);
-        staged_partial = H.ranges > 0;
-    }
-    if (!staged_partial) H = plan_staged(rows, other_rows, indptr_host, by_len, max_batch);
-    RowPlan Q, Z;
-    if (n_short > 0) Q = plan_rows(rows, indptr_host, by_len, kPackMaxLen);
-    // the short rows' partition: for the SDDMM beside a partial staged plan, and for the launches that serve the
-    // long rows inside column tiles and the short ones outside (operands beyond the L2s)
-    if (n_short > 0 && n_short < rows) Z = plan_rows(rows, indptr_host, by_len, -1, kPackMaxLen);
-    int64_t long_nnz = 0;
-    for (int32_t r = 0; r < rows; ++r)
-        if (indptr_host[r + 1] - indptr_host[r] > kPackMaxLen) long_nnz += indptr_host[r + 1] - indptr_host[r];
-    // 16-byte records first so that they stay 16-byte aligned
-    std::vector<int32_t> &st = hp.staging;
-    st.reserve(P.blocks.size() + P.huge_rows.size() + P.waves.size() + H.rows.size() + Q.waves.size() + Z.waves.size() +
-               short_rows.size() + P.row_order.size() + H.groups.size() + 1);
-    hp.blocks_at = st.size(); st.insert(st.end(), P.blocks.begin(), P.blocks.end());
-    hp.huge_at = st.size(); st.insert(st.end(), P.huge_rows.begin(), P.huge_rows.end());
-    hp.waves_at = st.size(); st.insert(st.end(), P.waves.begin(), P.waves.end());
-    hp.staged_at = st.size(); st.insert(st.end(), H.rows.begin(), H.rows.end());  // (multiples of kStageRangeRows: what follows stays 16-byte aligned)
-    hp.long_at = st.size(); st.insert(st.end(), Q.waves.begin(), Q.waves.end());
-    hp.rest_at = st.size(); st.insert(st.end(), Z.waves.begin(), Z.waves.end());
-    hp.short_at = st.size(); st.insert(st.end(), short_rows.begin(), short_rows.end());
-    hp.order_at = st.size(); st.insert(st.end(), P.row_order.begin(), P.row_order.end());
-    hp.groups_at = st.size(); st.insert(st.end(), H.groups.begin(), H.groups.end());
-    if (st.empty()) st.push_back(0);
-    hp.ends_ints = H.ends_ints();
-    RowBlocks &v = hp.view;
-    v.n_short = n_short;
-    v.hot_share = hot_share;
-    v.n_long_blocks = Q.n_blocks();
-    v.n_blocks = P.n_blocks();
-    v.n_huge_rows = P.n_huge_rows();
-    v.n_huge_blocks = P.n_huge_blocks;
-    v.staged_ranges = H.ranges;
-    v.staged_cblocks = H.cblocks;
-    v.staged_preferred = g_partition_mode.load() == NERVA_PARTITION_PREFER_STAGED;
-    v.staged_longest_share = H.longest_share;
-    v.staged_longest_row = longest_row;
-    v.staged_partial = staged_partial;
-    v.n_rest_blocks = Z.n_blocks();
-    v.long_nnz = static_cast<int32_t>(long_nnz);
-    v.staged_row_count = H.n_rows;
-    v.staged_nnz = static_cast<int32_t>(H.nnz);
-    return hp;
-}
-
-// the plan's tables at their device address
-RowBlocks plan_view(const HostPlan &hp, const int32_t *mem)
-{
-    RowBlocks v = hp.view;
-    v.blocks = reinterpret_cast<const int4 *>(mem + hp.blocks_at);
-    v.huge_rows = reinterpret_cast<const int4 *>(mem + hp.huge_at);
-    v.waves = reinterpret_cast<const int4 *>(mem + hp.waves_at);
-    v.row_order = mem + hp.order_at;
-    v.long_waves = reinterpret_cast<const int4 *>(mem + hp.long_at);
-    v.rest_waves = reinterpret_cast<const int4 *>(mem + hp.rest_at);
-    v.short_rows = reinterpret_cast<const int4 *>(mem + hp.short_at);
-    v.staged_rows = v.staged_ranges ? mem + hp.staged_at : nullptr;
-    v.staged_ends = v.staged_ranges ? mem + hp.staging.size() : nullptr;
-    v.staged_groups = v.staged_ranges ? mem + hp.groups_at : nullptr;
+    RowBlocks v{};
+    v.huge_rows = t.huge_rows; v.waves = t.waves; v.short_rows = t.short_rows; v.long_waves = t.long_waves; v.rest_waves = t.rest_waves;
+    v.n_blocks = c.n_blocks; v.n_huge_rows = c.n_huge_rows; v.n_huge_blocks = c.n_huge_blocks;
+    v.n_short = c.n_short; v.n_long_blocks = c.n_long_blocks; v.n_rest_blocks = c.n_rest_blocks; v.long_nnz = c.long_nnz;
+    v.hot_share = nnz == 0 ? 0.f : other <= kHotRows ? 1.f : static_cast<float>(static_cast<double>(other_hot_nnz) / static_cast<double>(nnz));
+    v.staged_ranges = c.staged_ranges;
+    v.staged_cblocks = c.staged_ranges ? (other + kStageRows - 1) / kStageRows : 0;
+    v.staged_rows = c.staged_ranges ? t.staged_rows : nullptr;
+    v.staged_ends = c.staged_ranges ? t.staged_ends : nullptr;
+    v.staged_groups = c.staged_ranges ? t.staged_groups : nullptr;
+    v.staged_longest_share = c.staged_longest_share;
+    v.staged_longest_row = c.longest_row;
+    v.staged_partial = c.staged_partial;
+    v.staged_row_count = c.staged_rows;
+    v.staged_nnz = c.staged_nnz;
+    v.staged_preferred = mode == NERVA_PARTITION_PREFER_STAGED;
     return v;
 }
 
@@ -600,7 +548,6 @@ void free_pattern_buffers(PatternBuffers &b)
     (void)hipFree(b.indptr_t);
     (void)hipFree(b.mirror_mem);
     (void)hipFree(b.plan_mem);
-    (void)hipFree(b.plan_t_mem);
     b = PatternBuffers{};
 }
 
@@ -609,7 +556,7 @@ void free_layer_buffers(nerva_layer *l)
     free_pattern_buffers(l->cur);
     free_pattern_buffers(l->spare);
     (void)hipFree(l->build_work);
-    (void)hipFree(l->status);
+    if (l->bind_result) (void)hipHostFree(l->bind_result);
     (void)hipFree(l->scratch);
     (void)hipFree(l->partial);
     (void)hipFree(l->dense);
@@ -801,7 +748,7 @@ static int enable_dense(nerva_layer *layer, hipStream_t s);
 // the dense route needs a batch wide enough to fill its 16-column tiles
 static bool use_dense(const nerva_layer *l, int32_t batch) { return l->dense_on && batch >= 16; }
 
-// Message for the status word of the device-side CSR check (launch_validate_csr).
+// Message for the status word of the device-side CSR check (bind_check_kernel).
 static int csr_status_error(const int32_t *st)
 {
     const int f = st[0];
@@ -816,10 +763,9 @@ static int csr_status_error(const int32_t *st)
 
 // Everything a pattern allows to be precomputed, for a layer `l` that describes the NEW pattern (sizes,
 // caller-owned arrays, max_batch) and owns the buffers to build into: l->spare receives the mirror and the
-// partition tables (l->cur, if any, is not touched), the scratch buffers grow as needed.  What grows with
-// the stored entries runs on the device: the CSR check, the mirror with its position maps (a stable
-// counting sort by column) and the staged plans' segment bounds; the row partitions, which depend on the
-// row lengths only, are planned on the host from copies of the two row-pointer arrays.  On failure
+// partition tables (l->cur, if any, is not touched), the scratch buffers grow as needed.  All of it -- the CSR check,
+// the mirror with its position maps, the partitions of both orientations -- runs on the device in one chain of
+// launches (structure.hip); the host waits once, for the check's verdict and the partitions' sizes.  On failure
 // (NERVA_ERR_CSR, NERVA_ERR_HIP) nothing that a product reads has been changed.  On success the caller swaps
 // l->spare into l->cur and adopts `plan`, `plan_t`.
 struct BuiltPattern {
@@ -833,52 +779,60 @@ struct BuiltPattern {
 static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, const int32_t *indices, const float *values,
                             BuiltPattern *out, hipStream_t s)
 {
-    const int32_t rows = l->rows, cols = l->cols, max_batch = l->max_batch;
+    const int32_t rows = l->rows, cols = l->cols, max_batch = l->max_batch, mode = g_partition_mode.load();
+    static_assert(kPlanBalanced == NERVA_PARTITION_BALANCED && kPlanRowSplit == NERVA_PARTITION_ROW_SPLIT &&
+                  kPlanPreferStaged == NERVA_PARTITION_PREFER_STAGED, "header and kernels disagree");
     PatternBuffers &B = l->spare;
-    // 1. the pattern is checked where it lives; the row pointers come to the host for the partitions
-    std::vector<int32_t> h_indptr(static_cast<size_t>(rows) + 1), h_indptr_t(static_cast<size_t>(cols) + 1);
-    int32_t h_status[4] = {0, 0, 0, 0};
-    if (!l->status) HIP_TRY(hipMalloc(&l->status, 4 * sizeof(int32_t)));
-    HIP_TRY(launch_validate_csr(rows, cols, nnz, indptr, indices, l->status, s));
-    HIP_TRY(hipMemcpyAsync(h_indptr.data(), indptr, h_indptr.size() * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(h_status, l->status, sizeof h_status, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (h_status[0] != 0) return csr_status_error(h_status);
-
-    // 2. the mirror, on the device, into the spare set
     const size_t n64 = static_cast<size_t>(round_up(nnz > 0 ? nnz : 1, 64));
-    const int32_t T = mirror_tiles(rows, cols, nnz);
     size_t indptr_t_have = B.indptr_t ? static_cast<size_t>(cols) + 1 : 0;
     HIP_TRY(reserve(&B.indptr_t, &indptr_t_have, static_cast<size_t>(cols) + 1));
     HIP_TRY(reserve(&B.mirror_mem, &B.mirror_ints, 4 * n64));
-    HIP_TRY(reserve(&l->build_work, &l->build_work_ints, mirror_work_ints(cols, T)));
-    int32_t *indices_t = B.mirror_mem, *perm = B.mirror_mem + n64, *pos_t = B.mirror_mem + 2 * n64;
-    float *values_t = reinterpret_cast<float *>(B.mirror_mem + 3 * n64);
-    HIP_TRY(launch_build_mirror(rows, cols, nnz, indptr, indices, B.indptr_t, indices_t, perm, pos_t, l->build_work, T, s));
-    HIP_TRY(hipMemcpyAsync(h_indptr_t.data(), B.indptr_t, h_indptr_t.size() * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(launch_gather(values_t, values, perm, nnz, s));
-    // ... while the host orders the rows by length
-    const RowsByLength by_len = rows_by_length(rows, h_indptr.data());
+    const PlanRoom room(rows, cols, nnz, max_batch), room_t(cols, rows, nnz, max_batch);
+    const size_t plan_ints = static_cast<size_t>(round_up(static_cast<int64_t>(room.ints()), 64));
+    HIP_TRY(reserve(&B.plan_mem, &B.plan_ints, plan_ints + room_t.ints()));
+    if (!l->bind_result) HIP_TRY(hipHostMalloc(&l->bind_result, sizeof(BindResult), hipHostMallocDefault));
+
+    // scratch of the set-up kernels: carved out of one buffer
+    const MirrorGeometry geo = mirror_geometry(rows, cols, nnz);
+    const int64_t col_blocks = (static_cast<int64_t>(cols) + geo.block_cols - 1) / geo.block_cols;
+    size_t ints = 0;
+    auto carve = [&](size_t n) { const size_t at = ints; ints += (n + 63) / 64 * 64; return at; };
+    const size_t status_at = carve(4), base_at = carve(static_cast<size_t>(col_blocks) + 1), total_at = carve(geo.bins),
+                 counts_at = carve(static_cast<size_t>(geo.bins) * geo.tiles), bucket_at = carve(2 * n64), bucket_col_at = carve(n64);
+    size_t work_at[2];
+    const int32_t side_rows[2] = {rows, cols}, side_ranges[2] = {room.ranges, room_t.ranges};
+    constexpr size_t kCountInts = sizeof(PlanCounts) / 4;
+    for (int k = 0; k < 2; ++k) work_at[k] = carve(6 * static_cast<size_t>(side_rows[k]) + static_cast<size_t>(side_ranges[k]) + 1 + kCountInts);
+    HIP_TRY(reserve(&l->build_work, &l->build_work_ints, ints));
+    int32_t *W = l->build_work;
+
+    MirrorArgs m{};
+    static_cast<MirrorGeometry &>(m) = geo;
+    m.rows = rows; m.cols = cols; m.nnz = nnz; m.indptr = indptr; m.indices = indices; m.values = values;
+    m.status = W + status_at; m.block_base = W + base_at; m.bin_total = W + total_at; m.counts = W + counts_at;
+    m.bucket = reinterpret_cast<int2 *>(W + bucket_at); m.bucket_col = W + bucket_col_at;
+    m.indptr_t = B.indptr_t; m.indices_t = B.mirror_mem; m.perm = B.mirror_mem + n64; m.pos_t = B.mirror_mem + 2 * n64;
+    m.values_t = reinterpret_cast<float *>(B.mirror_mem + 3 * n64);
+    PlanArgs p{};
+    p.nnz = nnz; p.max_batch = max_batch; p.mode = mode; p.status = m.status; p.result = l->bind_result;
+    for (int k = 0; k < 2; ++k) {
+        PlanSide &side = p.side[k];
+        side.rows = side_rows[k]; side.other = side_rows[1 - k]; side.range_bound = side_ranges[k];
+        side.indptr = k == 0 ? indptr : B.indptr_t; side.indices = k == 0 ? indices : m.indices_t;
+        side.tables = k == 0 ? room.at(B.plan_mem) : room_t.at(B.plan_mem + plan_ints);
+        int32_t *w = W + work_at[k];
+        const size_t r = static_cast<size_t>(side.rows);
+        side.work = PlanWork{w, w + r, w + 2 * r, w + 3 * r, w + 4 * r, w + 5 * r, w + 6 * r,
+                             reinterpret_cast<PlanCounts *>(w + 6 * r + static_cast<size_t>(side.range_bound) + 1)};
+    }
+    HIP_TRY(launch_bind(m, p, s));
     HIP_TRY(hipStreamSynchronize(s));
-    const RowsByLength by_len_t = rows_by_length(cols, h_indptr_t.data());
+    const BindResult &R = *l->bind_result;
+    if (R.status[0] != 0) return csr_status_error(R.status);
+    out->plan = plan_view(p.side[0].tables, R.plan[0], cols, nnz, R.plan[1].hot_nnz, mode);
+    out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
 
-    // 3. the partitions of both orientations (integer work on row lengths), then their tables to the device
-    const HostPlan hp = make_plan(rows, h_indptr.data(), by_len, max_batch, cols, hot_row_share(cols, h_indptr_t.data(), by_len_t));
-    const HostPlan hp_t = make_plan(cols, h_indptr_t.data(), by_len_t, max_batch, rows, hot_row_share(rows, h_indptr.data(), by_len));
-    HIP_TRY(reserve(&B.plan_mem, &B.plan_ints, hp.total_ints()));
-    HIP_TRY(reserve(&B.plan_t_mem, &B.plan_t_ints, hp_t.total_ints()));
-    HIP_TRY(hipMemcpyAsync(B.plan_mem, hp.staging.data(), hp.staging.size() * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(B.plan_t_mem, hp_t.staging.data(), hp_t.staging.size() * 4, hipMemcpyHostToDevice, s));
-    out->plan = plan_view(hp, B.plan_mem);
-    out->plan_t = plan_view(hp_t, B.plan_t_mem);
-    if (out->plan.staged_ranges)
-        HIP_TRY(launch_staged_ends(indptr, indices, out->plan.staged_rows, const_cast<int32_t *>(out->plan.staged_ends),
-                                   out->plan.staged_ranges, out->plan.staged_cblocks, s));
-    if (out->plan_t.staged_ranges)
-        HIP_TRY(launch_staged_ends(B.indptr_t, indices_t, out->plan_t.staged_rows, const_cast<int32_t *>(out->plan_t.staged_ends),
-                                   out->plan_t.staged_ranges, out->plan_t.staged_cblocks, s));
-
-    // 4. scratch buffers (they hold nothing between calls: grown in place)
+    // scratch buffers of the products (they hold nothing between calls: grown in place)
     {
         // room for the column-tiled SDDMM at max_batch columns, if that batch would be tiled
         const int w = tile_columns(cols, max_batch, nnz, rows, out->plan.hot_share, false, true);
@@ -910,7 +864,6 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
             HIP_TRY(hipMalloc(&l->full_scratch, static_cast<size_t>(slices) * rows * out->full_scratch_ld * 4));
         }
     }
-    HIP_TRY(hipStreamSynchronize(s));  // the host staging vectors die at return
     return NERVA_OK;
 }
 
@@ -973,7 +926,7 @@ int sparse_linear_rebind(nerva_layer *layer, int32_t nnz, const int32_t *indptr,
     if (!layer) return fail(NERVA_ERR_ARGUMENT, "layer is null");
     if (nnz < 0 || !indptr || (nnz > 0 && (!indices || !values))) return fail(NERVA_ERR_ARGUMENT, "null pattern or values pointer");
     hipStream_t s = as_stream(stream);
-    HIP_TRY(hipStreamSynchronize(s));  // launches already queued on this stream still use the old structures
+    // (launches already queued on this stream use the old structures, which the new ones do not overwrite)
     BuiltPattern bp;
     const int rc = build_structures(layer, nnz, indptr, indices, values, &bp, s);
     if (rc != NERVA_OK) return rc;  // the layer keeps its old pattern: only the spare set and scratch buffers were written

@@ -14,11 +14,8 @@ constexpr int kWavesPerBlock = 16;   // 1024 threads
 // into several work-groups; each produces a partial result that a second, small kernel adds
 // up in share order.  Huge work-groups come first, so blockIdx.x is also their scratch slot.
 struct RowBlocks {
-    const int32_t *row_order;  // [rows - n_huge_rows] ordinary row ids, grouped by lg (descending)
-    const int4 *blocks;        // [n_blocks] ordinary: {lg | rows served << 8, first slot of row_order, 0, 0}
-                               //            huge:     {kHugeFlag | share index, row, first entry, end entry}
     const int4 *huge_rows;     // [n_huge_rows] {row, first work-group, number of work-groups, 0}
-    const int4 *waves;         // [n_blocks * kWavesPerBlock] the same partition spelled out per wave:
+    const int4 *waves;         // [n_blocks * kWavesPerBlock] the partition, spelled out per wave:
                                // {row or -1, first entry, end entry, part | lg << 4 | lead << 8 | huge << 9}
     int32_t n_blocks;
     int32_t n_huge_rows;
@@ -64,6 +61,7 @@ constexpr int32_t kStageCols = 64;       // columns of the operand (examples) pe
 constexpr int32_t kStageJ = 8;           // rows per row of 16 lanes
 constexpr int32_t kStageQuad = 1 << 30;  // flag in staged_rows: the slot is one of the four of a split row
 constexpr int32_t kStageRangeRows = 512; // rows per work-group: 16 waves x 4 lane rows x kStageJ
+constexpr int32_t kStageRangeFill = kStageRangeRows - 4;  // slots after which a range is cut (a split row takes four at once)
 constexpr int32_t kStageMinBatch = 128;  // narrower batches never take the staged product
 constexpr int32_t kStageTargetGroups = 256;  // work-groups wanted at max_batch (one per compute unit)
 constexpr float kStageMinReuse = 2.f;    // stored entries per staged operand row and work-group, at least
@@ -73,7 +71,6 @@ constexpr int32_t kStageLongSegmentSddmm = 20;  // ... and the SDDMM (measured o
 constexpr int64_t kStageBigOperand = 48ll << 20;  // operand bytes no set of L2s holds: staging pays for shorter segments,
 constexpr int32_t kStageSegmentBigOperand = 7;    // ... from this many entries per segment on
 constexpr int32_t kHotRows = 1024;
-constexpr int32_t kHugeFlag = 0x40000000;
 constexpr int32_t kPackMaxLen = 128;     // longest row served by the packed path
 constexpr int32_t kPackMinRows = 2048;   // fewer short rows than this: no packed path
 constexpr int32_t kPackSets = 1;         // row sets (64/GS rows each) per wave; measured on the wide MLP: 1 / 2 / 4 / 8 sets give 500 / 504 / 527 / 548 us per step
@@ -266,24 +263,113 @@ hipError_t launch_dense_sddmm_update(const DenseUpdateArgs &a, const float *X, i
 hipError_t launch_dense_refresh(const int32_t *indptr, const int32_t *indices, const float *values, int32_t rows, float *D, int64_t ld,
                                 hipStream_t s);
 
-// ---- binding a pattern: the work that grows with the number of stored entries, on the device ----
-// Check that device arrays hold a canonical CSR pattern.  status (device, 4 ints) receives
-// {OR of the kCsr* flags found, first row with wrong row pointers, first entry with a wrong column
-// index, 0}; rows whose pointers are wrong are not walked, so nothing outside the arrays is read.
+// ---- binding a pattern: one chain of launches on the device (structure.hip) ----
+// Flags of the check that device arrays hold a canonical CSR pattern: status (device, 4 ints) receives {OR of the
+// flags found, first row with wrong row pointers, first entry with a wrong column index, 0}.
 enum : int32_t { kCsrBadFirst = 1, kCsrDecreasing = 2, kCsrBeyondNnz = 4, kCsrBadLast = 8, kCsrColumnRange = 16, kCsrNotAscending = 32 };
-hipError_t launch_validate_csr(int32_t rows, int32_t cols, int32_t nnz, const int32_t *indptr, const int32_t *indices,
-                               int32_t *status, hipStream_t s);
-// CSC mirror of a canonical CSR pattern (stable counting sort by column): indptr_t[cols + 1],
-// indices_t[nnz] (row of each mirror entry), perm[nnz] (mirror position -> CSR position), pos_t[nnz]
-// (the inverse).  work: mirror_work_ints(cols, T) ints of scratch, T = mirror_tiles(rows, cols, nnz).
-int32_t mirror_tiles(int32_t rows, int32_t cols, int32_t nnz);
-size_t mirror_work_ints(int32_t cols, int32_t T);
-hipError_t launch_build_mirror(int32_t rows, int32_t cols, int32_t nnz, const int32_t *indptr, const int32_t *indices,
-                               int32_t *indptr_t, int32_t *indices_t, int32_t *perm, int32_t *pos_t, int32_t *work, int32_t T,
-                               hipStream_t s);
-// RowBlocks::staged_ends from RowBlocks::staged_rows and the pattern
-hipError_t launch_staged_ends(const int32_t *indptr, const int32_t *indices, const int32_t *slot_rows, int32_t *ends, int32_t ranges,
-                              int32_t n_cb, hipStream_t s);
+
+// How the mirror build cuts a matrix: tiles of entries, bins of 2^bin_shift columns, a bin's bitmap over seg_words * 32
+// rows at a time, launches of block_cols columns.
+struct MirrorGeometry {
+    int32_t bin_shift, bins, seg_words, tiles, tile_entries, block_cols;
+};
+MirrorGeometry mirror_geometry(int32_t rows, int32_t cols, int32_t nnz);
+struct MirrorArgs : MirrorGeometry {
+    int32_t rows, cols, nnz;
+    int32_t col_lo, cols_here;       // columns of the launch (set by launch_bind)
+    const int32_t *indptr, *indices;
+    const float *values;
+    int32_t *status;
+    int32_t *counts;                 // [bins * tiles]
+    int32_t *bin_total;              // [bins]
+    int32_t *block_base;             // [blocks of columns + 1] mirror position of a block's first entry
+    int2 *bucket;                    // [nnz] {row, entry}, bin by bin
+    int32_t *bucket_col;             // [nnz]
+    // CSR of W^T: row pointers, row of each mirror entry, mirror position -> CSR position and back, values
+    int32_t *indptr_t, *indices_t, *perm, *pos_t;
+    float *values_t;
+};
+
+// What the planner reports of one orientation; RowBlocks holds the meanings.
+struct PlanCounts {
+    int32_t n_blocks, n_huge_rows, n_huge_blocks, n_short, n_long_blocks, n_rest_blocks, long_nnz, longest_row;
+    int32_t n_long_rows;             // rows of more than kPackMaxLen entries
+    int32_t hot_nnz;                 // stored entries of the kHotRows longest rows
+    int32_t staged_ranges, staged_partial, staged_rows, staged_nnz, staged_quad_len, staged_longest_share;
+    int32_t cls[3][5];               // rows per class of the partitions waves / long_waves / rest_waves
+};
+struct PlanTables {
+    int4 *waves, *huge_rows, *long_waves, *rest_waves, *short_rows;
+    int32_t *staged_rows, *staged_groups, *staged_ends;
+};
+struct PlanWork {                    // scratch, [rows] ints each but for the last two
+    int32_t *order, *tmp, *lens, *covered, *cut, *slots;
+    int32_t *range_first;            // [range_bound + 1]
+    PlanCounts *counts;
+};
+struct PlanSide {
+    int32_t rows, other;             // of this orientation
+    int32_t range_bound;             // ranges the staged tables have room for, 0: no staged plan
+    const int32_t *indptr, *indices;
+    PlanTables tables;
+    PlanWork work;
+};
+struct BindResult {                  // pinned host memory
+    int32_t status[4];
+    PlanCounts plan[2];
+};
+enum : int32_t { kPlanBalanced = 0, kPlanRowSplit = 1, kPlanPreferStaged = 2 };
+struct PlanArgs {
+    PlanSide side[2];                // W, its mirror
+    int32_t nnz, max_batch, mode;
+    const int32_t *status;
+    BindResult *result;
+};
+hipError_t launch_bind(const MirrorArgs &m, const PlanArgs &p, hipStream_t s);
+
+// Ranges a staged plan over `rows` rows with `nnz` entries aims at, 0: such a plan would never be chosen.  (Host and
+// device; `cols`: operand rows.)
+__host__ __device__ inline int32_t staged_ranges_aim(int32_t rows, int32_t max_batch)
+{
+    const int32_t n_tiles = (max_batch + kStageCols - 1) / kStageCols;
+    int32_t want = kStageTargetGroups / n_tiles;
+    if (want > rows / 64) want = rows / 64;
+    // (ranges cut by cost are not equally long: leave an eighth of the slots as slack)
+    const int32_t at_least = (rows + kStageRangeRows * 7 / 8 - 1) / (kStageRangeRows * 7 / 8);
+    if (want < at_least) want = at_least;
+    // one work-group fits a compute unit at a time: fill the last round of the grid as well
+    if (static_cast<int64_t>(want) * n_tiles > kStageTargetGroups) {
+        const int64_t rounds = (static_cast<int64_t>(want) * n_tiles + kStageTargetGroups - 1) / kStageTargetGroups;
+        want = static_cast<int32_t>(rounds * kStageTargetGroups / n_tiles);
+    }
+    return want;
+}
+__host__ __device__ inline int32_t staged_ranges_wanted(int32_t rows, int64_t nnz, int32_t cols, int32_t max_batch, int32_t mode,
+                                                        int32_t range_bound)
+{
+    if (range_bound == 0 || mode == kPlanRowSplit || max_batch < kStageMinBatch || nnz == 0) return 0;
+    const int32_t want = staged_ranges_aim(rows, max_batch);
+    if (mode != kPlanPreferStaged && static_cast<double>(nnz) < static_cast<double>(kStageMinReuse) * want * cols) return 0;
+    return want;
+}
+// Most ranges any staged plan of a matrix with that many rows can have; 0 where its tables would pass 1 GiB.  A plan over
+// some of the rows aims at no more ranges than one over all of them, but for the rounding to whole rounds of the grid;
+// the ranges that overflow add one per kStageRangeFill slots, of which split rows take three more each
+// (at most 32 split rows per range aimed at).
+__host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols, int32_t max_batch)
+{
+    if (max_batch < kStageMinBatch) return 0;
+    const int32_t n_tiles = (max_batch + kStageCols - 1) / kStageCols;
+    const int64_t want = (static_cast<int64_t>(rows) + kStageRangeRows * 7 / 8 - 1) / (kStageRangeRows * 7 / 8) + 2 * (kStageTargetGroups / n_tiles) + 2;
+    const int64_t bound = want + (rows + 96 * want) / kStageRangeFill + 2;
+    return bound * ((cols + kStageRows - 1) / kStageRows + 1) * kStageRangeRows > (1ll << 28) ? 0 : static_cast<int32_t>(bound);
+}
+// which of `want` equal shares of the total cost a row falls into that has `done` of it before it
+__host__ __device__ inline int32_t staged_cut(int64_t done, int32_t want, int64_t total)
+{
+    const int32_t cut = static_cast<int32_t>(static_cast<double>(done) * want / static_cast<double>(total));
+    return cut < want ? cut : want - 1;
+}
 
 // The end of the forward pass and the start of the backward pass for a small output layer, in
 // one launch: logits Z = W X + b, softmax cross-entropy (loss and dZ = (softmax - onehot) / batch),
