@@ -123,6 +123,9 @@ struct nerva_layer {
     size_t partial_floats = 0;
     int64_t partial_stride = 0, partial_db_at = 0;
     int32_t partial_tiles = 0;
+    // owned, only for a ReLU layer: dZ of a stand-alone backward pass, (rows, dz_ld); nullptr: too large to be worth it
+    float *dz = nullptr;
+    int64_t dz_ld = 0;
     // owned, only on the dense route (sparse_linear_enable_dense, or chosen when the pattern was bound): a
     // zero-filled dense copy of W (rows x dense_ld, dense_ld = cols rounded up to kDenseLdAlign) and a dense
     // gradient of the same shape
@@ -559,6 +562,7 @@ void free_layer_buffers(nerva_layer *l)
     if (l->bind_result) (void)hipHostFree(l->bind_result);
     (void)hipFree(l->scratch);
     (void)hipFree(l->partial);
+    (void)hipFree(l->dz);
     (void)hipFree(l->dense);
     (void)hipFree(l->dense_g);
     (void)hipFree(l->full_scratch);
@@ -900,7 +904,13 @@ int sparse_linear_create(nerva_layer **out, int32_t rows, int32_t cols, int32_t 
     if (!l) return fail(NERVA_ERR_ARGUMENT, "out of host memory");
     l->rows = rows; l->cols = cols; l->activation = activation; l->max_batch = max_batch; l->bias = bias;
     BuiltPattern bp;
-    const int rc = build_structures(l, nnz, indptr, indices, values, &bp, as_stream(stream));
+    int rc = build_structures(l, nnz, indptr, indices, values, &bp, as_stream(stream));
+    l->dz_ld = round_up(max_batch, 32);
+    const size_t dz_bytes = static_cast<size_t>(rows) * l->dz_ld * 4;
+    if (rc == NERVA_OK && activation == NERVA_ACT_RELU && dz_bytes <= (1ull << 30)) {
+        const hipError_t e = hipMalloc(&l->dz, dz_bytes);
+        if (e != hipSuccess) rc = hip_fail(e, "gradient scratch");
+    }
     if (rc != NERVA_OK) {
         free_layer_buffers(l);
         delete l;
@@ -1041,17 +1051,28 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
     if (rc == NERVA_OK && batch > layer->max_batch) rc = fail(NERVA_ERR_SHAPE, "batch %d exceeds the layer's max_batch %d", batch, layer->max_batch);
     if (rc != NERVA_OK) return rc;
     hipStream_t s = as_stream(stream);
-    if (dX && use_dense(layer, batch) && !relu) {
+    // dZ of a ReLU layer: formed once where a transposed product would gather its rows from two operands, unless the
+    // matrix is so sparse that the pass over dY and Y costs more than the gathers it saves
+    const bool form_dz = dX && relu && layer->dz && batch > 4 && layer->nnz >= 4 * static_cast<int64_t>(layer->rows);
+    if (form_dz) {
+        HIP_TRY(launch_backward_prep(layer->values_t, layer->values, layer->perm, layer->nnz, dY, lddy, Y, ldy, layer->dz, layer->dz_ld,
+                                     layer->rows, batch, s));
+        layer->mirror_stale = false;
+        dY = layer->dz;
+        lddy = static_cast<int32_t>(layer->dz_ld);
+    }
+    const bool mask = relu && !form_dz;  // dY still is the gradient of the output
+    if (dX && use_dense(layer, batch) && !mask) {
         HIP_TRY(refresh_dense_copies(layer, s));
         HIP_TRY(dense_transposed(layer, dY, lddy, dX, lddx, nullptr, 0, batch, s));
     } else if (dX) {
-        HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
+        if (!form_dz) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
         layer->mirror_stale = false;
         SpmmArgs a{};
         a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.scratch_ld = layer->scratch_ld;
         a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
         a.X = dY; a.ldx = lddy;
-        if (relu) { a.XM = Y; a.ldxm = ldy; }
+        if (mask) { a.XM = Y; a.ldxm = ldy; }
         a.Y = dX; a.ldy = lddx; a.rows = layer->cols; a.x_rows = layer->rows; a.batch = batch;
         HIP_TRY(launch_spmm(a, s));
     }
@@ -1060,7 +1081,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
         a.blocks = layer->plan;
         a.indptr = layer->indptr; a.indices = layer->indices;
         a.dZ = dY; a.lddz = lddy;
-        if (relu) { a.ZM = Y; a.ldzm = ldy; }
+        if (mask) { a.ZM = Y; a.ldzm = ldy; }
         a.X = X; a.ldx = ldx; a.g = dvalues; a.db = dbias;
         a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.nnz = layer->nnz;
         a.partial = layer->partial; a.partial_stride = layer->partial_stride;

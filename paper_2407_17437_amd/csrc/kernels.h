@@ -215,6 +215,9 @@ hipError_t launch_momentum(float *w, float *v, const float *g, int64_t n, float 
 // values_t[q] = values[perm[q]]
 hipError_t launch_gather(float *values_t, const float *values, const int32_t *perm, int64_t n,
                          hipStream_t s);
+// the same, and dZ = dY * [Y > 0] (rows x batch, batch >= 4) in one launch
+hipError_t launch_backward_prep(float *values_t, const float *values, const int32_t *perm, int64_t nnz, const float *dY, int64_t lddy,
+                                const float *Y, int64_t ldy, float *dZ, int64_t lddz, int32_t rows, int32_t batch, hipStream_t s);
 hipError_t launch_softmax_ce(const float *Z, int64_t ldz, const int32_t *labels, int32_t classes,
                              int32_t batch, float *dZ, int64_t lddz, float *loss, hipStream_t s);
 hipError_t launch_copy(float *dst, const float *src, int64_t n, hipStream_t s);

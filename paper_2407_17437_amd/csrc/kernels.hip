@@ -1888,6 +1888,29 @@ __global__ __launch_bounds__(kEwBlock) void gather_kernel(float *__restrict__ ds
         dst[i] = src[perm[i]];
 }
 
+// What a stand-alone backward pass needs before its products, in one grid: the mirror's values (work-groups [0, n_gather)),
+// and dZ = dY * [Y > 0] of a ReLU layer, four columns per thread.  The transposed product gathers a row of dZ per stored
+// entry; with the mask as a second operand it gathered two (4096 x 3072 at 5 %, batch 128: 37.9 us, 16.4 from dZ,
+// which takes 0.8 us more than the values alone).
+__global__ __launch_bounds__(kEwBlock) void backward_prep_kernel(float *__restrict__ values_t, const float *__restrict__ values,
+                                                                 const int32_t *__restrict__ perm, int64_t nnz, int n_gather,
+                                                                 const float *__restrict__ dY, int64_t lddy, const float *__restrict__ Y,
+                                                                 int64_t ldy, float *__restrict__ dZ, int64_t lddz, int rows, int batch)
+{
+    if (static_cast<int>(blockIdx.x) < n_gather) {
+        const int64_t stride = static_cast<int64_t>(n_gather) * kEwBlock;
+        for (int64_t i = static_cast<int64_t>(blockIdx.x) * kEwBlock + threadIdx.x; i < nnz; i += stride) values_t[i] = values[perm[i]];
+        return;
+    }
+    const int quads = (batch + 3) / 4;   // batch >= 4
+    const int64_t n = static_cast<int64_t>(rows) * quads, stride = static_cast<int64_t>(gridDim.x - n_gather) * kEwBlock;
+    for (int64_t k = static_cast<int64_t>(blockIdx.x - n_gather) * kEwBlock + threadIdx.x; k < n; k += stride) {
+        const int64_t row = k / quads;
+        const int c = four_columns(static_cast<int>(k - row * quads) * 4, batch);
+        st4(dZ + row * lddz + c, keep_where_positive(ld4(dY + row * lddy + c), ld4(Y + row * ldy + c)));
+    }
+}
+
 __global__ __launch_bounds__(kEwBlock) void copy_kernel(float *__restrict__ dst, const float *__restrict__ src,
                                                         int64_t n, int vec4)
 {
@@ -2708,6 +2731,16 @@ hipError_t launch_gather(float *values_t, const float *values, const int32_t *pe
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(gather_kernel, dim3(elementwise_blocks(n)), dim3(kEwBlock), 0, s, values_t, values, perm, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_prep(float *values_t, const float *values, const int32_t *perm, int64_t nnz, const float *dY, int64_t lddy,
+                                const float *Y, int64_t ldy, float *dZ, int64_t lddz, int32_t rows, int32_t batch, hipStream_t s)
+{
+    const int n_gather = nnz > 0 ? elementwise_blocks(nnz) : 0;
+    const int n_mask = elementwise_blocks(static_cast<int64_t>(rows) * ((batch + 3) / 4));
+    hipLaunchKernelGGL(backward_prep_kernel, dim3(n_gather + n_mask), dim3(kEwBlock), 0, s, values_t, values, perm, nnz, n_gather, dY, lddy, Y,
+                       ldy, dZ, lddz, rows, batch);
     return hipGetLastError();
 }
 
