@@ -91,6 +91,9 @@ struct PatternBuffers {
     size_t mirror_ints = 0;
     int32_t *plan_mem = nullptr;    // tables of both orientations
     size_t plan_ints = 0;
+    int32_t *table = nullptr;       // pattern table, 2 ints per row and 32 columns
+    size_t table_ints = 0;
+    bool has_table = false;         // it holds the pattern (else the layer is too sparse for it)
 };
 
 struct nerva_layer {
@@ -127,10 +130,9 @@ struct nerva_layer {
     float *dz = nullptr;
     int64_t dz_ld = 0;
     // owned, only on the dense route (sparse_linear_enable_dense, or chosen when the pattern was bound): a
-    // zero-filled dense copy of W (rows x dense_ld, dense_ld = cols rounded up to kDenseLdAlign) and a dense
-    // gradient of the same shape
+    // zero-filled dense copy of W (rows x dense_ld, dense_ld = cols rounded up to kDenseLdAlign)
     bool dense_on = false;
-    float *dense = nullptr, *dense_g = nullptr;
+    float *dense = nullptr;
     int64_t dense_ld = 0;
     // owned, only for a matrix that stores every entry and has at most kFullMaxRows rows
     bool full = false;               // the bound pattern is such a matrix
@@ -551,6 +553,7 @@ void free_pattern_buffers(PatternBuffers &b)
     (void)hipFree(b.indptr_t);
     (void)hipFree(b.mirror_mem);
     (void)hipFree(b.plan_mem);
+    (void)hipFree(b.table);
     b = PatternBuffers{};
 }
 
@@ -564,7 +567,6 @@ void free_layer_buffers(nerva_layer *l)
     (void)hipFree(l->partial);
     (void)hipFree(l->dz);
     (void)hipFree(l->dense);
-    (void)hipFree(l->dense_g);
     (void)hipFree(l->full_scratch);
 }
 
@@ -710,13 +712,21 @@ static bool dense_shape_ok(int32_t rows, int32_t cols)
     return rows >= 64 && cols >= 64 && static_cast<int64_t>(rows) * round_up(cols, kDenseLdAlign) < (1ll << 29);
 }
 
-// The dense copy for the dense route: allocated zero, then filled from the stored entries; and the dense gradient.
+static int32_t table_words(const nerva_layer *l) { return (l->cols + 31) / 32; }
+
+// The dense copy for the dense route: allocated zero, then filled from the stored entries; and the pattern table, where
+// the layer has none yet.
 static hipError_t build_dense_copies(nerva_layer *l, hipStream_t s)
 {
     l->dense_ld = round_up(l->cols, kDenseLdAlign);
     const size_t bytes = static_cast<size_t>(l->rows) * l->dense_ld * 4;
     hipError_t e = hipMalloc(&l->dense, bytes);
-    if (e == hipSuccess) e = hipMalloc(&l->dense_g, bytes);
+    if (e == hipSuccess && !l->cur.has_table) {
+        e = reserve(&l->cur.table, &l->cur.table_ints, static_cast<size_t>(l->rows) * table_words(l) * 2);
+        if (e == hipSuccess)
+            e = launch_pattern_table(l->indptr, l->indices, l->rows, table_words(l), reinterpret_cast<uint2 *>(l->cur.table), nullptr, s);
+        if (e == hipSuccess) l->cur.has_table = true;
+    }
     if (e == hipSuccess) e = hipMemsetAsync(l->dense, 0, bytes, s);
     if (e == hipSuccess) e = launch_dense_refresh(l->indptr, l->indices, l->values, l->rows, l->dense, l->dense_ld, s);
     return e;
@@ -830,6 +840,11 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
                              reinterpret_cast<PlanCounts *>(w + 6 * r + static_cast<size_t>(side.range_bound) + 1)};
     }
     HIP_TRY(launch_bind(m, p, s));
+    B.has_table = l->dense_on || static_cast<double>(nnz) >= static_cast<double>(kTableFromDensity) * rows * cols;
+    if (B.has_table) {
+        HIP_TRY(reserve(&B.table, &B.table_ints, static_cast<size_t>(rows) * table_words(l) * 2));
+        HIP_TRY(launch_pattern_table(indptr, indices, rows, table_words(l), reinterpret_cast<uint2 *>(B.table), m.status, s));
+    }
     HIP_TRY(hipStreamSynchronize(s));
     const BindResult &R = *l->bind_result;
     if (R.status[0] != 0) return csr_status_error(R.status);
@@ -963,8 +978,7 @@ static int enable_dense(nerva_layer *layer, hipStream_t s)
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(layer->dense);
-        (void)hipFree(layer->dense_g);
-        layer->dense = layer->dense_g = nullptr;
+        layer->dense = nullptr;
         return hip_fail(e, "sparse_linear_enable_dense");
     }
     layer->dense_on = true;
@@ -1087,6 +1101,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
         a.partial = layer->partial; a.partial_stride = layer->partial_stride;
         a.partial_db_at = layer->partial_db_at; a.partial_tiles = layer->partial_tiles;
         a.skip_products = dvalues ? 0 : 1;  // only the bias gradient is wanted
+        if (layer->cur.has_table) { a.table = reinterpret_cast<const uint2 *>(layer->cur.table); a.table_words = table_words(layer); }
         HIP_TRY(launch_sddmm(a, s));
     }
     return NERVA_OK;
@@ -1394,6 +1409,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         g.rows = ly->rows; g.x_rows = ly->cols; g.batch = batch; g.nnz = ly->nnz;
         g.partial = ly->partial; g.partial_stride = ly->partial_stride;
         g.partial_db_at = ly->partial_db_at; g.partial_tiles = ly->partial_tiles;
+        if (ly->cur.has_table) { g.table = reinterpret_cast<const uint2 *>(ly->cur.table); g.table_words = table_words(ly); }
         if ((head || ce_fused) && l == n - 1 && loss_out) { g.loss_cols = mlp->head_scratch; g.loss_out = loss_out; g.loss_n = batch; }
         if (fused) {
             g.fused = 1; g.nesterov = nesterov; g.lr = lr; g.momentum = momentum;
@@ -1450,30 +1466,32 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         // `pending`: a layer whose transposed product has run and whose S has not.  Where a layer's T and S
         // can share their gathers (backward_fused_ok) they run as one launch and nothing stays pending.
         int pending = -1;
-        // S_l through the dense gradient: for a layer on the dense route whose operands allow 16-byte accesses
-        auto dense_S_ok = [&](int l) {
-            const nerva_layer *ly = mlp->layers[l];
-            const float *in = l > 0 ? A(l - 1) : X;
-            const int64_t ldin = l > 0 ? L.ld : ldx;
-            return use_dense(ly, batch) && ly->nnz > 0 && ldin % 4 == 0 && (reinterpret_cast<uintptr_t>(in) & 15u) == 0 &&
-                   !(head && l == n - 1 && loss_out);
+        // Layers whose S runs as MFMA tiles sampled on the pattern (sddmm_sampled_ok) wait for the end of the step and
+        // share one grid; nothing in the step depends on them.
+        SampledArgs sampled{};
+        int last_sampled = 0;
+        auto flush_sampled = [&]() -> int {
+            if (sampled.n == 0) return NERVA_OK;
+            const bool dense_alone = sampled.n == 1 && mlp->layers[last_sampled]->dense_on;
+            Timed tm(mlp->prof, s, dense_alone ? "dense_sddmm_update" : sampled.n == 1 ? "sddmm_update" : "sddmm_update+sddmm_update", last_sampled);
+            HIP_TRY(launch_sampled(sampled, s));
+            sampled = SampledArgs{};
+            return NERVA_OK;
+        };
+        auto defer_S = [&](int l) -> int {
+            // (timed launch by launch, every layer on the dense route gets a slot of its own)
+            const bool apart = mlp->prof.on && mlp->layers[l]->dense_on;
+            if (sampled.n == kSampledLayers || (apart && sampled.n > 0))
+                if (const int e = flush_sampled(); e != NERVA_OK) return e;
+            add_sampled(sampled, make_S(l));
+            last_sampled = l;
+            return apart ? flush_sampled() : static_cast<int>(NERVA_OK);
         };
         auto run_S_alone = [&](int l) -> int {
-            if (dense_S_ok(l)) {
-                nerva_layer *ly = mlp->layers[l];
-                DenseUpdateArgs u{};
-                u.indptr = ly->indptr; u.indices = ly->indices; u.dZ = dZ(l); u.lddz = L.ld;
-                u.G = ly->dense_g; u.ldg = ly->dense_ld; u.D = ly->dense; u.ldw = ly->dense_ld;
-                u.values = ly->values; u.velocity = mlp->vel[l];
-                if (l > 0) { u.values_t = ly->values_t; u.pos_t = ly->pos_t; }
-                if (l != bias_done) { u.bias = ly->bias; u.bias_velocity = mlp->bias_vel[l]; }
-                u.rows = ly->rows; u.cols = ly->cols; u.batch = batch; u.nesterov = nesterov; u.lr = lr; u.momentum = momentum;
-                Timed tm(mlp->prof, s, "dense_sddmm_update", l);
-                HIP_TRY(launch_dense_sddmm_update(u, l > 0 ? A(l - 1) : X, l > 0 ? L.ld : ldx, s));
-                return NERVA_OK;
-            }
+            const SddmmArgs g = make_S(l);
+            if (sddmm_sampled_ok(g)) return defer_S(l);
             Timed tm(mlp->prof, s, "sddmm_update", l);
-            HIP_TRY(launch_sddmm(make_S(l), s));
+            HIP_TRY(launch_sddmm(g, s));
             return NERVA_OK;
         };
         if (head) pending = n - 1;  // the head launch has run T_{n-1}
@@ -1481,7 +1499,8 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
             // dZ_l is ready: T_l (which hands dZ_{l-1} down) and S_l
             const SpmmArgs t = make_T(l);
             if (use_dense(mlp->layers[l], batch)) {
-                if (pending >= 0 && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
+                // (no grid to share with a dense product: a small output layer joins the sampled ones where it has a table)
+                if (pending >= 0 && (rc = sddmm_sampled_possible(make_S(pending)) ? defer_S(pending) : run_S_alone(pending)) != NERVA_OK) return rc;
                 { Timed tm(mlp->prof, s, "dense_transposed", l); HIP_TRY(dense_T(l)); }
                 pending = l;
                 continue;
@@ -1509,7 +1528,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
             }
             if (pending >= 0) {
                 const SddmmArgs g = make_S(pending);
-                if (!dense_S_ok(pending) && can_pair(t, g)) {
+                if (can_pair(t, g)) {
                     Timed tm(mlp->prof, s, "spmm_transposed+sddmm_update", l);
                     HIP_TRY(launch_pair(t, g, s));
                 } else {
@@ -1525,7 +1544,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         // the first layer has no transposed product: its S, with the one still pending if any
         if (pending >= 0) {
             const SddmmArgs gp = make_S(pending), g0 = make_S(0);
-            if (pending == 1 && !dense_S_ok(0) && !dense_S_ok(1) && can_pair(g0, gp)) {
+            if (pending == 1 && can_pair(g0, gp)) {
                 Timed tm(mlp->prof, s, "sddmm_update+sddmm_update", 0);
                 HIP_TRY(launch_pair(g0, gp, s));  // the larger layer's work-groups start first
             } else {
@@ -1535,6 +1554,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         } else if ((rc = run_S_alone(0)) != NERVA_OK) {
             return rc;
         }
+        if ((rc = flush_sampled()) != NERVA_OK) return rc;
     } else {
         for (int l = n - 1; l >= 0; --l) {
             nerva_layer *ly = mlp->layers[l];

@@ -169,6 +169,9 @@ struct SddmmArgs {
     // weight there too, dense[row * dense_ld + col]
     float *dense;
     int64_t dense_ld;
+    // pattern table of a layer dense enough for the sampled gradient (or nullptr): [rows * table_words]
+    const uint2 *table;
+    int32_t table_words;
 };
 // Column-tile width (in columns) the products use when their gathered operand has x_rows rows and
 // does not fit an L2; 0: no tiling.  Shared by the kernels' dispatch and by the sizing of the
@@ -228,6 +231,7 @@ hipError_t launch_copy(float *dst, const float *src, int64_t n, hipStream_t s);
 // the forward product, the transposed product (the same copy read down its columns) and, through a dense
 // gradient G = dZ X^T of the same shape, the update of the stored entries.
 constexpr int32_t kDenseLdAlign = 64;
+constexpr float kTableFromDensity = 0.15f;  // layers at least this dense get a pattern table when they are bound
 constexpr float kDenseFromDensity = 0.4f;   // layers at least this dense take the dense route by themselves (measured cut-over)
 struct DenseArgs {
     const float *W;      // the dense copy, (rows, ldw)
@@ -244,24 +248,39 @@ struct DenseArgs {
     int32_t relu;
 };
 hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s);
-// G = dZ X^T (rows x cols, dense), then per stored entry the momentum step with its element of G, the new weight
-// written to values[], the mirror and the dense copy; bias gradient = row sums of dZ.  Needs 16-byte aligned
-// operands with leading dimensions that are multiples of 4.
-struct DenseUpdateArgs {
-    const int32_t *indptr, *indices;
-    const float *dZ;     // (rows, lddz)
-    int64_t lddz;
-    float *G;            // (rows, ldg) scratch
-    int64_t ldg;
-    float *D;            // the dense copy
-    int64_t ldw;
-    float *values, *velocity, *values_t;   // values_t may be nullptr
+// Gradient and update of up to kSampledLayers layers in one grid: G = dZ X^T in MFMA tiles, of which the entries on the
+// pattern are stored or take the momentum step (sampled_update_kernel in dense.hip).
+constexpr int kSampledLayers = 4;
+constexpr int32_t kSampledMinBatch = 16;
+struct SampledLayer {
+    const uint2 *table;  // [rows * words] {bits of 32 columns of the row's pattern, CSR position of the first of them}
+    int32_t words, rows, cols, nnz, fused;
+    int32_t tiles_i, tiles_j, first_block; // set by launch_sampled
+    const float *dZ, *X;
+    int64_t lddz, ldx;
+    float *g, *db;                         // stored unless nullptr
+    float *values, *velocity, *values_t;   // fused: values_t may be nullptr
     const int32_t *pos_t;
-    float *bias, *bias_velocity;           // may be nullptr
-    int32_t rows, cols, batch, nesterov;
-    float lr, momentum;
+    float *dense;                          // fused: dense copy or nullptr
+    int64_t dense_ld;
+    float *bias, *bias_velocity;           // fused: may be nullptr
 };
-hipError_t launch_dense_sddmm_update(const DenseUpdateArgs &a, const float *X, int64_t ldx, hipStream_t s);
+struct SampledArgs {
+    SampledLayer layer[kSampledLayers];
+    int32_t n, batch, nesterov;
+    float lr, momentum;
+    const float *loss_cols;                // by-product as in SddmmArgs
+    float *loss_out;
+    int32_t loss_n;
+};
+// whether launch_sddmm takes that route for `a`, and whether it could be served by it beside layers that do
+bool sddmm_sampled_ok(const SddmmArgs &a);
+bool sddmm_sampled_possible(const SddmmArgs &a);
+void add_sampled(SampledArgs &list, const SddmmArgs &a);
+hipError_t launch_sampled(SampledArgs &a, hipStream_t s);
+// status: result of the pattern check (the launch does nothing where it is not 0), or nullptr
+hipError_t launch_pattern_table(const int32_t *indptr, const int32_t *indices, int32_t rows, int32_t words, uint2 *table, const int32_t *status,
+                                hipStream_t s);
 // D[i * ld + j] = values[p] for every stored entry p = (i, j); the rest of D is not touched (zero since allocation)
 hipError_t launch_dense_refresh(const int32_t *indptr, const int32_t *indices, const float *values, int32_t rows, float *D, int64_t ld,
                                 hipStream_t s);
