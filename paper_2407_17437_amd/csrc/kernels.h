@@ -95,6 +95,7 @@ struct SpmmArgs {
     int32_t x_rows;          // rows of the gathered operand (columns of the sparse matrix)
     int32_t batch;
     int32_t relu;            // clamp the result at zero
+    int32_t wide_offsets;    // an operand spans 4 GiB or more (set by the launch)
     int32_t nnz;             // length of indices/values
     float *scratch;          // partial rows of huge-row work-groups, (n_huge_blocks, scratch_ld)
     int64_t scratch_ld;

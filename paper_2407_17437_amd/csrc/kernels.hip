@@ -57,10 +57,9 @@ __device__ __forceinline__ void fma_into(float (&acc)[4], float w, float4 x)
 }
 
 // U consecutive stored entries starting at p: all index/weight fetches, then all gathers, then
-// the FMAs, so that U*NV reads are in flight per wave.
-template <int NV, bool XMASK, int U>
-__device__ __forceinline__ void spmm_step(const SpmmArgs &a, int p, uint32_t ldxb, uint32_t ldmb,
-                                          const uint32_t (&off)[NV], float (&acc)[NV][4])
+// the FMAs, so that U reads are in flight per wave.
+template <bool XMASK, int U>
+__device__ __forceinline__ void spmm_step(const SpmmArgs &a, int p, uint32_t ldxb, uint32_t ldmb, uint32_t off, float (&acc)[4])
 {
     int j[U];
     float w[U];
@@ -69,22 +68,14 @@ __device__ __forceinline__ void spmm_step(const SpmmArgs &a, int p, uint32_t ldx
         j[u] = a.indices[p + u];
         w[u] = a.values[p + u];
     }
-    float4 x[U][NV];
+    float4 x[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const gmem_ptr xr = row_base(a.X, j[u], ldxb);
-#pragma unroll
-        for (int t = 0; t < NV; ++t) x[u][t] = gload4(xr, off[t]);
-        if constexpr (XMASK) {
-            const gmem_ptr mr = row_base(a.XM, j[u], ldmb);
-#pragma unroll
-            for (int t = 0; t < NV; ++t) x[u][t] = keep_where_positive(x[u][t], gload4(mr, off[t]));
-        }
+        x[u] = gload4(row_base(a.X, j[u], ldxb), off);
+        if constexpr (XMASK) x[u] = keep_where_positive(x[u], gload4(row_base(a.XM, j[u], ldmb), off));
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int t = 0; t < NV; ++t) fma_into(acc[t], w[u], x[u][t]);
+    for (int u = 0; u < U; ++u) fma_into(acc, w[u], x[u]);
 }
 
 // Bias, ReLU and the optional output mask on the four columns from `col` on of one row, and their store.
@@ -103,33 +94,22 @@ __device__ __forceinline__ void spmm_store(const SpmmArgs &a, int row, int col, 
 }
 
 // ---------------------------------------------------------------------------------------
-// SpMM, 16-byte accesses.  A wave covers 64*4*NV columns; blockIdx.y walks over column tiles.
+// SpMM on 256 columns: a wave covers them with one 16-byte access per lane and entry.
 // ---------------------------------------------------------------------------------------
-template <int NV, bool XMASK>
-__device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, const int col_tile)
+template <bool XMASK>
+__device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, const int col0)
 {
-    constexpr int U = NV >= 4 ? 2 : (NV == 2 ? 4 : 8);
-    __shared__ float red[kWavesPerBlock][NV][4][kWave];
+    constexpr int U = 8;
+    __shared__ float red[kWavesPerBlock][4][kWave];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = wave_in_block();
     const WaveTask task = wave_task(a.blocks, block);
-    const int col_base = col_tile * (kWave * 4 * NV);
-
     // Lanes whose columns lie beyond the batch re-read the tile's first columns and are never stored.
-    int col[NV];
-    bool on[NV];
-    uint32_t off[NV];
-    float acc[NV][4];
-#pragma unroll
-    for (int t = 0; t < NV; ++t) {
-        col[t] = col_base + (t * kWave + lane) * 4;
-        on[t] = col[t] < a.batch;
-        col[t] = four_columns(on[t] ? col[t] : col_base, a.batch);
-        off[t] = static_cast<uint32_t>(col[t]) * 4u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[t][k] = 0.f;
-    }
+    const bool on = col0 + lane * 4 < a.batch;
+    const int col = four_columns(on ? col0 + lane * 4 : col0, a.batch);
+    const uint32_t off = static_cast<uint32_t>(col) * 4u;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
 
     if (task.row >= 0) {
         const uint32_t ldxb = static_cast<uint32_t>(a.ldx) * 4u;
@@ -137,43 +117,30 @@ __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, co
         int p = task.s0;
         const int pe = task.s1;
         // only entries of this wave's share are gathered: the gather stream is what the kernel pays for
-        for (; p + U <= pe; p += U) spmm_step<NV, XMASK, U>(a, p, ldxb, ldmb, off, acc);
-        if constexpr (U >= 8)
-            if (p + 4 <= pe) { spmm_step<NV, XMASK, 4>(a, p, ldxb, ldmb, off, acc); p += 4; }
-        if constexpr (U >= 4)
-            if (p + 2 <= pe) { spmm_step<NV, XMASK, 2>(a, p, ldxb, ldmb, off, acc); p += 2; }
-        if (p < pe) spmm_step<NV, XMASK, 1>(a, p, ldxb, ldmb, off, acc);
+        for (; p + U <= pe; p += U) spmm_step<XMASK, U>(a, p, ldxb, ldmb, off, acc);
+        if (p + 4 <= pe) { spmm_step<XMASK, 4>(a, p, ldxb, ldmb, off, acc); p += 4; }
+        if (p + 2 <= pe) { spmm_step<XMASK, 2>(a, p, ldxb, ldmb, off, acc); p += 2; }
+        if (p < pe) spmm_step<XMASK, 1>(a, p, ldxb, ldmb, off, acc);
     }
 
     if (task.lg > 0) {  // uniform over the work-group
         if (task.part != 0) {
 #pragma unroll
-            for (int t = 0; t < NV; ++t)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) red[wv][t][k][lane] = acc[t][k];
+            for (int k = 0; k < 4; ++k) red[wv][k][lane] = acc[k];
         }
         __syncthreads();
         if (task.part == 0) {
             for (int s = 1; s < (1 << task.lg); ++s)
 #pragma unroll
-                for (int t = 0; t < NV; ++t)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) acc[t][k] += red[wv + s][t][k][lane];
+                for (int k = 0; k < 4; ++k) acc[k] += red[wv + s][k][lane];
         }
     }
-    if (task.row < 0 || task.part != 0) return;
+    if (task.row < 0 || task.part != 0 || !on) return;
 
-    if (task.huge) {
-        // one share of a huge row: the raw partial sum goes to this work-group's scratch row
-        float *sr = a.scratch + static_cast<int64_t>(block) * a.scratch_ld;
-#pragma unroll
-        for (int t = 0; t < NV; ++t)
-            if (on[t]) st4(sr + col[t], make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]));
-        return;
-    }
-#pragma unroll
-    for (int t = 0; t < NV; ++t)
-        if (on[t]) spmm_store(a, task.row, col[t], acc[t]);
+    if (task.huge)  // one share of a huge row: the raw partial sum goes to this work-group's scratch row
+        st4(a.scratch + static_cast<int64_t>(block) * a.scratch_ld + col, make_float4(acc[0], acc[1], acc[2], acc[3]));
+    else
+        spmm_store(a, task.row, col, acc);
 }
 
 // One pass of U gather instructions of the grouped SpMM: every index move, then every gather,
@@ -431,10 +398,24 @@ __global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, co
     spmm_body_grouped<GS, XMASK>(a, rb, tile * GS * 4);
 }
 
-template <int NV, bool XMASK>
+// Wide batches: the columns in tiles of 256, a work-group of the row partition each -- more, shorter work-groups than one
+// wave carrying up to 1024 columns of its entries (power-law 2957 x 948 at batch 585: 22.4 us, 12.4 in tiles; 1024 x 600 at
+// batch 1024: 19.3, 10.0; even rows the same) -- and what is left of the batch in the kernels for as few columns.
+template <bool XMASK>
+__device__ __forceinline__ void spmm_wide_body(const SpmmArgs &a, const int block, const int col0)
+{
+    const int left = a.batch - col0;
+    if (left > 128 || a.wide_offsets)
+        spmm_body<XMASK>(a, block, col0);
+    else if (left > 64)
+        spmm_body_grouped<32, XMASK>(a, block, col0);
+    else
+        spmm_body_grouped<16, XMASK>(a, block, col0);
+}
+template <bool XMASK>
 __global__ __launch_bounds__(kBlock) void spmm_kernel(const SpmmArgs a)
 {
-    spmm_body<NV, XMASK>(a, blockIdx.x, blockIdx.y);
+    spmm_wide_body<XMASK>(a, blockIdx.x, blockIdx.y * 256);
 }
 
 // SpMM for batches of at most 4 columns (inference on one or a few examples): there is no batch
@@ -1647,14 +1628,14 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
 
 // Two independent launches of a training step in one grid: work-groups [0, na) run the first,
 // the rest the second.  Saves a launch (and its drain) on the step's critical path.
-template <int GS_S, int NV_S, int G, int NV_D>
+template <int GS_S, int G, int NV_D>
 __global__ __launch_bounds__(kBlock) void spmm_sddmm_pair_kernel(const SpmmArgs a, const SddmmArgs b, const int na)
 {
     if (static_cast<int>(blockIdx.x) < na) {
         if constexpr (GS_S < kWave)
             spmm_body_grouped<GS_S, false>(a, blockIdx.x);
         else
-            spmm_body<NV_S, false>(a, blockIdx.x, 0);
+            spmm_wide_body<false>(a, blockIdx.x % a.blocks.n_blocks, blockIdx.x / a.blocks.n_blocks * 256);
     } else {
         sddmm_body<G, NV_D>(b, blockIdx.x - na);
     }
@@ -2046,15 +2027,16 @@ inline int elementwise_blocks(int64_t work_items)
     return static_cast<int>(b);
 }
 
-template <int NV>
-hipError_t spmm_go(const SpmmArgs &a, hipStream_t s)
+bool spmm_offsets_ok(const SpmmArgs &a);
+
+hipError_t spmm_go(SpmmArgs a, hipStream_t s)
 {
-    const int tile = kWave * 4 * NV;
-    dim3 grid(a.blocks.n_blocks, (a.batch + tile - 1) / tile);
+    a.wide_offsets = !spmm_offsets_ok(a);
+    dim3 grid(a.blocks.n_blocks, (a.batch + 255) / 256);
     if (a.XM)
-        hipLaunchKernelGGL((spmm_kernel<NV, true>), grid, dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(spmm_kernel<true>, grid, dim3(kBlock), 0, s, a);
     else
-        hipLaunchKernelGGL((spmm_kernel<NV, false>), grid, dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(spmm_kernel<false>, grid, dim3(kBlock), 0, s, a);
     if (a.blocks.n_huge_rows > 0)
         hipLaunchKernelGGL(spmm_finish_kernel, dim3(a.blocks.n_huge_rows, (a.batch + 255) / 256), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -2182,7 +2164,6 @@ bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t
 }
 
 int spmm_tile_group(const SpmmArgs &a);
-bool spmm_offsets_ok(const SpmmArgs &a);
 constexpr int64_t kSplitMinOperand = 48ll << 20;  // operand bytes from which long rows go into column tiles of their own: beyond the eight L2s
 
 // Lanes per row (4 columns each) of the column tiles in which the LONG rows of a matrix run while its short rows run
@@ -2262,12 +2243,12 @@ bool sddmm_offsets_ok(const SddmmArgs &a)
     return a.batch >= 4 && (a.skip_products || spans_below_4gib(a.x_rows, a.ldx));
 }
 
-template <int GS_S, int NV_S, int G, int NV_D>
+template <int GS_S, int G, int NV_D>
 hipError_t pair_go(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
 {
-    const int na = a.blocks.n_blocks;
+    const int na = a.blocks.n_blocks * (GS_S == kWave ? (a.batch + 255) / 256 : 1);
     dim3 grid(na + b.blocks.n_blocks);
-    hipLaunchKernelGGL((spmm_sddmm_pair_kernel<GS_S, NV_S, G, NV_D>), grid, dim3(kBlock), 0, s, a, b, na);
+    hipLaunchKernelGGL((spmm_sddmm_pair_kernel<GS_S, G, NV_D>), grid, dim3(kBlock), 0, s, a, b, na);
     if (a.blocks.n_huge_rows > 0)
         hipLaunchKernelGGL(spmm_finish_kernel, dim3(a.blocks.n_huge_rows, (a.batch + 255) / 256), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -2347,11 +2328,11 @@ bool can_pair(const SddmmArgs &a, const SddmmArgs &b)
 
 hipError_t launch_pair(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
 {
-    if (a.batch <= 64) return pair_go<16, 1, 16, 1>(a, b, s);
-    if (a.batch <= 128) return pair_go<32, 1, 16, 2>(a, b, s);
-    if (a.batch <= 256) return pair_go<64, 1, 16, 4>(a, b, s);
-    if (a.batch <= 512) return pair_go<64, 2, 64, 2>(a, b, s);
-    return pair_go<64, 4, 64, 4>(a, b, s);
+    if (a.batch <= 64) return pair_go<16, 16, 1>(a, b, s);
+    if (a.batch <= 128) return pair_go<32, 16, 2>(a, b, s);
+    if (a.batch <= 256) return pair_go<64, 16, 4>(a, b, s);
+    if (a.batch <= 512) return pair_go<64, 64, 2>(a, b, s);
+    return pair_go<64, 64, 4>(a, b, s);
 }
 
 hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
@@ -2539,9 +2520,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         if (a.batch <= 64) return spmm_grouped_go<16>(a, s);
         if (a.batch <= 128) return spmm_grouped_go<32>(a, s);
     }
-    if (a.batch <= 256) return spmm_go<1>(a, s);
-    if (a.batch <= 512) return spmm_go<2>(a, s);
-    return spmm_go<4>(a, s);
+    return spmm_go(a, s);
 }
 
 // Columns per tile of the column-tiled SDDMM, 0: one pass over the whole batch.
