@@ -94,6 +94,11 @@ struct PatternBuffers {
     int32_t *table = nullptr;       // pattern table, 2 ints per row and 32 columns
     size_t table_ints = 0;
     bool has_table = false;         // it holds the pattern (else the layer is too sparse for it)
+    int32_t *row_table = nullptr;   // the same of the dense rows alone (DenseRows)
+    size_t row_table_ints = 0;
+    float *row_partial = nullptr;   // sliced results of their product
+    size_t row_partial_floats = 0;
+    DenseSplit split{};             // views into plan_mem and row_table
 };
 
 struct nerva_layer {
@@ -485,10 +490,14 @@ void fill_staged_ends_host(StagedPlan &H, const int32_t *indptr, const int32_t *
 // Sizes of the tables of one orientation, from bounds that hold for every pattern with these row and entry counts:
 // the tables are laid out before the planner, which runs on the device, has counted anything.
 struct PlanRoom {
-    int64_t blocks, long_blocks, rest_blocks, huge_rows, short_rows;
+    int64_t blocks, long_blocks, rest_blocks, huge_rows, short_rows, dense_rows = 0, dense_flags = 0;
     int32_t ranges, cblocks;
-    PlanRoom(int32_t rows, int32_t other, int64_t nnz, int32_t max_batch)
+    PlanRoom(int32_t rows, int32_t other, int64_t nnz, int32_t max_batch, int32_t dense_len = INT32_MAX)
     {
+        if (dense_len < INT32_MAX) {
+            dense_rows = round_up(std::min<int64_t>(rows, nnz / dense_len), 4);
+            dense_flags = round_up(rows, 16) / 4;
+        }
         const int64_t target = std::min<int64_t>(std::max<int64_t>(nnz / 4096, 8), 64);
         const int64_t cap = std::min<int64_t>(std::max<int64_t>(nnz / 16384, 8), 64) * kWavesPerBlock;
         // a row's waves number 1 or fewer than 2 * entries / target; a class ends in a work-group that may not be full
@@ -506,7 +515,8 @@ struct PlanRoom {
     size_t ints() const
     {
         return static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks + rest_blocks) + huge_rows + short_rows)) +
-               static_cast<size_t>(ranges) * (kStageRangeRows * (cblocks + 2) + 4);
+               static_cast<size_t>(ranges) * (kStageRangeRows * (cblocks + 2) + 4) + static_cast<size_t>(dense_rows + dense_flags) +
+               (dense_flags ? static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks) + huge_rows)) : 0);
     }
     // the tables at `mem` (16-byte records first)
     PlanTables at(int32_t *mem) const
@@ -518,7 +528,15 @@ struct PlanRoom {
         t.rest_waves = r; r += kWavesPerBlock * rest_blocks;
         t.huge_rows = r; r += huge_rows;
         t.short_rows = r; r += short_rows;
+        t.other_waves = t.other_long_waves = t.other_huge_rows = nullptr;
+        if (dense_flags) {
+            t.other_waves = r; r += kWavesPerBlock * blocks;
+            t.other_long_waves = r; r += kWavesPerBlock * long_blocks;
+            t.other_huge_rows = r; r += huge_rows;
+        }
         int32_t *i = reinterpret_cast<int32_t *>(r);
+        t.dense_rows = i; i += dense_rows;
+        t.dense_flag = reinterpret_cast<uint8_t *>(i); i += dense_flags;
         t.staged_rows = i; i += static_cast<size_t>(ranges) * kStageRangeRows;
         t.staged_ends = i; i += static_cast<size_t>(ranges) * kStageRangeRows * (cblocks + 1);
         t.staged_groups = i;
@@ -554,6 +572,8 @@ void free_pattern_buffers(PatternBuffers &b)
     (void)hipFree(b.mirror_mem);
     (void)hipFree(b.plan_mem);
     (void)hipFree(b.table);
+    (void)hipFree(b.row_table);
+    (void)hipFree(b.row_partial);
     b = PatternBuffers{};
 }
 
@@ -724,7 +744,7 @@ static hipError_t build_dense_copies(nerva_layer *l, hipStream_t s)
     if (e == hipSuccess && !l->cur.has_table) {
         e = reserve(&l->cur.table, &l->cur.table_ints, static_cast<size_t>(l->rows) * table_words(l) * 2);
         if (e == hipSuccess)
-            e = launch_pattern_table(l->indptr, l->indices, l->rows, table_words(l), reinterpret_cast<uint2 *>(l->cur.table), nullptr, s);
+            e = launch_pattern_table(l->indptr, l->indices, nullptr, l->rows, table_words(l), reinterpret_cast<uint2 *>(l->cur.table), nullptr, s);
         if (e == hipSuccess) l->cur.has_table = true;
     }
     if (e == hipSuccess) e = hipMemsetAsync(l->dense, 0, bytes, s);
@@ -759,8 +779,17 @@ static hipError_t dense_transposed(const nerva_layer *l, const float *dZ, int64_
 
 static int enable_dense(nerva_layer *layer, hipStream_t s);
 
+// whether a layer is, or with `nnz` entries is going to be, on the dense route
+static bool takes_dense_route(const nerva_layer *l, int32_t nnz)
+{
+    return l->dense_on || (dense_shape_ok(l->rows, l->cols) &&
+                           static_cast<double>(nnz) >= static_cast<double>(g_dense_threshold.load()) * l->rows * l->cols);
+}
+
 // the dense route needs a batch wide enough to fill its 16-column tiles
 static bool use_dense(const nerva_layer *l, int32_t batch) { return l->dense_on && batch >= 16; }
+
+static const DenseSplit *split_of(const nerva_layer *l) { return l->cur.split.rows.n > 0 ? &l->cur.split : nullptr; }
 
 // Message for the status word of the device-side CSR check (bind_check_kernel).
 static int csr_status_error(const int32_t *st)
@@ -801,7 +830,11 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     size_t indptr_t_have = B.indptr_t ? static_cast<size_t>(cols) + 1 : 0;
     HIP_TRY(reserve(&B.indptr_t, &indptr_t_have, static_cast<size_t>(cols) + 1));
     HIP_TRY(reserve(&B.mirror_mem, &B.mirror_ints, 4 * n64));
-    const PlanRoom room(rows, cols, nnz, max_batch), room_t(cols, rows, nnz, max_batch);
+    // rows long enough for matrix instructions are looked for unless the layer takes the dense route as a whole
+    const bool seek_dense = mode == NERVA_PARTITION_BALANCED && cols >= kDenseRowsMinCols && max_batch >= kDenseRowsMinBatch && nnz < (1 << 30) &&
+                            !takes_dense_route(l, nnz);
+    const int32_t dense_len = seek_dense ? dense_row_length(cols) : INT32_MAX;
+    const PlanRoom room(rows, cols, nnz, max_batch, dense_len), room_t(cols, rows, nnz, max_batch);
     const size_t plan_ints = static_cast<size_t>(round_up(static_cast<int64_t>(room.ints()), 64));
     HIP_TRY(reserve(&B.plan_mem, &B.plan_ints, plan_ints + room_t.ints()));
     if (!l->bind_result) HIP_TRY(hipHostMalloc(&l->bind_result, sizeof(BindResult), hipHostMallocDefault));
@@ -832,6 +865,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     for (int k = 0; k < 2; ++k) {
         PlanSide &side = p.side[k];
         side.rows = side_rows[k]; side.other = side_rows[1 - k]; side.range_bound = side_ranges[k];
+        side.dense_len = k == 0 ? dense_len : INT32_MAX;
         side.indptr = k == 0 ? indptr : B.indptr_t; side.indices = k == 0 ? indices : m.indices_t;
         side.tables = k == 0 ? room.at(B.plan_mem) : room_t.at(B.plan_mem + plan_ints);
         int32_t *w = W + work_at[k];
@@ -843,12 +877,30 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     B.has_table = l->dense_on || static_cast<double>(nnz) >= static_cast<double>(kTableFromDensity) * rows * cols;
     if (B.has_table) {
         HIP_TRY(reserve(&B.table, &B.table_ints, static_cast<size_t>(rows) * table_words(l) * 2));
-        HIP_TRY(launch_pattern_table(indptr, indices, rows, table_words(l), reinterpret_cast<uint2 *>(B.table), m.status, s));
+        HIP_TRY(launch_pattern_table(indptr, indices, nullptr, rows, table_words(l), reinterpret_cast<uint2 *>(B.table), m.status, s));
     }
     HIP_TRY(hipStreamSynchronize(s));
     const BindResult &R = *l->bind_result;
     if (R.status[0] != 0) return csr_status_error(R.status);
     out->plan = plan_view(p.side[0].tables, R.plan[0], cols, nnz, R.plan[1].hot_nnz, mode);
+    B.split = DenseSplit{};
+    if (R.plan[0].n_dense > 0) {
+        const PlanTables &t = p.side[0].tables;
+        DenseRows &D = B.split.rows;
+        D.list = t.dense_rows; D.n = R.plan[0].n_dense; D.words = table_words(l);
+        HIP_TRY(reserve(&B.row_table, &B.row_table_ints, static_cast<size_t>(D.n) * D.words * 2));
+        D.table = reinterpret_cast<const uint2 *>(B.row_table);
+        D.partial_floats = dense_rows_partial(D.n, cols, max_batch);
+        if (D.partial_floats > 0) HIP_TRY(reserve(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(D.partial_floats)));
+        D.partial = B.row_partial;
+        B.split.flag = t.dense_flag;
+        B.split.others = out->plan;
+        B.split.others.waves = t.other_waves;
+        B.split.others.long_waves = t.other_long_waves;
+        B.split.others.huge_rows = t.other_huge_rows;
+        out->plan.staged_rows = nullptr;   // (it covers the other rows only)
+        HIP_TRY(launch_pattern_table(indptr, indices, D.list, D.n, D.words, reinterpret_cast<uint2 *>(B.row_table), nullptr, s));
+    }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
 
     // scratch buffers of the products (they hold nothing between calls: grown in place)
@@ -856,7 +908,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         // room for the column-tiled SDDMM at max_batch columns, if that batch would be tiled
         const int w = tile_columns(cols, max_batch, nnz, rows, out->plan.hot_share, false, true);
         int32_t tiles = w > 0 ? (max_batch + w - 1) / w : 0;
-        if (out->plan.staged_rows && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
+        if ((out->plan.staged_rows || B.split.others.staged_rows) && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
         // ... and for the backward pass on one gather stream (products in mirror order, one slice per tile of the
         // transposed product), which runs where every row of the mirror is short
         if (out->plan_t.n_short == cols && out->plan_t.n_long_blocks == 0) {
@@ -933,7 +985,7 @@ int sparse_linear_create(nerva_layer **out, int32_t rows, int32_t cols, int32_t 
     }
     adopt_pattern(l, nnz, indptr, indices, values, bp);
     // the density-adaptive choice: dense products where the pattern is dense enough for them to be the faster ones
-    if (dense_shape_ok(rows, cols) && static_cast<double>(nnz) >= static_cast<double>(g_dense_threshold.load()) * rows * cols) {
+    if (takes_dense_route(l, nnz)) {
         const int rd = enable_dense(l, as_stream(stream));
         if (rd != NERVA_OK) {
             free_layer_buffers(l);
@@ -956,8 +1008,7 @@ int sparse_linear_rebind(nerva_layer *layer, int32_t nnz, const int32_t *indptr,
     const int rc = build_structures(layer, nnz, indptr, indices, values, &bp, s);
     if (rc != NERVA_OK) return rc;  // the layer keeps its old pattern: only the spare set and scratch buffers were written
     adopt_pattern(layer, nnz, indptr, indices, values, bp);
-    if (!layer->dense_on && dense_shape_ok(layer->rows, layer->cols) &&
-        static_cast<double>(nnz) >= static_cast<double>(g_dense_threshold.load()) * layer->rows * layer->cols)
+    if (!layer->dense_on && takes_dense_route(layer, nnz))
         return enable_dense(layer, s);   // (a pattern that has grown dense; a route once taken is kept)
     if (layer->dense_on) {
         // the dense copies hold the old pattern's entries: cleared and filled again
@@ -1046,6 +1097,7 @@ int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx,
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
     a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.relu = layer->activation == NERVA_ACT_RELU;
     a.full_scratch = layer->full ? layer->full_scratch : nullptr; a.full_scratch_ld = layer->full_scratch_ld;
+    a.split = split_of(layer);
     HIP_TRY(launch_spmm(a, as_stream(stream)));
     return NERVA_OK;
 }
@@ -1102,6 +1154,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
         a.partial_db_at = layer->partial_db_at; a.partial_tiles = layer->partial_tiles;
         a.skip_products = dvalues ? 0 : 1;  // only the bias gradient is wanted
         if (layer->cur.has_table) { a.table = reinterpret_cast<const uint2 *>(layer->cur.table); a.table_words = table_words(layer); }
+        a.split = split_of(layer);
         HIP_TRY(launch_sddmm(a, s));
     }
     return NERVA_OK;
@@ -1292,6 +1345,7 @@ static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldi
     a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
     a.rows = ly->rows; a.x_rows = ly->cols; a.batch = batch; a.relu = ly->activation == NERVA_ACT_RELU;
     a.full_scratch = ly->full ? ly->full_scratch : nullptr; a.full_scratch_ld = ly->full_scratch_ld;
+    a.split = split_of(ly);
     return a;
 }
 
@@ -1410,6 +1464,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         g.partial = ly->partial; g.partial_stride = ly->partial_stride;
         g.partial_db_at = ly->partial_db_at; g.partial_tiles = ly->partial_tiles;
         if (ly->cur.has_table) { g.table = reinterpret_cast<const uint2 *>(ly->cur.table); g.table_words = table_words(ly); }
+        g.split = split_of(ly);
         if ((head || ce_fused) && l == n - 1 && loss_out) { g.loss_cols = mlp->head_scratch; g.loss_out = loss_out; g.loss_n = batch; }
         if (fused) {
             g.fused = 1; g.nesterov = nesterov; g.lr = lr; g.momentum = momentum;

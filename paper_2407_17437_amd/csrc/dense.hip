@@ -18,6 +18,8 @@
 #include "device.h"
 #include "kernels.h"
 
+#include <algorithm>
+
 namespace nerva {
 namespace {
 
@@ -288,7 +290,8 @@ __global__ __launch_bounds__(kSampledWaves * kWave) void sampled_update_kernel(c
     uint32_t z_row[4], x_row[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        z_row[u] = static_cast<uint32_t>(min(ib + sr + 16 * u, L.rows - 1)) * (static_cast<uint32_t>(L.lddz) * 4u);
+        const int zi = min(ib + sr + 16 * u, L.rows - 1);
+        z_row[u] = static_cast<uint32_t>(L.list ? L.list[zi] : zi) * (static_cast<uint32_t>(L.lddz) * 4u);
         x_row[u] = static_cast<uint32_t>(min(jb + sr + 16 * u, L.cols - 1)) * (static_cast<uint32_t>(L.ldx) * 4u);
     }
     auto fetch = [&](int kb) {
@@ -405,8 +408,9 @@ __global__ __launch_bounds__(kSampledWaves * kWave) void sampled_update_kernel(c
             float s = row_sum[m];
             s += __shfl_xor(s, 16, kWave);
             s += __shfl_xor(s, 32, kWave);
-            const int i = ib + wi + 16 * m + r;
+            int i = ib + wi + 16 * m + r;
             if (q == 0 && i < L.rows) {
+                if (L.list) i = L.list[i];
                 if (L.db) L.db[i] = s;
                 if (L.fused && L.bias) {
                     float bw = L.bias[i], bv = L.bias_velocity[i];
@@ -476,15 +480,203 @@ __global__ __launch_bounds__(kSampledWaves * kWave) void sampled_update_kernel(c
     }
 }
 
+// ---- dense rows ----------------------------------------------------------------------------------
+// Y[i, :] = act(W[i, :] X + b[i]) for the rows of a sparse matrix that store an eighth of their columns or more (the heads
+// of power-law matrices; evenly filled matrices of 30 to 40 %): an MFMA product whose left operand is made dense on the
+// way into LDS.  A work-group of 4 waves owns 64 of the listed rows and 32 T columns of the batch; 64 columns of the matrix
+// at a time, a wave places the entries of 16 rows, a lane per column: the pattern table says whether there is one and where
+// (a row's entries are a run of values[]), the others are 0.  The operand's 64 rows come through LDS as well.  Both travel
+// a step ahead, the table two.  K is cut into slices where the tiles do not fill the chip; dense_rows_finish_kernel adds them in
+// slice order.  A step whose operand holds an Inf or NaN goes entry by entry, so that only rows that store the entry see it.
+// What bounds it: the MFMA pipes, 4096 cycles of a step of T = 4.  Measured on 16384^2 power-law rows at 10 %, batch 1024:
+// the 2611 dense rows (69 % of the entries) take 800 us (110 TFLOP/s), the others 1021 in the staged kernel, which took
+// 3320 for all; at 3 %: 1787 -> 735.
+constexpr int kDrRows = 64, kDrK = 64, kDrALd = kDrK + 4;
+
+__host__ __device__ __forceinline__ int64_t dense_rows_ld(int32_t batch) { return (batch + 31) / 32 * 32; }
+
+__device__ __forceinline__ void dense_rows_store(const SpmmArgs &a, int row, int col, float4 y)
+{
+    const float b = a.bias ? a.bias[row] : 0.f;
+    y = make_float4(y.x + b, y.y + b, y.z + b, y.w + b);
+    if (a.relu) y = make_float4(y.x > 0.f ? y.x : 0.f, y.y > 0.f ? y.y : 0.f, y.z > 0.f ? y.z : 0.f, y.w > 0.f ? y.w : 0.f);
+    if (a.YM) y = keep_where_positive(y, ld4(a.YM + static_cast<int64_t>(row) * a.ldym + col));
+    st4(a.Y + static_cast<int64_t>(row) * a.ldy + col, y);
+}
+
+template <int T>
+__global__ __launch_bounds__(kDenseBlock) __attribute__((amdgpu_waves_per_eu(3))) void dense_rows_kernel(const SpmmArgs a, const DenseRows D,
+                                                                                                             const int slices)
+{
+    constexpr int kCols = 32 * T, kQuads = kCols / 4, kRound = kDenseBlock / kQuads;   // operand rows the work-group brings at a time
+    __shared__ float as[kDrRows][kDrALd];
+    __shared__ float xs[kDrK][kCols + (T == 4 ? 4 : 8)];   // (rows that lanes read together start in different banks)
+    __shared__ uint2 tab[2][kDrRows][2];
+    __shared__ int4 odd_wave;   // per wave: it has brought an operand that is not finite
+    const int lane = threadIdx.x & (kWave - 1), wv = wave_id(), tid = threadIdx.x;
+    const int r = lane & 15, q = lane >> 4;
+    const int row_tiles = (D.n + kDrRows - 1) / kDrRows;
+    // consecutive work-groups share the slice of the operand: row tiles run fastest
+    const int row_tile = blockIdx.x % row_tiles, rest = blockIdx.x / row_tiles, slice = rest % slices, n0 = rest / slices * kCols;
+    const int ib = row_tile * kDrRows, wi = (wv >> 1) * 32, wj = (wv & 1) * 16 * T;
+    const int chunks = (a.x_rows + kDrK - 1) / kDrK, per = (chunks + slices - 1) / slices;
+    const int c_begin = min(slice * per, chunks), c_end = min(c_begin + per, chunks);
+    const gmem_ptr X = as_gmem(a.X), values = as_gmem(a.values);
+    const uint32_t last = static_cast<uint32_t>(a.nnz - 1) * 4u, ldxb = static_cast<uint32_t>(a.ldx) * 4u;
+
+    uint2 tab_next;
+    auto load_table = [&](int c) {  // threads 0 .. 127: row tid / 2, word tid & 1 of chunk c
+        const int word = c * 2 + (tid & 1), i = min(ib + ((tid >> 1) & 63), D.n - 1);
+        tab_next = D.table[static_cast<int64_t>(i) * D.words + min(word, D.words - 1)];
+        if (word >= D.words || c >= c_end) tab_next.x = 0;
+    };
+    auto keep_table = [&](int buf) { if (tid < 2 * kDrRows) tab[buf][tid >> 1][tid & 1] = tab_next; };
+    float av[16];
+    uint32_t set = 0;
+    float4 xv[kDrK / kRound];
+    const int xr = tid / kQuads, xq = tid % kQuads;
+    const int own = n0 + xq * 4, xcol = four_columns(own < a.batch ? own : n0, a.batch);
+    auto fetch = [&](int c, int buf) {
+        set = 0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const uint2 t = tab[buf][wv * 16 + u][lane >> 5];
+            const uint32_t bit = 1u << (lane & 31);
+            set |= t.x & bit ? 1u << u : 0u;
+            av[u] = gload1(values, min((t.y + static_cast<uint32_t>(__popc(t.x & (bit - 1u)))) * 4u, last));
+        }
+#pragma unroll
+        for (int u = 0; u < kDrK / kRound; ++u) {
+            const int k = min(c * kDrK + xr + kRound * u, a.x_rows - 1);
+            xv[u] = gload4(X, static_cast<uint32_t>(k) * ldxb + static_cast<uint32_t>(xcol) * 4u);
+        }
+    };
+    v4f acc[2][T];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[m][t] = v4f{0.f, 0.f, 0.f, 0.f};
+    load_table(c_begin);
+    keep_table(0);
+    __syncthreads();
+    if (c_begin < c_end) fetch(c_begin, 0);
+    load_table(c_begin + 1);
+    for (int c = c_begin; c < c_end; ++c) {
+        const int next = (c + 1 - c_begin) & 1;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 16; ++u) as[wv * 16 + u][lane] = set & (1u << u) ? av[u] : 0.f;
+#pragma unroll
+        for (int u = 0; u < kDrK / kRound; ++u) *reinterpret_cast<float4 *>(&xs[xr + kRound * u][xq * 4]) = xv[u];
+        float zero = 0.f;
+#pragma unroll
+        for (int u = 0; u < kDrK / kRound; ++u) zero = fmaf(xv[u].x, 0.f, fmaf(xv[u].y, 0.f, fmaf(xv[u].z, 0.f, fmaf(xv[u].w, 0.f, zero))));
+        const bool odd_here = __any(!(zero == 0.f));
+        if (lane == 0) reinterpret_cast<int *>(&odd_wave)[wv] = odd_here;
+        keep_table(next);
+        __syncthreads();
+        const int4 odd4 = odd_wave;
+        const bool odd = __builtin_amdgcn_readfirstlane(odd4.x | odd4.y | odd4.z | odd4.w);
+        if (c + 1 < c_end) {
+            fetch(c + 1, next);
+            load_table(c + 2);
+        }
+        if (odd) {  // an entry that is not stored must not meet an Inf or NaN with its 0: entry by entry
+            for (int k = 0; k < kDrK; ++k) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int i = wi + 16 * m + 4 * q + g;
+                        const bool stored = (tab[1 - next][i][k >> 5].x >> (k & 31)) & 1u;
+                        const float w = as[i][k];
+#pragma unroll
+                        for (int t = 0; t < T; ++t) acc[m][t][g] = stored ? fmaf(w, xs[k][wj + T * r + t], acc[m][t][g]) : acc[m][t][g];
+                    }
+            }
+            continue;
+        }
+#pragma unroll
+        for (int d = 0; d < kDrK / 16; ++d) {
+            float4 f[2];
+            float x[4][T];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) f[m] = *reinterpret_cast<const float4 *>(&as[wi + 16 * m + r][16 * d + 4 * q]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float *p = &xs[16 * d + 4 * q + s][wj + T * r];   // (tile t holds the columns wj + T r + t)
+                if constexpr (T == 4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(p);
+                    x[s][0] = v.x; x[s][1] = v.y; x[s][2] = v.z; x[s][3] = v.w;
+                } else {
+                    const float2 v = *reinterpret_cast<const float2 *>(p);
+                    x[s][0] = v.x; x[s][1] = v.y;
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const float fs = s == 0 ? f[m].x : s == 1 ? f[m].y : s == 2 ? f[m].z : f[m].w;
+#pragma unroll
+                    for (int t = 0; t < T; ++t) acc[m][t] = mfma(fs, x[s][t], acc[m][t]);
+                }
+        }
+    }
+    // A lane stores four columns at a time: with T = 2 it has two of them, and of a pair of lanes the even one takes all
+    // four of its row of the first 16, the odd one of the other 16.
+    auto store = [&](int k, int own_out, float4 y) {
+        if (k >= D.n || own_out >= a.batch) return;
+        const int col = four_columns(own_out, a.batch);
+        if (slices > 1)
+            st4(D.partial + (static_cast<int64_t>(slice) * D.n + k) * dense_rows_ld(a.batch) + col, y);
+        else
+            dense_rows_store(a, D.list[k], col, y);
+    };
+    if constexpr (T == 4) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                store(ib + wi + 16 * m + 4 * q + g, n0 + wj + 4 * r, make_float4(acc[m][0][g], acc[m][1][g], acc[m][2][g], acc[m][3][g]));
+    } else {
+        const bool odd = r & 1;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float give0 = odd ? acc[0][0][g] : acc[1][0][g], give1 = odd ? acc[0][1][g] : acc[1][1][g];
+            const float got0 = __shfl_xor(give0, 1, kWave), got1 = __shfl_xor(give1, 1, kWave);
+            const float4 y = odd ? make_float4(got0, got1, acc[1][0][g], acc[1][1][g]) : make_float4(acc[0][0][g], acc[0][1][g], got0, got1);
+            store(ib + wi + (odd ? 16 : 0) + 4 * q + g, n0 + wj + 4 * (r >> 1), y);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kDenseBlock) void dense_rows_finish_kernel(const SpmmArgs a, const DenseRows D, const int slices)
+{
+    const int quads = (a.batch + 3) / 4;
+    const int64_t n = static_cast<int64_t>(D.n) * quads, ld = dense_rows_ld(a.batch), step = D.n * ld;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kDenseBlock + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * kDenseBlock) {
+        const int64_t k = i / quads;
+        const int col = four_columns(static_cast<int>(i - k * quads) * 4, a.batch);
+        const float *p = D.partial + k * ld + col;
+        float4 y = ld4(p);
+        for (int q = 1; q < slices; ++q) {
+            const float4 v = ld4(p + q * step);
+            y.x += v.x; y.y += v.y; y.z += v.z; y.w += v.w;
+        }
+        dense_rows_store(a, D.list[k], col, y);
+    }
+}
+
 // The pattern table: a thread per 32 columns of a row finds the row's first entry among them and collects their bits.
 __global__ __launch_bounds__(kDenseBlock) void pattern_table_kernel(const int32_t *__restrict__ indptr, const int32_t *__restrict__ indices,
-                                                                   int rows, int words, uint2 *__restrict__ table, const int32_t *status)
+                                                                   const int32_t *__restrict__ list, int rows, int words, uint2 *__restrict__ table, const int32_t *status)
 {
     if (status && status[0] != 0) return;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kDenseBlock, n = static_cast<int64_t>(rows) * words;
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * kDenseBlock + threadIdx.x; k < n; k += stride) {
-        const int row = static_cast<int>(k / words);
-        const int64_t j0 = (k - static_cast<int64_t>(row) * words) * 32;
+        const int at = static_cast<int>(k / words), row = list ? list[at] : at;
+        const int64_t j0 = (k - static_cast<int64_t>(at) * words) * 32;
         int32_t lo = indptr[row], hi = indptr[row + 1];
         const int32_t end = hi;
         while (lo < hi) {
@@ -552,12 +744,15 @@ hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-bool sddmm_sampled_possible(const SddmmArgs &a)
+// what the sampled kernel asks of a layer's arrays: 32-bit byte offsets
+bool sampled_operands_ok(const SddmmArgs &a)
 {
-    return a.table && a.nnz > 0 && a.nnz < (1 << 30) && a.batch >= kSampledMinBatch && !a.ZM && !a.skip_products &&
+    return a.nnz > 0 && a.nnz < (1 << 30) && a.batch >= kSampledMinBatch && !a.ZM && !a.skip_products &&
            static_cast<int64_t>(a.rows) * a.lddz < (1 << 30) && static_cast<int64_t>(a.x_rows) * a.ldx < (1 << 30) &&
-           (!a.dense || static_cast<int64_t>(a.rows) * a.dense_ld < (1 << 30));   // (32-bit byte offsets)
+           (!a.dense || static_cast<int64_t>(a.rows) * a.dense_ld < (1 << 30));
 }
+
+bool sddmm_sampled_possible(const SddmmArgs &a) { return a.table && sampled_operands_ok(a); }
 
 bool sddmm_sampled_ok(const SddmmArgs &a)
 {
@@ -568,6 +763,77 @@ bool sddmm_sampled_ok(const SddmmArgs &a)
     const int64_t tiles = static_cast<int64_t>((a.rows + 63) / 64) * ((a.x_rows + 63) / 64);
     const double from = tiles >= 512 ? kTableFromDensity : 2.3 * kTableFromDensity;
     return a.dense || static_cast<double>(a.nnz) >= from * a.rows * a.x_rows;
+}
+
+// How a product of n dense rows is cut: columns of the batch per work-group, slices of K.
+struct DenseRowsCut {
+    int cols, slices;
+    int64_t tiles;
+};
+// The cheapest by an estimate: a compute unit holds 3 (4) work-groups of 128 (64) columns, which take 2.0 (1.1) us a step
+// each when they keep its pipes busy together and 3.7 (2.6) alone; the slices' results go out and come back at 3.3 TB/s.
+// (Within 3 to 7 % of the best of 20 cuts on matrices of 1024 to 16384 rows at batches of 128 to 1024.)
+static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch)
+{
+    const int64_t chunks = (static_cast<int64_t>(cols) + kDrK - 1) / kDrK;
+    DenseRowsCut best{};
+    double best_time = 0.;
+    for (int wide = 1; wide >= 0; --wide) {
+        const int tile_cols = wide ? 128 : 64, fit = wide ? 3 : 4;
+        const double alone = wide ? 3.7 : 2.6, step = wide ? 2. : 1.1;
+        const int64_t tiles = static_cast<int64_t>((n + kDrRows - 1) / kDrRows) * ((batch + tile_cols - 1) / tile_cols);
+        for (int s = 1; s == 1 || (s <= 64 && s * 2 <= chunks); ++s) {
+            const int64_t per_unit = (tiles * s + 255) / 256, full = per_unit / fit, left = per_unit % fit;
+            const double rounds = full * std::max(alone, step * fit) + (left ? std::max(alone, step * left) : 0.);
+            const double time = rounds * static_cast<double>((chunks + s - 1) / s) + (s > 1 ? 2. + 1.2e-6 * s * n * static_cast<double>(dense_rows_ld(batch)) : 0.);
+            if (best.tiles == 0 || time < best_time) {
+                best = DenseRowsCut{tile_cols, s, tiles};
+                best_time = time;
+            }
+        }
+    }
+    return best;
+}
+
+bool dense_rows_ok(const DenseSplit *d, int32_t batch) { return d && d->rows.n > 0 && batch >= kDenseRowsMinBatch; }
+
+int64_t dense_rows_partial(int32_t n, int32_t cols, int32_t max_batch)
+{
+    int64_t most = 0;
+    for (int64_t c = 64; c - 64 < max_batch; c += 64) {
+        const int32_t batch = static_cast<int32_t>(c < max_batch ? c : max_batch);
+        const DenseRowsCut cut = dense_rows_cut(n, cols, batch);
+        if (cut.slices > 1) most = std::max(most, static_cast<int64_t>(cut.slices) * n * dense_rows_ld(batch));
+    }
+    return std::min<int64_t>(most, 1ll << 28);   // (what does not fit is not sliced)
+}
+
+hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s)
+{
+    const DenseRows &D = a.split->rows;
+    const DenseRowsCut cut = dense_rows_cut(D.n, a.x_rows, a.batch);
+    int slices = cut.slices;
+    if (static_cast<int64_t>(slices) * D.n * dense_rows_ld(a.batch) > D.partial_floats) slices = 1;
+    const dim3 grid(static_cast<unsigned>(cut.tiles * slices));
+    if (cut.cols == 128)
+        hipLaunchKernelGGL(dense_rows_kernel<4>, grid, dim3(kDenseBlock), 0, s, a, D, slices);
+    else
+        hipLaunchKernelGGL(dense_rows_kernel<2>, grid, dim3(kDenseBlock), 0, s, a, D, slices);
+    if (slices > 1) {
+        const int64_t work = static_cast<int64_t>(D.n) * ((a.batch + 3) / 4);
+        const int64_t blocks = std::min<int64_t>((work + kDenseBlock - 1) / kDenseBlock, 4096);
+        hipLaunchKernelGGL(dense_rows_finish_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kDenseBlock), 0, s, a, D, slices);
+    }
+    return hipGetLastError();
+}
+
+void add_sampled_rows(SampledArgs &list, const SddmmArgs &a)
+{
+    add_sampled(list, a);
+    SampledLayer &L = list.layer[list.n - 1];
+    const DenseRows &D = a.split->rows;
+    L.list = D.list; L.rows = D.n; L.table = D.table; L.words = D.words;
+    if (D.n < a.rows) list.loss_cols = nullptr;   // (the other rows' launch takes the mean of the losses)
 }
 
 void add_sampled(SampledArgs &list, const SddmmArgs &a)
@@ -596,12 +862,12 @@ hipError_t launch_sampled(SampledArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pattern_table(const int32_t *indptr, const int32_t *indices, int32_t rows, int32_t words, uint2 *table, const int32_t *status,
-                                hipStream_t s)
+hipError_t launch_pattern_table(const int32_t *indptr, const int32_t *indices, const int32_t *list, int32_t rows, int32_t words, uint2 *table,
+                                const int32_t *status, hipStream_t s)
 {
     int64_t b = (static_cast<int64_t>(rows) * words + kDenseBlock - 1) / kDenseBlock;
     if (b > 8192) b = 8192;
-    hipLaunchKernelGGL(pattern_table_kernel, dim3(static_cast<unsigned>(b)), dim3(kDenseBlock), 0, s, indptr, indices, rows, words, table, status);
+    hipLaunchKernelGGL(pattern_table_kernel, dim3(static_cast<unsigned>(b)), dim3(kDenseBlock), 0, s, indptr, indices, list, rows, words, table, status);
     return hipGetLastError();
 }
 

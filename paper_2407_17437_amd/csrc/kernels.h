@@ -56,6 +56,7 @@ struct RowBlocks {
     int32_t staged_nnz;            // and their stored entries
     int32_t staged_preferred;      // measurement aid: take the staged kernels wherever they can run
 };
+
 constexpr int32_t kStageRows = 512;      // operand rows held in LDS at a time
 constexpr int32_t kStageCols = 64;       // columns of the operand (examples) per work-group
 constexpr int32_t kStageJ = 8;           // rows per row of 16 lanes
@@ -74,6 +75,29 @@ constexpr int32_t kHotRows = 1024;
 constexpr int32_t kPackMaxLen = 128;     // longest row served by the packed path
 constexpr int32_t kPackMinRows = 2048;   // fewer short rows than this: no packed path
 constexpr int32_t kPackSets = 1;         // row sets (64/GS rows each) per wave; measured on the wide MLP: 1 / 2 / 4 / 8 sets give 500 / 504 / 527 / 548 us per step
+
+// Rows of a matrix that are dense enough for matrix instructions (dense_rows_kernel in dense.hip), and their pattern table.
+struct DenseRows {
+    const int32_t *list;           // [n] ascending
+    const uint2 *table;            // [n * words] {bits of 32 columns, CSR position of the first of them}
+    int32_t n, words;
+    float *partial;                // results of the slices of K, partial_floats long
+    int64_t partial_floats;
+};
+// A matrix some of whose rows are served that way: those, and the partition without them that the others then run on
+// (the staged plan is part of it alone).  Host memory.
+struct DenseSplit {
+    DenseRows rows;                // n = 0: there are none, or too few
+    const uint8_t *flag;           // [rows of the matrix] 1: a dense row
+    RowBlocks others;
+};
+constexpr int32_t kDenseRowsMinCols = 1024;    // (so that a dense row is longer than kPackMaxLen)
+constexpr int32_t kDenseRowsMin = 17;          // fewer rows than this stay with the others
+constexpr int64_t kDenseRowsMinWork = 192 << 20;  // entries times columns of the batch from which the extra launch pays
+constexpr int32_t kDenseRowsMinBatch = kStageMinBatch;   // (below it the staged plan, which leaves the dense rows out, is not needed either)
+// Stored entries from which a row counts as dense: an eighth of its columns.  At batch 1024 such a row costs the matrix units
+// 0.30 us per 16384 columns and the staged kernel 2.0 us times its density among power-law rows.
+__host__ __device__ inline int32_t dense_row_length(int32_t cols) { return cols / 8 > 128 ? cols / 8 : 129; }
 
 // Y = epilogue( W * gather(X) ) for a CSR matrix W (rows x cols); also used on the CSC
 // mirror, where "rows" are W's columns.
@@ -112,6 +136,7 @@ struct SpmmArgs {
     float *ce_dZ;              // (rows, ce_lddz)
     int64_t ce_lddz;
     float *ce_loss_cols;       // [batch]
+    const DenseSplit *split;   // (for the launch) or nullptr
 };
 bool spmm_softmax_epilogue_ok(const SpmmArgs &a);
 constexpr int32_t kFullMaxRows = 16;
@@ -173,6 +198,8 @@ struct SddmmArgs {
     // pattern table of a layer dense enough for the sampled gradient (or nullptr): [rows * table_words]
     const uint2 *table;
     int32_t table_words;
+    const DenseSplit *split;        // (for the launch) or nullptr
+    const DenseSplit *split_done;   // (set by the launch) the dense rows are served already
 };
 // Column-tile width (in columns) the products use when their gathered operand has x_rows rows and
 // does not fit an L2; 0: no tiling.  Shared by the kernels' dispatch and by the sizing of the
@@ -254,6 +281,7 @@ hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s);
 constexpr int kSampledLayers = 4;
 constexpr int32_t kSampledMinBatch = 16;
 struct SampledLayer {
+    const int32_t *list; // the rows, or nullptr: 0 .. rows - 1
     const uint2 *table;  // [rows * words] {bits of 32 columns of the row's pattern, CSR position of the first of them}
     int32_t words, rows, cols, nnz, fused;
     int32_t tiles_i, tiles_j, first_block; // set by launch_sampled
@@ -279,9 +307,16 @@ bool sddmm_sampled_ok(const SddmmArgs &a);
 bool sddmm_sampled_possible(const SddmmArgs &a);
 void add_sampled(SampledArgs &list, const SddmmArgs &a);
 hipError_t launch_sampled(SampledArgs &a, hipStream_t s);
+// Y = act(W X + b) of a matrix's dense rows, and how many floats of DenseRows::partial that takes at up to max_batch columns
+bool dense_rows_ok(const DenseSplit *d, int32_t batch);
+bool sampled_operands_ok(const SddmmArgs &a);
+hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s);
+int64_t dense_rows_partial(int32_t n, int32_t cols, int32_t max_batch);
+void add_sampled_rows(SampledArgs &list, const SddmmArgs &a);
 // status: result of the pattern check (the launch does nothing where it is not 0), or nullptr
-hipError_t launch_pattern_table(const int32_t *indptr, const int32_t *indices, int32_t rows, int32_t words, uint2 *table, const int32_t *status,
-                                hipStream_t s);
+// list: the rows (or nullptr: 0 .. rows - 1)
+hipError_t launch_pattern_table(const int32_t *indptr, const int32_t *indices, const int32_t *list, int32_t rows, int32_t words, uint2 *table,
+                                const int32_t *status, hipStream_t s);
 // D[i * ld + j] = values[p] for every stored entry p = (i, j); the rest of D is not touched (zero since allocation)
 hipError_t launch_dense_refresh(const int32_t *indptr, const int32_t *indices, const float *values, int32_t rows, float *D, int64_t ld,
                                 hipStream_t s);
@@ -318,12 +353,16 @@ struct PlanCounts {
     int32_t n_blocks, n_huge_rows, n_huge_blocks, n_short, n_long_blocks, n_rest_blocks, long_nnz, longest_row;
     int32_t n_long_rows;             // rows of more than kPackMaxLen entries
     int32_t hot_nnz;                 // stored entries of the kHotRows longest rows
+    int32_t n_dense, dense_nnz;      // rows of PlanSide::dense_len entries or more, and their entries
     int32_t staged_ranges, staged_partial, staged_rows, staged_nnz, staged_quad_len, staged_longest_share;
     int32_t cls[3][5];               // rows per class of the partitions waves / long_waves / rest_waves
 };
 struct PlanTables {
     int4 *waves, *huge_rows, *long_waves, *rest_waves, *short_rows;
     int32_t *staged_rows, *staged_groups, *staged_ends;
+    int32_t *dense_rows;             // [room for the rows of dense_len entries or more] ascending
+    uint8_t *dense_flag;             // [rows]
+    int4 *other_waves, *other_long_waves, *other_huge_rows;   // copies of the tables above with row -1 in the place of dense rows
 };
 struct PlanWork {                    // scratch, [rows] ints each but for the last two
     int32_t *order, *tmp, *lens, *covered, *cut, *slots;
@@ -333,6 +372,7 @@ struct PlanWork {                    // scratch, [rows] ints each but for the la
 struct PlanSide {
     int32_t rows, other;             // of this orientation
     int32_t range_bound;             // ranges the staged tables have room for, 0: no staged plan
+    int32_t dense_len;               // rows this long are listed, and left out of the staged plan where they are many (INT32_MAX: none)
     const int32_t *indptr, *indices;
     PlanTables tables;
     PlanWork work;
@@ -386,6 +426,14 @@ __host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols
     const int64_t want = (static_cast<int64_t>(rows) + kStageRangeRows * 7 / 8 - 1) / (kStageRangeRows * 7 / 8) + 2 * (kStageTargetGroups / n_tiles) + 2;
     const int64_t bound = want + (rows + 96 * want) / kStageRangeFill + 2;
     return bound * ((cols + kStageRows - 1) / kStageRows + 1) * kStageRangeRows > (1ll << 28) ? 0 : static_cast<int32_t>(bound);
+}
+// Whether the listed rows are worth a route of their own.  Start -> with it, forward product: power-law 4096^2 at 5 % (297 rows,
+// 0.53 M entries) at batch 256 / 512 / 1024: 48 -> 50, 81 -> 77, 129 -> 120 us; 8192 x 1024 at 10 %: 35 -> 36, 87 -> 51, 109 -> 82.
+// Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even at 30 % (324 us; 20 %: 235 -> 326).
+__host__ __device__ inline bool dense_rows_pay(int32_t n_dense, int64_t dense_nnz, int64_t nnz, int32_t cols, int32_t max_batch)
+{
+    return n_dense >= kDenseRowsMin && dense_nnz * 8 >= nnz && dense_nnz * 10 >= static_cast<int64_t>(n_dense) * cols * 3 &&
+           dense_nnz * max_batch >= kDenseRowsMinWork;
 }
 // which of `want` equal shares of the total cost a row falls into that has `done` of it before it
 __host__ __device__ inline int32_t staged_cut(int64_t done, int32_t want, int64_t total)

@@ -895,7 +895,7 @@ __global__ __launch_bounds__(256) void spmm_finish_kernel(const SpmmArgs a)
 {
     const int4 h = a.blocks.huge_rows[blockIdx.x];
     const int c = blockIdx.y * 256 + threadIdx.x;
-    if (c >= a.batch) return;
+    if (c >= a.batch || h.x < 0) return;   // (-1: another launch serves the row)
     const float *sr = a.scratch + static_cast<int64_t>(h.y) * a.scratch_ld + c;
     float y = 0.f;
     int q = 0;
@@ -1408,10 +1408,33 @@ __global__ __launch_bounds__(kBlock) void full_sddmm_kernel(const SddmmArgs a, c
 
 // Second pass of the tiled SDDMM: adds the tiles' partial products in tile order, then stores the
 // gradient or applies the fused momentum step (and the mirror scatter); the same for the biases.
-__global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs a, const int n_tiles)
+// Rows that another launch serves (DenseRows) are runs of entries and left alone: `ahead` is the first listed row that does
+// not end before the work-group's entries.
+__global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs a, const int n_tiles, const DenseRows dense,
+                                                               const uint8_t *__restrict__ dense_flag)
 {
     const int64_t stride = static_cast<int64_t>(blockDim.x) * gridDim.x;
-    for (int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; p < a.nnz; p += stride) {
+    const bool skip = dense.n > 0;
+    for (int64_t base = static_cast<int64_t>(blockIdx.x) * blockDim.x; base < a.nnz; base += stride) {
+        const int64_t p = base + threadIdx.x;
+        bool mine = p < a.nnz;
+        if (skip) {
+            int ahead = 0, hi = dense.n;
+            while (ahead < hi) {
+                const int mid = (ahead + hi) / 2;
+                if (a.indptr[dense.list[mid] + 1] <= base)
+                    ahead = mid + 1;
+                else
+                    hi = mid;
+            }
+            for (; ahead < dense.n; ++ahead) {   // uniform: one or two rows
+                const int row = dense.list[ahead];
+                const int from = a.indptr[row], to = a.indptr[row + 1];
+                if (from >= base + static_cast<int>(blockDim.x)) break;
+                mine = mine && !(p >= from && p < to);
+            }
+        }
+        if (!mine) continue;
         float g = 0.f;
         int t = 0;
         for (; t + 8 <= n_tiles; t += 8) {  // eight loads in flight, added in tile order
@@ -1433,6 +1456,7 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
     }
     if (!(a.db || (a.fused && a.bias))) return;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < a.rows; i += stride) {
+        if (skip && dense_flag[i]) continue;
         float s = 0.f;
         for (int t = 0; t < n_tiles; ++t) s += a.partial[static_cast<int64_t>(t) * a.partial_stride + a.partial_db_at + i];
         if (a.db) a.db[i] = s;
@@ -2135,6 +2159,15 @@ inline bool spans_below_4gib(int64_t rows, int64_t ld) { return rows * ld * 4 < 
 // L2 and evenly used (the gathers of the other kernels then go to memory); and where no single lane row's share,
 // served at about one entry per 60 ns, outlasts the rest of the matrix, which
 // the chip's 256 LDS serve at about one entry and tile per 3.3 ns each.
+bool spmm_dense_rows_ok(const SpmmArgs &a)
+{
+    return dense_rows_ok(a.split, a.batch) && !a.XM && spmm_offsets_ok(a);
+}
+bool sddmm_dense_rows_ok(const SddmmArgs &a)
+{
+    return dense_rows_ok(a.split, a.batch) && sampled_operands_ok(a);
+}
+
 bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t long_segment)
 {
     if (!blocks.staged_rows || batch < kStageMinBatch) return false;
@@ -2223,6 +2256,13 @@ bool spmm_offsets_ok(const SpmmArgs &a)
     return spans_below_4gib(a.x_rows, a.ldx) && (!a.XM || spans_below_4gib(a.x_rows, a.ldxm));
 }
 
+void sddmm_finish_go(const SddmmArgs &a, int n_tiles, hipStream_t s)
+{
+    const int64_t work = a.nnz > a.rows ? a.nnz : a.rows;
+    hipLaunchKernelGGL(sddmm_finish_kernel, dim3(elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles,
+                       a.split_done ? a.split_done->rows : DenseRows{}, a.split_done ? a.split_done->flag : nullptr);
+}
+
 template <int G, int NV>
 hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
 {
@@ -2232,8 +2272,7 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
     const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * a.blocks.n_blocks;
     dim3 grid(static_cast<unsigned>(ids));
     hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
-    const int64_t work = a.nnz > a.rows ? a.nnz : a.rows;
-    hipLaunchKernelGGL(sddmm_finish_kernel, dim3(elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles);
+    sddmm_finish_go(a, n_tiles, s);
     return hipGetLastError();
 }
 
@@ -2312,7 +2351,7 @@ int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, float
 
 bool can_pair(const SpmmArgs &a, const SddmmArgs &b)
 {
-    return !sddmm_sampled_ok(b) && a.batch == b.batch && a.batch > 4 && a.batch <= 1024 && !a.XM && a.rows > 0 && b.rows > 0 &&
+    return !sddmm_sampled_ok(b) && !sddmm_dense_rows_ok(b) && a.batch == b.batch && a.batch > 4 && a.batch <= 1024 && !a.XM && a.rows > 0 && b.rows > 0 &&
            a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && spmm_offsets_ok(a) &&
            sddmm_offsets_ok(b) && spmm_tile_group(a) == 0 && !spmm_staged_ok(a) && sddmm_tile_columns(b) == 0 &&
            !sddmm_staged_ok(b) && !sddmm_full_ok(b);
@@ -2320,7 +2359,7 @@ bool can_pair(const SpmmArgs &a, const SddmmArgs &b)
 
 bool can_pair(const SddmmArgs &a, const SddmmArgs &b)
 {
-    return !sddmm_sampled_ok(a) && !sddmm_sampled_ok(b) && a.batch == b.batch && a.batch > 0 && a.batch <= 1024 && a.rows > 0 && b.rows > 0 &&
+    return !sddmm_sampled_ok(a) && !sddmm_sampled_ok(b) && !sddmm_dense_rows_ok(a) && !sddmm_dense_rows_ok(b) && a.batch == b.batch && a.batch > 0 && a.batch <= 1024 && a.rows > 0 && b.rows > 0 &&
            a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && sddmm_offsets_ok(a) && sddmm_offsets_ok(b) &&
            sddmm_tile_columns(a) == 0 && sddmm_tile_columns(b) == 0 && !sddmm_staged_ok(a) && !sddmm_staged_ok(b) &&
            !sddmm_full_ok(a) && !sddmm_full_ok(b);
@@ -2451,6 +2490,15 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
             hipLaunchKernelGGL(full_rows_finish_kernel, dim3(a.rows, (a.batch + kEwBlock - 1) / kEwBlock), dim3(kEwBlock), 0, s, a, n_slices);
         return hipGetLastError();
     }
+    if (spmm_dense_rows_ok(a)) {
+        // the dense rows by matrix instructions, then the others as ever, told to leave these out
+        const hipError_t e = launch_dense_rows(a, s);
+        if (e != hipSuccess || a.split->rows.n == a.rows) return e;
+        SpmmArgs others = a;
+        others.blocks = a.split->others;
+        others.split = nullptr;
+        return launch_spmm(others, s);
+    }
     if (spmm_staged_ok(a)) {
         const int n_tiles = (a.batch + kStageCols - 1) / kStageCols;
         const dim3 grid(n_tiles * a.blocks.staged_ranges), block(kStageWaves * kWave);
@@ -2545,6 +2593,17 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
         add_sampled(one, a);
         return launch_sampled(one, s);
     }
+    if (sddmm_dense_rows_ok(a)) {
+        SampledArgs rows{};
+        add_sampled_rows(rows, a);
+        const hipError_t e = launch_sampled(rows, s);
+        if (e != hipSuccess || a.split->rows.n == a.rows) return e;
+        SddmmArgs others = a;
+        others.blocks = a.split->others;
+        others.split = nullptr;
+        others.split_done = a.split;
+        return launch_sddmm(others, s);
+    }
     if (sddmm_full_ok(a)) {
         const int n_chunks = (a.batch + 255) / 256;
         const int groups = (a.x_rows + kWavesPerBlock - 1) / kWavesPerBlock;  // one row of X per wave, up to two rounds of work-groups
@@ -2564,8 +2623,7 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
             const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * rest.blocks.n_blocks;
             hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles, spread);
         }
-        const int64_t work = a.nnz > a.rows ? a.nnz : a.rows;
-        hipLaunchKernelGGL(sddmm_finish_kernel, dim3(elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles);
+        sddmm_finish_go(a, n_tiles, s);
         return hipGetLastError();
     }
     switch (sddmm_tile_columns(a)) {

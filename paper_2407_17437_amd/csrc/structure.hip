@@ -366,6 +366,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     extern __shared__ int32_t plan_lds[];
     __shared__ int32_t cnt[16];
     __shared__ int64_t cnt64;
+    __shared__ int32_t dense_cnt[3];   // rows, their entries, and the length from which the staged plan leaves rows out
     const PlanSide &S = A.side[blockIdx.x];
     const int32_t n = S.rows, nnz = A.nnz, tid = threadIdx.x;
     const int lane = lane_id(), wv = wave_id();
@@ -450,6 +451,50 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             parts_before += __shfl(incl, kWave - 1, kWave);
         }
 
+    // rows long enough for the matrix instructions: listed where they hold enough of the entries
+    if (tid == 0) { dense_cnt[0] = 0; dense_cnt[1] = 0; dense_cnt[2] = INT_MAX; }
+    if (S.dense_len < INT_MAX && longest >= S.dense_len) {   // uniform
+        int32_t mine = 0;
+        int64_t entries = 0;
+        for (int32_t i = k_lo + lane; i < k_hi; i += kWave)
+            if (lens[i] >= S.dense_len) {
+                ++mine;
+                entries += lens[i];
+            }
+        mine = wave_sum(mine);
+        entries = wave_sum(entries);
+        if (lane == 0) { wtot[wv][1] = entries; hist[wv][0] = mine; }
+        __syncthreads();
+        if (tid == 0) {
+            int32_t rows = 0;
+            entries = 0;
+            for (int w = 0; w < kWaves; ++w) {
+                const int32_t here = hist[w][0];
+                hist[w][0] = rows;
+                rows += here;
+                entries += wtot[w][1];
+            }
+            if (dense_rows_pay(rows, entries, nnz, S.other, A.max_batch)) {
+                dense_cnt[0] = rows;
+                dense_cnt[1] = static_cast<int32_t>(entries);
+                dense_cnt[2] = S.dense_len;
+            }
+        }
+        __syncthreads();
+        if (dense_cnt[0] > 0) {
+            int32_t at = hist[wv][0];
+            for (int32_t i0 = k_lo; i0 < k_hi; i0 += kWave) {
+                const int32_t i = i0 + lane;
+                const bool dense = i < k_hi && lens[i] >= S.dense_len;
+                const uint64_t mask = __ballot(dense);
+                if (dense) S.tables.dense_rows[at + lanes_below(mask)] = i;
+                if (i < k_hi) S.tables.dense_flag[i] = dense;
+                at += __popcll(mask);
+            }
+        }
+    }
+    __syncthreads();
+
     // rows by length, longest first, ties in row order: radix sort of longest - length, 8 bits a pass, stable because
     // every wave ranks its chunk in order
     int32_t *from = S.work.tmp, *to = S.work.order;
@@ -509,11 +554,12 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         int64_t sum = 0;
         for (int32_t k = tid; k < top; k += kBig) sum += lens[order[k]];
         sum = wave_sum(sum);
-        if (lane == 0) wtot[wv][1] = sum;
+        if (lane == 0) wtot[wv][2] = sum;
     }
     __syncthreads();
     int64_t hot = 0;
-    for (int w = 0; w < kWaves; ++w) hot += wtot[w][1];
+    for (int w = 0; w < kWaves; ++w) hot += wtot[w][2];
+    __syncthreads();
 
     PlanCounts &C = *S.work.counts;   // (written by the first thread)
     const int32_t n_short = n_le >= kPackMinRows && nnz > 0 && !row_split ? n_le : 0;
@@ -540,6 +586,8 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             for (int k = 0; k < 5; ++k) C.cls[v][k] = cls[v][k];
         C.longest_row = longest;
         C.hot_nnz = static_cast<int32_t>(hot);
+        C.n_dense = dense_cnt[0];
+        C.dense_nnz = dense_cnt[1];
         C.long_nnz = static_cast<int32_t>(long_nnz);
         C.n_huge_rows = n_huge;
         C.n_huge_blocks = parts;
@@ -552,16 +600,18 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 
     // the staged plan: of the long rows alone where the rows differ widely, of all rows otherwise
     const int32_t cblocks = (S.other + kStageRows - 1) / kStageRows;
+    const int32_t n_dense = __builtin_amdgcn_readfirstlane(dense_cnt[0]), dense_nnz = __builtin_amdgcn_readfirstlane(dense_cnt[1]),
+                  below = __builtin_amdgcn_readfirstlane(dense_cnt[2]);
     int32_t min_len = 0, want = 0;
     int32_t ranges = 0, quad_len = 0, n_cov = 0, longest_share = 0;
     if (n_short > 0 && n_short < n && A.mode == kPlanBalanced && static_cast<int64_t>(longest) * n > 4ll * nnz) {
         min_len = kPackMaxLen + 1;
-        want = staged_ranges_wanted(n - n_le, long_nnz, S.other, A.max_batch, A.mode, S.range_bound);
+        want = staged_ranges_wanted(n - n_le - n_dense, long_nnz - dense_nnz, S.other, A.max_batch, A.mode, S.range_bound);
     }
     const bool partial = want > 0;
     if (want == 0) {
         min_len = 0;
-        want = staged_ranges_wanted(n, nnz, S.other, A.max_batch, A.mode, S.range_bound);
+        want = staged_ranges_wanted(n - n_dense, nnz - dense_nnz, S.other, A.max_batch, A.mode, S.range_bound);
     }
     if (want > 0) {
         auto cost = [&](int32_t len) { return static_cast<int64_t>(len) + 2 * min(len, cblocks) + 1; };
@@ -570,8 +620,9 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         for (int32_t i0 = k_lo; i0 < k_hi; i0 += kWave) {
             const int32_t i = i0 + lane;
             const int32_t len = i < k_hi ? lens[i] : -1;
-            if (len >= min_len) sum += cost(len);
-            covered += __popcll(__ballot(len >= min_len));
+            const bool in = len >= min_len && len < below;
+            if (in) sum += cost(len);
+            covered += __popcll(__ballot(in));
         }
         sum = wave_sum(sum);
         if (lane == 0) { wtot[wv][2] = sum; wtot[wv][3] = covered; }
@@ -586,28 +637,34 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         }
         quad_len = static_cast<int32_t>(max(static_cast<int64_t>(256), total / want / 32));
         // slots before the wave's chunk
-        int32_t slots = 0, longest_single = 0;
+        int32_t slots = 0, longest_single = 0, longest_in = 0;
         for (int32_t i0 = k_lo; i0 < k_hi; i0 += kWave) {
             const int32_t i = i0 + lane;
             const int32_t len = i < k_hi ? lens[i] : -1;
-            slots += len >= min_len ? (len >= quad_len ? 4 : 1) : 0;
-            if (len < quad_len) longest_single = max(longest_single, len);
+            const bool in = len >= min_len && len < below;
+            slots += in ? (len >= quad_len ? 4 : 1) : 0;
+            if (in && len < quad_len) longest_single = max(longest_single, len);
+            if (in) longest_in = max(longest_in, len);
         }
         slots = wave_sum(slots);
 #pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) longest_single = max(longest_single, __shfl_xor(longest_single, d, kWave));
-        if (lane == 0) { wtot[wv][4] = slots; wtot[wv][5] = longest_single; }
+        for (int d = 1; d < kWave; d <<= 1) {
+            longest_single = max(longest_single, __shfl_xor(longest_single, d, kWave));
+            longest_in = max(longest_in, __shfl_xor(longest_in, d, kWave));
+        }
+        if (lane == 0) { wtot[wv][4] = slots; wtot[wv][5] = longest_single; wtot[wv][7] = longest_in; }
         __syncthreads();
         slots = 0;
         for (int w = 0; w < kWaves; ++w) {
             slots += w < wv ? static_cast<int32_t>(wtot[w][4]) : 0;
             longest_single = max(longest_single, static_cast<int32_t>(wtot[w][5]));
+            longest_in = max(longest_in, static_cast<int32_t>(wtot[w][7]));
         }
         // covered rows in row order, with the part of the total cost and the slots before them
         for (int32_t i0 = k_lo; i0 < k_hi; i0 += kWave) {
             const int32_t i = i0 + lane;
             const int32_t len = i < k_hi ? lens[i] : -1;
-            const bool in = len >= min_len;
+            const bool in = len >= min_len && len < below;
             const uint64_t mask = __ballot(in);
             const int64_t c = in ? cost(len) : 0, c_incl = wave_inclusive(c);
             const int32_t s = in ? (len >= quad_len ? 4 : 1) : 0, s_incl = wave_inclusive(s);
@@ -650,14 +707,14 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 S.work.range_first[at + piece] = piece == 0 ? k0 : lower_bound(sl, k0, n_cov, s0 + piece * kStageRangeFill);
         }
         if (tid == 0) S.work.range_first[ranges] = n_cov;
-        longest_share = max(longest >= quad_len ? (longest + 3) / 4 : 0, longest_single);
+        longest_share = max(longest_in >= quad_len ? (longest_in + 3) / 4 : 0, longest_single);
     }
     if (tid == 0) {
         C.staged_ranges = ranges;
         C.staged_partial = partial;
         C.staged_quad_len = quad_len;
         C.staged_rows = n_cov;
-        C.staged_nnz = static_cast<int32_t>(want == 0 ? 0 : min_len > 0 ? long_nnz : nnz);
+        C.staged_nnz = static_cast<int32_t>(want == 0 ? 0 : (min_len > 0 ? long_nnz : nnz) - dense_nnz);
         C.staged_longest_share = longest_share;
         A.result->plan[blockIdx.x] = C;
     }
@@ -710,6 +767,13 @@ __device__ __forceinline__ int4 wave_record(const PlanSide &S, const PlanCounts 
     return make_int4(row, s0, s1, part | (lg << 4) | (lead ? 256 : 0) | (huge ? 512 : 0));
 }
 
+// A record of a partition as the launch of the rows that are not dense sees it.
+__device__ __forceinline__ int4 without_dense(const PlanSide &S, int4 d)
+{
+    if (d.x >= 0 && S.tables.dense_flag[d.x]) d.x = -1;
+    return d;
+}
+
 // The tables of both orientations (blockIdx.y).  Staged ranges: a work-group per range ranks its rows by counting
 // the longer ones; records and short rows: an element per thread.
 __global__ __launch_bounds__(kStageRangeRows) void plan_fill_kernel(const PlanArgs A)
@@ -746,15 +810,22 @@ __global__ __launch_bounds__(kStageRangeRows) void plan_fill_kernel(const PlanAr
         if (tid == 0) S.tables.staged_groups[q] = (m + 3 * nq + 63) / 64;
         __syncthreads();
     }
+    if (C.n_dense > 0)
+        for (int32_t k = blockIdx.x * kStageRangeRows + tid; k < C.n_huge_rows; k += gridDim.x * kStageRangeRows)
+            S.tables.other_huge_rows[k] = without_dense(S, S.tables.huge_rows[k]);
     const int32_t cap = min(max(A.nnz / 16384, 8), 64) * kWavesPerBlock;
     const int64_t n_w = static_cast<int64_t>(C.n_blocks) * kWavesPerBlock, n_l = n_w + static_cast<int64_t>(C.n_long_blocks) * kWavesPerBlock;
     const int64_t n_r = n_l + static_cast<int64_t>(C.n_rest_blocks) * kWavesPerBlock, n_all = n_r + (C.n_short + 63) / 64 * 64;
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * kStageRangeRows + tid; k < n_all; k += static_cast<int64_t>(gridDim.x) * kStageRangeRows) {
         if (k < n_w) {
-            S.tables.waves[k] = wave_record(S, C, C.cls[0], C.n_huge_rows, C.n_huge_blocks, cap, k / kWavesPerBlock, k % kWavesPerBlock);
+            const int4 d = wave_record(S, C, C.cls[0], C.n_huge_rows, C.n_huge_blocks, cap, k / kWavesPerBlock, k % kWavesPerBlock);
+            S.tables.waves[k] = d;
+            if (C.n_dense > 0) S.tables.other_waves[k] = without_dense(S, d);
         } else if (k < n_l) {
             const int64_t e = k - n_w;
-            S.tables.long_waves[e] = wave_record(S, C, C.cls[1], C.n_huge_rows, C.n_huge_blocks, cap, e / kWavesPerBlock, e % kWavesPerBlock);
+            const int4 d = wave_record(S, C, C.cls[1], C.n_huge_rows, C.n_huge_blocks, cap, e / kWavesPerBlock, e % kWavesPerBlock);
+            S.tables.long_waves[e] = d;
+            if (C.n_dense > 0) S.tables.other_long_waves[e] = without_dense(S, d);
         } else if (k < n_r) {
             const int64_t e = k - n_l;
             S.tables.rest_waves[e] = wave_record(S, C, C.cls[2], C.n_long_rows, 0, cap, e / kWavesPerBlock, e % kWavesPerBlock);

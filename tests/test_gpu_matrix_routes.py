@@ -1,0 +1,104 @@
+"""The routes through the matrix instructions and the column tiles of wide batches, at the sizes where they can go wrong:
+edges of tiles, remainders, the ends of their dispatch ranges.  Checked against the CPU oracle."""
+import numpy as np
+import pytest
+
+from paper_2407_17437_amd import workloads as wl
+from test_gpu_parity import close, layer_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nb():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2407_17437_amd import binding
+    return binding
+
+
+def check_layer(nb, oracle, lay, batch, ld=None, max_batch=None, seed=1, backward=True):
+    import torch
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((lay.cols, batch)).astype(np.float32); dY = rng.standard_normal((lay.rows, batch)).astype(np.float32)
+    L = nb.SparseLinear(lay, max_batch=max_batch or batch)
+    Xd, dYd = nb.to_dense(X, ld=ld), nb.to_dense(dY, ld=ld)
+    Yd, dXd = nb.dense(lay.rows, batch, ld=ld), nb.dense(lay.cols, batch, ld=ld)
+    g, db = torch.full((lay.nnz,), float("nan"), device="cuda"), torch.full((lay.rows,), float("nan"), device="cuda")
+    nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+    torch.cuda.synchronize()
+    Y, S = oracle.spmm(lay.rows, lay.cols, lay.indptr, lay.indices, lay.values, lay.bias, X, lay.relu)
+    close(Yd.cpu().numpy(), Y, S, what="Y")
+    if backward:
+        nb.sparse_linear_backward(L.handle, Xd, Yd if lay.relu else None, dYd, dXd, g, db, batch)
+        torch.cuda.synchronize()
+        dZ = oracle.relu_backward(dY, Yd.cpu().numpy()) if lay.relu else dY
+        dX, SdX = oracle.spmm_t(lay.rows, lay.cols, lay.indptr, lay.indices, lay.values, dZ)
+        close(dXd.cpu().numpy(), dX, SdX, what="dX")
+        gr, Sg, dbr, Sdb = oracle.sddmm(lay.rows, lay.cols, lay.indptr, lay.indices, dZ, X)
+        close(g.cpu().numpy(), gr, Sg, what="dvalues")
+        close(db.cpu().numpy(), dbr, Sdb, what="dbias")
+    L.close()
+
+
+@pytest.mark.parametrize("rows,cols,density,batch,ld", [
+    (64, 64, 0.36, 16, None), (65, 127, 0.5, 17, 17), (129, 64, 1.0, 63, 63),      # few tiles: the narrowest batches, ragged tiles
+    (100, 300, 0.35, 65, None), (300, 100, 0.38, 128, 129),
+    (1500, 1410, 0.16, 100, None), (1473, 1409, 0.15, 67, 67),                     # 552 tiles, the last of them one row and one column
+])
+def test_sampled_gradient(nb, oracle, rows, cols, density, batch, ld):
+    check_layer(nb, oracle, layer_case(rows, cols, density, seed=rows + batch), batch, ld=ld)
+
+
+def mixed_rows(rows, cols, n_dense, density, seed, relu=False):
+    """n_dense rows that store `density` of their columns among short, empty and middling ones."""
+    rng = np.random.default_rng(seed)
+    lens = np.where(rng.random(rows) < 0.05, rng.integers(125, 137, rows), rng.integers(0, 30, rows))
+    lens[rng.permutation(rows)[:n_dense]] = (density * cols + rng.integers(-20, 20, n_dense)).clip(1, cols).astype(np.int64)
+    indptr, indices = wl.pattern_from_row_nnz(lens, cols, seed=seed)
+    return wl.SparseLayerData(rows, cols, indptr, indices, wl.init_values(indptr, seed), rng.standard_normal(rows).astype(np.float32), relu)
+
+
+@pytest.mark.parametrize("rows,cols,n_dense,density,batch,ld,relu", [
+    (2300, 1300, 129, 0.6, 128, None, True),    # short rows packed; a row tile with one row
+    (2300, 1345, 128, 1.0, 131, 131, False),    # full row tiles, full rows, a last step of one column
+    (600, 1407, 200, 0.5, 300, 301, True),      # too few short rows to be packed
+    (1000, 2049, 64, 0.9, 513, None, False),    # a batch that leaves one column over
+    (130, 1500, 130, 0.7, 192, None, False),    # nothing but dense rows
+    (20000, 1100, 300, 0.4, 129, 129, True),
+])
+def test_dense_rows(nb, oracle, rows, cols, n_dense, density, batch, ld, relu):
+    # (bound for batches up to 4096, at which the dense rows are worth a launch of their own)
+    check_layer(nb, oracle, mixed_rows(rows, cols, n_dense, density, rows + cols, relu), batch, ld=ld, max_batch=4096)
+
+
+def test_dense_rows_keep_a_non_finite_operand_row_to_the_rows_that_read_it(nb, oracle):
+    import torch
+    lay, batch = mixed_rows(900, 1300, 150, 0.5, 3), 256
+    X = np.random.default_rng(4).standard_normal((lay.cols, batch)).astype(np.float32)
+    Xf = X.copy()
+    odd = (0, 63, 64, 700, 1299)
+    X[odd, :] = np.inf
+    X[700, :] = np.nan
+    Xf[odd, :] = 0.0
+    L = nb.SparseLinear(lay, max_batch=4096)
+    Yd = nb.dense(lay.rows, batch)
+    nb.sparse_linear_forward(L.handle, nb.to_dense(X), Yd, batch)
+    torch.cuda.synchronize()
+    Y = Yd.cpu().numpy()
+    touched = np.zeros(lay.rows, dtype=bool)
+    touched[np.repeat(np.arange(lay.rows), np.diff(lay.indptr))[np.isin(lay.indices, odd)]] = True
+    Yr, S = oracle.spmm(lay.rows, lay.cols, lay.indptr, lay.indices, lay.values, lay.bias, Xf, False)
+    close(Y[~touched], Yr[~touched], S[~touched], what="rows that do not reference the odd rows")
+    assert (~touched & (np.diff(lay.indptr) > 500)).any() and not np.isfinite(Y[touched]).all(axis=1).any()
+    L.close()
+
+
+@pytest.mark.parametrize("batch", [257, 300, 320, 385, 511, 512, 513, 640, 1023, 1024, 1025])
+def test_wide_batches_in_column_tiles(nb, oracle, batch):
+    # (operands of 300 rows, which no rule tiles; rows cut over several waves and several work-groups)
+    rng = np.random.default_rng(batch)
+    lens = np.where(rng.random(120) < 0.1, 300, rng.integers(0, 40, 120))
+    indptr, indices = wl.pattern_from_row_nnz(lens, 300, seed=batch)
+    lay = wl.SparseLayerData(120, 300, indptr, indices, wl.init_values(indptr, 1), rng.standard_normal(120).astype(np.float32), True)
+    check_layer(nb, oracle, lay, batch, ld=batch if batch % 2 else None)
