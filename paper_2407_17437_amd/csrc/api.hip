@@ -490,7 +490,7 @@ void fill_staged_ends_host(StagedPlan &H, const int32_t *indptr, const int32_t *
 // Sizes of the tables of one orientation, from bounds that hold for every pattern with these row and entry counts:
 // the tables are laid out before the planner, which runs on the device, has counted anything.
 struct PlanRoom {
-    int64_t blocks, long_blocks, rest_blocks, huge_rows, short_rows, dense_rows = 0, dense_flags = 0;
+    int64_t blocks, long_blocks, rest_blocks, huge_rows, rows_by_length, dense_rows = 0, dense_flags = 0;
     int32_t ranges, cblocks;
     PlanRoom(int32_t rows, int32_t other, int64_t nnz, int32_t max_batch, int32_t dense_len = INT32_MAX)
     {
@@ -508,13 +508,13 @@ struct PlanRoom {
         const bool packed = rows >= kPackMinRows;
         long_blocks = packed ? room(std::min<int64_t>(rows, nnz / kPackMaxLen), nnz) + huge_blocks : 0;
         rest_blocks = packed ? room(rows, std::min<int64_t>(nnz, static_cast<int64_t>(rows) * kPackMaxLen)) : 0;
-        short_rows = packed ? round_up(rows, 64) : 0;
+        rows_by_length = rows_table_size(rows);
         ranges = staged_range_bound(rows, other, max_batch);
         cblocks = (other + kStageRows - 1) / kStageRows;
     }
     size_t ints() const
     {
-        return static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks + rest_blocks) + huge_rows + short_rows)) +
+        return static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks + rest_blocks) + huge_rows + rows_by_length)) +
                static_cast<size_t>(ranges) * (kStageRangeRows * (cblocks + 2) + 4) + static_cast<size_t>(dense_rows + dense_flags) +
                (dense_flags ? static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks) + huge_rows)) : 0);
     }
@@ -527,7 +527,7 @@ struct PlanRoom {
         t.long_waves = r; r += kWavesPerBlock * long_blocks;
         t.rest_waves = r; r += kWavesPerBlock * rest_blocks;
         t.huge_rows = r; r += huge_rows;
-        t.short_rows = r; r += short_rows;
+        t.rows_by_length = r; r += rows_by_length;
         t.other_waves = t.other_long_waves = t.other_huge_rows = nullptr;
         if (dense_flags) {
             t.other_waves = r; r += kWavesPerBlock * blocks;
@@ -548,7 +548,7 @@ struct PlanRoom {
 RowBlocks plan_view(const PlanTables &t, const PlanCounts &c, int32_t other, int32_t nnz, int32_t other_hot_nnz, int32_t mode)
 {
     RowBlocks v{};
-    v.huge_rows = t.huge_rows; v.waves = t.waves; v.short_rows = t.short_rows; v.long_waves = t.long_waves; v.rest_waves = t.rest_waves;
+    v.huge_rows = t.huge_rows; v.waves = t.waves; v.long_waves = t.long_waves; v.rest_waves = t.rest_waves;
     v.n_blocks = c.n_blocks; v.n_huge_rows = c.n_huge_rows; v.n_huge_blocks = c.n_huge_blocks;
     v.n_short = c.n_short; v.n_long_blocks = c.n_long_blocks; v.n_rest_blocks = c.n_rest_blocks; v.long_nnz = c.long_nnz;
     v.hot_share = nnz == 0 ? 0.f : other <= kHotRows ? 1.f : static_cast<float>(static_cast<double>(other_hot_nnz) / static_cast<double>(nnz));
@@ -562,6 +562,8 @@ RowBlocks plan_view(const PlanTables &t, const PlanCounts &c, int32_t other, int
     v.staged_partial = c.staged_partial;
     v.staged_row_count = c.staged_rows;
     v.staged_nnz = c.staged_nnz;
+    v.rows_by_length = t.rows_by_length;
+    v.short_rows = t.rows_by_length + (c.n_short > 0 ? c.n_long_rows : 0);
     v.staged_preferred = mode == NERVA_PARTITION_PREFER_STAGED;
     return v;
 }
@@ -909,12 +911,8 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         const int w = tile_columns(cols, max_batch, nnz, rows, out->plan.hot_share, false, true);
         int32_t tiles = w > 0 ? (max_batch + w - 1) / w : 0;
         if ((out->plan.staged_rows || B.split.others.staged_rows) && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
-        // ... and for the backward pass on one gather stream (products in mirror order, one slice per tile of the
-        // transposed product), which runs where every row of the mirror is short
-        if (out->plan_t.n_short == cols && out->plan_t.n_long_blocks == 0) {
-            const int wt = tile_columns(rows, max_batch, nnz, cols, out->plan_t.hot_share, false);
-            if (wt > 0 && (max_batch + wt - 1) / wt > tiles) tiles = (max_batch + wt - 1) / wt;
-        }
+        // ... and for the backward pass on one gather stream (products in mirror order, a slice per column tile)
+        tiles = std::max(tiles, (max_batch + 63) / 64);
         out->partial_tiles = 0;
         if (tiles > 0) {
             out->partial_db_at = round_up(nnz, 64);
@@ -1128,24 +1126,19 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
         lddy = static_cast<int32_t>(layer->dz_ld);
     }
     const bool mask = relu && !form_dz;  // dY still is the gradient of the output
-    if (dX && use_dense(layer, batch) && !mask) {
-        HIP_TRY(refresh_dense_copies(layer, s));
-        HIP_TRY(dense_transposed(layer, dY, lddy, dX, lddx, nullptr, 0, batch, s));
-    } else if (dX) {
-        if (!form_dz) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
-        layer->mirror_stale = false;
+    auto make_t = [&] {
         SpmmArgs a{};
         a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.scratch_ld = layer->scratch_ld;
         a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
         a.X = dY; a.ldx = lddy;
         if (mask) { a.XM = Y; a.ldxm = ldy; }
         a.Y = dX; a.ldy = lddx; a.rows = layer->cols; a.x_rows = layer->rows; a.batch = batch;
-        HIP_TRY(launch_spmm(a, s));
-    }
-    if (dvalues || dbias) {
+        return a;
+    };
+    auto make_g = [&] {
         SddmmArgs a{};
         a.blocks = layer->plan;
-        a.indptr = layer->indptr; a.indices = layer->indices;
+        a.indptr = layer->indptr; a.indices = layer->indices; a.perm = layer->perm;
         a.dZ = dY; a.lddz = lddy;
         if (mask) { a.ZM = Y; a.ldzm = ldy; }
         a.X = X; a.ldx = ldx; a.g = dvalues; a.db = dbias;
@@ -1153,9 +1146,26 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
         a.partial = layer->partial; a.partial_stride = layer->partial_stride;
         a.partial_db_at = layer->partial_db_at; a.partial_tiles = layer->partial_tiles;
         a.skip_products = dvalues ? 0 : 1;  // only the bias gradient is wanted
+        if (!form_dz) { a.values = layer->values; a.values_t = layer->values_t; }   // (where the mirror values are not up to date yet)
         if (layer->cur.has_table) { a.table = reinterpret_cast<const uint2 *>(layer->cur.table); a.table_words = table_words(layer); }
         a.split = split_of(layer);
-        HIP_TRY(launch_sddmm(a, s));
+        return a;
+    };
+    if (dX && use_dense(layer, batch) && !mask) {
+        HIP_TRY(refresh_dense_copies(layer, s));
+        HIP_TRY(dense_transposed(layer, dY, lddy, dX, lddx, nullptr, 0, batch, s));
+    } else if (dX && dvalues && !mask && backward_fused_ok(make_t(), make_g(), true)) {
+        if (!form_dz && !backward_fused_refreshes(make_t(), make_g())) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
+        layer->mirror_stale = false;
+        HIP_TRY(launch_backward_fused(make_t(), make_g(), true, s));
+        return NERVA_OK;
+    } else if (dX) {
+        if (!form_dz) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
+        layer->mirror_stale = false;
+        HIP_TRY(launch_spmm(make_t(), s));
+    }
+    if (dvalues || dbias) {
+        HIP_TRY(launch_sddmm(make_g(), s));
     }
     return NERVA_OK;
 }
@@ -1574,11 +1584,11 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 HIP_TRY(launch_full_backward(t, g_full, s));
                 continue;
             }
-            if (backward_fused_ok(t, g_same)) {
+            if (backward_fused_ok(t, g_same, false)) {
                 if (pending >= 0 && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
                 pending = -1;
                 Timed tm(mlp->prof, s, "backward_fused", l);
-                HIP_TRY(launch_backward_fused(t, g_same, s));
+                HIP_TRY(launch_backward_fused(t, g_same, false, s));
                 continue;
             }
             if (pending >= 0) {

@@ -55,6 +55,7 @@ struct RowBlocks {
     int32_t long_nnz;              // stored entries of the rows beyond kPackMaxLen (those of long_waves)
     int32_t staged_nnz;            // and their stored entries
     int32_t staged_preferred;      // measurement aid: take the staged kernels wherever they can run
+    const int4 *rows_by_length;    // every row, as in short_rows (which is the end of this table)
 };
 
 constexpr int32_t kStageRows = 512;      // operand rows held in LDS at a time
@@ -223,6 +224,7 @@ struct BackwardArgs {
     float *partial;              // [tile][partial_stride]: products in mirror order
     int64_t partial_stride;
     const int32_t *perm;         // mirror position -> CSR position
+    const float *refresh;        // values[] (CSR order), from which the launch brings the mirror values up to date (w_t), or nullptr
     // what the second pass does with the sums: store them (g, db: CSR order) and / or the momentum step
     float *g, *db;
     int32_t fused, nesterov;
@@ -230,8 +232,11 @@ struct BackwardArgs {
     float *w, *velocity, *w_t;   // values[], velocity[] (CSR order), mirror values
     float *bias, *bias_velocity;
 };
-bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g);
-hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, hipStream_t s);
+// alone: a single call, not part of a training step, where the two may share their launches with other layers' instead
+bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone);
+// whether such a call also brings the mirror values (g.values_t) up to date with g.values, so that the caller need not
+bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g);
+hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s);
 bool full_backward_ok(const SpmmArgs &t, const SddmmArgs &g);
 hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream_t s);
 
@@ -358,12 +363,14 @@ struct PlanCounts {
     int32_t cls[3][5];               // rows per class of the partitions waves / long_waves / rest_waves
 };
 struct PlanTables {
-    int4 *waves, *huge_rows, *long_waves, *rest_waves, *short_rows;
+    int4 *waves, *huge_rows, *long_waves, *rest_waves, *rows_by_length;
     int32_t *staged_rows, *staged_groups, *staged_ends;
     int32_t *dense_rows;             // [room for the rows of dense_len entries or more] ascending
     uint8_t *dense_flag;             // [rows]
     int4 *other_waves, *other_long_waves, *other_huge_rows;   // copies of the tables above with row -1 in the place of dense rows
 };
+// Records of PlanTables::rows_by_length: padded, so that sets of up to 64 rows from any row on can be read.
+__host__ __device__ inline int64_t rows_table_size(int32_t rows) { return (static_cast<int64_t>(rows) + 63) / 64 * 64 + 64; }
 struct PlanWork {                    // scratch, [rows] ints each but for the last two
     int32_t *order, *tmp, *lens, *covered, *cut, *slots;
     int32_t *range_first;            // [range_bound + 1]

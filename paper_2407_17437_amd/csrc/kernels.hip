@@ -1469,7 +1469,7 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
     }
 }
 
-// ---- backward pass of a hidden layer in one gather stream --------------------------------------
+// ---- both gradients of a layer in one gather stream ---------------------------------------------
 // The transposed product dX = W^T dZ and the SDDMM g = (dZ X^T) on W's pattern gather the same
 // rows: taken in the mirror's order (row j of W^T, its entries i ascending), stored entry (i, j)
 // needs dZ[i, :] for both.  One kernel walks the mirror like spmm_body_packed (one mirror row per
@@ -1477,9 +1477,12 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
 //     acc[j, tile]        += values_t[q] * dZ[i, tile]
 //     partial[tile][q]     = <dZ[i, tile], X[j, tile]>        (X[j, tile] is held by the lane group)
 // and stores dX[j, tile] = acc * [X[j, tile] > 0] (the ReLU derivative of the layer below, whose
-// output X is).  The per-tile partial products, in mirror order, are added in tile order by
-// backward_finish_kernel, which applies the momentum step through perm (mirror -> CSR position)
-// and also forms the bias gradient (row sums of dZ).  Every mirror row must be short (packed).
+// output X is; a call on its own stores acc).  The per-tile partial products, in mirror order, are added in tile order by
+// backward_finish_kernel, which stores the gradient or applies the momentum step through perm (mirror -> CSR position) and
+// forms the bias gradient (row sums of dZ).  A single tile needs no second pass.  Where the mirror rows do not make enough
+// waves several groups share a row.  What bounds it is the gathers, half of what the two products apart take: backward call
+// on 16384^2 power-law rows at 1 %, batch 1024: 1088 -> 570 us; uniform 8192^2 at 0.5 % / 5 %: 146 -> 91, 982 -> 648; at batch
+// 32: 18.1 -> 10.8, 100 -> 68; 1000 x 1000 at 0.5 %, one launch instead of three: 13.5 -> 5.8.
 constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and smaller groups schedule finer (measured on the wide MLP:
                               // 134 / 138 / 142 us with 4 / 8 / 16 waves; gather depth 4 instead of 8 and a register cap of 64 change nothing)
 
@@ -1509,10 +1512,42 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, int src, int my_ro, float 
     }
 }
 
-template <int GS>
-__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
-                                                                          const int n_pack_blocks)
+// Sums of the rows of dZ, a wave per row: the bias gradient, stored or applied.
+__device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t wave, int64_t n_waves)
 {
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int64_t i = wave; i < a.x_rows; i += n_waves) {
+        const float *zr = a.dZ + i * a.lddz;
+        float s = 0.f;
+        for (int c = lane * 4; c < a.batch; c += kWave * 4) {
+            const int first = four_columns(c, a.batch);
+            const float4 z = drop_shared(ld4(zr + first), c, first);
+            s += (z.x + z.y) + (z.z + z.w);
+        }
+        s = group_sum<kWave>(s);
+        if (lane == 0) {
+            if (a.db) a.db[i] = s;
+            if (a.fused && a.bias) {
+                float w = a.bias[i], v = a.bias_velocity[i];
+                momentum_step(w, v, s, a.lr, a.momentum, a.nesterov);
+                a.bias[i] = w;
+                a.bias_velocity[i] = v;
+            }
+        }
+    }
+}
+
+// ONE: a single column tile -- the products are whole and are stored as the gradient by the work-groups that form them, and
+// the work-groups after those of the rows sum the rows of dZ: there is no second pass.
+template <int GS, bool ONE>
+__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
+                                                                          const int n_pack_blocks, const int lg_split)
+{
+    if (ONE && static_cast<int>(blockIdx.x) >= n_pack_blocks) {
+        backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_pack_blocks) * kBwdWaves + wave_in_block(),
+                          static_cast<int64_t>(gridDim.x - n_pack_blocks) * kBwdWaves);
+        return;
+    }
     int tile, rb;
     if (spread) {
         const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
@@ -1535,24 +1570,32 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     const uint32_t off = static_cast<uint32_t>(col) * 4u;
     const uint32_t ldzb = static_cast<uint32_t>(a.lddz) * 4u;
     const gmem_ptr Zg = as_gmem(a.dZ);
-    const int n_sets = (a.blocks.n_short + NE - 1) / NE;
+    const int per_set = NE >> lg_split, part = grp & ((1 << lg_split) - 1);   // rows per wave; the group's share of its row
+    const int n_sets = (a.rows + per_set - 1) / per_set;
     const int src0 = grp * GS * 4;
     const int n_waves = n_pack_blocks * kBwdWaves;
     const int first_set = rb * kBwdWaves + wv;
     if (first_set >= n_sets) return;  // wave-uniform
-    float *gp = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
+    float *gp = ONE ? nullptr : a.partial + static_cast<int64_t>(tile) * a.partial_stride;
 
-    auto fetch = [&](int s0, int len, int base, int &j, float &w) {  // as in spmm_body_packed
-        const int e = base + lig;
+    auto fetch = [&](int s0, int len, int base, int &j, float &w, int &at, float &v) {  // as in spmm_body_packed
+        const int e = base + part * GS + lig;
         const bool ok = e < len;
         const int p = len > 0 ? s0 + (ok ? e : 0) : 0;
         j = a.indices[p];
-        w = a.values[p];
+        if (ONE || a.refresh) at = a.perm[p];
+        if (a.refresh) {   // uniform
+            w = a.refresh[at];
+            if (ok && tile == 0) a.w_t[p] = w;
+        } else {
+            w = a.values[p];
+        }
+        if (ONE && a.fused) v = a.velocity[at];
         w = ok ? w : 0.f;
     };
 
     for (int set = first_set; set < n_sets; set += n_waves) {
-        const int4 d = a.blocks.short_rows[set * NE + grp];  // the table is padded to whole sets
+        const int4 d = a.blocks.rows_by_length[set * per_set + (grp >> lg_split)];  // the table is padded to whole sets
         const int row = d.x, s0 = d.y, len = d.z;
         const int maxlen = __builtin_amdgcn_readfirstlane(len);  // group 0 holds the set's longest row
         // the group's row of X: the second operand of its entries' products, and the mask of its result;
@@ -1563,13 +1606,14 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
             ax = drop_shared(mask, own_col, col);
         }
         float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        int cur_j;
-        float cur_w;
-        fetch(s0, len, 0, cur_j, cur_w);
-        for (int base = 0; base < maxlen; base += GS) {
-            int next_j = 0;
-            float next_w = 0.f;
-            if (base + GS < maxlen) fetch(s0, len, base + GS, next_j, next_w);  // wave-uniform: one chunk ahead
+        int cur_j, cur_at = 0;
+        float cur_w, cur_v = 0.f;
+        fetch(s0, len, 0, cur_j, cur_w, cur_at, cur_v);
+        for (int base = 0; base < maxlen; base += GS << lg_split) {
+            int next_j = 0, next_at = 0;
+            float next_w = 0.f, next_v = 0.f;
+            if (base + (GS << lg_split) < maxlen)  // wave-uniform: one chunk ahead
+                fetch(s0, len, base + (GS << lg_split), next_j, next_w, next_at, next_v);
             const int my_ro = static_cast<int>(static_cast<uint32_t>(cur_j) * ldzb);
             const int steps = min(GS, maxlen - base);
             float res = 0.f;
@@ -1585,11 +1629,29 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                 u0 += 2; src += 8;
             }
             if (u0 < steps) bwd_pass<1, GS>(Zg, src, my_ro, cur_w, off, ax, u0, lig, acc, res);
-            if (row >= 0 && base + lig < len) gp[s0 + base + lig] = res;  // GS consecutive entries of the row: one coalesced store
+            const int e = base + part * GS + lig;
+            if (row >= 0 && e < len) {
+                if constexpr (ONE) {
+                    if (a.g) a.g[cur_at] = res;
+                    if (a.fused) {
+                        momentum_step(cur_w, cur_v, res, a.lr, a.momentum, a.nesterov);
+                        a.w[cur_at] = cur_w;
+                        a.velocity[cur_at] = cur_v;
+                        a.w_t[s0 + e] = cur_w;
+                    }
+                } else {
+                    gp[s0 + e] = res;  // GS consecutive entries of the row: one coalesced store
+                }
+            }
             cur_j = next_j;
             cur_w = next_w;
+            cur_at = next_at;
+            cur_v = next_v;
         }
-        if (row < 0 || !on) continue;
+        for (int d = GS; d < GS << lg_split; d <<= 1)   // the shares of a row, in one fixed order
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], d, kWave);
+        if (row < 0 || !on || part != 0) continue;
         float4 y = len > 0 ? make_float4(acc[0], acc[1], acc[2], acc[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
         if (a.mask) y = keep_where_positive(y, mask);
         st4(a.dX + static_cast<int64_t>(row) * a.lddx + col, y);
@@ -1627,27 +1689,8 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
         return;
     }
     if (!(a.db || (a.fused && a.bias))) return;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t n_waves = static_cast<int64_t>(gridDim.x - n_entry_blocks) * (kEwBlock / kWave);
-    for (int64_t i = static_cast<int64_t>(blockIdx.x - n_entry_blocks) * (kEwBlock / kWave) + (threadIdx.x >> 6); i < a.x_rows; i += n_waves) {
-        const float *zr = a.dZ + i * a.lddz;
-        float s = 0.f;
-        for (int c = lane * 4; c < a.batch; c += kWave * 4) {
-            const int first = four_columns(c, a.batch);
-            const float4 z = drop_shared(ld4(zr + first), c, first);
-            s += (z.x + z.y) + (z.z + z.w);
-        }
-        s = group_sum<kWave>(s);
-        if (lane == 0) {
-            if (a.db) a.db[i] = s;
-            if (a.fused && a.bias) {
-                float w = a.bias[i], v = a.bias_velocity[i];
-                momentum_step(w, v, s, a.lr, a.momentum, a.nesterov);
-                a.bias[i] = w;
-                a.bias_velocity[i] = v;
-            }
-        }
-    }
+    backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_entry_blocks) * (kEwBlock / kWave) + wave_in_block(),
+                      static_cast<int64_t>(gridDim.x - n_entry_blocks) * (kEwBlock / kWave));
 }
 
 // Two independent launches of a training step in one grid: work-groups [0, na) run the first,
@@ -2387,29 +2430,56 @@ hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 // packed kernel inside column tiles on a mirror all of whose rows are short, its result mask is the
 // SDDMM's second operand (the output of the layer below), and the layer's partial buffer has a slice
 // per tile for the products in mirror order.
-// Lanes per mirror row of the fused backward pass: the transposed product's own tiles, widened to 128 columns
+// Lanes per mirror row of the fused backward pass: the transposed product's own tiles where it has any, else one tile up to 128
+// columns, up to 256 where the operand is small or the rows are short (16384 x 2000 power-law at batch 256 in two tiles: 26 us, in one 29;
+// 12000^2 at 0.1 %: 27 and 24), and tiles of 128 beyond; its own tiles are widened to 128 columns
 // while a tile of dZ still fills no more than an L2 -- half as many tiles halve the partial products that go
 // out and come back (wide MLP, 8192 x 8192 layer: 128.6 -> 122.6 us; the product alone loses 7 % with them).
 static int backward_tile_group(const SpmmArgs &t)
 {
     const int tg = spmm_tile_group(t);
     if (tg == 16 && t.batch > 128 && static_cast<int64_t>(t.x_rows) * 4 * 128 <= (4ll << 20)) return 32;
+    if (tg == 0) return t.batch <= 32 ? 8 : t.batch <= 64 ? 16 : t.batch <= 128 || t.batch > 256 || (t.x_rows > 4096 && t.nnz > 16 * static_cast<int64_t>(t.rows)) ? 32 : 64;
+    if (tg == 8) return 16;
     return tg;
 }
-
-bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g)
+// log2 of the lane groups that share a mirror row: more of them where the rows alone do not make 4096 waves, as long as the
+// shares are not shorter than a pass
+static int backward_split(const SpmmArgs &t, int tg, int n_tiles)
 {
-    if (t.batch != g.batch || t.batch < 4 || t.XM || !t.YM || t.YM != g.X || t.ldym != g.ldx || t.X != g.dZ || t.ldx != g.lddz) return false;
+    int lg = 0;
+    while ((tg << lg) < kWave && (static_cast<int64_t>(t.rows) * tg << lg) / kWave * n_tiles < 4096 && static_cast<int64_t>(t.rows) * (16 << lg) <= t.nnz) ++lg;
+    return lg;
+}
+static int backward_tiles(const SpmmArgs &t, int tg) { return (t.batch + tg * 4 - 1) / (tg * 4); }
+
+// (reading values[] through the position map costs a scattered read per entry and tile, a launch of its own 3.5 us)
+bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g)
+{
+    const int tiles = backward_tiles(t, backward_tile_group(t));
+    return tiles == 1 || static_cast<int64_t>(tiles) * t.nnz <= (1 << 20);
+}
+
+// Within a training step small layers do better with T and S in the grids of their neighbours: entries times columns from
+// which the pass pays there (steps of 3072-1024-512-10 at 10 %, batch 100, 5 M in the middle layer: 38.6 -> 42.5 us with it;
+// 2000-4000-3000-10 at 3 %, batch 128, 46 M: 72.4 -> 70.2; three layers of 3000 at 5 %, batch 100: 128 -> 116).
+constexpr int64_t kFusedMinWork = 16 << 20;
+bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
+{
+    if (t.batch != g.batch || t.batch < 4 || t.XM || t.X != g.dZ || t.ldx != g.lddz) return false;
+    if (t.YM && (t.YM != g.X || t.ldym != g.ldx)) return false;
     if (t.rows != g.x_rows || t.x_rows != g.rows || t.nnz != g.nnz || t.nnz <= 0) return false;
     if (g.ZM || g.skip_products || g.dense || g.loss_cols || !g.partial || !g.perm) return false;
-    if (!spmm_offsets_ok(t) || !sddmm_offsets_ok(g) || spmm_staged_ok(t)) return false;
-    if (t.blocks.n_short != t.rows || t.blocks.n_long_blocks != 0) return false;  // every mirror row packed
+    if (!spmm_offsets_ok(t) || !sddmm_offsets_ok(g) || (!alone && spmm_staged_ok(t))) return false;
     const int tg = backward_tile_group(t);
-    if (tg != 16 && tg != 32) return false;  // (32-column tiles are only chosen for rows too long to be packed)
-    const int n_tiles = (t.batch + tg * 4 - 1) / (tg * 4);
+    if (!alone && static_cast<int64_t>(t.nnz) * t.batch < kFusedMinWork) return false;
+    const int n_tiles = backward_tiles(t, tg);
     if (n_tiles > g.partial_tiles || g.partial_stride < t.nnz) return false;
-    const int64_t sets = (static_cast<int64_t>(t.blocks.n_short) + kWave / tg - 1) / (kWave / tg);
-    return ((n_tiles + 7) / 8) * 8 * ((sets + kBwdWaves - 1) / kBwdWaves) <= kMaxGridIds;
+    // (no row so long that its lane groups outlast the rest of the launch; a pass over 128 entries is short enough on any matrix)
+    const int64_t longest = t.blocks.staged_longest_row >> backward_split(t, tg, n_tiles);
+    if (longest > kPackMaxLen && longest * 4096 > static_cast<int64_t>(t.nnz) * ((t.batch + 63) / 64)) return false;
+    const int64_t per_set = (kWave / tg) >> backward_split(t, tg, n_tiles), sets = (static_cast<int64_t>(t.rows) + per_set - 1) / per_set;
+    return ((n_tiles + 7) / 8) * 8 * ((sets + kBwdWaves - 1) / kBwdWaves) + 2048 <= kMaxGridIds;
 }
 
 // The same sharing for a full matrix of few rows (a saturated output layer): its SDDMM streams the layer's
@@ -2432,28 +2502,41 @@ hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, hipStream_t s)
+hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s)
 {
     BackwardArgs a{};
     a.blocks = t.blocks; a.indices = t.indices; a.values = t.values;
-    a.dZ = t.X; a.lddz = t.ldx; a.X = g.X; a.ldx = g.ldx; a.dX = t.Y; a.lddx = t.ldy; a.mask = 1;
+    a.dZ = t.X; a.lddz = t.ldx; a.X = g.X; a.ldx = g.ldx; a.dX = t.Y; a.lddx = t.ldy; a.mask = t.YM != nullptr;
     a.rows = t.rows; a.x_rows = t.x_rows; a.batch = t.batch; a.nnz = t.nnz;
     a.partial = g.partial; a.partial_stride = g.partial_stride; a.perm = g.perm;
     a.g = g.g; a.db = g.db; a.fused = g.fused; a.nesterov = g.nesterov; a.lr = g.lr; a.momentum = g.momentum;
     a.w = g.values; a.velocity = g.velocity; a.w_t = g.values_t; a.bias = g.bias; a.bias_velocity = g.bias_velocity;
-    const int tg = backward_tile_group(t);
-    const int n_tiles = (t.batch + tg * 4 - 1) / (tg * 4);
+    const int tg = backward_tile_group(t), n_tiles = backward_tiles(t, tg);
+    if (alone && g.values && backward_fused_refreshes(t, g)) a.refresh = g.values;
     const int spread = n_tiles >= 8;
-    const int64_t sets = (static_cast<int64_t>(t.blocks.n_short) + kWave / tg - 1) / (kWave / tg);
+    const int lg_split = backward_split(t, tg, n_tiles);
+    const int64_t per_set = (kWave / tg) >> lg_split, sets = (static_cast<int64_t>(t.rows) + per_set - 1) / per_set;
     const int n_pack_blocks = static_cast<int>((sets + kBwdWaves - 1) / kBwdWaves);
-    const int64_t ids = static_cast<int64_t>(spread ? (n_tiles + 7) / 8 * 8 : n_tiles) * n_pack_blocks;
-    if (tg == 32)
-        hipLaunchKernelGGL(backward_fused_kernel<32>, dim3(static_cast<unsigned>(ids)), dim3(kBwdWaves * kWave), 0, s, a, n_tiles, spread, n_pack_blocks);
-    else
-        hipLaunchKernelGGL(backward_fused_kernel<16>, dim3(static_cast<unsigned>(ids)), dim3(kBwdWaves * kWave), 0, s, a, n_tiles, spread, n_pack_blocks);
-    const int n_entry_blocks = elementwise_blocks(t.nnz);
-    const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kEwBlock / kWave - 1) / (kEwBlock / kWave);
+    const bool one = n_tiles == 1;
+    const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
+    const int64_t ids = static_cast<int64_t>(spread ? (n_tiles + 7) / 8 * 8 : n_tiles) * n_pack_blocks + (one ? n_row_blocks : 0);
+    auto go = [&](auto group) {
+        constexpr int GS = decltype(group)::value;
+        const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
+        if (one)
+            hipLaunchKernelGGL((backward_fused_kernel<GS, true>), grid, block, 0, s, a, n_tiles, spread, n_pack_blocks, lg_split);
+        else
+            hipLaunchKernelGGL((backward_fused_kernel<GS, false>), grid, block, 0, s, a, n_tiles, spread, n_pack_blocks, lg_split);
+    };
+    switch (tg) {
+        case 64: go(std::integral_constant<int, 64>{}); break;
+        case 32: go(std::integral_constant<int, 32>{}); break;
+        case 16: go(std::integral_constant<int, 16>{}); break;
+        default: go(std::integral_constant<int, 8>{}); break;
+    }
+    if (one) return hipGetLastError();
+    const int n_entry_blocks = elementwise_blocks(t.nnz);
     hipLaunchKernelGGL(backward_finish_kernel, dim3(n_entry_blocks + n_row_blocks), dim3(kEwBlock), 0, s, a, n_tiles, n_entry_blocks);
     return hipGetLastError();
 }

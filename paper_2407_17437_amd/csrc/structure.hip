@@ -815,7 +815,7 @@ __global__ __launch_bounds__(kStageRangeRows) void plan_fill_kernel(const PlanAr
             S.tables.other_huge_rows[k] = without_dense(S, S.tables.huge_rows[k]);
     const int32_t cap = min(max(A.nnz / 16384, 8), 64) * kWavesPerBlock;
     const int64_t n_w = static_cast<int64_t>(C.n_blocks) * kWavesPerBlock, n_l = n_w + static_cast<int64_t>(C.n_long_blocks) * kWavesPerBlock;
-    const int64_t n_r = n_l + static_cast<int64_t>(C.n_rest_blocks) * kWavesPerBlock, n_all = n_r + (C.n_short + 63) / 64 * 64;
+    const int64_t n_r = n_l + static_cast<int64_t>(C.n_rest_blocks) * kWavesPerBlock, n_all = n_r + rows_table_size(S.rows);
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * kStageRangeRows + tid; k < n_all; k += static_cast<int64_t>(gridDim.x) * kStageRangeRows) {
         if (k < n_w) {
             const int4 d = wave_record(S, C, C.cls[0], C.n_huge_rows, C.n_huge_blocks, cap, k / kWavesPerBlock, k % kWavesPerBlock);
@@ -832,11 +832,11 @@ __global__ __launch_bounds__(kStageRangeRows) void plan_fill_kernel(const PlanAr
         } else {
             const int64_t e = k - n_r;
             int4 d = make_int4(-1, 0, 0, 0);
-            if (e < C.n_short) {
-                const int32_t r = S.work.order[C.n_long_rows + e];
+            if (e < S.rows) {
+                const int32_t r = S.work.order[e];
                 d = make_int4(r, S.indptr[r], S.indptr[r + 1] - S.indptr[r], 0);
             }
-            S.tables.short_rows[e] = d;
+            S.tables.rows_by_length[e] = d;
         }
     }
 }

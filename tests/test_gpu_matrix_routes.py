@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2407_17437_amd import workloads as wl
-from test_gpu_parity import close, layer_case
+from test_gpu_parity import close, layer_case, raw_f32, raw_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -102,3 +102,47 @@ def test_wide_batches_in_column_tiles(nb, oracle, batch):
     indptr, indices = wl.pattern_from_row_nnz(lens, 300, seed=batch)
     lay = wl.SparseLayerData(120, 300, indptr, indices, wl.init_values(indptr, 1), rng.standard_normal(120).astype(np.float32), True)
     check_layer(nb, oracle, lay, batch, ld=batch if batch % 2 else None)
+
+
+@pytest.mark.parametrize("rows,cols,density,batch,ld,relu", [
+    (40, 3000, 0.02, 5, 5, False), (40, 3000, 0.02, 32, None, True), (3000, 40, 0.02, 33, 33, False),     # lane groups of 8 and 16
+    (900, 500, 0.05, 64, None, True), (900, 500, 0.3, 65, 65, False), (500, 900, 0.01, 128, None, False),  # one tile of 64 and 128 columns
+    (700, 1000, 0.04, 129, 129, False), (700, 1000, 0.04, 256, None, True),                                # one tile of 256
+    (6000, 700, 0.01, 200, None, False), (700, 1000, 0.04, 257, 257, True), (600, 9000, 0.005, 700, None, False),   # several tiles
+    (9000, 400, 0.02, 16, None, False), (3, 1500, 0.5, 100, None, False),   # rows shared by lane groups; hardly any rows to sum
+])
+def test_both_gradients_in_one_pass(nb, oracle, rows, cols, density, batch, ld, relu):
+    lay = layer_case(rows, cols, density, seed=rows + cols + batch, relu=relu)
+    check_layer(nb, oracle, lay, batch, ld=ld)
+    # the mirror's values follow values[] in the same call
+    import torch
+    L = nb.SparseLinear(lay, max_batch=batch)
+    L.values.mul_(3.0)
+    X, Y, dY, dX = (nb.dense(n, batch) for n in (cols, rows, rows, cols))
+    for t in (X, Y, dY):
+        t.normal_()
+    g, db = torch.empty(lay.nnz, device="cuda"), torch.empty(rows, device="cuda")
+    nb.sparse_linear_backward(L.handle, X, Y if relu else None, dY, dX, g, db, batch)
+    torch.cuda.synchronize()
+    _, _, v_t, perm = nb.sparse_linear_mirror(L.handle)
+    assert np.array_equal(raw_f32(nb, torch, v_t, lay.nnz), L.values.cpu().numpy()[raw_i32(nb, torch, perm, lay.nnz)])
+    L.close()
+
+
+@pytest.mark.parametrize("batch,hidden", [(60, (2000, 1500)), (64, (2000, 3000)), (200, (900, 1300)), (300, (1100, 1000))])
+def test_training_step_with_both_gradients_in_one_pass(nb, batch, hidden):
+    """Against the same step by separate products: one and several column tiles, momentum applied inside the pass and after it."""
+    import torch
+    data = wl.make_mlp((300,) + hidden + (10,), sparsity=0.9)
+    X, labels = nb.dense(300, batch), torch.randint(10, (batch,), device="cuda", dtype=torch.int32)
+    X.normal_()
+    out = []
+    for flags in (nb.NERVA_MLP_DEFAULT, nb.NERVA_MLP_UNFUSED):
+        m = nb.MLP(data, batch, flags)
+        for _ in range(3):
+            m.train_step(X, labels, batch, 0.05, 0.9)
+        torch.cuda.synchronize()
+        out.append([t.clone() for l in m.layers for t in (l.values, l.velocity, l.bias, l.bias_velocity)] + [m.loss.clone()])
+        m.close()
+    for a, b in zip(*out):
+        assert torch.allclose(a, b, rtol=1e-3, atol=2e-6 * max(1.0, float(b.abs().max())))
