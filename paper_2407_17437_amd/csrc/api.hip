@@ -813,6 +813,7 @@ static int csr_status_error(const int32_t *st)
 // launches (structure.hip); the host waits once, for the check's verdict and the partitions' sizes.  On failure
 // (NERVA_ERR_CSR, NERVA_ERR_HIP) nothing that a product reads has been changed.  On success the caller swaps
 // l->spare into l->cur and adopts `plan`, `plan_t`.
+constexpr size_t kPartialMaxBytes = 4ull << 30;
 struct BuiltPattern {
     RowBlocks plan{}, plan_t{};
     int64_t partial_stride = 0, partial_db_at = 0;
@@ -912,13 +913,14 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         int32_t tiles = w > 0 ? (max_batch + w - 1) / w : 0;
         if ((out->plan.staged_rows || B.split.others.staged_rows) && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
         // ... and for the backward pass on one gather stream (products in mirror order, a slice per column tile)
-        tiles = std::max(tiles, (max_batch + 63) / 64);
+        const int32_t tiles_fused = std::max(tiles, (max_batch + 63) / 64);
+        if (static_cast<size_t>(tiles_fused) * (round_up(nnz, 64) + round_up(rows, 64)) * 4 <= kPartialMaxBytes) tiles = tiles_fused;
         out->partial_tiles = 0;
         if (tiles > 0) {
             out->partial_db_at = round_up(nnz, 64);
             out->partial_stride = out->partial_db_at + round_up(rows, 64);
             const size_t floats = static_cast<size_t>(tiles) * out->partial_stride;
-            if (floats * 4 <= (4ull << 30)) {  // (beyond that it is too large to be worth it: the untiled kernel stays)
+            if (floats * 4 <= kPartialMaxBytes) {  // (beyond that it is too large to be worth it: the untiled kernel stays)
                 HIP_TRY(reserve(&l->partial, &l->partial_floats, floats));
                 out->partial_tiles = tiles;
             }

@@ -1858,60 +1858,151 @@ __global__ __launch_bounds__(kEwBlock) void copy_kernel(float *__restrict__ dst,
     }
 }
 
-// Softmax cross-entropy, one column (example) per thread, a single work-group so that the
-// mean over the batch is summed in one fixed order (wave sums by DPP, then the wave leaders'
-// values in wave order).  The logits matrix is classes x batch: small next to the layers that
-// feed it.  CMAX > 0: classes <= CMAX and a column's logits are read once into registers.
+// Softmax cross-entropy for up to 16 classes, one column (example) per thread with its logits in registers, a single
+// work-group so that the mean over the batch is summed in one fixed order (wave sums by DPP, then the wave leaders'
+// values in wave order).
 constexpr int kSoftmaxBlock = 1024;
-template <int CMAX>
-__global__ __launch_bounds__(kSoftmaxBlock) void softmax_ce_kernel(const float *Z, int64_t ldz,
-                                                                   const int32_t *__restrict__ labels,
-                                                                   int classes, int batch, float *dZ,
-                                                                   int64_t lddz, float *loss_out)
+constexpr int kSoftmaxWaves = kSoftmaxBlock / kWave;
+constexpr int kSoftmaxFew = 16;
+
+// *loss_out = mean over the batch of the threads' shares; every thread of the work-group arrives here
+__device__ __forceinline__ void softmax_mean(float loss, float inv_b, float (&wave_loss)[kSoftmaxWaves], float *loss_out)
 {
-    __shared__ float wave_loss[kSoftmaxBlock / kWave];
-    const float inv_b = 1.0f / static_cast<float>(batch);
-    float loss = 0.f;
-    for (int c = threadIdx.x; c < batch; c += blockDim.x) {
-        const int t = labels[c];
-        if constexpr (CMAX > 0) {
-            float z[CMAX];
-#pragma unroll
-            for (int i = 0; i < CMAX; ++i) z[i] = i < classes ? Z[static_cast<int64_t>(i) * ldz + c] : -INFINITY;
-            float m = z[0];
-#pragma unroll
-            for (int i = 1; i < CMAX; ++i) m = fmaxf(m, z[i]);
-            float s = 0.f, zt = 0.f;
-#pragma unroll
-            for (int i = 0; i < CMAX; ++i) {
-                if (i < classes) s += expf(z[i] - m);
-                zt = i == t ? z[i] : zt;
-            }
-            const float lse = m + logf(s);
-            loss += lse - zt;
-#pragma unroll
-            for (int i = 0; i < CMAX; ++i)
-                if (i < classes) dZ[static_cast<int64_t>(i) * lddz + c] = (expf(z[i] - lse) - (i == t ? 1.f : 0.f)) * inv_b;
-        } else {
-            float m = -INFINITY;
-            for (int i = 0; i < classes; ++i) m = fmaxf(m, Z[static_cast<int64_t>(i) * ldz + c]);
-            float s = 0.f;
-            for (int i = 0; i < classes; ++i) s += expf(Z[static_cast<int64_t>(i) * ldz + c] - m);
-            const float lse = m + logf(s);
-            loss += lse - Z[static_cast<int64_t>(t) * ldz + c];
-            for (int i = 0; i < classes; ++i) {
-                const float p = expf(Z[static_cast<int64_t>(i) * ldz + c] - lse);
-                dZ[static_cast<int64_t>(i) * lddz + c] = (p - (i == t ? 1.f : 0.f)) * inv_b;
-            }
-        }
-    }
-    loss = group_sum<kWave>(loss);  // every lane of every wave arrives here
+    loss = group_sum<kWave>(loss);
     if ((threadIdx.x & (kWave - 1)) == 0) wave_loss[threadIdx.x >> 6] = loss;
     __syncthreads();
     if (threadIdx.x == 0 && loss_out) {
         float total = 0.f;
         for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) total += wave_loss[w];
         *loss_out = total * inv_b;
+    }
+}
+
+__global__ __launch_bounds__(kSoftmaxBlock) void softmax_ce_few_kernel(const float *Z, int64_t ldz, const int32_t *__restrict__ labels,
+                                                                       int classes, int batch, float *dZ, int64_t lddz, float *loss_out)
+{
+    __shared__ float wave_loss[kSoftmaxWaves];
+    const float inv_b = 1.0f / static_cast<float>(batch);
+    float loss = 0.f;
+    for (int c = threadIdx.x; c < batch; c += blockDim.x) {
+        const int t = labels[c];
+        float z[kSoftmaxFew];
+#pragma unroll
+        for (int i = 0; i < kSoftmaxFew; ++i) z[i] = i < classes ? Z[static_cast<int64_t>(i) * ldz + c] : -INFINITY;
+        float m = z[0];
+#pragma unroll
+        for (int i = 1; i < kSoftmaxFew; ++i) m = fmaxf(m, z[i]);
+        float s = 0.f, zt = 0.f;
+#pragma unroll
+        for (int i = 0; i < kSoftmaxFew; ++i) {
+            if (i < classes) s += expf(z[i] - m);
+            zt = i == t ? z[i] : zt;
+        }
+        const float lse = m + logf(s);
+        loss += lse - zt;
+#pragma unroll
+        for (int i = 0; i < kSoftmaxFew; ++i)
+            if (i < classes) dZ[static_cast<int64_t>(i) * lddz + c] = (expf(z[i] - lse) - (i == t ? 1.f : 0.f)) * inv_b;
+    }
+    softmax_mean(loss, inv_b, wave_loss, loss_out);
+}
+
+// The same for more classes.  Work-group b < n_tiles forms the gradient of 64 columns, a column per lane, wave w taking the
+// classes w, w + 16, ...: eight of a lane's logits are read at a time (and kept, up to 128 classes), and the waves meet in LDS for
+// the maximum and for the sum.  The loss needs every column, so the last work-group forms it on its own from all the
+// logits, with as many waves to a column as there are to spare: it waits for nobody, and one launch does.
+// (One thread per column that walked the classes three times: 49 us for 85 classes at batch 256.)
+// dZ may be Z: then the loss takes its own launch, before the gradients overwrite the logits.
+constexpr int kSoftmaxKept = 8;
+__device__ __forceinline__ float finite_or_zero(float m) { return m == -INFINITY ? 0.f : m; }   // (-Inf logits: exp(z - m) is 0, not NaN)
+
+__device__ __forceinline__ void softmax_loss(const float *Z, int64_t ldz, const int32_t *__restrict__ labels, int classes, int batch,
+                                             float *loss_out, float (&red)[2][kSoftmaxWaves][kWave], float (&wave_loss)[kSoftmaxWaves])
+{
+    const int lane = threadIdx.x & (kWave - 1), wv = wave_in_block();
+    int lg = 0;   // waves per column
+    while (lg < 4 && ((batch - 1) >> (10 - lg - 1)) == 0) ++lg;
+    const int share = wv & ((1 << lg) - 1), step = 1 << lg, wide = (kSoftmaxWaves >> lg) * kWave;
+    float loss = 0.f;
+    for (int base = 0; base < batch; base += wide) {
+        const int own = base + (wv >> lg) * kWave + lane, c = min(own, batch - 1);
+        float m = -INFINITY, s = 0.f;
+        for (int i0 = share; i0 < classes; i0 += step * kSoftmaxKept) {
+            float z[kSoftmaxKept], top = m;
+#pragma unroll
+            for (int u = 0; u < kSoftmaxKept; ++u) z[u] = Z[static_cast<int64_t>(min(i0 + u * step, classes - 1)) * ldz + c];
+#pragma unroll
+            for (int u = 0; u < kSoftmaxKept; ++u) top = i0 + u * step < classes ? fmaxf(top, z[u]) : top;
+            const float shift = finite_or_zero(top);
+            s *= expf(m - shift);
+#pragma unroll
+            for (int u = 0; u < kSoftmaxKept; ++u) s += i0 + u * step < classes ? expf(z[u] - shift) : 0.f;
+            m = top;
+        }
+        red[0][wv][lane] = m;
+        red[1][wv][lane] = s;
+        __syncthreads();
+        if (share == 0 && own < batch) {
+            float top = m;
+            for (int w = 1; w < step; ++w) top = fmaxf(top, red[0][wv + w][lane]);
+            const float shift = finite_or_zero(top);
+            float sum = 0.f;
+            for (int w = 0; w < step; ++w) sum += red[1][wv + w][lane] * expf(red[0][wv + w][lane] - shift);
+            loss += (top + logf(sum)) - Z[static_cast<int64_t>(labels[c]) * ldz + c];
+        }
+        __syncthreads();
+    }
+    softmax_mean(loss, 1.0f / static_cast<float>(batch), wave_loss, loss_out);
+}
+
+__global__ __launch_bounds__(kSoftmaxBlock) void softmax_ce_kernel(const float *Z, int64_t ldz, const int32_t *__restrict__ labels, int classes,
+                                                                   int batch, float *dZ, int64_t lddz, float *loss_out, const int n_tiles)
+{
+    __shared__ float red[2][kSoftmaxWaves][kWave];
+    __shared__ float wave_loss[kSoftmaxWaves];
+    if (static_cast<int>(blockIdx.x) == n_tiles) {
+        softmax_loss(Z, ldz, labels, classes, batch, loss_out, red, wave_loss);
+        return;
+    }
+    const int lane = threadIdx.x & (kWave - 1), wv = wave_in_block();
+    const int own = blockIdx.x * kWave + lane, c = min(own, batch - 1);
+    const int t = labels[c];
+    constexpr int kStep = kSoftmaxWaves * kSoftmaxKept;
+    float z[kSoftmaxKept];
+    auto fetch = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < kSoftmaxKept; ++u) z[u] = Z[static_cast<int64_t>(min(i0 + u * kSoftmaxWaves, classes - 1)) * ldz + c];
+    };
+    float m = -INFINITY;
+    for (int i0 = wv; i0 < classes; i0 += kStep) {
+        fetch(i0);
+#pragma unroll
+        for (int u = 0; u < kSoftmaxKept; ++u) m = fmaxf(m, z[u]);   // (past the end: the last class again)
+    }
+    red[0][wv][lane] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSoftmaxWaves; ++w) m = fmaxf(m, red[0][w][lane]);
+    float s = 0.f;
+    for (int i0 = wv; i0 < classes; i0 += kStep) {
+        if (classes > kStep) fetch(i0);
+#pragma unroll
+        for (int u = 0; u < kSoftmaxKept; ++u) s += i0 + u * kSoftmaxWaves < classes ? expf(z[u] - m) : 0.f;
+    }
+    red[1][wv][lane] = s;
+    __syncthreads();
+    s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSoftmaxWaves; ++w) s += red[1][w][lane];
+    const float lse = m + logf(s), inv_b = 1.0f / static_cast<float>(batch);
+    if (own >= batch) return;
+    for (int i0 = wv; i0 < classes; i0 += kStep) {
+        if (classes > kStep) fetch(i0);
+#pragma unroll
+        for (int u = 0; u < kSoftmaxKept; ++u) {
+            const int i = i0 + u * kSoftmaxWaves;
+            if (i < classes) dZ[static_cast<int64_t>(i) * lddz + c] = (expf(z[u] - lse) - (i == t ? 1.f : 0.f)) * inv_b;
+        }
     }
 }
 
@@ -2426,10 +2517,9 @@ hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
     return sddmm_pair_go<64, 4>(a, b, s);
 }
 
-// The transposed product t and the SDDMM g of one layer can share their gathers when t would run the
-// packed kernel inside column tiles on a mirror all of whose rows are short, its result mask is the
-// SDDMM's second operand (the output of the layer below), and the layer's partial buffer has a slice
-// per tile for the products in mirror order.
+// The transposed product t and the SDDMM g of one layer can share their gathers when its result mask, if any, is the
+// SDDMM's second operand (the output of the layer below), no mirror row outlasts the rest, and the layer's partial
+// buffer has a slice per tile for the products in mirror order.
 // Lanes per mirror row of the fused backward pass: the transposed product's own tiles where it has any, else one tile up to 128
 // columns, up to 256 where the operand is small or the rows are short (16384 x 2000 power-law at batch 256 in two tiles: 26 us, in one 29;
 // 12000^2 at 0.1 %: 27 and 24), and tiles of 128 beyond; its own tiles are widened to 128 columns
@@ -2756,14 +2846,18 @@ hipError_t launch_backward_prep(float *values_t, const float *values, const int3
 hipError_t launch_softmax_ce(const float *Z, int64_t ldz, const int32_t *labels, int32_t classes, int32_t batch,
                              float *dZ, int64_t lddz, float *loss, hipStream_t s)
 {
-    int threads = (batch + kWave - 1) / kWave * kWave;
-    if (threads > kSoftmaxBlock) threads = kSoftmaxBlock;
-    if (classes <= 16)
-        hipLaunchKernelGGL(softmax_ce_kernel<16>, dim3(1), dim3(threads), 0, s, Z, ldz, labels, classes, batch, dZ,
-                           lddz, loss);
-    else
-        hipLaunchKernelGGL(softmax_ce_kernel<0>, dim3(1), dim3(threads), 0, s, Z, ldz, labels, classes, batch, dZ,
-                           lddz, loss);
+    if (classes <= kSoftmaxFew) {
+        int threads = (batch + kWave - 1) / kWave * kWave;
+        if (threads > kSoftmaxBlock) threads = kSoftmaxBlock;
+        hipLaunchKernelGGL(softmax_ce_few_kernel, dim3(1), dim3(threads), 0, s, Z, ldz, labels, classes, batch, dZ, lddz, loss);
+        return hipGetLastError();
+    }
+    const int n_tiles = (batch + kWave - 1) / kWave;
+    const bool in_place = dZ < Z + static_cast<int64_t>(classes) * ldz && Z < dZ + static_cast<int64_t>(classes) * lddz;
+    if (in_place && loss) hipLaunchKernelGGL(softmax_ce_kernel, dim3(1), dim3(kSoftmaxBlock), 0, s, Z, ldz, labels, classes, batch, dZ, lddz, loss, 0);
+    const bool with_loss = loss && !in_place;
+    hipLaunchKernelGGL(softmax_ce_kernel, dim3(n_tiles + (with_loss ? 1 : 0)), dim3(kSoftmaxBlock), 0, s, Z, ldz, labels, classes, batch, dZ, lddz,
+                       loss, n_tiles);
     return hipGetLastError();
 }
 

@@ -146,3 +146,20 @@ def test_training_step_with_both_gradients_in_one_pass(nb, batch, hidden):
         m.close()
     for a, b in zip(*out):
         assert torch.allclose(a, b, rtol=1e-3, atol=2e-6 * max(1.0, float(b.abs().max())))
+
+
+@pytest.mark.parametrize("classes,batch", [(16, 65), (17, 1), (17, 64), (33, 129), (128, 63), (129, 512), (300, 513), (100, 1025)])
+def test_softmax_of_many_classes(nb, oracle, classes, batch):
+    import torch
+    rng = np.random.default_rng(classes)
+    Z = (rng.standard_normal((classes, batch)) * 3).astype(np.float32)
+    labels = rng.integers(0, classes, size=batch).astype(np.int32)
+    ref, Sl, dZr, SdZ = oracle.softmax_ce(Z, labels)
+    lab = torch.as_tensor(labels).cuda()
+    Zd, dZd = nb.to_dense(Z), nb.dense(classes, batch)
+    for out in (dZd, Zd):   # apart, in place
+        loss = torch.zeros(1, device="cuda")
+        nb.softmax_cross_entropy(Zd, lab, classes, batch, out, loss)
+        torch.cuda.synchronize()
+        close(out.cpu().numpy(), dZr, SdZ, what="dZ")
+        assert abs(float(loss.item()) - ref) <= 1e-5 * Sl
