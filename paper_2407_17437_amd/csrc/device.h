@@ -71,11 +71,16 @@ __device__ __forceinline__ float row16_sum(float x)
     return x;
 }
 
-// Sum over groups of G lanes (8: per half row; 16: per row; 64: whole wave, returned wave-uniform).
+// Sum over groups of G lanes (4: per quad; 8: per half row; 16: per row; 64: whole wave, returned wave-uniform).
 template <int G>
 __device__ __forceinline__ float group_sum(float x)
 {
-    static_assert(G == 8 || G == 16 || G == 32 || G == 64, "group sizes with a reduction");
+    static_assert(G == 4 || G == 8 || G == 16 || G == 32 || G == 64, "group sizes with a reduction");
+    if constexpr (G == 4) {
+        x += dpp<0xB1>(x);   // quad_perm [1,0,3,2]
+        x += dpp<0x4E>(x);   // quad_perm [2,3,0,1]
+        return x;
+    }
     if constexpr (G == 8) {
         x += dpp<0xB1>(x);   // quad_perm [1,0,3,2]
         x += dpp<0x4E>(x);   // quad_perm [2,3,0,1]

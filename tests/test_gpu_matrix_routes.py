@@ -163,3 +163,12 @@ def test_softmax_of_many_classes(nb, oracle, classes, batch):
         torch.cuda.synchronize()
         close(out.cpu().numpy(), dZr, SdZ, what="dZ")
         assert abs(float(loss.item()) - ref) <= 1e-5 * Sl
+
+
+@pytest.mark.parametrize("batch", [5, 15, 16, 17, 31, 32, 33])
+def test_narrow_batches(nb, oracle, batch):
+    # rows of every class: shared by 1 to 16 waves, and cut into work-groups
+    lens = np.concatenate([np.arange(0, 300, 7), [1, 63, 64, 65, 900, 1400, 1400]])
+    indptr, indices = wl.pattern_from_row_nnz(lens, 1400, seed=batch)
+    lay = wl.SparseLayerData(len(lens), 1400, indptr, indices, wl.init_values(indptr, 1), np.ones(len(lens), np.float32), batch % 2 == 0)
+    check_layer(nb, oracle, lay, batch, ld=batch)
