@@ -122,7 +122,7 @@ struct nerva_layer {
     size_t build_work_ints = 0;
     BindResult *bind_result = nullptr;
     // owned: partial rows of huge-row work-groups, shared by the forward and the transposed product
-    float *scratch = nullptr;
+    float *scratch_mem = nullptr, *scratch = nullptr;   // tickets of the huge rows, partial rows (SpmmArgs::scratch)
     size_t scratch_floats = 0;
     int64_t scratch_ld = 0;
     // owned: per-tile partial products of the column-tiled SDDMM (only for layers whose input
@@ -516,7 +516,7 @@ struct PlanRoom {
     {
         return static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks + rest_blocks) + huge_rows + rows_by_length)) +
                static_cast<size_t>(ranges) * (kStageRangeRows * (cblocks + 2) + 4) + static_cast<size_t>(dense_rows + dense_flags) +
-               (dense_flags ? static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks) + huge_rows)) : 0);
+               (dense_flags ? static_cast<size_t>(4 * kWavesPerBlock * (blocks + long_blocks)) : 0);
     }
     // the tables at `mem` (16-byte records first)
     PlanTables at(int32_t *mem) const
@@ -528,11 +528,10 @@ struct PlanRoom {
         t.rest_waves = r; r += kWavesPerBlock * rest_blocks;
         t.huge_rows = r; r += huge_rows;
         t.rows_by_length = r; r += rows_by_length;
-        t.other_waves = t.other_long_waves = t.other_huge_rows = nullptr;
+        t.other_waves = t.other_long_waves = nullptr;
         if (dense_flags) {
             t.other_waves = r; r += kWavesPerBlock * blocks;
             t.other_long_waves = r; r += kWavesPerBlock * long_blocks;
-            t.other_huge_rows = r; r += huge_rows;
         }
         int32_t *i = reinterpret_cast<int32_t *>(r);
         t.dense_rows = i; i += dense_rows;
@@ -585,7 +584,7 @@ void free_layer_buffers(nerva_layer *l)
     free_pattern_buffers(l->spare);
     (void)hipFree(l->build_work);
     if (l->bind_result) (void)hipHostFree(l->bind_result);
-    (void)hipFree(l->scratch);
+    (void)hipFree(l->scratch_mem);
     (void)hipFree(l->partial);
     (void)hipFree(l->dz);
     (void)hipFree(l->dense);
@@ -819,6 +818,7 @@ struct BuiltPattern {
     int64_t partial_stride = 0, partial_db_at = 0;
     int32_t partial_tiles = 0;
     int64_t scratch_ld = 0, full_scratch_ld = 0;
+    float *scratch = nullptr;
     bool full = false;
 };
 
@@ -886,6 +886,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     const BindResult &R = *l->bind_result;
     if (R.status[0] != 0) return csr_status_error(R.status);
     out->plan = plan_view(p.side[0].tables, R.plan[0], cols, nnz, R.plan[1].hot_nnz, mode);
+    bool more_work = false;   // launches after the wait
     B.split = DenseSplit{};
     if (R.plan[0].n_dense > 0) {
         const PlanTables &t = p.side[0].tables;
@@ -900,9 +901,9 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         B.split.others = out->plan;
         B.split.others.waves = t.other_waves;
         B.split.others.long_waves = t.other_long_waves;
-        B.split.others.huge_rows = t.other_huge_rows;
         out->plan.staged_rows = nullptr;   // (it covers the other rows only)
         HIP_TRY(launch_pattern_table(indptr, indices, D.list, D.n, D.words, reinterpret_cast<uint2 *>(B.row_table), nullptr, s));
+        more_work = true;
     }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
 
@@ -927,7 +928,14 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         }
         const int64_t slots = out->plan.n_huge_blocks > out->plan_t.n_huge_blocks ? out->plan.n_huge_blocks : out->plan_t.n_huge_blocks;
         out->scratch_ld = round_up(max_batch, 64);
-        if (slots > 0) HIP_TRY(reserve(&l->scratch, &l->scratch_floats, static_cast<size_t>(slots) * out->scratch_ld));
+        if (slots > 0) {
+            const int64_t huge = std::max(out->plan.n_huge_rows, out->plan_t.n_huge_rows);
+            const int64_t tickets = round_up(huge * huge_row_tickets(out->scratch_ld), 64);
+            HIP_TRY(reserve(&l->scratch_mem, &l->scratch_floats, static_cast<size_t>(tickets + slots * out->scratch_ld)));
+            HIP_TRY(hipMemsetAsync(l->scratch_mem, 0, static_cast<size_t>(tickets) * 4, s));
+            out->scratch = l->scratch_mem + tickets;
+            more_work = true;
+        }
         out->full = rows <= kFullMaxRows && static_cast<int64_t>(nnz) == static_cast<int64_t>(rows) * cols;
         out->full_scratch_ld = round_up(max_batch, 64);
         if (out->full && !l->full_scratch) {
@@ -935,6 +943,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
             HIP_TRY(hipMalloc(&l->full_scratch, static_cast<size_t>(slices) * rows * out->full_scratch_ld * 4));
         }
     }
+    if (more_work) HIP_TRY(hipStreamSynchronize(s));   // (a product on another stream may follow)
     return NERVA_OK;
 }
 
@@ -951,7 +960,7 @@ static void adopt_pattern(nerva_layer *l, int32_t nnz, const int32_t *indptr, co
     l->values_t = reinterpret_cast<float *>(l->cur.mirror_mem + 3 * n64);
     l->plan = bp.plan; l->plan_t = bp.plan_t;
     l->partial_stride = bp.partial_stride; l->partial_db_at = bp.partial_db_at; l->partial_tiles = bp.partial_tiles;
-    l->scratch_ld = bp.scratch_ld;
+    l->scratch = bp.scratch; l->scratch_ld = bp.scratch_ld;
     l->full_scratch_ld = bp.full_scratch_ld;
     l->full = bp.full;
     l->mirror_stale = false;

@@ -11,12 +11,12 @@ constexpr int kWavesPerBlock = 16;   // 1024 threads
 // A work-group has kWavesPerBlock waves.  Ordinary rows: the work-group serves
 // (kWavesPerBlock >> lg) rows, 2^lg waves per row, each wave taking a contiguous share of the
 // row's stored entries.  Huge rows (more entries than a whole work-group should take) are cut
-// into several work-groups; each produces a partial result that a second, small kernel adds
+// into several work-groups; each leaves a partial result, and the last of them to do so adds them
 // up in share order.  Huge work-groups come first, so blockIdx.x is also their scratch slot.
 struct RowBlocks {
     const int4 *huge_rows;     // [n_huge_rows] {row, first work-group, number of work-groups, 0}
     const int4 *waves;         // [n_blocks * kWavesPerBlock] the partition, spelled out per wave:
-                               // {row or -1, first entry, end entry, part | lg << 4 | lead << 8 | huge << 9}
+                               // {row or -1, first entry, end entry, part | lg << 4 | lead << 8 | huge << 9 | index in huge_rows << 10}
     int32_t n_blocks;
     int32_t n_huge_rows;
     int32_t n_huge_blocks;
@@ -122,8 +122,8 @@ struct SpmmArgs {
     int32_t relu;            // clamp the result at zero
     int32_t wide_offsets;    // an operand spans 4 GiB or more (set by the launch)
     int32_t nnz;             // length of indices/values
-    float *scratch;          // partial rows of huge-row work-groups, (n_huge_blocks, scratch_ld)
-    int64_t scratch_ld;
+    float *scratch;          // partial rows of huge-row work-groups, (n_huge_blocks, scratch_ld); before it, growing downwards, the
+    int64_t scratch_ld;      // tickets of the huge rows (huge_row_tickets), all 0 between launches
     // Only for a matrix that stores every entry and has at most kFullMaxRows rows (a saturated
     // output layer): values[] is then the row-major dense matrix, and the product streams the
     // operand once for all rows instead of gathering it once per row.  Partial results of the
@@ -139,6 +139,8 @@ struct SpmmArgs {
     float *ce_loss_cols;       // [batch]
     const DenseSplit *split;   // (for the launch) or nullptr
 };
+// tickets per huge row, one per 32 columns
+__host__ __device__ inline int64_t huge_row_tickets(int64_t scratch_ld) { return scratch_ld / 32; }
 bool spmm_softmax_epilogue_ok(const SpmmArgs &a);
 constexpr int32_t kFullMaxRows = 16;
 constexpr int32_t kFullSlice = 128;   // columns of W (rows of the operand) per work-group
@@ -367,7 +369,7 @@ struct PlanTables {
     int32_t *staged_rows, *staged_groups, *staged_ends;
     int32_t *dense_rows;             // [room for the rows of dense_len entries or more] ascending
     uint8_t *dense_flag;             // [rows]
-    int4 *other_waves, *other_long_waves, *other_huge_rows;   // copies of the tables above with row -1 in the place of dense rows
+    int4 *other_waves, *other_long_waves;   // copies of the tables above with row -1 in the place of dense rows
 };
 // Records of PlanTables::rows_by_length: padded, so that sets of up to 64 rows from any row on can be read.
 __host__ __device__ inline int64_t rows_table_size(int32_t rows) { return (static_cast<int64_t>(rows) + 63) / 64 * 64 + 64; }

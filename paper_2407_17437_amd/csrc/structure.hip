@@ -725,7 +725,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 __device__ __forceinline__ int4 wave_record(const PlanSide &S, const PlanCounts &C, const int32_t (&cls)[5], int32_t first, int32_t huge_blocks,
                                             int32_t cap, int32_t b, int w)
 {
-    int32_t row = -1, lg = 4, p0 = 0, p1 = 0;
+    int32_t row = -1, lg = 4, p0 = 0, p1 = 0, index = 0;
     bool lead = false;
     const bool huge = b < huge_blocks;
     if (huge) {
@@ -736,6 +736,7 @@ __device__ __forceinline__ int4 wave_record(const PlanSide &S, const PlanCounts 
         }
         const int4 h = S.tables.huge_rows[lo];
         row = h.x;
+        index = lo;
         const int32_t q = b - h.y, len = S.indptr[row + 1] - S.indptr[row], share = (len + h.z - 1) / h.z;
         p0 = S.indptr[row] + min(q * share, len);
         p1 = S.indptr[row] + min(q * share + share, len);
@@ -764,7 +765,7 @@ __device__ __forceinline__ int4 wave_record(const PlanSide &S, const PlanCounts 
     per = (per + 3) / 4 * 4;
     const int32_t s0 = min(static_cast<int64_t>(p0) + static_cast<int64_t>(part) * per, static_cast<int64_t>(p1));
     const int32_t s1 = min(static_cast<int64_t>(s0) + per, static_cast<int64_t>(p1));
-    return make_int4(row, s0, s1, part | (lg << 4) | (lead ? 256 : 0) | (huge ? 512 : 0));
+    return make_int4(row, s0, s1, part | (lg << 4) | (lead ? 256 : 0) | (huge ? 512 : 0) | (index << 10));
 }
 
 // A record of a partition as the launch of the rows that are not dense sees it.
@@ -810,9 +811,6 @@ __global__ __launch_bounds__(kStageRangeRows) void plan_fill_kernel(const PlanAr
         if (tid == 0) S.tables.staged_groups[q] = (m + 3 * nq + 63) / 64;
         __syncthreads();
     }
-    if (C.n_dense > 0)
-        for (int32_t k = blockIdx.x * kStageRangeRows + tid; k < C.n_huge_rows; k += gridDim.x * kStageRangeRows)
-            S.tables.other_huge_rows[k] = without_dense(S, S.tables.huge_rows[k]);
     const int32_t cap = min(max(A.nnz / 16384, 8), 64) * kWavesPerBlock;
     const int64_t n_w = static_cast<int64_t>(C.n_blocks) * kWavesPerBlock, n_l = n_w + static_cast<int64_t>(C.n_long_blocks) * kWavesPerBlock;
     const int64_t n_r = n_l + static_cast<int64_t>(C.n_rest_blocks) * kWavesPerBlock, n_all = n_r + rows_table_size(S.rows);
