@@ -910,7 +910,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     // scratch buffers of the products (they hold nothing between calls: grown in place)
     {
         // room for the column-tiled SDDMM at max_batch columns, if that batch would be tiled
-        const int w = tile_columns(cols, max_batch, nnz, rows, out->plan.hot_share, false, true);
+        const int w = tile_columns(cols, max_batch, nnz, rows, out->plan.staged_longest_row, out->plan.hot_share, false, true);
         int32_t tiles = w > 0 ? (max_batch + w - 1) / w : 0;
         if ((out->plan.staged_rows || B.split.others.staged_rows) && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
         // ... and for the backward pass on one gather stream (products in mirror order, a slice per column tile)

@@ -2282,7 +2282,7 @@ hipError_t spmm_grouped_go(const SpmmArgs &a, hipStream_t s)
 int spmm_tile_group(const SpmmArgs &a)
 {
     if (static_cast<int64_t>(a.blocks.n_blocks) * ((a.batch + 31) / 32 + 8) >= (1ll << 31)) return 0;
-    return tile_columns(a.x_rows, a.batch, a.nnz, a.rows, a.blocks.hot_share, a.XM != nullptr) / 4;
+    return tile_columns(a.x_rows, a.batch, a.nnz, a.rows, a.blocks.staged_longest_row, a.blocks.hot_share, a.XM != nullptr) / 4;
 }
 
 template <int GS>
@@ -2497,7 +2497,7 @@ hipError_t sddmm_pair_go(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 
 int sddmm_tile_columns(const SddmmArgs &a);
 
-int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, float hot_share, bool masked, bool for_sddmm)
+static int tile_columns_wanted(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, bool skewed, float hot_share, bool masked, bool for_sddmm)
 {
     const int64_t budget = (masked ? 5 : 10) * (1 << 18);  // 2.5 MiB (half of it with a mask operand)
     const int64_t row_bytes = static_cast<int64_t>(x_rows) * 4;
@@ -2507,7 +2507,9 @@ int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, float
     if (rows <= 256) return 0;
     // (the SDDMM, whose second operand is a row per matrix row and not a gather, still gains from 128-column
     // tiles when they fill a whole L2: config 4's 8192-row operand, 120 -> 113 us, where the product loses 7 %)
-    if (row_bytes * 128 <= (for_sddmm ? (4ll << 20) : budget) && batch > 128) return 128;
+    // (and so do rows of very different lengths, most of them too short for the pass over them that every tile costs:
+    // 9106 x 9383 power-law at 0.1 %, batch 1000: forward 63 us in 64-column tiles, 49 in 128; SDDMM 79 and 54)
+    if (row_bytes * 128 <= (for_sddmm || skewed ? (5ll << 20) : budget) && batch > 128) return 128;
     if (row_bytes * 64 <= budget && batch > 64) return 64;
     if (batch <= 32) return 0;
     // Short rows on an operand whose 64-column tile (4 MiB for 16384 rows) no longer fits beside the rest in an L2: wide tiles
@@ -2538,6 +2540,21 @@ int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, float
     if (nnz >= static_cast<int64_t>(rows) * 1024) return 32;
     if (nnz >= static_cast<int64_t>(rows) * 128 && hot_share < 0.5f && row_bytes * batch >= (16ll << 20)) return 32;
     return 0;
+}
+
+int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, int32_t longest_row, float hot_share, bool masked, bool for_sddmm)
+{
+    const bool skewed = static_cast<int64_t>(longest_row) * rows > 16 * nnz;
+    const int w = tile_columns_wanted(x_rows, batch, nnz, rows, skewed, hot_share, masked, for_sddmm);
+    if (w == 0 || (batch + w - 1) / w >= 8) return w;
+    // Fewer tiles than XCDs: every L2 sees every tile, and an eighth of the gathers from it.  The tile then pays where an L2 gathers
+    // a row of it several times and the untiled operand is well beyond the L2; on rows of very different lengths only
+    // for operands beyond all L2s or long rows throughout.  Untiled / in tiles: 9106 x 9383 at 0.3 % (27 entries per operand row), batch
+    // 100 / 182 / 400: forward 11.2 / 17.7 / 40.5 against 16.1 / 18.4 / 39.7 us; at 0.1 %: SDDMM 7.8 / 11.2 / 22.4 against 10.4 / 16.1 / 28.1; power-law
+    // 12000 x 3000 at 0.3 %, batch 256 / 700: forward 12.3 / 32.6 against 22.1 / 45.7, 3000 x 12000 at 1 %, batch 700: 102 against 87.
+    const int64_t operand = static_cast<int64_t>(x_rows) * batch * 4;
+    const bool pays = skewed ? operand >= (32ll << 20) || (operand >= (8ll << 20) && nnz >= 128ll * x_rows) : operand >= (6ll << 20) && nnz >= 24ll * x_rows;
+    return pays ? w : 0;
 }
 
 bool can_pair(const SpmmArgs &a, const SddmmArgs &b)
@@ -2810,7 +2827,7 @@ int sddmm_tile_columns(const SddmmArgs &a)
     if (!a.partial || a.skip_products || a.dense || !sddmm_offsets_ok(a)) return 0;  // (the finish pass does not know an entry's row)
     // the operand rows an entry gathers are named by its column index: the matrix's own partition
     // carries the share of the most referenced ones
-    const int w = tile_columns(a.x_rows, a.batch, a.nnz, a.rows, a.blocks.hot_share, false, true);
+    const int w = tile_columns(a.x_rows, a.batch, a.nnz, a.rows, a.blocks.staged_longest_row, a.blocks.hot_share, false, true);
     if (w == 0) return 0;
     const int n_tiles = (a.batch + w - 1) / w;
     if (n_tiles > a.partial_tiles) return 0;
