@@ -1249,7 +1249,7 @@ int mlp_create(nerva_mlp **out, int32_t n_layers, nerva_layer *const *layers, fl
     m->max_batch = max_batch;
     m->flags = flags;
     const nerva_layer *last = layers[n_layers - 1];
-    m->head = n_layers >= 2 && !(flags & NERVA_MLP_SEPARATE_HEAD) && head_ok(last->rows, last->cols, last->nnz);
+    m->head = n_layers >= 2 && !(flags & NERVA_MLP_SEPARATE_HEAD) && head_ok(last->rows, last->cols, last->nnz, 1);
     if (m->head || (n_layers >= 2 && last->full && last->rows <= kFullMaxRows)) {   // per-column losses between two launches of a step
         const size_t bytes = static_cast<size_t>(max_batch) * 4;
         hipError_t e = hipMalloc(&m->head_scratch, bytes);
@@ -1457,7 +1457,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
 
     // feedforward, then the loss gradient / batch size
     const nerva_layer *last = mlp->layers[n - 1];
-    const bool head = mlp->head && head_ok(last->rows, last->cols, last->nnz);  // (a rebind may have grown the layer)
+    const bool head = mlp->head && head_ok(last->rows, last->cols, last->nnz, batch);  // (a rebind may have grown the layer)
     bool ce_fused = false;  // softmax cross-entropy in the finish pass of the output layer's forward product
     int bias_done = -1;     // a layer whose biases the launch that formed its dZ has already updated
     // backpropagate and optimize, last layer first.  Layer l's transposed product T_l runs before

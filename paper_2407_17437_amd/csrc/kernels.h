@@ -473,7 +473,7 @@ struct HeadArgs {
     int64_t lddx;
     float *loss_cols;                     // [batch]: per-column losses; a later launch takes their mean (SddmmArgs)
 };
-bool head_ok(int32_t rows, int32_t cols, int32_t nnz);
+bool head_ok(int32_t rows, int32_t cols, int32_t nnz, int32_t batch);
 hipError_t launch_head(const HeadArgs &a, hipStream_t s);
 
 }  // namespace nerva

@@ -2941,9 +2941,13 @@ hipError_t launch_softmax_ce(const float *Z, int64_t ldz, const int32_t *labels,
 }
 
 // One work-group re-reads the whole layer for its 4 columns: only for layers of a few thousand entries.
-bool head_ok(int32_t rows, int32_t cols, int32_t nnz)
+// Its accesses to the layer's input and to dX are 16 bytes per row, so it loses to three launches on long layers and wide batches: steps of
+// 300-cols-10 with it / without, at batch 16, 100, 1024: 1024 columns and 1 %: 13.0 / 18.8, 13.9 / 18.1, 26.1 / 26.1 us; 2048: 15.2 / 19.0,
+// 17.5 / 19.1, 36.8 / 32.3 (10 %: 18.7 / 19.8, 21.3 / 21.0, 46.5 / 38.2); 8192: 33.7 / 24.3, 42.8 / 25.1, 101 / 51.
+bool head_ok(int32_t rows, int32_t cols, int32_t nnz, int32_t batch)
 {
-    return rows > 0 && rows <= kHeadMaxRows && cols > 0 && nnz <= 8192;
+    return rows > 0 && rows <= kHeadMaxRows && cols > 0 && nnz <= 8192 &&
+           static_cast<double>(cols) * cols * (batch + 200.) <= 1.25e9;
 }
 
 hipError_t launch_head(const HeadArgs &a, hipStream_t s)
