@@ -165,8 +165,8 @@ def test_softmax_of_many_classes(nb, oracle, classes, batch):
         assert abs(float(loss.item()) - ref) <= 1e-5 * Sl
 
 
-@pytest.mark.parametrize("batch", [5, 15, 16, 17, 31, 32, 33])
-def test_narrow_batches(nb, oracle, batch):
+@pytest.mark.parametrize("batch", [5, 15, 16, 17, 31, 32, 33, 48, 49, 77, 96, 97, 129, 192, 193, 257, 384, 385, 513, 768, 769])
+def test_lane_groups_of_every_batch(nb, oracle, batch):
     # rows of every class: shared by 1 to 16 waves, and cut into work-groups
     lens = np.concatenate([np.arange(0, 300, 7), [1, 63, 64, 65, 900, 1400, 1400]])
     indptr, indices = wl.pattern_from_row_nnz(lens, 1400, seed=batch)
