@@ -1126,17 +1126,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
     if (rc == NERVA_OK && batch > layer->max_batch) rc = fail(NERVA_ERR_SHAPE, "batch %d exceeds the layer's max_batch %d", batch, layer->max_batch);
     if (rc != NERVA_OK) return rc;
     hipStream_t s = as_stream(stream);
-    // dZ of a ReLU layer: formed once where a transposed product would gather its rows from two operands, unless the
-    // matrix is so sparse that the pass over dY and Y costs more than the gathers it saves
-    const bool form_dz = dX && relu && layer->dz && batch > 4 && layer->nnz >= 4 * static_cast<int64_t>(layer->rows);
-    if (form_dz) {
-        HIP_TRY(launch_backward_prep(layer->values_t, layer->values, layer->perm, layer->nnz, dY, lddy, Y, ldy, layer->dz, layer->dz_ld,
-                                     layer->rows, batch, s));
-        layer->mirror_stale = false;
-        dY = layer->dz;
-        lddy = static_cast<int32_t>(layer->dz_ld);
-    }
-    const bool mask = relu && !form_dz;  // dY still is the gradient of the output
+    bool form_dz = false, mask = relu;   // mask: dY still is the gradient of the output
     auto make_t = [&] {
         SpmmArgs a{};
         a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.scratch_ld = layer->scratch_ld;
@@ -1162,10 +1152,23 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
         a.split = split_of(layer);
         return a;
     };
+    // (a small layer takes both gradients, and the mask, in one launch)
+    const bool in_one = relu && dX && dvalues && !use_dense(layer, batch) && backward_fused_ok(make_t(), make_g(), true);
+    // dZ of a ReLU layer: formed once where a transposed product would gather its rows from two operands, unless the
+    // matrix is so sparse that the pass over dY and Y costs more than the gathers it saves
+    form_dz = !in_one && dX && relu && layer->dz && batch > 4 && layer->nnz >= 4 * static_cast<int64_t>(layer->rows);
+    if (form_dz) {
+        HIP_TRY(launch_backward_prep(layer->values_t, layer->values, layer->perm, layer->nnz, dY, lddy, Y, ldy, layer->dz, layer->dz_ld,
+                                     layer->rows, batch, s));
+        layer->mirror_stale = false;
+        dY = layer->dz;
+        lddy = static_cast<int32_t>(layer->dz_ld);
+    }
+    mask = relu && !form_dz;
     if (dX && use_dense(layer, batch) && !mask) {
         HIP_TRY(refresh_dense_copies(layer, s));
         HIP_TRY(dense_transposed(layer, dY, lddy, dX, lddx, nullptr, 0, batch, s));
-    } else if (dX && dvalues && !mask && backward_fused_ok(make_t(), make_g(), true)) {
+    } else if (dX && dvalues && (in_one || (!mask && backward_fused_ok(make_t(), make_g(), true)))) {
         if (!form_dz && !backward_fused_refreshes(make_t(), make_g())) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
         layer->mirror_stale = false;
         HIP_TRY(launch_backward_fused(make_t(), make_g(), true, s));

@@ -217,6 +217,8 @@ struct BackwardArgs {
     const float *values;         // mirror values
     const float *dZ;             // (rows of W, lddz): gathered
     int64_t lddz;
+    const float *ZM;             // optional: dZ is multiplied by [ZM > 0]
+    int64_t ldzm;
     const float *X;              // (cols of W, ldx): the layer's input; second operand of the products and mask of dX
     int64_t ldx;
     float *dX;                   // (cols of W, lddx)

@@ -1553,20 +1553,25 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
 constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and smaller groups schedule finer (measured on the wide MLP:
                               // 134 / 138 / 142 us with 4 / 8 / 16 waves; gather depth 4 instead of 8 and a register cap of 64 change nothing)
 
-template <int U, int GS>
-__device__ __forceinline__ void bwd_pass(gmem_ptr Zg, int src, int my_ro, float my_w, uint32_t off, const float4 &ax, int it0, int lig,
+template <int U, int GS, bool XMASK>
+__device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, float my_w, uint32_t off, const float4 &ax, int it0, int lig,
                                          float (&acc)[4], float &res)
 {
-    uint32_t ro[U];
+    uint32_t ro[U], mo[U];
     float w[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         ro[u] = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src + u * 4, my_ro));
+        if constexpr (XMASK) mo[u] = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src + u * 4, my_mo));
         w[u] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(src + u * 4, __builtin_bit_cast(int, my_w)));
     }
     float4 x[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) x[u] = gload4(Zg, ro[u] + off);
+    if constexpr (XMASK) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = keep_where_positive(x[u], gload4(Mg, mo[u] + off));
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         acc[0] = fmaf(w[u], x[u].x, acc[0]);
@@ -1588,7 +1593,9 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
         float s = 0.f;
         for (int c = lane * 4; c < a.batch; c += kWave * 4) {
             const int first = four_columns(c, a.batch);
-            const float4 z = drop_shared(ld4(zr + first), c, first);
+            float4 z = ld4(zr + first);
+            if (a.ZM) z = keep_where_positive(z, ld4(a.ZM + i * a.ldzm + first));
+            z = drop_shared(z, c, first);
             s += (z.x + z.y) + (z.z + z.w);
         }
         s = group_sum<kWave>(s);
@@ -1604,19 +1611,26 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
     }
 }
 
-// ONE: a single column tile -- the products are whole and are stored as the gradient by the work-groups that form them, and
-// the work-groups after those of the rows sum the rows of dZ: there is no second pass.
-template <int GS, bool ONE>
+// Otherwise than in kBackwardTiles there is no second pass -- the products are whole and are stored as the gradient by the work-groups that form them, and
+// the work-groups after those of the rows sum the rows of dZ.  For a single column tile, or where the rows are no longer than
+// the lane groups and the matrix is small: then a wave takes its entries through all tiles.  XMASK: dZ is dY times
+// [Y > 0], gathered from both.
+enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
+template <int GS, BackwardPass PASS, bool XMASK>
 __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
                                                                           const int n_pack_blocks, const int lg_split)
 {
+    constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped;
     if (ONE && static_cast<int>(blockIdx.x) >= n_pack_blocks) {
         backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_pack_blocks) * kBwdWaves + wave_in_block(),
                           static_cast<int64_t>(gridDim.x - n_pack_blocks) * kBwdWaves);
         return;
     }
     int tile, rb;
-    if (spread) {
+    if constexpr (ONE) {
+        tile = 0;
+        rb = blockIdx.x;
+    } else if (spread) {
         const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
         tile = (k / n_pack_blocks) * 8 + xcd;
         rb = k % n_pack_blocks;
@@ -1626,17 +1640,12 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     }
     if (tile >= n_tiles) return;
     constexpr int NE = kWave / GS;
-    const int col0 = tile * GS * 4;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = wave_in_block();
     const int grp = lane / GS;
     const int lig = lane % GS;
-    const int own_col = col0 + lig * 4;
-    const bool on = own_col < a.batch;
-    const int col = four_columns(on ? own_col : col0, a.batch);
-    const uint32_t off = static_cast<uint32_t>(col) * 4u;
-    const uint32_t ldzb = static_cast<uint32_t>(a.lddz) * 4u;
-    const gmem_ptr Zg = as_gmem(a.dZ);
+    const uint32_t ldzb = static_cast<uint32_t>(a.lddz) * 4u, ldmb = XMASK ? static_cast<uint32_t>(a.ldzm) * 4u : 0u;
+    const gmem_ptr Zg = as_gmem(a.dZ), Mg = as_gmem(a.ZM);
     const int per_set = NE >> lg_split, part = grp & ((1 << lg_split) - 1);   // rows per wave; the group's share of its row
     const int n_sets = (a.rows + per_set - 1) / per_set;
     const int src0 = grp * GS * 4;
@@ -1653,7 +1662,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
         if (ONE || a.refresh) at = a.perm[p];
         if (a.refresh) {   // uniform
             w = a.refresh[at];
-            if (ok && tile == 0) a.w_t[p] = w;
+            if (ok && (ONE || tile == 0)) a.w_t[p] = w;
         } else {
             w = a.values[p];
         }
@@ -1665,63 +1674,76 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
         const int4 d = a.blocks.rows_by_length[set * per_set + (grp >> lg_split)];  // the table is padded to whole sets
         const int row = d.x, s0 = d.y, len = d.z;
         const int maxlen = __builtin_amdgcn_readfirstlane(len);  // group 0 holds the set's longest row
-        // the group's row of X: the second operand of its entries' products, and the mask of its result;
-        // lanes beyond the batch hold zeros, so that the columns they re-read add nothing to a product
-        float4 ax = make_float4(0.f, 0.f, 0.f, 0.f), mask = ax;
-        if (row >= 0 && on) {
-            mask = ld4(a.X + static_cast<int64_t>(row) * a.ldx + col);
-            ax = drop_shared(mask, own_col, col);
-        }
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        int cur_j, cur_at = 0;
-        float cur_w, cur_v = 0.f;
-        fetch(s0, len, 0, cur_j, cur_w, cur_at, cur_v);
-        for (int base = 0; base < maxlen; base += GS << lg_split) {
-            int next_j = 0, next_at = 0;
-            float next_w = 0.f, next_v = 0.f;
-            if (base + (GS << lg_split) < maxlen)  // wave-uniform: one chunk ahead
-                fetch(s0, len, base + (GS << lg_split), next_j, next_w, next_at, next_v);
-            const int my_ro = static_cast<int>(static_cast<uint32_t>(cur_j) * ldzb);
-            const int steps = min(GS, maxlen - base);
-            float res = 0.f;
-            int src = src0;
-            int u0 = 0;
-            for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS>(Zg, src, my_ro, cur_w, off, ax, u0, lig, acc, res);
-            if (u0 + 4 <= steps) {
-                bwd_pass<4, GS>(Zg, src, my_ro, cur_w, off, ax, u0, lig, acc, res);
-                u0 += 4; src += 16;
-            }
-            if (u0 + 2 <= steps) {
-                bwd_pass<2, GS>(Zg, src, my_ro, cur_w, off, ax, u0, lig, acc, res);
-                u0 += 2; src += 8;
-            }
-            if (u0 < steps) bwd_pass<1, GS>(Zg, src, my_ro, cur_w, off, ax, u0, lig, acc, res);
-            const int e = base + part * GS + lig;
-            if (row >= 0 && e < len) {
-                if constexpr (ONE) {
-                    if (a.g) a.g[cur_at] = res;
-                    if (a.fused) {
-                        momentum_step(cur_w, cur_v, res, a.lr, a.momentum, a.nesterov);
-                        a.w[cur_at] = cur_w;
-                        a.velocity[cur_at] = cur_v;
-                        a.w_t[s0 + e] = cur_w;
-                    }
-                } else {
-                    gp[s0 + e] = res;  // GS consecutive entries of the row: one coalesced store
+        float whole = 0.f;   // the lane's product over all tiles
+        for (int tile_now = tile; tile_now < (LOOPED ? n_tiles : tile + 1); ++tile_now) {
+                const int col0 = tile_now * GS * 4, own_col = col0 + lig * 4;
+                const bool on = own_col < a.batch;
+                const int col = four_columns(on ? own_col : col0, a.batch);
+                const uint32_t off = static_cast<uint32_t>(col) * 4u;
+                // the group's row of X: the second operand of its entries' products, and the mask of its result;
+                // lanes beyond the batch hold zeros, so that the columns they re-read add nothing to a product
+                float4 ax = make_float4(0.f, 0.f, 0.f, 0.f), mask = ax;
+                if (row >= 0 && on) {
+                    mask = ld4(a.X + static_cast<int64_t>(row) * a.ldx + col);
+                    ax = drop_shared(mask, own_col, col);
                 }
-            }
-            cur_j = next_j;
-            cur_w = next_w;
-            cur_at = next_at;
-            cur_v = next_v;
-        }
-        for (int d = GS; d < GS << lg_split; d <<= 1)   // the shares of a row, in one fixed order
+                float acc[4] = {0.f, 0.f, 0.f, 0.f};
+                int cur_j, cur_at = 0;
+                float cur_w, cur_v = 0.f;
+                fetch(s0, len, 0, cur_j, cur_w, cur_at, cur_v);
+                for (int base = 0; base < maxlen; base += GS << lg_split) {
+                    int next_j = 0, next_at = 0;
+                    float next_w = 0.f, next_v = 0.f;
+                    if (base + (GS << lg_split) < maxlen)  // wave-uniform: one chunk ahead
+                        fetch(s0, len, base + (GS << lg_split), next_j, next_w, next_at, next_v);
+                    const int my_ro = static_cast<int>(static_cast<uint32_t>(cur_j) * ldzb);
+                    const int my_mo = XMASK ? static_cast<int>(static_cast<uint32_t>(cur_j) * ldmb) : 0;
+                    const int steps = min(GS, maxlen - base);
+                    float res = 0.f;
+                    int src = src0;
+                    int u0 = 0;
+                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                    if (u0 + 4 <= steps) {
+                        bwd_pass<4, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                        u0 += 4; src += 16;
+                    }
+                    if (u0 + 2 <= steps) {
+                        bwd_pass<2, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                        u0 += 2; src += 8;
+                    }
+                    if (u0 < steps) bwd_pass<1, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                    const int e = base + part * GS + lig;
+                    if (row >= 0 && e < len) {
+                        if constexpr (ONE) {
+                            if constexpr (LOOPED) {   // (the row has one chunk)
+                                whole += res;
+                                if (tile_now + 1 < n_tiles) continue;
+                                res = whole;
+                            }
+                            if (a.g) a.g[cur_at] = res;
+                            if (a.fused) {
+                                momentum_step(cur_w, cur_v, res, a.lr, a.momentum, a.nesterov);
+                                a.w[cur_at] = cur_w;
+                                a.velocity[cur_at] = cur_v;
+                                a.w_t[s0 + e] = cur_w;
+                            }
+                        } else {
+                            gp[s0 + e] = res;  // GS consecutive entries of the row: one coalesced store
+                        }
+                    }
+                    cur_j = next_j;
+                    cur_w = next_w;
+                    cur_at = next_at;
+                    cur_v = next_v;
+                }
+                for (int d = GS; d < GS << lg_split; d <<= 1)   // the shares of a row, in one fixed order
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], d, kWave);
-        if (row < 0 || !on || part != 0) continue;
-        float4 y = len > 0 ? make_float4(acc[0], acc[1], acc[2], acc[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
-        if (a.mask) y = keep_where_positive(y, mask);
-        st4(a.dX + static_cast<int64_t>(row) * a.lddx + col, y);
+                    for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], d, kWave);
+                if (row < 0 || !on || part != 0) continue;
+                float4 y = len > 0 ? make_float4(acc[0], acc[1], acc[2], acc[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+                if (a.mask) y = keep_where_positive(y, mask);
+                st4(a.dX + static_cast<int64_t>(row) * a.lddx + col, y);
+        }
     }
 }
 
@@ -2610,6 +2632,13 @@ hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 // The transposed product t and the SDDMM g of one layer can share their gathers when its result mask, if any, is the
 // SDDMM's second operand (the output of the layer below), no mirror row outlasts the rest, and the layer's partial
 // buffer has a slice per tile for the products in mirror order.
+// Small work on short rows, two column tiles: a wave takes its entries through both, which leaves no second launch (546 x 2764 at
+// 0.12 %, batch 300: 16.3 -> 6.4 us; through four tiles it is the longer way, 2592 x 702 at batch 933: 18).
+constexpr int64_t kBackwardSmallWork = 8 << 20;   // entries times columns: a few us of gathers, a launch costs 3.5
+static bool backward_looped(const SpmmArgs &t)
+{
+    return t.batch > 128 && t.batch <= 512 && t.blocks.staged_longest_row <= kWave && static_cast<int64_t>(t.nnz) * t.batch <= kBackwardSmallWork;
+}
 // Lanes per mirror row of the fused backward pass: the transposed product's own tiles where it has any, else one tile up to 128
 // columns, up to 256 where the operand is small or the rows are short (16384 x 2000 power-law at batch 256 in two tiles: 26 us, in one 29;
 // 12000^2 at 0.1 %: 27 and 24), and tiles of 128 beyond; its own tiles are widened to 128 columns
@@ -2617,6 +2646,7 @@ hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 // out and come back (wide MLP, 8192 x 8192 layer: 128.6 -> 122.6 us; the product alone loses 7 % with them).
 static int backward_tile_group(const SpmmArgs &t)
 {
+    if (backward_looped(t)) return 64;
     const int tg = spmm_tile_group(t);
     if (tg == 16 && t.batch > 128 && static_cast<int64_t>(t.x_rows) * 4 * 128 <= (4ll << 20)) return 32;
     if (tg == 0) return t.batch <= 32 ? 8 : t.batch <= 64 ? 16 : t.batch <= 128 || t.batch > 256 || (t.x_rows > 4096 && t.nnz > 16 * static_cast<int64_t>(t.rows)) ? 32 : 64;
@@ -2634,10 +2664,10 @@ static int backward_split(const SpmmArgs &t, int tg, int n_tiles)
 static int backward_tiles(const SpmmArgs &t, int tg) { return (t.batch + tg * 4 - 1) / (tg * 4); }
 
 // (reading values[] through the position map costs a scattered read per entry and tile, a launch of its own 3.5 us)
-bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g)
+bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &)
 {
     const int tiles = backward_tiles(t, backward_tile_group(t));
-    return tiles == 1 || static_cast<int64_t>(tiles) * t.nnz <= (1 << 20);
+    return tiles == 1 || backward_looped(t) || static_cast<int64_t>(tiles) * t.nnz <= (1 << 20);
 }
 
 // Within a training step small layers do better with T and S in the grids of their neighbours: entries times columns from
@@ -2646,14 +2676,16 @@ bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g)
 constexpr int64_t kFusedMinWork = 16 << 20;
 bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
 {
-    if (t.batch != g.batch || t.batch < 4 || t.XM || t.X != g.dZ || t.ldx != g.lddz) return false;
+    if (t.batch != g.batch || t.batch < 4 || t.X != g.dZ || t.ldx != g.lddz || t.XM != g.ZM || t.ldxm != g.ldzm) return false;
     if (t.YM && (t.YM != g.X || t.ldym != g.ldx)) return false;
     if (t.rows != g.x_rows || t.x_rows != g.rows || t.nnz != g.nnz || t.nnz <= 0) return false;
-    if (g.ZM || g.skip_products || g.dense || g.loss_cols || !g.partial || !g.perm) return false;
+    if (g.skip_products || g.dense || g.loss_cols || !g.partial || !g.perm) return false;
     if (!spmm_offsets_ok(t) || !sddmm_offsets_ok(g) || (!alone && spmm_staged_ok(t))) return false;
     const int tg = backward_tile_group(t);
     if (!alone && static_cast<int64_t>(t.nnz) * t.batch < kFusedMinWork) return false;
     const int n_tiles = backward_tiles(t, tg);
+    // (a masked dZ only where gathering the mask as well costs less than the launch that would form dZ)
+    if (t.XM && (!alone || static_cast<int64_t>(t.nnz) * t.batch > kBackwardSmallWork)) return false;
     if (n_tiles > g.partial_tiles || g.partial_stride < t.nnz) return false;
     // (no row so long that its lane groups outlast the rest of the launch; a pass over 128 entries is short enough on any matrix)
     const int64_t longest = t.blocks.staged_longest_row >> backward_split(t, tg, n_tiles);
@@ -2687,6 +2719,7 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     BackwardArgs a{};
     a.blocks = t.blocks; a.indices = t.indices; a.values = t.values;
     a.dZ = t.X; a.lddz = t.ldx; a.X = g.X; a.ldx = g.ldx; a.dX = t.Y; a.lddx = t.ldy; a.mask = t.YM != nullptr;
+    a.ZM = t.XM; a.ldzm = t.ldxm;
     a.rows = t.rows; a.x_rows = t.x_rows; a.batch = t.batch; a.nnz = t.nnz;
     a.partial = g.partial; a.partial_stride = g.partial_stride; a.perm = g.perm;
     a.g = g.g; a.db = g.db; a.fused = g.fused; a.nesterov = g.nesterov; a.lr = g.lr; a.momentum = g.momentum;
@@ -2697,17 +2730,28 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     const int lg_split = backward_split(t, tg, n_tiles);
     const int64_t per_set = (kWave / tg) >> lg_split, sets = (static_cast<int64_t>(t.rows) + per_set - 1) / per_set;
     const int n_pack_blocks = static_cast<int>((sets + kBwdWaves - 1) / kBwdWaves);
-    const bool one = n_tiles == 1;
+    const bool one = n_tiles == 1 || (alone && backward_looped(t));
     const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
-    const int64_t ids = static_cast<int64_t>(spread ? (n_tiles + 7) / 8 * 8 : n_tiles) * n_pack_blocks + (one ? n_row_blocks : 0);
+    const int64_t ids = one ? n_pack_blocks + n_row_blocks : static_cast<int64_t>(spread ? (n_tiles + 7) / 8 * 8 : n_tiles) * n_pack_blocks;
     auto go = [&](auto group) {
         constexpr int GS = decltype(group)::value;
         const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
-        if (one)
-            hipLaunchKernelGGL((backward_fused_kernel<GS, true>), grid, block, 0, s, a, n_tiles, spread, n_pack_blocks, lg_split);
-        else
-            hipLaunchKernelGGL((backward_fused_kernel<GS, false>), grid, block, 0, s, a, n_tiles, spread, n_pack_blocks, lg_split);
+        auto launch = [&](auto pass, auto mask) {
+            hipLaunchKernelGGL((backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value>), grid, block, 0, s, a, n_tiles, spread, n_pack_blocks,
+                               lg_split);
+        };
+        using tiles = std::integral_constant<BackwardPass, kBackwardTiles>;
+        using single = std::integral_constant<BackwardPass, kBackwardOneTile>;
+        using looped = std::integral_constant<BackwardPass, kBackwardLooped>;
+        if (!one && a.ZM) launch(tiles{}, std::true_type{});
+        else if (!one) launch(tiles{}, std::false_type{});
+        else if (n_tiles == 1 && a.ZM) launch(single{}, std::true_type{});
+        else if (n_tiles == 1) launch(single{}, std::false_type{});
+        else if constexpr (GS == kWave) {
+            if (a.ZM) launch(looped{}, std::true_type{});
+            else launch(looped{}, std::false_type{});
+        }
     };
     switch (tg) {
         case 64: go(std::integral_constant<int, 64>{}); break;

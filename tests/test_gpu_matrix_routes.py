@@ -109,6 +109,8 @@ def test_wide_batches_in_column_tiles(nb, oracle, batch):
     (900, 500, 0.05, 64, None, True), (900, 500, 0.3, 65, 65, False), (500, 900, 0.01, 128, None, False),  # one tile of 64 and 128 columns
     (700, 1000, 0.04, 129, 129, False), (700, 1000, 0.04, 256, None, True),                                # one tile of 256
     (6000, 700, 0.01, 200, None, False), (700, 1000, 0.04, 257, 257, True), (600, 9000, 0.005, 700, None, False),   # several tiles
+    (700, 1000, 0.03, 300, None, True), (300, 2000, 0.02, 1025, 1025, False), (300, 2000, 0.02, 513, None, True),   # rows through all tiles
+    (700, 1000, 0.03, 300, None, True), (300, 2000, 0.02, 1025, 1025, False), (300, 2000, 0.02, 513, None, True),   # rows through all tiles
     (9000, 400, 0.02, 16, None, False), (3, 1500, 0.5, 100, None, False),   # rows shared by lane groups; hardly any rows to sum
 ])
 def test_both_gradients_in_one_pass(nb, oracle, rows, cols, density, batch, ld, relu):
