@@ -563,6 +563,71 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(const SpmmArgs a)
     a.Y[static_cast<int64_t>(task.row) * a.ldy + lane] = y;
 }
 
+// The same for matrices of more entries than the chip's waves hold at 64 each: there a wave took one load of its share and
+// waited out three round trips for it, wave after wave (3030 x 2039 at 33 %, 2 M entries, 1 / 4 examples: 16.6 / 36 us, now 11.6 / 11.8).
+// Here the waves are as many as the chip holds, 2^lg to a row, rows longest first, with four or eight loads of a lane in flight.
+template <int NB>
+__global__ __launch_bounds__(kBlock) void spmv_rows_kernel(const SpmmArgs a, const int lg)
+{
+    constexpr int U = NB == 1 ? 8 : 4;
+    __shared__ float red[kWavesPerBlock][NB];
+    const int lane = threadIdx.x & (kWave - 1), wv = wave_in_block(), part = wv & ((1 << lg) - 1);
+    const int at = (blockIdx.x * kWavesPerBlock + wv) >> lg;
+    const int4 d = at < a.rows ? a.blocks.rows_by_length[at] : make_int4(-1, 0, 0, 0);
+    const int share = (((d.z + (1 << lg) - 1) >> lg) + kWave - 1) / kWave * kWave, end = d.y + d.z;
+    const int s0 = min(d.y + part * share, end), s1 = min(s0 + share, end);
+    const gmem_ptr X = as_gmem(a.X), M = as_gmem(a.XM);
+    const uint32_t ldxb = static_cast<uint32_t>(a.ldx) * 4u, ldmb = static_cast<uint32_t>(a.ldxm) * 4u;
+    float acc[NB];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) acc[c] = 0.f;
+    for (int p = s0 + lane; p - lane < s1; p += kWave * U) {   // wave-uniform
+        int j[U];
+        float w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int at_u = min(p + u * kWave, s1 - 1);
+            j[u] = a.indices[at_u];
+            w[u] = a.values[at_u];
+        }
+        float x[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (NB == 4 && a.batch == 4) {   // uniform
+                float4 v = gload4(X, static_cast<uint32_t>(j[u]) * ldxb);
+                if (a.XM) v = keep_where_positive(v, gload4(M, static_cast<uint32_t>(j[u]) * ldmb));
+                x[u][0] = v.x; x[u][1 % NB] = v.y; x[u][2 % NB] = v.z; x[u][3 % NB] = v.w;
+                continue;
+            }
+#pragma unroll
+            for (int c = 0; c < NB; ++c) {
+                const uint32_t column = static_cast<uint32_t>(min(c, a.batch - 1)) * 4u;
+                x[u][c] = gload1(X, static_cast<uint32_t>(j[u]) * ldxb + column);
+                if (a.XM) x[u][c] = keep_where_positive(x[u][c], gload1(M, static_cast<uint32_t>(j[u]) * ldmb + column));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool mine = p + u * kWave < s1;   // (past the end: the last entry again, not added)
+#pragma unroll
+            for (int c = 0; c < NB; ++c) acc[c] = mine ? fmaf(w[u], x[u][c], acc[c]) : acc[c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NB; ++c) acc[c] = group_sum<kWave>(acc[c]);
+    if (lane == 0)
+#pragma unroll
+        for (int c = 0; c < NB; ++c) red[wv][c] = acc[c];
+    __syncthreads();
+    if (d.x < 0 || part != 0 || lane >= a.batch || lane >= NB) return;
+    float y = 0.f;
+    for (int s = 0; s < (1 << lg); ++s) y += red[wv + s][lane];
+    y += a.bias ? a.bias[d.x] : 0.f;
+    if (a.relu) y = y > 0.f ? y : 0.f;
+    if (a.YM) y = keep_where_positive(y, a.YM[static_cast<int64_t>(d.x) * a.ldym + lane]);
+    a.Y[static_cast<int64_t>(d.x) * a.ldy + lane] = y;
+}
+
 // Product with a FULL matrix of few rows (every entry stored, rows <= kFullMaxRows): values[] is
 // the row-major dense matrix, so instead of gathering the operand once per row the kernel streams
 // it once for all rows.  A work-group of 4 waves owns kFullSlice consecutive operand rows and 256
@@ -2775,10 +2840,30 @@ bool spmm_softmax_epilogue_ok(const SpmmArgs &a)
     return a.rows > 0 && a.blocks.n_blocks > 0 && spmm_full_rows_ok(a) && !a.relu && !a.YM && a.ce_labels && a.ce_dZ && a.ce_loss_cols;
 }
 
+// log2 of the waves per row of spmv_rows_kernel, -1: not for this matrix.  It needs more entries than 8192 waves hold at 64
+// each, and no row that keeps its waves busy for more than 16 rounds.
+static int spmv_rows_split(const SpmmArgs &a)
+{
+    if (a.nnz < 8192 * kWave || !spmm_offsets_ok(a)) return -1;
+    int lg = 0;
+    while (lg < 4 && (static_cast<int64_t>(a.rows) << (lg + 1)) <= 8192) ++lg;
+    return (a.blocks.staged_longest_row >> lg) <= 16 * 4 * kWave ? lg : -1;
+}
+
 hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
 {
     if (a.rows <= 0 || a.batch <= 0 || a.blocks.n_blocks <= 0) return hipSuccess;
     if (a.batch <= 4) {
+        if (const int lg = spmv_rows_split(a); lg >= 0) {
+            const dim3 grid(static_cast<unsigned>(((static_cast<int64_t>(a.rows) << lg) + kWavesPerBlock - 1) / kWavesPerBlock));
+            if (a.batch == 1)
+                hipLaunchKernelGGL(spmv_rows_kernel<1>, grid, dim3(kBlock), 0, s, a, lg);
+            else if (a.batch == 2)
+                hipLaunchKernelGGL(spmv_rows_kernel<2>, grid, dim3(kBlock), 0, s, a, lg);
+            else
+                hipLaunchKernelGGL(spmv_rows_kernel<4>, grid, dim3(kBlock), 0, s, a, lg);
+            return hipGetLastError();
+        }
         if (a.batch == 1)
             hipLaunchKernelGGL(spmv_kernel<1>, dim3(a.blocks.n_blocks), dim3(kBlock), 0, s, a);
         else

@@ -174,3 +174,14 @@ def test_lane_groups_of_every_batch(nb, oracle, batch):
     indptr, indices = wl.pattern_from_row_nnz(lens, 1400, seed=batch)
     lay = wl.SparseLayerData(len(lens), 1400, indptr, indices, wl.init_values(indptr, 1), np.ones(len(lens), np.float32), batch % 2 == 0)
     check_layer(nb, oracle, lay, batch, ld=batch)
+
+
+@pytest.mark.parametrize("rows,cols,density,batch,relu", [
+    (1000, 1000, 0.53, 1, True), (9000, 700, 0.09, 3, False), (700, 9000, 0.09, 4, True), (33, 70000, 0.25, 2, False),
+])
+def test_one_to_four_examples_on_many_entries(nb, oracle, rows, cols, density, batch, relu):
+    nb.nerva_set_dense_threshold(2.0)
+    try:
+        check_layer(nb, oracle, layer_case(rows, cols, density, seed=rows, relu=relu), batch, ld=batch)
+    finally:
+        nb.nerva_set_dense_threshold(0.4)
