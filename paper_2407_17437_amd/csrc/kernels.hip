@@ -2528,7 +2528,7 @@ bool sddmm_staged_ok(const SddmmArgs &a)
 {
     if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     if ((a.batch + kStageCols - 1) / kStageCols > a.partial_tiles) return false;
-    return staged_pays(a.blocks, a.x_rows, a.batch, kStageLongSegmentSddmm) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
+    return staged_pays(a.blocks, a.x_rows, a.batch, a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : kStageLongSegmentSddmm) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
 }
 
 bool spmm_offsets_ok(const SpmmArgs &a)
