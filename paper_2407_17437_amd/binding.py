@@ -93,6 +93,12 @@ def _load() -> ctypes.CDLL:
 
 lib = _load()
 
+# the calls that loops are made of, without ctypes (csrc/fastcall.cpp): they go to the entry points of `lib`
+from . import _fastcall  # noqa: E402  (built beside the library)
+
+_fastcall.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+    "sparse_linear_forward", "sparse_linear_backward", "sgd_update_values", "sgd_update_values_nesterov", "mlp_train_step", "mlp_forward")))
+
 
 def last_error() -> str:
     return lib.nerva_last_error().decode()
@@ -225,22 +231,27 @@ def sparse_linear_mirror(layer: int):
 
 
 def sparse_linear_forward(layer: int, X, Y, batch: int, stream=None) -> None:
-    _check(lib.sparse_linear_forward(layer, _ptr(X), _ld(X), _ptr(Y), _ld(Y), batch, _stream(stream)))
+    rc = _fastcall.forward(layer, X, Y, batch, stream)
+    if rc:
+        _check(rc)
 
 
 def sparse_linear_backward(layer: int, X, Y, dY, dX, dvalues, dbias, batch: int, stream=None) -> None:
-    _check(lib.sparse_linear_backward(layer, _ptr(X), _ld(X) if X is not None else 0,
-                                      _ptr(Y), _ld(Y) if Y is not None else 0, _ptr(dY), _ld(dY),
-                                      _ptr(dX), _ld(dX) if dX is not None else 0, _ptr(dvalues), _ptr(dbias),
-                                      batch, _stream(stream)))
+    rc = _fastcall.backward(layer, X, Y, dY, dX, dvalues, dbias, batch, stream)
+    if rc:
+        _check(rc)
 
 
 def sgd_update_values(values, velocity, grad, n: int, lr: float, momentum: float, stream=None) -> None:
-    _check(lib.sgd_update_values(_ptr(values), _ptr(velocity), _ptr(grad), n, lr, momentum, _stream(stream)))
+    rc = _fastcall.update(values, velocity, grad, n, lr, momentum, 0, stream)
+    if rc:
+        _check(rc)
 
 
 def sgd_update_values_nesterov(values, velocity, grad, n: int, lr: float, momentum: float, stream=None) -> None:
-    _check(lib.sgd_update_values_nesterov(_ptr(values), _ptr(velocity), _ptr(grad), n, lr, momentum, _stream(stream)))
+    rc = _fastcall.update(values, velocity, grad, n, lr, momentum, 1, stream)
+    if rc:
+        _check(rc)
 
 
 def softmax_cross_entropy(Z, labels, classes: int, batch: int, dZ, loss_out, stream=None) -> None:
@@ -272,13 +283,12 @@ def mlp_workspace_layout(mlp: int, batch: int, n_layers: int) -> List[int]:
     return list(out)
 
 
-def mlp_train_step(mlp: int, X, ldx: int, labels, batch: int, lr: float, momentum: float, workspace,
+def mlp_train_step(mlp: int, X, ldx: Optional[int], labels, batch: int, lr: float, momentum: float, workspace,
                    loss_out, stream=None) -> None:
-    """X may be a tensor or a raw device address (int); ldx in floats."""
-    xp = X if isinstance(X, int) else _ptr(X)
-    lp = labels if isinstance(labels, int) else _ptr(labels)
-    _check(lib.mlp_train_step(mlp, xp, ldx, lp, batch, lr, momentum, _ptr(workspace),
-                              workspace.numel() * workspace.element_size(), _ptr(loss_out), _stream(stream)))
+    """X may be a tensor or a raw device address (int); ldx in floats (None: the tensor's own)."""
+    rc = _fastcall.train_step(mlp, X, ldx, labels, batch, lr, momentum, workspace, loss_out, stream)
+    if rc:
+        _check(rc)
 
 
 def mlp_train_step_static(mlp: int, X, ldx: int, labels, batch: int, lr: float, momentum: float, loss_out, stream=None) -> None:
@@ -288,10 +298,10 @@ def mlp_train_step_static(mlp: int, X, ldx: int, labels, batch: int, lr: float, 
     _check(lib.mlp_train_step_static(mlp, xp, ldx, lp, batch, lr, momentum, _ptr(loss_out), _stream(stream)))
 
 
-def mlp_forward(mlp: int, X, ldx: int, batch: int, workspace, stream=None) -> None:
-    xp = X if isinstance(X, int) else _ptr(X)
-    _check(lib.mlp_forward(mlp, xp, ldx, batch, _ptr(workspace), workspace.numel() * workspace.element_size(),
-                           _stream(stream)))
+def mlp_forward(mlp: int, X, ldx: Optional[int], batch: int, workspace, stream=None) -> None:
+    rc = _fastcall.mlp_forward(mlp, X, ldx, batch, workspace, stream)
+    if rc:
+        _check(rc)
 
 
 def mlp_profile_enable(mlp: int, max_steps: int) -> None:
@@ -424,13 +434,9 @@ class MLP:
             self.workspace = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device=self.workspace.device)
 
     def train_step(self, X, labels, batch: int, lr: float, momentum: float, ldx: Optional[int] = None):
-        if ldx is None:
-            ldx = _ld(X)
         mlp_train_step(self.handle, X, ldx, labels, batch, lr, momentum, self.workspace, self.loss)
 
     def forward(self, X, batch: int, ldx: Optional[int] = None):
-        if ldx is None:
-            ldx = _ld(X)
         mlp_forward(self.handle, X, ldx, batch, self.workspace)
         return self.view("A", len(self.layers) - 1, batch)
 

@@ -1,14 +1,16 @@
-"""Compile the HIP library for gfx950 in-tree (hipcc cross-compiles without a GPU)."""
+"""Compile the HIP library for gfx950 and the Python call layer in-tree (hipcc cross-compiles without a GPU)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libnerva_sparse.so")
 SOURCES = ["kernels.hip", "structure.hip", "dense.hip", "api.hip"]
+FASTCALL = os.path.join(PKG, "_fastcall.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -31,7 +33,25 @@ def build_library(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed")
     if verbose and err.strip():
         print(err)
+    build_fastcall(verbose)
     return LIB
+
+
+def build_fastcall(verbose: bool = False) -> str:
+    """Host code only: Python.h and torch's headers, no kernels."""
+    from torch.utils import cpp_extension
+    includes = [*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    libs = cpp_extension.library_paths()[0]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", *[f"-isystem{i}" for i in includes],
+           os.path.join(CSRC, "fastcall.cpp"), f"-L{libs}", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           f"-Wl,-rpath,{libs}", "-o", FASTCALL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, cwd=CSRC, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stderr)
+        raise RuntimeError("the Python call layer does not compile")
+    return FASTCALL
 
 
 if __name__ == "__main__":
