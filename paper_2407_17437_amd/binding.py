@@ -419,7 +419,7 @@ class MLP:
         off = lay[1 + 4 * l + k] // 4
         L = self.layers[l]
         if kind in ("A", "dZ"):
-            return self.workspace.as_strided((L.rows, batch), (ld, 1), self.workspace.storage_offset() + off)   # (one torch call: part of every forward())
+            return _fastcall.view(self.workspace, L.rows, batch, ld, off)
         n = L.nnz if kind == "g" else L.rows
         return self.workspace[off: off + n]
 
@@ -437,8 +437,11 @@ class MLP:
         mlp_train_step(self.handle, X, ldx, labels, batch, lr, momentum, self.workspace, self.loss)
 
     def forward(self, X, batch: int, ldx: Optional[int] = None):
-        mlp_forward(self.handle, X, ldx, batch, self.workspace)
-        return self.view("A", len(self.layers) - 1, batch)
+        rc = _fastcall.mlp_forward(self.handle, X, ldx, batch, self.workspace, None)
+        if rc:
+            _check(rc)
+        lay = self._layout if self._layout_batch == batch else self.layout(batch)
+        return _fastcall.view(self.workspace, self.layers[-1].rows, batch, lay[0], lay[-4] // 4)
 
     def close(self):
         if self.handle:

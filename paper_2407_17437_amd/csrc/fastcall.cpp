@@ -231,6 +231,25 @@ PyObject *mlp_forward(PyObject *, PyObject *const *args, Py_ssize_t n)
     });
 }
 
+// (workspace, rows, batch, ld, offset in floats): the (rows, batch) matrix there
+PyObject *view(PyObject *, PyObject *const *args, Py_ssize_t n)
+{
+    if (n != 5) {
+        PyErr_Format(PyExc_TypeError, "%zd arguments, 5 expected", n);
+        return nullptr;
+    }
+    try {
+        Args a{args + 1};
+        const at::Tensor *ws = a.tensor(args[0]);
+        const int64_t rows = a.integer(), batch = a.integer(), ld = a.integer(), offset = a.integer();
+        if (!a.ok) return nullptr;
+        return THPVariable_Wrap(ws->as_strided({rows, batch}, {ld, 1}, ws->storage_offset() + offset));
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
+}
+
 // addresses of sparse_linear_forward, sparse_linear_backward, sgd_update_values, sgd_update_values_nesterov, mlp_train_step, mlp_forward
 PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
@@ -256,6 +275,7 @@ PyMethodDef methods[] = {
     {"update", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(update)), METH_FASTCALL, nullptr},
     {"train_step", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(train_step)), METH_FASTCALL, nullptr},
     {"mlp_forward", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(mlp_forward)), METH_FASTCALL, nullptr},
+    {"view", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(view)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 
