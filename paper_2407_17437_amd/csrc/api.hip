@@ -67,6 +67,7 @@ int fail(int code, const char *fmt, ...)
 
 int hip_fail(hipError_t e, const char *what)
 {
+    (void)hipGetLastError();   // reported here: the runtime keeps it, and the next launch that asks must not find it
     return fail(NERVA_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
@@ -1260,7 +1261,7 @@ int mlp_create(nerva_mlp **out, int32_t n_layers, nerva_layer *const *layers, fl
         if (e != hipSuccess) {
             if (m->head_scratch) (void)hipFree(m->head_scratch);
             delete m;
-            return fail(NERVA_ERR_HIP, "head work space: %s", hipGetErrorString(e));
+            return hip_fail(e, "head work space");
         }
     }
     *out = m;

@@ -1,0 +1,135 @@
+// A HIP runtime without a GPU, for tests of the library's host code: memory is host memory, kernels do not run, any call
+// can be made to fail, and the pointers that launches are given are checked against what has been freed.  Freed memory is
+// never handed out again.  The planner's launch leaves the counts that the test has set where the library reads them.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+
+#include "../paper_2407_17437_amd/csrc/kernels.h"
+
+using namespace nerva;
+
+namespace {
+std::map<uintptr_t, size_t> live, dead;
+std::map<const void *, std::string> kernels;
+std::string launched;
+PlanCounts counts[2];
+long calls_until_failure = -1;   // of the calls that allocate, fill or wait
+int bad_pointers = 0;
+size_t live_bytes = 0;
+hipError_t last = hipSuccess;
+
+bool fails(hipError_t e)
+{
+    if (calls_until_failure < 0 || calls_until_failure-- > 0) return false;
+    last = e;
+    return true;
+}
+hipError_t allocate(void **p, size_t n)
+{
+    *p = malloc(n);
+    memset(*p, 0xCB, n);
+    live[reinterpret_cast<uintptr_t>(*p)] = n;
+    live_bytes += n;
+    return hipSuccess;
+}
+hipError_t release(void *p)
+{
+    const auto it = live.find(reinterpret_cast<uintptr_t>(p));
+    if (!p) return hipSuccess;
+    if (it == live.end()) { ++bad_pointers; return hipSuccess; }
+    live_bytes -= it->second;
+    dead.insert(*it);
+    live.erase(it);
+    return hipSuccess;
+}
+void check(const void *args, size_t bytes)
+{
+    for (size_t at = 0; at + 8 <= bytes; at += 8) {
+        uintptr_t p;
+        memcpy(&p, static_cast<const char *>(args) + at, 8);
+        auto it = dead.upper_bound(p);
+        if (it != dead.begin() && (--it, p < it->first + it->second)) ++bad_pointers;
+    }
+}
+}  // namespace
+
+extern "C" {
+// ---- for the test
+void fake_fail_after(long calls) { calls_until_failure = calls; }
+int fake_bad_pointers() { return bad_pointers; }
+size_t fake_live_bytes() { return live_bytes; }
+const char *fake_launched() { static std::string out; out.swap(launched); launched.clear(); return out.c_str(); }
+int fake_set(int side, const char *field, int value)
+{
+#define FIELD(name) if (!strcmp(field, #name)) { counts[side].name = value; return 0; }
+    FIELD(n_blocks) FIELD(n_huge_rows) FIELD(n_huge_blocks) FIELD(n_short) FIELD(longest_row) FIELD(n_long_rows) FIELD(hot_nnz) FIELD(n_dense)
+    FIELD(dense_nnz) FIELD(staged_ranges) FIELD(staged_rows) FIELD(staged_nnz) FIELD(staged_longest_share)
+    return 1;
+}
+
+// ---- the runtime
+hipError_t hipMalloc(void **p, size_t n) { return fails(hipErrorOutOfMemory) ? hipErrorOutOfMemory : allocate(p, n); }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return fails(hipErrorOutOfMemory) ? hipErrorOutOfMemory : allocate(p, n); }
+hipError_t hipFree(void *p) { return release(p); }
+hipError_t hipHostFree(void *p) { return release(p); }
+hipError_t hipMemset(void *p, int v, size_t n)
+{
+    if (fails(hipErrorUnknown)) return hipErrorUnknown;
+    memset(p, v, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *p, int v, size_t n, hipStream_t) { return hipMemset(p, v, n); }
+hipError_t hipStreamSynchronize(hipStream_t) { return fails(hipErrorUnknown) ? hipErrorUnknown : hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) { static char symbol[256]; *p = symbol; return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }   // (also of calls before the last one)
+const char *hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
+hipError_t hipEventCreate(hipEvent_t *) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+void **__hipRegisterFatBinary(const void *) { static void *handle; return &handle; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *, void *, void *, int *) { kernels[host] = name; }
+
+static dim3 config_grid, config_block;
+static size_t config_lds;
+static hipStream_t config_stream;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s)
+{
+    config_grid = grid; config_block = block; config_lds = lds; config_stream = s;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *s)
+{
+    *grid = config_grid; *block = config_block; *lds = config_lds; *s = config_stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *kernel, dim3, dim3, void **args, size_t, hipStream_t)
+{
+    const std::string &name = kernels[kernel];
+    launched += name + "\n";
+    auto takes = [&](const char *type) { return name.find(type) != std::string::npos; };
+    if (takes("8SpmmArgs")) {
+        check(args[0], sizeof(SpmmArgs));
+    } else if (takes("9SddmmArgs")) {
+        check(args[0], sizeof(SddmmArgs));
+    } else if (takes("12BackwardArgs")) {
+        check(args[0], sizeof(BackwardArgs));
+    } else if (takes("11SampledArgs")) {
+        check(args[0], sizeof(SampledArgs));
+    } else if (takes("plan_kernel")) {
+        const PlanArgs &p = *static_cast<const PlanArgs *>(args[0]);
+        memset(p.result, 0, sizeof(BindResult));
+        memcpy(p.result->plan, counts, sizeof counts);
+    }
+    return hipSuccess;
+}
+}

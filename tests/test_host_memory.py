@@ -1,0 +1,84 @@
+"""Device memory that a layer owns, from the host's side: what it holds when a call of the runtime fails.  The library runs on
+a HIP runtime without a GPU (fake_hip.cpp), each test in a process of its own, where any allocation can be made to fail."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_2407_17437_amd", "libnerva_sparse.so")
+
+
+class Library:
+    """The library on the runtime at `fake`, and one layer whose pattern is whatever `counts` makes of it."""
+
+    def __init__(self, fake):
+        self.hip = ctypes.CDLL(fake, mode=ctypes.RTLD_GLOBAL)   # (before the library, which then binds to it)
+        self.hip.fake_launched.restype = ctypes.c_char_p
+        self.hip.fake_live_bytes.restype = ctypes.c_size_t
+        self.hip.fake_fail_after.argtypes = [ctypes.c_long]
+        self.lib = ctypes.CDLL(LIB)
+        self.lib.nerva_last_error.restype = ctypes.c_char_p
+        self.host = [(ctypes.c_float * (1 << 20))() for _ in range(4)]   # (never read: no kernel runs)
+        self.layer = ctypes.c_void_p()
+
+    def counts(self, side, **values):
+        for name, value in values.items():
+            assert self.hip.fake_set(side, name.encode(), value) == 0, name
+
+    def create(self, rows, cols, nnz, max_batch, relu=False):
+        self.rows, self.cols = rows, cols
+        a = [ctypes.addressof(h) for h in self.host]
+        return self.lib.sparse_linear_create(ctypes.byref(self.layer), rows, cols, nnz, ctypes.c_void_p(a[0]), ctypes.c_void_p(a[1]), ctypes.c_void_p(a[2]),
+                                             None, 1 if relu else 0, max_batch, None)
+
+    def rebind(self, nnz):
+        a = [ctypes.addressof(h) for h in self.host]
+        return self.lib.sparse_linear_rebind(self.layer, nnz, ctypes.c_void_p(a[0]), ctypes.c_void_p(a[1]), ctypes.c_void_p(a[2]), None)
+
+    def destroy(self):
+        self.lib.sparse_linear_destroy(self.layer)
+        self.layer = ctypes.c_void_p()
+
+    def forward(self, batch):
+        p = ctypes.c_void_p(ctypes.addressof(self.host[3]))
+        return self.lib.sparse_linear_forward(self.layer, p, batch, p, batch, batch, None)
+
+    def backward(self, batch, dx=True, dvalues=True):
+        p = ctypes.c_void_p(ctypes.addressof(self.host[3]))
+        return self.lib.sparse_linear_backward(self.layer, p, batch, p, batch, p, batch, p if dx else None, batch, p if dvalues else None, p, batch, None)
+
+    def launched(self):
+        return self.hip.fake_launched().decode().split()
+
+
+def a_failed_call_is_reported_once(L):
+    L.counts(0, n_blocks=8, longest_row=40)
+    L.counts(1, n_blocks=8, longest_row=40)
+    assert L.create(64, 512, 2000, 32) == 0
+    L.hip.fake_fail_after(0)
+    assert L.rebind(4000) == -5
+    assert L.forward(32) == 0 and L.backward(32) == 0, L.lib.nerva_last_error()   # (their launches are in order)
+
+
+CASES = [a_failed_call_is_reported_once]
+
+
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("hip") / "fake_hip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-isystem", "/opt/rocm/include",
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", out], check=True)
+    return out
+
+
+@pytest.mark.parametrize("case", [c.__name__ for c in CASES])
+def test_host_memory(fake_hip, case):
+    run = subprocess.run([sys.executable, os.path.abspath(__file__), fake_hip, case], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, run.stdout + run.stderr
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[2]](Library(sys.argv[1]))
