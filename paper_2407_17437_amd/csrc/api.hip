@@ -123,9 +123,12 @@ struct nerva_layer {
     size_t build_work_ints = 0;
     BindResult *bind_result = nullptr;
     // owned: partial rows of huge-row work-groups, shared by the forward and the transposed product
-    float *scratch_mem = nullptr, *scratch = nullptr;   // tickets of the huge rows, partial rows (SpmmArgs::scratch)
+    float *scratch = nullptr;
     size_t scratch_floats = 0;
     int64_t scratch_ld = 0;
+    // owned: tickets of the huge rows (SpmmArgs::tickets), 0 but while a product runs
+    int32_t *tickets = nullptr;
+    size_t ticket_ints = 0;
     // owned: per-tile partial products of the column-tiled SDDMM (only for layers whose input
     // at max_batch columns does not fit an L2)
     float *partial = nullptr;
@@ -585,7 +588,8 @@ void free_layer_buffers(nerva_layer *l)
     free_pattern_buffers(l->spare);
     (void)hipFree(l->build_work);
     if (l->bind_result) (void)hipHostFree(l->bind_result);
-    (void)hipFree(l->scratch_mem);
+    (void)hipFree(l->scratch);
+    (void)hipFree(l->tickets);
     (void)hipFree(l->partial);
     (void)hipFree(l->dz);
     (void)hipFree(l->dense);
@@ -593,16 +597,24 @@ void free_layer_buffers(nerva_layer *l)
 }
 
 // Room for `need` elements of 4 bytes in *ptr, whose capacity is *have: kept if large enough, else
-// replaced by a larger allocation (the old contents are not kept).  On failure nothing changes.
+// replaced by a larger allocation (the old contents are not kept; the new ones are 0 if `zeroed`).  On failure nothing changes.
 template <typename T>
-hipError_t reserve(T **ptr, size_t *have, size_t need)
+hipError_t reserve(T **ptr, size_t *have, size_t need, bool zeroed = false, hipStream_t s = nullptr)
 {
     if (need <= *have && *ptr) return hipSuccess;
     if (need == 0) need = 1;
     const size_t want = need + need / 8;
     void *fresh = nullptr;
-    const hipError_t e = hipMalloc(&fresh, want * 4);
+    hipError_t e = hipMalloc(&fresh, want * 4);
     if (e != hipSuccess) return e;
+    if (zeroed) {
+        e = hipMemsetAsync(fresh, 0, want * 4, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) {
+            (void)hipFree(fresh);
+            return e;
+        }
+    }
     (void)hipFree(*ptr);
     *ptr = static_cast<T *>(fresh);
     *have = want;
@@ -819,7 +831,6 @@ struct BuiltPattern {
     int64_t partial_stride = 0, partial_db_at = 0;
     int32_t partial_tiles = 0;
     int64_t scratch_ld = 0, full_scratch_ld = 0;
-    float *scratch = nullptr;
     bool full = false;
 };
 
@@ -908,7 +919,8 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
 
-    // scratch buffers of the products (they hold nothing between calls: grown in place)
+    // scratch buffers of the products (they hold nothing between calls, the tickets zeros: grown in place, so that the old
+    // pattern's products find them whatever fails from here on)
     {
         // room for the column-tiled SDDMM at max_batch columns, if that batch would be tiled
         const int w = tile_columns(cols, max_batch, nnz, rows, out->plan.staged_longest_row, out->plan.hot_share, false, true);
@@ -931,11 +943,8 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         out->scratch_ld = round_up(max_batch, 64);
         if (slots > 0) {
             const int64_t huge = std::max(out->plan.n_huge_rows, out->plan_t.n_huge_rows);
-            const int64_t tickets = round_up(huge * huge_row_tickets(out->scratch_ld), 64);
-            HIP_TRY(reserve(&l->scratch_mem, &l->scratch_floats, static_cast<size_t>(tickets + slots * out->scratch_ld)));
-            HIP_TRY(hipMemsetAsync(l->scratch_mem, 0, static_cast<size_t>(tickets) * 4, s));
-            out->scratch = l->scratch_mem + tickets;
-            more_work = true;
+            HIP_TRY(reserve(&l->tickets, &l->ticket_ints, static_cast<size_t>(huge * huge_row_tickets(out->scratch_ld)), true, s));
+            HIP_TRY(reserve(&l->scratch, &l->scratch_floats, static_cast<size_t>(slots * out->scratch_ld)));
         }
         out->full = rows <= kFullMaxRows && static_cast<int64_t>(nnz) == static_cast<int64_t>(rows) * cols;
         out->full_scratch_ld = round_up(max_batch, 64);
@@ -961,7 +970,7 @@ static void adopt_pattern(nerva_layer *l, int32_t nnz, const int32_t *indptr, co
     l->values_t = reinterpret_cast<float *>(l->cur.mirror_mem + 3 * n64);
     l->plan = bp.plan; l->plan_t = bp.plan_t;
     l->partial_stride = bp.partial_stride; l->partial_db_at = bp.partial_db_at; l->partial_tiles = bp.partial_tiles;
-    l->scratch = bp.scratch; l->scratch_ld = bp.scratch_ld;
+    l->scratch_ld = bp.scratch_ld;
     l->full_scratch_ld = bp.full_scratch_ld;
     l->full = bp.full;
     l->mirror_stale = false;
@@ -1102,7 +1111,7 @@ int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx,
         return NERVA_OK;
     }
     SpmmArgs a{};
-    a.blocks = layer->plan; a.nnz = layer->nnz; a.scratch = layer->scratch; a.scratch_ld = layer->scratch_ld;
+    a.blocks = layer->plan; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = layer->tickets; a.scratch_ld = layer->scratch_ld;
     a.indptr = layer->indptr; a.indices = layer->indices; a.values = layer->values; a.bias = layer->bias;
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
     a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.relu = layer->activation == NERVA_ACT_RELU;
@@ -1130,7 +1139,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
     bool form_dz = false, mask = relu;   // mask: dY still is the gradient of the output
     auto make_t = [&] {
         SpmmArgs a{};
-        a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.scratch_ld = layer->scratch_ld;
+        a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = layer->tickets; a.scratch_ld = layer->scratch_ld;
         a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
         a.X = dY; a.ldx = lddy;
         if (mask) { a.XM = Y; a.ldxm = ldy; }
@@ -1365,7 +1374,7 @@ static int check_step_args(const nerva_mlp *mlp, const float *X, int32_t ldx, in
 static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldin, float *out, int64_t ldout, int32_t batch)
 {
     SpmmArgs a{};
-    a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.scratch_ld = ly->scratch_ld;
+    a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = ly->tickets; a.scratch_ld = ly->scratch_ld;
     a.indptr = ly->indptr; a.indices = ly->indices; a.values = ly->values; a.bias = ly->bias;
     a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
     a.rows = ly->rows; a.x_rows = ly->cols; a.batch = batch; a.relu = ly->activation == NERVA_ACT_RELU;
@@ -1471,7 +1480,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         // applied as the transposed product is stored
         nerva_layer *ly = mlp->layers[l];
         SpmmArgs t{};
-        t.blocks = ly->plan_t; t.nnz = ly->nnz; t.scratch = ly->scratch; t.scratch_ld = ly->scratch_ld;
+        t.blocks = ly->plan_t; t.nnz = ly->nnz; t.scratch = ly->scratch; t.tickets = ly->tickets; t.scratch_ld = ly->scratch_ld;
         t.indptr = ly->indptr_t; t.indices = ly->indices_t; t.values = ly->values_t;
         t.X = dZ(l); t.ldx = L.ld; t.Y = dZ(l - 1); t.ldy = L.ld;
         t.YM = A(l - 1); t.ldym = L.ld;

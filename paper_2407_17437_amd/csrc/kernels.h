@@ -124,8 +124,9 @@ struct SpmmArgs {
     int32_t relu;            // clamp the result at zero
     int32_t wide_offsets;    // an operand spans 4 GiB or more (set by the launch)
     int32_t nnz;             // length of indices/values
-    float *scratch;          // partial rows of huge-row work-groups, (n_huge_blocks, scratch_ld); before it, growing downwards, the
-    int64_t scratch_ld;      // tickets of the huge rows (huge_row_tickets), all 0 between launches
+    float *scratch;          // partial rows of huge-row work-groups, (n_huge_blocks, scratch_ld)
+    int64_t scratch_ld;
+    int32_t *tickets;        // (n_huge_rows, huge_row_tickets(scratch_ld)), all 0 between launches
     // Only for a matrix that stores every entry and has at most kFullMaxRows rows (a saturated
     // output layer): values[] is then the row-major dense matrix, and the product streams the
     // operand once for all rows instead of gathering it once per row.  Partial results of the

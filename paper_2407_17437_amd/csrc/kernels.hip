@@ -125,7 +125,7 @@ __device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (lane == 0) {
-            int *ticket = reinterpret_cast<int *>(a.scratch) - 1 - (task.index * static_cast<int>(huge_row_tickets(a.scratch_ld)) + col0 / 32);
+            int *ticket = a.tickets + task.index * huge_row_tickets(a.scratch_ld) + col0 / 32;
             const int turn = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (turn == h.z - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             turn_s = turn;

@@ -19,7 +19,7 @@ std::map<const void *, std::string> kernels;
 std::string launched;
 PlanCounts counts[2];
 long calls_until_failure = -1;   // of the calls that allocate, fill or wait
-int bad_pointers = 0;
+int bad_pointers = 0, dirty_tickets = 0;
 size_t live_bytes = 0;
 hipError_t last = hipSuccess;
 
@@ -47,6 +47,12 @@ hipError_t release(void *p)
     live.erase(it);
     return hipSuccess;
 }
+bool holds(const void *at, size_t bytes)   // whether one allocation does
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(at);
+    auto it = live.upper_bound(p);
+    return it != live.begin() && (--it, p + bytes <= it->first + it->second);
+}
 void check(const void *args, size_t bytes)
 {
     for (size_t at = 0; at + 8 <= bytes; at += 8) {
@@ -62,6 +68,7 @@ extern "C" {
 // ---- for the test
 void fake_fail_after(long calls) { calls_until_failure = calls; }
 int fake_bad_pointers() { return bad_pointers; }
+int fake_dirty_tickets() { return dirty_tickets; }
 size_t fake_live_bytes() { return live_bytes; }
 const char *fake_launched() { static std::string out; out.swap(launched); launched.clear(); return out.c_str(); }
 int fake_set(int side, const char *field, int value)
@@ -118,7 +125,15 @@ hipError_t hipLaunchKernel(const void *kernel, dim3, dim3, void **args, size_t, 
     launched += name + "\n";
     auto takes = [&](const char *type) { return name.find(type) != std::string::npos; };
     if (takes("8SpmmArgs")) {
-        check(args[0], sizeof(SpmmArgs));
+        const SpmmArgs &a = *static_cast<const SpmmArgs *>(args[0]);
+        check(&a, sizeof a);
+        const int64_t tickets = a.blocks.n_huge_rows * huge_row_tickets(a.scratch_ld);
+        if (tickets > 0) {
+            if (!holds(a.scratch, a.blocks.n_huge_blocks * a.scratch_ld * 4) || !holds(a.tickets, tickets * 4))
+                ++bad_pointers;
+            else
+                for (int64_t k = 0; k < tickets; ++k) dirty_tickets += a.tickets[k] != 0;
+        }
     } else if (takes("9SddmmArgs")) {
         check(args[0], sizeof(SddmmArgs));
     } else if (takes("12BackwardArgs")) {

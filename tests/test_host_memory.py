@@ -63,7 +63,31 @@ def a_failed_call_is_reported_once(L):
     assert L.forward(32) == 0 and L.backward(32) == 0, L.lib.nerva_last_error()   # (their launches are in order)
 
 
-CASES = [a_failed_call_is_reported_once]
+def a_failed_rebind_leaves_nothing_freed_in_use(L):
+    """Whichever of its allocations, fills and waits fails, the layer goes on with the old pattern (few rows cut into many
+    work-groups, then many rows cut into few, and back)."""
+    few, many = dict(n_blocks=60, n_huge_rows=2, n_huge_blocks=50, longest_row=400), dict(n_blocks=400, n_huge_rows=150, n_huge_blocks=300, longest_row=400)
+    for old, new in ((few, many), (many, few)):
+        for k in range(100):
+            for side in (0, 1):
+                L.counts(side, **old)
+            assert L.create(256, 512, 2000, 128, relu=True) == 0
+            for side in (0, 1):
+                L.counts(side, **new)
+            L.hip.fake_fail_after(k)
+            rc = L.rebind(9000)
+            L.hip.fake_fail_after(-1)
+            for batch in (1, 100, 128):
+                assert L.forward(batch) == 0 and L.backward(batch) == 0, L.lib.nerva_last_error()
+            L.destroy()
+            assert L.hip.fake_bad_pointers() == 0 and L.hip.fake_dirty_tickets() == 0, k
+            if rc == 0:
+                break
+            assert rc == -5
+        assert 3 < k < 99
+
+
+CASES = [a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use]
 
 
 @pytest.fixture(scope="module")
