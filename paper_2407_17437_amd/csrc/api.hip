@@ -803,6 +803,9 @@ static bool takes_dense_route(const nerva_layer *l, int32_t nnz)
 // the dense route needs a batch wide enough to fill its 16-column tiles
 static bool use_dense(const nerva_layer *l, int32_t batch) { return l->dense_on && batch >= 16; }
 
+// tickets of the huge rows of W (side 0) or of its mirror (side 1): rows of the two alternate
+static int32_t *tickets_of(const nerva_layer *l, int side) { return l->tickets ? l->tickets + side * huge_row_tickets(l->scratch_ld) : nullptr; }
+
 static const DenseSplit *split_of(const nerva_layer *l) { return l->cur.split.rows.n > 0 ? &l->cur.split : nullptr; }
 
 // Message for the status word of the device-side CSR check (bind_check_kernel).
@@ -943,7 +946,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         out->scratch_ld = round_up(max_batch, 64);
         if (slots > 0) {
             const int64_t huge = std::max(out->plan.n_huge_rows, out->plan_t.n_huge_rows);
-            HIP_TRY(reserve(&l->tickets, &l->ticket_ints, static_cast<size_t>(huge * huge_row_tickets(out->scratch_ld)), true, s));
+            HIP_TRY(reserve(&l->tickets, &l->ticket_ints, static_cast<size_t>(2 * huge * huge_row_tickets(out->scratch_ld)), true, s));
             HIP_TRY(reserve(&l->scratch, &l->scratch_floats, static_cast<size_t>(slots * out->scratch_ld)));
         }
         out->full = rows <= kFullMaxRows && static_cast<int64_t>(nnz) == static_cast<int64_t>(rows) * cols;
@@ -1111,7 +1114,7 @@ int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx,
         return NERVA_OK;
     }
     SpmmArgs a{};
-    a.blocks = layer->plan; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = layer->tickets; a.scratch_ld = layer->scratch_ld;
+    a.blocks = layer->plan; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 0); a.scratch_ld = layer->scratch_ld;
     a.indptr = layer->indptr; a.indices = layer->indices; a.values = layer->values; a.bias = layer->bias;
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
     a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.relu = layer->activation == NERVA_ACT_RELU;
@@ -1139,7 +1142,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
     bool form_dz = false, mask = relu;   // mask: dY still is the gradient of the output
     auto make_t = [&] {
         SpmmArgs a{};
-        a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = layer->tickets; a.scratch_ld = layer->scratch_ld;
+        a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 1); a.scratch_ld = layer->scratch_ld;
         a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
         a.X = dY; a.ldx = lddy;
         if (mask) { a.XM = Y; a.ldxm = ldy; }
@@ -1374,7 +1377,7 @@ static int check_step_args(const nerva_mlp *mlp, const float *X, int32_t ldx, in
 static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldin, float *out, int64_t ldout, int32_t batch)
 {
     SpmmArgs a{};
-    a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = ly->tickets; a.scratch_ld = ly->scratch_ld;
+    a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = tickets_of(ly, 0); a.scratch_ld = ly->scratch_ld;
     a.indptr = ly->indptr; a.indices = ly->indices; a.values = ly->values; a.bias = ly->bias;
     a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
     a.rows = ly->rows; a.x_rows = ly->cols; a.batch = batch; a.relu = ly->activation == NERVA_ACT_RELU;
@@ -1480,7 +1483,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         // applied as the transposed product is stored
         nerva_layer *ly = mlp->layers[l];
         SpmmArgs t{};
-        t.blocks = ly->plan_t; t.nnz = ly->nnz; t.scratch = ly->scratch; t.tickets = ly->tickets; t.scratch_ld = ly->scratch_ld;
+        t.blocks = ly->plan_t; t.nnz = ly->nnz; t.scratch = ly->scratch; t.tickets = tickets_of(ly, 1); t.scratch_ld = ly->scratch_ld;
         t.indptr = ly->indptr_t; t.indices = ly->indices_t; t.values = ly->values_t;
         t.X = dZ(l); t.ldx = L.ld; t.Y = dZ(l - 1); t.ldy = L.ld;
         t.YM = A(l - 1); t.ldym = L.ld;

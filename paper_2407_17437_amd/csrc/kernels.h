@@ -126,7 +126,8 @@ struct SpmmArgs {
     int32_t nnz;             // length of indices/values
     float *scratch;          // partial rows of huge-row work-groups, (n_huge_blocks, scratch_ld)
     int64_t scratch_ld;
-    int32_t *tickets;        // (n_huge_rows, huge_row_tickets(scratch_ld)), all 0 between launches
+    int32_t *tickets;        // huge row k's: huge_row_tickets(scratch_ld) of them from tickets + 2 * k * huge_row_tickets(scratch_ld) on (the
+                             // other orientation's lie between); all 0 between launches
     // Only for a matrix that stores every entry and has at most kFullMaxRows rows (a saturated
     // output layer): values[] is then the row-major dense matrix, and the product streams the
     // operand once for all rows instead of gathering it once per row.  Partial results of the

@@ -127,7 +127,7 @@ hipError_t hipLaunchKernel(const void *kernel, dim3, dim3, void **args, size_t, 
     if (takes("8SpmmArgs")) {
         const SpmmArgs &a = *static_cast<const SpmmArgs *>(args[0]);
         check(&a, sizeof a);
-        const int64_t tickets = a.blocks.n_huge_rows * huge_row_tickets(a.scratch_ld);
+        const int64_t tickets = a.blocks.n_huge_rows > 0 ? (2 * a.blocks.n_huge_rows - 1) * huge_row_tickets(a.scratch_ld) : 0;
         if (tickets > 0) {
             if (!holds(a.scratch, a.blocks.n_huge_blocks * a.scratch_ld * 4) || !holds(a.tickets, tickets * 4))
                 ++bad_pointers;

@@ -94,6 +94,39 @@ def test_dense_rows_keep_a_non_finite_operand_row_to_the_rows_that_read_it(nb, o
     L.close()
 
 
+def test_huge_rows_after_products_that_overlapped(nb, oracle):
+    """Products of one layer on several streams at once may spoil one another (their results are not looked at), but no product
+    that is ordered after them: the shares of its huge rows are counted from 0 again, in both orientations."""
+    import torch
+    rng = np.random.default_rng(3)
+    rows, cols, batch = 5000, 6000, 100
+    lens = np.full(rows, 3)
+    lens[::125] = rng.integers(2000, 5900, 40)
+    indptr, indices = wl.pattern_from_row_nnz(lens, cols, seed=4)
+    for i in np.nonzero(lens == 3)[0]:
+        indices[indptr[i]:indptr[i + 1]] = np.sort(rng.choice(10, 3, replace=False))   # ten columns of 1500 entries
+    lay = wl.SparseLayerData(rows, cols, indptr, indices, wl.init_values(indptr, 5), np.zeros(rows, np.float32), False)
+    L = nb.SparseLinear(lay, max_batch=batch)
+    X, dY = (rng.standard_normal((n, batch)).astype(np.float32) for n in (cols, rows))
+    Xd, dYd = nb.to_dense(X), nb.to_dense(dY)
+    Ys, dXs = [nb.dense(rows, batch) for _ in range(3)], [nb.dense(cols, batch) for _ in range(3)]
+    streams = [torch.cuda.Stream() for _ in Ys]
+    torch.cuda.synchronize()
+    for _ in range(100):
+        for s, Y, dX in zip(streams, Ys, dXs):
+            nb.sparse_linear_forward(L.handle, Xd, Y, batch, s)
+            nb.sparse_linear_backward(L.handle, None, None, dYd, dX, None, None, batch, s)
+    torch.cuda.synchronize()
+    nb.sparse_linear_forward(L.handle, Xd, Ys[0], batch)
+    nb.sparse_linear_backward(L.handle, None, None, dYd, dXs[0], None, None, batch)
+    torch.cuda.synchronize()
+    Y, S = oracle.spmm(rows, cols, indptr, indices, lay.values, lay.bias, X, False)
+    close(Ys[0].cpu().numpy(), Y, S, what="Y")
+    dX, S = oracle.spmm_t(rows, cols, indptr, indices, lay.values, dY)
+    close(dXs[0].cpu().numpy(), dX, S, what="dX")
+    L.close()
+
+
 @pytest.mark.parametrize("batch", [257, 300, 320, 385, 511, 512, 513, 640, 1023, 1024, 1025])
 def test_wide_batches_in_column_tiles(nb, oracle, batch):
     # (operands of 300 rows, which no rule tiles; rows cut over several waves and several work-groups)
