@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kSampledWaves * kWave) void sampled_update_kernel(c
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 zn[u] = own < A.batch ? drop_shared(zn[u], own, c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                if (own >= A.batch) xn[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                xn[u] = own < A.batch ? drop_shared(xn[u], own, c) : make_float4(0.f, 0.f, 0.f, 0.f);
             }
         }
     };

@@ -44,13 +44,23 @@ __device__ __forceinline__ void st4(float *p, float4 v)
 // read or written whatever the leading dimension.  The columns that it shares with its neighbour are computed by both,
 // in the same order, to the same bits.
 __device__ __forceinline__ int four_columns(int col, int batch) { return min(col, batch - 4); }
-// ... and the lane's share of a sum over columns: those of its four that the neighbour does not have
+// ... and the lane's share of a sum over columns: those of its four that the neighbour does not have.  In a sum of products both
+// factors are dropped: 0 times an Inf or NaN is no 0.
 __device__ __forceinline__ float4 drop_shared(float4 x, int col, int first)
 {
     if (first < col) x.x = 0.f;
     if (first + 1 < col) x.y = 0.f;
     if (first + 2 < col) x.z = 0.f;
     return x;
+}
+// sum + the products of z and x over the lane's own columns (as above; none where col lies beyond the batch), whatever the others hold
+__device__ __forceinline__ float add_own_products(float sum, float4 z, float4 x, int col, int first, int batch)
+{
+    if (col >= batch) return sum;
+    if (first >= col) sum = fmaf(z.x, x.x, sum);
+    if (first + 1 >= col) sum = fmaf(z.y, x.y, sum);
+    if (first + 2 >= col) sum = fmaf(z.z, x.z, sum);
+    return fmaf(z.w, x.w, sum);
 }
 
 // Data-parallel-primitive move: lane l receives x from the lane that CTRL names; lanes in rows

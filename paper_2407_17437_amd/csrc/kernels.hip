@@ -1050,7 +1050,9 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
 // groups of 4 / 8), reduced inside the group with DPP
 // moves.  Results of up to 64 consecutive entries are collected one per lane, so the store of
 // g -- or the fused momentum step on values/velocity -- is a coalesced access.
-// Lanes whose columns lie beyond the batch hold dZ = 0 and re-read the row's first columns.
+// Lanes whose columns lie beyond the batch hold dZ = 0 and re-read the row's first columns.  SPARE: there are such lanes, or lanes
+// that share columns; a result that is NaN, which an Inf there would make it, is formed again from every lane's own columns
+// (asked once per 64 entries; dropping the gathered side of every entry instead takes four selects beside its four multiply-adds).
 // ---------------------------------------------------------------------------------------
 // By-product carried by an SDDMM launch: the mean of the per-column losses the head kernel left.
 __device__ __forceinline__ void mean_loss_task(const SddmmArgs &a, int block)
@@ -1096,8 +1098,30 @@ __device__ __forceinline__ void sddmm_pass(gmem_ptr Xg, int it0, int my_ro, cons
     }
 }
 
-// col0: first column of the pass, which covers G*4*NV columns of the batch.
+// The results of `iters` such iterations from every lane's own columns alone (col0: first column of the pass).
 template <int G, int NV>
+__device__ __forceinline__ float sddmm_own_columns(gmem_ptr Xg, int iters, int my_ro, const uint32_t (&off)[NV], const float4 (&dz)[NV], int col0,
+                                                   int batch)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int lig = lane % G;
+    float res = 0.f;
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+        const uint32_t ro = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(((lane / G) * G + it) * 4, my_ro));
+        float part = 0.f;
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            part = add_own_products(part, dz[t], gload4(Xg, ro + off[t]), col0 + (t * G + lig) * 4, static_cast<int>(off[t] >> 2), batch);
+        }
+        part = group_sum<G>(part);
+        if (lig == it) res = part;
+    }
+    return res;
+}
+
+// col0: first column of the pass, which covers G*4*NV columns of the batch.
+template <int G, int NV, bool SPARE>
 __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, const int col0 = 0)
 {
     constexpr int NG = kWave / G;
@@ -1158,6 +1182,7 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, 
     const uint32_t ldxb = static_cast<uint32_t>(a.ldx) * 4u;
     const gmem_ptr Xg = as_gmem(a.X);
     const int q_mine = lig * NG + grp;  // slot of this lane inside a chunk of 64 entries
+    const bool spare = SPARE && col0 + G * 4 * NV > a.batch;  // uniform
 
     for (int pc = s0; pc < s1; pc += kWave) {
         const int n = min(kWave, s1 - pc);
@@ -1183,6 +1208,7 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, 
         if constexpr (UI >= 4)
             if (it + 2 <= iters) { sddmm_pass<G, NV, 2>(Xg, it, my_ro, off, dz, res); it += 2; }
         if (it < iters) sddmm_pass<G, NV, 1>(Xg, it, my_ro, off, dz, res);
+        if (spare && __any(res != res)) res = sddmm_own_columns<G, NV>(Xg, iters, my_ro, off, dz, col0, a.batch);
         if (mine) {
             if (a.g) a.g[p] = res;
             if (a.fused) {
@@ -1196,17 +1222,17 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, 
     }
 }
 
-template <int G, int NV>
+template <int G, int NV, bool SPARE>
 __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 {
-    sddmm_body<G, NV>(a, blockIdx.x);
+    sddmm_body<G, NV, SPARE>(a, blockIdx.x);
 }
 
 // Column-tiled SDDMM for operands X that no L2 holds: tile t covers columns [t*W, t*W + W), W =
 // G*4*NV; a work-group computes the partial products of its rows over one tile and stores them (and the partial row
 // sums of dZ) in the tile's slice of the partial buffer.  Work-group ids are decoded XCD-first as
 // in spmm_tiled_kernel, so an operand tile stays in one L2 while every entry gathers from it.
-template <int G, int NV>
+template <int G, int NV, bool SPARE>
 __global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const int spread)
 {
     const int nrb = a.blocks.n_blocks;
@@ -1225,7 +1251,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, 
     t.g = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
     t.db = t.g + a.partial_db_at;
     if (tile != 0) t.loss_cols = nullptr;
-    sddmm_body<G, NV>(t, rb, tile * (G * 4 * NV));
+    sddmm_body<G, NV, SPARE>(t, rb, tile * (G * 4 * NV));
 }
 
 // ---- staged SDDMM --------------------------------------------------------------------------
@@ -1402,7 +1428,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
                 if (k < a.x_rows && col_on) v[i] = ld4(a.X + static_cast<int64_t>(k) * a.ldx + col);
             }
 #pragma unroll
-            for (int i = 0; i < kHalf; ++i) stage[((h * kHalf + i) * 64 + (threadIdx.x >> 4)) * 16 + lig] = v[i];
+            for (int i = 0; i < kHalf; ++i) stage[((h * kHalf + i) * 64 + (threadIdx.x >> 4)) * 16 + lig] = drop_shared(v[i], own_col, col);
         }
         int off_next[kStageJ];
         int e3 = e2;
@@ -1486,7 +1512,7 @@ __global__ __launch_bounds__(kBlock) void full_sddmm_kernel(const SddmmArgs a, c
         for (int ch = 0; ch < n_chunks; ++ch) {
             const int own = (ch * kWave + lane) * 4;
             const int col = four_columns(own, a.batch);
-            const float4 x = own < a.batch ? ld4(xr + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 x = own < a.batch ? drop_shared(ld4(xr + col), own, col) : make_float4(0.f, 0.f, 0.f, 0.f);
             float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int i = 0; i < kFullMaxRows; ++i) {
@@ -1648,6 +1674,22 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int 
     }
 }
 
+// The products of `steps` such entries from every lane's own columns alone, where a lane's others made one of them NaN.
+template <int GS, bool XMASK>
+__device__ __forceinline__ float bwd_own_columns(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, uint32_t off, const float4 &ax, int steps, int lig,
+                                                 int own_col, int batch)
+{
+    float res = 0.f;
+#pragma unroll 1
+    for (int u = 0; u < steps; ++u) {
+        float4 x = gload4(Zg, static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src + u * 4, my_ro)) + off);
+        if constexpr (XMASK) x = keep_where_positive(x, gload4(Mg, static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src + u * 4, my_mo)) + off));
+        const float part = group_sum<GS>(add_own_products(0.f, ax, x, own_col, static_cast<int>(off >> 2), batch));
+        res = lig == u ? part : res;
+    }
+    return res;
+}
+
 // Sums of the rows of dZ, a wave per row: the bias gradient, stored or applied.
 __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t wave, int64_t n_waves)
 {
@@ -1680,8 +1722,11 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // the lane groups and the matrix is small: then a wave takes its entries through all tiles.  XMASK: dZ is dY times
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
-template <int GS, BackwardPass PASS, bool XMASK>
-__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
+// SPARE: as in sddmm_body.
+// (waves per SIMD that the registers of the gathers allow: the products that are formed again are not to cost any)
+constexpr int backward_waves(BackwardPass pass, bool masked) { return pass == kBackwardTiles ? (masked ? 6 : 8) : pass == kBackwardOneTile ? (masked ? 5 : 6) : (masked ? 4 : 6); }
+template <int GS, BackwardPass PASS, bool XMASK, bool SPARE>
+__global__ __launch_bounds__(kBwdWaves * kWave) __attribute__((amdgpu_waves_per_eu(SPARE ? backward_waves(PASS, XMASK) : 1))) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
                                                                           const int n_pack_blocks, const int lg_split)
 {
     constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped;
@@ -1745,7 +1790,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                 const int col = four_columns(on ? own_col : col0, a.batch);
                 const uint32_t off = static_cast<uint32_t>(col) * 4u;
                 // the group's row of X: the second operand of its entries' products, and the mask of its result;
-                // lanes beyond the batch hold zeros, so that the columns they re-read add nothing to a product
+                // lanes beyond the batch hold zeros, so that the columns they re-read add nothing to a product (Inf or NaN there: see below)
                 float4 ax = make_float4(0.f, 0.f, 0.f, 0.f), mask = ax;
                 if (row >= 0 && on) {
                     mask = ld4(a.X + static_cast<int64_t>(row) * a.ldx + col);
@@ -1776,6 +1821,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                         u0 += 2; src += 8;
                     }
                     if (u0 < steps) bwd_pass<1, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                    if (SPARE && col0 + GS * 4 > a.batch && __any(res != res)) res = bwd_own_columns<GS, XMASK>(Zg, Mg, src0, my_ro, my_mo, off, ax, steps, lig, own_col, a.batch);
                     const int e = base + part * GS + lig;
                     if (row >= 0 && e < len) {
                         if constexpr (ONE) {
@@ -1848,7 +1894,7 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
 
 // Two independent launches of a training step in one grid: work-groups [0, na) run the first,
 // the rest the second.  Saves a launch (and its drain) on the step's critical path.
-template <int GS_S, int G, int NV_D>
+template <int GS_S, int G, int NV_D, bool SPARE>
 __global__ __launch_bounds__(kBlock) void spmm_sddmm_pair_kernel(const SpmmArgs a, const SddmmArgs b, const int na)
 {
     if (static_cast<int>(blockIdx.x) < na) {
@@ -1857,16 +1903,16 @@ __global__ __launch_bounds__(kBlock) void spmm_sddmm_pair_kernel(const SpmmArgs 
         else
             spmm_wide_body<false>(a, blockIdx.x % a.blocks.n_blocks, blockIdx.x / a.blocks.n_blocks * 256);
     } else {
-        sddmm_body<G, NV_D>(b, blockIdx.x - na);
+        sddmm_body<G, NV_D, SPARE>(b, blockIdx.x - na);
     }
 }
-template <int G, int NV_D>
-__global__ __launch_bounds__(kBlock) void sddmm_pair_kernel(const SddmmArgs a, const SddmmArgs b, const int na)
+template <int G, int NV_D, bool SPARE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SPARE ? 8 : 1))) void sddmm_pair_kernel(const SddmmArgs a, const SddmmArgs b, const int na)
 {
     if (static_cast<int>(blockIdx.x) < na)
-        sddmm_body<G, NV_D>(a, blockIdx.x);
+        sddmm_body<G, NV_D, SPARE>(a, blockIdx.x);
     else
-        sddmm_body<G, NV_D>(b, blockIdx.x - na);
+        sddmm_body<G, NV_D, SPARE>(b, blockIdx.x - na);
 }
 
 // Any batch size, operands of any span: one column per lane and pass, both operands re-read per stored
@@ -2421,11 +2467,19 @@ hipError_t spmm_packed_go(const SpmmArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+// go(SPARE) for kernels whose work-groups cover `columns` of the batch at a time
+template <typename F>
+void with_spare(int batch, int columns, F &&go)
+{
+    if (batch % columns) go(std::true_type{});
+    else go(std::false_type{});
+}
+
 template <int G, int NV>
 hipError_t sddmm_go(const SddmmArgs &a, hipStream_t s)
 {
     dim3 grid(a.blocks.n_blocks);
-    hipLaunchKernelGGL((sddmm_kernel<G, NV>), grid, dim3(kBlock), 0, s, a);
+    with_spare(a.batch, G * 4 * NV, [&](auto spare) { hipLaunchKernelGGL((sddmm_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a); });
     return hipGetLastError();
 }
 
@@ -2550,7 +2604,9 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
     const int spread = n_tiles >= 8;
     const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * a.blocks.n_blocks;
     dim3 grid(static_cast<unsigned>(ids));
-    hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
+    with_spare(a.batch, W, [&](auto spare) {
+        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
+    });
     sddmm_finish_go(a, n_tiles, s);
     return hipGetLastError();
 }
@@ -2566,7 +2622,9 @@ hipError_t pair_go(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
 {
     const int na = a.blocks.n_blocks * (GS_S == kWave ? (a.batch + 255) / 256 : 1);
     dim3 grid(na + b.blocks.n_blocks);
-    hipLaunchKernelGGL((spmm_sddmm_pair_kernel<GS_S, G, NV_D>), grid, dim3(kBlock), 0, s, a, b, na);
+    with_spare(b.batch, G * 4 * NV_D, [&](auto spare) {
+        hipLaunchKernelGGL((spmm_sddmm_pair_kernel<GS_S, G, NV_D, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, b, na);
+    });
     return hipGetLastError();
 }
 
@@ -2575,7 +2633,9 @@ hipError_t sddmm_pair_go(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 {
     const int na = a.blocks.n_blocks;
     dim3 grid(na + b.blocks.n_blocks);
-    hipLaunchKernelGGL((sddmm_pair_kernel<G, NV_D>), grid, dim3(kBlock), 0, s, a, b, na);
+    with_spare(b.batch, G * 4 * NV_D, [&](auto spare) {
+        hipLaunchKernelGGL((sddmm_pair_kernel<G, NV_D, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, b, na);
+    });
     return hipGetLastError();
 }
 
@@ -2802,8 +2862,10 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         constexpr int GS = decltype(group)::value;
         const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
         auto launch = [&](auto pass, auto mask) {
-            hipLaunchKernelGGL((backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value>), grid, block, 0, s, a, n_tiles, spread, n_pack_blocks,
-                               lg_split);
+            with_spare(a.batch, GS * 4, [&](auto spare) {
+                hipLaunchKernelGGL((backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value>), grid, block, 0, s, a,
+                                   n_tiles, spread, n_pack_blocks, lg_split);
+            });
         };
         using tiles = std::integral_constant<BackwardPass, kBackwardTiles>;
         using single = std::integral_constant<BackwardPass, kBackwardOneTile>;
@@ -3011,7 +3073,10 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
             const int spread = n_tiles >= 8;
             const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * rest.blocks.n_blocks;
-            hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles, spread);
+            with_spare(a.batch, kStageCols, [&](auto spare) {
+                hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1, decltype(spare)::value>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles,
+                                   spread);
+            });
         }
         sddmm_finish_go(a, n_tiles, s);
         return hipGetLastError();

@@ -127,6 +127,56 @@ def test_huge_rows_after_products_that_overlapped(nb, oracle):
     L.close()
 
 
+def with_infinities(rng, features, batch):
+    """Every third row holds an infinity: in the first column, which idle lanes re-read, or in one of the last four, which the lanes
+    of a ragged batch share."""
+    M = rng.standard_normal((features, batch)).astype(np.float32)
+    at = np.arange(0, features, 3)
+    M[at, np.where(at % 2 == 0, 0, np.maximum(batch - 1 - at % 4, 0))] = np.where(at % 5 == 0, -np.inf, np.inf)
+    return M
+
+
+@pytest.mark.parametrize("rows,cols,density,batch,relu,dx", [
+    # gathered entry by entry: every number of lanes per entry and of columns per lane
+    *[(150, 260, 0.1, batch, False, False) for batch in (5, 16, 21, 33, 50, 63, 77, 97, 100, 129, 150, 193, 257, 385, 513, 769, 1023)],
+    (700, 9000, 0.002, 101, False, False), (2100, 13000, 0.001, 650, False, False),   # column tiles
+    (600, 700, 0.4, 67, False, False), (600, 700, 0.4, 130, False, True),    # sampled from the matrix units' tiles
+    (10, 400, 1.0, 70, False, False), (10, 400, 1.0, 301, False, False),     # a full matrix of few rows
+    # with the other gradient, on one gather stream: a single tile, rows through all tiles, several tiles; masked by the output
+    (300, 500, 0.05, 6, False, True), (300, 500, 0.05, 41, True, True), (300, 500, 0.05, 101, False, True), (300, 500, 0.05, 203, True, True),
+    (700, 1000, 0.04, 301, False, True), (700, 1000, 0.02, 302, True, True), (3000, 700, 0.02, 999, False, True),
+    (900, 2000, "staged", 259, False, False), (900, 2000, "staged", 449, False, False),
+])
+def test_infinities_reach_the_gradients_of_their_own_columns(nb, rows, cols, density, batch, relu, dx):
+    """An entry's gradient is the sum over the batch's columns, whatever the lanes that have none of them re-read: infinite where
+    one product is, and NaN only where two of them cancel or one is 0 times infinity."""
+    import torch
+    staged = density == "staged"
+    lay = layer_case(rows, cols, 0.02 if staged else density, seed=rows + batch, relu=relu)
+    rng = np.random.default_rng(batch)
+    X, dY = with_infinities(rng, cols, batch), with_infinities(rng, rows, batch)
+    Y = rng.standard_normal((rows, batch)).astype(np.float32)
+    if staged:
+        nb.nerva_set_partition_mode(nb.NERVA_PARTITION_PREFER_STAGED)
+    try:
+        L = nb.SparseLinear(lay, max_batch=batch)
+    finally:
+        nb.nerva_set_partition_mode(nb.NERVA_PARTITION_BALANCED)
+    g, db = torch.full((lay.nnz,), 7.0, device="cuda"), torch.full((rows,), 7.0, device="cuda")
+    nb.sparse_linear_backward(L.handle, nb.to_dense(X, ld=batch), nb.to_dense(Y, ld=batch) if relu else None, nb.to_dense(dY, ld=batch),
+                              nb.dense(cols, batch, ld=batch) if dx else None, g, db, batch)
+    torch.cuda.synchronize()
+    dZ = np.where(Y > 0, dY, np.float32(0)).astype(np.float64) if relu else dY.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        products = dZ[np.repeat(np.arange(rows), np.diff(lay.indptr))] * X[lay.indices].astype(np.float64)
+        for what, got, ref, S in (("dvalues", g, products.sum(1), np.abs(products).sum(1)), ("dbias", db, dZ.sum(1), np.abs(dZ).sum(1))):
+            got, fine = got.cpu().numpy(), np.isfinite(ref)
+            assert fine.any() and np.isinf(ref).any()
+            close(got[fine], ref[fine], S[fine], what=what)
+            assert np.array_equal(got[~fine], ref[~fine].astype(np.float32), equal_nan=True), what
+    L.close()
+
+
 @pytest.mark.parametrize("batch", [257, 300, 320, 385, 511, 512, 513, 640, 1023, 1024, 1025])
 def test_wide_batches_in_column_tiles(nb, oracle, batch):
     # (operands of 300 rows, which no rule tiles; rows cut over several waves and several work-groups)
@@ -142,7 +192,6 @@ def test_wide_batches_in_column_tiles(nb, oracle, batch):
     (900, 500, 0.05, 64, None, True), (900, 500, 0.3, 65, 65, False), (500, 900, 0.01, 128, None, False),  # one tile of 64 and 128 columns
     (700, 1000, 0.04, 129, 129, False), (700, 1000, 0.04, 256, None, True),                                # one tile of 256
     (6000, 700, 0.01, 200, None, False), (700, 1000, 0.04, 257, 257, True), (600, 9000, 0.005, 700, None, False),   # several tiles
-    (700, 1000, 0.03, 300, None, True), (300, 2000, 0.02, 1025, 1025, False), (300, 2000, 0.02, 513, None, True),   # rows through all tiles
     (700, 1000, 0.03, 300, None, True), (300, 2000, 0.02, 1025, 1025, False), (300, 2000, 0.02, 513, None, True),   # rows through all tiles
     (9000, 400, 0.02, 16, None, False), (3, 1500, 0.5, 100, None, False),   # rows shared by lane groups; hardly any rows to sum
 ])
