@@ -19,9 +19,10 @@ extern "C" {
  * rows, no staged products -- so that the balanced partition can be timed against it on the same
  * matrix.  NERVA_PARTITION_PREFER_STAGED: the balanced partition, but the staged products and the
  * staged SDDMM (see nerva_plan_staged_host) run wherever they can (batch of at least
- * NERVA_STAGE_MIN_BATCH columns, a multiple of 4), also where the library's own rule expects them
- * to be slower. */
-enum { NERVA_PARTITION_BALANCED = 0, NERVA_PARTITION_ROW_SPLIT = 1, NERVA_PARTITION_PREFER_STAGED = 2 };
+ * NERVA_STAGE_MIN_BATCH columns), also where the library's own rule expects them
+ * to be slower.  NERVA_PARTITION_PREFER_DENSE_ROWS: the balanced partition, but where a matrix has rows dense enough
+ * for matrix instructions at the layer's max_batch, these serve them at every batch from 128 columns on. */
+enum { NERVA_PARTITION_BALANCED = 0, NERVA_PARTITION_ROW_SPLIT = 1, NERVA_PARTITION_PREFER_STAGED = 2, NERVA_PARTITION_PREFER_DENSE_ROWS = 3 };
 int nerva_set_partition_mode(int32_t mode);
 
 /* Measurement aid: the density from which sparse_linear_create / sparse_linear_rebind put a layer on the

@@ -99,6 +99,8 @@ struct PatternBuffers {
     size_t row_table_ints = 0;
     float *row_partial = nullptr;   // sliced results of their product
     size_t row_partial_floats = 0;
+    int32_t *whole_staged = nullptr;   // staged plan of all rows beside that of the rows that are not dense
+    size_t whole_staged_ints = 0;
     DenseSplit split{};             // views into plan_mem and row_table
 };
 
@@ -516,10 +518,11 @@ struct PlanRoom {
         ranges = staged_range_bound(rows, other, max_batch);
         cblocks = (other + kStageRows - 1) / kStageRows;
     }
+    size_t staged_ints() const { return static_cast<size_t>(ranges) * (kStageRangeRows * (cblocks + 2) + 4); }
     size_t ints() const
     {
         return static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks + rest_blocks) + huge_rows + rows_by_length)) +
-               static_cast<size_t>(ranges) * (kStageRangeRows * (cblocks + 2) + 4) + static_cast<size_t>(dense_rows + dense_flags) +
+               staged_ints() + static_cast<size_t>(dense_rows + dense_flags) +
                (dense_flags ? static_cast<size_t>(4 * kWavesPerBlock * (blocks + long_blocks)) : 0);
     }
     // the tables at `mem` (16-byte records first)
@@ -540,10 +543,14 @@ struct PlanRoom {
         int32_t *i = reinterpret_cast<int32_t *>(r);
         t.dense_rows = i; i += dense_rows;
         t.dense_flag = reinterpret_cast<uint8_t *>(i); i += dense_flags;
+        staged_at(t, i);
+        return t;
+    }
+    void staged_at(PlanTables &t, int32_t *i) const
+    {
         t.staged_rows = i; i += static_cast<size_t>(ranges) * kStageRangeRows;
         t.staged_ends = i; i += static_cast<size_t>(ranges) * kStageRangeRows * (cblocks + 1);
         t.staged_groups = i;
-        return t;
     }
 };
 
@@ -579,6 +586,7 @@ void free_pattern_buffers(PatternBuffers &b)
     (void)hipFree(b.table);
     (void)hipFree(b.row_table);
     (void)hipFree(b.row_partial);
+    (void)hipFree(b.whole_staged);
     b = PatternBuffers{};
 }
 
@@ -681,7 +689,7 @@ int nerva_validate_csr_host(int32_t rows, int32_t cols, int64_t nnz, const int32
 
 int nerva_set_partition_mode(int32_t mode)
 {
-    if (mode != NERVA_PARTITION_BALANCED && mode != NERVA_PARTITION_ROW_SPLIT && mode != NERVA_PARTITION_PREFER_STAGED) return fail(NERVA_ERR_ARGUMENT, "unknown partition mode %d", mode);
+    if (mode < NERVA_PARTITION_BALANCED || mode > NERVA_PARTITION_PREFER_DENSE_ROWS) return fail(NERVA_ERR_ARGUMENT, "unknown partition mode %d", mode);
     g_partition_mode.store(mode);
     return NERVA_OK;
 }
@@ -840,7 +848,8 @@ struct BuiltPattern {
 static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, const int32_t *indices, const float *values,
                             BuiltPattern *out, hipStream_t s)
 {
-    const int32_t rows = l->rows, cols = l->cols, max_batch = l->max_batch, mode = g_partition_mode.load();
+    const int32_t rows = l->rows, cols = l->cols, max_batch = l->max_batch, asked = g_partition_mode.load();
+    const int32_t mode = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? NERVA_PARTITION_BALANCED : asked;
     static_assert(kPlanBalanced == NERVA_PARTITION_BALANCED && kPlanRowSplit == NERVA_PARTITION_ROW_SPLIT &&
                   kPlanPreferStaged == NERVA_PARTITION_PREFER_STAGED, "header and kernels disagree");
     PatternBuffers &B = l->spare;
@@ -898,7 +907,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         HIP_TRY(launch_pattern_table(indptr, indices, nullptr, rows, table_words(l), reinterpret_cast<uint2 *>(B.table), m.status, s));
     }
     HIP_TRY(hipStreamSynchronize(s));
-    const BindResult &R = *l->bind_result;
+    const BindResult R = *l->bind_result;
     if (R.status[0] != 0) return csr_status_error(R.status);
     out->plan = plan_view(p.side[0].tables, R.plan[0], cols, nnz, R.plan[1].hot_nnz, mode);
     bool more_work = false;   // launches after the wait
@@ -916,7 +925,20 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         B.split.others = out->plan;
         B.split.others.waves = t.other_waves;
         B.split.others.long_waves = t.other_long_waves;
-        out->plan.staged_rows = nullptr;   // (it covers the other rows only)
+        B.split.from_batch = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? kDenseRowsMinBatch : dense_rows_from(R.plan[0].dense_nnz);
+        // The staged plan covers the other rows only.  Narrower batches, at which the dense rows are rows like any other, get one of
+        // all rows where the widest of them that fills its tiles (staged_pays) has work-groups enough for it.
+        out->plan.staged_rows = nullptr;
+        const int32_t tiles = static_cast<int32_t>(std::min<int64_t>(5ll * (B.split.from_batch - 1), 5ll * max_batch) / (4 * kStageCols));
+        if (B.split.from_batch > kStageMinBatch && room.ranges > 0 && tiles * staged_ranges_aim(rows, max_batch) >= kStageTargetGroups / 2) {
+            HIP_TRY(reserve(&B.whole_staged, &B.whole_staged_ints, room.staged_ints()));
+            PlanArgs whole = p;
+            whole.side[0].dense_len = INT32_MAX;
+            room.staged_at(whole.side[0].tables, B.whole_staged);
+            HIP_TRY(launch_plan(whole, 1, s));   // (the other tables come out as they are)
+            HIP_TRY(hipStreamSynchronize(s));
+            out->plan = plan_view(whole.side[0].tables, l->bind_result->plan[0], cols, nnz, R.plan[1].hot_nnz, mode);
+        }
         HIP_TRY(launch_pattern_table(indptr, indices, D.list, D.n, D.words, reinterpret_cast<uint2 *>(B.row_table), nullptr, s));
         more_work = true;
     }

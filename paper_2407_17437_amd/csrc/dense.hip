@@ -795,7 +795,7 @@ static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch)
     return best;
 }
 
-bool dense_rows_ok(const DenseSplit *d, int32_t batch) { return d && d->rows.n > 0 && batch >= kDenseRowsMinBatch; }
+bool dense_rows_ok(const DenseSplit *d, int32_t batch) { return d && d->rows.n > 0 && batch >= d->from_batch; }
 
 int64_t dense_rows_partial(int32_t n, int32_t cols, int32_t max_batch)
 {

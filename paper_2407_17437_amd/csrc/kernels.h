@@ -87,17 +87,24 @@ struct DenseRows {
     float *partial;                // results of the slices of K, partial_floats long
     int64_t partial_floats;
 };
-// A matrix some of whose rows are served that way: those, and the partition without them that the others then run on
-// (the staged plan is part of it alone).  Host memory.
+// A matrix some of whose rows are served that way, from `from_batch` columns on: those, and the partition without them that the
+// others then run on.  Host memory.
 struct DenseSplit {
     DenseRows rows;                // n = 0: there are none, or too few
+    int32_t from_batch;
     const uint8_t *flag;           // [rows of the matrix] 1: a dense row
     RowBlocks others;
 };
 constexpr int32_t kDenseRowsMinCols = 1024;    // (so that a dense row is longer than kPackMaxLen)
 constexpr int32_t kDenseRowsMin = 17;          // fewer rows than this stay with the others
 constexpr int64_t kDenseRowsMinWork = 192 << 20;  // entries times columns of the batch from which the extra launch pays
-constexpr int32_t kDenseRowsMinBatch = kStageMinBatch;   // (below it the staged plan, which leaves the dense rows out, is not needed either)
+constexpr int32_t kDenseRowsMinBatch = 128;    // (narrower ones leave much of a tile of 64 or 128 columns idle)
+// the batch from which the listed rows have that much work
+__host__ __device__ inline int32_t dense_rows_from(int64_t dense_nnz)
+{
+    const int64_t b = (kDenseRowsMinWork + dense_nnz - 1) / dense_nnz;
+    return b > kDenseRowsMinBatch ? static_cast<int32_t>(b) : kDenseRowsMinBatch;
+}
 // Stored entries from which a row counts as dense: an eighth of its columns.  At batch 1024 such a row costs the matrix units
 // 0.30 us per 16384 columns and the staged kernel 2.0 us times its density among power-law rows.
 __host__ __device__ inline int32_t dense_row_length(int32_t cols) { return cols / 8 > 128 ? cols / 8 : 129; }
@@ -404,6 +411,7 @@ struct PlanArgs {
     BindResult *result;
 };
 hipError_t launch_bind(const MirrorArgs &m, const PlanArgs &p, hipStream_t s);
+hipError_t launch_plan(const PlanArgs &p, int sides, hipStream_t s);   // its last part alone: the partitions of W, or of W and its mirror
 
 // Ranges a staged plan over `rows` rows with `nnz` entries aims at, 0: such a plan would never be chosen.  (Host and
 // device; `cols`: operand rows.)
@@ -442,13 +450,13 @@ __host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols
     const int64_t bound = want + (rows + 96 * want) / kStageRangeFill + 2;
     return bound * ((cols + kStageRows - 1) / kStageRows + 1) * kStageRangeRows > (1ll << 28) ? 0 : static_cast<int32_t>(bound);
 }
-// Whether the listed rows are worth a route of their own.  Start -> with it, forward product: power-law 4096^2 at 5 % (297 rows,
+// Whether the listed rows are worth a route of their own at max_batch columns (narrower calls ask again: dense_rows_ok).  Start -> with it, forward product: power-law 4096^2 at 5 % (297 rows,
 // 0.53 M entries) at batch 256 / 512 / 1024: 48 -> 50, 81 -> 77, 129 -> 120 us; 8192 x 1024 at 10 %: 35 -> 36, 87 -> 51, 109 -> 82.
 // Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even at 30 % (324 us; 20 %: 235 -> 326).
 __host__ __device__ inline bool dense_rows_pay(int32_t n_dense, int64_t dense_nnz, int64_t nnz, int32_t cols, int32_t max_batch)
 {
     return n_dense >= kDenseRowsMin && dense_nnz * 8 >= nnz && dense_nnz * 10 >= static_cast<int64_t>(n_dense) * cols * 3 &&
-           dense_nnz * max_batch >= kDenseRowsMinWork;
+           max_batch >= dense_rows_from(dense_nnz);
 }
 // which of `want` equal shares of the total cost a row falls into that has `done` of it before it
 __host__ __device__ inline int32_t staged_cut(int64_t done, int32_t want, int64_t total)

@@ -901,14 +901,19 @@ hipError_t launch_bind(const MirrorArgs &whole, const PlanArgs &p, hipStream_t s
         if (m.nnz > 0) hipLaunchKernelGGL(bin_scatter_kernel, dim3(m.tiles), dim3(kBig), static_cast<size_t>(m.bins) * 4, s, m);
         hipLaunchKernelGGL(bin_place_kernel, dim3(m.bins), dim3(kPlaceBlock), (3ll * width + 2ll * width * m.seg_words) * 4, s, m);
     }
+    return launch_plan(p, 2, s);
+}
+
+hipError_t launch_plan(const PlanArgs &p, int sides, hipStream_t s)
+{
     const int64_t plan_rows = p.side[0].rows > p.side[1].rows ? p.side[0].rows : p.side[1].rows;
     const int64_t plan_arrays = kPlanLds / 4 / plan_rows < 3 ? kPlanLds / 4 / plan_rows : 3;   // of the larger side; the smaller one may keep more
     const int64_t small = p.side[0].rows + p.side[1].rows - plan_rows, small_arrays = kPlanLds / 4 / small < 3 ? kPlanLds / 4 / small : 3;
     const int64_t plan_lds = 4 * (plan_arrays * plan_rows > small_arrays * small ? plan_arrays * plan_rows : small_arrays * small);
-    hipLaunchKernelGGL(plan_kernel, dim3(2), dim3(kBig), static_cast<size_t>(plan_lds), s, p);
-    hipLaunchKernelGGL(plan_fill_kernel, dim3(256, 2), dim3(kStageRangeRows), 0, s, p);
-    if (p.side[0].range_bound > 0 || p.side[1].range_bound > 0)
-        hipLaunchKernelGGL(staged_ends_kernel, dim3(1024, 2), dim3(kSetupBlock), 0, s, p);
+    hipLaunchKernelGGL(plan_kernel, dim3(sides), dim3(kBig), static_cast<size_t>(plan_lds), s, p);
+    hipLaunchKernelGGL(plan_fill_kernel, dim3(256, sides), dim3(kStageRangeRows), 0, s, p);
+    if (p.side[0].range_bound > 0 || (sides > 1 && p.side[1].range_bound > 0))
+        hipLaunchKernelGGL(staged_ends_kernel, dim3(1024, sides), dim3(kSetupBlock), 0, s, p);
     return hipGetLastError();
 }
 

@@ -59,6 +59,14 @@ def mixed_rows(rows, cols, n_dense, density, seed, relu=False):
     return wl.SparseLayerData(rows, cols, indptr, indices, wl.init_values(indptr, seed), rng.standard_normal(rows).astype(np.float32), relu)
 
 
+@pytest.fixture
+def dense_rows_at_any_batch(nb):
+    nb.nerva_set_partition_mode(nb.NERVA_PARTITION_PREFER_DENSE_ROWS)
+    yield
+    nb.nerva_set_partition_mode(nb.NERVA_PARTITION_BALANCED)
+
+
+@pytest.mark.usefixtures("dense_rows_at_any_batch")
 @pytest.mark.parametrize("rows,cols,n_dense,density,batch,ld,relu", [
     (2300, 1300, 129, 0.6, 128, None, True),    # short rows packed; a row tile with one row
     (2300, 1345, 128, 1.0, 131, 131, False),    # full row tiles, full rows, a last step of one column
@@ -72,6 +80,18 @@ def test_dense_rows(nb, oracle, rows, cols, n_dense, density, batch, ld, relu):
     check_layer(nb, oracle, mixed_rows(rows, cols, n_dense, density, rows + cols, relu), batch, ld=ld, max_batch=4096)
 
 
+@pytest.mark.parametrize("batch", [130, 320, 448])
+def test_dense_rows_on_either_side_of_their_batch(nb, oracle, batch):
+    """550 thousand entries in dense rows, bound for 1024 columns: up to 366 columns they are staged with all the others, or
+    gathered, from there on they go apart and the others are staged alone."""
+    rng = np.random.default_rng(8)
+    lens = rng.integers(180, 220, 16384)
+    lens[rng.permutation(16384)[:500]] = 1100
+    indptr, indices = wl.pattern_from_row_nnz(lens, 2048, seed=9)
+    check_layer(nb, oracle, wl.SparseLayerData(16384, 2048, indptr, indices, wl.init_values(indptr, 7), np.zeros(16384, np.float32), False), batch, max_batch=1024)
+
+
+@pytest.mark.usefixtures("dense_rows_at_any_batch")
 def test_dense_rows_keep_a_non_finite_operand_row_to_the_rows_that_read_it(nb, oracle):
     import torch
     lay, batch = mixed_rows(900, 1300, 150, 0.5, 3), 256

@@ -87,7 +87,22 @@ def a_failed_rebind_leaves_nothing_freed_in_use(L):
         assert 3 < k < 99
 
 
-CASES = [a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use]
+def dense_rows_go_apart_by_the_batch_of_the_call(L):
+    """500 dense rows of 1100 entries: the work that pays for their launch is there from 367 columns on, whatever the layer is bound for."""
+    for max_batch in (367, 1024, 4096):
+        L.counts(0, n_blocks=600, n_dense=500, dense_nnz=550000, longest_row=1100)
+        L.counts(1, n_blocks=600, longest_row=2000)
+        assert L.create(16384, 2048, 3700000, max_batch) == 0
+        for batch in (128, 366, 367, max_batch):
+            L.launched()
+            assert L.forward(batch) == 0
+            assert any("dense_rows_kernel" in k for k in L.launched()) == (batch >= 367), (max_batch, batch)
+            assert L.backward(batch, dx=False) == 0
+            assert any("sampled_update_kernel" in k for k in L.launched()) == (batch >= 367), (max_batch, batch)
+        L.destroy()
+
+
+CASES = [a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
