@@ -158,15 +158,29 @@ int nerva_plan_staged_host(int32_t rows, int32_t cols, const int32_t *indptr_hos
  * for the output layer (Section 5.1). `bias` may be NULL (no bias).  max_batch bounds the
  * batch of later calls on this layer (a later call with a larger batch returns
  * NERVA_ERR_SHAPE) and is the batch the static tables are laid out for: the scratch rows of
- * huge-row work-groups, the row ranges of the staged products (nerva_plan_staged_host; a much
- * smaller batch falls back to the other kernels), and, where the SDDMM would run in column
- * tiles at that batch, a buffer of per-tile partial products: tiles x (nnz + rows) floats, at
- * most 4 GiB (beyond that the SDDMM stays untiled).  Device memory owned by the layer besides
- * that buffer: 16 bytes per stored entry (mirror and position maps) and the partition tables (a
- * 16-byte record per wave of each partition; with a staged plan 4 bytes per row and block of 512
- * columns, for the matrix and for its mirror; room for any pattern of the same size) -- twice that
- * once the layer has been rebound (see sparse_linear_rebind) -- and the scratch of the set-up
- * (12 bytes per stored entry, 24 per row and column).  */
+ * huge-row work-groups and the row ranges of the staged products (nerva_plan_staged_host; a much
+ * smaller batch falls back to the other kernels).
+ * Device memory owned by the layer (buffers that depend on the pattern with an eighth to spare):
+ *   - 16 bytes per stored entry (mirror and position maps) and the partition tables: a 16-byte
+ *     record per wave of each partition and per row and column; with a staged plan 4 bytes per row
+ *     and block of 512 columns, for the matrix and for its mirror; room for any pattern of the same size;
+ *   - from 15 % density on a pattern table, 8 bytes per row and 32 columns; where a matrix has
+ *     rows of an eighth of its columns or more that matrix instructions serve, such a table of
+ *     theirs, the sliced results of their product (at most 1 GiB), and a second staged plan
+ *     for narrower batches where one could be taken;
+ *   - all of this a second time once the layer has been rebound (see sparse_linear_rebind);
+ *   - the scratch of the set-up, 12 bytes per stored entry and 24 per row and column;
+ *   - scratch rows and tickets of the huge rows, round_up(max_batch, 64) floats per work-group of theirs;
+ *   - per-tile partial products of the SDDMM and of the call for both gradients, tiles x (nnz +
+ *     rows) floats, at most 4 GiB, where any batch up to max_batch takes more than one tile (of 128
+ *     columns as a rule, of 64 or 32 where the operand is large or the products are staged);
+ *   - for a ReLU layer of at least 4 entries per row, dZ of sparse_linear_backward: rows x
+ *     round_up(max_batch, 32) floats, at most 1 GiB;
+ *   - for a matrix of at most 16 rows that stores every entry, slice results of its product:
+ *     cols / 128 x rows x round_up(max_batch, 64) floats;
+ *   - on the dense route the copy that sparse_linear_enable_dense describes.
+ * Pattern tables, partial products, dZ, the dense rows' and slice results and the second staged
+ * plan only make calls faster: where there is no room for one the layer is created without it.  */
 int sparse_linear_create(nerva_layer **out, int32_t rows, int32_t cols, int32_t nnz,
                          const int32_t *indptr, const int32_t *indices,
                          float *values, float *bias, int32_t activation, int32_t max_batch,

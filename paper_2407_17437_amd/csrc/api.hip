@@ -131,14 +131,16 @@ struct nerva_layer {
     // owned: tickets of the huge rows (SpmmArgs::tickets), 0 but while a product runs
     int32_t *tickets = nullptr;
     size_t ticket_ints = 0;
-    // owned: per-tile partial products of the column-tiled SDDMM (only for layers whose input
-    // at max_batch columns does not fit an L2)
+    // owned: per-tile partial products of the SDDMM and of the backward pass on one gather stream, as many tiles as
+    // they take at any batch up to max_batch; fewer or none where there was no room for them
     float *partial = nullptr;
     size_t partial_floats = 0;
     int64_t partial_stride = 0, partial_db_at = 0;
     int32_t partial_tiles = 0;
-    // owned, only for a ReLU layer: dZ of a stand-alone backward pass, (rows, dz_ld); nullptr: too large to be worth it
+    // owned, only for a ReLU layer with entries enough: dZ of a stand-alone backward pass, (rows, dz_ld); nullptr: too large to be
+    // worth it, or no room
     float *dz = nullptr;
+    size_t dz_floats = 0;
     int64_t dz_ld = 0;
     // owned, only on the dense route (sparse_linear_enable_dense, or chosen when the pattern was bound): a
     // zero-filled dense copy of W (rows x dense_ld, dense_ld = cols rounded up to kDenseLdAlign)
@@ -147,7 +149,8 @@ struct nerva_layer {
     int64_t dense_ld = 0;
     // owned, only for a matrix that stores every entry and has at most kFullMaxRows rows
     bool full = false;               // the bound pattern is such a matrix
-    float *full_scratch = nullptr;   // slice partials of the streaming product, (slices * rows, full_scratch_ld); kept once allocated
+    float *full_scratch = nullptr;   // slice partials of the streaming product, (slices * rows, full_scratch_ld); kept once allocated, nullptr: no room
+    size_t full_scratch_floats = 0;
     int64_t full_scratch_ld = 0;
     // values_t lags behind values[]: a training step updated this layer as the first layer of an MLP,
     // whose mirror no product reads, and left the mirror's values alone.  Whoever reads values_t next
@@ -605,13 +608,14 @@ void free_layer_buffers(nerva_layer *l)
 }
 
 // Room for `need` elements of 4 bytes in *ptr, whose capacity is *have: kept if large enough, else
-// replaced by a larger allocation (the old contents are not kept; the new ones are 0 if `zeroed`).  On failure nothing changes.
+// replaced by a larger allocation (the old contents are not kept; the new ones are 0 if `zeroed`; an eighth more than asked for if
+// `spare`, for the patterns to come).  On failure nothing changes.
 template <typename T>
-hipError_t reserve(T **ptr, size_t *have, size_t need, bool zeroed = false, hipStream_t s = nullptr)
+hipError_t reserve(T **ptr, size_t *have, size_t need, bool zeroed = false, hipStream_t s = nullptr, bool spare = true)
 {
     if (need <= *have && *ptr) return hipSuccess;
     if (need == 0) need = 1;
-    const size_t want = need + need / 8;
+    const size_t want = need + (spare ? need / 8 : 0);
     void *fresh = nullptr;
     hipError_t e = hipMalloc(&fresh, want * 4);
     if (e != hipSuccess) return e;
@@ -627,6 +631,15 @@ hipError_t reserve(T **ptr, size_t *have, size_t need, bool zeroed = false, hipS
     *ptr = static_cast<T *>(fresh);
     *have = want;
     return hipSuccess;
+}
+
+// The same for a buffer that the layer can do without: whether there was room for it.
+template <typename T>
+bool reserve_optional(T **ptr, size_t *have, size_t need, bool spare = true)
+{
+    if (reserve(ptr, have, need, false, nullptr, spare) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
 }
 
 // Marks the start of one launch with an event while profiling is on; costs one branch otherwise.
@@ -763,10 +776,8 @@ static hipError_t build_dense_copies(nerva_layer *l, hipStream_t s)
     l->dense_ld = round_up(l->cols, kDenseLdAlign);
     const size_t bytes = static_cast<size_t>(l->rows) * l->dense_ld * 4;
     hipError_t e = hipMalloc(&l->dense, bytes);
-    if (e == hipSuccess && !l->cur.has_table) {
-        e = reserve(&l->cur.table, &l->cur.table_ints, static_cast<size_t>(l->rows) * table_words(l) * 2);
-        if (e == hipSuccess)
-            e = launch_pattern_table(l->indptr, l->indices, nullptr, l->rows, table_words(l), reinterpret_cast<uint2 *>(l->cur.table), nullptr, s);
+    if (e == hipSuccess && !l->cur.has_table && reserve_optional(&l->cur.table, &l->cur.table_ints, static_cast<size_t>(l->rows) * table_words(l) * 2)) {
+        e = launch_pattern_table(l->indptr, l->indices, nullptr, l->rows, table_words(l), reinterpret_cast<uint2 *>(l->cur.table), nullptr, s);
         if (e == hipSuccess) l->cur.has_table = true;
     }
     if (e == hipSuccess) e = hipMemsetAsync(l->dense, 0, bytes, s);
@@ -836,7 +847,7 @@ static int csr_status_error(const int32_t *st)
 // launches (structure.hip); the host waits once, for the check's verdict and the partitions' sizes.  On failure
 // (NERVA_ERR_CSR, NERVA_ERR_HIP) nothing that a product reads has been changed.  On success the caller swaps
 // l->spare into l->cur and adopts `plan`, `plan_t`.
-constexpr size_t kPartialMaxBytes = 4ull << 30;
+constexpr size_t kPartialMaxBytes = 4ull << 30, kDzMaxBytes = 1ull << 30;
 struct BuiltPattern {
     RowBlocks plan{}, plan_t{};
     int64_t partial_stride = 0, partial_db_at = 0;
@@ -901,9 +912,9 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
                              reinterpret_cast<PlanCounts *>(w + 6 * r + static_cast<size_t>(side.range_bound) + 1)};
     }
     HIP_TRY(launch_bind(m, p, s));
-    B.has_table = l->dense_on || static_cast<double>(nnz) >= static_cast<double>(kTableFromDensity) * rows * cols;
+    B.has_table = (l->dense_on || static_cast<double>(nnz) >= static_cast<double>(kTableFromDensity) * rows * cols) &&
+                  reserve_optional(&B.table, &B.table_ints, static_cast<size_t>(rows) * table_words(l) * 2);
     if (B.has_table) {
-        HIP_TRY(reserve(&B.table, &B.table_ints, static_cast<size_t>(rows) * table_words(l) * 2));
         HIP_TRY(launch_pattern_table(indptr, indices, nullptr, rows, table_words(l), reinterpret_cast<uint2 *>(B.table), m.status, s));
     }
     HIP_TRY(hipStreamSynchronize(s));
@@ -912,14 +923,16 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     out->plan = plan_view(p.side[0].tables, R.plan[0], cols, nnz, R.plan[1].hot_nnz, mode);
     bool more_work = false;   // launches after the wait
     B.split = DenseSplit{};
-    if (R.plan[0].n_dense > 0) {
+    const int32_t n_dense = R.plan[0].n_dense;
+    if (n_dense > 0 && !reserve_optional(&B.row_table, &B.row_table_ints, static_cast<size_t>(n_dense) * table_words(l) * 2)) {
+        out->plan.staged_rows = nullptr;   // (it covers the other rows only: the dense ones stay with them, unstaged)
+    } else if (n_dense > 0) {
         const PlanTables &t = p.side[0].tables;
         DenseRows &D = B.split.rows;
-        D.list = t.dense_rows; D.n = R.plan[0].n_dense; D.words = table_words(l);
-        HIP_TRY(reserve(&B.row_table, &B.row_table_ints, static_cast<size_t>(D.n) * D.words * 2));
+        D.list = t.dense_rows; D.n = n_dense; D.words = table_words(l);
         D.table = reinterpret_cast<const uint2 *>(B.row_table);
         D.partial_floats = dense_rows_partial(D.n, cols, max_batch);
-        if (D.partial_floats > 0) HIP_TRY(reserve(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(D.partial_floats)));
+        if (D.partial_floats > 0 && !reserve_optional(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(D.partial_floats))) D.partial_floats = 0;
         D.partial = B.row_partial;
         B.split.flag = t.dense_flag;
         B.split.others = out->plan;
@@ -930,8 +943,8 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         // all rows where the widest of them that fills its tiles (staged_pays) has work-groups enough for it.
         out->plan.staged_rows = nullptr;
         const int32_t tiles = static_cast<int32_t>(std::min<int64_t>(5ll * (B.split.from_batch - 1), 5ll * max_batch) / (4 * kStageCols));
-        if (B.split.from_batch > kStageMinBatch && room.ranges > 0 && tiles * staged_ranges_aim(rows, max_batch) >= kStageTargetGroups / 2) {
-            HIP_TRY(reserve(&B.whole_staged, &B.whole_staged_ints, room.staged_ints()));
+        if (B.split.from_batch > kStageMinBatch && room.ranges > 0 && tiles * staged_ranges_aim(rows, max_batch) >= kStageTargetGroups / 2 &&
+            reserve_optional(&B.whole_staged, &B.whole_staged_ints, room.staged_ints())) {
             PlanArgs whole = p;
             whole.side[0].dense_len = INT32_MAX;
             room.staged_at(whole.side[0].tables, B.whole_staged);
@@ -947,23 +960,21 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     // scratch buffers of the products (they hold nothing between calls, the tickets zeros: grown in place, so that the old
     // pattern's products find them whatever fails from here on)
     {
-        // room for the column-tiled SDDMM at max_batch columns, if that batch would be tiled
-        const int w = tile_columns(cols, max_batch, nnz, rows, out->plan.staged_longest_row, out->plan.hot_share, false, true);
-        int32_t tiles = w > 0 ? (max_batch + w - 1) / w : 0;
+        // per-tile partial products: room for the tiles of every batch, or what there is room for (kPartialMaxBytes: beyond
+        // that they are not worth it), below which the kernels without them stay
+        int32_t tiles = partial_tiles_wanted(out->plan, out->plan_t, rows, cols, nnz, max_batch);
         if ((out->plan.staged_rows || B.split.others.staged_rows) && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
-        // ... and for the backward pass on one gather stream (products in mirror order, a slice per column tile)
-        const int32_t tiles_fused = std::max(tiles, (max_batch + 63) / 64);
-        if (static_cast<size_t>(tiles_fused) * (round_up(nnz, 64) + round_up(rows, 64)) * 4 <= kPartialMaxBytes) tiles = tiles_fused;
-        out->partial_tiles = 0;
-        if (tiles > 0) {
-            out->partial_db_at = round_up(nnz, 64);
-            out->partial_stride = out->partial_db_at + round_up(rows, 64);
-            const size_t floats = static_cast<size_t>(tiles) * out->partial_stride;
-            if (floats * 4 <= kPartialMaxBytes) {  // (beyond that it is too large to be worth it: the untiled kernel stays)
-                HIP_TRY(reserve(&l->partial, &l->partial_floats, floats));
-                out->partial_tiles = tiles;
-            }
-        }
+        out->partial_db_at = round_up(nnz, 64);
+        out->partial_stride = out->partial_db_at + round_up(rows, 64);
+        const size_t slice = static_cast<size_t>(out->partial_stride);
+        tiles = static_cast<int32_t>(std::min<size_t>(tiles, kPartialMaxBytes / 4 / slice));
+        out->partial_tiles = tiles;
+        if (tiles > 0 && !reserve_optional(&l->partial, &l->partial_floats, tiles * slice))
+            out->partial_tiles = static_cast<int32_t>(std::min<size_t>(tiles, l->partial_floats / slice));
+        l->dz_ld = round_up(max_batch, 32);
+        const size_t dz = static_cast<size_t>(rows) * l->dz_ld;
+        if (l->activation == NERVA_ACT_RELU && max_batch > 4 && nnz >= 4 * static_cast<int64_t>(rows) && dz * 4 <= kDzMaxBytes)
+            (void)reserve_optional(&l->dz, &l->dz_floats, dz, false);
         const int64_t slots = out->plan.n_huge_blocks > out->plan_t.n_huge_blocks ? out->plan.n_huge_blocks : out->plan_t.n_huge_blocks;
         out->scratch_ld = round_up(max_batch, 64);
         if (slots > 0) {
@@ -973,9 +984,9 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         }
         out->full = rows <= kFullMaxRows && static_cast<int64_t>(nnz) == static_cast<int64_t>(rows) * cols;
         out->full_scratch_ld = round_up(max_batch, 64);
-        if (out->full && !l->full_scratch) {
+        if (out->full) {
             const int64_t slices = (cols + kFullSlice - 1) / kFullSlice;
-            HIP_TRY(hipMalloc(&l->full_scratch, static_cast<size_t>(slices) * rows * out->full_scratch_ld * 4));
+            (void)reserve_optional(&l->full_scratch, &l->full_scratch_floats, static_cast<size_t>(slices) * rows * out->full_scratch_ld, false);
         }
     }
     if (more_work) HIP_TRY(hipStreamSynchronize(s));   // (a product on another stream may follow)
@@ -1015,13 +1026,7 @@ int sparse_linear_create(nerva_layer **out, int32_t rows, int32_t cols, int32_t 
     if (!l) return fail(NERVA_ERR_ARGUMENT, "out of host memory");
     l->rows = rows; l->cols = cols; l->activation = activation; l->max_batch = max_batch; l->bias = bias;
     BuiltPattern bp;
-    int rc = build_structures(l, nnz, indptr, indices, values, &bp, as_stream(stream));
-    l->dz_ld = round_up(max_batch, 32);
-    const size_t dz_bytes = static_cast<size_t>(rows) * l->dz_ld * 4;
-    if (rc == NERVA_OK && activation == NERVA_ACT_RELU && dz_bytes <= (1ull << 30)) {
-        const hipError_t e = hipMalloc(&l->dz, dz_bytes);
-        if (e != hipSuccess) rc = hip_fail(e, "gradient scratch");
-    }
+    const int rc = build_structures(l, nnz, indptr, indices, values, &bp, as_stream(stream));
     if (rc != NERVA_OK) {
         free_layer_buffers(l);
         delete l;

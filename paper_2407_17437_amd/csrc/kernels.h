@@ -220,6 +220,8 @@ struct SddmmArgs {
 // SDDMM partial buffer when a layer is created.
 int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, int32_t longest_row, float hot_share, bool masked, bool for_sddmm = false);
 hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s);
+// Slices of partial products (SddmmArgs::partial) that the column-tiled SDDMM and the fused backward pass take at any batch up to max_batch
+int32_t partial_tiles_wanted(const RowBlocks &plan, const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch);
 
 // Transposed product and SDDMM of one layer on one gather stream (backward_fused_kernel).
 struct BackwardArgs {

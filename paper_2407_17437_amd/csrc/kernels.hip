@@ -2803,19 +2803,42 @@ bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
     if (t.batch != g.batch || t.batch < 4 || t.X != g.dZ || t.ldx != g.lddz || t.XM != g.ZM || t.ldxm != g.ldzm) return false;
     if (t.YM && (t.YM != g.X || t.ldym != g.ldx)) return false;
     if (t.rows != g.x_rows || t.x_rows != g.rows || t.nnz != g.nnz || t.nnz <= 0) return false;
-    if (g.skip_products || g.dense || g.loss_cols || !g.partial || !g.perm) return false;
+    if (g.skip_products || g.dense || g.loss_cols || !g.perm) return false;
     if (!spmm_offsets_ok(t) || !sddmm_offsets_ok(g) || (!alone && spmm_staged_ok(t))) return false;
     const int tg = backward_tile_group(t);
     if (!alone && static_cast<int64_t>(t.nnz) * t.batch < kFusedMinWork) return false;
     const int n_tiles = backward_tiles(t, tg);
     // (a masked dZ only where gathering the mask as well costs less than the launch that would form dZ)
     if (t.XM && (!alone || static_cast<int64_t>(t.nnz) * t.batch > kBackwardSmallWork)) return false;
-    if (n_tiles > g.partial_tiles || g.partial_stride < t.nnz) return false;
+    const bool one = n_tiles == 1 || (alone && backward_looped(t));   // (then the products need no second pass)
+    if (!one && (!g.partial || n_tiles > g.partial_tiles || g.partial_stride < t.nnz)) return false;
     // (no row so long that its lane groups outlast the rest of the launch; a pass over 128 entries is short enough on any matrix)
     const int64_t longest = t.blocks.staged_longest_row >> backward_split(t, tg, n_tiles);
     if (longest > kPackMaxLen && longest * 4096 > static_cast<int64_t>(t.nnz) * ((t.batch + 63) / 64)) return false;
     const int64_t per_set = (kWave / tg) >> backward_split(t, tg, n_tiles), sets = (static_cast<int64_t>(t.rows) + per_set - 1) / per_set;
     return ((n_tiles + 7) / 8) * 8 * ((sets + kBwdWaves - 1) / kBwdWaves) + 2048 <= kMaxGridIds;
+}
+
+int32_t partial_tiles_wanted(const RowBlocks &plan, const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch)
+{
+    SpmmArgs t{};
+    t.blocks = plan_t; t.rows = cols; t.x_rows = rows; t.nnz = nnz;
+    if (nnz <= 0) return 0;
+    // The rules are asked at either end of every 64 columns, and tiles counted to the far end: none is narrower than 32 columns.
+    constexpr int64_t kMostAsked = 1 << 18;
+    if (max_batch > kMostAsked) return max_batch / 32 + 1;
+    int64_t most = 0;
+    for (int64_t lo = 0; lo < max_batch; lo += 64) {
+        const int64_t hi = lo + 64 < max_batch ? lo + 64 : max_batch;
+        for (const int64_t batch : {lo + 1, hi}) {
+            t.batch = static_cast<int32_t>(batch);
+            const int w = tile_columns(cols, t.batch, nnz, rows, plan.staged_longest_row, plan.hot_share, false, true);
+            if (w > 0) most = most > (hi + w - 1) / w ? most : (hi + w - 1) / w;
+            const int64_t columns = 4ll * backward_tile_group(t), n = (hi + columns - 1) / columns;
+            if (n > 1 && !(backward_looped(t) && hi <= 512)) most = most > n ? most : n;
+        }
+    }
+    return static_cast<int32_t>(most);
 }
 
 // The same sharing for a full matrix of few rows (a saturated output layer): its SDDMM streams the layer's

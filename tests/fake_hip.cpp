@@ -25,14 +25,14 @@ hipError_t last = hipSuccess;
 
 bool fails(hipError_t e)
 {
-    if (calls_until_failure < 0 || calls_until_failure-- > 0) return false;
+    if (calls_until_failure < 0 || calls_until_failure-- > 0) return false;   // (-1 once it has)
     last = e;
     return true;
 }
 hipError_t allocate(void **p, size_t n)
 {
     *p = malloc(n);
-    memset(*p, 0xCB, n);
+    memset(*p, 0xCB, n < (1 << 20) ? n : 1 << 20);
     live[reinterpret_cast<uintptr_t>(*p)] = n;
     live_bytes += n;
     return hipSuccess;
@@ -67,6 +67,7 @@ void check(const void *args, size_t bytes)
 extern "C" {
 // ---- for the test
 void fake_fail_after(long calls) { calls_until_failure = calls; }
+long fake_fail_after_left() { return calls_until_failure; }
 int fake_bad_pointers() { return bad_pointers; }
 int fake_dirty_tickets() { return dirty_tickets; }
 size_t fake_live_bytes() { return live_bytes; }

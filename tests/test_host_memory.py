@@ -19,6 +19,7 @@ class Library:
         self.hip.fake_launched.restype = ctypes.c_char_p
         self.hip.fake_live_bytes.restype = ctypes.c_size_t
         self.hip.fake_fail_after.argtypes = [ctypes.c_long]
+        self.hip.fake_fail_after_left.restype = ctypes.c_long
         self.lib = ctypes.CDLL(LIB)
         self.lib.nerva_last_error.restype = ctypes.c_char_p
         self.host = [(ctypes.c_float * (1 << 20))() for _ in range(4)]   # (never read: no kernel runs)
@@ -102,7 +103,44 @@ def dense_rows_go_apart_by_the_batch_of_the_call(L):
         L.destroy()
 
 
-CASES = [a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def a_layer_is_created_without_what_it_can_do_without(L):
+    """Dense rows with sliced results, a staged plan for the batches below theirs, partial products, dZ of a ReLU layer: each of them
+    fails once.  (The calls fail one after another; those whose failure the create survives are these.)"""
+    survived = 0
+    for k in range(100):
+        L.counts(0, n_blocks=600, n_dense=500, dense_nnz=550000, longest_row=1100, staged_ranges=48, staged_rows=16000, staged_nnz=3000000)
+        L.counts(1, n_blocks=600, longest_row=2000)
+        L.hip.fake_fail_after(k)
+        rc = L.create(16384, 2048, 3700000, 1024, relu=True)
+        failed = L.hip.fake_fail_after_left() < 0
+        L.hip.fake_fail_after(-1)
+        if rc == 0:
+            for batch in (1, 100, 128, 320, 700, 1024):
+                assert L.forward(batch) == 0 and L.backward(batch) == 0 and L.backward(batch, dx=False) == 0, L.lib.nerva_last_error()
+            L.destroy()
+            if not failed:
+                break
+            survived += 1
+        assert rc in (0, -5) and L.hip.fake_bad_pointers() == 0
+        assert L.hip.fake_live_bytes() == 0, "a failed create, or a destroyed layer, holds memory"
+    assert survived == 5
+
+
+def a_single_tile_needs_no_partial_products(L):
+    held = []
+    for max_batch in (64, 100):
+        L.counts(0, n_blocks=600, longest_row=400)
+        L.counts(1, n_blocks=600, longest_row=150)
+        assert L.create(1024, 3072, 315000, max_batch, relu=True) == 0
+        held.append(L.hip.fake_live_bytes())
+        L.launched()
+        assert L.backward(max_batch) == 0
+        assert any("backward_fused_kernel" in k for k in L.launched())
+        L.destroy()
+    assert held[1] - held[0] == 1024 * (128 - 64) * 4, held   # (dZ, whose rows are 128 and 64 columns apart)
+
+
+CASES = [a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
