@@ -1,4 +1,5 @@
-"""ctypes binding of libnerva_sparse.so: argument marshalling only.
+"""Binding of libnerva_sparse.so: argument marshalling only, in native code for the calls of a loop (csrc/fastcall.cpp),
+through ctypes for the others.
 
 Every function below has the name and the argument order of the C entry point it calls
 (see include/nerva_sparse.h); tensors are torch CUDA tensors used for their device
@@ -93,12 +94,6 @@ def _load() -> ctypes.CDLL:
 
 lib = _load()
 
-# the calls that loops are made of, without ctypes (csrc/fastcall.cpp): they go to the entry points of `lib`
-from . import _fastcall  # noqa: E402  (built beside the library)
-
-_fastcall.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
-    "sparse_linear_forward", "sparse_linear_backward", "sgd_update_values", "sgd_update_values_nesterov", "mlp_train_step", "mlp_forward")))
-
 
 def last_error() -> str:
     return lib.nerva_last_error().decode()
@@ -125,6 +120,16 @@ def _stream(stream) -> Optional[int]:
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream or None
     return stream or None
+
+
+# the calls that loops are made of, without ctypes (csrc/fastcall.cpp): they go to the entry points of `lib`
+try:
+    from . import _fastcall  # built beside the library where torch's headers are
+    _fastcall.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+        "sparse_linear_forward", "sparse_linear_backward", "sgd_update_values", "sgd_update_values_nesterov", "mlp_train_step", "mlp_forward")))
+except ImportError:
+    from .calls import Calls
+    _fastcall = Calls(lib, _stream)
 
 
 def _ld(t: torch.Tensor) -> int:

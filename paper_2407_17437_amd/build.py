@@ -33,12 +33,11 @@ def build_library(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed")
     if verbose and err.strip():
         print(err)
-    build_fastcall(verbose)
     return LIB
 
 
 def build_fastcall(verbose: bool = False) -> str:
-    """Host code only: Python.h and torch's headers, no kernels."""
+    """Host code only: Python.h and torch's headers, no kernels.  (Without it the package makes these calls through ctypes.)"""
     from torch.utils import cpp_extension
     includes = [*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]
     libs = cpp_extension.library_paths()[0]
@@ -56,3 +55,4 @@ def build_fastcall(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_fastcall(verbose=True))

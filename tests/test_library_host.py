@@ -37,6 +37,57 @@ def test_library_is_newer_than_its_sources(nb):
     assert not stale, f"rebuild the library: {stale} changed after it was built"
 
 
+def test_package_works_without_the_compiled_call_layer(nb):
+    """Importing it blocked, and every call that it makes against the same call through ctypes, argument by argument."""
+    import subprocess, sys
+    code = ("import sys; sys.modules['paper_2407_17437_amd._fastcall'] = None\n"
+            "from paper_2407_17437_amd import binding as nb\n"
+            "from paper_2407_17437_amd.calls import Calls\n"
+            "assert isinstance(nb._fastcall, Calls) and 'gfx950' in nb.build_info()\n")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
+
+    import torch
+    from paper_2407_17437_amd import _fastcall
+    from paper_2407_17437_amd.calls import Calls
+    names = ("sparse_linear_forward", "sparse_linear_backward", "sgd_update_values", "sgd_update_values_nesterov", "mlp_train_step", "mlp_forward")
+    seen = []
+
+    class Recorder:
+        pass
+
+    recorder = Recorder()
+    for name in names:
+        fn = getattr(nb.lib, name)
+        setattr(recorder, name, ctypes.CFUNCTYPE(fn.restype, *fn.argtypes)(lambda *a, name=name: seen.append((name,) + a) or len(seen)))
+    M, V = torch.zeros(6, 9)[:, :7], torch.zeros(40)
+    labels = torch.zeros(7, dtype=torch.int32)
+
+    class Stream:
+        cuda_stream = 77
+
+    calls = [("forward", (5, M, M, 7, 3)), ("forward", (5, None, M, 7, Stream())), ("backward", (5, M, None, M, None, V, None, 7, 3)),
+             ("backward", (5, None, M, M, M, None, V, 7, 3)), ("update", (V, V, V, 40, 0.5, 0.25, 0, 3)), ("update", (V, V, V, 40, 0.5, 0.25, 1, 3)),
+             ("train_step", (6, M, None, labels, 7, 0.5, 0.25, V, V, 3)), ("train_step", (6, 1234, 8, 4321, 7, 0.5, 0.25, V, None, 3)),
+             ("mlp_forward", (6, M, None, 7, V, 3)), ("mlp_forward", (6, M, 11, 7, V, 3))]
+    through_ctypes = Calls(recorder, lambda s: getattr(s, "cuda_stream", s))
+    _fastcall.bind(*(ctypes.cast(getattr(recorder, name), ctypes.c_void_p).value for name in names))
+    try:
+        for name, args in calls:
+            seen.clear()
+            assert getattr(_fastcall, name)(*args) == 1 and getattr(through_ctypes, name)(*args) == 2
+            assert seen[0] == seen[1], (name, seen)
+        for layer in (_fastcall, through_ctypes):
+            for bad in (M.T, M.double(), V):
+                with pytest.raises(AssertionError):
+                    layer.forward(5, bad, M, 7, 3)
+            with pytest.raises(TypeError):
+                layer.forward(5, 12, M, 7, 3)
+            w = layer.view(V[4:], 3, 4, 5, 2)
+            assert w.shape == (3, 4) and w.stride() == (5, 1) and w.data_ptr() == V.data_ptr() + 6 * 4
+    finally:
+        _fastcall.bind(*(ctypes.cast(getattr(nb.lib, name), ctypes.c_void_p).value for name in names))
+
+
 def test_validate_csr_accepts_generated_patterns(nb):
     for rows, cols, nnz in [(5, 7, 0), (5, 7, 35), (64, 33, 500)]:
         indptr, indices = wl.uniform_pattern(rows, cols, nnz, seed=1)
