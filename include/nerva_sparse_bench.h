@@ -1,5 +1,5 @@
 /* nerva_sparse_bench.h -- measurement aids of the library, kept apart from the product's C ABI
- * (nerva_sparse.h): a partition mode for A/B timings, per-launch event timing of a training
+ * (nerva_sparse.h): a partition mode for A/B timings, the partition tables for inspection, per-launch event timing of a training
  * step, and a plain copy kernel of known size that memory-traffic counters are scaled by.
  * Benchmarks and tests use them; a training program needs none of them.
  */
@@ -24,6 +24,14 @@ extern "C" {
  * for matrix instructions at the layer's max_batch, these serve them at every batch from 128 columns on. */
 enum { NERVA_PARTITION_BALANCED = 0, NERVA_PARTITION_ROW_SPLIT = 1, NERVA_PARTITION_PREFER_STAGED = 2, NERVA_PARTITION_PREFER_DENSE_ROWS = 3 };
 int nerva_set_partition_mode(int32_t mode);
+
+/* Inspection aid: the partition tables that binding a pattern has left on the device, entry for entry those that the
+ * nerva_plan_*_host calls compute for the same row pointers (but for waves of huge rows, whose last word also holds the
+ * row's index in the table of huge rows from bit 10 on).  side 0: the matrix, 1: its mirror; table: one of the values below.
+ * *table_out receives the device address (valid until the next rebind; NULL if empty), *ints_out its length in int32. */
+enum { NERVA_TABLE_WAVES = 0, NERVA_TABLE_HUGE_ROWS = 1, NERVA_TABLE_SHORT_ROWS = 2, NERVA_TABLE_LONG_WAVES = 3, NERVA_TABLE_STAGED_ROWS = 4,
+       NERVA_TABLE_STAGED_ENDS = 5 };
+int sparse_linear_partition(const nerva_layer *layer, int32_t side, int32_t table, const int32_t **table_out, int64_t *ints_out);
 
 /* Measurement aid: the density from which sparse_linear_create / sparse_linear_rebind put a layer on the
  * dense route by themselves (process-wide; layers already bound keep their route).  Default 0.4; a value above

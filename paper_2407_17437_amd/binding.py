@@ -26,6 +26,7 @@ NERVA_STAGE_ROWS, NERVA_STAGE_COLS, NERVA_STAGE_MIN_BATCH, NERVA_STAGE_RANGE_ROW
 NERVA_PARTITION_BALANCED, NERVA_PARTITION_ROW_SPLIT, NERVA_PARTITION_PREFER_STAGED, NERVA_PARTITION_PREFER_DENSE_ROWS = 0, 1, 2, 3
 NERVA_MLP_DEFAULT, NERVA_MLP_UNFUSED, NERVA_MLP_NESTEROV, NERVA_MLP_SEPARATE_HEAD = 0, 1, 2, 4
 NERVA_WAVES_PER_BLOCK = 16
+(NERVA_TABLE_WAVES, NERVA_TABLE_HUGE_ROWS, NERVA_TABLE_SHORT_ROWS, NERVA_TABLE_LONG_WAVES, NERVA_TABLE_STAGED_ROWS, NERVA_TABLE_STAGED_ENDS) = range(6)
 NERVA_STATIC_WORKSPACE_BYTES = 32 << 20
 NERVA_HUGE_FLAG = 0x40000000
 
@@ -35,7 +36,7 @@ EXPORTS = [
     "sparse_linear_forward", "sparse_linear_backward", "sgd_update_values", "sgd_update_values_nesterov",
     "softmax_cross_entropy", "mlp_create", "mlp_destroy", "mlp_rebind_velocity", "mlp_workspace_bytes",
     "mlp_workspace_layout", "mlp_train_step", "mlp_train_step_static", "mlp_forward", "nerva_copy_f32",
-    "mlp_profile_enable", "mlp_profile_read", "mlp_profile_slot_name",
+    "mlp_profile_enable", "mlp_profile_read", "mlp_profile_slot_name", "sparse_linear_partition",
 ]
 
 
@@ -81,6 +82,7 @@ def _load() -> ctypes.CDLL:
         "mlp_train_step_static": (ctypes.c_int, [vp, vp, i32, vp, i32, f32, f32, vp, vp]),
         "mlp_forward": (ctypes.c_int, [vp, vp, i32, i32, vp, sz, vp]),
         "nerva_copy_f32": (ctypes.c_int, [vp, vp, i64, vp]),
+        "sparse_linear_partition": (ctypes.c_int, [vp, i32, i32, vp, vp]),
         "mlp_profile_enable": (ctypes.c_int, [vp, i32]),
         "mlp_profile_read": (ctypes.c_int, [vp, i32, vp, vp, vp]),
         "mlp_profile_slot_name": (ctypes.c_char_p, [vp, i32]),
@@ -233,6 +235,13 @@ def sparse_linear_mirror(layer: int):
     out = [ctypes.c_void_p() for _ in range(4)]
     _check(lib.sparse_linear_mirror(layer, *[ctypes.addressof(o) for o in out]))
     return tuple(o.value for o in out)
+
+
+def sparse_linear_partition(layer: int, side: int, table: int):
+    """(device address or None, length in int32) of one of the NERVA_TABLE_* of a layer (side 1: of its mirror)."""
+    p, n = ctypes.c_void_p(), ctypes.c_int64()
+    _check(lib.sparse_linear_partition(layer, side, table, ctypes.addressof(p), ctypes.addressof(n)))
+    return p.value, n.value
 
 
 def sparse_linear_forward(layer: int, X, Y, batch: int, stream=None) -> None:

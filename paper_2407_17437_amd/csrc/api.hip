@@ -1126,6 +1126,26 @@ int sparse_linear_mirror(const nerva_layer *layer, const int32_t **indptr_t, con
     return NERVA_OK;
 }
 
+int sparse_linear_partition(const nerva_layer *layer, int32_t side, int32_t table, const int32_t **table_out, int64_t *ints_out)
+{
+    if (!layer || !table_out || !ints_out || side < 0 || side > 1) return fail(NERVA_ERR_ARGUMENT, "bad argument");
+    const RowBlocks &b = side ? layer->plan_t : layer->plan;
+    const void *p = nullptr;
+    int64_t n = 0;
+    switch (table) {
+        case NERVA_TABLE_WAVES: p = b.waves; n = 4ll * kWavesPerBlock * b.n_blocks; break;
+        case NERVA_TABLE_HUGE_ROWS: p = b.huge_rows; n = 4ll * b.n_huge_rows; break;
+        case NERVA_TABLE_SHORT_ROWS: p = b.short_rows; n = 4 * round_up(b.n_short, 64); break;
+        case NERVA_TABLE_LONG_WAVES: p = b.long_waves; n = 4ll * kWavesPerBlock * b.n_long_blocks; break;
+        case NERVA_TABLE_STAGED_ROWS: p = b.staged_rows; n = b.staged_rows ? static_cast<int64_t>(b.staged_ranges) * kStageRangeRows : 0; break;
+        case NERVA_TABLE_STAGED_ENDS: p = b.staged_ends; n = b.staged_rows ? static_cast<int64_t>(b.staged_ranges) * kStageRangeRows * (b.staged_cblocks + 1) : 0; break;
+        default: return fail(NERVA_ERR_ARGUMENT, "unknown table %d", table);
+    }
+    *table_out = n > 0 ? static_cast<const int32_t *>(p) : nullptr;
+    *ints_out = n;
+    return NERVA_OK;
+}
+
 int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx, float *Y, int32_t ldy,
                           int32_t batch, void *stream)
 {

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2407_17437_amd import workloads as wl
-from test_gpu_parity import _mirror_check, close
+from test_gpu_parity import _mirror_check, close, raw_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +35,67 @@ def test_mirror_where_the_build_changes_shape(nb, rows, cols, nnz):
         flat = np.unique(np.concatenate([flat, [(1 << 25) - 1, 1 << 25, cols - 1, cols + (1 << 25) - 1]]))   # either side of the border
     indptr = np.concatenate([[0], np.cumsum(np.bincount(flat // cols, minlength=rows))])
     _mirror_check(nb, torch, rows, cols, indptr, (flat % cols).astype(np.int32))
+
+
+def device_tables(nb, torch, layer, side):
+    out = []
+    for table in range(6):
+        p, n = nb.sparse_linear_partition(layer, side, table)
+        out.append(raw_i32(nb, torch, p, n) if n else np.zeros(0, np.int32))
+    return out
+
+
+@pytest.mark.parametrize("rows,cols,max_batch,lens", [
+    (1, 1, 1, lambda r: [1]), (5, 9, 64, lambda r: np.zeros(5)), (300, 77, 16, lambda r: r.integers(0, 78, 300)),
+    (1025, 3072, 100, lambda r: r.integers(250, 360, 1025)),                                        # classes that hand rows up
+    (2047, 900, 256, lambda r: r.integers(0, 129, 2047)), (2048, 900, 256, lambda r: r.integers(0, 129, 2048)),   # no packed rows, all packed
+    (3000, 5000, 128, lambda r: np.where(r.random(3000) < 0.02, r.integers(1000, 5000, 3000), r.integers(0, 200, 3000))),   # huge rows among packed ones
+    (40, 20000, 64, lambda r: r.integers(15000, 20001, 40)),                                        # nothing but huge rows
+    (1200, 1500, 512, lambda r: np.where(r.random(1200) < 0.03, 1500, 220)),                        # all rows staged, some of them split
+    (9000, 4000, 1024, lambda r: np.where(r.random(9000) < 0.1, r.integers(200, 490, 9000), r.integers(0, 40, 9000))),      # the long rows staged
+    (4096, 4096, 1024, lambda r: np.minimum(4096, 2e5 / (1 + np.arange(4096.)))),                   # power law
+], ids=str)
+def test_tables_equal_the_host_planner(nb, rows, cols, max_batch, lens):
+    """Entry for entry, of the matrix and of its mirror, also after a rebind has used the other set of buffers."""
+    import torch
+    rng = np.random.default_rng(rows)
+    n = np.asarray(lens(rng)).astype(np.int64)
+    nb.nerva_set_dense_threshold(2.0)
+    try:
+        for take in (slice(None), slice(None, None, -1)):   # (then the same rows in the other order, by rebinding)
+            indptr, indices = wl.pattern_from_row_nnz(n[take], cols, seed=rows + cols)
+            values = wl.init_values(indptr, 1)
+            if take.step is None:
+                L = nb.SparseLinear(wl.SparseLayerData(rows, cols, indptr, indices, values, np.zeros(rows, np.float32), False), max_batch=max_batch)
+            else:
+                L.rebind(indptr, indices, values)
+            row = np.repeat(np.arange(rows), np.diff(indptr))
+            order = np.lexsort((row, indices))
+            indptr_t = np.concatenate([[0], np.cumsum(np.bincount(indices, minlength=cols))]).astype(np.int32)
+            for side, (m, k, ip, ix) in enumerate(((rows, cols, indptr, indices), (cols, rows, indptr_t, row[order].astype(np.int32)))):
+                waves, huge, short, long_waves, staged_rows, staged_ends = device_tables(nb, torch, L.handle, side)
+                _, _, h_huge, _, h_waves = nb.nerva_plan_rows_host(m, ip)
+                h_short, n_short, h_long, _ = nb.nerva_plan_short_rows_host(m, ip)
+                assert np.array_equal(huge, h_huge.ravel()), "huge rows"
+                assert np.array_equal(short, h_short.ravel()), "short rows"
+                for got, ref in ((waves, h_waves), (long_waves, h_long)):
+                    got, ref = got.reshape(-1, 4), ref.reshape(-1, 4)
+                    assert got.shape == ref.shape and np.array_equal(got[:, :3], ref[:, :3]) and np.array_equal(got[:, 3] & 1023, ref[:, 3])
+                    is_huge = (got[:, 3] >> 9 & 1).astype(bool) & (got[:, 0] >= 0)
+                    assert np.array_equal(h_huge[got[is_huge, 3] >> 10, 0], got[is_huge, 0])
+                # dense rows leave the staged plan to the others, and only a batch below theirs has one of all rows
+                lengths = np.diff(ip)
+                partial = 0 < n_short < m and int(lengths.max()) * m > 4 * int(ip[-1])
+                plans = [nb.nerva_plan_staged_host(m, k, ip, ix, max_batch, e) for e in ((nb.NERVA_PACK_MAX_LEN + 1, 0) if partial else (0,))]
+                ref_rows, ref_ends = next(((r, e) for r, e in plans if len(r)), plans[-1])
+                dense = side == 0 and cols >= 1024 and max_batch >= 128 and (lengths >= max(cols // 8, 129)).sum() >= 17
+                assert len(staged_rows) or side or (rows, cols) not in ((1200, 1500), (9000, 4000))
+                if len(staged_rows) or not dense:
+                    assert np.array_equal(staged_rows, ref_rows.ravel()), "staged rows"
+                    assert np.array_equal(staged_ends, ref_ends.ravel()), "staged ends"
+    finally:
+        nb.nerva_set_dense_threshold(0.4)
+    L.close()
 
 
 @pytest.mark.parametrize("rows,cols,lens", [

@@ -252,6 +252,39 @@ def test_training_step_with_both_gradients_in_one_pass(nb, batch, hidden):
         assert torch.allclose(a, b, rtol=1e-3, atol=2e-6 * max(1.0, float(b.abs().max())))
 
 
+@pytest.mark.parametrize("flags", ["plain", "nesterov"])
+@pytest.mark.parametrize("batch,max_batch", [(640, 640), (577, 640)])
+def test_training_step_with_dense_rows_above_the_first_layer(nb, batch, max_batch, flags):
+    """Their gradients, the momentum step and the new weights' places in the mirror come from the matrix units' launch, the other
+    rows' from theirs: against the same step by separate products."""
+    import types
+    import torch
+    upper = mixed_rows(3000, 1500, 420, 0.6, 11, relu=True)
+    first, last = layer_case(1500, 200, 0.1, 12, relu=True), layer_case(10, 3000, 0.2, 13)
+    data = types.SimpleNamespace(layers=[first, upper, last])
+    X, labels = nb.dense(200, batch), torch.randint(10, (batch,), device="cuda", dtype=torch.int32)
+    X.normal_()
+    extra = nb.NERVA_MLP_NESTEROV if flags == "nesterov" else 0
+    out = []
+    for how in (nb.NERVA_MLP_DEFAULT, nb.NERVA_MLP_UNFUSED):
+        m = nb.MLP(data, max_batch, how | extra)
+        for _ in range(3):
+            m.train_step(X, labels, batch, 0.05, 0.9)
+        torch.cuda.synchronize()
+        out.append([t.clone() for l in m.layers for t in (l.values, l.velocity, l.bias, l.bias_velocity)] + [m.loss.clone()])
+        L = m.layers[1]
+        _, _, v_t, perm = nb.sparse_linear_mirror(L.handle)
+        assert np.array_equal(raw_f32(nb, torch, v_t, L.nnz), L.values.cpu().numpy()[raw_i32(nb, torch, perm, L.nnz)])
+        if how == nb.NERVA_MLP_DEFAULT:   # (not the launch that forms both gradients on one gather stream)
+            nb.mlp_profile_enable(m.handle, 1)
+            m.train_step(X, labels, batch, 0.0, 0.0)
+            names = [name for name, _ in nb.mlp_profile_read(m.handle)[1]]
+            assert "sddmm_update[1]" in names and "spmm_transposed[1]" in names, names
+        m.close()
+    for a, b in zip(*out):
+        assert torch.allclose(a, b, rtol=1e-3, atol=2e-6 * max(1.0, float(b.abs().max())))
+
+
 @pytest.mark.parametrize("classes,batch", [(16, 65), (17, 1), (17, 64), (33, 129), (128, 63), (129, 512), (300, 513), (100, 1025)])
 def test_softmax_of_many_classes(nb, oracle, classes, batch):
     import torch
