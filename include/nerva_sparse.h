@@ -22,15 +22,17 @@
  * - Dense matrices hold one example per column (Appendix B listing: Xtrain[:, batch]).
  *   They are fp32, row-major (features, ld): element (i, c) is at base[i*ld + c], with
  *   ld >= batch.  Columns batch..ld-1 are padding: never written, and their contents
- *   never influence a result.  Any ld and any 4-byte aligned base take the same kernels; they
- *   are fastest when every row starts on a 128-byte line (ld a multiple of 32).
+ *   never influence a result.  Any ld and any 4-byte aligned base are taken, by the same sparse
+ *   kernels; they are fastest when every row starts on a 128-byte line (ld a multiple of 32), and the
+ *   dense products load several columns at a time only from rows on 16-byte boundaries.
  * - Biases are dense fp32 vectors of length rows (Section 3: biases are not sparsified).
  * - Every pointer is a DEVICE pointer owned by the caller unless the comment says
  *   "host".  The library owns only what *_create builds and frees it in *_destroy.
  * - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Except for
- *   the *_create calls, every call only enqueues kernels on that stream: it allocates
- *   nothing, never synchronises, and may be captured in a HIP graph.  Calls on one
- *   handle from several streams at once are not ordered by the library.
+ *   the *_create calls, sparse_linear_rebind and sparse_linear_enable_dense, every call only enqueues
+ *   kernels on that stream: it allocates nothing, never synchronises, and may be captured in a HIP
+ *   graph.  Calls on one handle from several streams at once are not ordered by the library: their
+ *   results are undefined where they overlap, those of calls ordered after them are not.
  * - Return value: 0 on success, a negative nerva_status otherwise; nothing has been
  *   enqueued when an argument error is returned.  nerva_last_error() gives a
  *   thread-local message for the last failing call.
@@ -78,8 +80,8 @@ int nerva_validate_csr_host(int32_t rows, int32_t cols, int64_t nnz,
  * below the target; a work-group serves NERVA_WAVES_PER_BLOCK >> lg of them, and a class whose
  * rows do not fill its last work-group hands that work-group's rows, its longest, to class lg + 1
  * where that class's own last work-group has room for them (one work-group fewer).  A row with more stored entries than one work-group should
- * take is "huge": it is cut into several work-groups whose partial results a second kernel adds
- * in order.  Outputs (any array may be NULL to get only the counts):
+ * take is "huge": it is cut into several work-groups, the last of which to finish adds their partial
+ * results in order.  Outputs (any array may be NULL to get only the counts):
  *   counts_host[4]            {ordinary rows, work-groups, huge rows, huge work-groups}
  *   row_order_host[rows]      ordinary row ids in serving order: by lg descending, inside one lg by
  *                             stored entries descending, ties by row id
@@ -209,8 +211,7 @@ int sparse_linear_rebind(nerva_layer *layer, int32_t nnz, const int32_t *indptr,
 /* Density-adaptive layer ("Discussion and Conclusion" and Appendix C.3: dense computation where a layer is
  * not sparse enough for the sparse kernels to win; Section 5.3 shows masks winning at 50 % sparsity and the
  * sparse kernels from about 80 % on).  A layer on the dense route keeps one zero-filled dense copy of its
- * weights (rows x cols floats, columns padded to a multiple of 64; owned by the layer) and a dense gradient of
- * the same shape.  On batches of at least 16 columns its products Y = S X and Y = S^T X run as fp32 MFMA
+ * weights (rows x cols floats, columns padded to a multiple of 64; owned by the layer).  On batches of at least 16 columns its products Y = S X and Y = S^T X run as fp32 MFMA
  * products on that copy, and inside mlp_train_step S = A B^T is formed as a dense product of which only the
  * entries on the pattern are used.  values[] stays the layer's state, in CSR, and the momentum update touches
  * the stored entries only: the pattern is as immutable as on the sparse route, and every update the library

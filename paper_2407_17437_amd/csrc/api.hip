@@ -763,7 +763,7 @@ std::atomic<float> g_dense_threshold{kDenseFromDensity};
 
 static bool dense_shape_ok(int32_t rows, int32_t cols)
 {
-    // (a thin full matrix has its own streaming kernels; the copy and the dense gradient stay below 2 GiB each)
+    // (a thin full matrix has its own streaming kernels; the copy stays below 2 GiB)
     return rows >= 64 && cols >= 64 && static_cast<int64_t>(rows) * round_up(cols, kDenseLdAlign) < (1ll << 29);
 }
 

@@ -186,14 +186,14 @@ struct SddmmArgs {
     const int32_t *perm;     // mirror position -> CSR position (only the fused backward pass needs it)
     float *bias;             // [rows] or nullptr
     float *bias_velocity;    // [rows] or nullptr
-    // by-product, unrelated to the layer: *loss_out = mean(loss_cols[0..loss_n)), summed in one fixed
-    // order by the first wave of the launch.  The head kernel leaves one loss per batch column; a
-    // grid-wide sum inside it would need device-scope fences, which write back and invalidate the L2s.
     // launch_full_backward only: the biases of the layer BELOW and their momentum buffer, or nullptr.  That layer's
     // bias gradient is the row sum of the dX this launch forms, a wave per row, so its update can ride along
     // (the caller then leaves the biases out of that layer's own update).
     float *below_bias;
     float *below_bias_velocity;
+    // by-product, unrelated to the layer: *loss_out = mean(loss_cols[0..loss_n)), summed in one fixed
+    // order by the first wave of the launch.  The head kernel leaves one loss per batch column; a
+    // grid-wide sum inside it would need device-scope fences, which write back and invalidate the L2s.
     const float *loss_cols;  // or nullptr
     float *loss_out;
     int32_t loss_n;
@@ -278,8 +278,8 @@ hipError_t launch_copy(float *dst, const float *src, int64_t n, hipStream_t s);
 // Dense route of a layer whose density is high (the density-adaptive layer the paper plans in
 // "Discussion and Conclusion" and Appendix C.3).  One zero-filled dense copy of the weights, row-major
 // W[i * ldw + j] with ldw = cols rounded up to kDenseLdAlign (zero off the pattern and in the padding), serves
-// the forward product, the transposed product (the same copy read down its columns) and, through a dense
-// gradient G = dZ X^T of the same shape, the update of the stored entries.
+// the forward product and the transposed product (the same copy read down its columns); the update of the stored
+// entries is sampled from tiles of G = dZ X^T (SampledLayer below), which is never stored.
 constexpr int32_t kDenseLdAlign = 64;
 constexpr float kTableFromDensity = 0.15f;  // layers at least this dense get a pattern table when they are bound
 constexpr float kDenseFromDensity = 0.4f;   // layers at least this dense take the dense route by themselves (measured cut-over)

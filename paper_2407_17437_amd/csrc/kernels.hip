@@ -8,10 +8,10 @@
 // indices loaded one per lane and handed round with ds_bpermute.  Rows are handed to work-groups
 // by a static partition (RowBlocks) that gives long rows several waves, each with a contiguous
 // share of the row's stored entries; partial sums of one row meet in LDS and are added in a
-// fixed order.  There are no float atomics: every output element is produced by one lane in one
+// fixed order.  No float is added atomically: every output element is produced by one lane in one
 // order, so results are bit-reproducible from run to run.  (The exceptions to "along the batch":
-// spmv_kernel and head_kernel, whose lanes run across a row's entries, and the opt-in dense
-// route, an MFMA product.)
+// spmv_kernel, spmv_rows_kernel and head_kernel, whose lanes run across a row's entries, and the MFMA
+// products of dense.hip: dense layers, dense rows, sampled gradients.)
 #include "device.h"
 #include "kernels.h"
 
@@ -110,13 +110,18 @@ __device__ __forceinline__ void spmm_store(const SpmmArgs &a, int row, int col, 
 // them arrive first (a release fence would write back a whole L2).  The ticket counts modulo the number of shares: it is 0 after
 // every product, whatever ran beside it (products of one layer that overlap spoil each other's partial rows, but none after them).
 // Instead of a second launch: forward product of the power-law 16384^2 matrix at 0.1 %, batch 128: 21.4 -> 18.3 us.
+// `alone`: the first wave does it all and the others end at once.  Where a launch has several column tiles the work-groups outnumber
+// what the chip holds, and 16 waves that wait for one wave's round trips keep others out: the same matrix at batch 512 / 1024, with
+// a second launch instead 55.7 / 104 us, all waves waiting 58.8 / 114.4, one alone 56.1 / 108.9; at 0.3 %, batch 256: 98, 93, 86.
 template <int N, int LANES>
-__device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask &task, int block, int col0, int col, int own, bool on,
+__device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask &task, int block, int col0, int col, int own, bool on, bool alone,
                                                float (&acc)[N], float (&red)[kWavesPerBlock][N][LANES])
 {
     __shared__ int turn_s;
     const int lane = threadIdx.x & (kWave - 1), wv = wave_in_block();
+    if (alone && wv != 0) return;
     const int4 h = a.blocks.huge_rows[task.index];
+    int turn = 0;
     if (wv == 0) {
         float *mine = a.scratch + static_cast<int64_t>(block) * a.scratch_ld + col;
         if (on) {
@@ -127,37 +132,45 @@ __device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (lane == 0) {
             int *ticket = a.tickets + 2 * task.index * huge_row_tickets(a.scratch_ld) + col0 / 32;
-            turn_s = static_cast<int>(atomicInc(reinterpret_cast<unsigned *>(ticket), static_cast<unsigned>(h.z - 1)));
+            turn = static_cast<int>(atomicInc(reinterpret_cast<unsigned *>(ticket), static_cast<unsigned>(h.z - 1)));
         }
+        turn = __builtin_amdgcn_readfirstlane(turn);
     }
-    __syncthreads();
-    if (turn_s != h.z - 1) return;  // uniform
+    const int step = alone ? 1 : kWavesPerBlock;   // shares from one of the wave's to its next
+    if (!alone) {
+        if (threadIdx.x == 0) turn_s = turn;
+        __syncthreads();
+        turn = turn_s;
+    }
+    if (turn != h.z - 1) return;  // uniform
     if (on) {
         const float *first = a.scratch + static_cast<int64_t>(h.y) * a.scratch_ld + col;
 #pragma unroll
         for (int k = 0; k < N; ++k) acc[k] = 0.f;
-        constexpr int U = 4;
-        for (int q = wv; q < h.z; q += U * kWavesPerBlock) {
+        constexpr int U = 4;   // (8 of them cost the packed kernel its second work-group per compute unit)
+        for (int q = wv; q < h.z; q += U * step) {
             float v[U][N];
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int k = 0; k < N; ++k)
-                    v[u][k] = __hip_atomic_load(first + static_cast<int64_t>(min(q + u * kWavesPerBlock, h.z - 1)) * a.scratch_ld + k, __ATOMIC_RELAXED,
+                    v[u][k] = __hip_atomic_load(first + static_cast<int64_t>(min(q + u * step, h.z - 1)) * a.scratch_ld + k, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int k = 0; k < N; ++k) acc[k] = q + u * kWavesPerBlock < h.z ? acc[k] + v[u][k] : acc[k];
+                for (int k = 0; k < N; ++k) acc[k] = q + u * step < h.z ? acc[k] + v[u][k] : acc[k];
         }
+        if (!alone)
 #pragma unroll
-        for (int k = 0; k < N; ++k) red[wv][k][lane] = acc[k];
+            for (int k = 0; k < N; ++k) red[wv][k][lane] = acc[k];
     }
-    __syncthreads();
+    if (!alone) __syncthreads();
     if (wv != 0 || !on) return;
-    for (int w = 1; w < min(h.z, kWavesPerBlock); ++w)
+    if (!alone)
+        for (int w = 1; w < min(h.z, kWavesPerBlock); ++w)
 #pragma unroll
-        for (int k = 0; k < N; ++k) acc[k] += red[w][k][lane];
+            for (int k = 0; k < N; ++k) acc[k] += red[w][k][lane];
     if constexpr (N == 4) {
         spmm_store(a, task.row, col, own, acc);
     } else {
@@ -211,7 +224,7 @@ __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, co
         }
     }
     if (task.row >= 0 && task.huge) {  // uniform over the work-group
-        huge_row_share(a, task, block, col0, col, col0 + lane * 4, on, acc, red);
+        huge_row_share(a, task, block, col0, col, col0 + lane * 4, on, a.batch > 4 * kWave, acc, red);
         return;
     }
     if (task.row < 0 || task.part != 0 || !on) return;
@@ -335,7 +348,7 @@ __device__ __forceinline__ void spmm_body_grouped(const SpmmArgs &a, const int b
                 for (int k = 0; k < 4; ++k) acc[k] += red[wv + s][k][g * GS + lig];
     }
     if (task.huge) {  // uniform over the work-group
-        huge_row_share(a, task, block, col0, col, col0 + lig * 4, on && grp == 0, acc, red);
+        huge_row_share(a, task, block, col0, col, col0 + lig * 4, on && grp == 0, a.batch > 4 * GS, acc, red);
         return;
     }
     if (on) spmm_store(a, task.row, col, col0 + lig * 4, acc);
@@ -553,7 +566,7 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(const SpmmArgs a)
     for (int c = 1; c < NB; ++c) y = lane == c ? acc[c] : y;
     if (task.huge) {  // uniform over the work-group
         float one[1] = {y};
-        huge_row_share(a, task, blockIdx.x, 0, lane, lane, lane < a.batch && lane < NB, one, shares);
+        huge_row_share(a, task, blockIdx.x, 0, lane, lane, lane < a.batch && lane < NB, false, one, shares);
         return;
     }
     y += a.bias ? a.bias[task.row] : 0.f;
