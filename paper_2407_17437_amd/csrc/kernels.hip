@@ -110,16 +110,16 @@ __device__ __forceinline__ void spmm_store(const SpmmArgs &a, int row, int col, 
 // them arrive first (a release fence would write back a whole L2).  The ticket counts modulo the number of shares: it is 0 after
 // every product, whatever ran beside it (products of one layer that overlap spoil each other's partial rows, but none after them).
 // Instead of a second launch: forward product of the power-law 16384^2 matrix at 0.1 %, batch 128: 21.4 -> 18.3 us.
-// `alone`: the first wave does it all and the others end at once.  Where a launch has several column tiles the work-groups outnumber
-// what the chip holds, and 16 waves that wait for one wave's round trips keep others out: the same matrix at batch 512 / 1024, with
-// a second launch instead 55.7 / 104 us, all waves waiting 58.8 / 114.4, one alone 56.1 / 108.9; at 0.3 %, batch 256: 98, 93, 86.
-template <int N, int LANES>
-__device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask &task, int block, int col0, int col, int own, bool on, bool alone,
+// ALONE: the first wave does it all and the others end at once.  In column tiles the work-groups outnumber what the chip holds,
+// and 16 waves that wait for one wave's round trips keep others out: the same matrix at batch 512 / 1024, with a second launch instead
+// 55.7 / 104 us, all waves waiting 58.8 / 114.4, one alone 55.8 / 108.4.
+template <bool ALONE, int N, int LANES>
+__device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask &task, int block, int col0, int col, int own, bool on,
                                                float (&acc)[N], float (&red)[kWavesPerBlock][N][LANES])
 {
     __shared__ int turn_s;
     const int lane = threadIdx.x & (kWave - 1), wv = wave_in_block();
-    if (alone && wv != 0) return;
+    if (ALONE && wv != 0) return;
     const int4 h = a.blocks.huge_rows[task.index];
     int turn = 0;
     if (wv == 0) {
@@ -136,8 +136,8 @@ __device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask
         }
         turn = __builtin_amdgcn_readfirstlane(turn);
     }
-    const int step = alone ? 1 : kWavesPerBlock;   // shares from one of the wave's to its next
-    if (!alone) {
+    constexpr int step = ALONE ? 1 : kWavesPerBlock;   // shares from one of the wave's to its next
+    if constexpr (!ALONE) {
         if (threadIdx.x == 0) turn_s = turn;
         __syncthreads();
         turn = turn_s;
@@ -161,13 +161,13 @@ __device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask
 #pragma unroll
                 for (int k = 0; k < N; ++k) acc[k] = q + u * step < h.z ? acc[k] + v[u][k] : acc[k];
         }
-        if (!alone)
+        if constexpr (!ALONE)
 #pragma unroll
             for (int k = 0; k < N; ++k) red[wv][k][lane] = acc[k];
     }
-    if (!alone) __syncthreads();
+    if constexpr (!ALONE) __syncthreads();
     if (wv != 0 || !on) return;
-    if (!alone)
+    if constexpr (!ALONE)
         for (int w = 1; w < min(h.z, kWavesPerBlock); ++w)
 #pragma unroll
             for (int k = 0; k < N; ++k) acc[k] += red[w][k][lane];
@@ -224,7 +224,7 @@ __device__ __forceinline__ void spmm_body(const SpmmArgs &a, const int block, co
         }
     }
     if (task.row >= 0 && task.huge) {  // uniform over the work-group
-        huge_row_share(a, task, block, col0, col, col0 + lane * 4, on, a.batch > 4 * kWave, acc, red);
+        huge_row_share<false>(a, task, block, col0, col, col0 + lane * 4, on, acc, red);
         return;
     }
     if (task.row < 0 || task.part != 0 || !on) return;
@@ -274,7 +274,7 @@ __device__ __forceinline__ void grouped_pass(gmem_ptr Xg, gmem_ptr Mg, int src, 
 // 16 in groups of 4, but 5.3 instead of 5.1 on 1000 x 3000: not kept).
 // Row offsets are 32-bit byte offsets from the operand's base: the operand (and its mask) must
 // span less than 4 GiB, which the launcher checks.
-template <int GS, bool XMASK>
+template <int GS, bool XMASK, bool TILED = false>
 __device__ __forceinline__ void spmm_body_grouped(const SpmmArgs &a, const int block, const int col0 = 0)
 {
     constexpr int NE = kWave / GS;   // entries per gather instruction
@@ -348,7 +348,7 @@ __device__ __forceinline__ void spmm_body_grouped(const SpmmArgs &a, const int b
                 for (int k = 0; k < 4; ++k) acc[k] += red[wv + s][k][g * GS + lig];
     }
     if (task.huge) {  // uniform over the work-group
-        huge_row_share(a, task, block, col0, col, col0 + lig * 4, on && grp == 0, a.batch > 4 * GS, acc, red);
+        huge_row_share<TILED>(a, task, block, col0, col, col0 + lig * 4, on && grp == 0, acc, red);
         return;
     }
     if (on) spmm_store(a, task.row, col, col0 + lig * 4, acc);
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(kBlock) void spmm_packed_kernel(const SpmmArgs a, c
     } else {
         SpmmArgs al = a;
         al.blocks.waves = a.blocks.long_waves;
-        spmm_body_grouped<GS, XMASK>(al, rb - n_pack_blocks, tile * GS * 4);
+        spmm_body_grouped<GS, XMASK, true>(al, rb - n_pack_blocks, tile * GS * 4);
     }
 }
 
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, co
         rb = blockIdx.x % nrb;
     }
     if (tile >= n_tiles) return;
-    spmm_body_grouped<GS, XMASK>(a, rb, tile * GS * 4);
+    spmm_body_grouped<GS, XMASK, true>(a, rb, tile * GS * 4);
 }
 
 // Wide batches: the columns in tiles of 256, a work-group of the row partition each -- more, shorter work-groups than one
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(const SpmmArgs a)
     for (int c = 1; c < NB; ++c) y = lane == c ? acc[c] : y;
     if (task.huge) {  // uniform over the work-group
         float one[1] = {y};
-        huge_row_share(a, task, blockIdx.x, 0, lane, lane, lane < a.batch && lane < NB, false, one, shares);
+        huge_row_share<false>(a, task, blockIdx.x, 0, lane, lane, lane < a.batch && lane < NB, one, shares);
         return;
     }
     y += a.bias ? a.bias[task.row] : 0.f;
