@@ -1656,9 +1656,13 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
 constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and smaller groups schedule finer (measured on the wide MLP:
                               // 134 / 138 / 142 us with 4 / 8 / 16 waves; gather depth 4 instead of 8 and a register cap of 64 change nothing)
 
-template <int U, int GS, bool XMASK>
-__device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, float my_w, uint32_t off, const float4 &ax, int it0, int lig,
-                                         float (&acc)[4], float &res)
+// SPARE: lanes re-read columns that are not their own.  What they have gathered there is dropped by a bitwise and with a mask
+// of all ones or zeros, which costs nothing measurable beside the gathers (the 1585-521 layer in a step of 355-1585-521-1999-10 at 32 %, batch 66:
+// 19.1 us without, 18.8 with; forming a NaN result again, as sddmm_body does, takes registers of the other path: 23.1).
+__device__ __forceinline__ float keep_bits(float x, uint32_t mask) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & mask); }
+template <int U, int GS, bool XMASK, bool SPARE>
+__device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, float my_w, uint32_t off, const float4 &ax,
+                                         const uint32_t (&own)[4], int it0, int lig, float (&acc)[4], float &res)
 {
     uint32_t ro[U], mo[U];
     float w[U];
@@ -1681,26 +1685,12 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int 
         acc[1] = fmaf(w[u], x[u].y, acc[1]);
         acc[2] = fmaf(w[u], x[u].z, acc[2]);
         acc[3] = fmaf(w[u], x[u].w, acc[3]);
-        float part = fmaf(ax.w, x[u].w, fmaf(ax.z, x[u].z, fmaf(ax.y, x[u].y, ax.x * x[u].x)));
+        float4 y = x[u];
+        if constexpr (SPARE) y = make_float4(keep_bits(y.x, own[0]), keep_bits(y.y, own[1]), keep_bits(y.z, own[2]), keep_bits(y.w, own[3]));
+        float part = fmaf(ax.w, y.w, fmaf(ax.z, y.z, fmaf(ax.y, y.y, ax.x * y.x)));
         part = group_sum<GS>(part);
         res = lig == it0 + u ? part : res;
     }
-}
-
-// The products of `steps` such entries from every lane's own columns alone, where a lane's others made one of them NaN.
-template <int GS, bool XMASK>
-__device__ __forceinline__ float bwd_own_columns(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, uint32_t off, const float4 &ax, int steps, int lig,
-                                                 int own_col, int batch)
-{
-    float res = 0.f;
-#pragma unroll 1
-    for (int u = 0; u < steps; ++u) {
-        float4 x = gload4(Zg, static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src + u * 4, my_ro)) + off);
-        if constexpr (XMASK) x = keep_where_positive(x, gload4(Mg, static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src + u * 4, my_mo)) + off));
-        const float part = group_sum<GS>(add_own_products(0.f, ax, x, own_col, static_cast<int>(off >> 2), batch));
-        res = lig == u ? part : res;
-    }
-    return res;
 }
 
 // Sums of the rows of dZ, a wave per row: the bias gradient, stored or applied.
@@ -1735,11 +1725,8 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // the lane groups and the matrix is small: then a wave takes its entries through all tiles.  XMASK: dZ is dY times
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
-// SPARE: as in sddmm_body.
-// (waves per SIMD that the registers of the gathers allow: the products that are formed again are not to cost any)
-constexpr int backward_waves(BackwardPass pass, bool masked) { return pass == kBackwardTiles ? (masked ? 6 : 8) : pass == kBackwardOneTile ? (masked ? 5 : 6) : (masked ? 4 : 6); }
 template <int GS, BackwardPass PASS, bool XMASK, bool SPARE>
-__global__ __launch_bounds__(kBwdWaves * kWave) __attribute__((amdgpu_waves_per_eu(SPARE ? backward_waves(PASS, XMASK) : 1))) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
+__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
                                                                           const int n_pack_blocks, const int lg_split)
 {
     constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped;
@@ -1803,12 +1790,15 @@ __global__ __launch_bounds__(kBwdWaves * kWave) __attribute__((amdgpu_waves_per_
                 const int col = four_columns(on ? own_col : col0, a.batch);
                 const uint32_t off = static_cast<uint32_t>(col) * 4u;
                 // the group's row of X: the second operand of its entries' products, and the mask of its result;
-                // lanes beyond the batch hold zeros, so that the columns they re-read add nothing to a product (Inf or NaN there: see below)
+                // lanes beyond the batch hold zeros, so that the columns they re-read add nothing to a product
                 float4 ax = make_float4(0.f, 0.f, 0.f, 0.f), mask = ax;
                 if (row >= 0 && on) {
                     mask = ld4(a.X + static_cast<int64_t>(row) * a.ldx + col);
                     ax = drop_shared(mask, own_col, col);
                 }
+                uint32_t own[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) own[k] = on && col + k >= own_col ? ~0u : 0u;
                 float acc[4] = {0.f, 0.f, 0.f, 0.f};
                 int cur_j, cur_at = 0;
                 float cur_w, cur_v = 0.f;
@@ -1824,17 +1814,16 @@ __global__ __launch_bounds__(kBwdWaves * kWave) __attribute__((amdgpu_waves_per_
                     float res = 0.f;
                     int src = src0;
                     int u0 = 0;
-                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                     if (u0 + 4 <= steps) {
-                        bwd_pass<4, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                        bwd_pass<4, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                         u0 += 4; src += 16;
                     }
                     if (u0 + 2 <= steps) {
-                        bwd_pass<2, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
+                        bwd_pass<2, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                         u0 += 2; src += 8;
                     }
-                    if (u0 < steps) bwd_pass<1, GS, XMASK>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, u0, lig, acc, res);
-                    if (SPARE && col0 + GS * 4 > a.batch && __any(res != res)) res = bwd_own_columns<GS, XMASK>(Zg, Mg, src0, my_ro, my_mo, off, ax, steps, lig, own_col, a.batch);
+                    if (u0 < steps) bwd_pass<1, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                     const int e = base + part * GS + lig;
                     if (row >= 0 && e < len) {
                         if constexpr (ONE) {
