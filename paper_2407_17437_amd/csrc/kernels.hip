@@ -1657,8 +1657,10 @@ constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and
                               // 134 / 138 / 142 us with 4 / 8 / 16 waves; gather depth 4 instead of 8 and a register cap of 64 change nothing)
 
 // SPARE: lanes re-read columns that are not their own.  What they have gathered there is dropped by a bitwise and with a mask
-// of all ones or zeros, which costs nothing measurable beside the gathers (the 1585-521 layer in a step of 355-1585-521-1999-10 at 32 %, batch 66:
-// 19.1 us without, 18.8 with; forming a NaN result again, as sddmm_body does, takes registers of the other path: 23.1).
+// of all ones or zeros; of the result they store their own columns.  One tile without / with: the 1585-521 layer in a step of
+// 355-1585-521-1999-10 at 32 %, batch 66, 19.0 / 18.9 us; 713 x 2042 at 6.6 %, batch 36, 6.2 / 5.7; 15969 x 11666 at 0.6 %, batch 51, 29.5 / 32.3;
+// 64-column tiles, 14024 x 5061 at 0.3 %, batch 845, 79.5 / 79.4.  (Forming a NaN result again, as sddmm_body does, takes registers
+// of the pass itself: the first of these 23.1.)
 __device__ __forceinline__ float keep_bits(float x, uint32_t mask) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & mask); }
 template <int U, int GS, bool XMASK, bool SPARE>
 __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, float my_w, uint32_t off, const float4 &ax,
@@ -1681,13 +1683,12 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int 
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+        if constexpr (SPARE) x[u] = make_float4(keep_bits(x[u].x, own[0]), keep_bits(x[u].y, own[1]), keep_bits(x[u].z, own[2]), keep_bits(x[u].w, own[3]));
         acc[0] = fmaf(w[u], x[u].x, acc[0]);
         acc[1] = fmaf(w[u], x[u].y, acc[1]);
         acc[2] = fmaf(w[u], x[u].z, acc[2]);
         acc[3] = fmaf(w[u], x[u].w, acc[3]);
-        float4 y = x[u];
-        if constexpr (SPARE) y = make_float4(keep_bits(y.x, own[0]), keep_bits(y.y, own[1]), keep_bits(y.z, own[2]), keep_bits(y.w, own[3]));
-        float part = fmaf(ax.w, y.w, fmaf(ax.z, y.z, fmaf(ax.y, y.y, ax.x * y.x)));
+        float part = fmaf(ax.w, x[u].w, fmaf(ax.z, x[u].z, fmaf(ax.y, x[u].y, ax.x * x[u].x)));
         part = group_sum<GS>(part);
         res = lig == it0 + u ? part : res;
     }
@@ -1854,7 +1855,14 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                 if (row < 0 || !on || part != 0) continue;
                 float4 y = len > 0 ? make_float4(acc[0], acc[1], acc[2], acc[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
                 if (a.mask) y = keep_where_positive(y, mask);
-                st4(a.dX + static_cast<int64_t>(row) * a.lddx + col, y);
+                float *out = a.dX + static_cast<int64_t>(row) * a.lddx + col;
+                if (!SPARE || col == own_col) {
+                    st4(out, y);
+                } else {   // (the lane's own columns of the batch's last four)
+                    if (own_col <= col + 1) out[1] = y.y;
+                    if (own_col <= col + 2) out[2] = y.z;
+                    out[3] = y.w;
+                }
         }
     }
 }
