@@ -73,8 +73,8 @@ def slot_bytes(name: str, layer, batch: int, has_mirror_scatter: bool) -> float:
         return 20 * m
     if kind == "mirror_refresh":
         return 12 * nnz
-    if kind == "dense_sddmm_update":  # dZ and X in, the dense gradient written and read on the pattern, the update, the dense copy
-        return 4 * n * (m + k) + 4 * m * k + 4 * nnz + 4 * nnz + 16 * nnz + 4 * nnz + 16 * m + (8 * nnz if has_mirror_scatter else 0)
+    if kind == "dense_sddmm_update":  # dZ and X in, the table of pattern bits (8 bytes per 32 columns), the update, the dense copy
+        return 4 * n * (m + k) + m * k / 4 + 16 * nnz + 4 * nnz + 16 * m + (8 * nnz if has_mirror_scatter else 0)
     if kind == "dense_forward":       # the dense copy of the weights, X in, Y out, bias
         return 4 * m * k + 4 * n * (k + m) + 4 * m
     if kind == "dense_transposed":    # the dense copy, dZ in, dX out, ReLU mask in
@@ -464,7 +464,7 @@ def main() -> int:
                   "samples_per_s": round(r["samples_per_s"], 1), "route": "sparse"}
             if 1.0 - s >= DENSE_FROM_DENSITY and args.dense_from_density is None:
                 # the library put the large layers on the dense route by itself: the sparse route on the same network too
-                pt["route"] = "dense products and dense gradient (the library's choice at this density)"
+                pt["route"] = "dense products and sampled gradient (the library's choice at this density)"
                 nb.nerva_set_dense_threshold(2.0)
                 try:
                     r2_ = measure_mlp(env, f"sweep{s}", Ks, Ws, 0, args, copy_gbs)

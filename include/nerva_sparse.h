@@ -203,7 +203,7 @@ void sparse_linear_destroy(nerva_layer *layer);
  * entries as the method prescribes (zero for grown ones), with mlp_rebind_velocity, and ask
  * mlp_workspace_bytes / mlp_workspace_layout again: the workspace holds one float per stored
  * entry of every layer, so its size and offsets move with nnz.  Everything runs on
- * the device (measured on an MI355X: 0.06 ms for a 1024 x 3072 layer with 315 k entries, 0.3 ms for a
+ * the device (measured on an MI355X: 0.07 ms for a 1024 x 3072 layer with 315 k entries, 0.34 ms for a
  * 16384 x 16384 matrix with 2.7 M) -- cheap enough for a topology update every few dozen steps. */
 int sparse_linear_rebind(nerva_layer *layer, int32_t nnz, const int32_t *indptr,
                          const int32_t *indices, float *values, void *stream);
@@ -218,9 +218,8 @@ int sparse_linear_rebind(nerva_layer *layer, int32_t nnz, const int32_t *indptr,
  * applies is written to the copy as well.  Results agree with the sparse route to rounding (other summation
  * order); entries off the pattern contribute 0 * x, so an operand that holds Inf/NaN spreads differently.
  * sparse_linear_create and sparse_linear_rebind take the route by themselves for a pattern of at least 40 %
- * density with at least 64 rows and 64 columns (the cut-over measured on the 3072-1024-512-10 network at batch
- * 100: the dense route's step takes 81 - 91 us whatever the density, the sparse route's 106 us at 50 % and
- * 57 us at 80 % sparsity); this call switches any layer over by hand.  A route once taken is kept across sparse_linear_rebind.
+ * density with at least 64 rows and 64 columns (the 3072-1024-512-10 network at batch 100: a step takes
+ * 59 us on the dense route and 79 on the sparse one at 50 % sparsity, 54 and 57 at 80 %); this call switches any layer over by hand.  A route once taken is kept across sparse_linear_rebind.
  * Errors: NERVA_ERR_SHAPE (rows x cols beyond 2^31), NERVA_ERR_HIP. */
 int sparse_linear_enable_dense(nerva_layer *layer, void *stream);
 

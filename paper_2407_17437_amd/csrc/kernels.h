@@ -282,7 +282,8 @@ hipError_t launch_copy(float *dst, const float *src, int64_t n, hipStream_t s);
 // entries is sampled from tiles of G = dZ X^T (SampledLayer below), which is never stored.
 constexpr int32_t kDenseLdAlign = 64;
 constexpr float kTableFromDensity = 0.15f;  // layers at least this dense get a pattern table when they are bound
-constexpr float kDenseFromDensity = 0.4f;   // layers at least this dense take the dense route by themselves (measured cut-over)
+constexpr float kDenseFromDensity = 0.4f;   // layers at least this dense take the dense route by themselves (steps of 3072-1024-512-10, batch 100, dense /
+                                            // sparse route: 58.8 / 79.3 us at 50 % density, 53.8 / 56.9 at 20 %: the line lay at 40 % before both sampled the gradient)
 struct DenseArgs {
     const float *W;      // the dense copy, (rows, ldw)
     int64_t ldw;
