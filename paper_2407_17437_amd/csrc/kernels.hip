@@ -112,7 +112,7 @@ __device__ __forceinline__ void spmm_store(const SpmmArgs &a, int row, int col, 
 // Instead of a second launch: forward product of the power-law 16384^2 matrix at 0.1 %, batch 128: 21.4 -> 18.3 us.
 // ALONE: the first wave does it all and the others end at once.  In column tiles the work-groups outnumber what the chip holds,
 // and 16 waves that wait for one wave's round trips keep others out: the same matrix at batch 512 / 1024, with a second launch instead
-// 55.7 / 104 us, all waves waiting 58.8 / 114.4, one alone 55.8 / 108.4.
+// 55.7 / 104 us, all waves waiting 58.8 / 114.4, one alone 56.2 / 107.2.
 template <bool ALONE, int N, int LANES>
 __device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask &task, int block, int col0, int col, int own, bool on,
                                                float (&acc)[N], float (&red)[kWavesPerBlock][N][LANES])
@@ -156,10 +156,19 @@ __device__ __forceinline__ void huge_row_share(const SpmmArgs &a, const WaveTask
                 for (int k = 0; k < N; ++k)
                     v[u][k] = __hip_atomic_load(first + static_cast<int64_t>(min(q + u * step, h.z - 1)) * a.scratch_ld + k, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (ALONE) {   // (in pairs: one chain over all shares would round more often than the 16 waves' sums do)
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+                for (int k = 0; k < N; ++k) {
 #pragma unroll
-                for (int k = 0; k < N; ++k) acc[k] = q + u * step < h.z ? acc[k] + v[u][k] : acc[k];
+                    for (int u = 1; u < U; ++u) v[u][k] = q + u < h.z ? v[u][k] : 0.f;
+                    acc[k] += (v[0][k] + v[1][k]) + (v[2][k] + v[3][k]);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < N; ++k) acc[k] = q + u * step < h.z ? acc[k] + v[u][k] : acc[k];
+            }
         }
         if constexpr (!ALONE)
 #pragma unroll
