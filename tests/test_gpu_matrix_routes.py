@@ -197,6 +197,17 @@ def test_infinities_reach_the_gradients_of_their_own_columns(nb, rows, cols, den
     L.close()
 
 
+@pytest.mark.parametrize("rows,batch", [(2600, 1024), (2600, 1001), (700, 1024)])
+def test_huge_rows_in_column_tiles(nb, oracle, rows, batch):
+    """Rows cut into 3, 4, 5, 6, 9, ... 36 work-groups per tile, the shares added by one wave; beside packed rows and without."""
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(0, 20, rows)
+    lens[rng.permutation(rows)[:11]] = [513, 768, 769, 1024, 1025, 1280, 1281, 2049, 4000, 8999, 9000]
+    indptr, indices = wl.pattern_from_row_nnz(lens, 9000, seed=rows)
+    lay = wl.SparseLayerData(rows, 9000, indptr, indices, wl.init_values(indptr, 1), rng.standard_normal(rows).astype(np.float32), True)
+    check_layer(nb, oracle, lay, batch, ld=batch)
+
+
 @pytest.mark.parametrize("batch", [257, 300, 320, 385, 511, 512, 513, 640, 1023, 1024, 1025])
 def test_wide_batches_in_column_tiles(nb, oracle, batch):
     # (operands of 300 rows, which no rule tiles; rows cut over several waves and several work-groups)
