@@ -1665,13 +1665,15 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
 constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and smaller groups schedule finer (measured on the wide MLP:
                               // 134 / 138 / 142 us with 4 / 8 / 16 waves; gather depth 4 instead of 8 and a register cap of 64 change nothing)
 
-// SPARE: lanes re-read columns that are not their own.  What they have gathered there is dropped by a bitwise and with a mask
+// Lanes may re-read columns that are not their own.  What they have gathered there is dropped by a bitwise and with a mask
 // of all ones or zeros; of the result they store their own columns.  One tile without / with: the 1585-521 layer in a step of
 // 355-1585-521-1999-10 at 32 %, batch 66, 19.0 / 18.9 us; 713 x 2042 at 6.6 %, batch 36, 6.2 / 5.7; 15969 x 11666 at 0.6 %, batch 51, 29.5 / 32.3;
 // 64-column tiles, 14024 x 5061 at 0.3 %, batch 845, 79.5 / 79.4.  (Forming a NaN result again, as sddmm_body does, takes registers
-// of the pass itself: the first of these 23.1.)
+// of the pass itself: the first of these 23.1.)  In tiles, where batches are multiples of 4 and lanes have all four columns or
+// none, masking the product alone leaves the registers as they are: 7413 x 4010 at 0.5 %, batch 212, 17.4 without, 18.3 with four masks, 17.7 with one.
+enum BackwardSpare { kSpareNone, kSpareLanes, kSpareColumns };
 __device__ __forceinline__ float keep_bits(float x, uint32_t mask) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & mask); }
-template <int U, int GS, bool XMASK, bool SPARE>
+template <int U, int GS, bool XMASK, BackwardSpare SPARE>
 __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, float my_w, uint32_t off, const float4 &ax,
                                          const uint32_t (&own)[4], int it0, int lig, float (&acc)[4], float &res)
 {
@@ -1692,12 +1694,13 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int 
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if constexpr (SPARE) x[u] = make_float4(keep_bits(x[u].x, own[0]), keep_bits(x[u].y, own[1]), keep_bits(x[u].z, own[2]), keep_bits(x[u].w, own[3]));
+        if constexpr (SPARE == kSpareColumns) x[u] = make_float4(keep_bits(x[u].x, own[0]), keep_bits(x[u].y, own[1]), keep_bits(x[u].z, own[2]), keep_bits(x[u].w, own[3]));
         acc[0] = fmaf(w[u], x[u].x, acc[0]);
         acc[1] = fmaf(w[u], x[u].y, acc[1]);
         acc[2] = fmaf(w[u], x[u].z, acc[2]);
         acc[3] = fmaf(w[u], x[u].w, acc[3]);
         float part = fmaf(ax.w, x[u].w, fmaf(ax.z, x[u].z, fmaf(ax.y, x[u].y, ax.x * x[u].x)));
+        if constexpr (SPARE == kSpareLanes) part = keep_bits(part, own[3]);
         part = group_sum<GS>(part);
         res = lig == it0 + u ? part : res;
     }
@@ -1735,7 +1738,7 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // the lane groups and the matrix is small: then a wave takes its entries through all tiles.  XMASK: dZ is dY times
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
-template <int GS, BackwardPass PASS, bool XMASK, bool SPARE>
+template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE>
 __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
                                                                           const int n_pack_blocks, const int lg_split)
 {
@@ -1865,7 +1868,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                 float4 y = len > 0 ? make_float4(acc[0], acc[1], acc[2], acc[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
                 if (a.mask) y = keep_where_positive(y, mask);
                 float *out = a.dX + static_cast<int64_t>(row) * a.lddx + col;
-                if (!SPARE || col == own_col) {
+                if (SPARE != kSpareColumns || col == own_col) {
                     st4(out, y);
                 } else {   // (the lane's own columns of the batch's last four)
                     if (own_col <= col + 1) out[1] = y.y;
@@ -2904,10 +2907,14 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         constexpr int GS = decltype(group)::value;
         const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
         auto launch = [&](auto pass, auto mask) {
-            with_spare(a.batch, GS * 4, [&](auto spare) {
+            auto with = [&](auto spare) {
                 hipLaunchKernelGGL((backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value>), grid, block, 0, s, a,
                                    n_tiles, spread, n_pack_blocks, lg_split);
-            });
+            };
+            if (a.batch % (GS * 4) == 0) return with(std::integral_constant<BackwardSpare, kSpareNone>{});
+            if constexpr (decltype(pass)::value == kBackwardTiles)
+                if (a.batch % 4 == 0) return with(std::integral_constant<BackwardSpare, kSpareLanes>{});
+            with(std::integral_constant<BackwardSpare, kSpareColumns>{});
         };
         using tiles = std::integral_constant<BackwardPass, kBackwardTiles>;
         using single = std::integral_constant<BackwardPass, kBackwardOneTile>;
