@@ -9,7 +9,7 @@ import sysconfig
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libnerva_sparse.so")
-SOURCES = ["kernels.hip", "structure.hip", "dense.hip", "api.hip"]
+SOURCES = ["kernels.hip", "structure.hip", "dense.hip", "split.hip", "api.hip"]
 FASTCALL = os.path.join(PKG, "_fastcall.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

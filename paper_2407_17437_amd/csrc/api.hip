@@ -97,7 +97,7 @@ struct PatternBuffers {
     bool has_table = false;         // it holds the pattern (else the layer is too sparse for it)
     int32_t *row_table = nullptr;   // the same of the dense rows alone (DenseRows)
     size_t row_table_ints = 0;
-    float *row_partial = nullptr;   // sliced results of their product
+    float *row_partial = nullptr;   // sliced results of their product, and its operand's parts
     size_t row_partial_floats = 0;
     int32_t *whole_staged = nullptr;   // staged plan of all rows beside that of the rows that are not dense
     size_t whole_staged_ints = 0;
@@ -931,14 +931,19 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         DenseRows &D = B.split.rows;
         D.list = t.dense_rows; D.n = n_dense; D.words = table_words(l);
         D.table = reinterpret_cast<const uint2 *>(B.row_table);
-        D.partial_floats = dense_rows_partial(D.n, cols, max_batch);
-        if (D.partial_floats > 0 && !reserve_optional(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(D.partial_floats))) D.partial_floats = 0;
-        D.partial = B.row_partial;
+        const DenseRowsRoom want = dense_rows_room(D.n, cols, max_batch);
+        const int64_t partial = round_up(want.partial_floats, 64);
+        if (partial + want.parts_ints > 0 && reserve_optional(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(partial + want.parts_ints))) {
+            D.partial = B.row_partial;
+            D.partial_floats = want.partial_floats;
+            D.parts = reinterpret_cast<uint32_t *>(B.row_partial + partial);
+            D.parts_ints = want.parts_ints;
+        }
         B.split.flag = t.dense_flag;
         B.split.others = out->plan;
         B.split.others.waves = t.other_waves;
         B.split.others.long_waves = t.other_long_waves;
-        B.split.from_batch = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? kDenseRowsMinBatch : dense_rows_from(R.plan[0].dense_nnz);
+        B.split.from_batch = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? kDenseRowsMinBatch : dense_rows_from(n_dense, R.plan[0].dense_nnz, cols);
         // The staged plan covers the other rows only.  Narrower batches, at which the dense rows are rows like any other, get one of
         // all rows where the widest of them that fills its tiles (staged_pays) has work-groups enough for it.
         out->plan.staged_rows = nullptr;

@@ -493,8 +493,6 @@ __global__ __launch_bounds__(kSampledWaves * kWave) void sampled_update_kernel(c
 // 3320 for all; at 3 %: 1787 -> 735.
 constexpr int kDrRows = 64, kDrK = 64, kDrALd = kDrK + 4;
 
-__host__ __device__ __forceinline__ int64_t dense_rows_ld(int32_t batch) { return (batch + 31) / 32 * 32; }
-
 __device__ __forceinline__ void dense_rows_store(const SpmmArgs &a, int row, int col, float4 y)
 {
     const float b = a.bias ? a.bias[row] : 0.f;
@@ -765,19 +763,21 @@ bool sddmm_sampled_ok(const SddmmArgs &a)
     return a.dense || static_cast<double>(a.nnz) >= from * a.rows * a.x_rows;
 }
 
-// How a product of n dense rows is cut: columns of the batch per work-group, slices of K.
+// How a product of n dense rows is cut: columns of the batch per work-group, slices of K; on the bf16 units (split_dense_rows_kernel) or the
+// fp32 ones.
 struct DenseRowsCut {
     int cols, slices;
     int64_t tiles;
+    bool split;
+    double time;
 };
-// The cheapest by an estimate: a compute unit holds 3 (4) work-groups of 128 (64) columns, which take 2.0 (1.1) us a step
+// The cheapest by an estimate.  fp32: a compute unit holds 3 (4) work-groups of 128 (64) columns, which take 2.0 (1.1) us a step
 // each when they keep its pipes busy together and 3.7 (2.6) alone; the slices' results go out and come back at 3.3 TB/s.
 // (Within 3 to 7 % of the best of 20 cuts on matrices of 1024 to 16384 rows at batches of 128 to 1024.)
-static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch)
+static DenseRowsCut dense_rows_fp32_cut(int32_t n, int32_t cols, int32_t batch)
 {
     const int64_t chunks = (static_cast<int64_t>(cols) + kDrK - 1) / kDrK;
     DenseRowsCut best{};
-    double best_time = 0.;
     for (int wide = 1; wide >= 0; --wide) {
         const int tile_cols = wide ? 128 : 64, fit = wide ? 3 : 4;
         const double alone = wide ? 3.7 : 2.6, step = wide ? 2. : 1.1;
@@ -786,36 +786,65 @@ static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch)
             const int64_t per_unit = (tiles * s + 255) / 256, full = per_unit / fit, left = per_unit % fit;
             const double rounds = full * std::max(alone, step * fit) + (left ? std::max(alone, step * left) : 0.);
             const double time = rounds * static_cast<double>((chunks + s - 1) / s) + (s > 1 ? 2. + 1.2e-6 * s * n * static_cast<double>(dense_rows_ld(batch)) : 0.);
-            if (best.tiles == 0 || time < best_time) {
-                best = DenseRowsCut{tile_cols, s, tiles};
-                best_time = time;
-            }
+            if (best.tiles == 0 || time < best.time) best = DenseRowsCut{tile_cols, s, tiles, false, time};
         }
     }
     return best;
 }
 
+// Split operands: one work-group per compute unit, 2.6 us per 32 columns of the matrix; before it the operand's parts are formed (10 bytes a number
+// at 4.5 TB/s), after it the slices are added.  Measured on matrices of 35 %, fp32 -> split, us: 2600 rows of 16384 at batch 1024 / 512 / 256 /
+// 128: 837 -> 498, 469 -> 259, 246 -> 136, 134 -> 131; 700 of 16384: 260 -> 185, 145 -> 98, 82 -> 65, 55 -> 64; 8192 of 4096: 654 -> 367, 350 -> 194,
+// 184 -> 107, 101 -> 106; 2600 of 4096: 253 -> 138, 135 -> 81, 72 -> 52, 44 -> 50; 700 of 4096 at 1024 / 512 / 256: 81 -> 59, 46 -> 43, 30 -> 39; 100 of
+// 16384 at 1024: 63 -> 76; 2600 of 1024 at 1024 / 256: 81 -> 55, 29 -> 35.  The fp32 estimate is low on these by a quarter and a launch.
+static DenseRowsCut dense_rows_split_cut(int32_t n, int32_t cols, int32_t batch)
+{
+    const int64_t chunks = (static_cast<int64_t>(cols) + 31) / 32, tiles = split_dense_rows_tiles(n, batch);
+    const double parts = 3. + 10. * cols * static_cast<double>(operand_parts_ld(batch)) / 4.5e6;
+    DenseRowsCut best{};
+    for (int s = 1; s == 1 || (s <= 64 && s * 4 <= chunks); ++s) {
+        if ((chunks + s - 1) / s > kSplitMaxChunks || chunks > 65535) continue;   // (65535: grid of the parts' launch)
+        const double time = 8. + parts + 2.6 * static_cast<double>((tiles * s + 255) / 256 * ((chunks + s - 1) / s)) +
+                            (s > 1 ? 3. + 8. * s * n * static_cast<double>(dense_rows_ld(batch)) / 4.5e6 : 0.);
+        if (best.tiles == 0 || time < best.time) best = DenseRowsCut{0, s, tiles, true, time};
+    }
+    return best;
+}
+
+static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch)
+{
+    const DenseRowsCut fp32 = dense_rows_fp32_cut(n, cols, batch), split = dense_rows_split_cut(n, cols, batch);
+    return split.tiles > 0 && split.time < 6. + 1.25 * fp32.time && operand_parts_ints(cols, batch) < (1ll << 29) ? split : fp32;
+}
+
 bool dense_rows_ok(const DenseSplit *d, int32_t batch) { return d && d->rows.n > 0 && batch >= d->from_batch; }
 
-int64_t dense_rows_partial(int32_t n, int32_t cols, int32_t max_batch)
+DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch)
 {
-    int64_t most = 0;
+    DenseRowsRoom room{0, 0};
     for (int64_t c = 64; c - 64 < max_batch; c += 64) {
         const int32_t batch = static_cast<int32_t>(c < max_batch ? c : max_batch);
         const DenseRowsCut cut = dense_rows_cut(n, cols, batch);
-        if (cut.slices > 1) most = std::max(most, static_cast<int64_t>(cut.slices) * n * dense_rows_ld(batch));
+        if (cut.slices > 1) room.partial_floats = std::max(room.partial_floats, static_cast<int64_t>(cut.slices) * n * dense_rows_ld(batch));
+        if (cut.split) room.parts_ints = std::max(room.parts_ints, operand_parts_ints(cols, batch));
     }
-    return std::min<int64_t>(most, 1ll << 28);   // (what does not fit is not sliced)
+    room.partial_floats = std::min<int64_t>(room.partial_floats, 1ll << 28);   // (what does not fit is not sliced)
+    return room;
 }
 
 hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s)
 {
     const DenseRows &D = a.split->rows;
-    const DenseRowsCut cut = dense_rows_cut(D.n, a.x_rows, a.batch);
-    int slices = cut.slices;
-    if (static_cast<int64_t>(slices) * D.n * dense_rows_ld(a.batch) > D.partial_floats) slices = 1;
+    DenseRowsCut cut = dense_rows_cut(D.n, a.x_rows, a.batch);
+    auto fits = [&] { return static_cast<int64_t>(cut.slices) * D.n * dense_rows_ld(a.batch) <= D.partial_floats; };
+    // (a batch between those that the buffers were sized for may be cut finer than they are)
+    if (cut.split && (operand_parts_ints(a.x_rows, a.batch) > D.parts_ints || (cut.slices > 1 && !fits()))) cut = dense_rows_fp32_cut(D.n, a.x_rows, a.batch);
+    if (cut.slices > 1 && !fits()) cut.slices = 1;
+    const int slices = cut.slices;
     const dim3 grid(static_cast<unsigned>(cut.tiles * slices));
-    if (cut.cols == 128)
+    if (cut.split)
+        launch_split_dense_rows(a, D, slices, s);
+    else if (cut.cols == 128)
         hipLaunchKernelGGL(dense_rows_kernel<4>, grid, dim3(kDenseBlock), 0, s, a, D, slices);
     else
         hipLaunchKernelGGL(dense_rows_kernel<2>, grid, dim3(kDenseBlock), 0, s, a, D, slices);

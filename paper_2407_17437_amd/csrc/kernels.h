@@ -86,6 +86,8 @@ struct DenseRows {
     int32_t n, words;
     float *partial;                // results of the slices of K, partial_floats long
     int64_t partial_floats;
+    uint32_t *parts;               // parts of the operand for the product on the bf16 units, parts_ints long (operand_parts_ints)
+    int64_t parts_ints;
 };
 // A matrix some of whose rows are served that way, from `from_batch` columns on: those, and the partition without them that the
 // others then run on.  Host memory.
@@ -99,11 +101,18 @@ constexpr int32_t kDenseRowsMinCols = 1024;    // (so that a dense row is longer
 constexpr int32_t kDenseRowsMin = 17;          // fewer rows than this stay with the others
 constexpr int64_t kDenseRowsMinWork = 192 << 20;  // entries times columns of the batch from which the extra launch pays
 constexpr int32_t kDenseRowsMinBatch = 128;    // (narrower ones leave much of a tile of 64 or 128 columns idle)
+// Rows that together store less than 30 % of their columns pay on the bf16 units alone (split.hip), that is for many rows of many columns and
+// wide batches: uniform 25 %, gathered -> split, us: 2600 x 16384 at batch 1024 / 512 / 256: 738 -> 500, 481 -> 259, 530 -> 136 (break even at 17, 14,
+// 7 %); 8192 x 4096: 598 -> 367, 308 -> 194, 170 -> 107 (15, 16, 16 %); 700 x 4096 at 1024 / 512 / 256: 113 -> 59, 60 -> 43, 31 -> 39; 2600 x 1024 at 1024: 55 -> 55.
+constexpr int32_t kDenseRowsThinMin = 512, kDenseRowsThinCols = 2048, kDenseRowsThinBatch = 192, kDenseRowsThinPercent = 17;
+constexpr int64_t kDenseRowsThinWork = 384 << 20;
+__host__ __device__ inline bool dense_rows_thin(int32_t n, int64_t dense_nnz, int32_t cols) { return dense_nnz * 10 < static_cast<int64_t>(n) * cols * 3; }
 // the batch from which the listed rows have that much work
-__host__ __device__ inline int32_t dense_rows_from(int64_t dense_nnz)
+__host__ __device__ inline int32_t dense_rows_from(int32_t n, int64_t dense_nnz, int32_t cols)
 {
-    const int64_t b = (kDenseRowsMinWork + dense_nnz - 1) / dense_nnz;
-    return b > kDenseRowsMinBatch ? static_cast<int32_t>(b) : kDenseRowsMinBatch;
+    const bool thin = dense_rows_thin(n, dense_nnz, cols);
+    const int64_t b = ((thin ? kDenseRowsThinWork : kDenseRowsMinWork) + dense_nnz - 1) / dense_nnz, least = thin ? kDenseRowsThinBatch : kDenseRowsMinBatch;
+    return static_cast<int32_t>(b > least ? b : least);
 }
 // Stored entries from which a row counts as dense: an eighth of its columns.  At batch 1024 such a row costs the matrix units
 // 0.30 us per 16384 columns and the staged kernel 2.0 us times its density among power-law rows.
@@ -330,11 +339,27 @@ bool sddmm_sampled_ok(const SddmmArgs &a);
 bool sddmm_sampled_possible(const SddmmArgs &a);
 void add_sampled(SampledArgs &list, const SddmmArgs &a);
 hipError_t launch_sampled(SampledArgs &a, hipStream_t s);
-// Y = act(W X + b) of a matrix's dense rows, and how many floats of DenseRows::partial that takes at up to max_batch columns
+// Y = act(W X + b) of a matrix's dense rows, and the room in DenseRows that takes at up to max_batch columns
 bool dense_rows_ok(const DenseSplit *d, int32_t batch);
 bool sampled_operands_ok(const SddmmArgs &a);
 hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s);
-int64_t dense_rows_partial(int32_t n, int32_t cols, int32_t max_batch);
+__host__ __device__ inline int64_t dense_rows_ld(int32_t batch) { return (batch + 31) / 32 * 32; }
+// The same on the bf16 matrix units, every fp32 number as three bf16 ones (split.hip): work-groups, most chunks of 32 columns of the matrix in one
+// of them, and the operand's parts: 12 ints per 8 rows and column, columns rounded up to whole work-groups, and a flag per 32 rows
+// and work-group's columns.
+int64_t split_dense_rows_tiles(int32_t n, int32_t batch);
+void launch_split_dense_rows(const SpmmArgs &a, const DenseRows &D, int slices, hipStream_t s);
+constexpr int32_t kSplitMaxChunks = 2048, kSplitCols = 256;
+__host__ __device__ inline int64_t operand_parts_ld(int32_t batch) { return (batch + kSplitCols - 1) / kSplitCols * kSplitCols; }
+__host__ __device__ inline int64_t operand_parts_ints(int32_t rows, int32_t batch)
+{
+    const int64_t groups = (static_cast<int64_t>(rows) + 31) / 32;
+    return groups * 48 * operand_parts_ld(batch) + groups * (operand_parts_ld(batch) / kSplitCols);
+}
+struct DenseRowsRoom {
+    int64_t partial_floats, parts_ints;
+};
+DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch);
 void add_sampled_rows(SampledArgs &list, const SddmmArgs &a);
 // status: result of the pattern check (the launch does nothing where it is not 0), or nullptr
 // list: the rows (or nullptr: 0 .. rows - 1)
@@ -455,11 +480,12 @@ __host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols
 }
 // Whether the listed rows are worth a route of their own at max_batch columns (narrower calls ask again: dense_rows_ok).  Start -> with it, forward product: power-law 4096^2 at 5 % (297 rows,
 // 0.53 M entries) at batch 256 / 512 / 1024: 48 -> 50, 81 -> 77, 129 -> 120 us; 8192 x 1024 at 10 %: 35 -> 36, 87 -> 51, 109 -> 82.
-// Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even at 30 % (324 us; 20 %: 235 -> 326).
+// Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even with the fp32 units at 30 % (324 us; 20 %: 235 -> 326).
 __host__ __device__ inline bool dense_rows_pay(int32_t n_dense, int64_t dense_nnz, int64_t nnz, int32_t cols, int32_t max_batch)
 {
-    return n_dense >= kDenseRowsMin && dense_nnz * 8 >= nnz && dense_nnz * 10 >= static_cast<int64_t>(n_dense) * cols * 3 &&
-           max_batch >= dense_rows_from(dense_nnz);
+    if (n_dense < kDenseRowsMin || dense_nnz * 8 < nnz || max_batch < dense_rows_from(n_dense, dense_nnz, cols)) return false;
+    return !dense_rows_thin(n_dense, dense_nnz, cols) ||
+           (n_dense >= kDenseRowsThinMin && cols >= kDenseRowsThinCols && dense_nnz * 100 >= static_cast<int64_t>(n_dense) * cols * kDenseRowsThinPercent);
 }
 // which of `want` equal shares of the total cost a row falls into that has `done` of it before it
 __host__ __device__ inline int32_t staged_cut(int64_t done, int32_t want, int64_t total)

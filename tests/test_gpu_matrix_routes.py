@@ -114,6 +114,63 @@ def test_dense_rows_keep_a_non_finite_operand_row_to_the_rows_that_read_it(nb, o
     L.close()
 
 
+SPLIT_SHAPES = [   # rows, columns, dense rows, their density, batch, leading dimension, ReLU: on the bf16 units (test_host_memory)
+    (2500, 1057, 1030, 0.6, 1024, None, True),    # a row tile of six rows, a last chunk of one column, slices, short rows besides
+    (5000, 1030, 5000, 0.36, 193, 193, False),     # nothing but dense rows; a column tile of 193 of 256 columns
+    (1400, 2310, 1281, 0.42, 771, 773, False),     # row and column tiles of one row and of three columns
+    (4000, 1060, 4000, 0.35, 2000, None, True),   # as many tiles as compute units: no slices
+]
+
+
+@pytest.mark.usefixtures("dense_rows_at_any_batch")
+@pytest.mark.parametrize("rows,cols,n_dense,density,batch,ld,relu", SPLIT_SHAPES)
+def test_dense_rows_on_the_bf16_units(nb, oracle, rows, cols, n_dense, density, batch, ld, relu):
+    check_layer(nb, oracle, mixed_rows(rows, cols, n_dense, density, rows + cols, relu), batch, ld=ld, backward=False)
+
+
+@pytest.mark.usefixtures("dense_rows_at_any_batch")
+def test_dense_rows_on_the_bf16_units_with_infinities(nb, oracle):
+    """Numbers that are not finite, or that round to an infinity in bf16, in the operand and among the weights: entries that are
+    not stored do not meet them, and what is stored gives what fp32 gives."""
+    import torch
+    lay, batch = mixed_rows(2500, 1057, 1030, 0.6, 3), 1024
+    X = np.random.default_rng(4).standard_normal((lay.cols, batch)).astype(np.float32)
+    X[(0, 31, 32, 700, 1056), :] = np.array([np.inf, -np.inf, 3.4e38, np.nan, np.inf], np.float32)[:, None]
+    X[500, 77] = np.inf
+    dense = np.flatnonzero(np.diff(lay.indptr) > 500)
+    for row, v in zip(dense[[0, 5, 200, 1029]], (np.inf, np.nan, -3.4e38, -np.inf)):
+        lay.values[(lay.indptr[row] + lay.indptr[row + 1]) // 2] = v
+    L = nb.SparseLinear(lay, max_batch=batch)
+    Yd = nb.dense(lay.rows, batch)
+    nb.sparse_linear_forward(L.handle, nb.to_dense(X), Yd, batch)
+    torch.cuda.synchronize()
+    Y = Yd.cpu().numpy()
+    with np.errstate(all="ignore"):
+        for row in range(lay.rows):
+            at = slice(lay.indptr[row], lay.indptr[row + 1])
+            terms = lay.values[at, None].astype(np.float64) * X[lay.indices[at]]
+            terms = np.where(np.abs(terms) > np.finfo(np.float32).max, np.sign(terms) * np.inf, terms)
+            ref, S = terms.sum(0) + lay.bias[row], np.abs(terms).sum(0) + abs(lay.bias[row])
+            large = S > 1e37   # (sums of numbers near the end of the range may pass it in one order and not in another)
+            fine = np.isfinite(S) & ~large
+            np.testing.assert_allclose(Y[row, fine], ref[fine], rtol=0, atol=float((1e-5 * S[fine]).max(initial=0.0)))
+            assert not np.isfinite(Y[row, ~np.isfinite(S)]).any(), row
+            gone = np.isnan(ref) & ~large
+            assert np.isnan(Y[row, gone]).all(), row
+    assert np.isfinite(Y).any() and not np.isfinite(Y).all()
+    L.close()
+
+
+def test_uniform_rows_on_the_bf16_units(nb, oracle):
+    """20 % of 2100 columns: gathered up to 461 columns of the batch, on the bf16 units from there on (and bound for 600)."""
+    rng = np.random.default_rng(12)
+    indptr, indices = wl.pattern_from_row_nnz(rng.integers(390, 450, 2050), 2100, seed=9)
+    lay = wl.SparseLayerData(2050, 2100, indptr, indices, wl.init_values(indptr, 7), rng.standard_normal(2050).astype(np.float32), True)
+    for batch in (300, 600):
+        check_layer(nb, oracle, lay, batch, max_batch=600)
+
+
+
 def test_huge_rows_after_products_that_overlapped(nb, oracle):
     """Products of one layer on several streams at once may spoil one another (their results are not looked at), but no product
     that is ordered after them: the shares of its huge rows are counted from 0 again, in both orientations."""

@@ -103,6 +103,22 @@ def dense_rows_go_apart_by_the_batch_of_the_call(L):
         L.destroy()
 
 
+def wide_products_of_dense_rows_take_the_bf16_units(L):
+    """By the estimates of both; a narrow batch of the same layer, and few rows, stay on the fp32 ones."""
+    for rows, cols, n, nnz, batch, split in ((2500, 1057, 1030, 653000, 1024, True), (5000, 1030, 5000, 1854000, 193, True), (1400, 2310, 1281, 1243000, 771, True),
+                                            (4000, 1060, 4000, 1484000, 2000, True), (2500, 1057, 1030, 653000, 322, False), (3000, 16384, 205, 1680000, 1024, False)):
+        for max_batch in (batch, 2048):
+            L.counts(0, n_blocks=600, n_dense=n, dense_nnz=nnz, longest_row=2000)
+            L.counts(1, n_blocks=600, longest_row=2000)
+            assert L.create(rows, cols, nnz + 9000, max_batch) == 0
+            L.launched()
+            assert L.forward(batch) == 0
+            launched = L.launched()
+            assert any("split_dense_rows_kernel" in k for k in launched) == split, (rows, cols, batch, launched)
+            assert any("dense_rows_kernel" in k for k in launched)
+            L.destroy()
+
+
 def a_layer_is_created_without_what_it_can_do_without(L):
     """Dense rows with sliced results, a staged plan for the batches below theirs, partial products, dZ of a ReLU layer: each of them
     fails once.  (The calls fail one after another; those whose failure the create survives are these.)"""
@@ -140,7 +156,7 @@ def a_single_tile_needs_no_partial_products(L):
     assert held[1] - held[0] == 1024 * (128 - 64) * 4, held   # (dZ, whose rows are 128 and 64 columns apart)
 
 
-CASES = [a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
