@@ -1600,7 +1600,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
     }
 
     if (fused) {
-        // Launch order T_{n-1} | T_{n-2} + S_{n-1} | ... | T_1 + S_2 | S_1 + S_0: the fused
+        // Launch order T_{n-1} | T_{n-2} + S_{n-1} | ... | T_1 + S_2 | S_1 + S_0 (the last two as one where chain_ok): the fused
         // SDDMM+update S_l of a layer shares a grid with the transposed product of the layer
         // below, which no longer depends on it (S_l only needs dZ_l and must follow T_l).
         // dZ_{l-1} through the dense copy of layer l's weights
@@ -1639,6 +1639,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
             return NERVA_OK;
         };
         if (head) pending = n - 1;  // the head launch has run T_{n-1}
+        bool chained = false;       // S_0 has run
         for (int l = head ? n - 2 : n - 1; l >= 1; --l) {
             // dZ_l is ready: T_l (which hands dZ_{l-1} down) and S_l
             const SpmmArgs t = make_T(l);
@@ -1650,6 +1651,19 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 continue;
             }
             const SddmmArgs g_same = make_S(l);
+            if (l == 1 && !use_dense(mlp->layers[0], batch) && chain_ok(t, g_same, make_S(0))) {
+                // the rest of the step in one launch
+                const SddmmArgs g0 = make_S(0);
+                SddmmArgs waiting{};
+                if (pending >= 0) waiting = make_S(pending);
+                const bool along = pending >= 0 && can_pair(g0, waiting);
+                if (pending >= 0 && !along && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
+                Timed tm(mlp->prof, s, "backward_chain", 1);
+                HIP_TRY(launch_chain(t, g_same, g0, along ? &waiting : nullptr, s));
+                pending = -1;
+                chained = true;
+                continue;
+            }
             if (full_backward_ok(t, g_same)) {
                 if (pending >= 0 && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
                 pending = -1;
@@ -1686,7 +1700,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
             pending = l;
         }
         // the first layer has no transposed product: its S, with the one still pending if any
-        if (pending >= 0) {
+        if (!chained && pending >= 0) {
             const SddmmArgs gp = make_S(pending), g0 = make_S(0);
             if (pending == 1 && can_pair(g0, gp)) {
                 Timed tm(mlp->prof, s, "sddmm_update+sddmm_update", 0);
@@ -1695,7 +1709,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 if ((rc = run_S_alone(pending)) != NERVA_OK) return rc;
                 if (pending != 0 && (rc = run_S_alone(0)) != NERVA_OK) return rc;
             }
-        } else if ((rc = run_S_alone(0)) != NERVA_OK) {
+        } else if (!chained && (rc = run_S_alone(0)) != NERVA_OK) {
             return rc;
         }
         if ((rc = flush_sampled()) != NERVA_OK) return rc;
@@ -1708,7 +1722,10 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                     HIP_TRY(dense_transposed(ly, dZ(l), L.ld, dZ(l - 1), L.ld, A(l - 1), L.ld, batch, s));
                 } else {
                     Timed tm(mlp->prof, s, "spmm_transposed", l);
-                    HIP_TRY(launch_spmm(make_T(l), s));
+                    if (l == 1 && !use_dense(mlp->layers[0], batch) && chain_shape_ok(make_T(1), make_S(1), make_S(0)))
+                        HIP_TRY(launch_chain_transposed(make_T(1), make_S(1), make_S(0), s));
+                    else
+                        HIP_TRY(launch_spmm(make_T(l), s));
                 }
             }
             const SddmmArgs g = make_S(l);

@@ -270,6 +270,23 @@ hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream
 bool can_pair(const SpmmArgs &a, const SddmmArgs &b);
 bool can_pair(const SddmmArgs &a, const SddmmArgs &b);
 hipError_t launch_pair(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s);
+// The end of a training step in one launch (chain_kernel): T_1, S_1 and S_0, and the SDDMM of a layer above that waits for its update (or nullptr;
+// can_pair(g0, it)).
+struct ChainArgs {
+    const int32_t *indptr_t, *indices_t, *perm;   // W_1's mirror
+    float *values_t, *w, *velocity;               // its values, W_1's values[] and velocity[]
+    float *bias, *bias_velocity;                  // of W_1
+    const float *dZ, *A;                          // dZ_1 and A_0
+    float *dZ_below;                              // dZ_0
+    int64_t lddz, lda, lddz_below;
+    int32_t rows;                                 // of dZ_1
+};
+constexpr int32_t kChainMinRows = 256, kChainMaxBatch = 192;
+// chain_shape_ok: the part that does not depend on whether the updates are fused; then a step that keeps its launches apart forms dZ_0 in the same order.
+bool chain_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0);
+bool chain_shape_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0);
+hipError_t launch_chain_transposed(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, hipStream_t s);
+hipError_t launch_chain(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, const SddmmArgs *waiting, hipStream_t s);
 hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s);
 
 hipError_t launch_momentum(float *w, float *v, const float *g, int64_t n, float lr, float mu, int nesterov,

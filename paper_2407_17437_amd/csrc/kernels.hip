@@ -1142,46 +1142,16 @@ __device__ __forceinline__ float sddmm_own_columns(gmem_ptr Xg, int iters, int m
     return res;
 }
 
-// col0: first column of the pass, which covers G*4*NV columns of the batch.
+// The wave's entries of a row whose dZ it holds (off: where its columns lie), and the row's sum where it leads.
 template <int G, int NV, bool SPARE>
-__device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, const int col0 = 0)
+__device__ __forceinline__ void sddmm_row(const SddmmArgs &a, const WaveTask &task, const int col0, const uint32_t (&off)[NV], const float4 (&dz)[NV])
 {
     constexpr int NG = kWave / G;
     constexpr int UI = NV >= 3 ? 2 : (NV == 2 ? 4 : 8);   // 32 registers of gathered data: two 16-wave work-groups fit a compute unit
     const int lane = threadIdx.x & (kWave - 1);
-    mean_loss_task(a, block);
-    const WaveTask task = wave_task(a.blocks, block);
-    if (task.row < 0) return;
     const int row = task.row;
     const int grp = lane / G;
     const int lig = lane % G;
-
-    // the row of dZ: all its loads together, whole waves (lanes beyond the batch re-read columns of the pass and are zeroed)
-    float4 dz[NV];
-    uint32_t off[NV];
-    {
-        const gmem_ptr zr = as_gmem(a.dZ + static_cast<int64_t>(row) * a.lddz);
-#pragma unroll
-        for (int t = 0; t < NV; ++t) {
-            const int own = col0 + (t * G + lig) * 4;
-            off[t] = static_cast<uint32_t>(four_columns(own < a.batch ? own : col0, a.batch)) * 4u;
-            dz[t] = gload4(zr, off[t]);
-        }
-        if (a.ZM) {
-            const gmem_ptr zm = as_gmem(a.ZM + static_cast<int64_t>(row) * a.ldzm);
-            float4 m[NV];
-#pragma unroll
-            for (int t = 0; t < NV; ++t) m[t] = gload4(zm, off[t]);
-#pragma unroll
-            for (int t = 0; t < NV; ++t) dz[t] = keep_where_positive(dz[t], m[t]);
-        }
-#pragma unroll
-        for (int t = 0; t < NV; ++t) {
-            const int own = col0 + (t * G + lig) * 4;
-            dz[t] = own < a.batch ? drop_shared(dz[t], own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    }
-
     if (task.lead && (a.db || (a.fused && a.bias))) {
         float s = 0.f;
 #pragma unroll
@@ -1242,6 +1212,46 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, 
             }
         }
     }
+}
+
+// col0: first column of the pass, which covers G*4*NV columns of the batch.
+template <int G, int NV, bool SPARE>
+__device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, const int col0 = 0)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    mean_loss_task(a, block);
+    const WaveTask task = wave_task(a.blocks, block);
+    if (task.row < 0) return;
+    const int row = task.row;
+    const int lig = lane % G;
+
+    // the row of dZ: all its loads together, whole waves (lanes beyond the batch re-read columns of the pass and are zeroed)
+    float4 dz[NV];
+    uint32_t off[NV];
+    {
+        const gmem_ptr zr = as_gmem(a.dZ + static_cast<int64_t>(row) * a.lddz);
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int own = col0 + (t * G + lig) * 4;
+            off[t] = static_cast<uint32_t>(four_columns(own < a.batch ? own : col0, a.batch)) * 4u;
+            dz[t] = gload4(zr, off[t]);
+        }
+        if (a.ZM) {
+            const gmem_ptr zm = as_gmem(a.ZM + static_cast<int64_t>(row) * a.ldzm);
+            float4 m[NV];
+#pragma unroll
+            for (int t = 0; t < NV; ++t) m[t] = gload4(zm, off[t]);
+#pragma unroll
+            for (int t = 0; t < NV; ++t) dz[t] = keep_where_positive(dz[t], m[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int own = col0 + (t * G + lig) * 4;
+            dz[t] = own < a.batch ? drop_shared(dz[t], own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+
+    sddmm_row<G, NV, SPARE>(a, task, col0, off, dz);
 }
 
 template <int G, int NV, bool SPARE>
@@ -1912,6 +1922,199 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
     if (!(a.db || (a.fused && a.bias))) return;
     backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_entry_blocks) * (kEwBlock / kWave) + wave_in_block(),
                       static_cast<int64_t>(gridDim.x - n_entry_blocks) * (kEwBlock / kWave));
+}
+
+// ---- the end of a training step in one launch ----------------------------------------------------
+// Row j of dZ_0 = (W_1^T dZ_1) * [A_0 > 0] takes the mirror row j of W_1 only, and row j of W_0's gradient takes that row of dZ_0
+// only: the waves that serve row j of W_0 (its partition) form dZ_0[j, :] from their shares of the mirror row, each gathered row of
+// dZ_1 giving the products of W_1's gradient as well (as in backward_fused_kernel; a mirror entry is read and updated by one wave), add them up in LDS, and
+// go on to the entries of W_0.  After them in the grid: the waves that sum the rows of dZ_1 for W_1's biases, and, where a layer above still waits for its
+// update, that (sddmm_body).
+// What bounds it: the chain of memory round trips of its two halves; what it saves is a launch and the way of dZ_0 through
+// memory.  Steps of 3072-1024-512-10 at batch 100, 99 / 90 %: 23.2 -> 21.7 and 38.4 -> 34.6 us, 3001-1501-777-10 at
+// 5 %, batch 77: 39.0 -> 36.5; the launch 8.9 / 17.1 us, the two before 4.6 + 5.9 and 5.9 + 15.5.  (The column indices of the second half asked for
+// ahead, and the mask kept: 21.6, 34.9 and 37.7.)
+template <int G, int NV, int U, bool WHOLE>
+__device__ __forceinline__ void chain_pass(gmem_ptr Zg, int it0, int my_ro, float my_w, const uint32_t (&off)[NV], const float4 (&ax)[NV], float4 (&acc)[NV],
+                                           float &res)
+{
+    const int lane = threadIdx.x & (kWave - 1), lig = lane % G;
+    uint32_t ro[U];
+    float w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int src = ((lane / G) * G + it0 + u) * 4;
+        ro[u] = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, my_ro));
+        w[u] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(src, __builtin_bit_cast(int, my_w)));
+    }
+    float4 z[U][NV];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < NV; ++t) z[u][t] = gload4(Zg, ro[u] + off[t]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        float part = 0.f;
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            if constexpr (WHOLE) {
+                part = fmaf(ax[t].x, z[u][t].x, part);
+                part = fmaf(ax[t].y, z[u][t].y, part);
+                part = fmaf(ax[t].z, z[u][t].z, part);
+                part = fmaf(ax[t].w, z[u][t].w, part);
+            }
+            acc[t].x = fmaf(w[u], z[u][t].x, acc[t].x);
+            acc[t].y = fmaf(w[u], z[u][t].y, acc[t].y);
+            acc[t].z = fmaf(w[u], z[u][t].z, acc[t].z);
+            acc[t].w = fmaf(w[u], z[u][t].w, acc[t].w);
+        }
+        if constexpr (WHOLE) {
+            part = group_sum<G>(part);
+            if (lig == it0 + u) res = part;
+        }
+    }
+}
+
+template <int G, int NV, bool SPARE, bool WHOLE>
+__device__ __forceinline__ void chain_body(const ChainArgs &c, const SddmmArgs &a, const int block)
+{
+    constexpr int NG = kWave / G;
+    constexpr int UI = NV >= 3 ? 1 : (NV == 2 ? 2 : 4);
+    __shared__ float4 red[kWavesPerBlock][NV][G];
+    const int lane = threadIdx.x & (kWave - 1), wv = wave_in_block(), grp = lane / G, lig = lane % G;
+    const WaveTask task = wave_task(a.blocks, block);
+    const int row = task.row;
+    uint32_t off[NV];
+    float4 acc[NV];
+    const gmem_ptr ar = as_gmem(c.A + static_cast<int64_t>(max(row, 0)) * c.lda);
+#pragma unroll
+    for (int t = 0; t < NV; ++t) {
+        const int own = (t * G + lig) * 4;
+        off[t] = static_cast<uint32_t>(four_columns(own < a.batch ? own : 0, a.batch)) * 4u;
+        acc[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (row >= 0) {
+        float4 ax[NV];
+#pragma unroll
+        for (int t = 0; t < NV; ++t) ax[t] = gload4(ar, off[t]);
+        int q0 = c.indptr_t[row], q1 = c.indptr_t[row + 1];
+        const int share = (q1 - q0 + (1 << task.lg) - 1) >> task.lg;
+        q0 = min(q0 + task.part * share, q1);
+        q1 = min(q0 + share, q1);
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int own = (t * G + lig) * 4;
+            ax[t] = own < a.batch ? drop_shared(ax[t], own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        const uint32_t ldzb = static_cast<uint32_t>(c.lddz) * 4u;
+        const gmem_ptr Zg = as_gmem(c.dZ);
+        const int q_mine = lig * NG + grp;  // slot of this lane inside a chunk of 64 entries, as in sddmm_row
+        const bool spare = SPARE && G * 4 * NV > a.batch;  // uniform
+        for (int pc = q0; pc < q1; pc += kWave) {
+            const int n = min(kWave, q1 - pc);
+            const bool mine = q_mine < n;
+            const int p = pc + (mine ? q_mine : 0);
+            const int my_i = c.indices_t[p];
+            float w = c.values_t[p], v = 0.f;
+            int at = 0;
+            if constexpr (WHOLE) {
+                at = c.perm[p];
+                v = c.velocity[at];
+            }
+            const int my_ro = static_cast<int>(static_cast<uint32_t>(my_i) * ldzb);
+            const float my_w = mine ? w : 0.f;
+            const int iters = (n + NG - 1) / NG;
+            float res = 0.f;
+            int it = 0;
+            for (; it + UI <= iters; it += UI) chain_pass<G, NV, UI, WHOLE>(Zg, it, my_ro, my_w, off, ax, acc, res);
+            if constexpr (UI >= 4)
+                if (it + 2 <= iters) { chain_pass<G, NV, 2, WHOLE>(Zg, it, my_ro, my_w, off, ax, acc, res); it += 2; }
+            if constexpr (UI >= 2)
+                if (it < iters) chain_pass<G, NV, 1, WHOLE>(Zg, it, my_ro, my_w, off, ax, acc, res);
+            if constexpr (!WHOLE) continue;
+            if (spare && __any(res != res)) res = sddmm_own_columns<G, NV>(Zg, iters, my_ro, off, ax, 0, a.batch);
+            if (mine) {
+                momentum_step(w, v, res, a.lr, a.momentum, a.nesterov);
+                c.w[at] = w;
+                c.velocity[at] = v;
+                c.values_t[p] = w;
+            }
+        }
+    }
+    // the groups' sums, then the waves', each in one fixed order
+#pragma unroll
+    for (int d = G; d < kWave; d <<= 1)
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            acc[t].x += __shfl_xor(acc[t].x, d, kWave);
+            acc[t].y += __shfl_xor(acc[t].y, d, kWave);
+            acc[t].z += __shfl_xor(acc[t].z, d, kWave);
+            acc[t].w += __shfl_xor(acc[t].w, d, kWave);
+        }
+    if (task.lg > 0) {   // uniform over the work-group
+        if (grp == 0)
+#pragma unroll
+            for (int t = 0; t < NV; ++t) red[wv][t][lig] = acc[t];
+        __syncthreads();
+        const int first = wv - task.part;
+#pragma unroll
+        for (int t = 0; t < NV; ++t) acc[t] = red[first][t][lig];
+        for (int s = 1; s < (1 << task.lg); ++s)
+#pragma unroll
+            for (int t = 0; t < NV; ++t) {
+                const float4 r = red[first + s][t][lig];
+                acc[t].x += r.x; acc[t].y += r.y; acc[t].z += r.z; acc[t].w += r.w;
+            }
+    }
+    if (row < 0) return;
+    float4 dz[NV];
+#pragma unroll
+    for (int t = 0; t < NV; ++t) {
+        const int own = (t * G + lig) * 4;
+        const float4 y = keep_where_positive(acc[t], gload4(ar, off[t]));   // (read again: registers)
+        if (task.part == 0 && grp == 0 && own < a.batch) st4(c.dZ_below + static_cast<int64_t>(row) * c.lddz_below + (off[t] >> 2), y);
+        dz[t] = own < a.batch ? drop_shared(y, own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if constexpr (WHOLE) sddmm_row<G, NV, SPARE>(a, task, 0, off, dz);
+}
+
+// Biases of W_1: a group of lanes per row of dZ_1, added up as sddmm_row does.
+template <int G, int NV>
+__device__ __forceinline__ void chain_row_sums(const ChainArgs &c, const SddmmArgs &a, const int block)
+{
+    const int lane = threadIdx.x & (kWave - 1), lig = lane % G, i = (block * kWavesPerBlock + wave_in_block()) * (kWave / G) + lane / G;
+    const float *zr = c.dZ + static_cast<int64_t>(min(i, c.rows - 1)) * c.lddz;
+    float s = 0.f;
+#pragma unroll
+    for (int t = 0; t < NV; ++t) {
+        const int own = (t * G + lig) * 4, first = four_columns(own < a.batch ? own : 0, a.batch);
+        float4 z = ld4(zr + first);
+        z = own < a.batch ? drop_shared(z, own, first) : make_float4(0.f, 0.f, 0.f, 0.f);
+        s += (z.x + z.y) + (z.z + z.w);
+    }
+    s = group_sum<G>(s);
+    if (lig != 0 || i >= c.rows) return;
+    float w = c.bias[i], v = c.bias_velocity[i];
+    momentum_step(w, v, s, a.lr, a.momentum, a.nesterov);
+    c.bias[i] = w;
+    c.bias_velocity[i] = v;
+}
+
+template <int G, int NV, bool SPARE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void chain_kernel(const ChainArgs c, const SddmmArgs a, const SddmmArgs b, const int n_sum_blocks)
+{
+    int block = blockIdx.x;
+    if (block < a.blocks.n_blocks) return chain_body<G, NV, SPARE, true>(c, a, block);
+    block -= a.blocks.n_blocks;
+    if (block < n_sum_blocks) return chain_row_sums<G, NV>(c, a, block);
+    sddmm_body<G, NV, SPARE>(b, block - n_sum_blocks);
+}
+
+// Its first half alone, dZ_0: for a step whose launches are kept apart, so that both form the same sums.
+template <int G, int NV>
+__global__ __launch_bounds__(kBlock) void chain_transposed_kernel(const ChainArgs c, const SddmmArgs a)
+{
+    chain_body<G, NV, false, false>(c, a, blockIdx.x);
 }
 
 // Two independent launches of a training step in one grid: work-groups [0, na) run the first,
@@ -2773,6 +2976,60 @@ hipError_t launch_pair(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
 hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 {
     return with_sddmm_lanes(a.batch, [&](auto g, auto nv) { return sddmm_pair_go<decltype(g)::value, decltype(nv)::value>(a, b, s); });
+}
+
+// Whether T_1 (t), S_1 (g1) and S_0 (g0) of a step can be one launch (chain_kernel): all three untiled, T_1's operand and mask those of S_1, its result
+// that of S_0, no row of W_0 cut into several work-groups.  The waves of a row are those that W_0's partition gives it: the mirror must not be much the larger of the
+// two or have long rows.  Steps at batch 100 apart / in one, us: 500-1000-1000-10 at 10 % (twice W_0's entries) 34.3 / 29.8, 300-1000-1000-10 (three times)
+// 33.6 / 29.2; 3000-3000-3000-10 at 2 %, batch 128 (as many) 54.9 / 54.6.  Up to 192 columns: with four loads per row and lane the registers
+// do not suffice (2000-1500-400-10 at 5 %, batch 180 / 256: 37.2 / 34.4, 41.3 / 43.6).  Networks of a small hidden layer keep their two launches, which a
+// profile of the step shows one by one (256-128-64-10 at 20 %: 20.9 / 18.6).
+bool chain_shape_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
+{
+    if (t.batch != g1.batch || t.batch > kChainMaxBatch || t.X != g1.dZ || t.ldx != g1.lddz || !t.YM || t.YM != g1.X || t.ldym != g1.ldx || t.Y != g0.dZ || t.ldy != g0.lddz) return false;
+    if (!can_pair(t, g0) || !can_pair(t, g1) || t.nnz <= 0 || t.nnz != g1.nnz || t.rows != g0.rows) return false;
+    if (g1.dense || g0.dense || g1.loss_cols || g0.loss_cols || g0.values_t || g0.ZM || g1.ZM) return false;
+    return g0.blocks.n_huge_rows == 0 && t.rows >= kChainMinRows && t.blocks.staged_longest_row <= 2 * kPackMaxLen && t.nnz / 4 <= g0.nnz;
+}
+bool chain_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
+{
+    return g0.fused && g1.fused && g1.perm && g1.values_t && chain_shape_ok(t, g1, g0);
+}
+
+static ChainArgs chain_args(const SpmmArgs &t, const SddmmArgs &g1)
+{
+    ChainArgs c{};
+    c.indptr_t = t.indptr; c.indices_t = t.indices; c.values_t = const_cast<float *>(t.values); c.perm = g1.perm; c.w = g1.values; c.velocity = g1.velocity;
+    c.bias = g1.bias; c.bias_velocity = g1.bias_velocity; c.dZ = t.X; c.lddz = t.ldx; c.A = t.YM; c.lda = t.ldym; c.dZ_below = t.Y; c.lddz_below = t.ldy;
+    c.rows = t.x_rows;
+    return c;
+}
+
+hipError_t launch_chain(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, const SddmmArgs *waiting, hipStream_t s)
+{
+    const ChainArgs c = chain_args(t, g1);
+    SddmmArgs b{};
+    if (waiting) b = *waiting;
+    return with_sddmm_lanes(t.batch, [&](auto g, auto nv) {
+        constexpr int G = decltype(g)::value, NV = decltype(nv)::value, kRows = kWavesPerBlock * (kWave / G);
+        const int n_sum_blocks = c.bias ? (t.x_rows + kRows - 1) / kRows : 0;
+        const dim3 grid(g0.blocks.n_blocks + n_sum_blocks + b.blocks.n_blocks);
+        if constexpr (G * NV * 4 <= kChainMaxBatch)
+            with_spare(t.batch, G * 4 * NV, [&](auto spare) {
+                hipLaunchKernelGGL((chain_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, c, g0, b, n_sum_blocks);
+            });
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_chain_transposed(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, hipStream_t s)
+{
+    return with_sddmm_lanes(t.batch, [&](auto g, auto nv) {
+        constexpr int G = decltype(g)::value, NV = decltype(nv)::value;
+        if constexpr (G * NV * 4 <= kChainMaxBatch)
+            hipLaunchKernelGGL((chain_transposed_kernel<G, NV>), dim3(g0.blocks.n_blocks), dim3(kBlock), 0, s, chain_args(t, g1), g0);
+        return hipGetLastError();
+    });
 }
 
 // The transposed product t and the SDDMM g of one layer can share their gathers when its result mask, if any, is the
