@@ -15,6 +15,7 @@
 #include "device.h"
 #include "kernels.h"
 
+#include <numeric>
 #include <utility>
 
 namespace nerva {
@@ -453,21 +454,26 @@ __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int bl
 
 // Short rows through the packed body, the remaining rows through the grouped body, in one grid,
 // for every column tile; work-group ids are decoded XCD-first as in spmm_tiled_kernel.
+// Which column tile, and which of the launch's n_blocks work-groups of rows, a work-group serves.  stride 0: tile by tile, all XCDs on one tile.  Otherwise
+// the list of all of them is cut into eight equal runs, one per XCD (work-groups go to the XCDs in turn), so that an L2 sees an eighth of
+// the tiles and one more; the stride, which has no factor in common with n_blocks, is the order within a tile.  (tile_order chooses.)
+__device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, int stride, int &tile, int &block)
+{
+    int at = blockIdx.x;
+    if (stride > 0) at = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);   // (the grid is a multiple of 8)
+    tile = at / n_blocks;
+    block = at - tile * n_blocks;
+    if (stride > 1) block = static_cast<int>(static_cast<uint32_t>(block) * static_cast<uint32_t>(stride) % static_cast<uint32_t>(n_blocks));
+    return tile < n_tiles;
+}
+
 template <int GS, bool XMASK>
-__global__ __launch_bounds__(kBlock) void spmm_packed_kernel(const SpmmArgs a, const int n_tiles, const int spread,
+__global__ __launch_bounds__(kBlock) void spmm_packed_kernel(const SpmmArgs a, const int n_tiles, const int stride,
                                                              const int n_pack_blocks)
 {
     const int nrb = n_pack_blocks + a.blocks.n_long_blocks;
     int tile, rb;
-    if (spread) {
-        const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-        tile = (k / nrb) * 8 + xcd;
-        rb = k % nrb;
-    } else {
-        tile = blockIdx.x / nrb;
-        rb = blockIdx.x % nrb;
-    }
-    if (tile >= n_tiles) return;
+    if (!tile_of_block(n_tiles, nrb, stride, tile, rb)) return;
     if (rb < n_pack_blocks) {
         spmm_body_packed<GS, XMASK>(a, rb, tile * GS * 4, n_pack_blocks);
     } else {
@@ -490,19 +496,11 @@ __global__ __launch_bounds__(kBlock) void spmm_grouped_kernel(const SpmmArgs a)
 // owns every 8th tile (each tile is fetched from HBM by one L2 only) and sweeps the row partition
 // once per tile; with fewer tiles every XCD walks all tiles in the same order.
 template <int GS, bool XMASK>
-__global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, const int n_tiles, const int spread)
+__global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, const int n_tiles, const int stride)
 {
     const int nrb = a.blocks.n_blocks;
     int tile, rb;
-    if (spread) {
-        const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-        tile = (k / nrb) * 8 + xcd;
-        rb = k % nrb;
-    } else {
-        tile = blockIdx.x / nrb;
-        rb = blockIdx.x % nrb;
-    }
-    if (tile >= n_tiles) return;
+    if (!tile_of_block(n_tiles, nrb, stride, tile, rb)) return;
     spmm_body_grouped<GS, XMASK, true>(a, rb, tile * GS * 4);
 }
 
@@ -1265,19 +1263,11 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 // sums of dZ) in the tile's slice of the partial buffer.  Work-group ids are decoded XCD-first as
 // in spmm_tiled_kernel, so an operand tile stays in one L2 while every entry gathers from it.
 template <int G, int NV, bool SPARE>
-__global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const int spread)
+__global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const int stride)
 {
     const int nrb = a.blocks.n_blocks;
     int tile, rb;
-    if (spread) {
-        const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-        tile = (k / nrb) * 8 + xcd;
-        rb = k % nrb;
-    } else {
-        tile = blockIdx.x / nrb;
-        rb = blockIdx.x % nrb;
-    }
-    if (tile >= n_tiles) return;
+    if (!tile_of_block(n_tiles, nrb, stride, tile, rb)) return;
     SddmmArgs t = a;
     t.fused = 0;
     t.g = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
@@ -1749,7 +1739,7 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
 template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE>
-__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int spread,
+__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int stride,
                                                                           const int n_pack_blocks, const int lg_split)
 {
     constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped;
@@ -1762,15 +1752,9 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     if constexpr (ONE) {
         tile = 0;
         rb = blockIdx.x;
-    } else if (spread) {
-        const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-        tile = (k / n_pack_blocks) * 8 + xcd;
-        rb = k % n_pack_blocks;
     } else {
-        tile = blockIdx.x / n_pack_blocks;
-        rb = blockIdx.x % n_pack_blocks;
+        if (!tile_of_block(n_tiles, n_pack_blocks, stride, tile, rb)) return;
     }
-    if (tile >= n_tiles) return;
     constexpr int NE = kWave / GS;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = wave_in_block();
@@ -2642,28 +2626,42 @@ int spmm_tile_group(const SpmmArgs &a)
     return tile_columns(a.x_rows, a.batch, a.nnz, a.rows, a.blocks.staged_longest_row, a.blocks.hot_share, a.XM != nullptr) / 4;
 }
 
+constexpr int64_t kMaxGridIds = (1ll << 31) - 1;
+
+// Grid and order of launches in column tiles (tile_of_block).  Multiples of eight tiles go whole to the XCDs.  More than eight are dealt out in equal
+// runs: 8192^2 uniform at 0.6 %, batch 600 / 700 (10 / 11 tiles), forward 70.1 -> 48.7 and 71.9 -> 57.8 us against whole tiles, of which some XCDs had two
+// and the others one; 16384^2 at 1 %, batch 600: 633 -> 406.  Fewer: only products whose tile is well within an L2 (`small`; the former at batch 300,
+// 5 tiles: 35.9 -> 31.5), as gradients lose (5000^2 at 2 %, batch 200: 39.5 -> 42.9) and so do tiles that fill one (16384^2 at 1 %, batch 200: 161 -> 168).
+// Rows of very different lengths are strewn over a run that does not hold whole tiles, for the long ones come first in each.
+inline int64_t tile_grid(int64_t n_tiles, int64_t n_blocks) { return (n_tiles * n_blocks + 7) / 8 * 8; }
+inline int tile_order(int n_tiles, int64_t n_blocks, bool small, int longest_row, int rows, int64_t nnz)
+{
+    if (n_tiles < 8 && !small) return 0;
+    if (n_tiles % 8 == 0 || n_blocks < 8 || n_blocks >= (1 << 16) || static_cast<int64_t>(longest_row) * rows <= 4 * nnz) return 1;
+    int stride = static_cast<int>(n_blocks * 0.618);
+    while (std::gcd(stride, static_cast<int>(n_blocks)) != 1) ++stride;
+    return stride;
+}
+inline bool small_tile(int x_rows, int gs) { return static_cast<int64_t>(x_rows) * gs * 16 <= (5 << 19); }   // (2.5 MiB)
+
 template <int GS>
 hipError_t spmm_tiled_go(const SpmmArgs &a, hipStream_t s)
 {
     const int n_tiles = (a.batch + GS * 4 - 1) / (GS * 4);
-    const int spread = n_tiles >= 8;
-    const int64_t ids = spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 * a.blocks.n_blocks
-                               : static_cast<int64_t>(n_tiles) * a.blocks.n_blocks;
+    const int stride = tile_order(n_tiles, a.blocks.n_blocks, small_tile(a.x_rows, GS), a.blocks.staged_longest_row, a.rows, a.nnz);
+    const int64_t ids = tile_grid(n_tiles, a.blocks.n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
     if (a.XM)
-        hipLaunchKernelGGL((spmm_tiled_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
+        hipLaunchKernelGGL((spmm_tiled_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, stride);
     else
-        hipLaunchKernelGGL((spmm_tiled_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
+        hipLaunchKernelGGL((spmm_tiled_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, stride);
     return hipGetLastError();
 }
 
-constexpr int64_t kMaxGridIds = (1ll << 31) - 1;
-
 // Work-groups of the packed launch for lane groups of gs lanes: those that serve the short rows, and
-// the launch's grid size (tiles rounded up to whole rounds of the 8 XCDs when the ids are decoded
-// XCD-first).  One place, so that the launch and the checks that the grid fits agree.
+// the launch's grid size.  One place, so that the launch and the checks that the grid fits agree.
 struct PackedGrid {
-    int n_tiles, spread, n_pack_blocks;
+    int n_tiles, stride, n_pack_blocks;
     int64_t ids;
 };
 PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
@@ -2671,24 +2669,24 @@ PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
     PackedGrid g;
     const int ne = kWave / gs;
     g.n_tiles = (a.batch + gs * 4 - 1) / (gs * 4);
-    g.spread = g.n_tiles >= 8;
     const int64_t n_sets = (static_cast<int64_t>(a.blocks.n_short) + ne - 1) / ne;
     g.n_pack_blocks = static_cast<int>((n_sets + kWavesPerBlock * kPackSets - 1) / (kWavesPerBlock * kPackSets));
     const int64_t nrb = static_cast<int64_t>(g.n_pack_blocks) + (with_long_rows ? a.blocks.n_long_blocks : 0);
-    g.ids = (g.spread ? static_cast<int64_t>((g.n_tiles + 7) / 8) * 8 : g.n_tiles) * nrb;
+    g.stride = tile_order(g.n_tiles, nrb, small_tile(a.x_rows, gs), a.blocks.staged_longest_row, a.rows, a.nnz);
+    g.ids = tile_grid(g.n_tiles, nrb);
     return g;
 }
 template <int GS>
 hipError_t spmm_packed_go(const SpmmArgs &a, hipStream_t s)
 {
     const PackedGrid pg = packed_grid(a, GS, true);
-    const int n_tiles = pg.n_tiles, spread = pg.spread, n_pack_blocks = pg.n_pack_blocks;
+    const int n_tiles = pg.n_tiles, stride = pg.stride, n_pack_blocks = pg.n_pack_blocks;
     if (pg.ids > kMaxGridIds) return hipErrorInvalidConfiguration;  // (callers check before choosing this path)
     dim3 grid(static_cast<unsigned>(pg.ids));
     if (a.XM)
-        hipLaunchKernelGGL((spmm_packed_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, spread, n_pack_blocks);
+        hipLaunchKernelGGL((spmm_packed_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, stride, n_pack_blocks);
     else
-        hipLaunchKernelGGL((spmm_packed_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, spread, n_pack_blocks);
+        hipLaunchKernelGGL((spmm_packed_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, stride, n_pack_blocks);
     return hipGetLastError();
 }
 
@@ -2826,11 +2824,11 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
 {
     const int W = G * 4 * NV;
     const int n_tiles = (a.batch + W - 1) / W;
-    const int spread = n_tiles >= 8;
-    const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * a.blocks.n_blocks;
+    const int stride = tile_order(n_tiles, a.blocks.n_blocks, false, a.blocks.staged_longest_row, a.rows, a.nnz);
+    const int64_t ids = tile_grid(n_tiles, a.blocks.n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
     with_spare(a.batch, W, [&](auto spare) {
-        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, n_tiles, spread);
+        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, n_tiles, stride);
     });
     sddmm_finish_go(a, n_tiles, s);
     return hipGetLastError();
@@ -3152,21 +3150,21 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     a.w = g.values; a.velocity = g.velocity; a.w_t = g.values_t; a.bias = g.bias; a.bias_velocity = g.bias_velocity;
     const int tg = backward_tile_group(t), n_tiles = backward_tiles(t, tg);
     if (alone && g.values && backward_fused_refreshes(t, g)) a.refresh = g.values;
-    const int spread = n_tiles >= 8;
     const int lg_split = backward_split(t, tg, n_tiles);
     const int64_t per_set = (kWave / tg) >> lg_split, sets = (static_cast<int64_t>(t.rows) + per_set - 1) / per_set;
     const int n_pack_blocks = static_cast<int>((sets + kBwdWaves - 1) / kBwdWaves);
     const bool one = n_tiles == 1 || (alone && backward_looped(t));
     const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
-    const int64_t ids = one ? n_pack_blocks + n_row_blocks : static_cast<int64_t>(spread ? (n_tiles + 7) / 8 * 8 : n_tiles) * n_pack_blocks;
+    const int64_t ids = one ? n_pack_blocks + n_row_blocks : tile_grid(n_tiles, n_pack_blocks);
+    const int stride = tile_order(n_tiles, n_pack_blocks, false, t.blocks.staged_longest_row, t.rows, t.nnz);
     auto go = [&](auto group) {
         constexpr int GS = decltype(group)::value;
         const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
         auto launch = [&](auto pass, auto mask) {
             auto with = [&](auto spare) {
                 hipLaunchKernelGGL((backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value>), grid, block, 0, s, a,
-                                   n_tiles, spread, n_pack_blocks, lg_split);
+                                   n_tiles, stride, n_pack_blocks, lg_split);
             };
             if (a.batch % (GS * 4) == 0) return with(std::integral_constant<BackwardSpare, kSpareNone>{});
             if constexpr (decltype(pass)::value == kBackwardTiles)
@@ -3377,11 +3375,11 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
             SddmmArgs rest = a;
             rest.blocks.waves = a.blocks.rest_waves;
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
-            const int spread = n_tiles >= 8;
-            const int64_t ids = (spread ? static_cast<int64_t>((n_tiles + 7) / 8) * 8 : n_tiles) * rest.blocks.n_blocks;
+            const int stride = n_tiles >= 8;
+            const int64_t ids = tile_grid(n_tiles, rest.blocks.n_blocks);
             with_spare(a.batch, kStageCols, [&](auto spare) {
                 hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1, decltype(spare)::value>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles,
-                                   spread);
+                                   stride);
             });
         }
         sddmm_finish_go(a, n_tiles, s);
