@@ -454,13 +454,17 @@ __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int bl
 
 // Short rows through the packed body, the remaining rows through the grouped body, in one grid,
 // for every column tile; work-group ids are decoded XCD-first as in spmm_tiled_kernel.
-// Which column tile, and which of the launch's n_blocks work-groups of rows, a work-group serves.  stride 0: tile by tile, all XCDs on one tile.  Otherwise
+// Which column tile, and which of the launch's n_blocks work-groups of rows, a work-group serves.  Without runs: tile by tile, all XCDs on one tile.  Otherwise
 // the list of all of them is cut into eight equal runs, one per XCD (work-groups go to the XCDs in turn), so that an L2 sees an eighth of
 // the tiles and one more; the stride, which has no factor in common with n_blocks, is the order within a tile.  (tile_order chooses.)
-__device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, int stride, int &tile, int &block)
+struct TileOrder {
+    int per, stride;   // an eighth of the grid (an argument: the grid's size costs a load), or 0: no runs
+};
+__device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, TileOrder order, int &tile, int &block)
 {
+    const int stride = order.stride;
     int at = blockIdx.x;
-    if (stride > 0) at = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);   // (the grid is a multiple of 8)
+    if (order.per > 0) at = (blockIdx.x & 7) * order.per + (blockIdx.x >> 3);
     tile = at / n_blocks;
     block = at - tile * n_blocks;
     if (stride > 1) block = static_cast<int>(static_cast<uint32_t>(block) * static_cast<uint32_t>(stride) % static_cast<uint32_t>(n_blocks));
@@ -468,12 +472,12 @@ __device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, int str
 }
 
 template <int GS, bool XMASK>
-__global__ __launch_bounds__(kBlock) void spmm_packed_kernel(const SpmmArgs a, const int n_tiles, const int stride,
+__global__ __launch_bounds__(kBlock) void spmm_packed_kernel(const SpmmArgs a, const int n_tiles, const TileOrder order,
                                                              const int n_pack_blocks)
 {
     const int nrb = n_pack_blocks + a.blocks.n_long_blocks;
     int tile, rb;
-    if (!tile_of_block(n_tiles, nrb, stride, tile, rb)) return;
+    if (!tile_of_block(n_tiles, nrb, order, tile, rb)) return;
     if (rb < n_pack_blocks) {
         spmm_body_packed<GS, XMASK>(a, rb, tile * GS * 4, n_pack_blocks);
     } else {
@@ -496,11 +500,11 @@ __global__ __launch_bounds__(kBlock) void spmm_grouped_kernel(const SpmmArgs a)
 // owns every 8th tile (each tile is fetched from HBM by one L2 only) and sweeps the row partition
 // once per tile; with fewer tiles every XCD walks all tiles in the same order.
 template <int GS, bool XMASK>
-__global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, const int n_tiles, const int stride)
+__global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, const int n_tiles, const TileOrder order)
 {
     const int nrb = a.blocks.n_blocks;
     int tile, rb;
-    if (!tile_of_block(n_tiles, nrb, stride, tile, rb)) return;
+    if (!tile_of_block(n_tiles, nrb, order, tile, rb)) return;
     spmm_body_grouped<GS, XMASK, true>(a, rb, tile * GS * 4);
 }
 
@@ -1140,16 +1144,57 @@ __device__ __forceinline__ float sddmm_own_columns(gmem_ptr Xg, int iters, int m
     return res;
 }
 
-// The wave's entries of a row whose dZ it holds (off: where its columns lie), and the row's sum where it leads.
-template <int G, int NV, bool SPARE>
-__device__ __forceinline__ void sddmm_row(const SddmmArgs &a, const WaveTask &task, const int col0, const uint32_t (&off)[NV], const float4 (&dz)[NV])
+// col0: first column of the pass, which covers G*4*NV columns of the batch.  HELD: the wave's task and its row of dZ (without
+// the columns that are not the lanes' own) are there already.
+template <int G, int NV, bool SPARE, bool HELD = false>
+__device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, const int col0 = 0, const WaveTask *held_task = nullptr,
+                                           const float4 *held_dz = nullptr)
 {
     constexpr int NG = kWave / G;
     constexpr int UI = NV >= 3 ? 2 : (NV == 2 ? 4 : 8);   // 32 registers of gathered data: two 16-wave work-groups fit a compute unit
     const int lane = threadIdx.x & (kWave - 1);
+    if constexpr (!HELD) mean_loss_task(a, block);
+    WaveTask task;
+    if constexpr (HELD) task = *held_task;
+    else task = wave_task(a.blocks, block);
+    if (task.row < 0) return;
     const int row = task.row;
     const int grp = lane / G;
     const int lig = lane % G;
+
+    // the row of dZ: all its loads together, whole waves (lanes beyond the batch re-read columns of the pass and are zeroed)
+    float4 dz[NV];
+    uint32_t off[NV];
+    if constexpr (HELD) {
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int own = col0 + (t * G + lig) * 4;
+            off[t] = static_cast<uint32_t>(four_columns(own < a.batch ? own : col0, a.batch)) * 4u;
+            dz[t] = held_dz[t];
+        }
+    } else {
+        const gmem_ptr zr = as_gmem(a.dZ + static_cast<int64_t>(row) * a.lddz);
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int own = col0 + (t * G + lig) * 4;
+            off[t] = static_cast<uint32_t>(four_columns(own < a.batch ? own : col0, a.batch)) * 4u;
+            dz[t] = gload4(zr, off[t]);
+        }
+        if (a.ZM) {
+            const gmem_ptr zm = as_gmem(a.ZM + static_cast<int64_t>(row) * a.ldzm);
+            float4 m[NV];
+#pragma unroll
+            for (int t = 0; t < NV; ++t) m[t] = gload4(zm, off[t]);
+#pragma unroll
+            for (int t = 0; t < NV; ++t) dz[t] = keep_where_positive(dz[t], m[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int own = col0 + (t * G + lig) * 4;
+            dz[t] = own < a.batch ? drop_shared(dz[t], own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+
     if (task.lead && (a.db || (a.fused && a.bias))) {
         float s = 0.f;
 #pragma unroll
@@ -1212,46 +1257,6 @@ __device__ __forceinline__ void sddmm_row(const SddmmArgs &a, const WaveTask &ta
     }
 }
 
-// col0: first column of the pass, which covers G*4*NV columns of the batch.
-template <int G, int NV, bool SPARE>
-__device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, const int col0 = 0)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    mean_loss_task(a, block);
-    const WaveTask task = wave_task(a.blocks, block);
-    if (task.row < 0) return;
-    const int row = task.row;
-    const int lig = lane % G;
-
-    // the row of dZ: all its loads together, whole waves (lanes beyond the batch re-read columns of the pass and are zeroed)
-    float4 dz[NV];
-    uint32_t off[NV];
-    {
-        const gmem_ptr zr = as_gmem(a.dZ + static_cast<int64_t>(row) * a.lddz);
-#pragma unroll
-        for (int t = 0; t < NV; ++t) {
-            const int own = col0 + (t * G + lig) * 4;
-            off[t] = static_cast<uint32_t>(four_columns(own < a.batch ? own : col0, a.batch)) * 4u;
-            dz[t] = gload4(zr, off[t]);
-        }
-        if (a.ZM) {
-            const gmem_ptr zm = as_gmem(a.ZM + static_cast<int64_t>(row) * a.ldzm);
-            float4 m[NV];
-#pragma unroll
-            for (int t = 0; t < NV; ++t) m[t] = gload4(zm, off[t]);
-#pragma unroll
-            for (int t = 0; t < NV; ++t) dz[t] = keep_where_positive(dz[t], m[t]);
-        }
-#pragma unroll
-        for (int t = 0; t < NV; ++t) {
-            const int own = col0 + (t * G + lig) * 4;
-            dz[t] = own < a.batch ? drop_shared(dz[t], own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    }
-
-    sddmm_row<G, NV, SPARE>(a, task, col0, off, dz);
-}
-
 template <int G, int NV, bool SPARE>
 __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 {
@@ -1263,11 +1268,11 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 // sums of dZ) in the tile's slice of the partial buffer.  Work-group ids are decoded XCD-first as
 // in spmm_tiled_kernel, so an operand tile stays in one L2 while every entry gathers from it.
 template <int G, int NV, bool SPARE>
-__global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const int stride)
+__global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order)
 {
     const int nrb = a.blocks.n_blocks;
     int tile, rb;
-    if (!tile_of_block(n_tiles, nrb, stride, tile, rb)) return;
+    if (!tile_of_block(n_tiles, nrb, order, tile, rb)) return;
     SddmmArgs t = a;
     t.fused = 0;
     t.g = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
@@ -1739,7 +1744,7 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
 template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE>
-__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const int stride,
+__global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const TileOrder order,
                                                                           const int n_pack_blocks, const int lg_split)
 {
     constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped;
@@ -1753,7 +1758,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
         tile = 0;
         rb = blockIdx.x;
     } else {
-        if (!tile_of_block(n_tiles, n_pack_blocks, stride, tile, rb)) return;
+        if (!tile_of_block(n_tiles, n_pack_blocks, order, tile, rb)) return;
     }
     constexpr int NE = kWave / GS;
     const int lane = threadIdx.x & (kWave - 1);
@@ -1992,7 +1997,7 @@ __device__ __forceinline__ void chain_body(const ChainArgs &c, const SddmmArgs &
         }
         const uint32_t ldzb = static_cast<uint32_t>(c.lddz) * 4u;
         const gmem_ptr Zg = as_gmem(c.dZ);
-        const int q_mine = lig * NG + grp;  // slot of this lane inside a chunk of 64 entries, as in sddmm_row
+        const int q_mine = lig * NG + grp;  // slot of this lane inside a chunk of 64 entries, as in sddmm_body
         const bool spare = SPARE && G * 4 * NV > a.batch;  // uniform
         for (int pc = q0; pc < q1; pc += kWave) {
             const int n = min(kWave, q1 - pc);
@@ -2059,10 +2064,10 @@ __device__ __forceinline__ void chain_body(const ChainArgs &c, const SddmmArgs &
         if (task.part == 0 && grp == 0 && own < a.batch) st4(c.dZ_below + static_cast<int64_t>(row) * c.lddz_below + (off[t] >> 2), y);
         dz[t] = own < a.batch ? drop_shared(y, own, static_cast<int>(off[t] >> 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    if constexpr (WHOLE) sddmm_row<G, NV, SPARE>(a, task, 0, off, dz);
+    if constexpr (WHOLE) sddmm_body<G, NV, SPARE, true>(a, block, 0, &task, dz);
 }
 
-// Biases of W_1: a group of lanes per row of dZ_1, added up as sddmm_row does.
+// Biases of W_1: a group of lanes per row of dZ_1, added up as sddmm_body does.
 template <int G, int NV>
 __device__ __forceinline__ void chain_row_sums(const ChainArgs &c, const SddmmArgs &a, const int block)
 {
@@ -2634,13 +2639,15 @@ constexpr int64_t kMaxGridIds = (1ll << 31) - 1;
 // 5 tiles: 35.9 -> 31.5), as gradients lose (5000^2 at 2 %, batch 200: 39.5 -> 42.9) and so do tiles that fill one (16384^2 at 1 %, batch 200: 161 -> 168).
 // Rows of very different lengths are strewn over a run that does not hold whole tiles, for the long ones come first in each.
 inline int64_t tile_grid(int64_t n_tiles, int64_t n_blocks) { return (n_tiles * n_blocks + 7) / 8 * 8; }
-inline int tile_order(int n_tiles, int64_t n_blocks, bool small, int longest_row, int rows, int64_t nnz)
+inline TileOrder tile_order(int n_tiles, int64_t n_blocks, bool small, int longest_row, int rows, int64_t nnz)
 {
-    if (n_tiles < 8 && !small) return 0;
-    if (n_tiles % 8 == 0 || n_blocks < 8 || n_blocks >= (1 << 16) || static_cast<int64_t>(longest_row) * rows <= 4 * nnz) return 1;
-    int stride = static_cast<int>(n_blocks * 0.618);
-    while (std::gcd(stride, static_cast<int>(n_blocks)) != 1) ++stride;
-    return stride;
+    TileOrder order{0, 1};
+    if (n_tiles < 8 && !small) return order;
+    order.per = static_cast<int>(tile_grid(n_tiles, n_blocks) / 8);
+    if (n_tiles % 8 == 0 || n_blocks < 8 || n_blocks >= (1 << 16) || static_cast<int64_t>(longest_row) * rows <= 4 * nnz) return order;
+    order.stride = static_cast<int>(n_blocks * 0.618);
+    while (std::gcd(order.stride, static_cast<int>(n_blocks)) != 1) ++order.stride;
+    return order;
 }
 inline bool small_tile(int x_rows, int gs) { return static_cast<int64_t>(x_rows) * gs * 16 <= (5 << 19); }   // (2.5 MiB)
 
@@ -2648,20 +2655,21 @@ template <int GS>
 hipError_t spmm_tiled_go(const SpmmArgs &a, hipStream_t s)
 {
     const int n_tiles = (a.batch + GS * 4 - 1) / (GS * 4);
-    const int stride = tile_order(n_tiles, a.blocks.n_blocks, small_tile(a.x_rows, GS), a.blocks.staged_longest_row, a.rows, a.nnz);
+    const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, small_tile(a.x_rows, GS), a.blocks.staged_longest_row, a.rows, a.nnz);
     const int64_t ids = tile_grid(n_tiles, a.blocks.n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
     if (a.XM)
-        hipLaunchKernelGGL((spmm_tiled_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, stride);
+        hipLaunchKernelGGL((spmm_tiled_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, order);
     else
-        hipLaunchKernelGGL((spmm_tiled_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, stride);
+        hipLaunchKernelGGL((spmm_tiled_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, order);
     return hipGetLastError();
 }
 
 // Work-groups of the packed launch for lane groups of gs lanes: those that serve the short rows, and
 // the launch's grid size.  One place, so that the launch and the checks that the grid fits agree.
 struct PackedGrid {
-    int n_tiles, stride, n_pack_blocks;
+    int n_tiles, n_pack_blocks;
+    TileOrder order;
     int64_t ids;
 };
 PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
@@ -2672,7 +2680,7 @@ PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
     const int64_t n_sets = (static_cast<int64_t>(a.blocks.n_short) + ne - 1) / ne;
     g.n_pack_blocks = static_cast<int>((n_sets + kWavesPerBlock * kPackSets - 1) / (kWavesPerBlock * kPackSets));
     const int64_t nrb = static_cast<int64_t>(g.n_pack_blocks) + (with_long_rows ? a.blocks.n_long_blocks : 0);
-    g.stride = tile_order(g.n_tiles, nrb, small_tile(a.x_rows, gs), a.blocks.staged_longest_row, a.rows, a.nnz);
+    g.order = tile_order(g.n_tiles, nrb, small_tile(a.x_rows, gs), a.blocks.staged_longest_row, a.rows, a.nnz);
     g.ids = tile_grid(g.n_tiles, nrb);
     return g;
 }
@@ -2680,13 +2688,14 @@ template <int GS>
 hipError_t spmm_packed_go(const SpmmArgs &a, hipStream_t s)
 {
     const PackedGrid pg = packed_grid(a, GS, true);
-    const int n_tiles = pg.n_tiles, stride = pg.stride, n_pack_blocks = pg.n_pack_blocks;
+    const int n_tiles = pg.n_tiles, n_pack_blocks = pg.n_pack_blocks;
+    const TileOrder order = pg.order;
     if (pg.ids > kMaxGridIds) return hipErrorInvalidConfiguration;  // (callers check before choosing this path)
     dim3 grid(static_cast<unsigned>(pg.ids));
     if (a.XM)
-        hipLaunchKernelGGL((spmm_packed_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, stride, n_pack_blocks);
+        hipLaunchKernelGGL((spmm_packed_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, order, n_pack_blocks);
     else
-        hipLaunchKernelGGL((spmm_packed_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, stride, n_pack_blocks);
+        hipLaunchKernelGGL((spmm_packed_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, order, n_pack_blocks);
     return hipGetLastError();
 }
 
@@ -2824,11 +2833,11 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
 {
     const int W = G * 4 * NV;
     const int n_tiles = (a.batch + W - 1) / W;
-    const int stride = tile_order(n_tiles, a.blocks.n_blocks, false, a.blocks.staged_longest_row, a.rows, a.nnz);
+    const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, false, a.blocks.staged_longest_row, a.rows, a.nnz);
     const int64_t ids = tile_grid(n_tiles, a.blocks.n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
     with_spare(a.batch, W, [&](auto spare) {
-        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, n_tiles, stride);
+        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, n_tiles, order);
     });
     sddmm_finish_go(a, n_tiles, s);
     return hipGetLastError();
@@ -3157,14 +3166,14 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
     const int64_t ids = one ? n_pack_blocks + n_row_blocks : tile_grid(n_tiles, n_pack_blocks);
-    const int stride = tile_order(n_tiles, n_pack_blocks, false, t.blocks.staged_longest_row, t.rows, t.nnz);
+    const TileOrder order = tile_order(n_tiles, n_pack_blocks, false, t.blocks.staged_longest_row, t.rows, t.nnz);
     auto go = [&](auto group) {
         constexpr int GS = decltype(group)::value;
         const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
         auto launch = [&](auto pass, auto mask) {
             auto with = [&](auto spare) {
                 hipLaunchKernelGGL((backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value>), grid, block, 0, s, a,
-                                   n_tiles, stride, n_pack_blocks, lg_split);
+                                   n_tiles, order, n_pack_blocks, lg_split);
             };
             if (a.batch % (GS * 4) == 0) return with(std::integral_constant<BackwardSpare, kSpareNone>{});
             if constexpr (decltype(pass)::value == kBackwardTiles)
@@ -3375,11 +3384,11 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
             SddmmArgs rest = a;
             rest.blocks.waves = a.blocks.rest_waves;
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
-            const int stride = n_tiles >= 8;
+            const TileOrder order = tile_order(n_tiles, rest.blocks.n_blocks, false, 0, a.rows, a.nnz);
             const int64_t ids = tile_grid(n_tiles, rest.blocks.n_blocks);
             with_spare(a.batch, kStageCols, [&](auto spare) {
                 hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1, decltype(spare)::value>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles,
-                                   stride);
+                                   order);
             });
         }
         sddmm_finish_go(a, n_tiles, s);
