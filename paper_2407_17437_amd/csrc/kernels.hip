@@ -1678,7 +1678,9 @@ constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and
 // none, masking the product alone leaves the registers as they are: 7413 x 4010 at 0.5 %, batch 212, 17.4 without, 18.3 with four masks, 17.7 with one.
 enum BackwardSpare { kSpareNone, kSpareLanes, kSpareColumns };
 __device__ __forceinline__ float keep_bits(float x, uint32_t mask) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & mask); }
-template <int U, int GS, bool XMASK, BackwardSpare SPARE>
+// APART: every gather before the first product, which the compiler else mixes to save registers, with two or three in flight.  One tile on 4096 x 3072 at
+// 5 %, batch 128: 25.3 -> 23.4 us; column tiles lose with fewer waves (wide MLP 97.3 -> 99.2), and masked gathers take too many registers.
+template <int U, int GS, bool XMASK, BackwardSpare SPARE, bool APART>
 __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, float my_w, uint32_t off, const float4 &ax,
                                          const uint32_t (&own)[4], int it0, int lig, float (&acc)[4], float &res)
 {
@@ -1697,6 +1699,7 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int 
 #pragma unroll
         for (int u = 0; u < U; ++u) x[u] = keep_where_positive(x[u], gload4(Mg, mo[u] + off));
     }
+    if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         if constexpr (SPARE == kSpareColumns) x[u] = make_float4(keep_bits(x[u].x, own[0]), keep_bits(x[u].y, own[1]), keep_bits(x[u].z, own[2]), keep_bits(x[u].w, own[3]));
@@ -1747,7 +1750,7 @@ template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE>
 __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const TileOrder order,
                                                                           const int n_pack_blocks, const int lg_split)
 {
-    constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped;
+    constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped, kApart = PASS == kBackwardOneTile && !XMASK;
     if (ONE && static_cast<int>(blockIdx.x) >= n_pack_blocks) {
         backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_pack_blocks) * kBwdWaves + wave_in_block(),
                           static_cast<int64_t>(gridDim.x - n_pack_blocks) * kBwdWaves);
@@ -1826,16 +1829,16 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                     float res = 0.f;
                     int src = src0;
                     int u0 = 0;
-                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                     if (u0 + 4 <= steps) {
-                        bwd_pass<4, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                        bwd_pass<4, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                         u0 += 4; src += 16;
                     }
                     if (u0 + 2 <= steps) {
-                        bwd_pass<2, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                        bwd_pass<2, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                         u0 += 2; src += 8;
                     }
-                    if (u0 < steps) bwd_pass<1, GS, XMASK, SPARE>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                    if (u0 < steps) bwd_pass<1, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                     const int e = base + part * GS + lig;
                     if (row >= 0 && e < len) {
                         if constexpr (ONE) {
