@@ -481,9 +481,10 @@ __host__ __device__ inline int32_t staged_ranges_wanted(int32_t rows, int64_t nn
     if (range_bound == 0 || mode == kPlanRowSplit || max_batch < kStageMinBatch || nnz == 0) return 0;
     const int32_t want = staged_ranges_aim(rows, max_batch);
     if (mode != kPlanPreferStaged && static_cast<double>(nnz) < static_cast<double>(kStageMinReuse) * want * cols) return 0;
-    // segments shorter than at any batch pay (staged_pays): binding 8192 x 3072 at 1.7 %, whose plan nothing took, took 31 us more (plan, tables and
+    // segments shorter than at any batch pay (staged_pays) on an operand that stays small: binding 8192 x 3072 at 1.7 %, whose plan nothing took, took 31 us more (plan, tables and
     // segment bounds 39 + 14 + 9 -> 22 + 5 + 4)
-    if (mode != kPlanPreferStaged && nnz < static_cast<int64_t>(kStageSegmentBigOperand) * rows * ((cols + kStageRows - 1) / kStageRows)) return 0;
+    if (mode != kPlanPreferStaged && static_cast<int64_t>(cols) * max_batch * 4 < kStageBigOperand &&
+        nnz < static_cast<int64_t>(kStageSegmentBesideDense) * rows * ((cols + kStageRows - 1) / kStageRows)) return 0;
     return want;
 }
 // Most ranges any staged plan of a matrix with that many rows can have; 0 where its tables would pass 1 GiB.  A plan over
