@@ -40,76 +40,73 @@ __device__ __forceinline__ void dense_epilogue(const DenseArgs &a, int row, int 
 
 // Y (rows x batch) = act(D X + b).  Work-group: 16 rows x NB * 16 columns; its kNnWaves waves split K = cols
 // into contiguous slices (multiples of 16) and meet in LDS, where wave w adds register (w % 4) of all slices in
-// slice order for the tile columns t = w / 4, w / 4 + kNnWaves / 4, ...  The loads of kNnDepth chunks of 16 k are
-// all issued before the first of their MFMA steps.  (kSplitWaves: the same split in the transposed product.)
+// slice order for the tile columns t = w / 4, w / 4 + kNnWaves / 4, ...  The loads of the next chunks of 16 k are on their way
+// while a chunk's MFMA steps run; no branch stands between them, or every wait would be for all of them (and was: 1024 x 3072 at
+// batch 512 60.9 us, 41.0 now; 2048 x 4096 at batch 256 78, 50, at 1024 279, 186; 1024 x 3072 at batch 100 16.8, 16.0).
+// (kSplitWaves: the same split in the transposed product.)
 constexpr int kSplitWaves = 16;
 constexpr int kSplitBlock = kSplitWaves * kWave;
-constexpr int kNnDepth = 2;
 
 // VECX: the NB columns of a lane are consecutive (tile t holds the columns n0 + NB * r + t), so that one
 // 8- or 16-byte load along the batch feeds the NB tiles; needs X 16-byte aligned with ldx a multiple of 4.
-// A batch of kNnDepth chunks: its loads (nn_load) are issued while the MFMA steps of the batch before (nn_mfma)
-// run -- the waves of a work-group start together and would otherwise all load, then all multiply.
-template <int NB>
-struct NnBatch {
-    float4 w4[kNnDepth];
-    float b[kNnDepth][4][NB];
-};
-
-template <int NB, bool VECX>
-__device__ __forceinline__ void nn_load(const DenseArgs &a, const float *wrow, const int64_t (&xcol)[NB], int q, int c0, int n_chunks,
-                                        NnBatch<NB> &B)
-{
-    const int K = a.cols;
-#pragma unroll
-    for (int d = 0; d < kNnDepth; ++d) {
-        const int kb = (c0 + (d < n_chunks ? d : 0)) * 16;   // (chunks past the end repeat the first one and are not used)
-        B.w4[d] = ld4(wrow + kb);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int k = kb + q * 4 + s;
-            const float *xr = a.X + static_cast<int64_t>(k < K ? k : 0) * a.ldx;
-            if constexpr (VECX && NB == 4) {
-                const float4 x = ld4(xr + xcol[0]);
-                B.b[d][s][0] = x.x; B.b[d][s][1] = x.y; B.b[d][s][2] = x.z; B.b[d][s][3] = x.w;
-            } else if constexpr (VECX && NB == 2) {
-                const float2 x = *reinterpret_cast<const float2 *>(xr + xcol[0]);
-                B.b[d][s][0] = x.x; B.b[d][s][1] = x.y;
-            } else {
-#pragma unroll
-                for (int t = 0; t < NB; ++t) B.b[d][s][t] = xr[xcol[t]];
-            }
-        }
-    }
-}
-
 // EXACT: rows and K are multiples of 16, so no operand has to be zeroed (columns beyond the batch repeat column 0
 // and their results are never stored): the MFMA steps take the loaded registers as they are.
-template <int NB, bool EXACT>
-__device__ __forceinline__ void nn_mfma(int K, bool row_ok, const bool (&col_ok)[NB], int q, int c0, int n_chunks, const NnBatch<NB> &B,
-                                        v4f (&acc)[NB])
-{
-#pragma unroll
-    for (int d = 0; d < kNnDepth; ++d) {
-        if (d >= n_chunks) break;  // wave-uniform
-        const int kb = (c0 + d) * 16;
-        const float wv4[4] = {B.w4[d].x, B.w4[d].y, B.w4[d].z, B.w4[d].w};
+template <int NB>
+struct NnChunk {
+    float4 w4;
+    float b[4][NB];
+};
+
+// The slice's chunks one after another; past its last one the addresses stay there (what is read again is not used).
+template <int NB, bool VECX, bool EXACT>
+struct NnReader {
+    const float *w, *x;
+    int64_t ldx;
+    int k;       // the lane's first k of the chunk
+    int left;    // chunks from this one on
+
+    __device__ __forceinline__ void load(const DenseArgs &a, const int64_t (&xcol)[NB], NnChunk<NB> &C)
+    {
+        C.w4 = ld4(w);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const bool k_ok = kb + q * 4 + s < K;
+            const float *xr = EXACT || k + s < a.cols ? x + s * ldx : a.X;
+            if constexpr (VECX && NB == 4) {
+                const float4 v = ld4(xr + xcol[0]);
+                C.b[s][0] = v.x; C.b[s][1] = v.y; C.b[s][2] = v.z; C.b[s][3] = v.w;
+            } else if constexpr (VECX && NB == 2) {
+                const float2 v = *reinterpret_cast<const float2 *>(xr + xcol[0]);
+                C.b[s][0] = v.x; C.b[s][1] = v.y;
+            } else {
 #pragma unroll
-            for (int t = 0; t < NB; ++t) {
-                if constexpr (EXACT)
-                    acc[t] = mfma(wv4[s], B.b[d][s][t], acc[t]);
-                else
-                    acc[t] = mfma(row_ok ? wv4[s] : 0.f, (k_ok && col_ok[t]) ? B.b[d][s][t] : 0.f, acc[t]);
+                for (int t = 0; t < NB; ++t) C.b[s][t] = xr[xcol[t]];
             }
         }
+        const int step = left > 1 ? 16 : 0;   // uniform
+        --left;
+        w += step; k += step; x += step * ldx;
+        __builtin_amdgcn_sched_barrier(0);   // chunk after chunk, or the first one's loads come last and its wait is for all
     }
+};
+
+template <int NB, bool EXACT>
+__device__ __forceinline__ void nn_mfma(bool row_ok, const bool (&col_ok)[NB], int k_left, const NnChunk<NB> &C, v4f (&acc)[NB])
+{
+    const float wv4[4] = {C.w4.x, C.w4.y, C.w4.z, C.w4.w};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            if constexpr (EXACT)
+                acc[t] = mfma(wv4[s], C.b[s][t], acc[t]);
+            else
+                acc[t] = mfma(row_ok ? wv4[s] : 0.f, (s < k_left && col_ok[t]) ? C.b[s][t] : 0.f, acc[t]);
+        }
 }
 
-constexpr int kNnWaves = 8;   // measured on the 1024 x 3072 x 100 product: 21.3 / 18.6 / 20.6 us with 4 / 8 / 16 waves
+constexpr int kNnWaves = 4;   // 1024 x 3072 at batch 100, 4096 x 2048 at batch 256 with 4 / 8 / 16 waves: 16.0 / 16.5 / 17.7, 51.8 / 54.7 / 64.6 us
 constexpr int kNnBlock = kNnWaves * kWave;
+constexpr int kNnAhead = 2;    // chunks of a wave; the same with 1 / 2 / 3 / 6: 23.8 / 16.1 / 16.4 / 17.1, 52.9 / 50.8 / 51.8 / 59.9
 template <int NB, bool VECX, bool EXACT>
 __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a)
 {
@@ -143,14 +140,26 @@ __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a)
     v4f acc[NB];
 #pragma unroll
     for (int t = 0; t < NB; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
-    NnBatch<NB> B0, B1;
-    if (c_begin < c_end) nn_load<NB, VECX>(a, wrow, xcol, q, c_begin, min(kNnDepth, c_end - c_begin), B0);
-    for (int c = c_begin; c < c_end; c += 2 * kNnDepth) {
-        const int c1 = c + kNnDepth, c2 = c + 2 * kNnDepth;
-        if (c1 < c_end) nn_load<NB, VECX>(a, wrow, xcol, q, c1, min(kNnDepth, c_end - c1), B1);
-        nn_mfma<NB, EXACT>(K, row_ok, col_ok, q, c, min(kNnDepth, c_end - c), B0, acc);
-        if (c2 < c_end) nn_load<NB, VECX>(a, wrow, xcol, q, c2, min(kNnDepth, c_end - c2), B0);
-        if (c1 < c_end) nn_mfma<NB, EXACT>(K, row_ok, col_ok, q, c1, min(kNnDepth, c_end - c1), B1, acc);
+    NnChunk<NB> ring[kNnAhead];
+    const int k0 = min(c_begin, k16 - 1) * 16 + q * 4;   // (a slice may be empty)
+    NnReader<NB, VECX, EXACT> next{wrow + (k0 - q * 4), a.X + static_cast<int64_t>(k0) * a.ldx, a.ldx, k0, c_end - c_begin};
+    auto multiply = [&](int c, const NnChunk<NB> &C) __attribute__((always_inline)) {
+        nn_mfma<NB, EXACT>(row_ok, col_ok, K - (c * 16 + q * 4), C, acc);
+    };
+#pragma unroll
+    for (int d = 0; d < kNnAhead; ++d) next.load(a, xcol, ring[d]);
+    int c = c_begin;
+    for (; c + kNnAhead <= c_end; c += kNnAhead) {
+#pragma unroll
+        for (int d = 0; d < kNnAhead; ++d) {
+            multiply(c + d, ring[d]);
+            next.load(a, xcol, ring[d]);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < kNnAhead; ++d) {
+        if (c + d >= c_end) break;  // wave-uniform
+        multiply(c + d, ring[d]);
     }
 #pragma unroll
     for (int t = 0; t < NB; ++t)
@@ -168,11 +177,13 @@ __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a)
 
 // Y (cols x batch) = (D^T X) * [YM > 0].  Work-group: 64 output rows (four tiles fed by one 16-byte load along
 // the row of D: tile u holds the output rows j0 + 4 r' + u) x NB * 16 columns; the waves split K = rows, kTnDepth
-// steps of loads in flight.  Wave w adds tile (w / 4), register (w % 4) of all slices in slice order.
-constexpr int kTnDepth = 8;
+// steps of loads in flight.  Wave w adds tile (w / 4), register (w % 4) of all slices in slice order.  64 registers, so that two
+// work-groups fit on a compute unit: (512 x 1024 at batch 100, 2048 x 4096 at batch 256) 6.1 and 58 us, with 78 7.2 and 66.5; eight steps
+// requested and then multiplied 7.1 and 63.8.
+constexpr int kTnDepth = 3;
 
 template <int NB>
-__global__ __launch_bounds__(kSplitBlock) void dense_tn_kernel(const DenseArgs a)
+__global__ __launch_bounds__(kSplitBlock, 8) void dense_tn_kernel(const DenseArgs a)
 {
     __shared__ float part[kSplitWaves][4][NB][4][kWave];
     const int lane = threadIdx.x & (kWave - 1), wv = wave_id();
@@ -196,28 +207,42 @@ __global__ __launch_bounds__(kSplitBlock) void dense_tn_kernel(const DenseArgs a
     for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int t = 0; t < NB; ++t) acc[u][t] = v4f{0.f, 0.f, 0.f, 0.f};
-    for (int c = c_begin; c < c_end; c += kTnDepth) {
-        const int n_steps = min(kTnDepth, c_end - c);
-        float4 w4[kTnDepth];
-        float b[kTnDepth][NB];
+    float4 w4[kTnDepth];
+    float b[kTnDepth][NB];
+    int i = min(c_begin, k4 - 1) * 4 + q, left = c_end - c_begin - 1;   // (a slice may be empty)
+    const float *wp = wcol + i * a.ldw, *xp = a.X + i * a.ldx;
+    auto load = [&](int d) __attribute__((always_inline)) {   // as in NnReader: step after step, the last one again past the end
+        const bool ok = i < K;
+        w4[d] = ld4(ok ? wp : wcol);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) b[d][t] = (ok ? xp : a.X)[xcol[t]];
+        const int step = left > 0 ? 4 : 0;   // uniform
+        --left;
+        i += step; wp += step * a.ldw; xp += step * a.ldx;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int c, int d) __attribute__((always_inline)) {
+        const bool i_ok = c * 4 + q < K;
+        const float wv4[4] = {w4[d].x, w4[d].y, w4[d].z, w4[d].w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int t = 0; t < NB; ++t) acc[u][t] = mfma(i_ok ? wv4[u] : 0.f, (i_ok && col_ok[t]) ? b[d][t] : 0.f, acc[u][t]);
+    };
+#pragma unroll
+    for (int d = 0; d < kTnDepth; ++d) load(d);
+    int c = c_begin;
+    for (; c + kTnDepth <= c_end; c += kTnDepth) {
 #pragma unroll
         for (int d = 0; d < kTnDepth; ++d) {
-            const int i = (c + (d < n_steps ? d : 0)) * 4 + q;       // (steps past the end repeat the first one and are not used)
-            const int64_t ii = i < K ? i : 0;
-            w4[d] = ld4(wcol + ii * a.ldw);
-#pragma unroll
-            for (int t = 0; t < NB; ++t) b[d][t] = a.X[ii * a.ldx + xcol[t]];
+            multiply(c + d, d);
+            load(d);
         }
+    }
 #pragma unroll
-        for (int d = 0; d < kTnDepth; ++d) {
-            if (d >= n_steps) break;  // wave-uniform
-            const bool i_ok = (c + d) * 4 + q < K;
-            const float wv4[4] = {w4[d].x, w4[d].y, w4[d].z, w4[d].w};
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int t = 0; t < NB; ++t) acc[u][t] = mfma(i_ok ? wv4[u] : 0.f, (i_ok && col_ok[t]) ? b[d][t] : 0.f, acc[u][t]);
-        }
+    for (int d = 0; d < kTnDepth; ++d) {
+        if (c + d >= c_end) break;  // wave-uniform
+        multiply(c + d, d);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)

@@ -50,6 +50,15 @@ def test_sampled_gradient(nb, oracle, rows, cols, density, batch, ld):
     check_layer(nb, oracle, layer_case(rows, cols, density, seed=rows + batch), batch, ld=ld)
 
 
+@pytest.mark.parametrize("rows,cols,batch,ld", [
+    # slices of the sum that are empty, one chunk, whole rounds of chunks and one more; 1, 2 and 4 tiles of 16 columns to a work-group
+    (16, 16, 1, None), (17, 33, 5, 5), (48, 80, 16, None), (1041, 129, 33, 33), (1024, 256, 100, None), (1039, 271, 99, 99),
+    (1024, 320, 256, None), (1030, 330, 130, None), (1090, 61, 257, 257),
+])
+def test_products_of_the_dense_copy(nb, oracle, rows, cols, batch, ld):
+    check_layer(nb, oracle, layer_case(rows, cols, 0.6, seed=rows + batch), batch, ld=ld)
+
+
 def mixed_rows(rows, cols, n_dense, density, seed, relu=False):
     """n_dense rows that store `density` of their columns among short, empty and middling ones."""
     rng = np.random.default_rng(seed)
