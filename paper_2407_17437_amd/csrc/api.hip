@@ -147,6 +147,8 @@ struct nerva_layer {
     bool dense_on = false;
     float *dense = nullptr;
     int64_t dense_ld = 0;
+    float *dense_shares = nullptr;   // scratch of its forward product (DenseArgs::tickets, then ::partial), or nullptr
+    size_t dense_shares_floats = 0;
     // owned, only for a matrix that stores every entry and has at most kFullMaxRows rows
     bool full = false;               // the bound pattern is such a matrix
     float *full_scratch = nullptr;   // slice partials of the streaming product, (slices * rows, full_scratch_ld); kept once allocated, nullptr: no room
@@ -604,6 +606,7 @@ void free_layer_buffers(nerva_layer *l)
     (void)hipFree(l->partial);
     (void)hipFree(l->dz);
     (void)hipFree(l->dense);
+    (void)hipFree(l->dense_shares);
     (void)hipFree(l->full_scratch);
 }
 
@@ -780,6 +783,8 @@ static hipError_t build_dense_copies(nerva_layer *l, hipStream_t s)
         e = launch_pattern_table(l->indptr, l->indices, nullptr, l->rows, table_words(l), reinterpret_cast<uint2 *>(l->cur.table), nullptr, s);
         if (e == hipSuccess) l->cur.has_table = true;
     }
+    if (e == hipSuccess && reserve_optional(&l->dense_shares, &l->dense_shares_floats, static_cast<size_t>(kNnShareTiles) + kNnShareFloats, false))
+        e = hipMemsetAsync(l->dense_shares, 0, kNnShareTiles * 4, s);
     if (e == hipSuccess) e = hipMemsetAsync(l->dense, 0, bytes, s);
     if (e == hipSuccess) e = launch_dense_refresh(l->indptr, l->indices, l->values, l->rows, l->dense, l->dense_ld, s);
     return e;
@@ -797,6 +802,7 @@ static hipError_t dense_forward(const nerva_layer *l, const float *X, int64_t ld
     DenseArgs d{};
     d.W = l->dense; d.ldw = l->dense_ld; d.trans = 0; d.X = X; d.ldx = ldx; d.Y = Y; d.ldy = ldy; d.bias = l->bias;
     d.rows = l->rows; d.cols = l->cols; d.batch = batch; d.relu = l->activation == NERVA_ACT_RELU;
+    if (l->dense_shares) { d.tickets = reinterpret_cast<int32_t *>(l->dense_shares); d.partial = l->dense_shares + kNnShareTiles; }
     return launch_dense_product(d, s);
 }
 

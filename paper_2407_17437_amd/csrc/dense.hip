@@ -38,141 +38,187 @@ __device__ __forceinline__ void dense_epilogue(const DenseArgs &a, int row, int 
     a.Y[static_cast<int64_t>(row) * a.ldy + col] = y;
 }
 
-// Y (rows x batch) = act(D X + b).  Work-group: 16 rows x NB * 16 columns; its kNnWaves waves split K = cols
-// into contiguous slices (multiples of 16) and meet in LDS, where wave w adds register (w % 4) of all slices in
-// slice order for the tile columns t = w / 4, w / 4 + kNnWaves / 4, ...  The loads of the next chunks of 16 k are on their way
+// Y (rows x batch) = act(D X + b).  Work-group: MB * 16 rows x NB * 16 columns; its kNnWaves waves split K = cols (or, where several work-groups
+// share a tile, their part of it) into contiguous slices of whole chunks and meet in LDS, where wave w adds register w of all slices in
+// slice order.  The loads of the next chunks of 16 k are on their way
 // while a chunk's MFMA steps run; no branch stands between them, or every wait would be for all of them (and was: 1024 x 3072 at
-// batch 512 60.9 us, 41.0 now; 2048 x 4096 at batch 256 78, 50, at 1024 279, 186; 1024 x 3072 at batch 100 16.8, 16.0).
+// batch 512 60.9 us, 41.0 without; 2048 x 4096 at batch 256 78, 50, at 1024 279, 186; 1024 x 3072 at batch 100 16.8, 16.0).  Nor does the loop ask whether
+// a chunk is whole: the last one of a K that is no multiple of 16 comes after it (1001 columns and 777 rows at batch 77 8.4, 7.2).
 // (kSplitWaves: the same split in the transposed product.)
 constexpr int kSplitWaves = 16;
 constexpr int kSplitBlock = kSplitWaves * kWave;
 
-// VECX: the NB columns of a lane are consecutive (tile t holds the columns n0 + NB * r + t), so that one
-// 8- or 16-byte load along the batch feeds the NB tiles; needs X 16-byte aligned with ldx a multiple of 4.
-// EXACT: rows and K are multiples of 16, so no operand has to be zeroed (columns beyond the batch repeat column 0
-// and their results are never stored): the MFMA steps take the loaded registers as they are.
-template <int NB>
+// The NB columns of a lane are consecutive (tile t holds the columns n0 + NB * r + t), so that one load along the batch feeds the NB
+// tiles; at the end of the batch the lane takes its last NB columns (which another lane has as well: both store the same).
+template <int MB, int NB>
 struct NnChunk {
-    float4 w4;
+    float4 w4[MB];
     float b[4][NB];
 };
 
+template <int NB>
+__device__ __forceinline__ void nn_columns(const float *p, float (&b)[NB])
+{
+    typedef float columns __attribute__((ext_vector_type(NB == 1 ? 2 : NB), aligned(4)));   // (rows of any leading dimension)
+    if constexpr (NB == 1) {
+        b[0] = *p;
+    } else {
+        const columns v = *reinterpret_cast<const columns *>(p);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) b[t] = v[t];
+    }
+}
+
 // The slice's chunks one after another; past its last one the addresses stay there (what is read again is not used).
-template <int NB, bool VECX, bool EXACT>
+template <int MB, int NB>
 struct NnReader {
-    const float *w, *x;
+    const float *w[MB], *x;
     int64_t ldx;
-    int k;       // the lane's first k of the chunk
     int left;    // chunks from this one on
 
-    __device__ __forceinline__ void load(const DenseArgs &a, const int64_t (&xcol)[NB], NnChunk<NB> &C)
+    __device__ __forceinline__ void load(NnChunk<MB, NB> &C)
     {
-        C.w4 = ld4(w);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const float *xr = EXACT || k + s < a.cols ? x + s * ldx : a.X;
-            if constexpr (VECX && NB == 4) {
-                const float4 v = ld4(xr + xcol[0]);
-                C.b[s][0] = v.x; C.b[s][1] = v.y; C.b[s][2] = v.z; C.b[s][3] = v.w;
-            } else if constexpr (VECX && NB == 2) {
-                const float2 v = *reinterpret_cast<const float2 *>(xr + xcol[0]);
-                C.b[s][0] = v.x; C.b[s][1] = v.y;
-            } else {
+        for (int m = 0; m < MB; ++m) C.w4[m] = ld4(w[m]);
 #pragma unroll
-                for (int t = 0; t < NB; ++t) C.b[s][t] = xr[xcol[t]];
-            }
-        }
+        for (int s = 0; s < 4; ++s) nn_columns<NB>(x + s * ldx, C.b[s]);
         const int step = left > 1 ? 16 : 0;   // uniform
         --left;
-        w += step; k += step; x += step * ldx;
+#pragma unroll
+        for (int m = 0; m < MB; ++m) w[m] += step;
+        x += step * ldx;
         __builtin_amdgcn_sched_barrier(0);   // chunk after chunk, or the first one's loads come last and its wait is for all
     }
 };
 
-template <int NB, bool EXACT>
-__device__ __forceinline__ void nn_mfma(bool row_ok, const bool (&col_ok)[NB], int k_left, const NnChunk<NB> &C, v4f (&acc)[NB])
+template <int MB, int NB>
+__device__ __forceinline__ void nn_mfma(const NnChunk<MB, NB> &C, v4f (&acc)[MB][NB])
 {
-    const float wv4[4] = {C.w4.x, C.w4.y, C.w4.z, C.w4.w};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int t = 0; t < NB; ++t) {
-            if constexpr (EXACT)
-                acc[t] = mfma(wv4[s], C.b[s][t], acc[t]);
-            else
-                acc[t] = mfma(row_ok ? wv4[s] : 0.f, (s < k_left && col_ok[t]) ? C.b[s][t] : 0.f, acc[t]);
+        for (int m = 0; m < MB; ++m) {
+            const float w = s == 0 ? C.w4[m].x : s == 1 ? C.w4[m].y : s == 2 ? C.w4[m].z : C.w4[m].w;
+#pragma unroll
+            for (int t = 0; t < NB; ++t) acc[m][t] = mfma(w, C.b[s][t], acc[m][t]);
         }
 }
 
 constexpr int kNnWaves = 4;   // 1024 x 3072 at batch 100, 4096 x 2048 at batch 256 with 4 / 8 / 16 waves: 16.0 / 16.5 / 17.7, 51.8 / 54.7 / 64.6 us
 constexpr int kNnBlock = kNnWaves * kWave;
 constexpr int kNnAhead = 2;    // chunks of a wave; the same with 1 / 2 / 3 / 6: 23.8 / 16.1 / 16.4 / 17.1, 52.9 / 50.8 / 51.8 / 59.9
-template <int NB, bool VECX, bool EXACT>
-__global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a)
+template <int MB, int NB>
+__global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a, const int slices)
 {
-    __shared__ float part[kNnWaves][NB][4][kWave];
+    __shared__ float part[kNnWaves][MB][NB][4][kWave];
+    __shared__ int turn_s;
     const int lane = threadIdx.x & (kWave - 1), wv = wave_id();
     const int r = lane & 15, q = lane >> 4;
     // Work-group ids go round the 8 XCDs: the column tiles of one row tile get ids 8 apart, so that they run on one
     // XCD and the rows of the copy they all read come out of its L2 after the first of them has fetched them.
     const int n_col_tiles = (a.batch + 16 * NB - 1) / (16 * NB);
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int m_tile = (slot / n_col_tiles) * 8 + xcd;
-    if (m_tile * 16 >= a.rows) return;  // (the grid is padded to whole rounds of the XCDs)
-    const int i0 = m_tile * 16, n0 = (slot % n_col_tiles) * (16 * NB);
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, in_row = n_col_tiles * slices;
+    const int m_tile = (slot / in_row) * 8 + xcd, rest = slot % in_row, col_tile = rest % n_col_tiles, slice = rest / n_col_tiles;
+    if (m_tile * 16 * MB >= a.rows) return;  // (the grid is padded to whole rounds of the XCDs)
+    const int i0 = m_tile * 16 * MB, n0 = col_tile * (16 * NB);
     const int K = a.cols;
-    const int row = i0 + r;
-    const bool row_ok = row < a.rows;
-    const float *wrow = a.W + static_cast<int64_t>(row_ok ? row : 0) * a.ldw + q * 4;
-    int64_t xcol[NB];
-    bool col_ok[NB];
-    int col[NB];
+    const int col = min(n0 + NB * r, a.batch - NB);
+    const int k16 = K / 16;                                          // whole chunks of 16 k; the rest is the last wave's
+    const int per = (k16 + kNnWaves * slices - 1) / (kNnWaves * slices);
+    const int c_begin = min((slice * kNnWaves + wv) * per, k16), c_end = min(c_begin + per, k16);
+    v4f acc[MB][NB];
 #pragma unroll
-    for (int t = 0; t < NB; ++t) {
-        col[t] = VECX ? n0 + NB * r + t : n0 + 16 * t + r;
-        col_ok[t] = col[t] < a.batch;
-        xcol[t] = col_ok[t] ? col[t] : 0;     // lanes beyond the batch re-read column 0 and contribute 0
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) acc[m][t] = v4f{0.f, 0.f, 0.f, 0.f};
+    const float *wrow[MB];   // (rows past the last one repeat the first, their results are never stored)
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int row = i0 + 16 * m + r;
+        wrow[m] = a.W + static_cast<int64_t>(row < a.rows ? row : 0) * a.ldw + q * 4;
     }
-    if constexpr (VECX) xcol[0] = col_ok[0] ? col[0] : 0;  // (the access of NB columns starts inside the row when its first column does)
-    const int k16 = (K + 15) / 16;                                   // chunks of 16 k (the copy's rows are padded with zeros)
-    const int per = (k16 + kNnWaves - 1) / kNnWaves;
-    const int c_begin = min(wv * per, k16), c_end = min(c_begin + per, k16);
-    v4f acc[NB];
+    if (c_begin < c_end) {  // uniform
+        NnChunk<MB, NB> ring[kNnAhead];
+        NnReader<MB, NB> next;
 #pragma unroll
-    for (int t = 0; t < NB; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
-    NnChunk<NB> ring[kNnAhead];
-    const int k0 = min(c_begin, k16 - 1) * 16 + q * 4;   // (a slice may be empty)
-    NnReader<NB, VECX, EXACT> next{wrow + (k0 - q * 4), a.X + static_cast<int64_t>(k0) * a.ldx, a.ldx, k0, c_end - c_begin};
-    auto multiply = [&](int c, const NnChunk<NB> &C) __attribute__((always_inline)) {
-        nn_mfma<NB, EXACT>(row_ok, col_ok, K - (c * 16 + q * 4), C, acc);
-    };
+        for (int m = 0; m < MB; ++m) next.w[m] = wrow[m] + c_begin * 16;
+        next.x = a.X + static_cast<int64_t>(c_begin * 16 + q * 4) * a.ldx + col;
+        next.ldx = a.ldx; next.left = c_end - c_begin;
 #pragma unroll
-    for (int d = 0; d < kNnAhead; ++d) next.load(a, xcol, ring[d]);
-    int c = c_begin;
-    for (; c + kNnAhead <= c_end; c += kNnAhead) {
+        for (int d = 0; d < kNnAhead; ++d) next.load(ring[d]);
+        int c = c_begin;
+        for (; c + kNnAhead <= c_end; c += kNnAhead) {
+#pragma unroll
+            for (int d = 0; d < kNnAhead; ++d) {
+                nn_mfma<MB, NB>(ring[d], acc);
+                next.load(ring[d]);
+            }
+        }
 #pragma unroll
         for (int d = 0; d < kNnAhead; ++d) {
-            multiply(c + d, ring[d]);
-            next.load(a, xcol, ring[d]);
+            if (c + d >= c_end) break;  // wave-uniform
+            nn_mfma<MB, NB>(ring[d], acc);
         }
     }
+    if (k16 * 16 < K && wv == kNnWaves - 1 && slice == slices - 1) {  // uniform
+        NnChunk<MB, NB> C;   // the operand's rows past K count as 0 (the copy holds zeros there, which an infinity would not leave zero)
 #pragma unroll
-    for (int d = 0; d < kNnAhead; ++d) {
-        if (c + d >= c_end) break;  // wave-uniform
-        multiply(c + d, ring[d]);
+        for (int m = 0; m < MB; ++m) C.w4[m] = ld4(wrow[m] + k16 * 16);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int k = k16 * 16 + q * 4 + s;
+            nn_columns<NB>(a.X + static_cast<int64_t>(min(k, K - 1)) * a.ldx + col, C.b[s]);
+#pragma unroll
+            for (int t = 0; t < NB; ++t) C.b[s][t] = k < K ? C.b[s][t] : 0.f;
+        }
+        nn_mfma<MB, NB>(C, acc);
     }
 #pragma unroll
-    for (int t = 0; t < NB; ++t)
+    for (int m = 0; m < MB; ++m)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) part[wv][t][g][lane] = acc[t][g];
+        for (int t = 0; t < NB; ++t)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) part[wv][m][t][g][lane] = acc[m][t][g];
     __syncthreads();
-    const int g = wv & 3;
-    for (int t = wv >> 2; t < NB; t += kNnWaves / 4) {
-        float y = 0.f;
+    float y[MB][NB];
 #pragma unroll
-        for (int w = 0; w < kNnWaves; ++w) y += part[w][t][g][lane];
-        dense_epilogue(a, i0 + 4 * q + g, VECX ? n0 + NB * r + t : n0 + 16 * t + r, a.rows, y);
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            y[m][t] = 0.f;
+#pragma unroll
+            for (int w = 0; w < kNnWaves; ++w) y[m][t] += part[w][m][t][wv][lane];
+        }
+    if (slices > 1) {  // uniform
+        // as the shares of a huge row (huge_row_share): out and back past the L2s, the last work-group of the tile adds them in slice order
+        constexpr int kShare = MB * NB * kNnWaves * kWave;
+        const int tile = m_tile * n_col_tiles + col_tile;
+        float *tile_shares = a.partial + static_cast<int64_t>(tile) * slices * kShare + wv * kWave + lane;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+                __hip_atomic_store(tile_shares + slice * kShare + (m * NB + t) * (kNnWaves * kWave), y[m][t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) turn_s = static_cast<int>(atomicInc(reinterpret_cast<unsigned *>(a.tickets) + tile, static_cast<unsigned>(slices - 1)));
+        __syncthreads();
+        if (turn_s != slices - 1) return;  // uniform
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int t = 0; t < NB; ++t) y[m][t] = 0.f;
+        for (int s = 0; s < slices; ++s)
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int t = 0; t < NB; ++t)
+                    y[m][t] += __hip_atomic_load(tile_shares + s * kShare + (m * NB + t) * (kNnWaves * kWave), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) dense_epilogue(a, i0 + 16 * m + 4 * q + wv, n0 + NB * r < a.batch ? col + t : a.batch, a.rows, y[m][t]);
 }
 
 // Y (cols x batch) = (D^T X) * [YM > 0].  Work-group: 64 output rows (four tiles fed by one 16-byte load along
@@ -191,13 +237,11 @@ __global__ __launch_bounds__(kSplitBlock, 8) void dense_tn_kernel(const DenseArg
     const int j0 = blockIdx.x * 64, n0 = blockIdx.y * (16 * NB);
     const int K = a.rows;
     const float *wcol = a.W + j0 + r * 4;     // (ld is a multiple of 64: the access stays inside the row)
-    int64_t xcol[NB];
-    bool col_ok[NB];
+    int64_t xcol[NB];   // (columns past the batch repeat the first: their results are never stored)
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
         const int c = n0 + 16 * t + r;
-        col_ok[t] = c < a.batch;
-        xcol[t] = col_ok[t] ? c : 0;
+        xcol[t] = c < a.batch ? c : 0;
     }
     const int k4 = (K + 3) / 4;                                     // steps of 4 k (one per slot)
     const int per = (k4 + kSplitWaves - 1) / kSplitWaves;
@@ -222,12 +266,17 @@ __global__ __launch_bounds__(kSplitBlock, 8) void dense_tn_kernel(const DenseArg
         __builtin_amdgcn_sched_barrier(0);
     };
     auto multiply = [&](int c, int d) __attribute__((always_inline)) {
-        const bool i_ok = c * 4 + q < K;
+        if (c * 4 + 4 > K) {  // uniform: the last step
+            const bool i_ok = c * 4 + q < K;
+            w4[d] = i_ok ? w4[d] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int t = 0; t < NB; ++t) b[d][t] = i_ok ? b[d][t] : 0.f;
+        }
         const float wv4[4] = {w4[d].x, w4[d].y, w4[d].z, w4[d].w};
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int t = 0; t < NB; ++t) acc[u][t] = mfma(i_ok ? wv4[u] : 0.f, (i_ok && col_ok[t]) ? b[d][t] : 0.f, acc[u][t]);
+            for (int t = 0; t < NB; ++t) acc[u][t] = mfma(wv4[u], b[d][t], acc[u][t]);
     };
 #pragma unroll
     for (int d = 0; d < kTnDepth; ++d) load(d);
@@ -742,23 +791,34 @@ static int dense_nb(int64_t m_tiles, int batch)
     return 1;
 }
 
+// Tiles of 16 mb x 16 nb and slices of the sum of a forward product.  A compute unit takes a wave's loads in at 28 cycles each (its vector
+// memory pipe was 90 % busy, the MFMA pipes 39, at 16 x 32), so tiles are as wide as 256 of them allow: 64 columns are loaded as fast as 32.  Where
+// there are a few less and the sum is long, work-groups share a tile, which costs 3 to 4 us.  us, before -> with 16 x 64 in two slices:
+// 1024 x 3072 at batch 100 15.1 -> 13.0, 1024 x 1536 10.0 -> 9.5, 2048 x 2048 at 64 11.2 -> 10.8, 2048 x 4096 at 64 19.0 -> 15.8 (512 x 1024 at 100
+// 6.2 -> 7.7); in four: 1024 x 4096 at 64 16.3 -> 11.6, 512 x 3072 at 100 12.9 -> 10.2, 512 x 2048 9.4 -> 9.0, 1024 x 2000 at 64 9.6 -> 9.1.  With 32 x 64
+// (for long sums: 4096 x 2048 at batch 1024 189 -> 193): 1024 x 3072 at 512 38.8 -> 32.0, 2048 x 4096 at 256 48.1 -> 40.0, at 1024 186 -> 178.
+struct NnCut {
+    int mb, nb, slices;
+};
+static NnCut nn_cut(const DenseArgs &a)
+{
+    const int64_t wide = (a.batch + 63) / 64, tiles = (static_cast<int64_t>(a.rows) + 15) / 16 * wide;
+    if (a.cols >= 3072 && (static_cast<int64_t>(a.rows) + 31) / 32 * wide >= 256 && a.batch >= 4) return NnCut{2, 4, 1};
+    if (a.cols >= 1536 && a.batch > 32 && a.tickets && tiles >= kNnShareTiles / 4 && tiles < kNnShareTiles) return NnCut{1, 4, tiles < kNnShareTiles / 2 ? 4 : 2};
+    int nb = dense_nb((static_cast<int64_t>(a.rows) + 15) / 16, a.batch);
+    while (nb > a.batch) nb >>= 1;   // (a lane's columns lie within the batch)
+    return NnCut{1, nb, 1};
+}
+
 hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s)
 {
     if (a.rows <= 0 || a.cols <= 0 || a.batch <= 0) return hipSuccess;
     if (!a.trans) {
-        const int64_t mt = (a.rows + 15) / 16;
-        const int nb = dense_nb(mt, a.batch);
-        const dim3 grid(static_cast<unsigned>((mt + 7) / 8 * 8 * ((a.batch + 16 * nb - 1) / (16 * nb))));
-        const bool vec = a.ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15u) == 0;
-        const bool exact = a.rows % 16 == 0 && a.cols % 16 == 0;
-        if (nb == 4 && vec && exact) hipLaunchKernelGGL((dense_nn_kernel<4, true, true>), grid, dim3(kNnBlock), 0, s, a);
-        else if (nb == 4 && vec) hipLaunchKernelGGL((dense_nn_kernel<4, true, false>), grid, dim3(kNnBlock), 0, s, a);
-        else if (nb == 4) hipLaunchKernelGGL((dense_nn_kernel<4, false, false>), grid, dim3(kNnBlock), 0, s, a);
-        else if (nb == 2 && vec && exact) hipLaunchKernelGGL((dense_nn_kernel<2, true, true>), grid, dim3(kNnBlock), 0, s, a);
-        else if (nb == 2 && vec) hipLaunchKernelGGL((dense_nn_kernel<2, true, false>), grid, dim3(kNnBlock), 0, s, a);
-        else if (nb == 2) hipLaunchKernelGGL((dense_nn_kernel<2, false, false>), grid, dim3(kNnBlock), 0, s, a);
-        else if (exact) hipLaunchKernelGGL((dense_nn_kernel<1, false, true>), grid, dim3(kNnBlock), 0, s, a);
-        else hipLaunchKernelGGL((dense_nn_kernel<1, false, false>), grid, dim3(kNnBlock), 0, s, a);
+        const NnCut cut = nn_cut(a);
+        const int64_t mt = (a.rows + 16 * cut.mb - 1) / (16 * cut.mb);
+        const dim3 grid(static_cast<unsigned>((mt + 7) / 8 * 8 * ((a.batch + 16 * cut.nb - 1) / (16 * cut.nb)) * cut.slices));
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kNnBlock), 0, s, a, cut.slices); };
+        go(cut.mb == 2 ? dense_nn_kernel<2, 4> : cut.nb == 4 ? dense_nn_kernel<1, 4> : cut.nb == 2 ? dense_nn_kernel<1, 2> : dense_nn_kernel<1, 1>);
     } else {
         // (one tile column per work-group: the 16 slices of 4 x 4 registers already take 64 KiB of LDS)
         const dim3 grid(static_cast<unsigned>((a.cols + 63) / 64), (a.batch + 15) / 16);

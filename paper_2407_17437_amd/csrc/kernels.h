@@ -323,7 +323,10 @@ struct DenseArgs {
     int64_t ldym;
     int32_t rows, cols, batch;
     int32_t relu;
+    float *partial;      // forward: kNnShareFloats floats and kNnShareTiles zeros (as the product leaves them), for tiles that several work-groups
+    int32_t *tickets;    //   share; or nullptr: none is shared
 };
+constexpr int32_t kNnShareTiles = 256, kNnShareFloats = 2 * kNnShareTiles * 1024;   // (less than 2 * kNnShareTiles work-groups, 16 x 64 sums each)
 hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s);
 // Gradient and update of up to kSampledLayers layers in one grid: G = dZ X^T in MFMA tiles, of which the entries on the
 // pattern are stored or take the momentum step (sampled_update_kernel in dense.hip).

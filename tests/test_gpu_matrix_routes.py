@@ -54,9 +54,36 @@ def test_sampled_gradient(nb, oracle, rows, cols, density, batch, ld):
     # slices of the sum that are empty, one chunk, whole rounds of chunks and one more; 1, 2 and 4 tiles of 16 columns to a work-group
     (16, 16, 1, None), (17, 33, 5, 5), (48, 80, 16, None), (1041, 129, 33, 33), (1024, 256, 100, None), (1039, 271, 99, 99),
     (1024, 320, 256, None), (1030, 330, 130, None), (1090, 61, 257, 257),
+    # tiles of 64 columns shared by two and four work-groups, and tiles of 32 rows
+    (1024, 1536, 65, None), (1041, 1551, 97, 97), (1024, 1536, 33, None), (1009, 1549, 63, 63), (2049, 3073, 200, None),
 ])
 def test_products_of_the_dense_copy(nb, oracle, rows, cols, batch, ld):
     check_layer(nb, oracle, layer_case(rows, cols, 0.6, seed=rows + batch), batch, ld=ld)
+
+
+@pytest.mark.parametrize("rows,cols,batch", [(1041, 1551, 97), (1009, 1549, 63)])
+def test_shared_tiles_of_the_dense_copy_come_out_the_same_again(nb, oracle, rows, cols, batch):
+    """... whichever work-group was last, with an infinity in the operand's last row and with its neighbour NaN outside the batch."""
+    import torch
+    lay = layer_case(rows, cols, 0.6, seed=7, relu=False)
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal((cols, batch)).astype(np.float32)
+    L = nb.SparseLinear(lay, max_batch=batch)
+    Xd = torch.full((cols, batch + 3), float("nan"), device="cuda")[:, :batch]
+    Xd.copy_(torch.from_numpy(X))
+    Ys = [nb.dense(rows, batch) for _ in range(4)]
+    for Yd in Ys[:3]:
+        nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+    want, S = oracle.spmm(rows, cols, lay.indptr, lay.indices, lay.values, lay.bias, X, False)
+    close(Ys[0].cpu().numpy(), want, S, what="Y")
+    assert all(torch.equal(Ys[0], Yd) for Yd in Ys[1:3])
+    Xd[cols - 1, 5] = float("inf")
+    nb.sparse_linear_forward(L.handle, Xd, Ys[3], batch)
+    held = np.arange(batch) != 5
+    assert np.array_equal(Ys[3].cpu().numpy()[:, held], Ys[0].cpu().numpy()[:, held])
+    stored = lay.indices[lay.indptr[1:][np.diff(lay.indptr) > 0] - 1] == cols - 1
+    assert not np.isfinite(Ys[3].cpu().numpy()[np.diff(lay.indptr) > 0][stored, 5]).any()
+    L.close()
 
 
 def mixed_rows(rows, cols, n_dense, density, seed, relu=False):
