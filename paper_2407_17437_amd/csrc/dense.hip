@@ -223,28 +223,25 @@ __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a, c
 
 // Y (cols x batch) = (D^T X) * [YM > 0].  Work-group: 64 output rows (four tiles fed by one 16-byte load along
 // the row of D: tile u holds the output rows j0 + 4 r' + u) x NB * 16 columns; the waves split K = rows, kTnDepth
-// steps of loads in flight.  Wave w adds tile (w / 4), register (w % 4) of all slices in slice order.  64 registers, so that two
-// work-groups fit on a compute unit: (512 x 1024 at batch 100, 2048 x 4096 at batch 256) 6.1 and 58 us, with 78 7.2 and 66.5; eight steps
-// requested and then multiplied 7.1 and 63.8.
+// steps of loads in flight.  Wave w adds tile (w / 4), register (w % 4) of all slices in slice order.  Two work-groups fit on a compute unit
+// (64 registers with one column tile: (512 x 1024 at batch 100, 2048 x 4096 at batch 256) 6.1 and 58 us, with 78 7.2 and 66.5; eight steps
+// requested and then multiplied 7.1 and 63.8).  The more columns of the batch a work-group has, the fewer loads there are to a product, each of
+// which holds the compute unit's vector memory pipe; it has as many waves less, so that their slices fit in LDS.
 constexpr int kTnDepth = 3;
 
 template <int NB>
-__global__ __launch_bounds__(kSplitBlock, 8) void dense_tn_kernel(const DenseArgs a)
+__global__ __launch_bounds__(kSplitBlock / NB, 8 / NB) void dense_tn_kernel(const DenseArgs a)
 {
-    __shared__ float part[kSplitWaves][4][NB][4][kWave];
+    constexpr int kWaves = kSplitWaves / NB;
+    __shared__ float part[kWaves][4][NB][4][kWave];
     const int lane = threadIdx.x & (kWave - 1), wv = wave_id();
     const int r = lane & 15, q = lane >> 4;
     const int j0 = blockIdx.x * 64, n0 = blockIdx.y * (16 * NB);
     const int K = a.rows;
     const float *wcol = a.W + j0 + r * 4;     // (ld is a multiple of 64: the access stays inside the row)
-    int64_t xcol[NB];   // (columns past the batch repeat the first: their results are never stored)
-#pragma unroll
-    for (int t = 0; t < NB; ++t) {
-        const int c = n0 + 16 * t + r;
-        xcol[t] = c < a.batch ? c : 0;
-    }
+    const int col = min(n0 + NB * r, a.batch - NB);
     const int k4 = (K + 3) / 4;                                     // steps of 4 k (one per slot)
-    const int per = (k4 + kSplitWaves - 1) / kSplitWaves;
+    const int per = (k4 + kWaves - 1) / kWaves;
     const int c_begin = min(wv * per, k4), c_end = min(c_begin + per, k4);
     v4f acc[4][NB];
 #pragma unroll
@@ -254,12 +251,11 @@ __global__ __launch_bounds__(kSplitBlock, 8) void dense_tn_kernel(const DenseArg
     float4 w4[kTnDepth];
     float b[kTnDepth][NB];
     int i = min(c_begin, k4 - 1) * 4 + q, left = c_end - c_begin - 1;   // (a slice may be empty)
-    const float *wp = wcol + i * a.ldw, *xp = a.X + i * a.ldx;
+    const float *wp = wcol + i * a.ldw, *xp = a.X + i * a.ldx + col;
     auto load = [&](int d) __attribute__((always_inline)) {   // as in NnReader: step after step, the last one again past the end
         const bool ok = i < K;
         w4[d] = ld4(ok ? wp : wcol);
-#pragma unroll
-        for (int t = 0; t < NB; ++t) b[d][t] = (ok ? xp : a.X)[xcol[t]];
+        nn_columns<NB>(ok ? xp : a.X, b[d]);
         const int step = left > 0 ? 4 : 0;   // uniform
         --left;
         i += step; wp += step * a.ldw; xp += step * a.ldx;
@@ -300,14 +296,16 @@ __global__ __launch_bounds__(kSplitBlock, 8) void dense_tn_kernel(const DenseArg
 #pragma unroll
             for (int g = 0; g < 4; ++g) part[wv][u][t][g][lane] = acc[u][t][g];
     __syncthreads();
-    const int u = wv >> 2, g = wv & 3;
+    const int g = wv & 3;
 #pragma unroll
-    for (int t = 0; t < NB; ++t) {
-        float y = 0.f;
+    for (int u = wv >> 2; u < 4; u += kWaves / 4)
 #pragma unroll
-        for (int w = 0; w < kSplitWaves; ++w) y += part[w][u][t][g][lane];
-        dense_epilogue(a, j0 + 4 * (4 * q + g) + u, n0 + 16 * t + r, a.cols, y);
-    }
+        for (int t = 0; t < NB; ++t) {
+            float y = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) y += part[w][u][t][g][lane];
+            dense_epilogue(a, j0 + 4 * (4 * q + g) + u, n0 + NB * r < a.batch ? col + t : a.batch, a.cols, y);
+        }
 }
 
 // Sampled gradient: G = dZ X^T by MFMA tiles, of which only the entries on the pattern are used -- each tile takes the
@@ -820,9 +818,14 @@ hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s)
         auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kNnBlock), 0, s, a, cut.slices); };
         go(cut.mb == 2 ? dense_nn_kernel<2, 4> : cut.nb == 4 ? dense_nn_kernel<1, 4> : cut.nb == 2 ? dense_nn_kernel<1, 2> : dense_nn_kernel<1, 1>);
     } else {
-        // (one tile column per work-group: the 16 slices of 4 x 4 registers already take 64 KiB of LDS)
-        const dim3 grid(static_cast<unsigned>((a.cols + 63) / 64), (a.batch + 15) / 16);
-        hipLaunchKernelGGL(dense_tn_kernel<1>, grid, dim3(kSplitBlock), 0, s, a);
+        // One, two or four tiles of 16 columns, us: 2048 x 4096 at batch 256 54.9 / 47.7 / 50.3 (512 and 256 work-groups), at 1024 192 / 161 / 153;
+        // 1024 x 4096 at 512 57.7 / 48.7 / 47.2, 4096 x 4096 at 100 53.8 / 49.6 with two, 1201 x 2201 at 301 33.8 / 29.0.
+        const int64_t across = (static_cast<int64_t>(a.cols) + 63) / 64;
+        const int nb = a.batch >= 4 && across * ((a.batch + 63) / 64) >= 512 ? 4 : a.batch >= 2 && across * ((a.batch + 31) / 32) >= 256 ? 2 : 1;
+        const dim3 grid(static_cast<unsigned>(across), (a.batch + 16 * nb - 1) / (16 * nb)), block(kSplitBlock / nb);
+        if (nb == 4) hipLaunchKernelGGL(dense_tn_kernel<4>, grid, block, 0, s, a);
+        else if (nb == 2) hipLaunchKernelGGL(dense_tn_kernel<2>, grid, block, 0, s, a);
+        else hipLaunchKernelGGL(dense_tn_kernel<1>, grid, block, 0, s, a);
     }
     return hipGetLastError();
 }

@@ -56,6 +56,8 @@ def test_sampled_gradient(nb, oracle, rows, cols, density, batch, ld):
     (1024, 320, 256, None), (1030, 330, 130, None), (1090, 61, 257, 257),
     # tiles of 64 columns shared by two and four work-groups, and tiles of 32 rows
     (1024, 1536, 65, None), (1041, 1551, 97, 97), (1024, 1536, 33, None), (1009, 1549, 63, 63), (2049, 3073, 200, None),
+    # two and four tiles of columns in the transposed product
+    (67, 2049, 257, 257), (70, 4100, 511, None), (65, 16384, 33, None),
 ])
 def test_products_of_the_dense_copy(nb, oracle, rows, cols, batch, ld):
     check_layer(nb, oracle, layer_case(rows, cols, 0.6, seed=rows + batch), batch, ld=ld)
