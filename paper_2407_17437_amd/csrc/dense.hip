@@ -13,8 +13,8 @@
 // step; register r of lane l holds C(4 * (l / 16) + r, l % 16).  A lane's four k slots need not be
 // consecutive k as long as A and B agree, so one 16-byte load along k feeds four steps (slot q of
 // step s: k = base + 4 q + s), and one 16-byte load along the output rows feeds four tiles (tile u
-// holds the rows base + 4 r + u).  Small tiles (16 rows) on purpose: these products are a few hundred
-// MFLOP, and only thousands of tiles fill 1024 matrix units.  Every sum has one fixed order.
+// holds the rows base + 4 r + u).  Small tiles on purpose: these products are a few hundred
+// MFLOP, and only thousands of waves fill 1024 matrix units.  Every sum has one fixed order.
 #include "device.h"
 #include "kernels.h"
 

@@ -308,8 +308,10 @@ hipError_t launch_copy(float *dst, const float *src, int64_t n, hipStream_t s);
 // entries is sampled from tiles of G = dZ X^T (SampledLayer below), which is never stored.
 constexpr int32_t kDenseLdAlign = 64;
 constexpr float kTableFromDensity = 0.15f;  // layers at least this dense get a pattern table when they are bound
-constexpr float kDenseFromDensity = 0.4f;   // layers at least this dense take the dense route by themselves (steps of 3072-1024-512-10, batch 100, dense /
-                                            // sparse route: 58.8 / 79.3 us at 50 % density, 53.8 / 56.9 at 20 %: the line lay at 40 % before both sampled the gradient)
+// Layers at least this dense take the dense route by themselves.  Steps of 3072-1024-512-10 at batch 100, dense / sparse route: 53.7 / 79.3 us at
+// 50 % density, 51.9 / 81.0 at 40 %, 48.5 / 57.0 at 20 %; 2048-4096-2048-10 at batch 64 127 / 314, 121 / 264, 105 / 149, at 1024 857 / 843, 847 / 770, 833 / 654:
+// below the line the dense route would be the faster one for narrow batches too, but an infinity in an operand reaches every row on it.
+constexpr float kDenseFromDensity = 0.4f;
 struct DenseArgs {
     const float *W;      // the dense copy, (rows, ldw)
     int64_t ldw;

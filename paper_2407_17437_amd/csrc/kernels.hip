@@ -452,8 +452,6 @@ __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int bl
     }
 }
 
-// Short rows through the packed body, the remaining rows through the grouped body, in one grid,
-// for every column tile; work-group ids are decoded XCD-first as in spmm_tiled_kernel.
 // Which column tile, and which of the launch's n_blocks work-groups of rows, a work-group serves.  Without runs: tile by tile, all XCDs on one tile.  Otherwise
 // the list of all of them is cut into eight equal runs, one per XCD (work-groups go to the XCDs in turn), so that an L2 sees an eighth of
 // the tiles and one more; the stride, which has no factor in common with n_blocks, is the order within a tile.  (tile_order chooses.)
@@ -471,6 +469,7 @@ __device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, TileOrd
     return tile < n_tiles;
 }
 
+// Short rows through the packed body, the remaining rows through the grouped body, in one grid, for every column tile.
 template <int GS, bool XMASK>
 __global__ __launch_bounds__(kBlock) void spmm_packed_kernel(const SpmmArgs a, const int n_tiles, const TileOrder order,
                                                              const int n_pack_blocks)
@@ -495,10 +494,7 @@ __global__ __launch_bounds__(kBlock) void spmm_grouped_kernel(const SpmmArgs a)
 
 // Column-tiled launch for dense operands that do not fit an L2: the batch is cut into tiles of
 // GS*4 columns, narrow enough that one tile of the whole operand (x_rows x GS*4 floats) stays
-// resident in a 4 MiB L2 while every stored entry gathers from it.  Work-groups are dealt to the
-// 8 XCDs round-robin by their id, so the id is decoded XCD-first: with 8 or more tiles each XCD
-// owns every 8th tile (each tile is fetched from HBM by one L2 only) and sweeps the row partition
-// once per tile; with fewer tiles every XCD walks all tiles in the same order.
+// resident in a 4 MiB L2 while every stored entry gathers from it.  TileOrder says which XCD works on which tiles.
 template <int GS, bool XMASK>
 __global__ __launch_bounds__(kBlock) void spmm_tiled_kernel(const SpmmArgs a, const int n_tiles, const TileOrder order)
 {
@@ -1265,8 +1261,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 
 // Column-tiled SDDMM for operands X that no L2 holds: tile t covers columns [t*W, t*W + W), W =
 // G*4*NV; a work-group computes the partial products of its rows over one tile and stores them (and the partial row
-// sums of dZ) in the tile's slice of the partial buffer.  Work-group ids are decoded XCD-first as
-// in spmm_tiled_kernel, so an operand tile stays in one L2 while every entry gathers from it.
+// sums of dZ) in the tile's slice of the partial buffer.  Tiles go to the XCDs as in spmm_tiled_kernel, so that an operand
+// tile stays in one L2 while every entry gathers from it.
 template <int G, int NV, bool SPARE>
 __global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order)
 {
