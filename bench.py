@@ -63,8 +63,6 @@ def slot_bytes(name: str, layer, batch: int, has_mirror_scatter: bool) -> float:
     if kind == "backward_fused":      # transposed product and SDDMM + update of one layer on one gather stream: mirror pattern,
         # values and position map, dZ in once, the layer's input in once (mask and second operand), dX out, the update
         return 12 * nnz + 4 * (k + 1) + 4 * n * m + 4 * n * k + 4 * n * k + 16 * nnz + 4 * nnz + 16 * m
-    if kind == "backward_chain":      # the same for layer 1 with the gradient and update of layer 0 behind it (whose own state is not counted here)
-        return 12 * nnz + 4 * (k + 1) + 4 * n * m + 4 * n * k + 4 * n * k + 16 * nnz + 4 * nnz + 16 * m
     if kind == "backward_full":       # the same for a full matrix of few rows, streamed: dZ in, the layer's input in once, dX out, the update
         return 4 * n * m + 4 * n * k + 4 * n * k + 16 * nnz + 8 * nnz + 16 * m
     if kind == "sddmm":
@@ -218,8 +216,15 @@ def measure_mlp(env, name: str, K: int, W: int, profile_steps: int, args, copy_g
             kinds = slot.split("[")[0].split("+")
             if len(kinds) == 3:
                 kinds = ["+".join(kinds)]
-            byt = slot_bytes(kinds[0], M.layers[l], batch, has_mirror_scatter=(l > 0))
-            gat = slot_gather_bytes(kinds[0], M.layers[l], batch)
+            if kinds[0] == "backward_chain":
+                # the rest of the step: the backward pass of layer 1, gradient and update of layer 0 (whose dZ is not read
+                # again) and of the output layer
+                parts = [("backward_fused", l)] + [("sddmm_update", i) for i in (l - 1, l + 1) if i < len(M.layers)]
+                byt = sum(slot_bytes(kind, M.layers[i], batch, has_mirror_scatter=(i > 0)) for kind, i in parts) - 4 * batch * M.layers[l - 1].rows
+                gat = sum(slot_gather_bytes(kind, M.layers[i], batch) for kind, i in parts)
+            else:
+                byt = slot_bytes(kinds[0], M.layers[l], batch, has_mirror_scatter=(l > 0))
+                gat = slot_gather_bytes(kinds[0], M.layers[l], batch)
             if len(kinds) == 2 and kinds[1] == "softmax_ce":      # the loss gradient formed by the product's finish pass: same layer
                 byt += slot_bytes(kinds[1], M.layers[l], batch, has_mirror_scatter=False)
             elif len(kinds) == 2:
