@@ -147,8 +147,7 @@ struct nerva_layer {
     bool dense_on = false;
     float *dense = nullptr;
     int64_t dense_ld = 0;
-    float *dense_shares = nullptr;   // scratch of its forward product (DenseArgs::tickets, then ::partial), or nullptr
-    size_t dense_shares_floats = 0;
+    float *dense_shares = nullptr;   // behind it, scratch of its forward product (DenseArgs::tickets, then ::partial), or nullptr
     // owned, only for a matrix that stores every entry and has at most kFullMaxRows rows
     bool full = false;               // the bound pattern is such a matrix
     float *full_scratch = nullptr;   // slice partials of the streaming product, (slices * rows, full_scratch_ld); kept once allocated, nullptr: no room
@@ -606,7 +605,6 @@ void free_layer_buffers(nerva_layer *l)
     (void)hipFree(l->partial);
     (void)hipFree(l->dz);
     (void)hipFree(l->dense);
-    (void)hipFree(l->dense_shares);
     (void)hipFree(l->full_scratch);
 }
 
@@ -778,14 +776,20 @@ static hipError_t build_dense_copies(nerva_layer *l, hipStream_t s)
 {
     l->dense_ld = round_up(l->cols, kDenseLdAlign);
     const size_t bytes = static_cast<size_t>(l->rows) * l->dense_ld * 4;
-    hipError_t e = hipMalloc(&l->dense, bytes);
+    // behind the copy: tickets and shares of tiles that several work-groups form (one allocation: each costs a create a quarter of a millisecond)
+    size_t tickets = dense_shares_possible(l->rows, l->cols, l->max_batch) ? kNnShareTiles * 4 : 0;
+    hipError_t e = hipMalloc(&l->dense, bytes + tickets + (tickets ? static_cast<size_t>(kNnShareFloats) * 4 : 0));
+    if (e != hipSuccess && tickets) {
+        (void)hipGetLastError();
+        tickets = 0;
+        e = hipMalloc(&l->dense, bytes);
+    }
+    l->dense_shares = e == hipSuccess && tickets ? l->dense + bytes / 4 : nullptr;
     if (e == hipSuccess && !l->cur.has_table && reserve_optional(&l->cur.table, &l->cur.table_ints, static_cast<size_t>(l->rows) * table_words(l) * 2)) {
         e = launch_pattern_table(l->indptr, l->indices, nullptr, l->rows, table_words(l), reinterpret_cast<uint2 *>(l->cur.table), nullptr, s);
         if (e == hipSuccess) l->cur.has_table = true;
     }
-    if (e == hipSuccess && reserve_optional(&l->dense_shares, &l->dense_shares_floats, static_cast<size_t>(kNnShareTiles) + kNnShareFloats, false))
-        e = hipMemsetAsync(l->dense_shares, 0, kNnShareTiles * 4, s);
-    if (e == hipSuccess) e = hipMemsetAsync(l->dense, 0, bytes, s);
+    if (e == hipSuccess) e = hipMemsetAsync(l->dense, 0, bytes + tickets, s);
     if (e == hipSuccess) e = launch_dense_refresh(l->indptr, l->indices, l->values, l->rows, l->dense, l->dense_ld, s);
     return e;
 }
@@ -1089,7 +1093,7 @@ static int enable_dense(nerva_layer *layer, hipStream_t s)
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(layer->dense);
-        layer->dense = nullptr;
+        layer->dense = layer->dense_shares = nullptr;
         return hip_fail(e, "sparse_linear_enable_dense");
     }
     layer->dense_on = true;

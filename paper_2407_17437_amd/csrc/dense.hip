@@ -802,7 +802,7 @@ static NnCut nn_cut(const DenseArgs &a)
 {
     const int64_t wide = (a.batch + 63) / 64, tiles = (static_cast<int64_t>(a.rows) + 15) / 16 * wide;
     if (a.cols >= 3072 && (static_cast<int64_t>(a.rows) + 31) / 32 * wide >= 256 && a.batch >= 4) return NnCut{2, 4, 1};
-    if (a.cols >= 1536 && a.batch > 32 && a.tickets && tiles >= kNnShareTiles / 4 && tiles < kNnShareTiles) return NnCut{1, 4, tiles < kNnShareTiles / 2 ? 4 : 2};
+    if (a.cols >= kNnShareCols && a.batch > 32 && a.tickets && tiles >= kNnShareTiles / 4 && tiles < kNnShareTiles) return NnCut{1, 4, tiles < kNnShareTiles / 2 ? 4 : 2};
     int nb = dense_nb((static_cast<int64_t>(a.rows) + 15) / 16, a.batch);
     while (nb > a.batch) nb >>= 1;   // (a lane's columns lie within the batch)
     return NnCut{1, nb, 1};

@@ -329,6 +329,13 @@ struct DenseArgs {
     int32_t *tickets;    //   share; or nullptr: none is shared
 };
 constexpr int32_t kNnShareTiles = 256, kNnShareFloats = 2 * kNnShareTiles * 1024;   // (less than 2 * kNnShareTiles work-groups, 16 x 64 sums each)
+constexpr int32_t kNnShareCols = 1536;
+// whether some batch of up to max_batch columns has tiles shared (nn_cut)
+inline bool dense_shares_possible(int32_t rows, int32_t cols, int32_t max_batch)
+{
+    const int64_t across = (static_cast<int64_t>(rows) + 15) / 16;
+    return cols >= kNnShareCols && max_batch > 32 && across < kNnShareTiles && across * ((static_cast<int64_t>(max_batch) + 63) / 64) >= kNnShareTiles / 4;
+}
 hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s);
 // Gradient and update of up to kSampledLayers layers in one grid: G = dZ X^T in MFMA tiles, of which the entries on the
 // pattern are stored or take the momentum step (sampled_update_kernel in dense.hip).
