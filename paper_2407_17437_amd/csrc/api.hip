@@ -777,7 +777,7 @@ static hipError_t build_dense_copies(nerva_layer *l, hipStream_t s)
     l->dense_ld = round_up(l->cols, kDenseLdAlign);
     const size_t bytes = static_cast<size_t>(l->rows) * l->dense_ld * 4;
     // behind the copy: tickets and shares of tiles that several work-groups form (one allocation: each costs a create a quarter of a millisecond)
-    size_t tickets = dense_shares_possible(l->rows, l->cols, l->max_batch) ? kNnShareTiles * 4 : 0;
+    size_t tickets = dense_shares_possible(l->rows, l->cols, l->max_batch) ? kNnTickets * 4 : 0;
     hipError_t e = hipMalloc(&l->dense, bytes + tickets + (tickets ? static_cast<size_t>(kNnShareFloats) * 4 : 0));
     if (e != hipSuccess && tickets) {
         (void)hipGetLastError();
@@ -806,7 +806,7 @@ static hipError_t dense_forward(const nerva_layer *l, const float *X, int64_t ld
     DenseArgs d{};
     d.W = l->dense; d.ldw = l->dense_ld; d.trans = 0; d.X = X; d.ldx = ldx; d.Y = Y; d.ldy = ldy; d.bias = l->bias;
     d.rows = l->rows; d.cols = l->cols; d.batch = batch; d.relu = l->activation == NERVA_ACT_RELU;
-    if (l->dense_shares) { d.tickets = reinterpret_cast<int32_t *>(l->dense_shares); d.partial = l->dense_shares + kNnShareTiles; }
+    if (l->dense_shares) { d.tickets = reinterpret_cast<int32_t *>(l->dense_shares); d.partial = l->dense_shares + kNnTickets; }
     return launch_dense_product(d, s);
 }
 

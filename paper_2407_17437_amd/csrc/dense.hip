@@ -815,7 +815,9 @@ hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s)
         const NnCut cut = nn_cut(a);
         const int64_t mt = (a.rows + 16 * cut.mb - 1) / (16 * cut.mb);
         const dim3 grid(static_cast<unsigned>((mt + 7) / 8 * 8 * ((a.batch + 16 * cut.nb - 1) / (16 * cut.nb)) * cut.slices));
-        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kNnBlock), 0, s, a, cut.slices); };
+        DenseArgs own = a;
+        if (cut.slices == 4) own.tickets += kNnShareTiles;
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kNnBlock), 0, s, own, cut.slices); };
         go(cut.mb == 2 ? dense_nn_kernel<2, 4> : cut.nb == 4 ? dense_nn_kernel<1, 4> : cut.nb == 2 ? dense_nn_kernel<1, 2> : dense_nn_kernel<1, 1>);
     } else {
         // One, two or four tiles of 16 columns, us: 2048 x 4096 at batch 256 54.9 / 47.7 / 50.3 (512 and 256 work-groups), at 1024 192 / 161 / 153;

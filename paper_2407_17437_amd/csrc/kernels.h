@@ -327,10 +327,13 @@ struct DenseArgs {
     int64_t ldym;
     int32_t rows, cols, batch;
     int32_t relu;
-    float *partial;      // forward: kNnShareFloats floats and kNnShareTiles zeros (as the product leaves them), for tiles that several work-groups
+    float *partial;      // forward: kNnShareFloats floats and kNnTickets zeros (as the product leaves them), for tiles that several work-groups
     int32_t *tickets;    //   share; or nullptr: none is shared
 };
 constexpr int32_t kNnShareTiles = 256, kNnShareFloats = 2 * kNnShareTiles * 1024;   // (less than 2 * kNnShareTiles work-groups, 16 x 64 sums each)
+// A ticket always counts up to the same number: with one set for tiles in two and in four slices, calls of different batches that overlap
+// would leave it between the two, and calls after them would find it there.
+constexpr int32_t kNnTickets = kNnShareTiles + kNnShareTiles / 2;                   // of tiles in two slices, then in four (nn_cut)
 constexpr int32_t kNnShareCols = 1536;
 // whether some batch of up to max_batch columns has tiles shared (nn_cut)
 inline bool dense_shares_possible(int32_t rows, int32_t cols, int32_t max_batch)

@@ -19,7 +19,8 @@ std::map<const void *, std::string> kernels;
 std::string launched;
 PlanCounts counts[2];
 long calls_until_failure = -1;   // of the calls that allocate, fill or wait
-int bad_pointers = 0, dirty_tickets = 0;
+int bad_pointers = 0, dirty_tickets = 0, mixed_tickets = 0;
+std::map<const int32_t *, int> ticket_ends;   // what each ticket of a shared tile counts up to
 size_t live_bytes = 0;
 hipError_t last = hipSuccess;
 
@@ -70,6 +71,7 @@ void fake_fail_after(long calls) { calls_until_failure = calls; }
 long fake_fail_after_left() { return calls_until_failure; }
 int fake_bad_pointers() { return bad_pointers; }
 int fake_dirty_tickets() { return dirty_tickets; }
+int fake_mixed_tickets() { return mixed_tickets; }
 size_t fake_live_bytes() { return live_bytes; }
 const char *fake_launched() { static std::string out; out.swap(launched); launched.clear(); return out.c_str(); }
 int fake_set(int side, const char *field, int value)
@@ -120,7 +122,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
     *grid = config_grid; *block = config_block; *lds = config_lds; *s = config_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *kernel, dim3, dim3, void **args, size_t, hipStream_t)
+hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3, void **args, size_t, hipStream_t)
 {
     const std::string &name = kernels[kernel];
     launched += name + "\n";
@@ -141,6 +143,19 @@ hipError_t hipLaunchKernel(const void *kernel, dim3, dim3, void **args, size_t, 
         check(args[0], sizeof(BackwardArgs));
     } else if (takes("11SampledArgs")) {
         check(args[0], sizeof(SampledArgs));
+    } else if (takes("dense_nn_kernel")) {
+        const DenseArgs &a = *static_cast<const DenseArgs *>(args[0]);
+        const int slices = *static_cast<const int *>(args[1]);
+        check(&a, sizeof a);
+        if (slices > 1) {
+            const int64_t tiles = (static_cast<int64_t>(a.rows) + 15) / 16 * ((a.batch + 63) / 64);
+            if (tiles * slices > grid.x || !holds(a.tickets, tiles * 4) || !holds(a.partial, tiles * slices * 1024 * 4)) ++bad_pointers;
+            else
+                for (int64_t k = 0; k < tiles; ++k) {
+                    dirty_tickets += a.tickets[k] != 0;
+                    mixed_tickets += ticket_ends.emplace(a.tickets + k, slices).first->second != slices;
+                }
+        }
     } else if (takes("plan_kernel")) {
         const PlanArgs &p = *static_cast<const PlanArgs *>(args[0]);
         memset(p.result, 0, sizeof(BindResult));

@@ -242,6 +242,30 @@ def test_huge_rows_after_products_that_overlapped(nb, oracle):
     L.close()
 
 
+def test_shared_tiles_after_products_that_overlapped(nb, oracle):
+    """The same of tiles of the dense copy that work-groups share, two at some batches and four at others, all of them in flight at once."""
+    import torch
+    rows, cols, batches = 1024, 1551, (100, 64, 97, 33)
+    lay = layer_case(rows, cols, 0.6, seed=8, relu=False)
+    rng = np.random.default_rng(9)
+    L = nb.SparseLinear(lay, max_batch=100)
+    Xs = [rng.standard_normal((cols, batch)).astype(np.float32) for batch in batches]
+    Xd, Yd = [nb.to_dense(X) for X in Xs], [nb.dense(rows, batch) for batch in batches]
+    streams = [torch.cuda.Stream() for _ in batches]
+    torch.cuda.synchronize()
+    for _ in range(200):
+        for s, X, Y, batch in zip(streams, Xd, Yd, batches):
+            nb.sparse_linear_forward(L.handle, X, Y, batch, s)
+    torch.cuda.synchronize()
+    for X, x, Y, batch in zip(Xs, Xd, Yd, batches):
+        Y.fill_(float("nan"))
+        nb.sparse_linear_forward(L.handle, x, Y, batch)
+        torch.cuda.synchronize()
+        want, S = oracle.spmm(rows, cols, lay.indptr, lay.indices, lay.values, lay.bias, X, False)
+        close(Y.cpu().numpy(), want, S, what=f"Y at batch {batch}")
+    L.close()
+
+
 def with_infinities(rng, features, batch):
     """Every third row holds an infinity: in the first column, which idle lanes re-read, or in one of the last four, which the lanes
     of a ragged batch share."""

@@ -119,6 +119,19 @@ def wide_products_of_dense_rows_take_the_bf16_units(L):
             L.destroy()
 
 
+def a_ticket_of_a_shared_tile_counts_to_one_number(L):
+    """1024 x 3072 on the dense route: tiles in four slices up to 64 columns of the batch, in two from there to 192.  The calls of both
+    may overlap, and a ticket that both counted on, modulo 4 and modulo 2, would not be back at 0 after them."""
+    L.counts(0, n_blocks=64, longest_row=1600)
+    L.counts(1, n_blocks=64, longest_row=600)
+    assert L.create(1024, 3072, 1600000, 200) == 0
+    for batch in (64, 100, 33, 192, 200, 64):
+        assert L.forward(batch) == 0
+    assert any("dense_nn_kernel" in k for k in L.launched())
+    assert L.hip.fake_bad_pointers() == 0 and L.hip.fake_dirty_tickets() == 0 and L.hip.fake_mixed_tickets() == 0
+    L.destroy()
+
+
 def a_layer_is_created_without_what_it_can_do_without(L):
     """Dense rows with sliced results, a staged plan for the batches below theirs, partial products, dZ of a ReLU layer: each of them
     fails once.  (The calls fail one after another; those whose failure the create survives are these.)"""
@@ -156,7 +169,7 @@ def a_single_tile_needs_no_partial_products(L):
     assert held[1] - held[0] == 1024 * (128 - 64) * 4, held   # (dZ, whose rows are 128 and 64 columns apart)
 
 
-CASES = [wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
