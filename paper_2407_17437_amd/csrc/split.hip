@@ -1,5 +1,6 @@
 // Products on the bf16 matrix units at fp32 precision.
-// An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits of its 24: x = h + m + l exactly), so a product of two is the
+// An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits of its 24: x = h + m + l exactly, unless x is so small, from 2^-110 down, that its
+// last bits lie below the smallest bf16 number; blocks that hold such a number are left to fp32), so a product of two is the
 // sum of nine products of which three (m l, l m, l l: below 2^-24 of it) are left out.  The bf16 units multiply exactly
 // into fp32 and are 12 times as fast as the fp32 ones (1.73 against 0.14 PFLOP/s from registers on this card), so the six
 // products that are formed take half the time.  h h is added up in one accumulator and the five small ones in another, which
@@ -29,19 +30,18 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) { return __built
 __device__ __forceinline__ float low_half(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float high_half(uint32_t p) { return __builtin_bit_cast(float, p & 0xFFFF0000u); }
 
-// Numbers a and b become pair `i` of the parts.  `zero` stays 0 as long as every number's three parts are finite: not for an Inf, a NaN or one
-// that rounds to an Inf in bf16.
+// Numbers a and b become pair `i` of the parts.  `zero` stays 0 as long as every number is the sum of its three parts: not for an Inf, a NaN, one
+// that rounds to an Inf in bf16 or one too small.  (The units take and give subnormal numbers as they are.)
 __device__ __forceinline__ void split_pair(float a, float b, v4u (&part)[3], int i, float &zero)
 {
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
         const uint32_t h = bf16_pair(a, b);
         part[p][i] = h;
-        if (p == 2) break;
         a -= low_half(h);
         b -= high_half(h);
     }
-    zero = fmaf(a, 0.f, fmaf(b, 0.f, zero));
+    zero += fabsf(a) + fabsf(b);
 }
 
 // barrier for what is in LDS; global loads stay in flight across it
@@ -63,7 +63,7 @@ constexpr int kSpWaves = 8, kSpBlock = kSpWaves * kWave;
 constexpr int kSpRows = 128, kSpK = 32;
 
 // The operand's parts for the products below: planes[(8 rows) * 3 + part][column] of 16 bytes each, rows and columns beyond the
-// operand's 0.  odd[(32 rows) * column tiles + column tile]: some of them are not finite (or round to an Inf in bf16), and all parts there are 0.
+// operand's 0.  odd[(32 rows) * column tiles + column tile]: some of them are not the sum of their parts (split_pair), and all parts there are 0.
 // A work-group: 32 rows, 256 columns, a thread 8 rows of a column at a time.
 __global__ __launch_bounds__(kSplitCols) void split_operand_kernel(const float *__restrict__ X, int64_t ldx, int rows, int batch, v4u *__restrict__ planes,
                                                                 int32_t *__restrict__ odd)
@@ -257,7 +257,8 @@ __global__ __launch_bounds__(kSpBlock) __attribute__((amdgpu_waves_per_eu(2, 2))
         });
     };
     for (int c = c_begin; c < c_end; ++c) chunk(c, (c - c_begin) & 1);
-    // What is left out: an entry that is not stored must not meet an Inf or NaN with its 0, so entry by entry, in fp32.
+    // What is left out: an entry that is not stored must not meet an Inf or NaN with its 0, and bits of a number that is too small are
+    // missing in its parts, so entry by entry, in fp32.
     lds_barrier();
     auto left_out = [&](int c) {
         return x_odd[c * col_tiles + col_tile] ? 0x0101010101010101ull : *reinterpret_cast<const uint64_t *>(odd[c - c_begin]);

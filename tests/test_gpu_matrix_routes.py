@@ -199,6 +199,31 @@ def test_dense_rows_on_the_bf16_units_with_infinities(nb, oracle):
     L.close()
 
 
+@pytest.mark.usefixtures("dense_rows_at_any_batch")
+@pytest.mark.parametrize("small", ["operand", "weights"])
+def test_dense_rows_on_the_bf16_units_with_small_numbers(nb, oracle, small):
+    """Numbers down to the end of the normal range, of which three bf16 numbers do not hold all bits: columns of the operand, or rows of
+    the matrix, of very different scales.  Relative to the terms of each result, as everywhere."""
+    import torch
+    lay, batch = mixed_rows(2500, 1057, 1030, 0.6, 3), 1024
+    lay.bias[:] = 0
+    rng = np.random.default_rng(4)
+    X = rng.standard_normal((lay.cols, batch)).astype(np.float32)
+    scale = np.float32(10.0) ** -np.array([0, 30, 32, 33, 34, 35, 36], np.float32)
+    if small == "operand":
+        X *= scale[np.arange(batch) * 7 // batch][None, :]
+        X[:, :5] *= scale[2:7]   # (and next to the ordinary ones)
+    else:
+        lay.values *= np.repeat(scale[rng.integers(0, 7, lay.rows)], np.diff(lay.indptr))
+    L = nb.SparseLinear(lay, max_batch=batch)
+    Yd = nb.dense(lay.rows, batch)
+    nb.sparse_linear_forward(L.handle, nb.to_dense(X), Yd, batch)
+    torch.cuda.synchronize()
+    Y, S = oracle.spmm(lay.rows, lay.cols, lay.indptr, lay.indices, lay.values, lay.bias, X, False)
+    close(Yd.cpu().numpy(), Y, S, what="Y", tol=1e-6)   # (fp32 sums of 640 terms; the parts alone are off by 1e-3 at 1e-36)
+    L.close()
+
+
 def test_uniform_rows_on_the_bf16_units(nb, oracle):
     """20 % of 2100 columns: gathered up to 461 columns of the batch, on the bf16 units from there on (and bound for 600)."""
     rng = np.random.default_rng(12)
