@@ -882,11 +882,11 @@ static DenseRowsCut dense_rows_fp32_cut(int32_t n, int32_t cols, int32_t batch)
     return best;
 }
 
-// Split operands: one work-group per compute unit, 2.6 us per 32 columns of the matrix; before it the operand's parts are formed (10 bytes a number
-// at 4.5 TB/s), after it the slices are added.  Measured on matrices of 35 %, fp32 -> split, us: 2600 rows of 16384 at batch 1024 / 512 / 256 /
-// 128: 837 -> 498, 469 -> 259, 246 -> 136, 134 -> 131; 700 of 16384: 260 -> 185, 145 -> 98, 82 -> 65, 55 -> 64; 8192 of 4096: 654 -> 367, 350 -> 194,
-// 184 -> 107, 101 -> 106; 2600 of 4096: 253 -> 138, 135 -> 81, 72 -> 52, 44 -> 50; 700 of 4096 at 1024 / 512 / 256: 81 -> 59, 46 -> 43, 30 -> 39; 100 of
-// 16384 at 1024: 63 -> 76; 2600 of 1024 at 1024 / 256: 81 -> 55, 29 -> 35.  The fp32 estimate is low on these by a quarter and a launch.
+// Split operands: one work-group per compute unit, 2.8 us per 32 columns of the matrix; before it the operand's parts are formed (10 bytes a number
+// at 4.5 TB/s), after it the slices are added.  Within 8 % of 190 products measured.  fp32 -> split, us, matrices of 32 to 38 %: 2600 rows of 16384 at batch
+// 1024 / 512 / 256: 833 -> 567, 459 -> 303, 237 -> 165; 873 of 11642: 254 -> 175, 124 -> 93, 74 -> 61; 8192 of 4096: 648 -> 420, 339 -> 235, 176 -> 124;
+// 700 of 4096 at 1024: 75 -> 62; 2048 of 2048 at 1024 / 512: 95 -> 73, 53 -> 48.  The fp32 estimate is low on these by a quarter and a launch; 300 rows of 16384,
+// 1024 of 3072 up to 640 columns and the like stay with it.
 static DenseRowsCut dense_rows_split_cut(int32_t n, int32_t cols, int32_t batch)
 {
     const int64_t chunks = (static_cast<int64_t>(cols) + 31) / 32, tiles = split_dense_rows_tiles(n, batch);
@@ -894,7 +894,7 @@ static DenseRowsCut dense_rows_split_cut(int32_t n, int32_t cols, int32_t batch)
     DenseRowsCut best{};
     for (int s = 1; s == 1 || (s <= 64 && s * 4 <= chunks); ++s) {
         if ((chunks + s - 1) / s > kSplitMaxChunks || chunks > 65535) continue;   // (65535: grid of the parts' launch)
-        const double time = 8. + parts + 2.6 * static_cast<double>((tiles * s + 255) / 256 * ((chunks + s - 1) / s)) +
+        const double time = 2. + parts + 2.8 * static_cast<double>((tiles * s + 255) / 256 * ((chunks + s - 1) / s)) +
                             (s > 1 ? 3. + 8. * s * n * static_cast<double>(dense_rows_ld(batch)) / 4.5e6 : 0.);
         if (best.tiles == 0 || time < best.time) best = DenseRowsCut{0, s, tiles, true, time};
     }
@@ -904,7 +904,7 @@ static DenseRowsCut dense_rows_split_cut(int32_t n, int32_t cols, int32_t batch)
 static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch)
 {
     const DenseRowsCut fp32 = dense_rows_fp32_cut(n, cols, batch), split = dense_rows_split_cut(n, cols, batch);
-    return split.tiles > 0 && split.time < 6. + 1.25 * fp32.time && operand_parts_ints(cols, batch) < (1ll << 29) ? split : fp32;
+    return split.tiles > 0 && split.time < 4. + 1.25 * fp32.time && operand_parts_ints(cols, batch) < (1ll << 29) ? split : fp32;
 }
 
 bool dense_rows_ok(const DenseSplit *d, int32_t batch) { return d && d->rows.n > 0 && batch >= d->from_batch; }

@@ -115,9 +115,9 @@ __host__ __device__ inline int32_t dense_rows_from(int32_t n, int64_t dense_nnz,
     return static_cast<int32_t>(b > least ? b : least);
 }
 // Stored entries from which a row counts as dense: an eighth of its columns.  At batch 1024 such a row costs the matrix units
-// 0.30 us per 16384 columns and the staged kernel 2.0 us times its density among power-law rows.  On the bf16 units it costs 0.17, but the staged kernel
-// gains less from what is taken out of it: forward products of 16384^2 at batch 1024 with an 8th / 10th / 12th / 16th: 10 % 1480 / 1498 / 1506 / 1553 us,
-// 6 % 1141 / 1166 / 1159 / 1590, 3 % 670 / 673 / 675 / 683.
+// 0.30 us per 16384 columns and the staged kernel 2.0 us times its density among power-law rows.  On the bf16 units it costs 0.20, but the staged kernel
+// gains less from what is taken out of it: forward products of 16384^2 at batch 1024 with an 8th / 10th / 12th / 16th: 10 % 1590 / 1621 / 1635 / 1708 us,
+// 6 % 1204 / 1242 / 1233 / 1671, 3 % 703 / 709 / 711 / 722.
 __host__ __device__ inline int32_t dense_row_length(int32_t cols) { return cols / 8 > 128 ? cols / 8 : 129; }
 
 // Y = epilogue( W * gather(X) ) for a CSR matrix W (rows x cols); also used on the CSC

@@ -1,12 +1,14 @@
 // Products on the bf16 matrix units at fp32 precision.
 // An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits of its 24: x = h + m + l exactly, unless x is so small, from 2^-110 down, that its
-// last bits lie below the smallest bf16 number; blocks that hold such a number are left to fp32), so a product of two is the
-// sum of nine products of which three (m l, l m, l l: below 2^-24 of it) are left out.  The bf16 units multiply exactly
-// into fp32 and are 12 times as fast as the fp32 ones (1.73 against 0.14 PFLOP/s from registers on this card), so the six
-// products that are formed take half the time.  h h is added up in one accumulator and the five small ones in another, which
-// keeps the rounding of a small product from being that of the large sum: against 64 bits the result is 2 to 3 times as close as that of
-// the fp32 units (dot products of 64 / 512 / 4096 / 16384 normal numbers: 4.9e-8 / 1.3e-7 / 4.0e-7 / 8.1e-7 of the result's norm against 1.4e-7 / 4.0e-7 /
-// 1.2e-6 / 2.3e-6; with one accumulator for all six 1.1e-7 / 3.4e-7 / 1.0e-6 / 2.1e-6, and a bias).
+// last bits lie below the smallest bf16 number; blocks that hold such a number are left to fp32; the splitting is that of Henry, Tang and Heinecke, "Leveraging
+// the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019), so a product of two is the
+// sum of nine products, of which l l (below 2^-32 of it) is left out.  Without m l and l m as well, which can make 2^-24 of it, a result
+// of a single product was off by up to 8.9e-8 where fp32 rounds once, by 6.0e-8 at most.  The bf16 units multiply exactly
+// into fp32 and are 12 times as fast as the fp32 ones (1.73 against 0.14 PFLOP/s from registers on this card), so the eight
+// products that are formed take two thirds of the time.  h h is added up in one accumulator and the seven small ones in another, which
+// keeps the rounding of a small product from being that of the large sum.  Against 64 bits, error over the result's norm, fp32 units or gathered -> here:
+// 1024 x 16384 at 35 % 6.8e-7 -> 1.9e-7, 8192 x 4096 at 25 % 5.7e-7 -> 1.6e-7, 2500 x 1057 at 36 % 3.5e-7 -> 0.8e-7; all numbers of one sign 2.7e-7 -> 0.9e-7,
+// 4.4e-7 -> 1.3e-7, 2.9e-7 -> 0.6e-7 (no bias: the units round to nearest); one operand row in a column of the batch 2.9e-8 -> 2.9e-8.
 //
 // v_mfma_f32_32x32x16_bf16: lane l supplies A(l % 32, 8 (l / 32) + i) and B(8 (l / 32) + i, l % 32), i = 0 .. 7, of a
 // 32 x 16 by 16 x 32 step; register r of lane l holds C(8 (r / 4) + 4 (l / 32) + r % 4, l % 32).
@@ -99,11 +101,11 @@ __global__ __launch_bounds__(kSplitCols) void split_operand_kernel(const float *
 // lane per column of a row (the pattern table says whether there is one and where), turns them round in LDS and splits them for all waves, in
 // steps between its products; its own columns of the operand come straight from the parts, a chunk ahead.  K is cut into slices
 // where the tiles do not fill the chip.
-// What bounds it: the card's power at these units (from registers they reach 1.73 PFLOP/s at 1.8 GHz), and the waits at either end of a chunk: matrix
-// pipes 57 % busy at 1.96 GHz.  Measured on the 2611 dense rows of 16384^2 power-law rows at 10 %, batch 1024: 433 us (1.2 PFLOP/s) after 33 for
-// the parts and before 9 for the slices; dense_rows_kernel 813 + 9.  Without bringing entries and operand the same loop takes 324.
-// Tried: the operand split by the work-groups themselves (526), through LDS (480), one of a SIMD's two waves bringing entries while
-// the other multiplies (450).
+// What bounds it: the card's power at these units (from registers they reach 1.73 PFLOP/s at 1.8 GHz), and the waits at either end of a chunk.
+// Measured on the 2611 dense rows of 16384^2 power-law rows at 10 %, batch 1024: 510 us (1.4 PFLOP/s) after 32 for
+// the parts and before 10 for the slices; dense_rows_kernel 813 + 9.
+// Tried, with six of the products, which took 433: the operand split by the work-groups themselves (526), through LDS (480), one of a SIMD's two waves
+// bringing entries while the other multiplies (450); without bringing entries and operand the same loop took 324.
 __global__ __launch_bounds__(kSpBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void split_dense_rows_kernel(const SpmmArgs a, const DenseRows D,
                                                                                                                const v4u *__restrict__ planes,
                                                                                                                const int32_t *__restrict__ x_odd, const int slices)
@@ -207,7 +209,7 @@ __global__ __launch_bounds__(kSpBlock) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
             for (int p = 2; p >= 0; --p) {
 #pragma unroll
-                for (int pb = 2 - p; pb >= 0; --pb) product(p, pb);
+                for (int pb = p == 2 ? 1 : 2; pb >= 0; --pb) product(p, pb);
                 __builtin_amdgcn_sched_barrier(0);
                 if (pair + 1 < kPairs) read(pair + 1, p);
                 between(pair * 3 + 2 - p);

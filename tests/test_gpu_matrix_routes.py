@@ -224,6 +224,40 @@ def test_dense_rows_on_the_bf16_units_with_small_numbers(nb, oracle, small):
     L.close()
 
 
+@pytest.mark.usefixtures("dense_rows_at_any_batch")
+@pytest.mark.parametrize("kind", ["normal", "one sign", "one term"])
+def test_dense_rows_on_the_bf16_units_are_no_further_off_than_fp32_sums(nb, kind):
+    """Against 64 bits, beside a chain of fp32 sums: ordinary numbers, numbers of one sign (a biased rounding would show) and results of a
+    single product, which fp32 rounds once: 2^-24, and the product left out adds 2^-32 to it."""
+    import torch
+    lay, batch = mixed_rows(2500, 1057, 1030, 0.6, 3), 1024
+    lay.bias[:] = 0
+    X = np.random.default_rng(4).standard_normal((lay.cols, batch)).astype(np.float32)
+    if kind == "one sign":
+        X, lay.values[:] = np.abs(X), np.abs(lay.values)
+    elif kind == "one term":
+        X *= np.arange(lay.cols)[:, None] == np.arange(batch)[None, :]
+    L = nb.SparseLinear(lay, max_batch=batch)
+    Yd = nb.dense(lay.rows, batch)
+    nb.sparse_linear_forward(L.handle, nb.to_dense(X), Yd, batch)
+    torch.cuda.synchronize()
+    Y = Yd.cpu().numpy().astype(np.float64)
+    mine = chain = norm = worst = 0.0
+    for row in np.flatnonzero(np.diff(lay.indptr) > 500)[::40]:
+        at = slice(lay.indptr[row], lay.indptr[row + 1])
+        w, x = lay.values[at], X[lay.indices[at]]
+        want, s = w.astype(np.float64) @ x.astype(np.float64), np.zeros(batch, np.float32)
+        for k in range(w.size):
+            s += w[k] * x[k]
+        mine, chain, norm = mine + ((Y[row] - want) ** 2).sum(), chain + ((s - want) ** 2).sum(), norm + (want ** 2).sum()
+        worst = max(worst, float((np.abs(Y[row] - want) / np.maximum(np.abs(want), 1e-30)).max()))
+    if kind == "one term":
+        assert mine <= chain * 1.01 and worst <= 2.0 ** -24 * (1 + 2.0 ** -6), (np.sqrt(mine / norm), np.sqrt(chain / norm), worst)
+    else:
+        assert mine <= chain, (np.sqrt(mine / norm), np.sqrt(chain / norm))
+    L.close()
+
+
 def test_uniform_rows_on_the_bf16_units(nb, oracle):
     """20 % of 2100 columns: gathered up to 461 columns of the batch, on the bf16 units from there on (and bound for 600)."""
     rng = np.random.default_rng(12)
