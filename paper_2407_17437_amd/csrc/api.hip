@@ -948,6 +948,9 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
             D.partial_floats = want.partial_floats;
             D.parts = reinterpret_cast<uint32_t *>(B.row_partial + partial);
             D.parts_ints = want.parts_ints;
+        } else if (want.parts_ints > 0 && want.partial_floats > 0 && reserve_optional(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(want.partial_floats))) {
+            D.partial = B.row_partial;
+            D.partial_floats = want.partial_floats;
         }
         B.split.flag = t.dense_flag;
         B.split.others = out->plan;

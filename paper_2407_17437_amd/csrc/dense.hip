@@ -883,7 +883,7 @@ static DenseRowsCut dense_rows_fp32_cut(int32_t n, int32_t cols, int32_t batch)
 }
 
 // Split operands: one work-group per compute unit, 2.8 us per 32 columns of the matrix; before it the operand's parts are formed (10 bytes a number
-// at 4.5 TB/s), after it the slices are added.  Within 8 % of 190 products measured.  fp32 -> split, us, matrices of 32 to 38 %: 2600 rows of 16384 at batch
+// at 4.5 TB/s), after it the slices are added.  Within 12 % of 190 products measured.  fp32 -> split, us, matrices of 32 to 38 %: 2600 rows of 16384 at batch
 // 1024 / 512 / 256: 833 -> 567, 459 -> 303, 237 -> 165; 873 of 11642: 254 -> 175, 124 -> 93, 74 -> 61; 8192 of 4096: 648 -> 420, 339 -> 235, 176 -> 124;
 // 700 of 4096 at 1024: 75 -> 62; 2048 of 2048 at 1024 / 512: 95 -> 73, 53 -> 48.  The fp32 estimate is low on these by a quarter and a launch; 300 rows of 16384,
 // 1024 of 3072 up to 640 columns and the like stay with it.
@@ -901,9 +901,9 @@ static DenseRowsCut dense_rows_split_cut(int32_t n, int32_t cols, int32_t batch)
     return best;
 }
 
-static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch)
+static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch, const DenseRowsCut &fp32)
 {
-    const DenseRowsCut fp32 = dense_rows_fp32_cut(n, cols, batch), split = dense_rows_split_cut(n, cols, batch);
+    const DenseRowsCut split = dense_rows_split_cut(n, cols, batch);
     return split.tiles > 0 && split.time < 4. + 1.25 * fp32.time && operand_parts_ints(cols, batch) < (1ll << 29) ? split : fp32;
 }
 
@@ -914,8 +914,9 @@ DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch)
     DenseRowsRoom room{0, 0};
     for (int64_t c = 64; c - 64 < max_batch; c += 64) {
         const int32_t batch = static_cast<int32_t>(c < max_batch ? c : max_batch);
-        const DenseRowsCut cut = dense_rows_cut(n, cols, batch);
-        if (cut.slices > 1) room.partial_floats = std::max(room.partial_floats, static_cast<int64_t>(cut.slices) * n * dense_rows_ld(batch));
+        const DenseRowsCut fp32 = dense_rows_fp32_cut(n, cols, batch), cut = dense_rows_cut(n, cols, batch, fp32);
+        const int slices = std::max(cut.slices, fp32.slices);   // (the fp32 units take over where there is no room for the parts)
+        if (slices > 1) room.partial_floats = std::max(room.partial_floats, static_cast<int64_t>(slices) * n * dense_rows_ld(batch));
         if (cut.split) room.parts_ints = std::max(room.parts_ints, operand_parts_ints(cols, batch));
     }
     room.partial_floats = std::min<int64_t>(room.partial_floats, 1ll << 28);   // (what does not fit is not sliced)
@@ -925,10 +926,11 @@ DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch)
 hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s)
 {
     const DenseRows &D = a.split->rows;
-    DenseRowsCut cut = dense_rows_cut(D.n, a.x_rows, a.batch);
+    const DenseRowsCut fp32 = dense_rows_fp32_cut(D.n, a.x_rows, a.batch);
+    DenseRowsCut cut = dense_rows_cut(D.n, a.x_rows, a.batch, fp32);
     auto fits = [&] { return static_cast<int64_t>(cut.slices) * D.n * dense_rows_ld(a.batch) <= D.partial_floats; };
     // (a batch between those that the buffers were sized for may be cut finer than they are)
-    if (cut.split && (operand_parts_ints(a.x_rows, a.batch) > D.parts_ints || (cut.slices > 1 && !fits()))) cut = dense_rows_fp32_cut(D.n, a.x_rows, a.batch);
+    if (cut.split && (operand_parts_ints(a.x_rows, a.batch) > D.parts_ints || (cut.slices > 1 && !fits()))) cut = fp32;
     if (cut.slices > 1 && !fits()) cut.slices = 1;
     const int slices = cut.slices;
     const dim3 grid(static_cast<unsigned>(cut.tiles * slices));

@@ -132,6 +132,29 @@ def a_ticket_of_a_shared_tile_counts_to_one_number(L):
     L.destroy()
 
 
+def slices_of_dense_rows_stay_where_their_parts_have_no_room(L):
+    """Whichever allocation fails: a wide product of dense rows that does not get the bf16 units still has its sum cut into slices."""
+    seen = set()
+    for k in range(100):
+        L.counts(0, n_blocks=600, n_dense=1030, dense_nnz=653000, longest_row=800)
+        L.counts(1, n_blocks=600, longest_row=2000)
+        L.hip.fake_fail_after(k)
+        rc = L.create(2500, 1057, 662000, 1024)
+        failed = L.hip.fake_fail_after_left() < 0
+        L.hip.fake_fail_after(-1)
+        if rc == 0:
+            L.launched()
+            assert L.forward(1024) == 0
+            launched = L.launched()
+            if any("dense_rows" in name for name in launched):   # (else the row table is the one without room)
+                assert any("dense_rows_finish_kernel" in name for name in launched), (k, launched)
+                seen.add(any("split_dense_rows_kernel" in name for name in launched))
+            L.destroy()
+            if not failed:
+                break
+    assert seen == {True, False}
+
+
 def a_layer_is_created_without_what_it_can_do_without(L):
     """Dense rows with sliced results, a staged plan for the batches below theirs, partial products, dZ of a ReLU layer: each of them
     fails once.  (The calls fail one after another; those whose failure the create survives are these.)"""
@@ -169,7 +192,7 @@ def a_single_tile_needs_no_partial_products(L):
     assert held[1] - held[0] == 1024 * (128 - 64) * 4, held   # (dZ, whose rows are 128 and 64 columns apart)
 
 
-CASES = [a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
