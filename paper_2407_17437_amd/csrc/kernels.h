@@ -94,6 +94,8 @@ struct DenseRows {
 struct DenseSplit {
     DenseRows rows;                // n = 0: there are none, or too few
     int32_t from_batch;
+    int64_t thin_nnz;              // stored entries of the listed rows where they are thin (dense_rows_thin), or 0; then also
+    int32_t all_rows, cols, max_batch;   // the matrix and what it is bound for
     const uint8_t *flag;           // [rows of the matrix] 1: a dense row
     RowBlocks others;
 };
@@ -101,9 +103,8 @@ constexpr int32_t kDenseRowsMinCols = 1024;    // (so that a dense row is longer
 constexpr int32_t kDenseRowsMin = 17;          // fewer rows than this stay with the others
 constexpr int64_t kDenseRowsMinWork = 192 << 20;  // entries times columns of the batch from which the extra launch pays
 constexpr int32_t kDenseRowsMinBatch = 128;    // (narrower ones leave much of a tile of 64 or 128 columns idle)
-// Rows that together store less than 30 % of their columns pay on the bf16 units alone (split.hip), that is for many rows of many columns and
-// wide batches: uniform 25 %, gathered -> split, us: 2600 x 16384 at batch 1024 / 512 / 256: 738 -> 500, 481 -> 259, 530 -> 136 (break even at 17, 14,
-// 7 %); 8192 x 4096: 598 -> 367, 308 -> 194, 170 -> 107 (15, 16, 16 %); 700 x 4096 at 1024 / 512 / 256: 113 -> 59, 60 -> 43, 31 -> 39; 2600 x 1024 at 1024: 55 -> 55.
+// Rows that together store less than 30 % of their columns pay on the bf16 units alone (split.hip), and there at batches that fill its tiles of 256
+// columns and that gathering is slow at (dense_rows_product_ok): many rows of many columns and wide batches.
 constexpr int32_t kDenseRowsThinMin = 512, kDenseRowsThinCols = 2048, kDenseRowsThinBatch = 192, kDenseRowsThinPercent = 17;
 constexpr int64_t kDenseRowsThinWork = 384 << 20;
 __host__ __device__ inline bool dense_rows_thin(int32_t n, int64_t dense_nnz, int32_t cols) { return dense_nnz * 10 < static_cast<int64_t>(n) * cols * 3; }
@@ -374,7 +375,9 @@ bool sddmm_sampled_possible(const SddmmArgs &a);
 void add_sampled(SampledArgs &list, const SddmmArgs &a);
 hipError_t launch_sampled(SampledArgs &a, hipStream_t s);
 // Y = act(W X + b) of a matrix's dense rows, and the room in DenseRows that takes at up to max_batch columns
-bool dense_rows_ok(const DenseSplit *d, int32_t batch);
+bool dense_rows_product_ok(const DenseSplit *d, int32_t batch);
+bool dense_rows_sddmm_ok(const DenseSplit *d, int32_t batch);
+int32_t thin_rows_gathered_up_to(const DenseSplit &d);   // the widest batch at which a product leaves its thin rows with the others; -1: it always does
 bool sampled_operands_ok(const SddmmArgs &a);
 hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s);
 __host__ __device__ inline int64_t dense_rows_ld(int32_t batch) { return (batch + 31) / 32 * 32; }
@@ -393,7 +396,7 @@ __host__ __device__ inline int64_t operand_parts_ints(int32_t rows, int32_t batc
 struct DenseRowsRoom {
     int64_t partial_floats, parts_ints;
 };
-DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch);
+DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch, bool thin);
 void add_sampled_rows(SampledArgs &list, const SddmmArgs &a);
 // status: result of the pattern check (the launch does nothing where it is not 0), or nullptr
 // list: the rows (or nullptr: 0 .. rows - 1)
@@ -516,7 +519,7 @@ __host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols
     const int64_t bound = want + (rows + 96 * want) / kStageRangeFill + 2;
     return bound * ((cols + kStageRows - 1) / kStageRows + 1) * kStageRangeRows > (1ll << 28) ? 0 : static_cast<int32_t>(bound);
 }
-// Whether the listed rows are worth a route of their own at max_batch columns (narrower calls ask again: dense_rows_ok).  Start -> with it, forward product: power-law 4096^2 at 5 % (297 rows,
+// Whether the listed rows are worth a route of their own at max_batch columns (calls ask again: dense_rows_product_ok).  Start -> with it, forward product: power-law 4096^2 at 5 % (297 rows,
 // 0.53 M entries) at batch 256 / 512 / 1024: 48 -> 50, 81 -> 77, 129 -> 120 us; 8192 x 1024 at 10 %: 35 -> 36, 87 -> 51, 109 -> 82.
 // Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even with the fp32 units at 30 % (324 us; 20 %: 235 -> 326).
 __host__ __device__ inline bool dense_rows_pay(int32_t n_dense, int64_t dense_nnz, int64_t nnz, int32_t cols, int32_t max_batch)

@@ -258,14 +258,16 @@ def test_dense_rows_on_the_bf16_units_are_no_further_off_than_fp32_sums(nb, kind
     L.close()
 
 
-def test_uniform_rows_on_the_bf16_units(nb, oracle):
-    """20 % of 2100 columns: gathered up to 461 columns of the batch, on the bf16 units from there on (and bound for 600)."""
+@pytest.mark.parametrize("low,high,batches", [
+    (560, 609, (300, 600)),   # 28 % of 2100 columns, bound for 600: gathered at 300, on the bf16 units at 600 (test_host_memory)
+    (390, 450, (300, 470)),   # 20 %, bound for 470: long enough rows, but no batch pays
+])
+def test_uniform_rows_on_the_bf16_units(nb, oracle, low, high, batches):
     rng = np.random.default_rng(12)
-    indptr, indices = wl.pattern_from_row_nnz(rng.integers(390, 450, 2050), 2100, seed=9)
+    indptr, indices = wl.pattern_from_row_nnz(rng.integers(low, high, 2050), 2100, seed=9)
     lay = wl.SparseLayerData(2050, 2100, indptr, indices, wl.init_values(indptr, 7), rng.standard_normal(2050).astype(np.float32), True)
-    for batch in (300, 600):
-        check_layer(nb, oracle, lay, batch, max_batch=600)
-
+    for batch in batches:
+        check_layer(nb, oracle, lay, batch, max_batch=batches[1])
 
 
 def test_huge_rows_after_products_that_overlapped(nb, oracle):
