@@ -866,6 +866,20 @@ struct BuiltPattern {
     bool full = false;
 };
 
+// room for the product of the dense rows of the pattern in `B`: whether there was
+static bool reserve_dense_rows(PatternBuffers &B, const DenseRowsRoom &want)
+{
+    DenseRows &D = B.split.rows;
+    const int64_t partial = round_up(want.partial_floats, 64);
+    D.partial_floats = D.parts_ints = 0;
+    if (partial + want.parts_ints == 0 || !reserve_optional(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(partial + want.parts_ints))) return false;
+    D.partial = B.row_partial;
+    D.partial_floats = want.partial_floats;
+    D.parts = reinterpret_cast<uint32_t *>(B.row_partial + partial);
+    D.parts_ints = want.parts_ints;
+    return true;
+}
+
 static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, const int32_t *indices, const float *values,
                             BuiltPattern *out, hipStream_t s)
 {
@@ -934,61 +948,25 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     bool more_work = false;   // launches after the wait
     B.split = DenseSplit{};
     const int32_t n_dense = R.plan[0].n_dense;
-    const int64_t dense_nnz = R.plan[0].dense_nnz;
-    const bool thin = n_dense > 0 && asked != NERVA_PARTITION_PREFER_DENSE_ROWS && dense_rows_thin(n_dense, dense_nnz, cols);
-    bool apart = n_dense > 0;
-    int32_t with_others = 0;   // the widest batch at which the dense rows are rows like any other
-    if (apart) {
-        DenseRows &D = B.split.rows;
-        D.list = p.side[0].tables.dense_rows; D.n = n_dense; D.words = table_words(l);
-        B.split.from_batch = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? kDenseRowsMinBatch : dense_rows_from(n_dense, dense_nnz, cols);
-        with_others = B.split.from_batch - 1;
-        const DenseRowsRoom want = dense_rows_room(D.n, cols, max_batch, thin);
-        const int64_t partial = round_up(want.partial_floats, 64);
-        if (thin) {
-            B.split.thin_nnz = dense_nnz; B.split.all_rows = rows; B.split.cols = cols; B.split.max_batch = max_batch;
-            D.partial_floats = want.partial_floats; D.parts_ints = want.parts_ints;
-            with_others = thin_rows_gathered_up_to(B.split);
-            apart = with_others >= 0;
-            if (!dense_rows_sddmm_ok(&B.split, max_batch)) with_others = max_batch;
-        }
-        apart = apart && reserve_optional(&B.row_table, &B.row_table_ints, static_cast<size_t>(n_dense) * table_words(l) * 2);
-        D.table = reinterpret_cast<const uint2 *>(B.row_table);
-        if (apart && partial + want.parts_ints > 0) {
-            if (reserve_optional(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(partial + want.parts_ints))) {
-                D.partial = B.row_partial;
-                D.partial_floats = want.partial_floats;
-                D.parts = reinterpret_cast<uint32_t *>(B.row_partial + partial);
-                D.parts_ints = want.parts_ints;
-            } else if (thin) {
-                apart = false;
-            } else if (want.parts_ints > 0 && want.partial_floats > 0 && reserve_optional(&B.row_partial, &B.row_partial_floats, static_cast<size_t>(want.partial_floats))) {
-                D.partial = B.row_partial;
-                D.partial_floats = want.partial_floats;
-            }
-        }
-    }
-    if (!apart) B.split = DenseSplit{};
-    if (n_dense > 0 && !apart && thin) {
-        PlanArgs all = p;   // as if no row were dense
-        all.side[0].dense_len = INT32_MAX;
-        HIP_TRY(launch_plan(all, 1, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        out->plan = plan_view(all.side[0].tables, l->bind_result->plan[0], cols, nnz, R.plan[1].hot_nnz, mode);
-    } else if (n_dense > 0 && !apart) {
+    if (n_dense > 0 && !reserve_optional(&B.row_table, &B.row_table_ints, static_cast<size_t>(n_dense) * table_words(l) * 2)) {
         out->plan.staged_rows = nullptr;   // (it covers the other rows only: the dense ones stay with them, unstaged)
     } else if (n_dense > 0) {
         const PlanTables &t = p.side[0].tables;
-        const DenseRows &D = B.split.rows;
+        DenseRows &D = B.split.rows;
+        D.list = t.dense_rows; D.n = n_dense; D.words = table_words(l);
+        D.table = reinterpret_cast<const uint2 *>(B.row_table);
+        const DenseRowsRoom want = dense_rows_room(D.n, cols, max_batch, false);
+        if (!reserve_dense_rows(B, want) && want.parts_ints > 0) (void)reserve_dense_rows(B, DenseRowsRoom{want.partial_floats, 0});
+        B.split.from_batch = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? kDenseRowsMinBatch : dense_rows_from(R.plan[0].dense_nnz);
         B.split.flag = t.dense_flag;
         B.split.others = out->plan;
         B.split.others.waves = t.other_waves;
         B.split.others.long_waves = t.other_long_waves;
-        // The staged plan covers the other rows only.  Batches at which the dense rows are rows like any other get one of
+        // The staged plan covers the other rows only.  Narrower batches, at which the dense rows are rows like any other, get one of
         // all rows where the widest of them that fills its tiles (staged_pays) has work-groups enough for it.
         out->plan.staged_rows = nullptr;
-        const int32_t tiles = static_cast<int32_t>(std::min<int64_t>(5ll * with_others, 5ll * max_batch) / (4 * kStageCols));
-        if (with_others >= kStageMinBatch && room.ranges > 0 && tiles * staged_ranges_aim(rows, max_batch) >= kStageTargetGroups / 2 &&
+        const int32_t tiles = static_cast<int32_t>(std::min<int64_t>(5ll * (B.split.from_batch - 1), 5ll * max_batch) / (4 * kStageCols));
+        if (B.split.from_batch > kStageMinBatch && room.ranges > 0 && tiles * staged_ranges_aim(rows, max_batch) >= kStageTargetGroups / 2 &&
             reserve_optional(&B.whole_staged, &B.whole_staged_ints, room.staged_ints())) {
             PlanArgs whole = p;
             whole.side[0].dense_len = INT32_MAX;
@@ -999,6 +977,15 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         }
         HIP_TRY(launch_pattern_table(indptr, indices, D.list, D.n, D.words, reinterpret_cast<uint2 *>(B.row_table), nullptr, s));
         more_work = true;
+    } else if (asked == NERVA_PARTITION_BALANCED && seek_dense && B.has_table && rows >= kThinRows && cols >= kThinCols && max_batch >= kThinBatch &&
+               static_cast<double>(nnz) >= static_cast<double>(kThinDensity) * rows * cols) {
+        DenseRows &D = B.split.rows;
+        D.n = rows; D.words = table_words(l);
+        D.table = reinterpret_cast<const uint2 *>(B.table);
+        B.split.thin_nnz = nnz; B.split.max_batch = max_batch;
+        const DenseRowsRoom want = dense_rows_room(rows, cols, max_batch, true);
+        D.partial_floats = want.partial_floats; D.parts_ints = want.parts_ints;
+        if (!thin_rows_pay_somewhere(B.split, cols) || !reserve_dense_rows(B, want)) B.split = DenseSplit{};
     }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
 

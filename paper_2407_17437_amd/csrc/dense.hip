@@ -734,7 +734,7 @@ __global__ __launch_bounds__(kDenseBlock) void dense_rows_finish_kernel(const Sp
             const float4 v = ld4(p + q * step);
             y.x += v.x; y.y += v.y; y.z += v.z; y.w += v.w;
         }
-        dense_rows_store(a, D.list[k], col, y);
+        dense_rows_store(a, D.list ? D.list[k] : k, col, y);
     }
 }
 
@@ -842,7 +842,6 @@ bool sampled_operands_ok(const SddmmArgs &a)
 
 bool sddmm_sampled_possible(const SddmmArgs &a) { return a.table && sampled_operands_ok(a); }
 
-constexpr int64_t kSampledThinTiles = 512;
 bool sddmm_sampled_ok(const SddmmArgs &a)
 {
     if (!sddmm_sampled_possible(a) || a.rows < 64 || a.x_rows < 64) return false;
@@ -850,7 +849,7 @@ bool sddmm_sampled_ok(const SddmmArgs &a)
     // 238 there, 20 %: 43.5 / 238 against 59.5 / 299; 1024 x 3072, 20 %: 13.7 / 70 against 16.1 / 100.  Few tiles do not fill
     // the chip: 512 x 1024 (128 tiles) at 30 %: 8.9 / 32.4 against 7.3 / 38.9.
     const int64_t tiles = static_cast<int64_t>((a.rows + 63) / 64) * ((a.x_rows + 63) / 64);
-    const double from = tiles >= kSampledThinTiles ? kTableFromDensity : 2.3 * kTableFromDensity;
+    const double from = tiles >= 512 ? kTableFromDensity : 2.3 * kTableFromDensity;
     return a.dense || static_cast<double>(a.nnz) >= from * a.rows * a.x_rows;
 }
 
@@ -909,50 +908,42 @@ static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch, const
     return split.tiles > 0 && split.time < 4. + 1.25 * fp32.time && operand_parts_ints(cols, batch) < kPartsMaxInts ? split : fp32;
 }
 
-// Thin rows (dense_rows_thin): what gathering for them takes, along with the others.  Staged (as staged_pays has it): 0.95 ns an entry of a work-group's range and
+// What gathering for a thin matrix (kThinDensity) takes, us.  Staged (as staged_pays has it): 0.95 ns an entry of a work-group's range and
 // column tile, one work-group a compute unit, which copies its tile of the operand into LDS at 32 GB/s; else about 25 TB/s of gathers.  Within 10 % of 250
-// uniform matrices of 17 to 28 % with 600 to 16384 rows, each bound for the batch.
-static double thin_rows_gathered(const DenseSplit &d, int32_t batch)
+// products of uniform matrices of 17 to 28 % with 600 to 16384 rows, each bound for the batch.
+static double thin_rows_gathered(const DenseSplit &d, int32_t cols, int32_t batch)
 {
-    const int64_t tiles = (static_cast<int64_t>(batch) + kStageCols - 1) / kStageCols, ranges = staged_ranges_aim(d.all_rows, d.max_batch), groups = tiles * ranges;
+    const int64_t tiles = (static_cast<int64_t>(batch) + kStageCols - 1) / kStageCols, ranges = staged_ranges_aim(d.rows.n, d.max_batch), groups = tiles * ranges;
     if (static_cast<int64_t>(batch) * 5 < tiles * kStageCols * 4 || groups < kStageTargetGroups * 3 / 4) return static_cast<double>(d.thin_nnz) * batch * 4. / 25e6;
-    const double rounds = static_cast<double>((groups + kStageTargetGroups - 1) / kStageTargetGroups), entries = static_cast<double>(d.thin_nnz) / static_cast<double>(ranges);
-    return rounds * 0.95e-3 * entries + (d.rows.n == d.all_rows ? 5. + rounds * 8e-3 * d.cols : 0.);   // (other rows need the operand in any case)
+    return 5. + static_cast<double>((groups + kStageTargetGroups - 1) / kStageTargetGroups) * (0.95e-3 * static_cast<double>(d.thin_nnz) / static_cast<double>(ranges) + 8e-3 * cols);
 }
 
-// Thin rows go apart where the bf16 units take less than gathering does.  Start of each range of 256 columns against its end, gathered / split, us: 9019 x 2137 at
+// It goes to the bf16 units where they take less.  Start of each range of 256 columns against its end, gathered / split, us: 9019 x 2137 at
 // 26 %, batch 257 / 512: 122 / 161, 180 / 154; 8192 x 4096 at 20 %: 165 / 215, 251 / 219; at 513 / 1024: 270 / 335, 486 / 400; 2600 x 16384 at 20 %, batch
 // 256 / 512 / 1024: 356 / 156, 386 / 291, 605 / 537; 3000 x 6000 at 18 %: 136 / 75, 145 / 137, 244 / 257.  (The fp32 units lose: 20 % of 4096^2 at batch 1024 235 / 326.)
-static bool thin_rows_pay(const DenseSplit &d, int32_t batch)
+static bool thin_rows_pay(const DenseSplit &d, int32_t cols, int32_t batch)
 {
-    const DenseRowsCut cut = dense_rows_split_cut(d.rows.n, d.cols, batch);
-    return cut.tiles > 0 && operand_parts_ints(d.cols, batch) <= d.rows.parts_ints &&
-           (cut.slices == 1 || static_cast<int64_t>(cut.slices) * d.rows.n * dense_rows_ld(batch) <= d.rows.partial_floats) && cut.time * 1.05 < thin_rows_gathered(d, batch);
+    if (batch < kThinBatch || d.thin_nnz * batch < kThinWork) return false;
+    const DenseRowsCut cut = dense_rows_split_cut(d.rows.n, cols, batch);
+    return cut.tiles > 0 && operand_parts_ints(cols, batch) <= d.rows.parts_ints &&
+           (cut.slices == 1 || static_cast<int64_t>(cut.slices) * d.rows.n * dense_rows_ld(batch) <= d.rows.partial_floats) && cut.time * 1.05 < thin_rows_gathered(d, cols, batch);
 }
 
-bool dense_rows_product_ok(const DenseSplit *d, int32_t batch)
+bool thin_rows_pay_somewhere(const DenseSplit &d, int32_t cols)
 {
-    return d && d->rows.n > 0 && batch >= d->from_batch && (d->thin_nnz == 0 || thin_rows_pay(*d, batch));
-}
-
-// (thin rows as a layer of their density: sddmm_sampled_ok)
-bool dense_rows_sddmm_ok(const DenseSplit *d, int32_t batch)
-{
-    return d && d->rows.n > 0 && batch >= d->from_batch &&
-           (d->thin_nnz == 0 || static_cast<int64_t>((d->rows.n + 63) / 64) * ((d->cols + 63) / 64) >= kSampledThinTiles);
-}
-
-int32_t thin_rows_gathered_up_to(const DenseSplit &d)
-{
-    bool any = false;
-    int32_t widest = 0;
     // (the estimates go in steps of 32 columns; beyond 2048, where tiles are many, every 64th is looked at)
-    for (int32_t b = d.max_batch; b >= d.from_batch && !(any && widest > 0); b = (b - 1 - b / 64) / 32 * 32) {
-        if (thin_rows_pay(d, b)) any = true;
-        else if (widest == 0) widest = b;
-    }
-    return !any ? -1 : widest > 0 ? widest : d.from_batch - 1;
+    for (int32_t b = d.max_batch; b >= kThinBatch; b = (b - 1 - b / 64) / 32 * 32)
+        if (thin_rows_pay(d, cols, b)) return true;
+    return false;
 }
+
+bool dense_rows_product_ok(const DenseSplit *d, int32_t cols, int32_t batch)
+{
+    return d && d->rows.n > 0 && (d->thin_nnz > 0 ? thin_rows_pay(*d, cols, batch) : batch >= d->from_batch);
+}
+
+// (a thin matrix is one for sddmm_sampled_ok)
+bool dense_rows_sddmm_ok(const DenseSplit *d, int32_t batch) { return d && d->rows.n > 0 && d->thin_nnz == 0 && batch >= d->from_batch; }
 
 DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch, bool thin)
 {

@@ -81,7 +81,7 @@ constexpr int32_t kPackSets = 1;         // row sets (64/GS rows each) per wave;
 
 // Rows of a matrix that are dense enough for matrix instructions (dense_rows_kernel in dense.hip), and their pattern table.
 struct DenseRows {
-    const int32_t *list;           // [n] ascending
+    const int32_t *list;           // [n] ascending, or nullptr: all rows
     const uint2 *table;            // [n * words] {bits of 32 columns, CSR position of the first of them}
     int32_t n, words;
     float *partial;                // results of the slices of K, partial_floats long
@@ -94,8 +94,8 @@ struct DenseRows {
 struct DenseSplit {
     DenseRows rows;                // n = 0: there are none, or too few
     int32_t from_batch;
-    int64_t thin_nnz;              // stored entries of the listed rows where they are thin (dense_rows_thin), or 0; then also
-    int32_t all_rows, cols, max_batch;   // the matrix and what it is bound for
+    int64_t thin_nnz;              // all rows of a matrix of kThinDensity: its stored entries, or 0; then also
+    int32_t max_batch;             // what it is bound for
     const uint8_t *flag;           // [rows of the matrix] 1: a dense row
     RowBlocks others;
 };
@@ -103,18 +103,18 @@ constexpr int32_t kDenseRowsMinCols = 1024;    // (so that a dense row is longer
 constexpr int32_t kDenseRowsMin = 17;          // fewer rows than this stay with the others
 constexpr int64_t kDenseRowsMinWork = 192 << 20;  // entries times columns of the batch from which the extra launch pays
 constexpr int32_t kDenseRowsMinBatch = 128;    // (narrower ones leave much of a tile of 64 or 128 columns idle)
-// Rows that together store less than 30 % of their columns pay on the bf16 units alone (split.hip), and there at batches that fill its tiles of 256
-// columns and that gathering is slow at (dense_rows_product_ok): many rows of many columns and wide batches.
-constexpr int32_t kDenseRowsThinMin = 512, kDenseRowsThinCols = 2048, kDenseRowsThinBatch = 192, kDenseRowsThinPercent = 17;
-constexpr int64_t kDenseRowsThinWork = 384 << 20;
-__host__ __device__ inline bool dense_rows_thin(int32_t n, int64_t dense_nnz, int32_t cols) { return dense_nnz * 10 < static_cast<int64_t>(n) * cols * 3; }
 // the batch from which the listed rows have that much work
-__host__ __device__ inline int32_t dense_rows_from(int32_t n, int64_t dense_nnz, int32_t cols)
+__host__ __device__ inline int32_t dense_rows_from(int64_t dense_nnz)
 {
-    const bool thin = dense_rows_thin(n, dense_nnz, cols);
-    const int64_t b = ((thin ? kDenseRowsThinWork : kDenseRowsMinWork) + dense_nnz - 1) / dense_nnz, least = thin ? kDenseRowsThinBatch : kDenseRowsMinBatch;
-    return static_cast<int32_t>(b > least ? b : least);
+    const int64_t b = (kDenseRowsMinWork + dense_nnz - 1) / dense_nnz;
+    return b > kDenseRowsMinBatch ? static_cast<int32_t>(b) : kDenseRowsMinBatch;
 }
+// A matrix of at least kThinDensity that has no such rows (dense_rows_pay) pays on the bf16 units alone (split.hip), with all its rows, and there at batches that
+// fill their tiles of 256 columns and that gathering is slow at (dense_rows_product_ok): many rows of many columns, wide batches.  Its partitions stay
+// those of a sparse one, so that binding it takes no launch more.
+constexpr int32_t kThinRows = 512, kThinCols = 2048, kThinBatch = 192;
+constexpr int64_t kThinWork = 384 << 20;
+constexpr float kThinDensity = 0.17f;          // (has a pattern table: kTableFromDensity)
 // Stored entries from which a row counts as dense: an eighth of its columns.  At batch 1024 such a row costs the matrix units
 // 0.30 us per 16384 columns and the staged kernel 2.0 us times its density among power-law rows.  On the bf16 units it costs 0.20, but the staged kernel
 // gains less from what is taken out of it: forward products of 16384^2 at batch 1024 with an 8th / 10th / 12th / 16th: 10 % 1590 / 1621 / 1635 / 1708 us,
@@ -375,9 +375,9 @@ bool sddmm_sampled_possible(const SddmmArgs &a);
 void add_sampled(SampledArgs &list, const SddmmArgs &a);
 hipError_t launch_sampled(SampledArgs &a, hipStream_t s);
 // Y = act(W X + b) of a matrix's dense rows, and the room in DenseRows that takes at up to max_batch columns
-bool dense_rows_product_ok(const DenseSplit *d, int32_t batch);
+bool dense_rows_product_ok(const DenseSplit *d, int32_t cols, int32_t batch);
 bool dense_rows_sddmm_ok(const DenseSplit *d, int32_t batch);
-int32_t thin_rows_gathered_up_to(const DenseSplit &d);   // the widest batch at which a product leaves its thin rows with the others; -1: it always does
+bool thin_rows_pay_somewhere(const DenseSplit &d, int32_t cols);
 bool sampled_operands_ok(const SddmmArgs &a);
 hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s);
 __host__ __device__ inline int64_t dense_rows_ld(int32_t batch) { return (batch + 31) / 32 * 32; }
@@ -524,9 +524,8 @@ __host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols
 // Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even with the fp32 units at 30 % (324 us; 20 %: 235 -> 326).
 __host__ __device__ inline bool dense_rows_pay(int32_t n_dense, int64_t dense_nnz, int64_t nnz, int32_t cols, int32_t max_batch)
 {
-    if (n_dense < kDenseRowsMin || dense_nnz * 8 < nnz || max_batch < dense_rows_from(n_dense, dense_nnz, cols)) return false;
-    return !dense_rows_thin(n_dense, dense_nnz, cols) ||
-           (n_dense >= kDenseRowsThinMin && cols >= kDenseRowsThinCols && dense_nnz * 100 >= static_cast<int64_t>(n_dense) * cols * kDenseRowsThinPercent);
+    return n_dense >= kDenseRowsMin && dense_nnz * 8 >= nnz && dense_nnz * 10 >= static_cast<int64_t>(n_dense) * cols * 3 &&
+           max_batch >= dense_rows_from(dense_nnz);
 }
 // which of `want` equal shares of the total cost a row falls into that has `done` of it before it
 __host__ __device__ inline int32_t staged_cut(int64_t done, int32_t want, int64_t total)

@@ -2725,7 +2725,7 @@ inline bool spans_below_4gib(int64_t rows, int64_t ld) { return rows * ld * 4 < 
 // the chip's 256 LDS serve at about one entry and tile per 3.3 ns each.
 bool spmm_dense_rows_ok(const SpmmArgs &a)
 {
-    return dense_rows_product_ok(a.split, a.batch) && !a.XM && spmm_offsets_ok(a);
+    return dense_rows_product_ok(a.split, a.x_rows, a.batch) && !a.XM && spmm_offsets_ok(a);
 }
 bool sddmm_dense_rows_ok(const SddmmArgs &a)
 {

@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kSpBlock) __attribute__((amdgpu_waves_per_eu(2, 2))
                 D.partial[(static_cast<int64_t>(slice) * D.n + k) * dense_rows_ld(a.batch) + col] = y;
                 continue;
             }
-            const int row = D.list[k];
+            const int row = D.list ? D.list[k] : k;
             if (a.bias) y += a.bias[row];
             if (a.relu) y = y > 0.f ? y : 0.f;
             if (a.YM) y = a.YM[static_cast<int64_t>(row) * a.ldym + col] > 0.f ? y : 0.f;

@@ -160,7 +160,6 @@ hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3, void **args, siz
         const PlanArgs &p = *static_cast<const PlanArgs *>(args[0]);
         memset(p.result, 0, sizeof(BindResult));
         memcpy(p.result->plan, counts, sizeof counts);
-        if (p.side[0].dense_len == INT32_MAX) p.result->plan[0].n_dense = 0;
     }
     return hipSuccess;
 }

@@ -132,12 +132,12 @@ def a_ticket_of_a_shared_tile_counts_to_one_number(L):
     L.destroy()
 
 
-def thin_rows_go_apart_where_the_bf16_units_pay(L):
-    """Rows of 17 to 30 %: by the estimates of gathering (staged where the batch fills its tiles) and of the split product, never on the
-    fp32 units.  Bound for the batch, as those were measured; where the operand's parts have no room they stay with the others."""
+def a_thin_matrix_takes_the_bf16_units_where_they_pay(L):
+    """A matrix of 17 to 30 %: by the estimates of gathering (staged where the batch fills its tiles) and of the split product, never on the
+    fp32 units.  Bound for the batch, as those were measured; where the operand's parts have no room it is gathered."""
     def bound(rows, cols, density, max_batch):
         nnz = int(rows * cols * density)
-        L.counts(0, n_blocks=600, n_dense=rows, dense_nnz=nnz, longest_row=cols // 3)
+        L.counts(0, n_blocks=600, longest_row=cols // 3)
         L.counts(1, n_blocks=600, longest_row=2000)
         return L.create(rows, cols, nnz, max_batch)
 
@@ -152,7 +152,10 @@ def thin_rows_go_apart_where_the_bf16_units_pay(L):
             (9019, 2137, 0.26, 288, 288, False), (9019, 2137, 0.26, 768, 768, True), (873, 11642, 0.27, 270, 270, True), (8192, 4096, 0.2, 257, 257, False),
             (8192, 4096, 0.2, 512, 512, True), (8192, 4096, 0.2, 1024, 1024, True), (8192, 4096, 0.2, 1024, 520, True), (8192, 4096, 0.2, 520, 520, False), (2600, 16384, 0.2, 256, 256, True),
             (2050, 2100, 0.278, 600, 600, True), (2050, 2100, 0.278, 600, 300, False), (2050, 2100, 0.2, 470, 470, False), (600, 38138, 0.25, 10474, 10474, False), (600, 38138, 0.25, 10474, 1024, True)):
+        L.launched()
         assert bound(rows, cols, density, max_batch) == 0
+        names = L.launched()
+        assert sum("11plan_kernel" in k for k in names) == 1 and sum("pattern_table_kernel" in k for k in names) == 1, names
         assert forward(batch) == split, (rows, cols, density, max_batch, batch)
         L.destroy()
     for k in range(100):
@@ -229,7 +232,7 @@ def a_single_tile_needs_no_partial_products(L):
     assert held[1] - held[0] == 1024 * (128 - 64) * 4, held   # (dZ, whose rows are 128 and 64 columns apart)
 
 
-CASES = [thin_rows_go_apart_where_the_bf16_units_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
