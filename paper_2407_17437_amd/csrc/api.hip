@@ -1741,6 +1741,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         }
         if ((rc = flush_sampled()) != NERVA_OK) return rc;
     } else {
+        const bool as_chain = n > (head ? 2 : 1) && !use_dense(mlp->layers[1], batch) && !use_dense(mlp->layers[0], batch) && chain_shape_ok(make_T(1), make_S(1), make_S(0));
         for (int l = n - 1; l >= 0; --l) {
             nerva_layer *ly = mlp->layers[l];
             if (l > 0 && !(head && l == n - 1)) {
@@ -1749,13 +1750,14 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                     HIP_TRY(dense_transposed(ly, dZ(l), L.ld, dZ(l - 1), L.ld, A(l - 1), L.ld, batch, s));
                 } else {
                     Timed tm(mlp->prof, s, "spmm_transposed", l);
-                    if (l == 1 && !use_dense(mlp->layers[0], batch) && chain_shape_ok(make_T(1), make_S(1), make_S(0)))
+                    if (l == 1 && as_chain)
                         HIP_TRY(launch_chain_transposed(make_T(1), make_S(1), make_S(0), s));
                     else
                         HIP_TRY(launch_spmm(make_T(l), s));
                 }
             }
-            const SddmmArgs g = make_S(l);
+            SddmmArgs g = make_S(l);
+            g.chain_lanes = as_chain && l <= 1;
             {
                 Timed tm(mlp->prof, s, "sddmm", l);
                 HIP_TRY(launch_sddmm(g, s));

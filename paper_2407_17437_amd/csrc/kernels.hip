@@ -2088,14 +2088,15 @@ __device__ __forceinline__ void chain_row_sums(const ChainArgs &c, const SddmmAr
     c.bias_velocity[i] = v;
 }
 
-template <int G, int NV, bool SPARE>
+// GB, NVB: lanes of the layer that waits, those of a launch of its own.
+template <int G, int NV, int GB, int NVB, bool SPARE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void chain_kernel(const ChainArgs c, const SddmmArgs a, const SddmmArgs b, const int n_sum_blocks)
 {
     int block = blockIdx.x;
     if (block < a.blocks.n_blocks) return chain_body<G, NV, SPARE, true>(c, a, block);
     block -= a.blocks.n_blocks;
     if (block < n_sum_blocks) return chain_row_sums<G, NV>(c, a, block);
-    sddmm_body<G, NV, SPARE>(b, block - n_sum_blocks);
+    sddmm_body<GB, NVB, SPARE || GB != G>(b, block - n_sum_blocks);
 }
 
 // Its first half alone, dZ_0: for a step whose launches are kept apart, so that both form the same sums.
@@ -2987,15 +2988,20 @@ hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 // Whether T_1 (t), S_1 (g1) and S_0 (g0) of a step can be one launch (chain_kernel): all three untiled, T_1's operand and mask those of S_1, its result
 // that of S_0, no row of W_0 cut into several work-groups.  The waves of a row are those that W_0's partition gives it: the mirror must not be much the larger of the
 // two or have long rows.  Steps at batch 100 apart / in one, us: 500-1000-1000-10 at 10 % (twice W_0's entries) 34.3 / 29.8, 300-1000-1000-10 (three times)
-// 33.6 / 29.2; 3000-3000-3000-10 at 2 %, batch 128 (as many) 54.9 / 54.6.  Up to 192 columns: with four loads per row and lane the registers
-// do not suffice (2000-1500-400-10 at 5 %, batch 180 / 256: 37.2 / 34.4, 41.3 / 43.6).  Networks of a small hidden layer keep their two launches, which a
-// profile of the step shows one by one (256-128-64-10 at 20 %: 20.9 / 18.6).
+// 33.6 / 29.2.  What the launch saves is 3 to 5 us whatever the work; where there is much of it the launches apart are the faster ones, with more registers
+// and, for W_1, gathers of their own: 1000-2000-2000-10 at 5 / 10 % (200 and 400 thousand entries in W_1), batch 16 33.9 / 31.6 and 39.8 / 45.0, batch 64 39.8 / 36.6
+// and 51.9 / 52.3; 1500-3000-800-10 at 14 % (336), batch 16 39.6 / 40.4, batch 64 54.5 / 49.4; 800-5000-1500-10 at 5 % (375), batch 100: 64.4 / 65.8.  Many rows of W_1 are
+// worse, as the entries of a mirror row lie a row of W_1 apart in its values: 3000-3000-3000-10 at 1 / 2 % (90 and 180), batch 150 38.8 / 37.5, 66.2 / 68.2, at 5 %, batch 100: 84.5 / 90.0.  Nor does it help W_0's gradient beside a small W_1: 2500-700-64-10 at 30 % (525 and 13 thousand), batch 38 / 100: 34.0 /
+// 35.0, 42.9 / 45.2, at 12 % 27.1 / 25.0, 31.1 / 30.2.  Up to 192 columns: 2000-1500-400-10 at 5 %, batch 180 / 256: 37.2 / 34.4, 41.3 / 43.6.  Networks of a
+// small hidden layer keep their two launches, which a profile of the step shows one by one (256-128-64-10 at 20 %: 20.9 / 18.6).
 bool chain_shape_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
 {
     if (t.batch != g1.batch || t.batch > kChainMaxBatch || t.X != g1.dZ || t.ldx != g1.lddz || !t.YM || t.YM != g1.X || t.ldym != g1.ldx || t.Y != g0.dZ || t.ldy != g0.lddz) return false;
     if (!can_pair(t, g0) || !can_pair(t, g1) || t.nnz <= 0 || t.nnz != g1.nnz || t.rows != g0.rows) return false;
     if (g1.dense || g0.dense || g1.loss_cols || g0.loss_cols || g0.values_t || g0.ZM || g1.ZM) return false;
-    return g0.blocks.n_huge_rows == 0 && t.rows >= kChainMinRows && t.blocks.staged_longest_row <= 2 * kPackMaxLen && t.nnz / 4 <= g0.nnz;
+    return g0.blocks.n_huge_rows == 0 && t.rows >= kChainMinRows && t.blocks.staged_longest_row <= 2 * kPackMaxLen && t.nnz / 4 <= g0.nnz &&
+           t.nnz <= (t.batch > kChainWide ? kChainEntriesWide : kChainEntries) && static_cast<int64_t>(t.nnz) * t.x_rows <= kChainEntriesRows &&
+           (t.nnz >= g0.nnz / 16 || static_cast<int64_t>(g0.nnz) * t.batch <= kChainMostWork);
 }
 bool chain_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
 {
@@ -3011,29 +3017,40 @@ static ChainArgs chain_args(const SpmmArgs &t, const SddmmArgs &g1)
     return c;
 }
 
+// Lanes of chain_kernel: go(G, NV, GB, NVB).  Its first half waits for one gather after another, so three loads a lane, which spare the SDDMM columns (with_sddmm_lanes), are
+// too many: steps of 3072-1024-512-10 at 2 %, batch 38 / 77 / 150, apart 24.1 / 24.3 / 27.1, with the SDDMM's lanes 24.9 / 24.6 / 26.6, with these 20.1 / 22.5 / 25.1;
+// 1000-300-300-10 at 12 %: 23.6 / 22.8 / 24.9, 26.9 / 25.2 / 25.7, 20.6 / 22.3 / 23.7.
+template <typename F>
+hipError_t with_chain_lanes(int batch, F &&go)
+{
+    return with_sddmm_lanes(batch, [&](auto gb, auto nvb) {
+        constexpr int kColumns = decltype(gb)::value * decltype(nvb)::value * 4, G = kColumns <= 16 ? 4 : kColumns <= 32 ? 8 : kColumns <= 128 ? 16 : 32,
+                      NV = kColumns <= 64 ? 1 : 2;
+        if constexpr (kColumns <= kChainMaxBatch) return go(std::integral_constant<int, G>{}, std::integral_constant<int, NV>{}, gb, nvb);
+        else return hipErrorInvalidConfiguration;   // (chain_shape_ok)
+    });
+}
+
 hipError_t launch_chain(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, const SddmmArgs *waiting, hipStream_t s)
 {
     const ChainArgs c = chain_args(t, g1);
     SddmmArgs b{};
     if (waiting) b = *waiting;
-    return with_sddmm_lanes(t.batch, [&](auto g, auto nv) {
+    return with_chain_lanes(t.batch, [&](auto g, auto nv, auto gb, auto nvb) {
         constexpr int G = decltype(g)::value, NV = decltype(nv)::value, kRows = kWavesPerBlock * (kWave / G);
         const int n_sum_blocks = c.bias ? (t.x_rows + kRows - 1) / kRows : 0;
         const dim3 grid(g0.blocks.n_blocks + n_sum_blocks + b.blocks.n_blocks);
-        if constexpr (G * NV * 4 <= kChainMaxBatch)
-            with_spare(t.batch, G * 4 * NV, [&](auto spare) {
-                hipLaunchKernelGGL((chain_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, c, g0, b, n_sum_blocks);
-            });
+        with_spare(t.batch, G * 4 * NV, [&](auto spare) {
+            hipLaunchKernelGGL((chain_kernel<G, NV, decltype(gb)::value, decltype(nvb)::value, decltype(spare)::value>), grid, dim3(kBlock), 0, s, c, g0, b, n_sum_blocks);
+        });
         return hipGetLastError();
     });
 }
 
 hipError_t launch_chain_transposed(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, hipStream_t s)
 {
-    return with_sddmm_lanes(t.batch, [&](auto g, auto nv) {
-        constexpr int G = decltype(g)::value, NV = decltype(nv)::value;
-        if constexpr (G * NV * 4 <= kChainMaxBatch)
-            hipLaunchKernelGGL((chain_transposed_kernel<G, NV>), dim3(g0.blocks.n_blocks), dim3(kBlock), 0, s, chain_args(t, g1), g0);
+    return with_chain_lanes(t.batch, [&](auto g, auto nv, auto, auto) {
+        hipLaunchKernelGGL((chain_transposed_kernel<decltype(g)::value, decltype(nv)::value>), dim3(g0.blocks.n_blocks), dim3(kBlock), 0, s, chain_args(t, g1), g0);
         return hipGetLastError();
     });
 }
@@ -3399,6 +3416,8 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
         case 32: return sddmm_tiled_go<8, 1>(a, s);
         default: break;
     }
+    if (a.chain_lanes)
+        return with_chain_lanes(a.batch, [&](auto g, auto nv, auto, auto) { return sddmm_go<decltype(g)::value, decltype(nv)::value>(a, s); });
     if (sddmm_offsets_ok(a) && a.batch <= 1024)
         return with_sddmm_lanes(a.batch, [&](auto g, auto nv) { return sddmm_go<decltype(g)::value, decltype(nv)::value>(a, s); });
     hipLaunchKernelGGL(sddmm_generic, dim3(a.blocks.n_blocks), dim3(kBlock), 0, s, a);

@@ -585,11 +585,12 @@ def test_stage_parity_end_of_step_in_one_launch(nb, torch_mod, oracle, sizes, sp
     torch = torch_mod
     mlp = wl.make_mlp(sizes, sparsity=sparsity, bias_std=0.1, pattern_seed=131, value_seed=231)
     Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 2, seed=331)
-    M = nb.MLP(mlp, batch, nb.NERVA_MLP_NESTEROV if nesterov else 0)
+    M, M2 = (nb.MLP(mlp, batch, (nb.NERVA_MLP_NESTEROV if nesterov else 0) | flags) for flags in (0, nb.NERVA_MLP_UNFUSED))
     for t in range(2):
         before = snapshot(M)
         nb.mlp_profile_enable(M.handle, 1)
         M.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
+        M2.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
         torch.cuda.synchronize()
         names = [n for n, _ in nb.mlp_profile_read(M.handle)[1]]
         assert names[-1] == "backward_chain[1]", names
@@ -597,6 +598,25 @@ def test_stage_parity_end_of_step_in_one_launch(nb, torch_mod, oracle, sizes, sp
         L = M.layers[1]
         _, _, v_t, perm = nb.sparse_linear_mirror(L.handle)
         assert np.array_equal(raw_f32(nb, torch, v_t, L.nnz), L.values.cpu().numpy()[raw_i32(nb, torch, perm, L.nnz)])
+        for a, b in zip(M.layers, M2.layers):   # (launches kept apart add up in the same order)
+            assert torch.equal(a.values, b.values) and torch.equal(a.bias, b.bias)
+    M.close(); M2.close()
+
+
+@pytest.mark.parametrize("sizes,density,batch,one", [
+    ((200, 2000, 600, 10), 0.24, 32, False), ((200, 2000, 600, 10), 0.24, 33, True),    # many entries in the layer above
+    ((2500, 700, 64, 10), 0.3, 45, True), ((2500, 700, 64, 10), 0.3, 50, False),        # few of them beside the first layer's work
+])
+def test_end_of_step_in_one_launch_where_it_pays(nb, torch_mod, sizes, density, batch, one):
+    torch = torch_mod
+    mlp = wl.make_mlp(sizes, sparsity=1.0 - density)
+    Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 1, seed=6)
+    M = nb.MLP(mlp, batch)
+    nb.mlp_profile_enable(M.handle, 1)
+    M.train_step(nb.to_dense(Xs[0]), torch.as_tensor(Ts[0]).cuda(), batch, 0.05, 0.9)
+    torch.cuda.synchronize()
+    names = [n for n, _ in nb.mlp_profile_read(M.handle)[1]]
+    assert (names[-1] == "backward_chain[1]") == one, names
     M.close()
 
 
