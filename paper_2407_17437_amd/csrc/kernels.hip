@@ -1675,7 +1675,8 @@ constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and
 enum BackwardSpare { kSpareNone, kSpareLanes, kSpareColumns };
 __device__ __forceinline__ float keep_bits(float x, uint32_t mask) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & mask); }
 // APART: every gather before the first product, which the compiler else mixes to save registers, with two or three in flight.  One tile on 4096 x 3072 at
-// 5 %, batch 128: 25.3 -> 23.4 us; column tiles lose with fewer waves (wide MLP 97.3 -> 99.2), and masked gathers take too many registers.
+// 5 %, batch 128: 25.3 -> 23.4 us; column tiles lose with fewer waves (wide MLP 97.3 -> 99.2), and masked gathers take too many registers.  One tile loses as well
+// where its waves are more than fit at once with that many registers (backward_gathers_apart).
 template <int U, int GS, bool XMASK, BackwardSpare SPARE, bool APART>
 __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int my_ro, int my_mo, float my_w, uint32_t off, const float4 &ax,
                                          const uint32_t (&own)[4], int it0, int lig, float (&acc)[4], float &res)
@@ -1742,11 +1743,11 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // the lane groups and the matrix is small: then a wave takes its entries through all tiles.  XMASK: dZ is dY times
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
-template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE>
+template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE, bool APART>
 __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const TileOrder order,
                                                                           const int n_pack_blocks, const int lg_split)
 {
-    constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped, kApart = PASS == kBackwardOneTile && !XMASK;
+    constexpr bool ONE = PASS != kBackwardTiles, LOOPED = PASS == kBackwardLooped;
     if (ONE && static_cast<int>(blockIdx.x) >= n_pack_blocks) {
         backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_pack_blocks) * kBwdWaves + wave_in_block(),
                           static_cast<int64_t>(gridDim.x - n_pack_blocks) * kBwdWaves);
@@ -1825,16 +1826,16 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                     float res = 0.f;
                     int src = src0;
                     int u0 = 0;
-                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                     if (u0 + 4 <= steps) {
-                        bwd_pass<4, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                        bwd_pass<4, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                         u0 += 4; src += 16;
                     }
                     if (u0 + 2 <= steps) {
-                        bwd_pass<2, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                        bwd_pass<2, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                         u0 += 2; src += 8;
                     }
-                    if (u0 < steps) bwd_pass<1, GS, XMASK, SPARE, kApart>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                    if (u0 < steps) bwd_pass<1, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                     const int e = base + part * GS + lig;
                     if (row >= 0 && e < len) {
                         if constexpr (ONE) {
@@ -3163,6 +3164,15 @@ hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream
     return hipGetLastError();
 }
 
+// Whether the waves of one tile have all gathers of a pass in flight (APART, 70 to 82 registers, 5 to 7 waves a SIMD) or two or three (62 to 78, 6 to 8).  Uniform rows, apart /
+// mixed, us: batch 16, 8000 x 1000 at 12 % 3 % faster apart, 700 x 6000 at 12 % 12.6 / 11.6, 3000 x 16384 at 12 % 150 / 131; batch 64, 4096 x 3072 at 6 % 18 % faster,
+// 2000 x 4500 at 25 % 59.7 / 54.0, 1500 x 6400 at 12 % 31.9 / 36.6; batch 128, 2166 x 2945 at 12 % 8 % faster, 700 x 7000 at 25 % 44.9 / 41.0, 1500 x 8000 at 25 % 99 / 112,
+// 700 x 13000 at 12 % 40.0 / 38.0, 3000 x 16384 at 12 % 200 / 208; batch 256 never slower.
+static bool backward_gathers_apart(int gs, int64_t waves)
+{
+    return waves <= (gs == 8 ? 2048 : 4096) || gs == 64 || (gs == 16 && waves > 6144) || (gs == 32 && waves >= 16384);
+}
+
 hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s)
 {
     BackwardArgs a{};
@@ -3187,9 +3197,13 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         constexpr int GS = decltype(group)::value;
         const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
         auto launch = [&](auto pass, auto mask) {
+            constexpr bool kOne = decltype(pass)::value == kBackwardOneTile && !decltype(mask)::value;
             auto with = [&](auto spare) {
-                hipLaunchKernelGGL((backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value>), grid, block, 0, s, a,
-                                   n_tiles, order, n_pack_blocks, lg_split);
+                auto kernel = backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value, kOne>;
+                if constexpr (kOne && (GS == 8 || decltype(spare)::value == kSpareNone))   // (else both variants take the same registers)
+                    if (!backward_gathers_apart(GS, static_cast<int64_t>(n_pack_blocks) * kBwdWaves))
+                        kernel = backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value, false>;
+                hipLaunchKernelGGL(kernel, grid, block, 0, s, a, n_tiles, order, n_pack_blocks, lg_split);
             };
             if (a.batch % (GS * 4) == 0) return with(std::integral_constant<BackwardSpare, kSpareNone>{});
             if constexpr (decltype(pass)::value == kBackwardTiles)

@@ -270,6 +270,12 @@ def test_uniform_rows_on_the_bf16_units(nb, oracle, low, high, batches):
         check_layer(nb, oracle, lay, batch, max_batch=batches[1])
 
 
+@pytest.mark.parametrize("batch", [16, 32, 64, 128])
+def test_both_gradients_in_one_tile_of_more_waves_than_fit_at_once(nb, oracle, batch):
+    """2125, 4250 and 8500 waves: two or three gathers in flight (test_host_memory)."""
+    check_layer(nb, oracle, layer_case(60, 17000, 0.01, seed=batch), batch)
+
+
 def test_huge_rows_after_products_that_overlapped(nb, oracle):
     """Products of one layer on several streams at once may spoil one another (their results are not looked at), but no product
     that is ordered after them: the shares of its huge rows are counted from 0 again, in both orientations."""

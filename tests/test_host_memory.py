@@ -232,7 +232,20 @@ def a_single_tile_needs_no_partial_products(L):
     assert held[1] - held[0] == 1024 * (128 - 64) * 4, held   # (dZ, whose rows are 128 and 64 columns apart)
 
 
-CASES = [a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit(L):
+    for cols, batch, apart in ((17000, 16, False), (17000, 32, False), (17000, 64, False), (17000, 128, False), (17000, 256, True), (16000, 16, True), (16000, 32, True), (16000, 64, True), (8000, 128, True),
+                               (25000, 64, True), (33000, 128, True)):
+        L.counts(0, n_blocks=600, longest_row=300)
+        L.counts(1, n_blocks=600, longest_row=10)
+        assert L.create(60, cols, 10200, 256) == 0
+        L.launched()
+        assert L.backward(batch) == 0
+        names = [k for k in L.launched() if "backward_fused_kernel" in k]
+        assert len(names) == 1 and ("BackwardPassE1" in names[0]) and ("SpareE%dELb%dEE" % (2 if batch == 16 else 0, apart) in names[0]), (cols, batch, names)
+        L.destroy()
+
+
+CASES = [gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
