@@ -1757,6 +1757,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     if constexpr (ONE) {
         tile = 0;
         rb = blockIdx.x;
+        if (n_tiles <= 0) return;   // (never; the loop over all tiles takes 10 to 20 registers more where it might not run: 5000^2 at 0.1 %, batch 260 9.4 -> 11.6 us)
     } else {
         if (!tile_of_block(n_tiles, n_pack_blocks, order, tile, rb)) return;
     }
