@@ -3165,13 +3165,16 @@ hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream
     return hipGetLastError();
 }
 
-// Whether the waves of one tile have all gathers of a pass in flight (APART, 70 to 82 registers, 5 to 7 waves a SIMD) or two or three (62 to 78, 6 to 8).  Uniform rows, apart /
-// mixed, us: batch 16, 8000 x 1000 at 12 % 3 % faster apart, 700 x 6000 at 12 % 12.6 / 11.6, 3000 x 16384 at 12 % 150 / 131; batch 64, 4096 x 3072 at 6 % 18 % faster,
-// 2000 x 4500 at 25 % 59.7 / 54.0, 1500 x 6400 at 12 % 31.9 / 36.6; batch 128, 2166 x 2945 at 12 % 8 % faster, 700 x 7000 at 25 % 44.9 / 41.0, 1500 x 8000 at 25 % 99 / 112,
-// 700 x 13000 at 12 % 40.0 / 38.0, 3000 x 16384 at 12 % 200 / 208; batch 256 never slower.
-static bool backward_gathers_apart(int gs, int64_t waves)
+// Whether the waves of one tile have all gathers of a pass in flight (APART, 70 to 82 registers, 5 to 7 waves a SIMD) or two or three (62 to 78, 6 to 8): where few waves leave
+// room anyway, and in groups of 16 where rows are short.  Uniform rows, us, mixed -> apart: batch 16, 8000 x 1000 at 12 % 3 % faster, 700 x 6000 at 12 % 11.6 -> 12.6, 3000 x 16384 at
+// 12 % 131 -> 150; batch 64, 2048 x 3000 at 10 / 40 % 21.2 -> 18.6, 60.5 -> 53.9, 2048 x 4096 at 10 / 40 % 24.4 -> 23.0, 73.9 -> 79.4, 2048 x 5500 at 10 / 40 % 30.2 -> 30.7, 107 -> 124,
+// 3000 x 8192 at 5 / 40 % 34.8 -> 32.3, 226 -> 258; batch 128, 2048 x 3000 at 10 % 26.3 -> 25.1, 2048 x 3400 28.2 -> 28.6, 2048 x 6500 48.3 -> 50.6, 3000 x 13000 at 2 % 30.5 -> 33.2,
+// 3000 x 16384 at 12 % 208 -> 200; batch 256 not slower up to 25 %.
+static bool backward_gathers_apart(int gs, int64_t waves, const SpmmArgs &t)
 {
-    return waves <= (gs == 8 ? 2048 : 4096) || gs == 64 || (gs == 16 && waves > 6144) || (gs == 32 && waves >= 16384);
+    if (gs == 8) return waves <= 2048;
+    if (gs == 16) return waves <= 3072 || (t.nnz <= 256ll * t.rows && (waves <= 4096 || waves > 6144));
+    return gs == 64 || waves <= 3072 || waves >= 16384;
 }
 
 hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s)
@@ -3202,7 +3205,7 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
             auto with = [&](auto spare) {
                 auto kernel = backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value, kOne>;
                 if constexpr (kOne && (GS == 8 || decltype(spare)::value == kSpareNone))   // (else both variants take the same registers)
-                    if (!backward_gathers_apart(GS, static_cast<int64_t>(n_pack_blocks) * kBwdWaves))
+                    if (!backward_gathers_apart(GS, static_cast<int64_t>(n_pack_blocks) * kBwdWaves, t))
                         kernel = backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value, false>;
                 hipLaunchKernelGGL(kernel, grid, block, 0, s, a, n_tiles, order, n_pack_blocks, lg_split);
             };

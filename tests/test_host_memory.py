@@ -233,8 +233,8 @@ def a_single_tile_needs_no_partial_products(L):
 
 
 def gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit(L):
-    for cols, batch, apart in ((17000, 16, False), (17000, 32, False), (17000, 64, False), (17000, 128, False), (17000, 256, True), (16000, 16, True), (16000, 32, True), (16000, 64, True), (8000, 128, True),
-                               (25000, 64, True), (33000, 128, True)):
+    for cols, batch, apart in ((17000, 16, False), (17000, 32, False), (17000, 64, False), (17000, 128, False), (17000, 256, True), (16000, 16, True), (16000, 32, True), (16000, 64, True), (6100, 128, True),
+                               (6200, 128, False), (25000, 64, True), (33000, 128, True)):
         L.counts(0, n_blocks=600, longest_row=300)
         L.counts(1, n_blocks=600, longest_row=10)
         assert L.create(60, cols, 10200, 256) == 0
