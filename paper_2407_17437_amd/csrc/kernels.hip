@@ -452,19 +452,22 @@ __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int bl
     }
 }
 
-// Which column tile, and which of the launch's n_blocks work-groups of rows, a work-group serves.  Without runs: tile by tile, all XCDs on one tile.  Otherwise
-// the list of all of them is cut into eight equal runs, one per XCD (work-groups go to the XCDs in turn), so that an L2 sees an eighth of
-// the tiles and one more; the stride, which has no factor in common with n_blocks, is the order within a tile.  (tile_order chooses.)
+// Which column tile, and which of the launch's n_blocks work-groups of rows, a work-group serves (they go to the XCDs in turn).  One by one: tile by tile, all XCDs on one tile.
+// Whole: every eighth tile to an XCD, so that eight of them side by side are read at a time.  Otherwise the list of all work-groups is cut into eight equal runs, one per XCD, so that
+// an L2 sees an eighth of the tiles and one more; the stride, which has no factor in common with n_blocks, is the order within a tile.  (tile_order chooses.)
+enum : int { kTilesOneByOne = 0, kTilesWhole = -1 };
 struct TileOrder {
-    int per, stride;   // an eighth of the grid (an argument: the grid's size costs a load), or 0: no runs
+    int per, stride;   // an eighth of the grid (an argument: the grid's size costs a load), or one of the above
 };
 __device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, TileOrder order, int &tile, int &block)
 {
     const int stride = order.stride;
     int at = blockIdx.x;
     if (order.per > 0) at = (blockIdx.x & 7) * order.per + (blockIdx.x >> 3);
+    if (order.per < 0) at = blockIdx.x >> 3;
     tile = at / n_blocks;
     block = at - tile * n_blocks;
+    if (order.per < 0) tile = tile * 8 + (blockIdx.x & 7);
     if (stride > 1) block = static_cast<int>(static_cast<uint32_t>(block) * static_cast<uint32_t>(stride) % static_cast<uint32_t>(n_blocks));
     return tile < n_tiles;
 }
@@ -2635,30 +2638,53 @@ int spmm_tile_group(const SpmmArgs &a)
 
 constexpr int64_t kMaxGridIds = (1ll << 31) - 1;
 
-// Grid and order of launches in column tiles (tile_of_block).  Multiples of eight tiles go whole to the XCDs.  More than eight are dealt out in equal
-// runs: 8192^2 uniform at 0.6 %, batch 600 / 700 (10 / 11 tiles), forward 70.1 -> 48.7 and 71.9 -> 57.8 us against whole tiles, of which some XCDs had two
-// and the others one; 16384^2 at 1 %, batch 600: 633 -> 406.  Fewer: only products whose tile is well within an L2 (`small`; the former at batch 300,
-// 5 tiles: 35.9 -> 31.5), as gradients lose (5000^2 at 2 %, batch 200: 39.5 -> 42.9) and so do tiles that fill one (16384^2 at 1 %, batch 200: 161 -> 168).
+// Grid and order of launches in column tiles (tile_of_block).  Whole tiles leave some XCDs idle in the last round; equal runs do not, but an L2 then sees one tile more and
+// shares two.  From eight tiles on runs pay where whole tiles waste an eighth or more: 8192^2 uniform at 0.6 %, batch 600 / 700 (10 / 11 tiles), forward 70.1 -> 48.7
+// and 71.9 -> 57.8 us; 16384^2 at 1 %, batch 600: 633 -> 406, at batch 850 (14): 702 -> 625, at 900 (15) 707 -> 665; but 4000 x 9000 at 1.2 %, batch 850 / 900: 77.1 -> 84.0, 77.1 -> 87.6, and
+// with rows of different lengths 3000 x 12000 at 0.4 %: 66.9 -> 73.7, 66.5 -> 77.2.
+// Fewer tiles, which all XCDs walk together otherwise: only products whose tile is well within an L2 (8192^2 at 0.6 %, batch 300, 5 tiles: 35.9 -> 31.5), as gradients lose
+// (5000^2 at 2 %, batch 200: 39.5 -> 42.9) and so do tiles that fill one (16384^2 at 1 %, batch 200: 161 -> 168), and where an operand row is gathered so
+// rarely that bringing the tile counts: 4000 x 9000 at 1.2 % (48 entries a row), batch 300: 20 % faster, 8192^2 at 1.2 % (98), batch 200 / 300: 49.0 -> 53.0, 8 % faster, at 3 %
+// (245) 101 -> 110, 127 -> 145; power-law 8192^2 at 1.2 %, batch 256, transposed: 47.0 -> 58.3; 5000^2 at 7 %, batch 350 / 700 (3 / 6): 86 -> 93, 168 -> 152.
 // Rows of very different lengths are strewn over a run that does not hold whole tiles, for the long ones come first in each.
-inline int64_t tile_grid(int64_t n_tiles, int64_t n_blocks) { return (n_tiles * n_blocks + 7) / 8 * 8; }
-inline TileOrder tile_order(int n_tiles, int64_t n_blocks, bool small, int longest_row, int rows, int64_t nnz)
+struct TiledLaunch {
+    int x_rows, rows, longest_row;
+    int64_t nnz;
+    float hot_share;
+};
+inline TileOrder tile_order(int n_tiles, int64_t n_blocks, int gs, bool product, const TiledLaunch &t)
 {
-    TileOrder order{0, 1};
-    if (n_tiles < 8 && !small) return order;
-    order.per = static_cast<int>(tile_grid(n_tiles, n_blocks) / 8);
-    if (n_tiles % 8 == 0 || n_blocks < 8 || n_blocks >= (1 << 16) || static_cast<int64_t>(longest_row) * rows <= 4 * nnz) return order;
+    const int64_t tile_bytes = static_cast<int64_t>(t.x_rows) * gs * 16;
+    const bool small = product && tile_bytes <= (5 << 19);   // (2.5 MiB)
+    const bool skewed = static_cast<int64_t>(t.longest_row) * t.rows > 4 * t.nnz, hot = t.hot_share >= 0.5f;
+    if (n_tiles < 8) {
+        const bool rarely = t.nnz <= (skewed || hot ? (n_tiles == 7 ? 128ll : 40ll) : n_tiles >= 5 ? 128ll : 90ll) * t.x_rows;
+        const bool long_rows = skewed && !hot && n_tiles >= (gs == 32 && tile_bytes >= (15 << 17) ? 5 : 7);   // (among short ones)
+        if (!small || !(rarely || long_rows)) return TileOrder{kTilesOneByOne, 1};
+    } else {
+        const double waste = (n_tiles + 7) / 8 * 8 / static_cast<double>(n_tiles);
+        const bool runs = waste >= 1.15 || (!skewed && (waste >= 1.13 ? !small || 2 * t.rows >= t.x_rows : waste >= 1.06 && tile_bytes >= (7 << 19) && t.nnz <= 512ll * t.x_rows));
+        if (!runs) return TileOrder{kTilesWhole, 1};
+    }
+    TileOrder order{static_cast<int>((n_tiles * n_blocks + 7) / 8), 1};
+    if (n_blocks < 8 || n_blocks >= (1 << 16) || !skewed) return order;
     order.stride = static_cast<int>(n_blocks * 0.618);
     while (std::gcd(order.stride, static_cast<int>(n_blocks)) != 1) ++order.stride;
     return order;
 }
-inline bool small_tile(int x_rows, int gs) { return static_cast<int64_t>(x_rows) * gs * 16 <= (5 << 19); }   // (2.5 MiB)
+inline int64_t tile_grid(const TileOrder &order, int64_t n_tiles, int64_t n_blocks)
+{
+    return order.per > 0 ? 8ll * order.per : order.per == kTilesWhole ? (n_tiles + 7) / 8 * 8 * n_blocks : n_tiles * n_blocks;
+}
+template <typename Args>
+inline TiledLaunch tiled_launch(const Args &a) { return TiledLaunch{a.x_rows, a.rows, a.blocks.staged_longest_row, a.nnz, a.blocks.hot_share}; }
 
 template <int GS>
 hipError_t spmm_tiled_go(const SpmmArgs &a, hipStream_t s)
 {
     const int n_tiles = (a.batch + GS * 4 - 1) / (GS * 4);
-    const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, small_tile(a.x_rows, GS), a.blocks.staged_longest_row, a.rows, a.nnz);
-    const int64_t ids = tile_grid(n_tiles, a.blocks.n_blocks);
+    const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, GS, true, tiled_launch(a));
+    const int64_t ids = tile_grid(order, n_tiles, a.blocks.n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
     if (a.XM)
         hipLaunchKernelGGL((spmm_tiled_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, order);
@@ -2682,8 +2708,8 @@ PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
     const int64_t n_sets = (static_cast<int64_t>(a.blocks.n_short) + ne - 1) / ne;
     g.n_pack_blocks = static_cast<int>((n_sets + kWavesPerBlock * kPackSets - 1) / (kWavesPerBlock * kPackSets));
     const int64_t nrb = static_cast<int64_t>(g.n_pack_blocks) + (with_long_rows ? a.blocks.n_long_blocks : 0);
-    g.order = tile_order(g.n_tiles, nrb, small_tile(a.x_rows, gs), a.blocks.staged_longest_row, a.rows, a.nnz);
-    g.ids = tile_grid(g.n_tiles, nrb);
+    g.order = tile_order(g.n_tiles, nrb, gs, true, tiled_launch(a));
+    g.ids = tile_grid(g.order, g.n_tiles, nrb);
     return g;
 }
 template <int GS>
@@ -2835,8 +2861,8 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
 {
     const int W = G * 4 * NV;
     const int n_tiles = (a.batch + W - 1) / W;
-    const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, false, a.blocks.staged_longest_row, a.rows, a.nnz);
-    const int64_t ids = tile_grid(n_tiles, a.blocks.n_blocks);
+    const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, W / 4, false, tiled_launch(a));
+    const int64_t ids = tile_grid(order, n_tiles, a.blocks.n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
     with_spare(a.batch, W, [&](auto spare) {
         hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, n_tiles, order);
@@ -3195,8 +3221,8 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     const bool one = n_tiles == 1 || (alone && backward_looped(t));
     const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
-    const int64_t ids = one ? n_pack_blocks + n_row_blocks : tile_grid(n_tiles, n_pack_blocks);
-    const TileOrder order = tile_order(n_tiles, n_pack_blocks, false, t.blocks.staged_longest_row, t.rows, t.nnz);
+    const TileOrder order = tile_order(n_tiles, n_pack_blocks, tg, false, tiled_launch(t));
+    const int64_t ids = one ? n_pack_blocks + n_row_blocks : tile_grid(order, n_tiles, n_pack_blocks);
     auto go = [&](auto group) {
         constexpr int GS = decltype(group)::value;
         const dim3 grid(static_cast<unsigned>(ids)), block(kBwdWaves * kWave);
@@ -3418,8 +3444,10 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
             SddmmArgs rest = a;
             rest.blocks.waves = a.blocks.rest_waves;
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
-            const TileOrder order = tile_order(n_tiles, rest.blocks.n_blocks, false, 0, a.rows, a.nnz);
-            const int64_t ids = tile_grid(n_tiles, rest.blocks.n_blocks);
+            TiledLaunch like = tiled_launch(a);
+            like.longest_row = 0;   // (none of the rest is long)
+            const TileOrder order = tile_order(n_tiles, rest.blocks.n_blocks, kStageCols / 4, false, like);
+            const int64_t ids = tile_grid(order, n_tiles, rest.blocks.n_blocks);
             with_spare(a.batch, kStageCols, [&](auto spare) {
                 hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1, decltype(spare)::value>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles,
                                    order);
