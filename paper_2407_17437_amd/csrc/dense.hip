@@ -104,13 +104,15 @@ __device__ __forceinline__ void nn_mfma(const NnChunk<MB, NB> &C, v4f (&acc)[MB]
         }
 }
 
-constexpr int kNnWaves = 4;   // 1024 x 3072 at batch 100, 4096 x 2048 at batch 256 with 4 / 8 / 16 waves: 16.0 / 16.5 / 17.7, 51.8 / 54.7 / 64.6 us
-constexpr int kNnBlock = kNnWaves * kWave;
+// 1024 x 3072 at batch 100, 4096 x 2048 at batch 256 with 4 / 8 / 16 waves: 16.0 / 16.5 / 17.7, 51.8 / 54.7 / 64.6 us; twice as many (W) where work-groups of one tile leave
+// compute units idle: 512 x 1024 at batch 64 (with the copy's refresh) 9.6 -> 9.0, 1024 x 3072 at 20 24.0 -> 21.8, 300 x 5000 at 100 34.1 -> 31.2, but 512 x 1024 at 150 (320 work-groups)
+// 11.2 -> 11.9.
+constexpr int kNnWaves = 4;
 constexpr int kNnAhead = 2;    // chunks of a wave; the same with 1 / 2 / 3 / 6: 23.8 / 16.1 / 16.4 / 17.1, 52.9 / 50.8 / 51.8 / 59.9
-template <int MB, int NB>
-__global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a, const int slices)
+template <int MB, int NB, int W = kNnWaves>
+__global__ __launch_bounds__(W * kWave) void dense_nn_kernel(const DenseArgs a, const int slices)
 {
-    __shared__ float part[kNnWaves][MB][NB][4][kWave];
+    __shared__ float part[W][MB][NB][4][kWave];
     __shared__ int turn_s;
     const int lane = threadIdx.x & (kWave - 1), wv = wave_id();
     const int r = lane & 15, q = lane >> 4;
@@ -124,8 +126,8 @@ __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a, c
     const int K = a.cols;
     const int col = min(n0 + NB * r, a.batch - NB);
     const int k16 = K / 16;                                          // whole chunks of 16 k; the rest is the last wave's
-    const int per = (k16 + kNnWaves * slices - 1) / (kNnWaves * slices);
-    const int c_begin = min((slice * kNnWaves + wv) * per, k16), c_end = min(c_begin + per, k16);
+    const int per = (k16 + W * slices - 1) / (W * slices);
+    const int c_begin = min((slice * W + wv) * per, k16), c_end = min(c_begin + per, k16);
     v4f acc[MB][NB];
 #pragma unroll
     for (int m = 0; m < MB; ++m)
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a, c
             nn_mfma<MB, NB>(ring[d], acc);
         }
     }
-    if (k16 * 16 < K && wv == kNnWaves - 1 && slice == slices - 1) {  // uniform
+    if (k16 * 16 < K && wv == W - 1 && slice == slices - 1) {  // uniform
         NnChunk<MB, NB> C;   // the operand's rows past K count as 0 (the copy holds zeros there, which an infinity would not leave zero)
 #pragma unroll
         for (int m = 0; m < MB; ++m) C.w4[m] = ld4(wrow[m] + k16 * 16);
@@ -180,6 +182,7 @@ __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a, c
 #pragma unroll
             for (int g = 0; g < 4; ++g) part[wv][m][t][g][lane] = acc[m][t][g];
     __syncthreads();
+    if (W > kNnWaves && wv >= kNnWaves) return;   // (four registers to add up)
     float y[MB][NB];
 #pragma unroll
     for (int m = 0; m < MB; ++m)
@@ -187,9 +190,9 @@ __global__ __launch_bounds__(kNnBlock) void dense_nn_kernel(const DenseArgs a, c
         for (int t = 0; t < NB; ++t) {
             y[m][t] = 0.f;
 #pragma unroll
-            for (int w = 0; w < kNnWaves; ++w) y[m][t] += part[w][m][t][wv][lane];
+            for (int w = 0; w < W; ++w) y[m][t] += part[w][m][t][wv][lane];
         }
-    if (slices > 1) {  // uniform
+    if (W == kNnWaves && slices > 1) {  // uniform
         // as the shares of a huge row (huge_row_share): out and back past the L2s, the last work-group of the tile adds them in slice order
         constexpr int kShare = MB * NB * kNnWaves * kWave;
         const int tile = m_tile * n_col_tiles + col_tile;
@@ -793,16 +796,21 @@ static int dense_nb(int64_t m_tiles, int batch)
 // memory pipe was 90 % busy, the MFMA pipes 39, at 16 x 32), so tiles are as wide as 256 of them allow: 64 columns are loaded as fast as 32.  Where
 // there are a few less and the sum is long, work-groups share a tile, which costs 3 to 4 us.  us, before -> with 16 x 64 in two slices:
 // 1024 x 3072 at batch 100 15.1 -> 13.0, 1024 x 1536 10.0 -> 9.5, 2048 x 2048 at 64 11.2 -> 10.8, 2048 x 4096 at 64 19.0 -> 15.8 (512 x 1024 at 100
-// 6.2 -> 7.7); in four: 1024 x 4096 at 64 16.3 -> 11.6, 512 x 3072 at 100 12.9 -> 10.2, 512 x 2048 9.4 -> 9.0, 1024 x 2000 at 64 9.6 -> 9.1.  With 32 x 64
-// (for long sums: 4096 x 2048 at batch 1024 189 -> 193): 1024 x 3072 at 512 38.8 -> 32.0, 2048 x 4096 at 256 48.1 -> 40.0, at 1024 186 -> 178.
+// 6.2 -> 7.7); in four: 1024 x 4096 at 64 16.3 -> 11.6, 512 x 3072 at 100 12.9 -> 10.2, 512 x 2048 9.4 -> 9.0, 1024 x 2000 at 64 9.6 -> 9.1 (1024 x 1536 at 64, with the copy's refresh,
+// 13.1 -> 14.0).
+// 32 x 64 is a tenth faster than two of 16 x 64 one after the other, so it pays where it leaves no compute unit with more of them (with the copy's refresh): 1024 x 3072 at batch 512 (256
+// work-groups) 46.7 -> 40.8, 2048 x 2560 at 200 (256) 41.2 -> 36.9, 4096 x 2048 at 128 (256) 39.7 -> 36.0, at 1024 (2048) 203 -> 196; but 1024 x 3072 at 700 (352) 62.3 -> 76.5, 2048 x 3072 at
+// 300 (320) 63.5 -> 77.9, 4096 x 4096 at 400 (896) 177 -> 194; 8192 x 2048 at 512 (2048) 204 -> 209.
 struct NnCut {
     int mb, nb, slices;
 };
 static NnCut nn_cut(const DenseArgs &a)
 {
     const int64_t wide = (a.batch + 63) / 64, tiles = (static_cast<int64_t>(a.rows) + 15) / 16 * wide;
-    if (a.cols >= 3072 && (static_cast<int64_t>(a.rows) + 31) / 32 * wide >= 256 && a.batch >= 4) return NnCut{2, 4, 1};
-    if (a.cols >= kNnShareCols && a.batch > 32 && a.tickets && tiles >= kNnShareTiles / 4 && tiles < kNnShareTiles) return NnCut{1, 4, tiles < kNnShareTiles / 2 ? 4 : 2};
+    const int64_t pairs = (static_cast<int64_t>(a.rows) + 31) / 32 * wide;
+    if (a.cols >= 2048 && (a.cols >= 2560 || pairs <= 512) && pairs >= 256 && (pairs + 255) / 256 * 2 <= (tiles + 255) / 256 && a.batch >= 4) return NnCut{2, 4, 1};
+    if (a.cols >= (tiles < kNnShareTiles / 2 ? kNnShareFourCols : kNnShareCols) && a.batch > 32 && a.tickets && tiles >= kNnShareTiles / 4 && tiles < kNnShareTiles)
+        return NnCut{1, 4, tiles < kNnShareTiles / 2 ? 4 : 2};
     int nb = dense_nb((static_cast<int64_t>(a.rows) + 15) / 16, a.batch);
     while (nb > a.batch) nb >>= 1;   // (a lane's columns lie within the batch)
     return NnCut{1, nb, 1};
@@ -817,13 +825,16 @@ hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s)
         const dim3 grid(static_cast<unsigned>((mt + 7) / 8 * 8 * ((a.batch + 16 * cut.nb - 1) / (16 * cut.nb)) * cut.slices));
         DenseArgs own = a;
         if (cut.slices == 4) own.tickets += kNnShareTiles;
-        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kNnBlock), 0, s, own, cut.slices); };
-        go(cut.mb == 2 ? dense_nn_kernel<2, 4> : cut.nb == 4 ? dense_nn_kernel<1, 4> : cut.nb == 2 ? dense_nn_kernel<1, 2> : dense_nn_kernel<1, 1>);
+        auto go = [&](auto kernel, int waves = kNnWaves) { hipLaunchKernelGGL(kernel, grid, dim3(waves * kWave), 0, s, own, cut.slices); };
+        if (cut.mb == 1 && cut.nb == 1 && mt * ((a.batch + 15) / 16) <= 256) go(dense_nn_kernel<1, 1, 2 * kNnWaves>, 2 * kNnWaves);
+        else go(cut.mb == 2 ? dense_nn_kernel<2, 4> : cut.nb == 4 ? dense_nn_kernel<1, 4> : cut.nb == 2 ? dense_nn_kernel<1, 2> : dense_nn_kernel<1, 1>);
     } else {
         // One, two or four tiles of 16 columns, us: 2048 x 4096 at batch 256 54.9 / 47.7 / 50.3 (512 and 256 work-groups), at 1024 192 / 161 / 153;
-        // 1024 x 4096 at 512 57.7 / 48.7 / 47.2, 4096 x 4096 at 100 53.8 / 49.6 with two, 1201 x 2201 at 301 33.8 / 29.0.
-        const int64_t across = (static_cast<int64_t>(a.cols) + 63) / 64;
-        const int nb = a.batch >= 4 && across * ((a.batch + 63) / 64) >= 512 ? 4 : a.batch >= 2 && across * ((a.batch + 31) / 32) >= 256 ? 2 : 1;
+        // 1024 x 4096 at 512 57.7 / 48.7 / 47.2, 4096 x 4096 at 100 53.8 / 49.6 with two, 1201 x 2201 at 301 (350) 33.8 / 29.0; a few more than one to a compute unit lose:
+        // 2000 x 6000 at 77 (282) 57.9 / 62.6, 2048 x 4096 at 150 (320) 54.6 / 59.3, 1024 x 3072 at 200 (336, of 224 columns) 32.8 / 34.9, but 1000 x 4000 at 150 (315) 41.6 / 37.8.
+        const int64_t across = (static_cast<int64_t>(a.cols) + 63) / 64, twos = across * ((a.batch + 31) / 32);
+        const bool few_more = twos > 256 && twos <= 340 && (a.rows > 1024 || (a.batch + 31) / 32 * 200 > (a.batch + 15) / 16 * 106);
+        const int nb = a.batch >= 4 && across * ((a.batch + 63) / 64) >= 512 ? 4 : a.batch >= 2 && twos >= 256 && !few_more ? 2 : 1;
         const dim3 grid(static_cast<unsigned>(across), (a.batch + 16 * nb - 1) / (16 * nb)), block(kSplitBlock / nb);
         if (nb == 4) hipLaunchKernelGGL(dense_tn_kernel<4>, grid, block, 0, s, a);
         else if (nb == 2) hipLaunchKernelGGL(dense_tn_kernel<2>, grid, block, 0, s, a);

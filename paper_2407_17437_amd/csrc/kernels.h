@@ -339,7 +339,7 @@ constexpr int32_t kNnShareTiles = 256, kNnShareFloats = 2 * kNnShareTiles * 1024
 // A ticket always counts up to the same number: with one set for tiles in two and in four slices, calls of different batches that overlap
 // would leave it between the two, and calls after them would find it there.
 constexpr int32_t kNnTickets = kNnShareTiles + kNnShareTiles / 2;                   // of tiles in two slices, then in four (nn_cut)
-constexpr int32_t kNnShareCols = 1536;
+constexpr int32_t kNnShareCols = 1536, kNnShareFourCols = 1792;   // length of the sum, for two and for four slices
 // whether some batch of up to max_batch columns has tiles shared (nn_cut)
 inline bool dense_shares_possible(int32_t rows, int32_t cols, int32_t max_batch)
 {

@@ -53,17 +53,17 @@ def test_sampled_gradient(nb, oracle, rows, cols, density, batch, ld):
 @pytest.mark.parametrize("rows,cols,batch,ld", [
     # slices of the sum that are empty, one chunk, whole rounds of chunks and one more; 1, 2 and 4 tiles of 16 columns to a work-group
     (16, 16, 1, None), (17, 33, 5, 5), (48, 80, 16, None), (1041, 129, 33, 33), (1024, 256, 100, None), (1039, 271, 99, 99),
-    (1024, 320, 256, None), (1030, 330, 130, None), (1090, 61, 257, 257),
+    (1024, 320, 256, None), (1030, 330, 130, None), (1090, 61, 257, 257), (4081, 70, 16, None), (4097, 79, 15, 15),   # (256 work-groups of eight waves, 257 of four)
     # tiles of 64 columns shared by two and four work-groups, and tiles of 32 rows
-    (1024, 1536, 65, None), (1041, 1551, 97, 97), (1024, 1536, 33, None), (1009, 1549, 63, 63), (2049, 3073, 200, None),
+    (1024, 1536, 65, None), (1041, 1551, 97, 97), (1024, 1792, 33, None), (1009, 1801, 63, 63), (2049, 3073, 200, None),
     # two and four tiles of columns in the transposed product
-    (67, 2049, 257, 257), (70, 4100, 511, None), (65, 16384, 33, None),
+    (67, 2049, 257, 257), (70, 4100, 511, None), (65, 16384, 33, None), (66, 5500, 100, None), (66, 8192, 64, None),
 ])
 def test_products_of_the_dense_copy(nb, oracle, rows, cols, batch, ld):
     check_layer(nb, oracle, layer_case(rows, cols, 0.6, seed=rows + batch), batch, ld=ld)
 
 
-@pytest.mark.parametrize("rows,cols,batch", [(1041, 1551, 97), (1009, 1549, 63)])
+@pytest.mark.parametrize("rows,cols,batch", [(1041, 1551, 97), (1009, 1801, 63)])
 def test_shared_tiles_of_the_dense_copy_come_out_the_same_again(nb, oracle, rows, cols, batch):
     """... whichever work-group was last, with an infinity in the operand's last row and with its neighbour NaN outside the batch."""
     import torch
@@ -312,7 +312,7 @@ def test_huge_rows_after_products_that_overlapped(nb, oracle):
 def test_shared_tiles_after_products_that_overlapped(nb, oracle):
     """The same of tiles of the dense copy that work-groups share, two at some batches and four at others, all of them in flight at once."""
     import torch
-    rows, cols, batches = 1024, 1551, (100, 64, 97, 33)
+    rows, cols, batches = 1024, 1801, (100, 64, 97, 33)
     lay = layer_case(rows, cols, 0.6, seed=8, relu=False)
     rng = np.random.default_rng(9)
     L = nb.SparseLinear(lay, max_batch=100)
