@@ -632,10 +632,15 @@ def test_infinities_in_the_end_of_step_in_one_launch(nb, torch_mod, batch):
     out = []
     for flags in (nb.NERVA_MLP_DEFAULT, nb.NERVA_MLP_UNFUSED):
         M = nb.MLP(mlp, batch, flags)
+        nb.mlp_profile_enable(M.handle, 1)
         M.train_step(nb.to_dense(Xs[0]), torch.as_tensor(Ts[0]).cuda(), batch, 0.05, 0.9)
         torch.cuda.synchronize()
+        names = [n for n, _ in nb.mlp_profile_read(M.handle)[1]]
+        assert ("backward_chain[1]" in names) == (flags == nb.NERVA_MLP_DEFAULT), names
         out.append([t.cpu().numpy().copy() for l in M.layers for t in (l.values, l.velocity, l.bias)])
         M.close()
+    for values in (out[0][0], out[0][3]):   # (of both layers of the launch: some entries are reached and some are not)
+        assert np.isfinite(values).any() and not np.isfinite(values).all()
     for a, b in zip(*out):
         assert np.array_equal(np.isfinite(a), np.isfinite(b))
         fine = np.isfinite(a)
