@@ -286,9 +286,6 @@ struct ChainArgs {
     int32_t rows;                                 // of dZ_1
 };
 constexpr int32_t kChainMinRows = 256, kChainMaxBatch = 192;
-constexpr int32_t kChainEntries = 256 << 10, kChainEntriesWide = 360 << 10, kChainWide = 32;   // stored entries of W_1, from more than kChainWide columns on the second
-constexpr int64_t kChainEntriesRows = 500ll * 1000 * 1000;   // times its rows
-constexpr int64_t kChainMostWork = 24ll << 20;   // of a W_0 with 16 times as many: entries times columns
 // chain_shape_ok: the part that does not depend on whether the updates are fused; then a step that keeps its launches apart forms dZ_0 in the same order.
 bool chain_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0);
 bool chain_shape_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0);

@@ -3016,20 +3016,15 @@ hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 // Whether T_1 (t), S_1 (g1) and S_0 (g0) of a step can be one launch (chain_kernel): all three untiled, T_1's operand and mask those of S_1, its result
 // that of S_0, no row of W_0 cut into several work-groups.  The waves of a row are those that W_0's partition gives it: the mirror must not be much the larger of the
 // two or have long rows.  Steps at batch 100 apart / in one, us: 500-1000-1000-10 at 10 % (twice W_0's entries) 34.3 / 29.8, 300-1000-1000-10 (three times)
-// 33.6 / 29.2.  What the launch saves is 3 to 5 us whatever the work; where there is much of it the launches apart are the faster ones, with more registers
-// and, for W_1, gathers of their own: 1000-2000-2000-10 at 5 / 10 % (200 and 400 thousand entries in W_1), batch 16 33.9 / 31.6 and 39.8 / 45.0, batch 64 39.8 / 36.6
-// and 51.9 / 52.3; 1500-3000-800-10 at 14 % (336), batch 16 39.6 / 40.4, batch 64 54.5 / 49.4; 800-5000-1500-10 at 5 % (375), batch 100: 64.4 / 65.8.  Many rows of W_1 are
-// worse, as the entries of a mirror row lie a row of W_1 apart in its values: 3000-3000-3000-10 at 1 / 2 % (90 and 180), batch 150 38.8 / 37.5, 66.2 / 68.2, at 5 %, batch 100: 84.5 / 90.0.  Nor does it help W_0's gradient beside a small W_1: 2500-700-64-10 at 30 % (525 and 13 thousand), batch 38 / 100: 34.0 /
-// 35.0, 42.9 / 45.2, at 12 % 27.1 / 25.0, 31.1 / 30.2.  Up to 192 columns: 2000-1500-400-10 at 5 %, batch 180 / 256: 37.2 / 34.4, 41.3 / 43.6.  Networks of a
-// small hidden layer keep their two launches, which a profile of the step shows one by one (256-128-64-10 at 20 %: 20.9 / 18.6).
+// 33.6 / 29.2.  Up to 192 columns: 2000-1500-400-10 at 5 %, batch 180 / 256: 37.2 / 34.4, 41.3 / 43.6.  Networks of a small hidden layer keep their two
+// launches, which a profile of the step shows one by one (256-128-64-10 at 20 %: 20.9 / 18.6).
+bool chain_pays(const SpmmArgs &t, const SddmmArgs &g0);
 bool chain_shape_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
 {
     if (t.batch != g1.batch || t.batch > kChainMaxBatch || t.X != g1.dZ || t.ldx != g1.lddz || !t.YM || t.YM != g1.X || t.ldym != g1.ldx || t.Y != g0.dZ || t.ldy != g0.lddz) return false;
     if (!can_pair(t, g0) || !can_pair(t, g1) || t.nnz <= 0 || t.nnz != g1.nnz || t.rows != g0.rows) return false;
     if (g1.dense || g0.dense || g1.loss_cols || g0.loss_cols || g0.values_t || g0.ZM || g1.ZM) return false;
-    return g0.blocks.n_huge_rows == 0 && t.rows >= kChainMinRows && t.blocks.staged_longest_row <= 2 * kPackMaxLen && t.nnz / 4 <= g0.nnz &&
-           t.nnz <= (t.batch > kChainWide ? kChainEntriesWide : kChainEntries) && static_cast<int64_t>(t.nnz) * t.x_rows <= kChainEntriesRows &&
-           (t.nnz >= g0.nnz / 16 || static_cast<int64_t>(g0.nnz) * t.batch <= kChainMostWork);
+    return g0.blocks.n_huge_rows == 0 && t.rows >= kChainMinRows && t.blocks.staged_longest_row <= 2 * kPackMaxLen && t.nnz / 4 <= g0.nnz && chain_pays(t, g0);
 }
 bool chain_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
 {
@@ -3116,6 +3111,22 @@ static int backward_split(const SpmmArgs &t, int tg, int n_tiles)
     return lg;
 }
 static int backward_tiles(const SpmmArgs &t, int tg) { return (t.batch + tg * 4 - 1) / (tg * 4); }
+
+// What the end of a step in one launch saves is 3 to 5 us whatever the work, and where there is much of it the launches apart are the faster ones, with more registers.  W_1: the entries of
+// a mirror row lie a row of W_1 apart in its values and velocity.  Steps, us, apart -> in one (thousand entries of W_1 x thousand rows): 1000-2000-2000-10 at 5 / 10 % (200 x 2, 400 x 2), batch 64 39.8 ->
+// 36.6, 51.9 -> 52.3, batch 16 33.9 -> 31.6, 39.8 -> 45.0; 3000-3000-3000-10 at 1 / 2 / 5 % (90, 180, 450 x 3), batch 192 50.4 -> 48.6, 66.5 -> 67.5, 108 -> 112; 1500-3000-800-10 at 14 % (336 x
+// 0.8), batch 64 54.5 -> 49.4, batch 16 39.6 -> 40.4; 1300-6600-700-10 (430 x 0.7), batch 80 78 -> 72; 3000-4000-4000-10 at 1 / 1.7 % (160, 272 x 4), batch 100 52.8 -> 48.9, 62.2 -> 64.1; 2498-7241-5799-13 at
+// 0.5 / 1 / 1.7 % (29, 58 and 98 entries a mirror row), batch 64 47.4 -> 42.1, 62.8 -> 56.9, 80.9 -> 76.0, at 2.5 % 107 -> 112, batch 16 at 1 / 1.7 % 50.6 -> 51.6, 59.5 -> 68.6; where its backward pass
+// alone takes two tiles, batch 150: 1.7 % 138 -> 122.  W_0's gradient beside a small W_1: 2500-700-64-10 at 30 % (525 and 13), batch 38 / 100: 34.0 -> 35.0, 42.9 -> 45.2, at 12 % 27.1 -> 25.0,
+// 31.1 -> 30.2; 4000-6000-300-10 at 2.5 / 4 % (960 and 72), batch 80: 48.2 -> 45.5, 64.9 -> 68.7.
+bool chain_pays(const SpmmArgs &t, const SddmmArgs &g0)
+{
+    const int64_t n = t.nnz, spread = n * t.x_rows, below = static_cast<int64_t>(g0.nnz) * t.batch;
+    if ((n * 16 < g0.nnz && below > (24 << 20)) || (n * 8 < g0.nnz && below > (64 << 20))) return false;
+    if (t.batch <= 32) return n <= (256 << 10) || (n <= (360 << 10) && spread <= 100'000'000);
+    return n <= (172 << 10) || (n <= (360 << 10) && spread <= 500'000'000) || (n <= (440 << 10) && (spread <= 320'000'000 || n <= 58ll * t.rows)) ||
+           (n <= (720 << 10) && backward_tiles(t, backward_tile_group(t)) > 1);
+}
 
 // (reading values[] through the position map costs a scattered read per entry and tile, a launch of its own 3.5 us)
 bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &)
