@@ -2640,7 +2640,8 @@ constexpr int64_t kMaxGridIds = (1ll << 31) - 1;
 
 // Grid and order of launches in column tiles (tile_of_block).  Whole tiles leave some XCDs idle in the last round; equal runs do not, but an L2 then sees one tile more and
 // shares two.  From eight tiles on runs pay where whole tiles waste an eighth or more: 8192^2 uniform at 0.6 %, batch 600 / 700 (10 / 11 tiles), forward 70.1 -> 48.7
-// and 71.9 -> 57.8 us; 16384^2 at 1 %, batch 600: 633 -> 406, at batch 850 (14): 702 -> 625, at 900 (15) 707 -> 665; but 4000 x 9000 at 1.2 %, batch 850 / 900: 77.1 -> 84.0, 77.1 -> 87.6, and
+// and 71.9 -> 57.8 us; 16384^2 at 1 %, batch 600: 633 -> 406, at batch 850 (14): 702 -> 625, at 900 (15) 707 -> 665; 1314 x 6656 at 0.6 %, batch 850: 33.7 -> 31.1, 2000 x 8192
+// at 1.2 %: 52.5 -> 47.5; but 4000 x 9000 at 1.2 %, batch 850 / 900: 77.1 -> 84.0, 77.1 -> 87.6, and
 // with rows of different lengths 3000 x 12000 at 0.4 %: 66.9 -> 73.7, 66.5 -> 77.2.
 // Fewer tiles, which all XCDs walk together otherwise: only products whose tile is well within an L2 (8192^2 at 0.6 %, batch 300, 5 tiles: 35.9 -> 31.5), as gradients lose
 // (5000^2 at 2 %, batch 200: 39.5 -> 42.9) and so do tiles that fill one (16384^2 at 1 %, batch 200: 161 -> 168), and where an operand row is gathered so
@@ -2663,7 +2664,7 @@ inline TileOrder tile_order(int n_tiles, int64_t n_blocks, int gs, bool product,
         if (!small || !(rarely || long_rows)) return TileOrder{kTilesOneByOne, 1};
     } else {
         const double waste = (n_tiles + 7) / 8 * 8 / static_cast<double>(n_tiles);
-        const bool runs = waste >= 1.15 || (!skewed && (waste >= 1.13 ? !small || 2 * t.rows >= t.x_rows : waste >= 1.06 && tile_bytes >= (7 << 19) && t.nnz <= 512ll * t.x_rows));
+        const bool runs = waste >= 1.15 || (!skewed && (waste >= 1.13 ? !small || 2 * t.rows >= t.x_rows || t.rows <= 2048 : waste >= 1.06 && tile_bytes >= (7 << 19) && t.nnz <= 512ll * t.x_rows));
         if (!runs) return TileOrder{kTilesWhole, 1};
     }
     TileOrder order{static_cast<int>((n_tiles * n_blocks + 7) / 8), 1};
@@ -2972,22 +2973,42 @@ int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, int32
 {
     const bool skewed = static_cast<int64_t>(longest_row) * rows > 16 * nnz;
     const int w = tile_columns_wanted(x_rows, batch, nnz, rows, skewed, hot_share, masked, for_sddmm);
-    if (w == 0 || (batch + w - 1) / w >= 8) return w;
-    // Fewer tiles than XCDs: every L2 sees every tile, and an eighth of the gathers from it.  The tile then pays where an L2 gathers
-    // a row of it several times and the untiled operand is well beyond the L2; on rows of very different lengths only
-    // for operands beyond all L2s or long rows throughout.  Untiled / in tiles: 9106 x 9383 at 0.3 % (27 entries per operand row), batch
-    // 100 / 182 / 400: forward 11.2 / 17.7 / 40.5 against 16.1 / 18.4 / 39.7 us; at 0.1 %: SDDMM 7.8 / 11.2 / 22.4 against 10.4 / 16.1 / 28.1; power-law
-    // 12000 x 3000 at 0.3 %, batch 256 / 700: forward 12.3 / 32.6 against 22.1 / 45.7, 3000 x 12000 at 1 %, batch 700: 102 against 87.
-    const int64_t operand = static_cast<int64_t>(x_rows) * batch * 4;
-    const bool pays = skewed ? operand >= (32ll << 20) || (operand >= (8ll << 20) && nnz >= 128ll * x_rows) : operand >= (6ll << 20) && nnz >= 24ll * x_rows;
+    const int n_tiles = w > 0 ? (batch + w - 1) / w : 0;
+    if (w == 0 || n_tiles >= 8) return w;
+    // Fewer tiles than XCDs: either every L2 sees every tile, and an eighth of the gathers from it, or it sees few and its share of the work is short (tile_order).
+    // The tiles then pay where an L2 gathers a row of one several times and the untiled operand is well beyond the L2; a product's also on an operand
+    // beyond three L2s whose rows are gathered rarely.  Rows of very different lengths: where enough is gathered from an operand of two L2s; in products rows and columns of 48 entries, and
+    // tiles that fill much of an L2 (narrower ones lose), but no more than one where the last of seven is partly empty.
+    // Untiled / in tiles.  Even rows, 9106 x 9383 at 0.3 % (27 entries per operand row), batch 100 / 182 / 400: forward 11.2 / 17.7 / 40.5 and 16.1 / 18.4 / 39.7 us, at 0.1 %: SDDMM
+    // 7.8 / 11.2 / 22.4 and 10.4 / 16.1 / 28.1, forward at batch 400 18.9 and 14.5; 5000^2 at 0.3 %, batch 300 / 700 / 850: 11.5 / 21.2 / 25.9 and 10.6 / 17.4 / 18.8,
+    // but transposed 6656 x 1314 at 0.3 %, batch 400 (10 MiB): 10.1 and 15.6.  Power-law rows, forward: 9106 x 9383 at 0.6 %, batch 256 / 700: 48.3 / 112 and 38.4 / 94; 3000 x 12000 at 3.5 %, batch 256: 115 and 67, at 1.2 % 46.2 and 45.0;
+    // but 12000 x 3000 at 0.6 %, batch 700: 41.4 and 53.3, 5000^2 at 1.2 %: 52.6 and 61.3; 9106 x 9383 at 1.2 %, batch 850: 209 and 225.  SDDMM: 5000^2 at 2 %, batch 300 / 700: 47.6 / 139 and 44.4 / 79; 8192^2 at 0.6 %,
+    // batch 256 / 850: 39.2 / 161 and 32.4 / 95, at 0.3 %, batch 400: 39.0 and 41.1; 12000 x 3000 at 0.3 %, batch 850: 40.7 and 58.0.
+    const int64_t operand = static_cast<int64_t>(x_rows) * batch * 4, tile = static_cast<int64_t>(x_rows) * 4 * w;
+    bool pays;
+    if (!skewed)
+        pays = operand >= (6ll << 20) && (nnz >= 24ll * x_rows || (operand >= (11ll << 20) && !for_sddmm && hot_share < 0.5f));
+    else if (for_sddmm)
+        pays = operand >= (8ll << 20) && nnz >= 24ll * rows && nnz * batch >= (90ll << 20);
+    else
+        pays = operand >= (8ll << 20) && nnz >= 48ll * x_rows && nnz >= 48ll * rows && tile > (5ll << 19) && (tile <= (4ll << 20) || n_tiles < 7);
+    if (skewed) pays = pays || operand >= (32ll << 20) || (operand >= (8ll << 20) && nnz >= 128ll * x_rows);
     return pays ? w : 0;
+}
+
+// Few tiles of an operand whose rows are gathered rarely are for the product alone, with a gradient they lose: 9000 x 4000 at 0.3 %, batch 400, both
+// gradients 30.2 -> 33.6 us in them; 9106 x 9383 at 0.1 % 28.9 -> 29.8.
+static bool few_rare_tiles(const SpmmArgs &a)
+{
+    const int columns = 4 * spmm_tile_group(a);
+    return columns > 0 && (a.batch + columns - 1) / columns < 8 && a.nnz < 24ll * a.x_rows && static_cast<int64_t>(a.blocks.staged_longest_row) * a.rows <= 16 * a.nnz;
 }
 
 bool can_pair(const SpmmArgs &a, const SddmmArgs &b)
 {
     return !sddmm_sampled_ok(b) && !sddmm_dense_rows_ok(b) && a.batch == b.batch && a.batch > 4 && a.batch <= 1024 && !a.XM && a.rows > 0 && b.rows > 0 &&
            a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && spmm_offsets_ok(a) &&
-           sddmm_offsets_ok(b) && spmm_tile_group(a) == 0 && !spmm_staged_ok(a) && sddmm_tile_columns(b) == 0 &&
+           sddmm_offsets_ok(b) && (spmm_tile_group(a) == 0 || few_rare_tiles(a)) && !spmm_staged_ok(a) && sddmm_tile_columns(b) == 0 &&
            !sddmm_staged_ok(b) && !sddmm_full_ok(b);
 }
 
@@ -3096,7 +3117,7 @@ static bool backward_looped(const SpmmArgs &t)
 static int backward_tile_group(const SpmmArgs &t)
 {
     if (backward_looped(t)) return 64;
-    const int tg = spmm_tile_group(t);
+    const int tg = few_rare_tiles(t) ? 0 : spmm_tile_group(t);
     if (tg == 16 && t.batch > 128 && static_cast<int64_t>(t.x_rows) * 4 * 128 <= (4ll << 20)) return 32;
     if (tg == 0) return t.batch <= 32 ? 8 : t.batch <= 64 ? 16 : t.batch <= 128 || t.batch > 256 || (t.x_rows > 4096 && t.nnz > 16 * static_cast<int64_t>(t.rows)) ? 32 : 64;
     if (tg == 8) return 16;

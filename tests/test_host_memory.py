@@ -245,7 +245,30 @@ def gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit(L):
         L.destroy()
 
 
-CASES = [gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def few_column_tiles_serve_where_they_pay(L):
+    """Rows, columns, entries, longest row, batch; whether the forward product and the gradient alone run in column tiles (fewer than eight)."""
+    for rows, cols, nnz, longest, batch, product, gradient in (
+            (9106, 9383, 85441, 30, 400, True, False),       # even rows, an operand of 14 MiB gathered rarely
+            (9106, 9383, 85441, 30, 256, False, False),      # the same at 9 MiB
+            (9106, 9383, 256323, 60, 256, True, True),       # 27 entries an operand row
+            (8192, 8192, 402653, 2000, 256, True, True),     # rows of very different lengths, 49 entries a row
+            (8192, 8192, 402653, 2000, 128, False, False),
+            (5000, 5000, 300000, 2000, 700, False, True),    # tiles of 2.4 MiB
+            (12000, 3000, 108000, 2000, 850, False, False),  # nine entries a row
+            (9106, 9383, 1024320, 4000, 768, True, True),
+            (9106, 9383, 1024320, 4000, 850, False, True)):  # the seventh tile partly empty, a tile beyond an L2
+        L.counts(0, n_blocks=600, longest_row=longest)
+        L.counts(1, n_blocks=600, longest_row=60)
+        assert L.create(rows, cols, nnz, batch) == 0
+        L.launched()
+        assert L.forward(batch) == 0
+        assert any("spmm_tiled" in k or "spmm_packed" in k for k in L.launched()) == product, (rows, cols, nnz, batch)
+        assert L.backward(batch, dx=False) == 0
+        assert any("sddmm_tiled" in k for k in L.launched()) == gradient, (rows, cols, nnz, batch)
+        L.destroy()
+
+
+CASES = [few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
