@@ -3227,14 +3227,15 @@ hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream
 // room anyway, and in groups of 16 where rows are short.  Uniform rows, us, mixed -> apart: batch 16, 8000 x 1000 at 12 % 3 % faster, 700 x 6000 at 12 % 11.6 -> 12.6, 3000 x 16384 at
 // 12 % 131 -> 150; batch 64, 2048 x 3000 at 10 / 40 % 21.2 -> 18.6, 60.5 -> 53.9, 2048 x 4096 at 10 / 40 % 24.4 -> 23.0, 73.9 -> 79.4, 2048 x 5500 at 10 / 40 % 30.2 -> 30.7, 107 -> 124,
 // 3000 x 8192 at 5 / 40 % 34.8 -> 32.3, 226 -> 258; batch 128, 2048 x 3000 at 10 % 26.3 -> 25.1, 2048 x 3400 28.2 -> 28.6, 2048 x 6500 48.3 -> 50.6, 3000 x 13000 at 2 % 30.5 -> 33.2,
-// 3000 x 16384 at 12 % 208 -> 200; batch 256 not slower up to 25 %.  With the update, which loads more: steps of 3000-3000-3000-10, batch 64, at 15 / 25 % 121 -> 122, 185 -> 197, of
+// 3000 x 16384 at 12 % 208 -> 200,
+// 8192^2 at 0.3 / 0.6 / 2 / 7 % 14.3 -> 13.5, 20.9 -> 19.6, 51 -> 49.3, 151 -> 162, 9106 x 9383 at 0.3 / 0.6 / 2 % 16.7 -> 15.8, 24.4 -> 25.3, 65 -> 71.6; batch 256 not slower up to 25 %.  With the update, which loads more: steps of 3000-3000-3000-10, batch 64, at 15 / 25 % 121 -> 122, 185 -> 197, of
 // 2000-2000-2000-10 at 25 % 97 -> 90.
 static bool backward_gathers_apart(int gs, int64_t waves, const SpmmArgs &t, bool update)
 {
     if (update && gs < 64 && waves > 2048 && t.nnz > 400ll * t.rows) return false;
     if (gs == 8) return waves <= 2048;
     if (gs == 16) return waves <= 3072 || (t.nnz <= 256ll * t.rows && (waves <= 4096 || waves > 6144));
-    return gs == 64 || waves <= 3072 || waves >= 16384;
+    return gs == 64 || waves <= 3072 || waves >= 16384 || t.nnz <= 40ll * t.rows || (waves <= 4608 && t.nnz <= 192ll * t.rows);
 }
 
 hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s)

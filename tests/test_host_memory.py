@@ -233,15 +233,16 @@ def a_single_tile_needs_no_partial_products(L):
 
 
 def gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit(L):
-    for cols, batch, apart in ((17000, 16, False), (17000, 32, False), (17000, 64, False), (17000, 128, False), (17000, 256, True), (16000, 16, True), (16000, 32, True), (16000, 64, True), (6100, 128, True),
-                               (6200, 128, False), (25000, 64, True), (33000, 128, True)):
+    for cols, entries, batch, apart in ((17000, 10200, 16, False), (17000, 10200, 32, False), (17000, 10200, 64, False), (17000, 700000, 128, False), (17000, 10200, 128, True),
+                                        (17000, 10200, 256, True), (16000, 10200, 16, True), (16000, 10200, 32, True), (16000, 10200, 64, True), (6100, 10200, 128, True), (6200, 10200, 128, True),
+                                        (6200, 310000, 128, False), (4600, 200000, 128, True), (25000, 10200, 64, True), (33000, 10200, 128, True)):
         L.counts(0, n_blocks=600, longest_row=300)
         L.counts(1, n_blocks=600, longest_row=10)
-        assert L.create(60, cols, 10200, 256) == 0
+        assert L.create(60, cols, entries, 256) == 0
         L.launched()
         assert L.backward(batch) == 0
         names = [k for k in L.launched() if "backward_fused_kernel" in k]
-        assert len(names) == 1 and ("BackwardPassE1" in names[0]) and ("SpareE%dELb%dEE" % (2 if batch == 16 else 0, apart) in names[0]), (cols, batch, names)
+        assert len(names) == 1 and ("BackwardPassE1" in names[0]) and ("SpareE%dELb%dEE" % (2 if batch == 16 else 0, apart) in names[0]), (cols, entries, batch, names)
         L.destroy()
 
 
