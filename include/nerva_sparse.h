@@ -23,8 +23,7 @@
  *   They are fp32, row-major (features, ld): element (i, c) is at base[i*ld + c], with
  *   ld >= batch.  Columns batch..ld-1 are padding: never written, and their contents
  *   never influence a result.  Any ld and any 4-byte aligned base are taken, by the same sparse
- *   kernels; they are fastest when every row starts on a 128-byte line (ld a multiple of 32), and the
- *   dense products load several columns at a time only from rows on 16-byte boundaries.
+ *   kernels; they are fastest when every row starts on a 128-byte line (ld a multiple of 32).
  * - Biases are dense fp32 vectors of length rows (Section 3: biases are not sparsified).
  * - Every pointer is a DEVICE pointer owned by the caller unless the comment says
  *   "host".  The library owns only what *_create builds and frees it in *_destroy.
@@ -211,15 +210,19 @@ int sparse_linear_rebind(nerva_layer *layer, int32_t nnz, const int32_t *indptr,
 /* Density-adaptive layer ("Discussion and Conclusion" and Appendix C.3: dense computation where a layer is
  * not sparse enough for the sparse kernels to win; Section 5.3 shows masks winning at 50 % sparsity and the
  * sparse kernels from about 80 % on).  A layer on the dense route keeps one zero-filled dense copy of its
- * weights (rows x cols floats, columns padded to a multiple of 64; owned by the layer).  On batches of at least 16 columns its products Y = S X and Y = S^T X run as fp32 MFMA
- * products on that copy, and inside mlp_train_step S = A B^T is formed as a dense product of which only the
- * entries on the pattern are used.  values[] stays the layer's state, in CSR, and the momentum update touches
+ * weights (rows x cols floats, columns padded to a multiple of 64), and behind it up to 2 MiB in which
+ * work-groups that share a part of a product exchange their sums; both are owned by the layer, so that the rule
+ * above for calls on one handle from several streams holds for them too.  On batches of at least 16 columns its
+ * products Y = S X and Y = S^T X run as fp32 MFMA products on that copy, and inside mlp_train_step S = A B^T is
+ * formed as a dense product of which only the entries on the pattern are used.  values[] stays the layer's state,
+ * in CSR, and the momentum update touches
  * the stored entries only: the pattern is as immutable as on the sparse route, and every update the library
  * applies is written to the copy as well.  Results agree with the sparse route to rounding (other summation
  * order); entries off the pattern contribute 0 * x, so an operand that holds Inf/NaN spreads differently.
  * sparse_linear_create and sparse_linear_rebind take the route by themselves for a pattern of at least 40 %
  * density with at least 64 rows and 64 columns (the 3072-1024-512-10 network at batch 100: a step takes
- * 59 us on the dense route and 79 on the sparse one at 50 % sparsity, 54 and 57 at 80 %); this call switches any layer over by hand.  A route once taken is kept across sparse_linear_rebind.
+ * 53 us on the dense route and 79 on the sparse one at 50 % sparsity, 48 and 57 at 80 %); this call switches
+ * any layer over by hand.  A route once taken is kept across sparse_linear_rebind.
  * Errors: NERVA_ERR_SHAPE (rows x cols beyond 2^31), NERVA_ERR_HIP. */
 int sparse_linear_enable_dense(nerva_layer *layer, void *stream);
 

@@ -312,8 +312,8 @@ hipError_t launch_copy(float *dst, const float *src, int64_t n, hipStream_t s);
 // entries is sampled from tiles of G = dZ X^T (SampledLayer below), which is never stored.
 constexpr int32_t kDenseLdAlign = 64;
 constexpr float kTableFromDensity = 0.15f;  // layers at least this dense get a pattern table when they are bound
-// Layers at least this dense take the dense route by themselves.  Steps of 3072-1024-512-10 at batch 100, dense / sparse route: 53.7 / 79.3 us at
-// 50 % density, 51.9 / 81.0 at 40 %, 48.5 / 57.0 at 20 %; 2048-4096-2048-10 at batch 64 127 / 314, 121 / 264, 105 / 149, at 1024 857 / 843, 847 / 770, 833 / 654:
+// Layers at least this dense take the dense route by themselves.  Steps of 3072-1024-512-10 at batch 100, dense / sparse route: 53.2 / 78.6 us at
+// 50 % density, 51.2 / 80.6 at 40 %, 48.4 / 56.5 at 20 %; 2048-4096-2048-10 at batch 64 127 / 268, 121 / 229, 105 / 138, at 1024 854 / 856, 844 / 785, 830 / 683:
 // below the line the dense route would be the faster one for narrow batches too, but an infinity in an operand reaches every row on it.
 constexpr float kDenseFromDensity = 0.4f;
 struct DenseArgs {
@@ -520,7 +520,7 @@ __host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols
     const int64_t bound = want + (rows + 96 * want) / kStageRangeFill + 2;
     return bound * ((cols + kStageRows - 1) / kStageRows + 1) * kStageRangeRows > (1ll << 28) ? 0 : static_cast<int32_t>(bound);
 }
-// Whether the listed rows are worth a route of their own at max_batch columns (calls ask again: dense_rows_product_ok).  Start -> with it, forward product: power-law 4096^2 at 5 % (297 rows,
+// Whether the listed rows are worth a route of their own at max_batch columns (calls ask again: dense_rows_product_ok).  Without -> with it on the fp32 units, forward product: power-law 4096^2 at 5 % (297 rows,
 // 0.53 M entries) at batch 256 / 512 / 1024: 48 -> 50, 81 -> 77, 129 -> 120 us; 8192 x 1024 at 10 %: 35 -> 36, 87 -> 51, 109 -> 82.
 // Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even with the fp32 units at 30 % (324 us; 20 %: 235 -> 326).
 __host__ __device__ inline bool dense_rows_pay(int32_t n_dense, int64_t dense_nnz, int64_t nnz, int32_t cols, int32_t max_batch)

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kSplitCols) void split_operand_kernel(const float *
 // steps between its products; its own columns of the operand come straight from the parts, a chunk ahead.  K is cut into slices
 // where the tiles do not fill the chip.
 // What bounds it: the card's power at these units (from registers they reach 1.73 PFLOP/s at 1.8 GHz), and the waits at either end of a chunk.
-// Measured on the 2611 dense rows of 16384^2 power-law rows at 10 %, batch 1024: 510 us (1.4 PFLOP/s) after 32 for
+// Measured on the 2611 dense rows of 16384^2 power-law rows at 10 %, batch 1024: 490 to 510 us (1.4 PFLOP/s) after 32 for
 // the parts and before 10 for the slices; dense_rows_kernel 813 + 9.
 // Tried, with six of the products, which took 433: the operand split by the work-groups themselves (526), through LDS (480), one of a SIMD's two waves
 // bringing entries while the other multiplies (450); without bringing entries and operand the same loop took 324.
