@@ -793,9 +793,15 @@ __global__ __launch_bounds__(kBlock) void full_rows_finish_softmax_kernel(const 
 // and row.  The work-group walks the column blocks of the matrix in order: it copies the
 // block's kStageRows operand rows (128 KiB) into LDS, then every lane row serves, out of that
 // copy, the segment (row, block) of each of its rows.  A segment's (column, weight) pairs are
-// loaded one per lane, a block ahead, and reach the other lanes of the row through DPP row
-// broadcasts, so the only LDS traffic is the gather itself.  Bias, ReLU and the output mask are
-// applied when the rows are stored, once, after the last block.  A row marked kStageQuad is
+// loaded one per lane, two segments ahead, and reach the other lanes of the row through DPP row
+// broadcasts, so the only LDS traffic is the gather itself.  The next block's operand rows travel to registers
+// while a block is served.  Bias, ReLU and the output mask are
+// applied when the rows are stored, once, after the last block.
+// What bounds it: the latency of short runs of LDS gathers at four waves a SIMD (vector ALUs 65 % busy, LDS 45 %; a loop of nothing but whole chunks runs
+// 1.5 times as fast), not either pipe.  Segments, masks and offsets worked out once per block and not per use, the rows brought ahead, no wait for memory among
+// the gathers, the weight's move in the multiply-add: 16384^2 power-law rows at 10 %, batch 1024, 1087 -> 740 us (10.3 -> 6.5 vector instructions a gather);
+// forward products of uniform 8192^2 at 5 %, batch 1024, 374 -> 278, 16384^2 at 2 %, batch 512, 448 -> 334, 5000 x 7000 at 8 %, batch 511, 146 -> 115.
+// Slots dealt to the waves there and back change nothing, two runs of 8 gathers made one of 16 neither.  A row marked kStageQuad is
 // shared by the four lane rows of a wave, a quarter of each segment each, and their four results
 // are added in a fixed order before the store.  Every output element is summed in one order.
 // With a partial plan (RowBlocks::staged_partial) the kernel serves the long rows only and a
@@ -805,7 +811,7 @@ constexpr int kStageWaves = kWavesPerBlock;
 // gathers from, so that it multiplies its weight 0 with 0 and not with an operand row that the
 // output row does not reference (which may hold Inf or NaN).
 constexpr int kStageZeroRow = kStageRows * kStageCols * 4;
-constexpr int kStageRounds = 2;  // rounds in which a block is copied into LDS (8 / kStageRounds float4 per thread and round)
+constexpr int kStageRounds = 2;  // rounds in which the SDDMM copies a block into LDS (8 / kStageRounds float4 per thread and round)
 static_assert(kStageRangeRows == kStageWaves * 4 * kStageJ && kStageJ <= 16, "a lane row owns kStageJ rows of the range");
 
 template <int... I, typename F>
@@ -817,105 +823,58 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &
 // lane i of every row of 16 lanes receives the value of the row's lane I
 template <int I>
 __device__ __forceinline__ int row_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x150 + I, 0xF, 0xF, true); }
-// lane i of every row of 16 lanes receives the value of the row's lane (i + K) % 16
-template <int K>
-__device__ __forceinline__ int row_rotate_down(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x120 + (16 - K), 0xF, 0xF, true); }
-
-template <int I>
-__device__ __forceinline__ void staged_step(const char *lds, int off, float w, float4 &acc)
+// acc += w of the row's lane I times x, the move of w in the multiply-add itself (the compiler makes it an instruction of its own, one in six of
+// a step).  FIRST: w may have been written by the instruction before, and such an operand is only there two cycles later.
+template <int I, bool FIRST>
+__device__ __forceinline__ void fma_row_lane(float4 &acc, float w, const float4 &x)
 {
-    const int o = row_lane<I>(off);
-    const float wi = __builtin_bit_cast(float, row_lane<I>(__builtin_bit_cast(int, w)));
-    const float4 x = *reinterpret_cast<const float4 *>(lds + o);
-    acc.x = fmaf(wi, x.x, acc.x);
-    acc.y = fmaf(wi, x.y, acc.y);
-    acc.z = fmaf(wi, x.z, acc.z);
-    acc.w = fmaf(wi, x.w, acc.w);
+    if constexpr (FIRST)
+        asm("s_nop 1\n\t"
+            "v_fmac_f32_dpp %0, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %2, %4, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %3, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+            : "+&v"(acc.x), "+&v"(acc.y), "+&v"(acc.z), "+&v"(acc.w)
+            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(I));
+    else
+        asm("v_fmac_f32_dpp %0, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %2, %4, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %3, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+            : "+&v"(acc.x), "+&v"(acc.y), "+&v"(acc.z), "+&v"(acc.w)
+            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(I));
 }
-// the first N entries of every lane row, in entry order; afterwards entry N sits in lane 0
-template <int N>
-__device__ __forceinline__ void staged_pass(const char *lds, int &off, float &w, float4 &acc)
+// Entries B .. B + N - 1 of every lane row, in that order, out of the 16 that its lanes hold as (LDS byte offset, weight): four gathers
+// ahead of the one whose products are added.
+template <int B, int N>
+__device__ __forceinline__ void staged_steps(const char *lds, int off, float w, float4 &acc)
 {
-    staged_step<0>(lds, off, w, acc);
-    if constexpr (N > 1) staged_step<1>(lds, off, w, acc);
-    if constexpr (N > 2) { staged_step<2>(lds, off, w, acc); staged_step<3>(lds, off, w, acc); }
-    if constexpr (N > 4) {
-        staged_step<4>(lds, off, w, acc); staged_step<5>(lds, off, w, acc);
-        staged_step<6>(lds, off, w, acc); staged_step<7>(lds, off, w, acc);
-    }
-    if constexpr (N > 8) {
-        staged_step<8>(lds, off, w, acc); staged_step<9>(lds, off, w, acc);
-        staged_step<10>(lds, off, w, acc); staged_step<11>(lds, off, w, acc);
-        staged_step<12>(lds, off, w, acc); staged_step<13>(lds, off, w, acc);
-        staged_step<14>(lds, off, w, acc); staged_step<15>(lds, off, w, acc);
-    }
-    if constexpr (N < 16) {
-        off = row_rotate_down<N>(off);
-        w = __builtin_bit_cast(float, row_rotate_down<N>(__builtin_bit_cast(int, w)));
-    }
+    constexpr int kAhead = N < 4 ? N : 4;
+    float4 x[N];
+    auto gather = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        x[i] = *reinterpret_cast<const float4 *>(lds + row_lane<B + i>(off));
+    };
+    static_for(std::make_integer_sequence<int, kAhead>{}, gather);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (i + kAhead < N) gather(std::integral_constant<int, i + kAhead>{});
+        fma_row_lane<B + i, i == 0>(acc, w, x[i]);  // (in this order: each adds to acc)
+        if constexpr (i + kAhead < N) __builtin_amdgcn_sched_barrier(0);
+    });
 }
-
-// One segment per lane row: entries [p0, p0 + len) of one of the lane row's rows, the first 16
-// of them already in (off, w) as LDS byte offset and weight; adds the products to acc.
-__device__ __forceinline__ void staged_segment(const SpmmArgs &a, const char *lds, int cb0, int lig, int p0, int len,
-                                               int off, float w, float4 &acc)
+// the first n entries (n > 0) of lanes B .. B + 7, and one more at most.  (One if after the other: with else the sums of one way are kept
+// while the other is gone, and are copied back and forth.)
+template <int B>
+__device__ __forceinline__ void staged_half(const char *lds, int n, int off, float w, float4 &acc)
 {
-    // the longest of the four segments sets the number of steps; shorter ones ride along with weight 0
-    const int l01 = max(__builtin_amdgcn_readlane(len, 0), __builtin_amdgcn_readlane(len, 16));
-    const int l23 = max(__builtin_amdgcn_readlane(len, 32), __builtin_amdgcn_readlane(len, 48));
-    const int longest = max(l01, l23);
-    auto passes = [&](int n) {
-        if (n >= 16) {
-            staged_pass<16>(lds, off, w, acc);
-        } else {
-            if (n & 8) staged_pass<8>(lds, off, w, acc);
-            if (n & 4) staged_pass<4>(lds, off, w, acc);
-            if (n & 2) staged_pass<2>(lds, off, w, acc);
-            if (n & 1) staged_pass<1>(lds, off, w, acc);
-        }
-    };
-    if (longest <= 16) {
-        // no load in this path, hence no wait: whatever the kernel has in flight stays in flight
-        passes(longest);
-        return;
-    }
-    // long segments: kStageDepth chunks of 16 entries are served while the next kStageDepth travel
-    constexpr int kStageDepth = 2;
-    int o[kStageDepth], o2[kStageDepth];
-    float ww[kStageDepth], w2[kStageDepth];
-    auto load_chunk = [&](int first, int &oo, float &wo) {
-        oo = kStageZeroRow;
-        wo = 0.f;
-        if (first < longest) {  // uniform
-            const int e = first + lig;
-            if (e < len) {
-                oo = (a.indices[p0 + e] - cb0) * (kStageCols * 4);
-                wo = a.values[p0 + e];
-            }
-        }
-    };
-    o[0] = off;
-    ww[0] = w;
-#pragma unroll
-    for (int k = 1; k < kStageDepth; ++k) load_chunk(16 * k, o[k], ww[k]);
-    for (int c = 0; c < longest; c += 16 * kStageDepth) {
-#pragma unroll
-        for (int k = 0; k < kStageDepth; ++k) load_chunk(c + 16 * (kStageDepth + k), o2[k], w2[k]);
-#pragma unroll
-        for (int k = 0; k < kStageDepth; ++k) {
-            const int n = longest - c - 16 * k;
-            if (n > 0) {
-                off = o[k];
-                w = ww[k];
-                passes(n);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kStageDepth; ++k) {
-            o[k] = o2[k];
-            ww[k] = w2[k];
-        }
-    }
+    int ways = n > 6 ? 1 : n > 4 ? 6 : n > 2 ? 2 : 8;
+    asm("" : "+s"(ways));
+    if (ways & 1) staged_steps<B, 8>(lds, off, w, acc);
+    if (ways & 2) staged_steps<B, 4>(lds, off, w, acc);
+    if (ways & 4) staged_steps<B + 4, 2>(lds, off, w, acc);
+    if (ways & 8) staged_steps<B, 2>(lds, off, w, acc);
 }
 
 // Work-group barrier that orders LDS accesses only: global loads issued before it stay in flight
@@ -960,87 +919,128 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     if (threadIdx.x < kStageCols / 4) stage[kStageRows * kStageCols / 4 + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);  // (visible after the first barrier)
     const int n_cb = a.blocks.staged_cblocks;
     // The lane row's J-th row sits in slot (J * 16 + wave) * 4 + lrow of the range; lane J of the
-    // lane row keeps that slot's row id and, block after block, its segment bounds.
+    // lane row keeps that slot's row id and, block after block, its segment.
     const int my_slot = ((lig & (kStageJ - 1)) * kStageWaves + wv) * 4 + lrow;
     const int my_row = a.blocks.staged_rows[range * kStageRangeRows + my_slot];
+    const bool my_quad = my_row >= 0 && (my_row & kStageQuad);
     const int n_j = a.blocks.staged_groups[range];  // rows of the range / 64, rounded up
     const int32_t *ends = a.blocks.staged_ends + static_cast<int64_t>(range) * (n_cb + 1) * kStageRangeRows + my_slot;
     constexpr auto all_j = std::make_integer_sequence<int, kStageJ>{};
     float4 acc[kStageJ];
     static_for(all_j, [&](auto jc) { acc[decltype(jc)::value] = make_float4(0.f, 0.f, 0.f, 0.f); });
-    // first 16 entries of the segments of column block blk; e_lo, e_hi: the lane's bounds blk and blk + 1
-    // the lane row's J-th segment in a block whose bounds lane J holds in e_lo, e_hi: the slot's
-    // entries, or this lane row's quarter of them where the four lane rows share a long row
-    auto segment = [&](auto jc, int e_lo, int e_hi, int &p0, int &len) {
-        constexpr int j = decltype(jc)::value;
-        p0 = row_lane<j>(e_lo);
-        len = row_lane<j>(e_hi) - p0;
-        if (row_lane<j>(my_row) & kStageQuad) {
+    // The slot's entries [e_lo, e_hi) of a block, or this lane row's quarter of them where the four lane rows share a long row; the
+    // longest of the four segments that a wave serves side by side sets the number of steps, shorter ones ride along with weight 0.
+    struct Segments {
+        uint32_t at;     // bytes to its first entry
+        int left, most;  // 4 times its length; the longest of the four
+    };
+    auto segments = [&](int e_lo, int e_hi) {
+        int p0 = e_lo, len = e_hi - e_lo;
+        if (my_quad) {
             const int from = (len * lrow) >> 2;
             p0 += from;
             len = ((len * (lrow + 1)) >> 2) - from;
         }
+        int most = max(len, __shfl_xor(len, 16));
+        most = max(most, __shfl_xor(most, 32));
+        return Segments{static_cast<uint32_t>(p0) * 4u, len * 4, most};
     };
-    auto first_chunks = [&](int blk, int e_lo, int e_hi, int (&off)[kStageJ], float (&w)[kStageJ]) {
-        static_for(all_j, [&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            off[j] = kStageZeroRow;
-            w[j] = 0.f;
-            if (j < n_j) {
-                int p0, len;
-                segment(jc, e_lo, e_hi, p0, len);
-                if (lig < len) {
-                    off[j] = (a.indices[p0 + lig] - blk * kStageRows) * (kStageCols * 4);
-                    w[j] = a.values[p0 + lig];
-                }
-            }
-        });
+    // 16 entries of a segment, one per lane, as they are stored.  at: byte offset of the lane's one in the first chunk; left: 4 times the entries
+    // from there to the segment's end; lanes past it read near entry 0
+    struct Chunk {
+        int index;
+        float w;
     };
-    int e0 = ends[0], e1 = ends[kStageRangeRows];
+    const int lig4 = lig * 4;
+    auto load_chunk = [&](uint32_t at, int left, int first) {
+        const uint32_t o = left > first * 4 ? at : 0u;
+        return Chunk{__builtin_bit_cast(int, gload1(as_gmem(a.indices), o + static_cast<uint32_t>(first * 4))), gload1(as_gmem(a.values), o + static_cast<uint32_t>(first * 4))};
+    };
+    // the same as LDS byte offset and weight
+    auto placed = [&](const Chunk &c, bool on, int base, int &off, float &w) {
+        off = on ? (c.index << 8) - base : kStageZeroRow;
+        w = on ? c.w : 0.f;
+    };
+    static_assert(kStageCols * 4 == 1 << 8, "");
+    // The first two chunks of every slot are asked for kAheadJ slots before they are used, across the end of a block too.
+    constexpr int kAheadJ = 2, kHeld = 4;
+    static_assert(kStageJ % kHeld == 0 && kAheadJ < kHeld, "");
+    Chunk held[kHeld][2];
+    auto ask = [&](auto jc, const Segments &s) {
+        constexpr int j = decltype(jc)::value;
+        const uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(s.at)) + lig4);
+        const int left = row_lane<j>(s.left) - lig4;
+        held[j % kHeld][0] = load_chunk(at, left, 0);
+        held[j % kHeld][1] = load_chunk(at, left, 16);
+    };
+    // A block's operand rows on their way to LDS: thread t holds four columns of rows t / 16, t / 16 + 64, ... of it.  The last block starts
+    // early enough to be whole, and of fewer rows than a block's some are brought twice.
+    constexpr int kShare = kStageRows / 64;
+    static_assert(kShare % 2 == 0 && kShare / 2 <= kStageJ, "two of them are asked for beside each slot");
+    float4 v[kShare];
+    const float *const my_x = a.X + static_cast<int64_t>(threadIdx.x >> 4) * a.ldx + col;
+    const int last_block = max(a.x_rows - kStageRows, 0), last_rows = a.x_rows - 64;
+    auto block_row = [&](int b) { return min(b * kStageRows, last_block); };
+    auto ask_rows = [&](int i, int cb0) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + i * 64, last_rows)) * a.ldx); };
+    auto put_rows = [&](int cb0) {
+#pragma unroll
+        for (int i = 0; i < kShare; ++i) {
+            const int k = min(cb0 + i * 64, last_rows);
+            if constexpr (XMASK) v[i] = keep_where_positive(v[i], ld4(a.XM + static_cast<int64_t>(k + static_cast<int>(threadIdx.x >> 4)) * a.ldxm + col));
+            stage[(k - cb0) * 16 + static_cast<int>(threadIdx.x)] = v[i];
+        }
+    };
+    int e1 = ends[kStageRangeRows];
+    Segments now = segments(ends[0], e1);
     int e2 = n_cb >= 2 ? ends[2 * kStageRangeRows] : e1;
-    int off_cur[kStageJ];
-    float w_cur[kStageJ];
-    first_chunks(0, e0, e1, off_cur, w_cur);
+    static_for(std::make_integer_sequence<int, kAheadJ>{}, [&](auto jc) { ask(jc, now); });
+#pragma unroll
+    for (int i = 0; i < kShare; ++i) ask_rows(i, 0);
     for (int b = 0; b < n_cb; ++b) {
-        const int cb0 = b * kStageRows;
+        const int cb0 = block_row(b), cb_next = block_row(b + 1);
+        const int e3 = ends[min(b + 3, n_cb) * kStageRangeRows];
+        const Segments next = segments(e1, e2);  // (empty behind the last block)
         lds_barrier();  // the previous block's gathers are done
-#pragma unroll
-        for (int h = 0; h < kStageRounds; ++h) {
-            constexpr int kHalf = kStageRows / (64 * kStageRounds);
-            float4 v[kHalf];
-#pragma unroll
-            for (int i = 0; i < kHalf; ++i) {
-                const int k = cb0 + (h * kHalf + i) * 64 + static_cast<int>(threadIdx.x >> 4);
-                v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < a.x_rows && col_on) {
-                    v[i] = ld4(a.X + static_cast<int64_t>(k) * a.ldx + col);
-                    if constexpr (XMASK) v[i] = keep_where_positive(v[i], ld4(a.XM + static_cast<int64_t>(k) * a.ldxm + col));
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < kHalf; ++i) stage[((h * kHalf + i) * 64 + (threadIdx.x >> 4)) * 16 + lig] = v[i];
-        }
-        // the next block's first chunks travel while this block is served
-        int off_next[kStageJ];
-        float w_next[kStageJ];
-        int e3 = e2;
-        if (b + 1 < n_cb) {
-            first_chunks(b + 1, e1, e2, off_next, w_next);
-            if (b + 3 <= n_cb) e3 = ends[(b + 3) * kStageRangeRows];
-        } else {
-            static_for(all_j, [&](auto jc) { off_next[decltype(jc)::value] = kStageZeroRow; w_next[decltype(jc)::value] = 0.f; });
-        }
+        put_rows(cb0);
         lds_barrier();
+        const int base = cb0 << 8;
         static_for(all_j, [&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            if (j < n_j) {
-                int p0, len;
-                segment(jc, e0, e1, p0, len);
-                staged_segment(a, lds, cb0, lig, p0, len, off_cur[j], w_cur[j], acc[j]);
+            if constexpr (j < kShare / 2) {   // (early: their way is long, and a range of few rows has no last slots)
+                ask_rows(2 * j, cb_next);
+                ask_rows(2 * j + 1, cb_next);
+            }
+            if constexpr (j + kAheadJ < kStageJ) ask(std::integral_constant<int, j + kAheadJ>{}, now);
+            else ask(std::integral_constant<int, j + kAheadJ - kStageJ>{}, next);
+            __builtin_amdgcn_sched_barrier(0);
+            const int most = __builtin_amdgcn_readlane(now.most, j);
+            if (most > 0) {
+                uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(now.at)) + lig4);
+                int left = row_lane<j>(now.left) - lig4;
+                int off, off1;
+                float w, w1;
+                placed(held[j % kHeld][0], left > 0, base, off, w);
+                placed(held[j % kHeld][1], left > 64, base, off1, w1);
+                int n = most;
+                // (a loop of its own, so that whatever it asks for has come at its end, and the loop after it waits for no memory)
+                for (; n > 32; n -= 16, at += 64, left -= 64) {
+                    const Chunk c2 = load_chunk(at, left, 32);
+                    staged_steps<0, 16>(lds, off, w, acc[j]);
+                    off = off1;
+                    w = w1;
+                    placed(c2, left > 128, base, off1, w1);
+                }
+                for (;;) {
+                    staged_half<0>(lds, n, off, w, acc[j]);
+                    if (n > 8) staged_half<8>(lds, n - 8, off, w, acc[j]);
+                    n -= 16;
+                    if (n <= 0) break;
+                    off = off1;
+                    w = w1;
+                }
             }
         });
-        static_for(all_j, [&](auto jc) { off_cur[decltype(jc)::value] = off_next[decltype(jc)::value]; w_cur[decltype(jc)::value] = w_next[decltype(jc)::value]; });
-        e0 = e1;
+        now = next;
         e1 = e2;
         e2 = e3;
     }
@@ -2817,6 +2817,7 @@ int spmm_split_group(const SpmmArgs &a)
 
 bool spmm_staged_ok(const SpmmArgs &a)
 {
+    if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (it brings 64 operand rows at a time, and reads entries at 32-bit byte offsets, 32 past the first)
     if (!staged_pays(a.blocks, a.x_rows, a.batch, kStageLongSegment)) return false;
     return !a.blocks.staged_partial || a.blocks.n_rest_blocks > 0;  // (the rows the plan leaves out need a partition of their own)
 }

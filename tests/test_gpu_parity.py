@@ -460,6 +460,38 @@ def test_staged_kernels_on_awkward_shapes(nb, torch_mod, oracle, rows, cols, len
     L.close()
 
 
+@pytest.mark.parametrize("batch", [128, 190])
+def test_staged_segments_of_every_length(nb, torch_mod, oracle, batch):
+    """Segments of 0 to 83 entries in the first column block (whole chunks of 16, every remainder, one to three chunks beyond the two
+    that are fetched ahead) and of 0 to 88 in the last, which starts before its first column so that it is whole; an operand row
+    that only every fifth row references holds infinities."""
+    torch = torch_mod
+    rows, cols = 336, 600
+    rng = np.random.default_rng(batch)
+    per_row = [np.sort(np.concatenate([rng.choice(np.arange(1, 512), i % 84, replace=False), 512 + rng.choice(88, (i * 37) % 89, replace=False),
+                                       np.zeros(1 if i % 5 == 0 else 0, dtype=np.int64)])) for i in range(rows)]
+    indices = np.concatenate(per_row).astype(np.int32)
+    indptr = np.concatenate([[0], np.cumsum([len(r) for r in per_row])]).astype(np.int32)
+    lay = wl.SparseLayerData(rows, cols, indptr, indices, rng.standard_normal(len(indices)).astype(np.float32),
+                             (rng.standard_normal(rows) * 0.5).astype(np.float32), False)
+    X = rng.standard_normal((cols, batch)).astype(np.float32)
+    nb.nerva_set_partition_mode(nb.NERVA_PARTITION_PREFER_STAGED)
+    try:
+        L = nb.SparseLinear(lay, max_batch=batch)
+    finally:
+        nb.nerva_set_partition_mode(nb.NERVA_PARTITION_BALANCED)
+    Xd = nb.to_dense(X); Yd = nb.dense(rows, batch)
+    nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+    Y, S = oracle.spmm(rows, cols, indptr, indices, lay.values, lay.bias, X, False)
+    close(Yd.cpu().numpy(), Y, S, what="Y")
+    Xd[0] = float("inf")
+    nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+    finite = torch.isfinite(Yd).cpu().numpy()
+    assert np.array_equal(finite.all(axis=1), np.arange(rows) % 5 != 0) and not finite[::5].any()
+    close(Yd.cpu().numpy()[np.arange(rows) % 5 != 0], Y[np.arange(rows) % 5 != 0], S[np.arange(rows) % 5 != 0], what="Y beside infinities")
+    L.close()
+
+
 def test_power_law_rows_staged_and_ordinary_kernels_together(nb, torch_mod, oracle):
     """The same split on an operand small enough to stay untiled (600 rows x 1024 columns): without column tiles the
     packed path does not run, so the short rows of the forward product go through the wide kernel on a partition of
