@@ -811,7 +811,6 @@ constexpr int kStageWaves = kWavesPerBlock;
 // gathers from, so that it multiplies its weight 0 with 0 and not with an operand row that the
 // output row does not reference (which may hold Inf or NaN).
 constexpr int kStageZeroRow = kStageRows * kStageCols * 4;
-constexpr int kStageRounds = 2;  // rounds in which the SDDMM copies a block into LDS (8 / kStageRounds float4 per thread and round)
 static_assert(kStageRangeRows == kStageWaves * 4 * kStageJ && kStageJ <= 16, "a lane row owns kStageJ rows of the range");
 
 template <int... I, typename F>
@@ -903,6 +902,25 @@ __device__ __forceinline__ void staged_ids(int n_ranges, int n_tiles, int &range
     }
 }
 
+// A slot's entries [e_lo, e_hi) of a block, or this lane row's quarter of them where the four lane rows share a long row; the
+// longest of the four segments that a wave serves side by side sets the number of steps, shorter ones ride along with weight 0.
+struct StagedSegments {
+    uint32_t at;     // bytes to its first entry
+    int left, most;  // 4 times its length; the longest of the four
+};
+__device__ __forceinline__ StagedSegments staged_segments(int e_lo, int e_hi, bool quad, int lrow)
+{
+    int p0 = e_lo, len = e_hi - e_lo;
+    if (quad) {
+        const int from = (len * lrow) >> 2;
+        p0 += from;
+        len = ((len * (lrow + 1)) >> 2) - from;
+    }
+    int most = max(len, __shfl_xor(len, 16));
+    most = max(most, __shfl_xor(most, 32));
+    return StagedSegments{static_cast<uint32_t>(p0) * 4u, len * 4, most};
+}
+
 template <bool XMASK>
 __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const SpmmArgs a, const int n_tiles)
 {
@@ -928,23 +946,6 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     constexpr auto all_j = std::make_integer_sequence<int, kStageJ>{};
     float4 acc[kStageJ];
     static_for(all_j, [&](auto jc) { acc[decltype(jc)::value] = make_float4(0.f, 0.f, 0.f, 0.f); });
-    // The slot's entries [e_lo, e_hi) of a block, or this lane row's quarter of them where the four lane rows share a long row; the
-    // longest of the four segments that a wave serves side by side sets the number of steps, shorter ones ride along with weight 0.
-    struct Segments {
-        uint32_t at;     // bytes to its first entry
-        int left, most;  // 4 times its length; the longest of the four
-    };
-    auto segments = [&](int e_lo, int e_hi) {
-        int p0 = e_lo, len = e_hi - e_lo;
-        if (my_quad) {
-            const int from = (len * lrow) >> 2;
-            p0 += from;
-            len = ((len * (lrow + 1)) >> 2) - from;
-        }
-        int most = max(len, __shfl_xor(len, 16));
-        most = max(most, __shfl_xor(most, 32));
-        return Segments{static_cast<uint32_t>(p0) * 4u, len * 4, most};
-    };
     // 16 entries of a segment, one per lane, as they are stored.  at: byte offset of the lane's one in the first chunk; left: 4 times the entries
     // from there to the segment's end; lanes past it read near entry 0
     struct Chunk {
@@ -966,7 +967,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     constexpr int kAheadJ = 2, kHeld = 4;
     static_assert(kStageJ % kHeld == 0 && kAheadJ < kHeld, "");
     Chunk held[kHeld][2];
-    auto ask = [&](auto jc, const Segments &s) {
+    auto ask = [&](auto jc, const StagedSegments &s) {
         constexpr int j = decltype(jc)::value;
         const uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(s.at)) + lig4);
         const int left = row_lane<j>(s.left) - lig4;
@@ -991,7 +992,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
         }
     };
     int e1 = ends[kStageRangeRows];
-    Segments now = segments(ends[0], e1);
+    StagedSegments now = staged_segments(ends[0], e1, my_quad, lrow);
     int e2 = n_cb >= 2 ? ends[2 * kStageRangeRows] : e1;
     static_for(std::make_integer_sequence<int, kAheadJ>{}, [&](auto jc) { ask(jc, now); });
 #pragma unroll
@@ -999,7 +1000,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     for (int b = 0; b < n_cb; ++b) {
         const int cb0 = block_row(b), cb_next = block_row(b + 1);
         const int e3 = ends[min(b + 3, n_cb) * kStageRangeRows];
-        const Segments next = segments(e1, e2);  // (empty behind the last block)
+        const StagedSegments next = staged_segments(e1, e2, my_quad, lrow);  // (empty behind the last block)
         lds_barrier();  // the previous block's gathers are done
         put_rows(cb0);
         lds_barrier();
@@ -1284,97 +1285,84 @@ __global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, 
 // The SDDMM on the staged product's plan: same ranges, tiles, column blocks and LDS copy of the
 // operand; a lane row keeps the tile's 64 columns of dZ of its 8 rows in registers instead of
 // results.  An entry's product is a dot product over the lane row: each lane multiplies its four
-// columns, and 16 entries at a time are summed across the 16 lanes by a transposing butterfly
-// (45 instructions per 16 entries instead of 6 per entry), after which lane i holds entry i's sum
+// columns, and up to 16 entries at a time are summed across the 16 lanes by a transposing butterfly
+// (33 instructions per 16 entries instead of 6 per entry), after which lane i holds entry i's sum
 // and the lane row stores 16 consecutive partial products.  Partial products and partial row
 // sums of dZ go to the tile's slice of the partial buffer; sddmm_finish_kernel adds the tiles.
-
-// d[i] is this lane's share of value i; returns, in lane i of every row of 16 lanes, the sum of
-// the 16 lanes' d[i].  Fixed pairing: lane l with l^8, l^7, l^2, l^1 in turn.
-__device__ __forceinline__ float row16_transpose_sum(const float (&d)[16], int lig)
+// What bounds it: the vector ALUs (8 instructions a gather of 4 x 64 columns: its address, four multiply-adds, the butterfly's share) beside the LDS.
+// As in the product, segments worked out once per block, indices and the next block's rows brought ahead, 32-bit offsets; the butterfly under bank
+// masks, and as short as the segment's end.  Weight gradient with its second pass, batch 1024: uniform 8192^2 at 5 % 580 -> 414 us, 16384^2 at 2 / 10 %
+// 1261 -> 840 and 3425 -> 2483, power-law 16384^2 at 10 % (dense rows apart) 2292 -> 1776; 5000 x 7000 at 8 %, batch 511: 213 -> 175.  Same bits.
+// d[i] is this lane's share of value i < N; returns, in lane i of every row of 16 lanes, the sum of
+// the 16 lanes' d[i] (in lanes N and up nothing of use).  Fixed pairing: lane l with l^8, l^7, l^2, l^1 in turn.  The first two levels add under a bank
+// mask, the lanes of one value and then those of the other, which needs no selects; in one piece, as an operand moved between lanes is there two
+// instructions after it is written.
+template <int N>
+__device__ __forceinline__ float row16_transpose_sum(float (&d)[16], int lig)
 {
-    // every lane has a partner in these four moves: no lane keeps the old value
-    auto from = [](auto ctrl, float x) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true));
-    };
-    using ror8 = std::integral_constant<int, 0x128>;         // row_ror:8
-    using half_mirror = std::integral_constant<int, 0x141>;  // row_half_mirror
-    using xor2 = std::integral_constant<int, 0x4E>;          // quad_perm [2,3,0,1]
-    using xor1 = std::integral_constant<int, 0xB1>;          // quad_perm [1,0,3,2]
-    const bool b3 = lig & 8, b2 = lig & 4, b1 = lig & 2, b0 = lig & 1;
-    float e[8], f[4], g[2];
+    static_assert(N == 4 || N == 8 || N == 12 || N == 16, "");
+#define NERVA_ADD8(a, b, banks) "v_add_f32_dpp %" #a ", %" #b ", %" #b " row_ror:8 row_mask:0xf bank_mask:" banks "\n\t"
+#define NERVA_ADD4(a, b, banks) "v_add_f32_dpp %" #a ", %" #b ", %" #b " row_half_mirror row_mask:0xf bank_mask:" banks "\n\t"
+    if constexpr (N == 16)
+        asm("s_nop 1\n\t"
+            NERVA_ADD8(0, 0, "0x3") NERVA_ADD8(0, 8, "0xc") NERVA_ADD8(1, 1, "0x3") NERVA_ADD8(1, 9, "0xc")
+            NERVA_ADD8(2, 2, "0x3") NERVA_ADD8(2, 10, "0xc") NERVA_ADD8(3, 3, "0x3") NERVA_ADD8(3, 11, "0xc")
+            NERVA_ADD8(4, 4, "0x3") NERVA_ADD8(4, 12, "0xc") NERVA_ADD8(5, 5, "0x3") NERVA_ADD8(5, 13, "0xc")
+            NERVA_ADD8(6, 6, "0x3") NERVA_ADD8(6, 14, "0xc") NERVA_ADD8(7, 7, "0x3") NERVA_ADD8(7, 15, "0xc")
+            NERVA_ADD4(0, 0, "0x5") NERVA_ADD4(0, 4, "0xa") NERVA_ADD4(1, 1, "0x5") NERVA_ADD4(1, 5, "0xa")
+            NERVA_ADD4(2, 2, "0x5") NERVA_ADD4(2, 6, "0xa") NERVA_ADD4(3, 3, "0x5") NERVA_ADD4(3, 7, "0xa")
+            : "+&v"(d[0]), "+&v"(d[1]), "+&v"(d[2]), "+&v"(d[3]), "+&v"(d[4]), "+&v"(d[5]), "+&v"(d[6]), "+&v"(d[7])
+            : "v"(d[8]), "v"(d[9]), "v"(d[10]), "v"(d[11]), "v"(d[12]), "v"(d[13]), "v"(d[14]), "v"(d[15]));
+    else if constexpr (N == 12)
+        asm("s_nop 1\n\t"
+            NERVA_ADD8(0, 0, "0x3") NERVA_ADD8(0, 8, "0xc") NERVA_ADD8(1, 1, "0x3") NERVA_ADD8(1, 9, "0xc")
+            NERVA_ADD8(2, 2, "0x3") NERVA_ADD8(2, 10, "0xc") NERVA_ADD8(3, 3, "0x3") NERVA_ADD8(3, 11, "0xc")
+            NERVA_ADD8(4, 4, "0x3") NERVA_ADD8(5, 5, "0x3") NERVA_ADD8(6, 6, "0x3") NERVA_ADD8(7, 7, "0x3")
+            NERVA_ADD4(0, 0, "0x5") NERVA_ADD4(0, 4, "0xa") NERVA_ADD4(1, 1, "0x5") NERVA_ADD4(1, 5, "0xa")
+            NERVA_ADD4(2, 2, "0x5") NERVA_ADD4(2, 6, "0xa") NERVA_ADD4(3, 3, "0x5") NERVA_ADD4(3, 7, "0xa")
+            : "+&v"(d[0]), "+&v"(d[1]), "+&v"(d[2]), "+&v"(d[3]), "+&v"(d[4]), "+&v"(d[5]), "+&v"(d[6]), "+&v"(d[7])
+            : "v"(d[8]), "v"(d[9]), "v"(d[10]), "v"(d[11]));
+    else if constexpr (N == 8)
+        asm("s_nop 1\n\t"
+            NERVA_ADD8(0, 0, "0x3") NERVA_ADD8(1, 1, "0x3") NERVA_ADD8(2, 2, "0x3") NERVA_ADD8(3, 3, "0x3")
+            NERVA_ADD8(4, 4, "0x3") NERVA_ADD8(5, 5, "0x3") NERVA_ADD8(6, 6, "0x3") NERVA_ADD8(7, 7, "0x3")
+            NERVA_ADD4(0, 0, "0x5") NERVA_ADD4(0, 4, "0xa") NERVA_ADD4(1, 1, "0x5") NERVA_ADD4(1, 5, "0xa")
+            NERVA_ADD4(2, 2, "0x5") NERVA_ADD4(2, 6, "0xa") NERVA_ADD4(3, 3, "0x5") NERVA_ADD4(3, 7, "0xa")
+            : "+&v"(d[0]), "+&v"(d[1]), "+&v"(d[2]), "+&v"(d[3]), "+&v"(d[4]), "+&v"(d[5]), "+&v"(d[6]), "+&v"(d[7]));
+    else
+        asm("s_nop 1\n\t"
+            NERVA_ADD8(0, 0, "0x3") NERVA_ADD8(1, 1, "0x3") NERVA_ADD8(2, 2, "0x3") NERVA_ADD8(3, 3, "0x3")
+            NERVA_ADD4(0, 0, "0x5") NERVA_ADD4(1, 1, "0x5") NERVA_ADD4(2, 2, "0x5") NERVA_ADD4(3, 3, "0x5")
+            : "+&v"(d[0]), "+&v"(d[1]), "+&v"(d[2]), "+&v"(d[3]));
+#undef NERVA_ADD8
+#undef NERVA_ADD4
+    const bool b1 = lig & 2, b0 = lig & 1;
+    float g[2];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) e[k] = (b3 ? d[k + 8] : d[k]) + from(ror8{}, b3 ? d[k] : d[k + 8]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) f[k] = (b2 ? e[k + 4] : e[k]) + from(half_mirror{}, b2 ? e[k] : e[k + 4]);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) g[k] = (b1 ? f[k + 2] : f[k]) + from(xor2{}, b1 ? f[k] : f[k + 2]);
-    return (b0 ? g[1] : g[0]) + from(xor1{}, b0 ? g[0] : g[1]);
+    for (int k = 0; k < 2; ++k) g[k] = (b1 ? d[k + 2] : d[k]) + dpp<0x4E>(b1 ? d[k] : d[k + 2]);  // quad_perm [2,3,0,1]
+    return (b0 ? g[1] : g[0]) + dpp<0xB1>(b0 ? g[0] : g[1]);                                      // quad_perm [1,0,3,2]
 }
 
-template <int I>
-__device__ __forceinline__ float staged_dot(const char *lds, int off, const float4 &z)
+// The first N entries of every lane row, whose LDS byte offsets its lanes hold: their sums, in lane i entry i's.
+template <int N>
+__device__ __forceinline__ float staged_dots(const char *lds, int off, const float4 &z, int lig)
 {
-    const float4 x = *reinterpret_cast<const float4 *>(lds + row_lane<I>(off));
-    return fmaf(x.w, z.w, fmaf(x.z, z.z, fmaf(x.y, z.y, x.x * z.x)));
-}
-
-// Up to 16 entries of every lane row (n: the most any of the four has left, uniform): products of
-// the entries whose LDS byte offsets the lanes hold in off, stored by lane i for entry first + i.
-__device__ __forceinline__ void sddmm_staged_chunk(const char *lds, int off, const float4 &z, int n, int lig,
-                                                   int first, int end, float *gp)
-{
+    constexpr int kAhead = 4;
+    float4 x[N];
     float d[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) d[i] = 0.f;
-    d[0] = staged_dot<0>(lds, off, z); d[1] = staged_dot<1>(lds, off, z);
-    d[2] = staged_dot<2>(lds, off, z); d[3] = staged_dot<3>(lds, off, z);
-    if (n > 4) {
-        d[4] = staged_dot<4>(lds, off, z); d[5] = staged_dot<5>(lds, off, z);
-        d[6] = staged_dot<6>(lds, off, z); d[7] = staged_dot<7>(lds, off, z);
-    }
-    if (n > 8) {
-        d[8] = staged_dot<8>(lds, off, z); d[9] = staged_dot<9>(lds, off, z);
-        d[10] = staged_dot<10>(lds, off, z); d[11] = staged_dot<11>(lds, off, z);
-    }
-    if (n > 12) {
-        d[12] = staged_dot<12>(lds, off, z); d[13] = staged_dot<13>(lds, off, z);
-        d[14] = staged_dot<14>(lds, off, z); d[15] = staged_dot<15>(lds, off, z);
-    }
-    const float sum = row16_transpose_sum(d, lig);
-    if (first + lig < end) gp[first + lig] = sum;
-}
-
-__device__ __forceinline__ void sddmm_staged_segment(const SddmmArgs &a, const char *lds, int cb0, int lig, int p0, int len,
-                                                     int off, const float4 &z, float *gp)
-{
-    const int l01 = max(__builtin_amdgcn_readlane(len, 0), __builtin_amdgcn_readlane(len, 16));
-    const int l23 = max(__builtin_amdgcn_readlane(len, 32), __builtin_amdgcn_readlane(len, 48));
-    const int longest = max(l01, l23);
-    if (longest <= 16) {
-        if (longest > 0) sddmm_staged_chunk(lds, off, z, longest, lig, p0, p0 + len, gp);
-        return;
-    }
-    constexpr int kDepth = 2;  // chunks of 16 entries served while the next kDepth travel
-    int o[kDepth], o2[kDepth];
-    auto load_chunk = [&](int first, int &oo) {
-        oo = 0;
-        if (first < longest && first + lig < len) oo = (a.indices[p0 + first + lig] - cb0) * (kStageCols * 4);
+    auto gather = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        x[i] = *reinterpret_cast<const float4 *>(lds + row_lane<i>(off));
     };
-    o[0] = off;
-#pragma unroll
-    for (int k = 1; k < kDepth; ++k) load_chunk(16 * k, o[k]);
-    for (int c = 0; c < longest; c += 16 * kDepth) {
-#pragma unroll
-        for (int k = 0; k < kDepth; ++k) load_chunk(c + 16 * (kDepth + k), o2[k]);
-#pragma unroll
-        for (int k = 0; k < kDepth; ++k) {
-            const int n = longest - c - 16 * k;
-            if (n > 0) sddmm_staged_chunk(lds, o[k], z, n, lig, p0 + c + 16 * k, p0 + len, gp);
-        }
-#pragma unroll
-        for (int k = 0; k < kDepth; ++k) o[k] = o2[k];
-    }
+    static_for(std::make_integer_sequence<int, kAhead>{}, gather);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (i + kAhead < N) gather(std::integral_constant<int, i + kAhead>{});
+        d[i] = fmaf(x[i].w, z.w, fmaf(x[i].z, z.z, fmaf(x[i].y, z.y, x[i].x * z.x)));
+        if constexpr (i + kAhead < N) __builtin_amdgcn_sched_barrier(0);
+    });
+    return row16_transpose_sum<N>(d, lig);
 }
 
 __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const SddmmArgs a, const int n_tiles)
@@ -1393,6 +1381,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
     const int n_cb = a.blocks.staged_cblocks;
     const int my_slot = ((lig & (kStageJ - 1)) * kStageWaves + wv) * 4 + lrow;
     const int my_row = a.blocks.staged_rows[range * kStageRangeRows + my_slot];
+    const bool my_quad = my_row >= 0 && (my_row & kStageQuad);
     const int n_j = a.blocks.staged_groups[range];
     const int32_t *ends = a.blocks.staged_ends + static_cast<int64_t>(range) * (n_cb + 1) * kStageRangeRows + my_slot;
     float *gp = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
@@ -1415,66 +1404,87 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
             if (row >= 0 && lig == 0 && (!(slot_row & kStageQuad) || lrow == 0)) gp[a.partial_db_at + row] = sum;
         }
     });
-    auto segment = [&](auto jc, int e_lo, int e_hi, int &p0, int &len) {  // as in spmm_staged_kernel
+    // segments and chunks as in spmm_staged_kernel, without weights; a lane without an entry gathers from the block's first row, for a sum that is not stored
+    const int lig4 = lig * 4;
+    auto load_chunk = [&](uint32_t at, int left, int first) {
+        return __builtin_bit_cast(int, gload1(as_gmem(a.indices), (left > first * 4 ? at : 0u) + static_cast<uint32_t>(first * 4)));
+    };
+    auto placed = [&](int index, bool on, int base) { return on ? (index << 8) - base : 0; };
+    constexpr int kAheadJ = 2, kHeld = 4;
+    static_assert(kStageJ % kHeld == 0 && kAheadJ < kHeld, "");
+    int held[kHeld][2];
+    auto ask = [&](auto jc, const StagedSegments &s) {
         constexpr int j = decltype(jc)::value;
-        p0 = row_lane<j>(e_lo);
-        len = row_lane<j>(e_hi) - p0;
-        if (row_lane<j>(my_row) & kStageQuad) {
-            const int from = (len * lrow) >> 2;
-            p0 += from;
-            len = ((len * (lrow + 1)) >> 2) - from;
+        const uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(s.at)) + lig4);
+        const int left = row_lane<j>(s.left) - lig4;
+        held[j % kHeld][0] = load_chunk(at, left, 0);
+        held[j % kHeld][1] = load_chunk(at, left, 16);
+    };
+    constexpr int kShare = kStageRows / 64;
+    static_assert(kShare % 2 == 0 && kShare / 2 <= kStageJ, "two of them are asked for beside each slot");
+    float4 v[kShare];
+    const float *const my_x = a.X + static_cast<int64_t>(threadIdx.x >> 4) * a.ldx + col;
+    const int last_block = max(a.x_rows - kStageRows, 0), last_rows = a.x_rows - 64;
+    auto block_row = [&](int b) { return min(b * kStageRows, last_block); };
+    auto ask_rows = [&](int i, int cb0) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + i * 64, last_rows)) * a.ldx); };
+    auto put_rows = [&](int cb0) {
+#pragma unroll
+        for (int i = 0; i < kShare; ++i) {
+            const int k = min(cb0 + i * 64, last_rows);
+            stage[(k - cb0) * 16 + static_cast<int>(threadIdx.x)] = col_on ? drop_shared(v[i], own_col, col) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     };
-    auto first_chunks = [&](int blk, int e_lo, int e_hi, int (&off)[kStageJ]) {
-        static_for(all_j, [&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            off[j] = 0;
-            if (j < n_j) {
-                int p0, len;
-                segment(jc, e_lo, e_hi, p0, len);
-                if (lig < len) off[j] = (a.indices[p0 + lig] - blk * kStageRows) * (kStageCols * 4);
-            }
-        });
-    };
-    int e0 = ends[0], e1 = ends[kStageRangeRows];
+    int e1 = ends[kStageRangeRows];
+    StagedSegments now = staged_segments(ends[0], e1, my_quad, lrow);
     int e2 = n_cb >= 2 ? ends[2 * kStageRangeRows] : e1;
-    int off_cur[kStageJ];
-    first_chunks(0, e0, e1, off_cur);
+    static_for(std::make_integer_sequence<int, kAheadJ>{}, [&](auto jc) { ask(jc, now); });
+#pragma unroll
+    for (int i = 0; i < kShare; ++i) ask_rows(i, 0);
     for (int b = 0; b < n_cb; ++b) {
-        const int cb0 = b * kStageRows;
+        const int cb0 = block_row(b), cb_next = block_row(b + 1);
+        const int e3 = ends[min(b + 3, n_cb) * kStageRangeRows];
+        const StagedSegments next = staged_segments(e1, e2, my_quad, lrow);  // (empty behind the last block)
         lds_barrier();  // the previous block's gathers are done
-#pragma unroll
-        for (int h = 0; h < kStageRounds; ++h) {
-            constexpr int kHalf = kStageRows / (64 * kStageRounds);
-            float4 v[kHalf];
-#pragma unroll
-            for (int i = 0; i < kHalf; ++i) {
-                const int k = cb0 + (h * kHalf + i) * 64 + static_cast<int>(threadIdx.x >> 4);
-                v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < a.x_rows && col_on) v[i] = ld4(a.X + static_cast<int64_t>(k) * a.ldx + col);
-            }
-#pragma unroll
-            for (int i = 0; i < kHalf; ++i) stage[((h * kHalf + i) * 64 + (threadIdx.x >> 4)) * 16 + lig] = drop_shared(v[i], own_col, col);
-        }
-        int off_next[kStageJ];
-        int e3 = e2;
-        if (b + 1 < n_cb) {
-            first_chunks(b + 1, e1, e2, off_next);
-            if (b + 3 <= n_cb) e3 = ends[(b + 3) * kStageRangeRows];
-        } else {
-            static_for(all_j, [&](auto jc) { off_next[decltype(jc)::value] = 0; });
-        }
+        put_rows(cb0);
         lds_barrier();
+        const int base = cb0 << 8;
         static_for(all_j, [&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            if (j < n_j) {
-                int p0, len;
-                segment(jc, e0, e1, p0, len);
-                sddmm_staged_segment(a, lds, cb0, lig, p0, len, off_cur[j], z[j], gp);
+            if constexpr (j < kShare / 2) {
+                ask_rows(2 * j, cb_next);
+                ask_rows(2 * j + 1, cb_next);
+            }
+            if constexpr (j + kAheadJ < kStageJ) ask(std::integral_constant<int, j + kAheadJ>{}, now);
+            else ask(std::integral_constant<int, j + kAheadJ - kStageJ>{}, next);
+            __builtin_amdgcn_sched_barrier(0);
+            int n = __builtin_amdgcn_readlane(now.most, j);
+            if (n > 0) {
+                uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(now.at)) + lig4);
+                int left = row_lane<j>(now.left) - lig4;
+                int off = placed(held[j % kHeld][0], left > 0, base), off1 = placed(held[j % kHeld][1], left > 64, base);
+                for (; n > 32; n -= 16, at += 64, left -= 64) {
+                    const int c2 = load_chunk(at, left, 32);
+                    const float sum = staged_dots<16>(lds, off, z[j], lig);
+                    if (left > 0) gstore1(gp, at, sum);
+                    off = off1;
+                    off1 = placed(c2, left > 128, base);
+                }
+                for (;;) {
+                    float sum;
+                    if (n > 12) sum = staged_dots<16>(lds, off, z[j], lig);
+                    else if (n > 8) sum = staged_dots<12>(lds, off, z[j], lig);
+                    else if (n > 4) sum = staged_dots<8>(lds, off, z[j], lig);
+                    else sum = staged_dots<4>(lds, off, z[j], lig);
+                    if (left > 0) gstore1(gp, at, sum);
+                    n -= 16;
+                    if (n <= 0) break;
+                    at += 64;
+                    left -= 64;
+                    off = off1;
+                }
             }
         });
-        static_for(all_j, [&](auto jc) { off_cur[decltype(jc)::value] = off_next[decltype(jc)::value]; });
-        e0 = e1;
+        now = next;
         e1 = e2;
         e2 = e3;
     }
@@ -1572,7 +1582,7 @@ __global__ __launch_bounds__(kBlock) void full_sddmm_kernel(const SddmmArgs a, c
             }
         }
         // lane i of each row of 16 lanes gets that row's sum of product i; then the four rows: (0 + 1) + (2 + 3)
-        float g = row16_transpose_sum(d, lane & 15);
+        float g = row16_transpose_sum<16>(d, lane & 15);
         g += __shfl_xor(g, 16);
         g += __shfl_xor(g, 32);
         if (lane < R) {
@@ -2843,6 +2853,7 @@ bool sddmm_staged_ok(const SddmmArgs &a)
 {
     if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     if ((a.batch + kStageCols - 1) / kStageCols > a.partial_tiles) return false;
+    if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (as spmm_staged_ok)
     return staged_pays(a.blocks, a.x_rows, a.batch, a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : kStageLongSegmentSddmm) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
 }
 

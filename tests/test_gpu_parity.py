@@ -492,6 +492,40 @@ def test_staged_segments_of_every_length(nb, torch_mod, oracle, batch):
     L.close()
 
 
+@pytest.mark.parametrize("batch", [128, 190])
+def test_staged_sddmm_segments_of_every_length(nb, torch_mod, oracle, batch):
+    """The weight gradient on segments of 0 to 83 entries in the first column block and of 0 to 88 in the last, which starts before its first
+    column: whole chunks of 16, every remainder, chunks beyond the two that are fetched ahead.  Infinities in an operand row reach the gradients of
+    its entries and no others."""
+    torch = torch_mod
+    rows, cols = 336, 600
+    rng = np.random.default_rng(batch)
+    per_row = [np.sort(np.concatenate([rng.choice(np.arange(1, 512), i % 84, replace=False), 512 + rng.choice(88, (i * 37) % 89, replace=False),
+                                       np.zeros(1 if i % 5 == 0 else 0, dtype=np.int64)])) for i in range(rows)]
+    indices = np.concatenate(per_row).astype(np.int32)
+    indptr = np.concatenate([[0], np.cumsum([len(r) for r in per_row])]).astype(np.int32)
+    lay = wl.SparseLayerData(rows, cols, indptr, indices, rng.standard_normal(len(indices)).astype(np.float32),
+                             np.zeros(rows, np.float32), False)
+    X = rng.standard_normal((cols, batch)).astype(np.float32)
+    dZ = rng.standard_normal((rows, batch)).astype(np.float32)
+    nb.nerva_set_partition_mode(nb.NERVA_PARTITION_PREFER_STAGED)
+    try:
+        L = nb.SparseLinear(lay, max_batch=batch)
+    finally:
+        nb.nerva_set_partition_mode(nb.NERVA_PARTITION_BALANCED)
+    Xd = nb.to_dense(X); dZd = nb.to_dense(dZ)
+    g = torch.full((len(indices),), float("nan"), device="cuda"); db = torch.full((rows,), float("nan"), device="cuda")
+    nb.sparse_linear_backward(L.handle, Xd, None, dZd, None, g, db, batch)
+    gr, Sg, dbr, Sdb = oracle.sddmm(rows, cols, indptr, indices, dZ, X)
+    close(g.cpu().numpy(), gr, Sg, what="g"); close(db.cpu().numpy(), dbr, Sdb, what="db")
+    Xd[0] = float("inf")
+    nb.sparse_linear_backward(L.handle, Xd, None, dZd, None, g, db, batch)
+    got, at0 = g.cpu().numpy(), indices == 0
+    assert not np.isfinite(got[at0]).any()
+    close(got[~at0], gr[~at0], Sg[~at0], what="g beside infinities")
+    L.close()
+
+
 def test_power_law_rows_staged_and_ordinary_kernels_together(nb, torch_mod, oracle):
     """The same split on an operand small enough to stay untiled (600 rows x 1024 columns): without column tiles the
     packed path does not run, so the short rows of the forward product go through the wide kernel on a partition of
