@@ -2828,7 +2828,7 @@ int spmm_split_group(const SpmmArgs &a)
 bool spmm_staged_ok(const SpmmArgs &a)
 {
     if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (it brings 64 operand rows at a time, and reads entries at 32-bit byte offsets, 32 past the first)
-    if (!staged_pays(a.blocks, a.x_rows, a.batch, kStageLongSegment)) return false;
+    if (!staged_pays(a.blocks, a.x_rows, a.batch, static_cast<int64_t>(a.nnz) * a.batch >= kStageSomeWork ? kStageSegmentSomeWork : kStageLongSegment)) return false;
     return !a.blocks.staged_partial || a.blocks.n_rest_blocks > 0;  // (the rows the plan leaves out need a partition of their own)
 }
 
@@ -2854,7 +2854,7 @@ bool sddmm_staged_ok(const SddmmArgs &a)
     if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     if ((a.batch + kStageCols - 1) / kStageCols > a.partial_tiles) return false;
     if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (as spmm_staged_ok)
-    return staged_pays(a.blocks, a.x_rows, a.batch, a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : kStageLongSegmentSddmm) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
+    return staged_pays(a.blocks, a.x_rows, a.batch, a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : static_cast<int64_t>(a.nnz) * a.batch >= kStageMuchWork ? kStageSegmentMuchWork : kStageLongSegmentSddmm) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
 }
 
 bool spmm_offsets_ok(const SpmmArgs &a)
@@ -3172,13 +3172,35 @@ bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &)
 // which the pass pays there (steps of 3072-1024-512-10 at 10 %, batch 100, 5 M in the middle layer: 38.6 -> 42.5 us with it;
 // 2000-4000-3000-10 at 3 %, batch 128, 46 M: 72.4 -> 70.2; three layers of 3000 at 5 %, batch 100: 128 -> 116).
 constexpr int64_t kFusedMinWork = 16 << 20;
+// Both products staged through LDS against one stream of L2 gathers for both: apart they gather twice, from LDS at up to three times the rate.
+// What decides is the length of the mirror's segments, less of it where dZ is beyond the L2s and the stream is slow.  Both gradients, us, one stream / apart:
+// uniform 16384^2 at 3 / 5 / 10 %, batch 1024 1994 / 1830, 3246 / 2596, 6435 / 4595, at 2 / 5 / 8 %, batch 300 478 / 700, 1288 / 1008, 2271 / 1516; 11000^2 at 4.5 %, batch 256 / 448 /
+// 1024 375 / 381, 612 / 562, 1277 / 1060; 8192^2 at 5 / 10 %, batch 256 221 / 262, 416 / 411, batch 1024 671 / 721, 1292 / 1152; 6000 x 16384 at 6.5 %, batch 256 / 448 / 700 395 / 426, 657 / 664,
+// 932 / 856, at 9 % 557 / 537, 918 / 833, 1270 / 1084; power-law 16384^2 at 3 / 6 / 10 %, batch 384 710 / 740, 1503 / 1158, 3099 / 1801; of 3000 rows or columns never (12000 x 3000 at 6 %, batch 512 277 / 281).
+// In a training step the stream also has the updates to strew over values and velocity, which the SDDMM's second pass finds in order: steps of 3072-8192-8192-10 at 3 / 6 %, batch 256
+// 365 / 365 and 625 / 535, batch 1024 930 / 1082 and 1609 / 1466; 2000-5000-4000-100 at 6 %, batch 256 / 512 223 / 250 and 360 / 350.
+static bool backward_apart_pays(const SpmmArgs &t, const SddmmArgs &g, bool alone)
+{
+    if (!spmm_staged_ok(t)) return false;
+    SddmmArgs others = g;
+    if (sddmm_dense_rows_ok(g)) {
+        if (!alone) return true;   // (much of the gradient by matrix instructions)
+        others.blocks = g.split->others; others.split = nullptr; others.split_done = g.split;
+    }
+    if (!sddmm_staged_ok(others)) return false;
+    const int64_t segments = static_cast<int64_t>(t.rows) * t.blocks.staged_cblocks, work = static_cast<int64_t>(t.nnz) * t.batch;
+    if (!alone) return work >= 560'000'000 && t.nnz >= 20 * segments;
+    if (t.rows < 4096) return false;
+    if (t.x_rows >= 10000 && static_cast<int64_t>(t.x_rows) * t.batch * 4 >= (18ll << 20) && t.nnz >= 22 * segments) return true;
+    return work >= 1'400'000'000 && t.nnz >= (t.batch >= 384 || t.x_rows >= 10000 ? 32 : 44) * segments;
+}
 bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
 {
     if (t.batch != g.batch || t.batch < 4 || t.X != g.dZ || t.ldx != g.lddz || t.XM != g.ZM || t.ldxm != g.ldzm) return false;
     if (t.YM && (t.YM != g.X || t.ldym != g.ldx)) return false;
     if (t.rows != g.x_rows || t.x_rows != g.rows || t.nnz != g.nnz || t.nnz <= 0) return false;
     if (g.skip_products || g.dense || g.loss_cols || !g.perm) return false;
-    if (!spmm_offsets_ok(t) || !sddmm_offsets_ok(g) || (!alone && spmm_staged_ok(t))) return false;
+    if (!spmm_offsets_ok(t) || !sddmm_offsets_ok(g) || backward_apart_pays(t, g, alone)) return false;
     const int tg = backward_tile_group(t);
     if (!alone && static_cast<int64_t>(t.nnz) * t.batch < kFusedMinWork) return false;
     const int n_tiles = backward_tiles(t, tg);

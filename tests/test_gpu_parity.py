@@ -526,6 +526,30 @@ def test_staged_sddmm_segments_of_every_length(nb, torch_mod, oracle, batch):
     L.close()
 
 
+@pytest.mark.parametrize("relu,batch", [(False, 1000), (True, 1003)])
+def test_backward_of_long_segments_takes_the_staged_products_apart(nb, torch_mod, oracle, relu, batch):
+    """Both gradients where each is staged through LDS by itself (1.5 million entries, segments of about 41): the weight gradient has the bits of
+    the call that asks for it alone, the other is the oracle's."""
+    torch = torch_mod
+    rows, cols = 4608, 4100
+    lay = layer_case(rows, cols, 0.08, seed=batch, relu=relu)
+    rng = np.random.default_rng(batch)
+    X = rng.standard_normal((cols, batch)).astype(np.float32)
+    dY = rng.standard_normal((rows, batch)).astype(np.float32)
+    L = nb.SparseLinear(lay, max_batch=batch)
+    Xd = nb.to_dense(X); dYd = nb.to_dense(dY); Yd = nb.dense(rows, batch); dXd = nb.dense(cols, batch)
+    nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+    g, db = (torch.full((n,), float("nan"), device="cuda") for n in (L.nnz, rows))
+    g1, db1 = torch.empty_like(g), torch.empty_like(db)
+    nb.sparse_linear_backward(L.handle, Xd, Yd if relu else None, dYd, dXd, g, db, batch)
+    nb.sparse_linear_backward(L.handle, Xd, Yd if relu else None, dYd, None, g1, db1, batch)
+    assert torch.equal(g, g1) and torch.equal(db, db1)
+    dZ = oracle.relu_backward(dY, Yd.cpu().numpy()) if relu else dY
+    dX, SdX = oracle.spmm_t(rows, cols, lay.indptr, lay.indices, lay.values, dZ)
+    close(dXd.cpu().numpy(), dX, SdX, what="dX")
+    L.close()
+
+
 def test_power_law_rows_staged_and_ordinary_kernels_together(nb, torch_mod, oracle):
     """The same split on an operand small enough to stay untiled (600 rows x 1024 columns): without column tiles the
     packed path does not run, so the short rows of the forward product go through the wide kernel on a partition of
