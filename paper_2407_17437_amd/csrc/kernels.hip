@@ -59,6 +59,45 @@ __device__ __forceinline__ void fma_into(float (&acc)[4], float w, float4 x)
     acc[3] = fmaf(w, x.w, acc[3]);
 }
 
+// f(i) for 0 <= i < n, a work-group's threads side by side, in eight runs: n_blocks work-groups (a multiple of 8, the launch's first) go to the XCDs in turn, and each
+// XCD walks a run of its own in order.  For passes that step through one orientation's entries and reach the other's through the position map: entries of
+// neighbouring rows there lie side by side here, so the 128-byte lines that one XCD's run touches are a band that its L2 holds, and every line is
+// brought to (or written back from) one or two L2s instead of all eight.
+// The mirror's values of 16384^2 at 1 / 10 %, power-law: 20.9 -> 17.6 and 307 -> 192 us (what is left is a line from L2 per value); second pass of both gradients, at 1 % 52 -> 39 us, of a
+// step's 8192^2 layer at 0.6 % 24.5 -> 21.0.  Steps of 3072-8192-8192-10 at 5 %, batch 512 726 -> 694, of 1000-3000-3000-3000-30 262 -> 251.
+struct XcdRun {
+    int64_t first, end, step;   // the work-group's first item, its XCD's last, the way from one turn to the next
+};
+template <int EACH = 1>
+__device__ __forceinline__ XcdRun xcd_run(int64_t n, int n_blocks)
+{
+    constexpr int kItems = kEwBlock * EACH;
+    const int64_t per = ((n + kItems - 1) / kItems + 7) / 8 * kItems, first = (blockIdx.x & 7) * per;
+    return XcdRun{first + static_cast<int64_t>(blockIdx.x >> 3) * kItems, min(n, first + per), static_cast<int64_t>(n_blocks >> 3) * kItems};
+}
+template <typename F>
+__device__ __forceinline__ void for_runs_of_xcds(int64_t n, int n_blocks, F &&f)
+{
+    const XcdRun run = xcd_run(n, n_blocks);
+    for (int64_t i = run.first + threadIdx.x; i < run.end; i += run.step) f(i);
+}
+// dst[i] = src[perm[i]]: many in kGatherEach a thread, whose reads travel together, few in one
+constexpr int kGatherEach = 4;
+constexpr int64_t kGatherMany = 1 << 20;
+__device__ __forceinline__ void gather_runs(float *__restrict__ dst, const float *__restrict__ src, const int32_t *__restrict__ perm, int64_t n, int n_blocks)
+{
+    if (n < kGatherMany) return for_runs_of_xcds(n, n_blocks, [&](int64_t i) { dst[i] = src[perm[i]]; });
+    const XcdRun run = xcd_run<kGatherEach>(n, n_blocks);
+    for (int64_t base = run.first + threadIdx.x; base < run.end; base += run.step) {
+        float x[kGatherEach];
+#pragma unroll
+        for (int u = 0; u < kGatherEach; ++u) x[u] = src[perm[min(base + u * kEwBlock, run.end - 1)]];
+#pragma unroll
+        for (int u = 0; u < kGatherEach; ++u)
+            if (base + u * kEwBlock < run.end) dst[base + u * kEwBlock] = x[u];
+    }
+}
+
 // U consecutive stored entries starting at p: all index/weight fetches, then all gathers, then
 // the FMAs, so that U reads are in flight per wave.
 template <bool XMASK, int U>
@@ -1608,9 +1647,11 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
 {
     const int64_t stride = static_cast<int64_t>(blockDim.x) * gridDim.x;
     const bool skip = dense.n > 0;
-    for (int64_t base = static_cast<int64_t>(blockIdx.x) * blockDim.x; base < a.nnz; base += stride) {
+    // (only where new weights go to the mirror: 26.8 M gradients alone 213 us in turn, 233 in runs)
+    const XcdRun run = a.fused && a.values_t ? xcd_run(a.nnz, gridDim.x) : XcdRun{static_cast<int64_t>(blockIdx.x) * kEwBlock, a.nnz, stride};
+    for (int64_t base = run.first; base < run.end; base += run.step) {
         const int64_t p = base + threadIdx.x;
-        bool mine = p < a.nnz;
+        bool mine = p < run.end;
         if (skip) {
             int ahead = 0, hi = dense.n;
             while (ahead < hi) {
@@ -1898,8 +1939,8 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
 __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const BackwardArgs a, const int n_tiles, const int n_entry_blocks)
 {
     if (static_cast<int>(blockIdx.x) < n_entry_blocks) {
-        const int64_t stride = static_cast<int64_t>(kEwBlock) * n_entry_blocks;
-        for (int64_t q = static_cast<int64_t>(blockIdx.x) * kEwBlock + threadIdx.x; q < a.nnz; q += stride) {
+        for_runs_of_xcds(a.nnz, n_entry_blocks, [&](int64_t q) {
+            const int p = a.perm[q];
             float g = 0.f;
             int t = 0;
             for (; t + 8 <= n_tiles; t += 8) {  // eight loads in flight, added in tile order
@@ -1910,7 +1951,6 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
                 for (int u = 0; u < 8; ++u) g += v[u];
             }
             for (; t < n_tiles; ++t) g += a.partial[static_cast<int64_t>(t) * a.partial_stride + q];
-            const int p = a.perm[q];
             if (a.g) a.g[p] = g;
             if (a.fused) {
                 float w = a.w[p], v = a.velocity[p];
@@ -1919,7 +1959,7 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
                 a.velocity[p] = v;
                 a.w_t[q] = w;
             }
-        }
+        });
         return;
     }
     if (!(a.db || (a.fused && a.bias))) return;
@@ -2243,9 +2283,7 @@ __global__ __launch_bounds__(kEwBlock) void momentum_kernel(float *__restrict__ 
 __global__ __launch_bounds__(kEwBlock) void gather_kernel(float *__restrict__ dst, const float *__restrict__ src,
                                                           const int32_t *__restrict__ perm, int64_t n)
 {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride)
-        dst[i] = src[perm[i]];
+    gather_runs(dst, src, perm, n, gridDim.x);
 }
 
 // What a stand-alone backward pass needs before its products, in one grid: the mirror's values (work-groups [0, n_gather)),
@@ -2258,8 +2296,7 @@ __global__ __launch_bounds__(kEwBlock) void backward_prep_kernel(float *__restri
                                                                  int64_t ldy, float *__restrict__ dZ, int64_t lddz, int rows, int batch)
 {
     if (static_cast<int>(blockIdx.x) < n_gather) {
-        const int64_t stride = static_cast<int64_t>(n_gather) * kEwBlock;
-        for (int64_t i = static_cast<int64_t>(blockIdx.x) * kEwBlock + threadIdx.x; i < nnz; i += stride) values_t[i] = values[perm[i]];
+        gather_runs(values_t, values, perm, nnz, n_gather);
         return;
     }
     const int quads = (batch + 3) / 4;   // batch >= 4
@@ -2613,6 +2650,14 @@ inline int elementwise_blocks(int64_t work_items)
     return static_cast<int>(b);
 }
 
+// ... of for_runs_of_xcds, kEwBlock * each items to a work-group and turn: a turn for all, for the second would not follow the first's neighbours
+inline int xcd_run_blocks(int64_t work_items, int each = 1)
+{
+    const int64_t b = (work_items + kEwBlock * each - 1) / (kEwBlock * each);
+    return static_cast<int>(b < 1 ? 8 : b > (1 << 18) ? 1 << 18 : (b + 7) / 8 * 8);
+}
+inline int gather_blocks(int64_t n) { return xcd_run_blocks(n, n < kGatherMany ? 1 : kGatherEach); }
+
 bool spmm_offsets_ok(const SpmmArgs &a);
 
 hipError_t spmm_go(SpmmArgs a, hipStream_t s)
@@ -2865,7 +2910,7 @@ bool spmm_offsets_ok(const SpmmArgs &a)
 void sddmm_finish_go(const SddmmArgs &a, int n_tiles, hipStream_t s)
 {
     const int64_t work = a.nnz > a.rows ? a.nnz : a.rows;
-    hipLaunchKernelGGL(sddmm_finish_kernel, dim3(elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles,
+    hipLaunchKernelGGL(sddmm_finish_kernel, dim3(a.fused && a.values_t ? xcd_run_blocks(work) : elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles,
                        a.split_done ? a.split_done->rows : DenseRows{}, a.split_done ? a.split_done->flag : nullptr);
 }
 
@@ -3328,7 +3373,7 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         default: go(std::integral_constant<int, 8>{}); break;
     }
     if (one) return hipGetLastError();
-    const int n_entry_blocks = elementwise_blocks(t.nnz);
+    const int n_entry_blocks = xcd_run_blocks(t.nnz);
     hipLaunchKernelGGL(backward_finish_kernel, dim3(n_entry_blocks + n_row_blocks), dim3(kEwBlock), 0, s, a, n_tiles, n_entry_blocks);
     return hipGetLastError();
 }
@@ -3552,14 +3597,14 @@ hipError_t launch_momentum(float *w, float *v, const float *g, int64_t n, float 
 hipError_t launch_gather(float *values_t, const float *values, const int32_t *perm, int64_t n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gather_kernel, dim3(elementwise_blocks(n)), dim3(kEwBlock), 0, s, values_t, values, perm, n);
+    hipLaunchKernelGGL(gather_kernel, dim3(gather_blocks(n)), dim3(kEwBlock), 0, s, values_t, values, perm, n);
     return hipGetLastError();
 }
 
 hipError_t launch_backward_prep(float *values_t, const float *values, const int32_t *perm, int64_t nnz, const float *dY, int64_t lddy,
                                 const float *Y, int64_t ldy, float *dZ, int64_t lddz, int32_t rows, int32_t batch, hipStream_t s)
 {
-    const int n_gather = nnz > 0 ? elementwise_blocks(nnz) : 0;
+    const int n_gather = nnz > 0 ? gather_blocks(nnz) : 0;
     const int n_mask = elementwise_blocks(static_cast<int64_t>(rows) * ((batch + 3) / 4));
     hipLaunchKernelGGL(backward_prep_kernel, dim3(n_gather + n_mask), dim3(kEwBlock), 0, s, values_t, values, perm, nnz, n_gather, dY, lddy, Y,
                        ldy, dZ, lddz, rows, batch);

@@ -430,6 +430,28 @@ def test_both_gradients_in_one_pass(nb, oracle, rows, cols, density, batch, ld, 
     L.close()
 
 
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("nnz", [1, 2048, 2049, 70001, (1 << 20) - 1, 1 << 20, (1 << 20) + 1025])
+def test_mirror_values_follow_the_weights(nb, nnz, relu):
+    """Weights changed by the caller reach every mirror entry before the transposed product: numbers of entries about whole turns of the
+    launch's work-groups, and about where a thread begins to bring four."""
+    import torch
+    rows, cols, batch = 3001, 2000, 12
+    indptr, indices = wl.uniform_pattern(rows, cols, nnz, nnz)
+    lay = wl.SparseLayerData(rows, cols, indptr, indices, wl.init_values(indptr, 1), np.zeros(rows, np.float32), relu)
+    L = nb.SparseLinear(lay, max_batch=batch)
+    L.values.normal_()
+    X, Y, dY, dX = nb.dense(cols, batch), nb.dense(rows, batch), nb.dense(rows, batch), nb.dense(cols, batch)
+    for t in (X, dY):
+        t.normal_()
+    nb.sparse_linear_forward(L.handle, X, Y, batch)
+    nb.sparse_linear_backward(L.handle, X, Y if relu else None, dY, dX, None, None, batch)
+    torch.cuda.synchronize()
+    _, _, v_t, perm = nb.sparse_linear_mirror(L.handle)
+    assert np.array_equal(raw_f32(nb, torch, v_t, nnz), L.values.cpu().numpy()[raw_i32(nb, torch, perm, nnz)])
+    L.close()
+
+
 @pytest.mark.parametrize("batch,hidden", [(60, (2000, 1500)), (64, (2000, 3000)), (200, (900, 1300)), (300, (1100, 1000))])
 def test_training_step_with_both_gradients_in_one_pass(nb, batch, hidden):
     """Against the same step by separate products: one and several column tiles, momentum applied inside the pass and after it."""
