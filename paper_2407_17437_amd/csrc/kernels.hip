@@ -410,7 +410,7 @@ __device__ __forceinline__ void spmm_body_grouped(const SpmmArgs &a, const int b
 // can serve kPackSets sets one after the other, fetching the next set's rows and indices one
 // step ahead; measured, one set per wave is best (more, shorter work-groups balance better than
 // the saved start-up is worth).
-template <int GS, bool XMASK>
+template <int GS, bool XMASK, int W>
 __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int block, const int col0, const int n_pack_blocks)
 {
     constexpr int NE = kWave / GS;
@@ -431,8 +431,8 @@ __device__ __forceinline__ void spmm_body_packed(const SpmmArgs &a, const int bl
     // launch's n_waves takes sets k, k + n_waves, k + 2 n_waves, ... and every wave gets its share
     // of long and of short rows (consecutive sets per wave left the first work-groups 1.4x the work
     // of the average on rows of 40..85 entries, and a launch is one round of work-groups).
-    const int n_waves = n_pack_blocks * kWavesPerBlock;
-    const int first_set = block * kWavesPerBlock + wv;
+    const int n_waves = n_pack_blocks * W;
+    const int first_set = block * W + wv;
     if (first_set >= n_sets) return;  // wave-uniform
     const int last_set = first_set + ((n_sets - 1 - first_set) / n_waves) * n_waves;  // <= first_set + (kPackSets - 1) * n_waves
 
@@ -520,12 +520,25 @@ __global__ __launch_bounds__(kBlock) void spmm_packed_kernel(const SpmmArgs a, c
     int tile, rb;
     if (!tile_of_block(n_tiles, nrb, order, tile, rb)) return;
     if (rb < n_pack_blocks) {
-        spmm_body_packed<GS, XMASK>(a, rb, tile * GS * 4, n_pack_blocks);
+        spmm_body_packed<GS, XMASK, kWavesPerBlock>(a, rb, tile * GS * 4, n_pack_blocks);
     } else {
         SpmmArgs al = a;
         al.blocks.waves = a.blocks.long_waves;
         spmm_body_grouped<GS, XMASK, true>(al, rb - n_pack_blocks, tile * GS * 4);
     }
+}
+
+// The same without long rows, in work-groups of kPackWaves: nothing is shared among the waves, and where the launch is a round of work-groups and a little, the
+// little starts on every compute unit as waves end (infer 3072-8192-8192-10 at 1 %, batch 300: 74.8 us in work-groups of 16 waves, 70.8 of 8, 70.0 of 4, 69.8 of 1; 8192^2 at 1 %,
+// batch 300 48.9 -> 42.9; 3000 x 7000 at 1 %, batch 600 32.4 -> 28.8; wide MLP at batch 1024 as before).
+constexpr int kPackWaves = 4;
+template <int GS, bool XMASK>
+__global__ __launch_bounds__(kPackWaves * kWave) __attribute__((amdgpu_waves_per_eu(XMASK ? 1 : 8))) void spmm_packed_only_kernel(const SpmmArgs a, const int n_tiles,
+                                                                                                                            const TileOrder order, const int n_pack_blocks)
+{
+    int tile, rb;
+    if (!tile_of_block(n_tiles, n_pack_blocks, order, tile, rb)) return;
+    spmm_body_packed<GS, XMASK, kPackWaves>(a, rb, tile * GS * 4, n_pack_blocks);
 }
 
 template <int GS, bool XMASK>
@@ -2755,6 +2768,7 @@ struct PackedGrid {
     int n_tiles, n_pack_blocks;
     TileOrder order;
     int64_t ids;
+    bool long_rows;   // (else spmm_packed_only_kernel)
 };
 PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
 {
@@ -2762,8 +2776,10 @@ PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
     const int ne = kWave / gs;
     g.n_tiles = (a.batch + gs * 4 - 1) / (gs * 4);
     const int64_t n_sets = (static_cast<int64_t>(a.blocks.n_short) + ne - 1) / ne;
-    g.n_pack_blocks = static_cast<int>((n_sets + kWavesPerBlock * kPackSets - 1) / (kWavesPerBlock * kPackSets));
-    const int64_t nrb = static_cast<int64_t>(g.n_pack_blocks) + (with_long_rows ? a.blocks.n_long_blocks : 0);
+    g.long_rows = with_long_rows && a.blocks.n_long_blocks > 0;
+    const int sets = (g.long_rows ? kWavesPerBlock : kPackWaves) * kPackSets;   // of a work-group
+    g.n_pack_blocks = static_cast<int>((n_sets + sets - 1) / sets);
+    const int64_t nrb = static_cast<int64_t>(g.n_pack_blocks) + (g.long_rows ? a.blocks.n_long_blocks : 0);
     g.order = tile_order(g.n_tiles, nrb, gs, true, tiled_launch(a));
     g.ids = tile_grid(g.order, g.n_tiles, nrb);
     return g;
@@ -2776,7 +2792,10 @@ hipError_t spmm_packed_go(const SpmmArgs &a, hipStream_t s)
     const TileOrder order = pg.order;
     if (pg.ids > kMaxGridIds) return hipErrorInvalidConfiguration;  // (callers check before choosing this path)
     dim3 grid(static_cast<unsigned>(pg.ids));
-    if (a.XM)
+    if (!pg.long_rows) {
+        const auto kernel = a.XM ? spmm_packed_only_kernel<GS, true> : spmm_packed_only_kernel<GS, false>;
+        hipLaunchKernelGGL(kernel, grid, dim3(kPackWaves * kWave), 0, s, a, n_tiles, order, n_pack_blocks);
+    } else if (a.XM)
         hipLaunchKernelGGL((spmm_packed_kernel<GS, true>), grid, dim3(kBlock), 0, s, a, n_tiles, order, n_pack_blocks);
     else
         hipLaunchKernelGGL((spmm_packed_kernel<GS, false>), grid, dim3(kBlock), 0, s, a, n_tiles, order, n_pack_blocks);
@@ -2843,6 +2862,20 @@ bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t
                              static_cast<int64_t>(blocks.staged_longest_row) * rows <= 4 * nnz;
     const int64_t segment = big_operand ? std::min(long_segment, kStageSegmentBigOperand) : long_segment;
     return nnz >= segment * rows * blocks.staged_cblocks;
+}
+
+// Short even rows in 64-column tiles for the sake of the packed kernel and its small work-groups, where the rule of the tiles (tile_columns) leaves the operand whole: one beyond an
+// L2 whose rows are gathered a dozen times or more (and not so often that it stays in cache), tiles hardly empty.  Uniform rows, whole -> in tiles, us: 15997 x 15191 at 0.35 %, batch 372 126 -> 79;
+// 3894 x 6816 at 0.6 %, batch 227 15.9 -> 11.8; 16384^2 at 0.3 %, batch 300 103 -> 61; 10442 x 13851 at 0.37 %, batch 164 38.8 -> 27.9.  But tiles a fifth empty or more: 10681 x 8704 at 0.8 %, batch 134
+// 36.5 -> 42.3, 11466 x 5888 at 0.5 %, batch 263 30.2 -> 34.0; operands near an L2: 4545 x 5628 at 0.7 %, batch 189 13.1 -> 14.1; often gathered: 16000 x 5000 at 0.8 %, batch 200 29.0 -> 31.2,
+// 3182 x 2692 at 1.9 %, batch 580 25.7 -> 28.3; rarely: 3428 x 12999 at 0.33 %, batch 290 25.3 -> 26.7.
+static bool packed_tiles_pay(const SpmmArgs &a)
+{
+    if (a.batch <= 128 || a.XM || a.blocks.n_short != a.rows || a.blocks.hot_share >= 0.5f) return false;
+    if (static_cast<int64_t>(a.blocks.staged_longest_row) * a.rows > 4ll * a.nnz || (a.batch + 63) / 64 * 320 > 6 * a.batch) return false;
+    const int64_t row_bytes = static_cast<int64_t>(a.x_rows) * 4, operand = row_bytes * a.batch, most = operand >= (11ll << 20) ? 90 : 55;
+    return operand >= (21ll << 18) && row_bytes * 64 <= (4ll << 20) && a.nnz >= 28ll * a.rows && a.nnz >= 12ll * a.x_rows && a.nnz <= most * a.x_rows &&
+           packed_grid(a, 16, true).ids <= kMaxGridIds;
 }
 
 int spmm_tile_group(const SpmmArgs &a);
@@ -3467,7 +3500,8 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         return hipGetLastError();
     }
     if (spmm_offsets_ok(a)) {
-        const int tg = spmm_tile_group(a);
+        int tg = spmm_tile_group(a);
+        if (tg == 0 && packed_tiles_pay(a)) tg = 16;
         const int sg = tg == 0 ? spmm_split_group(a) : 0;
         if (sg != 0) {
             // Long rows inside column tiles (their gathers are most of the traffic and then hit in the L2s),

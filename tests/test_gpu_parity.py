@@ -550,6 +550,28 @@ def test_backward_of_long_segments_takes_the_staged_products_apart(nb, torch_mod
     L.close()
 
 
+@pytest.mark.parametrize("rows,cols,density,batch,padded", [(2049, 7001, 0.0065, 254, True), (2048, 7001, 0.0065, 253, False), (4100, 9000, 0.004, 318, False), (8192, 3072, 0.013, 300, True),
+                                                            (3000, 16384, 0.0045, 129, True), (3000, 16384, 0.0045, 379, True), (2500, 6000, 0.0099, 1001, False)])
+def test_short_rows_in_small_work_groups(nb, torch_mod, oracle, rows, cols, density, batch, padded):
+    """The packed product without long rows: rows that do not fill a wave's set or a work-group, tiles partly empty, in 64-column tiles for its
+    own sake and not; an operand row of infinities reaches the rows that reference it and no others."""
+    torch = torch_mod
+    lay = layer_case(rows, cols, density, seed=rows + batch, relu=False)
+    X = np.random.default_rng(batch).standard_normal((cols, batch)).astype(np.float32)
+    L = nb.SparseLinear(lay, max_batch=batch)
+    Xd = nb.to_dense(X) if padded else torch.as_tensor(X).cuda()
+    Yd = nb.dense(rows, batch) if padded else torch.empty(rows, batch, device="cuda")
+    nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+    Y, S = oracle.spmm(rows, cols, lay.indptr, lay.indices, lay.values, lay.bias, X, False)
+    close(Yd.cpu().numpy(), Y, S, what="Y")
+    Xd[cols // 2] = float("inf")
+    nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+    hit = np.zeros(rows, dtype=bool)
+    hit[np.repeat(np.arange(rows), np.diff(lay.indptr))[lay.indices == cols // 2]] = True
+    assert np.array_equal(torch.isfinite(Yd).all(dim=1).cpu().numpy(), ~hit)
+    L.close()
+
+
 def test_power_law_rows_staged_and_ordinary_kernels_together(nb, torch_mod, oracle):
     """The same split on an operand small enough to stay untiled (600 rows x 1024 columns): without column tiles the
     packed path does not run, so the short rows of the forward product go through the wide kernel on a partition of
