@@ -36,9 +36,11 @@ struct WaveTask {
 };
 // One 16-byte scalar load per wave: the partition table is spelled out per wave when the
 // pattern is bound, so nothing about the row has to be looked up before its entries are fetched.
+// W: waves of the work-group, fewer than the partition's where they share nothing.
+template <int W = kWavesPerBlock>
 __device__ __forceinline__ WaveTask wave_task(const RowBlocks &b, int block)
 {
-    const int4 d = b.waves[block * kWavesPerBlock + wave_in_block()];
+    const int4 d = b.waves[block * W + wave_in_block()];
     WaveTask t;
     t.row = d.x;
     t.s0 = d.y;
@@ -1198,7 +1200,7 @@ __device__ __forceinline__ float sddmm_own_columns(gmem_ptr Xg, int iters, int m
 
 // col0: first column of the pass, which covers G*4*NV columns of the batch.  HELD: the wave's task and its row of dZ (without
 // the columns that are not the lanes' own) are there already.
-template <int G, int NV, bool SPARE, bool HELD = false>
+template <int G, int NV, bool SPARE, bool HELD = false, int W = kWavesPerBlock>
 __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, const int col0 = 0, const WaveTask *held_task = nullptr,
                                            const float4 *held_dz = nullptr)
 {
@@ -1208,7 +1210,7 @@ __device__ __forceinline__ void sddmm_body(const SddmmArgs &a, const int block, 
     if constexpr (!HELD) mean_loss_task(a, block);
     WaveTask task;
     if constexpr (HELD) task = *held_task;
-    else task = wave_task(a.blocks, block);
+    else task = wave_task<W>(a.blocks, block);
     if (task.row < 0) return;
     const int row = task.row;
     const int grp = lane / G;
@@ -1319,10 +1321,13 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 // G*4*NV; a work-group computes the partial products of its rows over one tile and stores them (and the partial row
 // sums of dZ) in the tile's slice of the partial buffer.  Tiles go to the XCDs as in spmm_tiled_kernel, so that an operand
 // tile stays in one L2 while every entry gathers from it.
+// In work-groups of four waves, a quarter of one of the partition's (nothing is shared among them; see spmm_packed_only_kernel): of 16 / of 4 waves, weight gradients of 12000 x 5000 power-law at 0.5 %,
+// batch 300 / 450 / 700 30.0 / 30.4, 52.5 / 47.3, 74.8 / 66.2 us; 5000^2 at 1.2 % 28.0 / 28.0, 40.1 / 37.0, 56.0 / 51.1; 8192 x 3072 at 1.3 %, batch 700 / 1024 56.7 / 53.8, 68.3 / 67.1.
+constexpr int kSddmmWaves = 4, kSddmmParts = kWavesPerBlock / kSddmmWaves;
 template <int G, int NV, bool SPARE>
-__global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order)
+__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order)
 {
-    const int nrb = a.blocks.n_blocks;
+    const int nrb = a.blocks.n_blocks * kSddmmParts;
     int tile, rb;
     if (!tile_of_block(n_tiles, nrb, order, tile, rb)) return;
     SddmmArgs t = a;
@@ -1330,7 +1335,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_tiled_kernel(const SddmmArgs a, 
     t.g = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
     t.db = t.g + a.partial_db_at;
     if (tile != 0) t.loss_cols = nullptr;
-    sddmm_body<G, NV, SPARE>(t, rb, tile * (G * 4 * NV));
+    sddmm_body<G, NV, SPARE, false, kSddmmWaves>(t, rb, tile * (G * 4 * NV));
 }
 
 // ---- staged SDDMM --------------------------------------------------------------------------
@@ -2952,11 +2957,12 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
 {
     const int W = G * 4 * NV;
     const int n_tiles = (a.batch + W - 1) / W;
-    const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, W / 4, false, tiled_launch(a));
-    const int64_t ids = tile_grid(order, n_tiles, a.blocks.n_blocks);
+    const int n_blocks = a.blocks.n_blocks * kSddmmParts;
+    const TileOrder order = tile_order(n_tiles, n_blocks, W / 4, false, tiled_launch(a));
+    const int64_t ids = tile_grid(order, n_tiles, n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
     with_spare(a.batch, W, [&](auto spare) {
-        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a, n_tiles, order);
+        hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kSddmmWaves * kWave), 0, s, a, n_tiles, order);
     });
     sddmm_finish_go(a, n_tiles, s);
     return hipGetLastError();
@@ -3594,10 +3600,11 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
             TiledLaunch like = tiled_launch(a);
             like.longest_row = 0;   // (none of the rest is long)
-            const TileOrder order = tile_order(n_tiles, rest.blocks.n_blocks, kStageCols / 4, false, like);
-            const int64_t ids = tile_grid(order, n_tiles, rest.blocks.n_blocks);
+            const int n_blocks = rest.blocks.n_blocks * kSddmmParts;
+            const TileOrder order = tile_order(n_tiles, n_blocks, kStageCols / 4, false, like);
+            const int64_t ids = tile_grid(order, n_tiles, n_blocks);
             with_spare(a.batch, kStageCols, [&](auto spare) {
-                hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1, decltype(spare)::value>), dim3(static_cast<unsigned>(ids)), dim3(kBlock), 0, s, rest, n_tiles,
+                hipLaunchKernelGGL((sddmm_tiled_kernel<16, 1, decltype(spare)::value>), dim3(static_cast<unsigned>(ids)), dim3(kSddmmWaves * kWave), 0, s, rest, n_tiles,
                                    order);
             });
         }
