@@ -2874,12 +2874,13 @@ bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t
 // 3894 x 6816 at 0.6 %, batch 227 15.9 -> 11.8; 16384^2 at 0.3 %, batch 300 103 -> 61; 10442 x 13851 at 0.37 %, batch 164 38.8 -> 27.9.  But tiles a fifth empty or more: 10681 x 8704 at 0.8 %, batch 134
 // 36.5 -> 42.3, 11466 x 5888 at 0.5 %, batch 263 30.2 -> 34.0; operands near an L2: 4545 x 5628 at 0.7 %, batch 189 13.1 -> 14.1; often gathered: 16000 x 5000 at 0.8 %, batch 200 29.0 -> 31.2,
 // 3182 x 2692 at 1.9 %, batch 580 25.7 -> 28.3; rarely: 3428 x 12999 at 0.33 %, batch 290 25.3 -> 26.7.
+// (More work than kFusedMinWork whatever the shape: in a training step such a transposed product shares its gathers, and is in no other launch's grid, which would add in another order.)
 static bool packed_tiles_pay(const SpmmArgs &a)
 {
     if (a.batch <= 128 || a.XM || a.blocks.n_short != a.rows || a.blocks.hot_share >= 0.5f) return false;
     if (static_cast<int64_t>(a.blocks.staged_longest_row) * a.rows > 4ll * a.nnz || (a.batch + 63) / 64 * 320 > 6 * a.batch) return false;
     const int64_t row_bytes = static_cast<int64_t>(a.x_rows) * 4, operand = row_bytes * a.batch, most = operand >= (11ll << 20) ? 90 : 55;
-    return operand >= (21ll << 18) && row_bytes * 64 <= (4ll << 20) && a.nnz >= 28ll * a.rows && a.nnz >= 12ll * a.x_rows && a.nnz <= most * a.x_rows &&
+    return operand >= (21ll << 18) && row_bytes * 64 <= (4ll << 20) && a.nnz >= 28ll * a.rows && a.nnz >= 13ll * a.x_rows && a.nnz <= most * a.x_rows &&
            packed_grid(a, 16, true).ids <= kMaxGridIds;
 }
 
