@@ -877,25 +877,19 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &
 template <int I>
 __device__ __forceinline__ int row_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x150 + I, 0xF, 0xF, true); }
 // acc += w of the row's lane I times x, the move of w in the multiply-add itself (the compiler makes it an instruction of its own, one in six of
-// a step).  FIRST: w may have been written by the instruction before, and such an operand is only there two cycles later.
-template <int I, bool FIRST>
+// a step).  Such an operand is only there two cycles after it is written, the compiler sees to that in its own instructions alone, and nothing keeps it from writing w
+// (a copy, a reload) right before any step: each waits for itself.  Against one wait per run of steps: forward products of 16384^2 power-law at 10 %, batch 1024 1223 -> 1229 us, uniform at 10 %,
+// batch 512 891 -> 914, 8192^2 at 1.95 / 5 %, batch 1024 171 -> 173, 278 -> 285; two steps of one wait 1290, 936, 193, 304, as each then waits for two gathers.
+template <int I>
 __device__ __forceinline__ void fma_row_lane(float4 &acc, float w, const float4 &x)
 {
-    if constexpr (FIRST)
-        asm("s_nop 1\n\t"
-            "v_fmac_f32_dpp %0, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %2, %4, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %3, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-            : "+&v"(acc.x), "+&v"(acc.y), "+&v"(acc.z), "+&v"(acc.w)
-            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(I));
-    else
-        asm("v_fmac_f32_dpp %0, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %2, %4, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %3, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-            : "+&v"(acc.x), "+&v"(acc.y), "+&v"(acc.z), "+&v"(acc.w)
-            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(I));
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %4, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+&v"(acc.x), "+&v"(acc.y), "+&v"(acc.z), "+&v"(acc.w)
+        : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(I));
 }
 // Entries B .. B + N - 1 of every lane row, in that order, out of the 16 that its lanes hold as (LDS byte offset, weight): four gathers
 // ahead of the one whose products are added.
@@ -913,7 +907,7 @@ __device__ __forceinline__ void staged_steps(const char *lds, int off, float w, 
     static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
         constexpr int i = decltype(ic)::value;
         if constexpr (i + kAhead < N) gather(std::integral_constant<int, i + kAhead>{});
-        fma_row_lane<B + i, i == 0>(acc, w, x[i]);  // (in this order: each adds to acc)
+        fma_row_lane<B + i>(acc, w, x[i]);  // (in this order: each adds to acc)
         if constexpr (i + kAhead < N) __builtin_amdgcn_sched_barrier(0);
     });
 }

@@ -37,6 +37,21 @@ def test_library_is_newer_than_its_sources(nb):
     assert not stale, f"rebuild the library: {stale} changed after it was built"
 
 
+def test_lane_moves_in_asm_wait_for_their_operand():
+    """An operand moved between lanes is there two cycles after it is written, and the compiler may write one right before any asm statement
+    that names it: every statement with such moves begins with the wait."""
+    csrc = os.path.join(ROOT, "paper_2407_17437_amd", "csrc")
+    source = "".join(open(os.path.join(csrc, f)).read() for f in sorted(os.listdir(csrc)))
+    moves = set(re.findall(r'#define (\w+)\([^)]*\) "v_\w+_dpp', source))   # (macros of one instruction)
+    found = 0
+    for at in re.finditer(r"\basm\s*(?:volatile\s*)?\(", source):
+        body = source[at.end():source.index(";", at.end())]
+        if "_dpp" in body or any(m in body for m in moves):
+            found += 1
+            assert re.match(r'\s*"s_nop 1\\n\\t"', body), source[at.start():at.start() + 200]
+    assert found >= 5
+
+
 def test_package_works_without_the_compiled_call_layer(nb):
     """Importing it blocked, and every call that it makes against the same call through ctypes, argument by argument."""
     import subprocess, sys
