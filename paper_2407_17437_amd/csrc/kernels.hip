@@ -2863,6 +2863,15 @@ bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t
     return nnz >= segment * rows * blocks.staged_cblocks;
 }
 
+// Entries times columns for the rules of shorter segments: of the rows that the plan covers, which beside dense rows (DenseSplit) or in a plan of the long rows are a part of the matrix
+// (weight gradient of 5000^2 power-law at 10 %, batch 256, 640 M in all, 186 M staged: 78 us in column tiles, 103 staged), and none where copying the operand weighs
+// too much beside them (column tiles / staged, entries per copied row: products of 7278 x 12626 and 8772 x 13004, batch 256 97 / 102 us (2.2), 101 / 106 (2.3), 6024 x 14996, batch 384 171 / 125 (2.6);
+// gradients of 5901 x 11786, batch 192 93 / 104 (2.3), 4665 x 10700, batch 320 100 / 97 (2.6)).
+static int64_t staged_work(const RowBlocks &blocks, int32_t x_rows, int32_t batch)
+{
+    return blocks.staged_nnz * 2ll >= 5ll * blocks.staged_ranges * x_rows ? static_cast<int64_t>(blocks.staged_nnz) * batch : 0;
+}
+
 // Short even rows in 64-column tiles for the sake of the packed kernel and its small work-groups, where the rule of the tiles (tile_columns) leaves the operand whole: one beyond an
 // L2 whose rows are gathered a dozen times or more (and not so often that it stays in cache), tiles hardly empty.  Uniform rows, whole -> in tiles, us: 15997 x 15191 at 0.35 %, batch 372 126 -> 79;
 // 3894 x 6816 at 0.6 %, batch 227 15.9 -> 11.8; 16384^2 at 0.3 %, batch 300 103 -> 61; 10442 x 13851 at 0.37 %, batch 164 38.8 -> 27.9.  But tiles a fifth empty or more: 10681 x 8704 at 0.8 %, batch 134
@@ -2906,7 +2915,7 @@ int spmm_split_group(const SpmmArgs &a)
 bool spmm_staged_ok(const SpmmArgs &a)
 {
     if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (it brings 64 operand rows at a time, and reads entries at 32-bit byte offsets, 32 past the first)
-    if (!staged_pays(a.blocks, a.x_rows, a.batch, static_cast<int64_t>(a.nnz) * a.batch >= kStageSomeWork ? kStageSegmentSomeWork : kStageLongSegment)) return false;
+    if (!staged_pays(a.blocks, a.x_rows, a.batch, staged_work(a.blocks, a.x_rows, a.batch) >= kStageSomeWork ? kStageSegmentSomeWork : kStageLongSegment)) return false;
     return !a.blocks.staged_partial || a.blocks.n_rest_blocks > 0;  // (the rows the plan leaves out need a partition of their own)
 }
 
@@ -2932,7 +2941,9 @@ bool sddmm_staged_ok(const SddmmArgs &a)
     if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     if ((a.batch + kStageCols - 1) / kStageCols > a.partial_tiles) return false;
     if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (as spmm_staged_ok)
-    return staged_pays(a.blocks, a.x_rows, a.batch, a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : static_cast<int64_t>(a.nnz) * a.batch >= kStageMuchWork ? kStageSegmentMuchWork : kStageLongSegmentSddmm) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
+    const int64_t work = staged_work(a.blocks, a.x_rows, a.batch);
+    const int32_t segment = a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : work >= kStageMuchWork ? kStageSegmentMuchWork : kStageLongSegmentSddmm;
+    return staged_pays(a.blocks, a.x_rows, a.batch, segment) && (!a.blocks.staged_partial || a.blocks.n_rest_blocks > 0);
 }
 
 bool spmm_offsets_ok(const SpmmArgs &a)

@@ -269,7 +269,30 @@ def few_column_tiles_serve_where_they_pay(L):
         L.destroy()
 
 
-CASES = [few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def short_segments_are_staged_by_the_work_of_the_plan(L):
+    """Beside dense rows the plan covers a part of the matrix, and its entries, not the matrix's, are the work that shorter segments take; neither do
+    they pay where copying the operand weighs more than serving them."""
+    for rows, cols, nnz, n_dense, dense_nnz, plan, batch, product, gradient in (
+            (5000, 5000, 2500000, 600, 1700000, (64, 4000, 726000), 256, True, False),       # segments of 18, 186 M of 640 M entries times columns
+            (5000, 5000, 3600000, 600, 1700000, (64, 9000, 1730000), 256, True, True),       # of 19, 443 M
+            (16384, 5000, 2500000, 600, 1700000, (64, 8000, 726000), 256, False, False),     # of 9, 186 M
+            (16384, 5000, 3900000, 600, 1700000, (64, 15000, 1350000), 256, True, False),    # of 9, 346 M
+            (7278, 12626, 1788000, 0, 0, (64, 7278, 1788000), 256, False, False),            # of 9.8, 458 M, 2.2 entries per copied row
+            (7278, 12626, 1788000, 0, 0, (56, 7278, 1788000), 256, True, False)):            # 2.53
+        L.counts(0, n_blocks=600, n_dense=n_dense, dense_nnz=dense_nnz, longest_row=300, staged_ranges=plan[0], staged_rows=plan[1], staged_nnz=plan[2])
+        L.counts(1, n_blocks=600, longest_row=2000)
+        assert L.create(rows, cols, nnz, batch) == 0
+        L.launched()
+        assert L.forward(batch) == 0
+        launched = L.launched()
+        assert any("dense_rows" in k for k in launched) == (n_dense > 0)
+        assert any("spmm_staged_kernel" in k for k in launched) == product, (rows, cols, plan, launched)
+        assert L.backward(batch, dx=False) == 0
+        assert any("sddmm_staged_kernel" in k for k in L.launched()) == gradient, (rows, cols, plan)
+        L.destroy()
+
+
+CASES = [short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
