@@ -919,25 +919,26 @@ static DenseRowsCut dense_rows_cut(int32_t n, int32_t cols, int32_t batch, const
     return split.tiles > 0 && split.time < 4. + 1.25 * fp32.time && operand_parts_ints(cols, batch) < kPartsMaxInts ? split : fp32;
 }
 
-// What gathering for a thin matrix (kThinDensity) takes, us.  Staged (as staged_pays has it): 0.95 ns an entry of a work-group's range and
-// column tile, one work-group a compute unit, which copies its tile of the operand into LDS at 32 GB/s; else about 25 TB/s of gathers.  Within 10 % of 250
-// products of uniform matrices of 17 to 28 % with 600 to 16384 rows, each bound for the batch.
+// What gathering for a thin matrix (kThinDensity) takes, us.  Staged (as staged_pays has it): 0.84 ns an entry of a work-group's range and
+// column tile, one work-group a compute unit, which copies its tile of the operand into LDS beside that at 57 GB/s; else about 25 TB/s of gathers.  Within 3 % (root mean square; 8 at most) of 139
+// staged products of uniform matrices of 17 to 30 % with 600 to 16384 rows, each bound for the batch; within 10 % of most of 31 gathered ones (2600 x 16384 at 28 %, batch 256 takes 651 for 489).
 static double thin_rows_gathered(const DenseSplit &d, int32_t cols, int32_t batch)
 {
     const int64_t tiles = (static_cast<int64_t>(batch) + kStageCols - 1) / kStageCols, ranges = staged_ranges_aim(d.rows.n, d.max_batch), groups = tiles * ranges;
     if (static_cast<int64_t>(batch) * 5 < tiles * kStageCols * 4 || groups < kStageTargetGroups * 3 / 4) return static_cast<double>(d.thin_nnz) * batch * 4. / 25e6;
-    return 5. + static_cast<double>((groups + kStageTargetGroups - 1) / kStageTargetGroups) * (0.95e-3 * static_cast<double>(d.thin_nnz) / static_cast<double>(ranges) + 8e-3 * cols);
+    return 7.5 + static_cast<double>((groups + kStageTargetGroups - 1) / kStageTargetGroups) * (0.84e-3 * static_cast<double>(d.thin_nnz) / static_cast<double>(ranges) + 4.5e-3 * cols);
 }
 
-// It goes to the bf16 units where they take less.  Start of each range of 256 columns against its end, gathered / split, us: 9019 x 2137 at
-// 26 %, batch 257 / 512: 122 / 161, 180 / 154; 8192 x 4096 at 20 %: 165 / 215, 251 / 219; at 513 / 1024: 270 / 335, 486 / 400; 2600 x 16384 at 20 %, batch
-// 256 / 512 / 1024: 356 / 156, 386 / 291, 605 / 537; 3000 x 6000 at 18 %: 136 / 75, 145 / 137, 244 / 257.  (The fp32 units lose: 20 % of 4096^2 at batch 1024 235 / 326.)
+// It goes to the bf16 units where they take less; their estimate is 4 to 8 % above what these matrices take.  Gathered / split, us: 8192 x 4096 at 20 %, batch 256 / 512 / 520 / 1024:
+// 115 / 110, 205 / 201, 221 / 305, 408 / 380, at 24 %, batch 320 / 640 155 / 196, 295 / 310; 9019 x 2137 at 28 %, batch 256 / 1024 86 / 79, 317 / 296, at 24 %, batch 640 167 / 190;
+// 2600 x 16384 at 20 %, batch 256 / 512 / 1024: 353 / 142, 306 / 267, 506 / 510; 3000 x 6000: 147 / 71, 123 / 123, 227 / 237; 2050 x 2100 at 28 %, batch 512 / 600 51 / 48, 58 / 59.
+// (The fp32 units lose: 20 % of 4096^2 at batch 1024 235 / 326.)
 static bool thin_rows_pay(const DenseSplit &d, int32_t cols, int32_t batch)
 {
     if (batch < kThinBatch || d.thin_nnz * batch < kThinWork) return false;
     const DenseRowsCut cut = dense_rows_split_cut(d.rows.n, cols, batch);
     return cut.tiles > 0 && operand_parts_ints(cols, batch) <= d.rows.parts_ints &&
-           (cut.slices == 1 || static_cast<int64_t>(cut.slices) * d.rows.n * dense_rows_ld(batch) <= d.rows.partial_floats) && cut.time * 1.05 < thin_rows_gathered(d, cols, batch);
+           (cut.slices == 1 || static_cast<int64_t>(cut.slices) * d.rows.n * dense_rows_ld(batch) <= d.rows.partial_floats) && cut.time * 0.92 < thin_rows_gathered(d, cols, batch);
 }
 
 bool thin_rows_pay_somewhere(const DenseSplit &d, int32_t cols)

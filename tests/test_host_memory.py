@@ -151,6 +151,7 @@ def a_thin_matrix_takes_the_bf16_units_where_they_pay(L):
     for rows, cols, density, max_batch, batch, split in (
             (9019, 2137, 0.26, 288, 288, False), (9019, 2137, 0.26, 768, 768, True), (873, 11642, 0.27, 270, 270, True), (8192, 4096, 0.2, 257, 257, False),
             (8192, 4096, 0.2, 512, 512, True), (8192, 4096, 0.2, 1024, 1024, True), (8192, 4096, 0.2, 1024, 520, True), (8192, 4096, 0.2, 520, 520, False), (2600, 16384, 0.2, 256, 256, True),
+            (2600, 16384, 0.175, 320, 320, False), (3935, 8046, 0.2243, 384, 384, False), (2916, 2321, 0.2311, 500, 500, False), (1000, 8000, 0.175, 320, 320, True),
             (2050, 2100, 0.278, 600, 600, True), (2050, 2100, 0.278, 600, 300, False), (2050, 2100, 0.2, 470, 470, False), (600, 38138, 0.25, 10474, 10474, False), (600, 38138, 0.25, 10474, 1024, True)):
         L.launched()
         assert bound(rows, cols, density, max_batch) == 0
