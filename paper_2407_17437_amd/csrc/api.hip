@@ -958,6 +958,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         const DenseRowsRoom want = dense_rows_room(D.n, cols, max_batch, false);
         if (!reserve_dense_rows(B, want) && want.parts_ints > 0) (void)reserve_dense_rows(B, DenseRowsRoom{want.partial_floats, 0});
         B.split.from_batch = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? kDenseRowsMinBatch : dense_rows_from(R.plan[0].dense_nnz);
+        B.split.dense_nnz = R.plan[0].dense_nnz;
         B.split.flag = t.dense_flag;
         B.split.others = out->plan;
         B.split.others.waves = t.other_waves;

@@ -97,6 +97,7 @@ struct DenseRows {
 struct DenseSplit {
     DenseRows rows;                // n = 0: there are none, or too few
     int32_t from_batch;
+    int64_t dense_nnz;             // the listed rows' stored entries
     int64_t thin_nnz;              // all rows of a matrix of kThinDensity: its stored entries, or 0; then also
     int32_t max_batch;             // what it is bound for
     const uint8_t *flag;           // [rows of the matrix] 1: a dense row

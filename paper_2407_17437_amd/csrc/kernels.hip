@@ -3262,27 +3262,50 @@ bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &)
 // which the pass pays there (steps of 3072-1024-512-10 at 10 %, batch 100, 5 M in the middle layer: 38.6 -> 42.5 us with it;
 // 2000-4000-3000-10 at 3 %, batch 128, 46 M: 72.4 -> 70.2; three layers of 3000 at 5 %, batch 100: 128 -> 116).
 constexpr int64_t kFusedMinWork = 16 << 20;
-// Both products staged through LDS against one stream of L2 gathers for both: apart they gather twice, from LDS at up to three times the rate.
-// What decides is the length of the mirror's segments, less of it where dZ is beyond the L2s and the stream is slow.  Both gradients, us, one stream / apart:
-// uniform 16384^2 at 3 / 5 / 10 %, batch 1024 1994 / 1830, 3246 / 2596, 6435 / 4595, at 2 / 5 / 8 %, batch 300 478 / 700, 1288 / 1008, 2271 / 1516; 11000^2 at 4.5 %, batch 256 / 448 /
-// 1024 375 / 381, 612 / 562, 1277 / 1060; 8192^2 at 5 / 10 %, batch 256 221 / 262, 416 / 411, batch 1024 671 / 721, 1292 / 1152; 6000 x 16384 at 6.5 %, batch 256 / 448 / 700 395 / 426, 657 / 664,
-// 932 / 856, at 9 % 557 / 537, 918 / 833, 1270 / 1084; power-law 16384^2 at 3 / 6 / 10 %, batch 384 710 / 740, 1503 / 1158, 3099 / 1801; of 3000 rows or columns never (12000 x 3000 at 6 %, batch 512 277 / 281).
-// In a training step the stream also has the updates to strew over values and velocity, which the SDDMM's second pass finds in order: steps of 3072-8192-8192-10 at 3 / 6 %, batch 256
-// 365 / 365 and 625 / 535, batch 1024 930 / 1082 and 1609 / 1466; 2000-5000-4000-100 at 6 %, batch 256 / 512 223 / 250 and 360 / 350.
+// The transposed product staged through LDS and the gradient apart from it (staged too, or by matrix instructions sampled on the pattern) against one stream of L2 gathers for both: apart they read
+// the operands twice, from LDS at up to three times the rate, and copy them there.  Which is faster goes by estimates of both, us.  A staged launch takes rounds of a work-group per compute unit,
+// each a range's entries and the copy of its operand tile; the stream its gathers (more of them miss where dZ has many rows), and the strewing of results through the position map,
+// whose share grows with the entries.  Root mean square from what was measured, apart / stream, batch 128 to 1024: 4 / 4 % on 330 uniform layers of 1500 to 16384 rows and columns, 3 to 15 %; 3 / 5 %
+// on 94 power-law ones, where the staged gradient has the rows that are not dense, and the stream finds the operand rows of the dense ones in cache; 3 / 6 % on 75 of 15 to 40 % with a sampled gradient.
+// One stream -> apart: 12000 x 11500 at 7 %, batch 900 2103 -> 1677; 14000 x 6800 at 12 %, batch 640 1693 -> 1228; 9877 x 13217 at 9 %, batch 192 636 -> 545; 16384^2 at 5 / 10 %, batch 1024 3246 -> 2596,
+// 6435 -> 4595; power-law 14000 x 2800 at 12 %, batch 768 825 -> 593; 1896 x 8041 at 33 %, batch 300 360 -> 225; but 3336 x 14187 at 9 %, batch 640 483 -> 546, 6300 x 10100 at 9 %, batch 256 306 -> 334, power-law
+// 11600 x 4700 at 5 %, batch 512 310 -> 346.  Far from the estimates: segments shorter than those fitted (16384^2 at 2 %, batch 300 478 -> 700), little work (1525 x 1453 at 15 %, batch 900 69 -> 89,
+// 551 x 3748 at 31 %, batch 256 38 -> 46; steps of 604-1571-1495-10 at 8 %, batch 700 117 -> 129, 393-2977-692-10 at 17 %, batch 300 104 -> 110), and the stream of a mirror of few rows (11458 x 1073 at 8 %, batch 1024 198 -> 222).
+// In a training step the stream has the updates to strew over values and velocity as well, which the gradient's second pass finds in order: steps of 1245-6435-6257-10 at 14 %, batch 320
+// 732 -> 581, 1028-7029-8177-10 at 8 %, batch 900 1264 -> 1174, 1000-2917-7772-10 at 24 %, batch 160 564 -> 423, but with 5291 x 6610 at 3 %, batch 640 382 -> 407; with dense rows much of the
+// gradient goes by matrix instructions, and apart it stays.
+static double staged_launch_time(const RowBlocks &blocks, int64_t nnz, int32_t x_rows, int32_t batch)
+{
+    const int64_t groups = (static_cast<int64_t>(batch) + kStageCols - 1) / kStageCols * blocks.staged_ranges;
+    const double rounds = static_cast<double>((groups + kStageTargetGroups - 1) / kStageTargetGroups);
+    return rounds * (1.12e-3 * static_cast<double>(nnz) / blocks.staged_ranges + 5.9e-3 * x_rows);
+}
 static bool backward_apart_pays(const SpmmArgs &t, const SddmmArgs &g, bool alone)
 {
     if (!spmm_staged_ok(t)) return false;
+    const bool sampled = sddmm_sampled_ok(g), split = !sampled && sddmm_dense_rows_ok(g);
     SddmmArgs others = g;
-    if (sddmm_dense_rows_ok(g)) {
-        if (!alone) return true;   // (much of the gradient by matrix instructions)
+    if (split) {
+        if (!alone) return true;
         others.blocks = g.split->others; others.split = nullptr; others.split_done = g.split;
     }
-    if (!sddmm_staged_ok(others)) return false;
-    const int64_t segments = static_cast<int64_t>(t.rows) * t.blocks.staged_cblocks, work = static_cast<int64_t>(t.nnz) * t.batch;
-    if (!alone) return work >= 560'000'000 && t.nnz >= 20 * segments;
-    if (t.rows < 4096) return false;
-    if (t.x_rows >= 10000 && static_cast<int64_t>(t.x_rows) * t.batch * 4 >= (18ll << 20) && t.nnz >= 22 * segments) return true;
-    return work >= 1'400'000'000 && t.nnz >= (t.batch >= 384 || t.x_rows >= 10000 ? 32 : 44) * segments;
+    if (!sampled && !sddmm_staged_ok(others)) return false;
+    const int64_t work = static_cast<int64_t>(t.nnz) * t.batch, least = sampled ? (alone ? 300'000'000 : 120'000'000) : alone ? 600'000'000 : 400'000'000;
+    if (work < least || t.nnz < 20ll * t.rows * t.blocks.staged_cblocks) return false;
+    const int tg = backward_tile_group(t);
+    const double million = t.nnz * 1e-6, gathers = million * backward_tiles(t, tg) * tg * 4., full = static_cast<double>(g.x_rows) * g.batch;   // (tiles: of 128 columns, or of fewer)
+    double stream = 1.15 * million * std::min(million, 30.) + (alone ? 0. : 12. * million), apart = staged_launch_time(t.blocks, t.nnz, t.x_rows, t.batch);
+    if (split) {
+        const double other = static_cast<double>(t.nnz - g.split->dense_nnz);
+        stream += 28. + gathers * (tg >= 32 ? 0.141 + 0.020 / 8192 * t.x_rows : 0.179);
+        apart += 13. + staged_launch_time(others.blocks, others.blocks.staged_nnz, g.x_rows, g.batch) + 9.7e-9 * g.split->rows.n * full + 43e-6 * other +
+                 196e-9 * (other - others.blocks.staged_nnz) * g.batch;
+    } else {
+        stream += 23. + gathers * (tg >= 32 ? 0.152 + 0.019 / 8192 * t.x_rows : 0.182 + 0.040 / 16384 * t.x_rows);
+        if (sampled) apart = 22.5 + 0.69 * apart + 18.4e-9 * g.rows * full + 7.5 * million;
+        else apart += 4. + staged_launch_time(others.blocks, t.nnz, g.x_rows, g.batch) + 5.5 * million;
+    }
+    return apart < (!alone ? (sampled ? 1.03 : 0.96) : split ? 0.98 : t.rows < 2048 ? 0.93 : sampled ? 1.03 : 1.) * stream;
 }
 bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
 {

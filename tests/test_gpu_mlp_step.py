@@ -112,10 +112,19 @@ def test_stage_parity_small(nb, torch_mod, oracle, sizes, kw, batch, steps, unfu
     M.close()
 
 
+def _launch_names(nb, torch, M, X, labels, batch):
+    nb.mlp_profile_enable(M.handle, 1)
+    M.train_step(nb.to_dense(X), torch.as_tensor(labels).cuda(), batch, 0.0, 0.0)
+    torch.cuda.synchronize()
+    names = [n for n, _ in nb.mlp_profile_read(M.handle)[1]]
+    nb.mlp_profile_enable(M.handle, 0)
+    return names
+
+
 def test_stage_parity_staged_products(nb, torch_mod, oracle):
-    """A batch of 512 on layers with ~200 entries per row: the forward products of both hidden layers and the
-    transposed product of the second (with the ReLU mask of the first applied as it is stored) take the
-    staged kernel; two steps, so that the second uses weights and mirror values the first one updated."""
+    """A batch of 512 on layers with ~200 entries per row: the forward products of both hidden layers take the staged kernel; both
+    gradients of the second (215 M entries times columns) take one stream of gathers, with the ReLU mask of the first applied as its
+    result is stored; two steps, so that the second uses weights and mirror values the first one updated."""
     torch = torch_mod
     sizes, batch = (600, 2048, 2048, 10), 512
     mlp = wl.make_mlp(sizes, sparsity=0.9, bias_std=0.1, pattern_seed=101, value_seed=201)
@@ -129,6 +138,26 @@ def test_stage_parity_staged_products(nb, torch_mod, oracle):
         M.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
         torch.cuda.synchronize()
         stage_parity(nb, torch, oracle, M, mlp, before, Xs[t], Ts[t], batch, 0.05, 0.9, False)
+    assert "backward_fused[1]" in _launch_names(nb, torch, M, Xs[0], Ts[0], batch)
+    M.close()
+
+
+@pytest.mark.parametrize("hidden,sparsity", [((2600, 2600), 0.855), ((1800, 1300), 0.72)])
+def test_stage_parity_staged_gradients(nb, torch_mod, oracle, hidden, sparsity):
+    """A hidden layer in segments of 70 and 120 whose transposed product (with the ReLU mask of the layer below applied as it is stored) is staged, and
+    whose SDDMM + update is staged too (439 M entries times columns) or goes by matrix instructions; two steps, every stage against the oracle, the launches by name."""
+    torch = torch_mod
+    sizes, batch = (200, *hidden, 10), 448
+    mlp = wl.make_mlp(sizes, sparsity=sparsity, bias_std=0.1, pattern_seed=103, value_seed=203)
+    Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 2, seed=303)
+    M = nb.MLP(mlp, batch)
+    for t in range(2):
+        before = snapshot(M)
+        M.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
+        torch.cuda.synchronize()
+        stage_parity(nb, torch, oracle, M, mlp, before, Xs[t], Ts[t], batch, 0.05, 0.9, False)
+    names = _launch_names(nb, torch, M, Xs[0], Ts[0], batch)
+    assert "spmm_transposed[1]" in names and "sddmm_update[1]" in names and "backward_fused[1]" not in names, names
     M.close()
 
 

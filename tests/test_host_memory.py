@@ -293,7 +293,36 @@ def short_segments_are_staged_by_the_work_of_the_plan(L):
         L.destroy()
 
 
-CASES = [short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def both_gradients_go_apart_where_that_is_faster(L):
+    """rows, columns, entries, batch, ranges of W's plan and of its mirror's; dense rows, their entries, rows and entries of the plan beside them.  As measured,
+    us, on one stream of gathers and apart (with the mirror's values ahead)."""
+    for rows, cols, nnz, batch, ranges, dense, apart in (
+            (9877, 13217, 11592349, 192, (85, 85), None, True),      # 636 / 545
+            (7626, 7351, 5448993, 640, (25, 25), None, True),        # 647 / 598
+            (13983, 2818, 4562994, 768, (21, 21), (2648, 3245624, 3477, 718494), True),    # 825 / 593
+            (14473, 2876, 3000000, 1024, (48, 16), None, True),
+            (1896, 8041, 5070586, 300, (29, 51), None, True),        # 360 / 225, the gradient by matrix instructions
+            (2064, 1450, 459694, 640, (25, 22), None, False),        # 68 / 83, as well
+            (3336, 14187, 4368363, 640, (25, 51), None, False),      # 483 / 546
+            (6304, 10132, 5812395, 256, (64, 64), None, False),      # 306 / 334
+            (11649, 4703, 2969360, 512, (32, 32), (925, 1891006, 2354, 606578), False),    # 310 / 346
+            (9535, 4605, 5576402, 256, (64, 64), (2012, 4030623, 4998, 1277028), False),   # 284 / 324
+            (11458, 1073, 944212, 1024, (32, 16), None, False),      # 198 / 222
+            (1525, 1453, 334363, 900, (17, 17), None, False)):       # 69 / 89: 301 M entries times columns
+        n_dense, dense_nnz, plan_rows, plan_nnz = dense or (0, 0, rows, nnz)
+        L.counts(0, n_blocks=600, n_dense=n_dense, dense_nnz=dense_nnz, longest_row=cols // 3, staged_ranges=ranges[0], staged_rows=plan_rows, staged_nnz=plan_nnz)
+        L.counts(1, n_blocks=600, longest_row=rows // 5, staged_ranges=ranges[1], staged_rows=cols, staged_nnz=nnz)
+        assert L.create(rows, cols, nnz, batch) == 0
+        L.launched()
+        assert L.backward(batch) == 0
+        names = L.launched()
+        assert any("backward_fused_kernel" in k for k in names) != apart, (rows, cols, batch, names)
+        gradient = "sampled_update_kernel" if nnz >= 0.15 * rows * cols else "sddmm_staged_kernel"
+        assert (any("spmm_staged_kernel" in k for k in names) and any(gradient in k for k in names)) == apart, (rows, cols, batch, names)
+        L.destroy()
+
+
+CASES = [both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
