@@ -3271,8 +3271,8 @@ constexpr int64_t kFusedMinWork = 16 << 20;
 // 6435 -> 4595; power-law 14000 x 2800 at 12 %, batch 768 825 -> 593; 1896 x 8041 at 33 %, batch 300 360 -> 225; but 3336 x 14187 at 9 %, batch 640 483 -> 546, 6300 x 10100 at 9 %, batch 256 306 -> 334, power-law
 // 11600 x 4700 at 5 %, batch 512 310 -> 346.  Far from the estimates: segments shorter than those fitted (16384^2 at 2 %, batch 300 478 -> 700), little work (1525 x 1453 at 15 %, batch 900 69 -> 89,
 // 551 x 3748 at 31 %, batch 256 38 -> 46; steps of 604-1571-1495-10 at 8 %, batch 700 117 -> 129, 393-2977-692-10 at 17 %, batch 300 104 -> 110), and the stream of a mirror of few rows (11458 x 1073 at 8 %, batch 1024 198 -> 222).
-// In a training step the stream has the updates to strew over values and velocity as well, which the gradient's second pass finds in order: steps of 1245-6435-6257-10 at 14 %, batch 320
-// 732 -> 581, 1028-7029-8177-10 at 8 %, batch 900 1264 -> 1174, 1000-2917-7772-10 at 24 %, batch 160 564 -> 423, but with 5291 x 6610 at 3 %, batch 640 382 -> 407; with dense rows much of the
+// In a training step the stream has the updates to strew over values and velocity as well, which the gradient's second pass finds in order: steps of 802-6257-6435-10 at 14 %, batch 320
+// 732 -> 581, 751-8177-7029-10 at 8 %, batch 900 1264 -> 1174, 1055-7772-2917-10 at 24 %, batch 160 564 -> 423, but of 750-6610-5291-10 at 5 %, batch 640 382 -> 407; with dense rows much of the
 // gradient goes by matrix instructions, and apart it stays.
 static double staged_launch_time(const RowBlocks &blocks, int64_t nnz, int32_t x_rows, int32_t batch)
 {
