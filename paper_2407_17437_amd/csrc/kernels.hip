@@ -855,6 +855,7 @@ __global__ __launch_bounds__(kBlock) void full_rows_finish_softmax_kernel(const 
 // 1.5 times as fast), not either pipe.  Segments, masks and offsets worked out once per block and not per use, the rows brought ahead, no wait for memory among
 // the gathers, the weight's move in the multiply-add: 16384^2 power-law rows at 10 %, batch 1024, 1087 -> 740 us (10.3 -> 6.5 vector instructions a gather);
 // forward products of uniform 8192^2 at 5 %, batch 1024, 374 -> 278, 16384^2 at 2 %, batch 512, 448 -> 334, 5000 x 7000 at 8 %, batch 511, 146 -> 115.
+// (48 KB of code, the gradient's 56, the instruction cache 64.  Two registers are stored before the block loop and reloaded after it; with a mask four, two of them reloaded once a block.)
 // Slots dealt to the waves there and back change nothing, two runs of 8 gathers made one of 16 neither.  A row marked kStageQuad is
 // shared by the four lane rows of a wave, a quarter of each segment each, and their four results
 // are added in a fixed order before the store.  Every output element is summed in one order.
@@ -1030,7 +1031,10 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     const float *const my_x = a.X + static_cast<int64_t>(threadIdx.x >> 4) * a.ldx + col;
     const int last_block = max(a.x_rows - kStageRows, 0), last_rows = a.x_rows - 64;
     auto block_row = [&](int b) { return min(b * kStageRows, last_block); };
-    auto ask_rows = [&](int i, int cb0) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + i * 64, last_rows)) * a.ldx); };
+    // (Behind the last block there is nothing to ask for: the requests go to the first 64 rows, all of a slot to the same, and find them in the L1.  Asking for the last block again was a
+    // third pass over an operand of two blocks: forward products of 16384 x 300 / 1000 / 2000 at 8 %, batch 1024 47.4 -> 45.9, 112.6 -> 113.0, 199.8 -> 194.8 us, 8192^2 at 1.95 % 177.9 -> 172.6; a
+    // branch around them 2 % slower on short segments.  The gradient as before: 79 / 143 / 265 -> 79 / 145 / 265.)
+    auto ask_rows = [&](int i, int cb0, int last) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + i * 64, last)) * a.ldx); };
     auto put_rows = [&](int cb0) {
 #pragma unroll
         for (int i = 0; i < kShare; ++i) {
@@ -1044,9 +1048,9 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     int e2 = n_cb >= 2 ? ends[2 * kStageRangeRows] : e1;
     static_for(std::make_integer_sequence<int, kAheadJ>{}, [&](auto jc) { ask(jc, now); });
 #pragma unroll
-    for (int i = 0; i < kShare; ++i) ask_rows(i, 0);
+    for (int i = 0; i < kShare; ++i) ask_rows(i, 0, last_rows);
     for (int b = 0; b < n_cb; ++b) {
-        const int cb0 = block_row(b), cb_next = block_row(b + 1);
+        const int cb0 = block_row(b), cb_next = block_row(b + 1), last_next = b + 1 < n_cb ? last_rows : 0;
         const int e3 = ends[min(b + 3, n_cb) * kStageRangeRows];
         const StagedSegments next = staged_segments(e1, e2, my_quad, lrow);  // (empty behind the last block)
         lds_barrier();  // the previous block's gathers are done
@@ -1056,8 +1060,8 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
         static_for(all_j, [&](auto jc) {
             constexpr int j = decltype(jc)::value;
             if constexpr (j < kShare / 2) {   // (early: their way is long, and a range of few rows has no last slots)
-                ask_rows(2 * j, cb_next);
-                ask_rows(2 * j + 1, cb_next);
+                ask_rows(2 * j, cb_next, last_next);
+                ask_rows(2 * j + 1, cb_next, last_next);
             }
             if constexpr (j + kAheadJ < kStageJ) ask(std::integral_constant<int, j + kAheadJ>{}, now);
             else ask(std::integral_constant<int, j + kAheadJ - kStageJ>{}, next);
@@ -1477,7 +1481,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
     const float *const my_x = a.X + static_cast<int64_t>(threadIdx.x >> 4) * a.ldx + col;
     const int last_block = max(a.x_rows - kStageRows, 0), last_rows = a.x_rows - 64;
     auto block_row = [&](int b) { return min(b * kStageRows, last_block); };
-    auto ask_rows = [&](int i, int cb0) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + i * 64, last_rows)) * a.ldx); };
+    auto ask_rows = [&](int i, int cb0, int last) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + i * 64, last)) * a.ldx); };
     auto put_rows = [&](int cb0) {
 #pragma unroll
         for (int i = 0; i < kShare; ++i) {
@@ -1490,9 +1494,9 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
     int e2 = n_cb >= 2 ? ends[2 * kStageRangeRows] : e1;
     static_for(std::make_integer_sequence<int, kAheadJ>{}, [&](auto jc) { ask(jc, now); });
 #pragma unroll
-    for (int i = 0; i < kShare; ++i) ask_rows(i, 0);
+    for (int i = 0; i < kShare; ++i) ask_rows(i, 0, last_rows);
     for (int b = 0; b < n_cb; ++b) {
-        const int cb0 = block_row(b), cb_next = block_row(b + 1);
+        const int cb0 = block_row(b), cb_next = block_row(b + 1), last_next = b + 1 < n_cb ? last_rows : 0;
         const int e3 = ends[min(b + 3, n_cb) * kStageRangeRows];
         const StagedSegments next = staged_segments(e1, e2, my_quad, lrow);  // (empty behind the last block)
         lds_barrier();  // the previous block's gathers are done
@@ -1502,8 +1506,8 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
         static_for(all_j, [&](auto jc) {
             constexpr int j = decltype(jc)::value;
             if constexpr (j < kShare / 2) {
-                ask_rows(2 * j, cb_next);
-                ask_rows(2 * j + 1, cb_next);
+                ask_rows(2 * j, cb_next, last_next);
+                ask_rows(2 * j + 1, cb_next, last_next);
             }
             if constexpr (j + kAheadJ < kStageJ) ask(std::integral_constant<int, j + kAheadJ>{}, now);
             else ask(std::integral_constant<int, j + kAheadJ - kStageJ>{}, next);
