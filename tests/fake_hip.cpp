@@ -19,7 +19,7 @@ std::map<const void *, std::string> kernels;
 std::string launched;
 PlanCounts counts[2];
 long calls_until_failure = -1;   // of the calls that allocate, fill or wait
-int bad_pointers = 0, dirty_tickets = 0, mixed_tickets = 0;
+int bad_pointers = 0, bad_grids = 0, dirty_tickets = 0, mixed_tickets = 0;
 std::map<const int32_t *, int> ticket_ends;   // what each ticket of a shared tile counts up to
 size_t live_bytes = 0;
 hipError_t last = hipSuccess;
@@ -70,6 +70,7 @@ extern "C" {
 void fake_fail_after(long calls) { calls_until_failure = calls; }
 long fake_fail_after_left() { return calls_until_failure; }
 int fake_bad_pointers() { return bad_pointers; }
+int fake_bad_grids() { return bad_grids; }
 int fake_dirty_tickets() { return dirty_tickets; }
 int fake_mixed_tickets() { return mixed_tickets; }
 size_t fake_live_bytes() { return live_bytes; }
@@ -126,6 +127,7 @@ hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3, void **args, siz
 {
     const std::string &name = kernels[kernel];
     launched += name + "\n";
+    if (grid.x == 0 || grid.x > 0x7FFFFFFFu) ++bad_grids;
     auto takes = [&](const char *type) { return name.find(type) != std::string::npos; };
     if (takes("8SpmmArgs")) {
         const SpmmArgs &a = *static_cast<const SpmmArgs *>(args[0]);

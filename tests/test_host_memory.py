@@ -322,7 +322,20 @@ def both_gradients_go_apart_where_that_is_faster(L):
         L.destroy()
 
 
-CASES = [both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def a_grid_has_no_more_work_groups_than_a_launch_can(L):
+    """The gradient in column tiles comes in quarters of the partition's work-groups: where these are too many for a grid, the rows go through all columns at once."""
+    for n_blocks, tiled in ((30_000_000, True), (60_000_000, False)):
+        L.counts(0, n_blocks=n_blocks, longest_row=2000)
+        L.counts(1, n_blocks=600, longest_row=60)
+        assert L.create(5000, 5000, 300000, 700) == 0
+        L.launched()
+        assert L.backward(700, dx=False) == 0
+        assert any("sddmm_tiled" in k for k in L.launched()) == tiled
+        assert L.hip.fake_bad_grids() == 0, n_blocks
+        L.destroy()
+
+
+CASES = [a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
