@@ -954,9 +954,10 @@ __device__ __forceinline__ void staged_ids(int n_ranges, int n_tiles, int &range
 // A slot's entries [e_lo, e_hi) of a block, or this lane row's quarter of them where the four lane rows share a long row; the
 // longest of the four segments that a wave serves side by side sets the number of steps, shorter ones ride along with weight 0.
 struct StagedSegments {
-    uint32_t at;     // bytes to its first entry
+    uint32_t at;     // bytes to its first entry, or entries (UNIT 4, 1)
     int left, most;  // 4 times its length; the longest of the four
 };
+template <int UNIT = 4>
 __device__ __forceinline__ StagedSegments staged_segments(int e_lo, int e_hi, bool quad, int lrow)
 {
     int p0 = e_lo, len = e_hi - e_lo;
@@ -967,10 +968,11 @@ __device__ __forceinline__ StagedSegments staged_segments(int e_lo, int e_hi, bo
     }
     int most = max(len, __shfl_xor(len, 16));
     most = max(most, __shfl_xor(most, 32));
-    return StagedSegments{static_cast<uint32_t>(p0) * 4u, len * 4, most};
+    return StagedSegments{static_cast<uint32_t>(p0) * UNIT, len * 4, most};
 }
 
-template <bool XMASK>
+// MANY: 2^30 entries or more, which 32-bit byte offsets do not reach; they are counted instead.  (65536 x 131072 at 12.5 %, batch 128, forward / transposed, with the mirror's values: 8.5 / 29 ms, gathered from memory 70 / 72.)
+template <bool XMASK, bool MANY>
 __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const SpmmArgs a, const int n_tiles)
 {
     __shared__ float4 stage[kStageRows * kStageCols / 4 + kStageCols / 4];  // the block, then one row of zeros
@@ -995,15 +997,17 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     constexpr auto all_j = std::make_integer_sequence<int, kStageJ>{};
     float4 acc[kStageJ];
     static_for(all_j, [&](auto jc) { acc[decltype(jc)::value] = make_float4(0.f, 0.f, 0.f, 0.f); });
-    // 16 entries of a segment, one per lane, as they are stored.  at: byte offset of the lane's one in the first chunk; left: 4 times the entries
+    // 16 entries of a segment, one per lane, as they are stored.  at: byte offset (MANY: number) of the lane's one in the first chunk; left: 4 times the entries
     // from there to the segment's end; lanes past it read near entry 0
     struct Chunk {
         int index;
         float w;
     };
+    constexpr int kUnit = MANY ? 1 : 4;
     const int lig4 = lig * 4;
     auto load_chunk = [&](uint32_t at, int left, int first) {
         const uint32_t o = left > first * 4 ? at : 0u;
+        if constexpr (MANY) return Chunk{a.indices[static_cast<int64_t>(o) + first], a.values[static_cast<int64_t>(o) + first]};
         return Chunk{__builtin_bit_cast(int, gload1(as_gmem(a.indices), o + static_cast<uint32_t>(first * 4))), gload1(as_gmem(a.values), o + static_cast<uint32_t>(first * 4))};
     };
     // the same as LDS byte offset and weight
@@ -1018,7 +1022,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     Chunk held[kHeld][2];
     auto ask = [&](auto jc, const StagedSegments &s) {
         constexpr int j = decltype(jc)::value;
-        const uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(s.at)) + lig4);
+        const uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(s.at)) + lig * kUnit);
         const int left = row_lane<j>(s.left) - lig4;
         held[j % kHeld][0] = load_chunk(at, left, 0);
         held[j % kHeld][1] = load_chunk(at, left, 16);
@@ -1044,7 +1048,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
         }
     };
     int e1 = ends[kStageRangeRows];
-    StagedSegments now = staged_segments(ends[0], e1, my_quad, lrow);
+    StagedSegments now = staged_segments<kUnit>(ends[0], e1, my_quad, lrow);
     int e2 = n_cb >= 2 ? ends[2 * kStageRangeRows] : e1;
     static_for(std::make_integer_sequence<int, kAheadJ>{}, [&](auto jc) { ask(jc, now); });
 #pragma unroll
@@ -1052,7 +1056,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     for (int b = 0; b < n_cb; ++b) {
         const int cb0 = block_row(b), cb_next = block_row(b + 1), last_next = b + 1 < n_cb ? last_rows : 0;
         const int e3 = ends[min(b + 3, n_cb) * kStageRangeRows];
-        const StagedSegments next = staged_segments(e1, e2, my_quad, lrow);  // (empty behind the last block)
+        const StagedSegments next = staged_segments<kUnit>(e1, e2, my_quad, lrow);  // (empty behind the last block)
         lds_barrier();  // the previous block's gathers are done
         put_rows(cb0);
         lds_barrier();
@@ -1068,7 +1072,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
             __builtin_amdgcn_sched_barrier(0);
             const int most = __builtin_amdgcn_readlane(now.most, j);
             if (most > 0) {
-                uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(now.at)) + lig4);
+                uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(now.at)) + lig * kUnit);
                 int left = row_lane<j>(now.left) - lig4;
                 int off, off1;
                 float w, w1;
@@ -1076,7 +1080,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
                 placed(held[j % kHeld][1], left > 64, base, off1, w1);
                 int n = most;
                 // (a loop of its own, so that whatever it asks for has come at its end, and the loop after it waits for no memory)
-                for (; n > 32; n -= 16, at += 64, left -= 64) {
+                for (; n > 32; n -= 16, at += 16 * kUnit, left -= 64) {
                     const Chunk c2 = load_chunk(at, left, 32);
                     staged_steps<0, 16>(lds, off, w, acc[j]);
                     off = off1;
@@ -2918,7 +2922,7 @@ int spmm_split_group(const SpmmArgs &a)
 
 bool spmm_staged_ok(const SpmmArgs &a)
 {
-    if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (it brings 64 operand rows at a time, and reads entries at 32-bit byte offsets, 32 past the first)
+    if (a.x_rows < 64 || a.nnz < 64) return false;  // (it brings 64 operand rows at a time, and reads entries up to 32 past the first)
     if (!staged_pays(a.blocks, a.x_rows, a.batch, staged_work(a.blocks, a.x_rows, a.batch) >= kStageSomeWork ? kStageSegmentSomeWork : kStageLongSegment)) return false;
     return !a.blocks.staged_partial || a.blocks.n_rest_blocks > 0;  // (the rows the plan leaves out need a partition of their own)
 }
@@ -2944,7 +2948,7 @@ bool sddmm_staged_ok(const SddmmArgs &a)
 {
     if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     if ((a.batch + kStageCols - 1) / kStageCols > a.partial_tiles) return false;
-    if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (as spmm_staged_ok)
+    if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (as spmm_staged_ok; its byte offsets have 32 bits, and for so many entries there is no room for partial products)
     const int64_t work = staged_work(a.blocks, a.x_rows, a.batch);
     const int32_t segment = a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : work >= kStageMuchWork ? kStageSegmentMuchWork : kStageLongSegmentSddmm;
     if (a.blocks.staged_partial && (a.blocks.n_rest_blocks <= 0 || static_cast<int64_t>(a.blocks.n_rest_blocks) * kSddmmParts * ((a.batch + kStageCols - 1) / kStageCols + 8) >= (1ll << 31))) return false;
@@ -3513,10 +3517,9 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
     if (spmm_staged_ok(a)) {
         const int n_tiles = (a.batch + kStageCols - 1) / kStageCols;
         const dim3 grid(n_tiles * a.blocks.staged_ranges), block(kStageWaves * kWave);
-        if (a.XM)
-            hipLaunchKernelGGL(spmm_staged_kernel<true>, grid, block, 0, s, a, n_tiles);
-        else
-            hipLaunchKernelGGL(spmm_staged_kernel<false>, grid, block, 0, s, a, n_tiles);
+        const bool many = a.nnz >= (1 << 30);
+        const auto kernel = a.XM ? (many ? spmm_staged_kernel<true, true> : spmm_staged_kernel<true, false>) : many ? spmm_staged_kernel<false, true> : spmm_staged_kernel<false, false>;
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, a, n_tiles);
         if (a.blocks.staged_partial) {
             // the short rows: packed where that path runs (inside column tiles), and nothing else in that grid;
             // otherwise whatever kernel the batch asks for, on the short rows' own partition

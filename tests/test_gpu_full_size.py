@@ -305,3 +305,35 @@ def test_operand_beyond_4gib(nb, torch_mod, oracle):
     gr, Sg, dbr, Sdb = oracle.sddmm(rows, len(used), indptr, compact.astype(np.int32), dY, Xs)
     close(gv.cpu().numpy(), gr, Sg, what="dvalues"); close(db.cpu().numpy(), dbr, Sdb, what="dbias")
     L.close()
+
+
+def test_staged_products_of_a_thousand_million_entries(nb, torch_mod):
+    """2^30 entries and a little more, whose byte offsets do not fit in 32 bits: both products staged, rows and columns from every part of the
+    matrix against sums in 64 bits."""
+    torch = torch_mod
+    rows, cols, per, batch = 65536, 131072, 16390, 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    indices = torch.empty(rows, per, dtype=torch.int32, device="cuda")
+    slots = torch.arange(per, device="cuda", dtype=torch.int32) * 7
+    for r in range(0, rows, 8192):
+        indices[r:r + 8192] = slots + torch.randint(0, 7, (8192, per), generator=gen, device="cuda", dtype=torch.int32)
+    values = torch.randn(rows, per, generator=gen, device="cuda") * 0.01
+    indptr = torch.arange(rows + 1, device="cuda", dtype=torch.int32) * per
+    bias = torch.randn(rows, generator=gen, device="cuda")
+    L = nb.SparseLinear(wl.SparseLayerData(rows, cols, indptr, indices.view(-1), values.view(-1), bias, True), max_batch=batch)
+    assert L.nnz >= 1 << 30
+    X, Y, dY, dX = nb.dense(cols, batch), nb.dense(rows, batch), nb.dense(rows, batch), nb.dense(cols, batch)
+    X.copy_(torch.randn(cols, batch, generator=gen, device="cuda"))
+    dY.copy_(torch.randn(rows, batch, generator=gen, device="cuda"))
+    nb.sparse_linear_forward(L.handle, X, Y, batch)
+    nb.sparse_linear_backward(L.handle, X, Y, dY, dX, None, None, batch)
+    for r in (0, 1, 777, rows // 2, 65499, rows - 2, rows - 1):
+        x, w = X[indices[r].long()].double(), values[r].double()
+        z, S = w @ x + bias[r].double(), w.abs() @ x.abs() + bias[r].abs().double()
+        assert torch.all((Y[r].double() - z.clamp(min=0)).abs() <= TOL * S), r
+    dZ = torch.where(Y > 0, dY, torch.zeros_like(dY)).double()
+    for c in (0, 6, 40000, cols // 2, 99999, 7 * per - 1, cols - 1):
+        w = torch.where(indices[:, c // 7] == c, values[:, c // 7], 0.0).double() if c < 7 * per else torch.zeros(rows, device="cuda", dtype=torch.float64)
+        assert torch.all((dX[c].double() - w @ dZ).abs() <= TOL * (w.abs() @ dZ.abs())), c
+    L.close()

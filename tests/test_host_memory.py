@@ -335,7 +335,20 @@ def a_grid_has_no_more_work_groups_than_a_launch_can(L):
         L.destroy()
 
 
-CASES = [a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def products_of_very_many_entries_are_staged(L):
+    """On either side of 2^30 entries, whose byte offsets do not fit in 32 bits."""
+    for nnz, many in (((1 << 30) - 4, "0"), (1 << 30, "1")):
+        L.counts(0, n_blocks=600, longest_row=17000, staged_ranges=147, staged_rows=65536, staged_nnz=nnz)
+        L.counts(1, n_blocks=600, longest_row=10000, staged_ranges=293, staged_rows=131072, staged_nnz=nnz)
+        assert L.create(65536, 131072, nnz, 128) == 0
+        L.launched()
+        assert L.forward(128) == 0 and L.backward(128, dvalues=False) == 0
+        names = [k for k in L.launched() if "spmm_staged_kernel" in k]
+        assert len(names) == 2 and all(f"ELb{many}E" in k for k in names), names
+        L.destroy()
+
+
+CASES = [products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
