@@ -68,11 +68,13 @@ constexpr int32_t kStageMinBatch = 128;  // narrower batches never take the stag
 constexpr int32_t kStageTargetGroups = 256;  // work-groups wanted at max_batch (one per compute unit)
 constexpr float kStageMinReuse = 2.f;    // stored entries per staged operand row and work-group, at least
 constexpr int32_t kStageLongSegment = 10;       // mean entries per segment from which staging pays whatever the operand's size: products,
-constexpr int32_t kStageSegmentSomeWork = 8;    // products of so many entries times columns (8.7 and 10 entries, in column tiles / staged, us: 8192^2 at 1.7 / 1.95 %, batch 256 / 512 / 1024
-constexpr int64_t kStageSomeWork = 324 << 20;   // 77 / 76, 136 / 99, 267 / 192 and 84 / 77, 152 / 104, 295 / 198; 4500^2 and 6000^2 at 1.75 %, batch 512 43 / 47, 61 / 64, batch 1024 65 / 59, 119 / 92; below 8 no plan is made),
+constexpr int32_t kStageSegmentSomeWork = 8;    // products of so many of the plan's entries times columns (8.7 and 10 entries, in column tiles / staged, us: 8192^2 at 1.7 / 1.95 %, batch 256 / 512 / 1024
+constexpr int64_t kStageSomeWork = 324 << 20;   // 77 / 76, 136 / 99, 267 / 192 and 84 / 77, 152 / 104, 295 / 198; 4500^2 and 6000^2 at 1.75 %, batch 512 43 / 47, 61 / 64, batch 1024 65 / 59, 119 / 92; of 44 more
+                                                // staged takes 0.59 to 1.01 of the time above the line and 0.81 to 1.52 below it, by shape and not by work; below 8 no plan is made but for operands of 48 MiB),
 constexpr int32_t kStageLongSegmentSddmm = 20;  // ... the SDDMM, which has its second pass to pay for as well,
-constexpr int32_t kStageSegmentMuchWork = 10;   // ... and the SDDMM of so many entries times columns (8192^2 at 1.95 / 2.5 / 3.5 %, batch 256 76 / 91 / 135 -> 86 / 97 / 116, batch 512
-constexpr int64_t kStageMuchWork = 420 << 20;   // 143 / 173 / 254 -> 128 / 147 / 177, batch 1024 271 / 328 / 477 -> 251 / 288 / 338; 5000^2, batch 512 54 / 69 / 90 -> 61 / 68 / 81; 12000^2 at 2.5 %, batch 256 / 1024 233 / 853 -> 177 / 529)
+constexpr int32_t kStageSegmentMuchWork = 10;   // ... and the SDDMM of so many (8192^2 at 1.95 / 2.5 / 3.5 %, batch 256 76 / 91 / 135 -> 86 / 97 / 116, batch 512
+constexpr int64_t kStageMuchWork = 420 << 20;   // 143 / 173 / 254 -> 128 / 147 / 177, batch 1024 271 / 328 / 477 -> 251 / 288 / 338; 5000^2, batch 512 54 / 69 / 90 -> 61 / 68 / 81; 12000^2 at 2.5 %, batch 256 / 1024 233 / 853 -> 177 / 529;
+                                                // of 58 more 0.67 to 1.04 above the line, 0.81 to 1.53 below)
 constexpr int32_t kStageSegmentBesideDense = 8;   // ... and the SDDMM of the rows beside dense ones (DenseSplit), from batch 512 on: power-law 16384^2 at 3 / 10 %,
                                                   // batch 1024: 1249 -> 932 and 3405 -> 2265 us; at batch 256 4096^2 loses (55 -> 84)
 constexpr int64_t kStageBigOperand = 48ll << 20;  // operand bytes no set of L2s holds: staging pays for shorter segments,

@@ -853,7 +853,7 @@ __global__ __launch_bounds__(kBlock) void full_rows_finish_softmax_kernel(const 
 // applied when the rows are stored, once, after the last block.
 // What bounds it: the latency of short runs of LDS gathers at four waves a SIMD (vector ALUs 65 % busy, LDS 45 %; a loop of nothing but whole chunks runs
 // 1.5 times as fast), not either pipe.  Segments, masks and offsets worked out once per block and not per use, the rows brought ahead, no wait for memory among
-// the gathers, the weight's move in the multiply-add: 16384^2 power-law rows at 10 %, batch 1024, 1087 -> 740 us (10.3 -> 6.5 vector instructions a gather);
+// the gathers, the weight's move in the multiply-add: 16384^2 power-law rows at 10 %, batch 1024, under the profiler 1087 -> 745 us (10.3 -> 6.5 vector instructions a gather; among other passes it takes 640 to 680);
 // forward products of uniform 8192^2 at 5 %, batch 1024, 374 -> 278, 16384^2 at 2 %, batch 512, 448 -> 334, 5000 x 7000 at 8 %, batch 511, 146 -> 115.
 // (48 KB of code, the gradient's 56, the instruction cache 64.  Two registers are stored before the block loop and reloaded after it; with a mask four, two of them reloaded once a block.)
 // Slots dealt to the waves there and back change nothing, two runs of 8 gathers made one of 16 neither.  A row marked kStageQuad is
@@ -2862,9 +2862,9 @@ bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t
     // An operand beyond the L2s, evenly used, on rows of similar length: shorter segments already pay, because the other
     // kernels' gathers partly go to memory there (a few hot operand rows that take most gathers would stay cached on
     // the other paths; on a power-law matrix most (row, block) pairs hold one entry or none and cost a visit all the
-    // same).  Measured on 16384^2 uniform matrices at batch 1024 against the column-tiled kernels, product / SDDMM:
-    // 0.7 % (3.6 entries per segment) 648 / 851 us staged against 429 / 595; 1 % (5.1) 692 / 1012 against 662 / 836;
-    // 2 % (10.2) 880 / 1259 against 1341 / 1642.
+    // same).  16384^2 uniform matrices at batch 1024, column-tiled -> staged, us: products at 0.6 / 0.7 / 0.79 / 1 / 2 % (3.1, 3.6, 4.0, 5.1 and 10.2 entries per segment)
+    // 345 -> 424, 414 -> 429, 525 -> 437, 662 -> 458, 1331 -> 598, SDDMM 512 -> 500, 594 -> 521, 666 -> 572, 834 -> 680, 1656 -> 805; 44 others of 12300 columns and more, batch 768 and more: 0.88 to 1.06
+    // below 4 entries, 0.50 to 0.92 from there on.
     const bool big_operand = static_cast<int64_t>(x_rows) * batch * 4 >= kStageBigOperand && blocks.hot_share < 0.5f &&
                              static_cast<int64_t>(blocks.staged_longest_row) * rows <= 4 * nnz;
     const int64_t segment = big_operand ? std::min(long_segment, kStageSegmentBigOperand) : long_segment;
@@ -2885,13 +2885,18 @@ static int64_t staged_work(const RowBlocks &blocks, int32_t x_rows, int32_t batc
 // 3894 x 6816 at 0.6 %, batch 227 15.9 -> 11.8; 16384^2 at 0.3 %, batch 300 103 -> 61; 10442 x 13851 at 0.37 %, batch 164 38.8 -> 27.9.  But tiles a fifth empty or more: 10681 x 8704 at 0.8 %, batch 134
 // 36.5 -> 42.3, 11466 x 5888 at 0.5 %, batch 263 30.2 -> 34.0; operands near an L2: 4545 x 5628 at 0.7 %, batch 189 13.1 -> 14.1; often gathered: 16000 x 5000 at 0.8 %, batch 200 29.0 -> 31.2,
 // 3182 x 2692 at 1.9 %, batch 580 25.7 -> 28.3; rarely: 3428 x 12999 at 0.33 %, batch 290 25.3 -> 26.7.
-// (More work than kFusedMinWork whatever the shape: in a training step such a transposed product shares its gathers, and is in no other launch's grid, which would add in another order.)
+// (More work than kFusedMinWork whatever the shape: in a training step such a transposed product shares its gathers, or both pipelines follow the chain's order (chain_shape_ok), and it is never
+// in another launch's grid, which would add in another order.)
+constexpr int64_t kFusedMinWork = 16 << 20;        // (backward_fused_ok)
+constexpr int64_t kPackTilesOperand = 21ll << 18;  // operand bytes
+constexpr int64_t kPackTilesGathers = 13;          // entries per operand row
+static_assert(kPackTilesOperand / 4 * kPackTilesGathers >= kFusedMinWork, "");
 static bool packed_tiles_pay(const SpmmArgs &a)
 {
     if (a.batch <= 128 || a.XM || a.blocks.n_short != a.rows || a.blocks.hot_share >= 0.5f) return false;
     if (static_cast<int64_t>(a.blocks.staged_longest_row) * a.rows > 4ll * a.nnz || (a.batch + 63) / 64 * 320 > 6 * a.batch) return false;
     const int64_t row_bytes = static_cast<int64_t>(a.x_rows) * 4, operand = row_bytes * a.batch, most = operand >= (11ll << 20) ? 90 : 55;
-    return operand >= (21ll << 18) && row_bytes * 64 <= (4ll << 20) && a.nnz >= 28ll * a.rows && a.nnz >= 13ll * a.x_rows && a.nnz <= most * a.x_rows &&
+    return operand >= kPackTilesOperand && row_bytes * 64 <= (4ll << 20) && a.nnz >= 28ll * a.rows && a.nnz >= kPackTilesGathers * a.x_rows && a.nnz <= most * a.x_rows &&
            packed_grid(a, 16, true).ids <= kMaxGridIds;
 }
 
@@ -3269,8 +3274,7 @@ bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &)
 
 // Within a training step small layers do better with T and S in the grids of their neighbours: entries times columns from
 // which the pass pays there (steps of 3072-1024-512-10 at 10 %, batch 100, 5 M in the middle layer: 38.6 -> 42.5 us with it;
-// 2000-4000-3000-10 at 3 %, batch 128, 46 M: 72.4 -> 70.2; three layers of 3000 at 5 %, batch 100: 128 -> 116).
-constexpr int64_t kFusedMinWork = 16 << 20;
+// 2000-4000-3000-10 at 3 %, batch 128, 46 M: 72.4 -> 70.2; three layers of 3000 at 5 %, batch 100: 128 -> 116): kFusedMinWork.
 // The transposed product staged through LDS and the gradient apart from it (staged too, or by matrix instructions sampled on the pattern) against one stream of L2 gathers for both: apart they read
 // the operands twice, from LDS at up to three times the rate, and copy them there.  Which is faster goes by estimates of both, us.  A staged launch takes rounds of a work-group per compute unit,
 // each a range's entries and the copy of its operand tile; the stream its gathers (more of them miss where dZ has many rows), and the strewing of results through the position map,
