@@ -455,6 +455,13 @@ def test_staged_kernels_on_awkward_shapes(nb, torch_mod, oracle, rows, cols, len
     close(dXd.cpu().numpy(), dX, SdX, what="dX")
     gr, Sg, dbr, Sdb = oracle.sddmm(rows, cols, indptr, indices, dZ, X)
     close(g.cpu().numpy(), gr, Sg, what="g"); close(db.cpu().numpy(), dbr, Sdb, what="db")
+    # each gradient alone: both together take one stream of gathers, not the staged kernels
+    dXd.fill_(float("nan")); g.fill_(float("nan")); db.fill_(float("nan"))
+    nb.sparse_linear_backward(L.handle, Xd, Yd, dYd, dXd, None, None, batch)
+    nb.sparse_linear_backward(L.handle, Xd, Yd, dYd, None, g, db, batch)
+    torch.cuda.synchronize()
+    close(dXd.cpu().numpy(), dX, SdX, what="dX alone")
+    close(g.cpu().numpy(), gr, Sg, what="g alone"); close(db.cpu().numpy(), dbr, Sdb, what="db alone")
     full = Yd._base if Yd._base is not None else Yd
     assert torch.isnan(full.view(rows, -1)[:, batch:]).all()     # padding columns of the output were not written
     L.close()
@@ -797,6 +804,14 @@ def _random_shape_parity(nb, torch_mod, oracle, k, prefer_staged):
     close(dXd.cpu().numpy(), dX, SdX, what="dX")
     gr, Sg, dbr, Sdb = oracle.sddmm(rows, cols, lay.indptr, lay.indices, dZ, X)
     close(g.cpu().numpy(), gr, Sg, what="dvalues"); close(db.cpu().numpy(), dbr, Sdb, what="dbias")
+    if prefer_staged:   # each gradient alone: both together take one stream of gathers
+        for t in (dXd, g, db):
+            t.fill_(float("nan"))
+        nb.sparse_linear_backward(L.handle, Xd, Yd, dYd, dXd, None, None, batch)
+        nb.sparse_linear_backward(L.handle, Xd, Yd, dYd, None, g, db, batch)
+        torch.cuda.synchronize()
+        close(dXd.cpu().numpy(), dX, SdX, what="dX alone")
+        close(g.cpu().numpy(), gr, Sg, what="dvalues alone"); close(db.cpu().numpy(), dbr, Sdb, what="dbias alone")
     L.close()
 
 
