@@ -21,8 +21,10 @@ extern "C" {
  * staged SDDMM (see nerva_plan_staged_host) run wherever they can (batch of at least
  * NERVA_STAGE_MIN_BATCH columns), also where the library's own rule expects them
  * to be slower.  NERVA_PARTITION_PREFER_DENSE_ROWS: the balanced partition, but where a matrix has rows dense enough
- * for matrix instructions at the layer's max_batch, these serve them at every batch from 128 columns on. */
-enum { NERVA_PARTITION_BALANCED = 0, NERVA_PARTITION_ROW_SPLIT = 1, NERVA_PARTITION_PREFER_STAGED = 2, NERVA_PARTITION_PREFER_DENSE_ROWS = 3 };
+ * for matrix instructions at the layer's max_batch, these serve them at every batch from 128 columns on.
+ * NERVA_PARTITION_PREFER_STRIPS: the balanced partition, but forward products run in strips wherever they can (256 columns of W or more, 193 of the batch). */
+enum { NERVA_PARTITION_BALANCED = 0, NERVA_PARTITION_ROW_SPLIT = 1, NERVA_PARTITION_PREFER_STAGED = 2, NERVA_PARTITION_PREFER_DENSE_ROWS = 3,
+       NERVA_PARTITION_PREFER_STRIPS = 4 };
 int nerva_set_partition_mode(int32_t mode);
 
 /* Inspection aid: the partition tables that binding a pattern has left on the device, entry for entry those that the

@@ -131,6 +131,9 @@ struct nerva_layer {
     // owned: tickets of the huge rows (SpmmArgs::tickets), 0 but while a product runs
     int32_t *tickets = nullptr;
     size_t ticket_ints = 0;
+    // owned: stream of a forward product in strips (SpmmArgs::strip_stream), or nullptr
+    float *strip_stream = nullptr;
+    size_t strip_floats = 0;
     // owned: per-tile partial products of the SDDMM and of the backward pass on one gather stream, as many tiles as
     // they take at any batch up to max_batch; fewer or none where there was no room for them
     float *partial = nullptr;
@@ -500,10 +503,14 @@ void fill_staged_ends_host(StagedPlan &H, const int32_t *indptr, const int32_t *
 // Sizes of the tables of one orientation, from bounds that hold for every pattern with these row and entry counts:
 // the tables are laid out before the planner, which runs on the device, has counted anything.
 struct PlanRoom {
-    int64_t blocks, long_blocks, rest_blocks, huge_rows, rows_by_length, dense_rows = 0, dense_flags = 0;
-    int32_t ranges, cblocks;
-    PlanRoom(int32_t rows, int32_t other, int64_t nnz, int32_t max_batch, int32_t dense_len = INT32_MAX)
+    int64_t blocks, long_blocks, rest_blocks, huge_rows, rows_by_length, dense_rows = 0, dense_flags = 0, strip_sets = 0;
+    int32_t ranges, cblocks, strip_blocks = 0;
+    PlanRoom(int32_t rows, int32_t other, int64_t nnz, int32_t max_batch, bool strips = false, int32_t dense_len = INT32_MAX)
     {
+        if (strips) {
+            strip_blocks = strip_blocks_of(other);
+            strip_sets = (static_cast<int64_t>(rows) + kStripSet - 1) / kStripSet;
+        }
         if (dense_len < INT32_MAX) {
             dense_rows = round_up(std::min<int64_t>(rows, nnz / dense_len), 4);
             dense_flags = round_up(rows, 16) / 4;
@@ -526,7 +533,7 @@ struct PlanRoom {
     size_t ints() const
     {
         return static_cast<size_t>(4 * (kWavesPerBlock * (blocks + long_blocks + rest_blocks) + huge_rows + rows_by_length)) +
-               staged_ints() + static_cast<size_t>(dense_rows + dense_flags) +
+               static_cast<size_t>(strip_sets * (2 * strip_blocks + kStripSet * (strip_blocks + 2))) + staged_ints() + static_cast<size_t>(dense_rows + dense_flags) +
                (dense_flags ? static_cast<size_t>(4 * kWavesPerBlock * (blocks + long_blocks)) : 0);
     }
     // the tables at `mem` (16-byte records first)
@@ -545,6 +552,9 @@ struct PlanRoom {
             t.other_long_waves = r; r += kWavesPerBlock * long_blocks;
         }
         int32_t *i = reinterpret_cast<int32_t *>(r);
+        t.strip_segs = reinterpret_cast<int2 *>(i); i += 2 * strip_sets * strip_blocks;
+        t.strip_cuts = i; i += strip_sets * kStripSet * (strip_blocks + 1);
+        t.strip_rows = i; i += strip_sets * kStripSet;
         t.dense_rows = i; i += dense_rows;
         t.dense_flag = reinterpret_cast<uint8_t *>(i); i += dense_flags;
         staged_at(t, i);
@@ -602,6 +612,7 @@ void free_layer_buffers(nerva_layer *l)
     if (l->bind_result) (void)hipHostFree(l->bind_result);
     (void)hipFree(l->scratch);
     (void)hipFree(l->tickets);
+    (void)hipFree(l->strip_stream);
     (void)hipFree(l->partial);
     (void)hipFree(l->dz);
     (void)hipFree(l->dense);
@@ -703,7 +714,7 @@ int nerva_validate_csr_host(int32_t rows, int32_t cols, int64_t nnz, const int32
 
 int nerva_set_partition_mode(int32_t mode)
 {
-    if (mode < NERVA_PARTITION_BALANCED || mode > NERVA_PARTITION_PREFER_DENSE_ROWS) return fail(NERVA_ERR_ARGUMENT, "unknown partition mode %d", mode);
+    if (mode < NERVA_PARTITION_BALANCED || mode > NERVA_PARTITION_PREFER_STRIPS) return fail(NERVA_ERR_ARGUMENT, "unknown partition mode %d", mode);
     g_partition_mode.store(mode);
     return NERVA_OK;
 }
@@ -857,7 +868,7 @@ static int csr_status_error(const int32_t *st)
 // launches (structure.hip); the host waits once, for the check's verdict and the partitions' sizes.  On failure
 // (NERVA_ERR_CSR, NERVA_ERR_HIP) nothing that a product reads has been changed.  On success the caller swaps
 // l->spare into l->cur and adopts `plan`, `plan_t`.
-constexpr size_t kPartialMaxBytes = 4ull << 30, kDzMaxBytes = 1ull << 30;
+constexpr size_t kPartialMaxBytes = 4ull << 30, kDzMaxBytes = 1ull << 30, kStripMaxBytes = 1ull << 30;
 struct BuiltPattern {
     RowBlocks plan{}, plan_t{};
     int64_t partial_stride = 0, partial_db_at = 0;
@@ -884,7 +895,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
                             BuiltPattern *out, hipStream_t s)
 {
     const int32_t rows = l->rows, cols = l->cols, max_batch = l->max_batch, asked = g_partition_mode.load();
-    const int32_t mode = asked == NERVA_PARTITION_PREFER_DENSE_ROWS ? NERVA_PARTITION_BALANCED : asked;
+    const int32_t mode = asked == NERVA_PARTITION_PREFER_DENSE_ROWS || asked == NERVA_PARTITION_PREFER_STRIPS ? NERVA_PARTITION_BALANCED : asked;
     static_assert(kPlanBalanced == NERVA_PARTITION_BALANCED && kPlanRowSplit == NERVA_PARTITION_ROW_SPLIT &&
                   kPlanPreferStaged == NERVA_PARTITION_PREFER_STAGED, "header and kernels disagree");
     PatternBuffers &B = l->spare;
@@ -893,10 +904,11 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     HIP_TRY(reserve(&B.indptr_t, &indptr_t_have, static_cast<size_t>(cols) + 1));
     HIP_TRY(reserve(&B.mirror_mem, &B.mirror_ints, 4 * n64));
     // rows long enough for matrix instructions are looked for unless the layer takes the dense route as a whole
-    const bool seek_dense = mode == NERVA_PARTITION_BALANCED && cols >= kDenseRowsMinCols && max_batch >= kDenseRowsMinBatch && nnz < (1 << 30) &&
+    const bool seek_dense = mode == NERVA_PARTITION_BALANCED && asked != NERVA_PARTITION_PREFER_STRIPS && cols >= kDenseRowsMinCols && max_batch >= kDenseRowsMinBatch && nnz < (1 << 30) &&
                             !takes_dense_route(l, nnz);
     const int32_t dense_len = seek_dense ? dense_row_length(cols) : INT32_MAX;
-    const PlanRoom room(rows, cols, nnz, max_batch, dense_len), room_t(cols, rows, nnz, max_batch);
+    const bool strips = !takes_dense_route(l, nnz) && (asked == NERVA_PARTITION_PREFER_STRIPS ? strip_possible(rows, cols, nnz, max_batch) : mode == NERVA_PARTITION_BALANCED && strip_wanted(rows, cols, nnz, max_batch));
+    const PlanRoom room(rows, cols, nnz, max_batch, strips, dense_len), room_t(cols, rows, nnz, max_batch);
     const size_t plan_ints = static_cast<size_t>(round_up(static_cast<int64_t>(room.ints()), 64));
     HIP_TRY(reserve(&B.plan_mem, &B.plan_ints, plan_ints + room_t.ints()));
     if (!l->bind_result) HIP_TRY(hipHostMalloc(&l->bind_result, sizeof(BindResult), hipHostMallocDefault));
@@ -912,6 +924,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     const int32_t side_rows[2] = {rows, cols}, side_ranges[2] = {room.ranges, room_t.ranges};
     constexpr size_t kCountInts = sizeof(PlanCounts) / 4;
     for (int k = 0; k < 2; ++k) work_at[k] = carve(6 * static_cast<size_t>(side_rows[k]) + static_cast<size_t>(side_ranges[k]) + 1 + kCountInts);
+    const size_t strip_at = carve(8);
     HIP_TRY(reserve(&l->build_work, &l->build_work_ints, ints));
     int32_t *W = l->build_work;
 
@@ -924,16 +937,19 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     m.values_t = reinterpret_cast<float *>(B.mirror_mem + 3 * n64);
     PlanArgs p{};
     p.nnz = nnz; p.max_batch = max_batch; p.mode = mode; p.status = m.status; p.result = l->bind_result;
+    p.result->strip = 0; p.prefer_strips = asked == NERVA_PARTITION_PREFER_STRIPS;
     for (int k = 0; k < 2; ++k) {
         PlanSide &side = p.side[k];
         side.rows = side_rows[k]; side.other = side_rows[1 - k]; side.range_bound = side_ranges[k];
+        side.strip_blocks = k == 0 ? room.strip_blocks : 0;
         side.dense_len = k == 0 ? dense_len : INT32_MAX;
         side.indptr = k == 0 ? indptr : B.indptr_t; side.indices = k == 0 ? indices : m.indices_t;
         side.tables = k == 0 ? room.at(B.plan_mem) : room_t.at(B.plan_mem + plan_ints);
         int32_t *w = W + work_at[k];
         const size_t r = static_cast<size_t>(side.rows);
         side.work = PlanWork{w, w + r, w + 2 * r, w + 3 * r, w + 4 * r, w + 5 * r, w + 6 * r,
-                             reinterpret_cast<PlanCounts *>(w + 6 * r + static_cast<size_t>(side.range_bound) + 1)};
+                             reinterpret_cast<PlanCounts *>(w + 6 * r + static_cast<size_t>(side.range_bound) + 1),
+                             reinterpret_cast<unsigned long long *>(W + strip_at)};
     }
     HIP_TRY(launch_bind(m, p, s));
     B.has_table = (l->dense_on || static_cast<double>(nnz) >= static_cast<double>(kTableFromDensity) * rows * cols) &&
@@ -1009,6 +1025,14 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         if (l->activation == NERVA_ACT_RELU && max_batch > 4 && nnz >= 4 * static_cast<int64_t>(rows) && dz * 4 <= kDzMaxBytes)
             (void)reserve_optional(&l->dz, &l->dz_floats, dz, false);
         const int64_t slots = out->plan.n_huge_blocks > out->plan_t.n_huge_blocks ? out->plan.n_huge_blocks : out->plan_t.n_huge_blocks;
+        if (const size_t chunks = static_cast<uint32_t>(R.strip), need = (chunks + 2) * kStripChunk * kStripSet * 2;
+            chunks > 0 && need * 4 <= kStripMaxBytes && reserve_optional(&l->strip_stream, &l->strip_floats, need)) {
+            RowBlocks &v = out->plan;
+            v.strip_rows = p.side[0].tables.strip_rows; v.strip_segs = p.side[0].tables.strip_segs; v.strip_cuts = p.side[0].tables.strip_cuts;
+            v.strip_blocks = room.strip_blocks; v.strip_block_rows = strip_block_rows_of(cols);
+            v.strip_chunks = static_cast<int32_t>(chunks); v.strip_steps = static_cast<int32_t>(R.strip >> 32);
+            v.strip_preferred = p.prefer_strips;
+        }
         out->scratch_ld = round_up(max_batch, 64);
         if (slots > 0) {
             const int64_t huge = std::max(out->plan.n_huge_rows, out->plan_t.n_huge_rows);
@@ -1195,6 +1219,7 @@ int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx,
     }
     SpmmArgs a{};
     a.blocks = layer->plan; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 0); a.scratch_ld = layer->scratch_ld;
+    a.strip_stream = reinterpret_cast<float4 *>(layer->strip_stream);
     a.indptr = layer->indptr; a.indices = layer->indices; a.values = layer->values; a.bias = layer->bias;
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
     a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.relu = layer->activation == NERVA_ACT_RELU;
@@ -1458,6 +1483,7 @@ static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldi
 {
     SpmmArgs a{};
     a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = tickets_of(ly, 0); a.scratch_ld = ly->scratch_ld;
+    a.strip_stream = reinterpret_cast<float4 *>(ly->strip_stream);
     a.indptr = ly->indptr; a.indices = ly->indices; a.values = ly->values; a.bias = ly->bias;
     a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
     a.rows = ly->rows; a.x_rows = ly->cols; a.batch = batch; a.relu = ly->activation == NERVA_ACT_RELU;
@@ -1469,12 +1495,30 @@ static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldi
 static int forward_chain(nerva_mlp *mlp, const float *X, int32_t ldx, int32_t batch, char *ws, const Layout &L,
                          hipStream_t s, size_t n_layers)
 {
+    auto A_of = [&](size_t l) { return reinterpret_cast<float *>(ws + L[l].A); };
+    auto args_of = [&](size_t l) { return forward_args(mlp->layers[l], l > 0 ? A_of(l - 1) : X, l > 0 ? L.ld : ldx, A_of(l), L.ld, batch); };
+    // the streams of products in strips, which depend on the weights alone, in one launch at the start
+    size_t ready = 0;   // layers below this one have theirs
+    if (batch > kStripFromBatch) {
+        SpmmArgs strips[kStripStreams];
+        int n = 0;
+        for (; ready < n_layers && n < kStripStreams; ++ready)
+            if (!use_dense(mlp->layers[ready], batch)) {
+                strips[n] = args_of(ready);
+                n += spmm_takes_strip(strips[n]);
+            }
+        if (n > 0) {
+            Timed tm(mlp->prof, s, "strip_streams", 0);
+            HIP_TRY(launch_strip_streams(strips, n, s));
+        }
+    }
     const float *in = X;
     int64_t ldin = ldx;
     for (size_t l = 0; l < n_layers; ++l) {
         const nerva_layer *ly = mlp->layers[l];
-        float *A = reinterpret_cast<float *>(ws + L[l].A);
-        const SpmmArgs a = forward_args(ly, in, ldin, A, L.ld, batch);
+        float *A = A_of(l);
+        SpmmArgs a = args_of(l);
+        a.strip_ready = l < ready;
         if (use_dense(ly, batch)) {
             Timed tm(mlp->prof, s, "dense_forward", static_cast<int>(l));
             HIP_TRY(dense_forward(ly, in, ldin, A, L.ld, batch, s));

@@ -56,7 +56,33 @@ struct RowBlocks {
     int32_t staged_nnz;            // and their stored entries
     int32_t staged_preferred;      // measurement aid: take the staged kernels wherever they can run
     const int4 *rows_by_length;    // every row, as in short_rows (which is the end of this table)
+    // Optional fourth form, for the product in strips (spmm_strip_kernel; strip_segs != nullptr): sets of kStripSet rows, longer ones first,
+    // cut into segments at the multiples of strip_block_rows in the column indices.
+    const int32_t *strip_rows;     // [sets * kStripSet] row or -1
+    const int2 *strip_segs;        // [sets * strip_blocks] {first chunk of the stream, entries of the longest of the set's segments in that block}
+    const int32_t *strip_cuts;     // [sets * (strip_blocks + 1) * kStripSet] position of a row's first entry of a block, and one past its last
+    int32_t strip_blocks, strip_block_rows;
+    int32_t strip_chunks, strip_steps;   // of the stream; the sum of the longest segments
+    int32_t strip_preferred;             // measurement aid: take it wherever it can run
 };
+
+// Strips: kStripRows operand rows of kStripCols columns lie in LDS at a time; the operand's blocks are of equal size, a multiple of 256 rows.
+constexpr int32_t kStripRows = 2048, kStripCols = 16, kStripSet = 16;
+constexpr int32_t kStripChunk = 8;       // entries of each of a set's rows in a chunk of the stream, kStripChunk * kStripSet * 8 bytes
+constexpr int32_t kStripFromBatch = 192; // wider ones only
+constexpr int32_t kStripMaxBlocks = 32;
+__host__ __device__ inline int32_t strip_blocks_of(int32_t x_rows) { return (x_rows + kStripRows - 1) / kStripRows; }
+__host__ __device__ inline int32_t strip_block_rows_of(int32_t x_rows)
+{
+    const int32_t n = strip_blocks_of(x_rows);
+    return ((x_rows + n - 1) / n + 255) / 256 * 256;
+}
+// first operand row that LDS holds in block b: the last block starts early enough to be whole
+__host__ __device__ inline int32_t strip_block_base(int32_t b, int32_t block_rows, int32_t x_rows)
+{
+    const int32_t last = x_rows > block_rows ? x_rows - block_rows : 0;
+    return b * block_rows < last ? b * block_rows : last;
+}
 
 constexpr int32_t kStageRows = 512;      // operand rows held in LDS at a time
 constexpr int32_t kStageCols = 64;       // columns of the operand (examples) per work-group
@@ -167,7 +193,23 @@ struct SpmmArgs {
     int64_t ce_lddz;
     float *ce_loss_cols;       // [batch]
     const DenseSplit *split;   // (for the launch) or nullptr
+    float4 *strip_stream;      // room for the plan's chunks and two more, or nullptr
+    int32_t strip_ready;       // (for the launch) launch_strip_streams has filled it
 };
+// What the product in strips is given in place of the matrix, for up to kStripStreams products in one launch.
+constexpr int kStripStreams = 4;
+struct StripStream {
+    const int2 *segs;
+    const int32_t *cuts, *indices;
+    const float *values;
+    float4 *out;
+    int32_t sets, blocks, block_rows, x_rows, nnz;
+};
+struct StripStreams {
+    StripStream of[kStripStreams];
+};
+bool spmm_takes_strip(const SpmmArgs &a);
+hipError_t launch_strip_streams(const SpmmArgs *list, int n, hipStream_t s);
 // tickets per huge row, one per 32 columns
 __host__ __device__ inline int64_t huge_row_tickets(int64_t scratch_ld) { return scratch_ld / 32; }
 bool spmm_softmax_epilogue_ok(const SpmmArgs &a);
@@ -452,6 +494,8 @@ struct PlanCounts {
 struct PlanTables {
     int4 *waves, *huge_rows, *long_waves, *rest_waves, *rows_by_length;
     int32_t *staged_rows, *staged_groups, *staged_ends;
+    int2 *strip_segs;
+    int32_t *strip_rows, *strip_cuts;
     int32_t *dense_rows;             // [room for the rows of dense_len entries or more] ascending
     uint8_t *dense_flag;             // [rows]
     int4 *other_waves, *other_long_waves;   // copies of the tables above with row -1 in the place of dense rows
@@ -462,10 +506,12 @@ struct PlanWork {                    // scratch, [rows] ints each but for the la
     int32_t *order, *tmp, *lens, *covered, *cut, *slots;
     int32_t *range_first;            // [range_bound + 1]
     PlanCounts *counts;
+    unsigned long long *strip_count; // {chunks, steps in the upper half, dealt out so far; work-groups done}
 };
 struct PlanSide {
     int32_t rows, other;             // of this orientation
     int32_t range_bound;             // ranges the staged tables have room for, 0: no staged plan
+    int32_t strip_blocks;            // of W alone, 0: no plan for strips
     int32_t dense_len;               // rows this long are listed, and left out of the staged plan where they are many (INT32_MAX: none)
     const int32_t *indptr, *indices;
     PlanTables tables;
@@ -474,17 +520,31 @@ struct PlanSide {
 struct BindResult {                  // pinned host memory
     int32_t status[4];
     PlanCounts plan[2];
+    unsigned long long strip;        // chunks, steps in the upper half; zeroed by the host, 0 without a plan for strips
 };
 enum : int32_t { kPlanBalanced = 0, kPlanRowSplit = 1, kPlanPreferStaged = 2 };
 struct PlanArgs {
     PlanSide side[2];                // W, its mirror
     int32_t nnz, max_batch, mode;
+    int32_t prefer_strips;
     const int32_t *status;
     BindResult *result;
 };
 hipError_t launch_bind(const MirrorArgs &m, const PlanArgs &p, hipStream_t s);
 hipError_t launch_plan(const PlanArgs &p, int sides, hipStream_t s);   // its last part alone: the partitions of W, or of W and its mirror
 
+// Whether the product in strips can run (256 operand rows travel at a time), and whether a matrix is looked at for a plan: enough work, segments neither so short that a set's differ
+// too much nor so long that the staged product, whose gathers are wider, is as fast (spmm_strip_ok asks more closely).  Rows of different lengths have no use for it: a wave would run as long as the longest.
+__host__ __device__ inline bool strip_possible(int32_t rows, int32_t cols, int64_t nnz, int32_t max_batch)
+{
+    return max_batch > kStripFromBatch && cols >= 256 && strip_blocks_of(cols) <= kStripMaxBlocks && nnz > 0 && nnz < (1 << 30) && static_cast<int64_t>(rows) * strip_blocks_of(cols) <= (1 << 28);
+}
+__host__ __device__ inline bool strip_wanted(int32_t rows, int32_t cols, int64_t nnz, int32_t max_batch)
+{
+    const int64_t segments = static_cast<int64_t>(rows) * strip_blocks_of(cols);
+    return strip_possible(rows, cols, nnz, max_batch) && rows >= 256 && cols >= 1024 && nnz * max_batch >= (96 << 20) && nnz >= 4 * segments && nnz <= 160 * segments;
+}
+__host__ __device__ inline bool strip_even(int32_t longest_row, int32_t rows, int64_t nnz) { return static_cast<int64_t>(longest_row) * rows <= 3 * nnz; }
 // Ranges a staged plan over `rows` rows with `nnz` entries aims at, 0: such a plan would never be chosen.  (Host and
 // device; `cols`: operand rows.)
 __host__ __device__ inline int32_t staged_ranges_aim(int32_t rows, int32_t max_batch)

@@ -1123,6 +1123,195 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
     });
 }
 
+// ---- product out of LDS in strips of 16 columns ------------------------------------------------------
+// The staged product in narrower tiles, for even rows of some 20 to some hundred entries a block at wide batches: a strip of kStripCols columns leaves room for kStripRows operand rows at a time
+// (128 KiB), four times as many as there, so that segments are four times as long and the operand is copied by a quarter of the work-groups.  A quad of lanes serves a row (four columns a lane),
+// a wave a set of sixteen rows, and an entry reaches the lanes of its quad by DPP quad_perm.  What all strips of a product have in common is done once, by strip_stream_kernel: it writes every entry
+// as the LDS offset of its operand row and its weight, in the order in which the waves take them, segments as long as the longest of the set, so that the product has nothing
+// to look up and nothing to mask (with its entries as they are stored, masked by every strip, 80 vector instructions a chunk: 371 us for the first matrix below, 92 for the second).
+// What bounds it: LDS and vector ALUs together, 4.2 ns a gather (62 TB/s; rows of 64 bytes meet in a bank group one time in four), of which 0.7 to 0.97 carry an entry (strip_plan in structure.hip);
+// around them a launch, 4.4 us until the first block is there, and 1 to 3 us a block for the last wave of it: the waves' priorities fall as they go through their sets, so that who is behind goes first (270 -> 257,
+// 62 -> 58).  Results are stored as the last block completes them, under the gathers of the sets that follow (49 -> 47).  Forward products at batch 1024, stream included, gathered from the L2s (staged: *) -> in
+// strips: 16384^2 at 1 % 456* -> 245, at 0.3 % 198 -> 133; 8192^2 at 0.74 % 93 -> 58; 8192 x 3072 at 1.4 % 59 -> 41; 5818 x 7889 at 1.6 %, batch 806 131* -> 63.
+constexpr int kStripJ = 8, kStripWaves = kWavesPerBlock;
+constexpr int kStripZeroRow = kStripRows * kStripCols * 4;   // as kStageZeroRow
+static_assert(kStripCols * 4 == 1 << 6 && kStripSet * 4 == kWave && kStripChunk == 8, "");
+
+// Chunk c of a segment: lane 4 q + l of the wave holds entries 8 c + 2 l and the next of row q, {offset, weight} each.  A wave per segment, a matrix per blockIdx.y.
+constexpr int kStripStreamWaves = 4;
+__global__ __launch_bounds__(kStripStreamWaves * kWave) void strip_stream_kernel(const StripStreams list)
+{
+    const StripStream &m = list.of[blockIdx.y];
+    const int at = blockIdx.x * kStripStreamWaves + wave_in_block();
+    if (at >= m.sets * m.blocks) return;
+    const int set = at / m.blocks, b = at - set * m.blocks;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int2 seg = m.segs[at];
+    const int32_t *cuts = m.cuts + (static_cast<int64_t>(set) * (m.blocks + 1) + b) * kStripSet + (lane >> 2);
+    const int lo = cuts[0], hi = cuts[kStripSet], base = strip_block_base(b, m.block_rows, m.x_rows);
+    float4 *out = m.out + static_cast<int64_t>(seg.x) * kWave + lane;
+#pragma unroll 4
+    for (int e = 0; e < seg.y; e += kStripChunk, out += kWave) {
+        const int p = lo + e + (lane & 3) * 2, p0 = min(p, m.nnz - 1), p1 = min(p + 1, m.nnz - 1);
+        const int j0 = m.indices[p0], j1 = m.indices[p1];
+        const float w0 = m.values[p0], w1 = m.values[p1];
+        *out = make_float4(__builtin_bit_cast(float, p < hi ? (j0 - base) * (kStripCols * 4) : kStripZeroRow), p < hi ? w0 : 0.f,
+                           __builtin_bit_cast(float, p + 1 < hi ? (j1 - base) * (kStripCols * 4) : kStripZeroRow), p + 1 < hi ? w1 : 0.f);
+    }
+}
+
+// every lane of a quad receives the value of the quad's lane I
+template <int I>
+__device__ __forceinline__ int quad_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, I * 0x55, 0xF, 0xF, true); }
+// acc += w of the quad's lane I times x (see fma_row_lane)
+template <int I>
+__device__ __forceinline__ void fma_quad_lane(float4 &acc, float w, const float4 &x)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %4, %5 quad_perm:[%9,%9,%9,%9] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %4, %6 quad_perm:[%9,%9,%9,%9] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %4, %7 quad_perm:[%9,%9,%9,%9] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %4, %8 quad_perm:[%9,%9,%9,%9] row_mask:0xf bank_mask:0xf"
+        : "+&v"(acc.x), "+&v"(acc.y), "+&v"(acc.z), "+&v"(acc.w)
+        : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(I));
+}
+// Entries B .. B + N - 1 of a chunk of every quad, in that order, four gathers ahead of the one whose products are added.
+template <int B, int N>
+__device__ __forceinline__ void strip_steps(const char *lds, const float4 &c, float4 &acc)
+{
+    constexpr int kAhead = N < 4 ? N : 4;
+    float4 x[N];
+    auto gather = [&](auto ic) {
+        constexpr int i = decltype(ic)::value, e = B + i;
+        x[i] = *reinterpret_cast<const float4 *>(lds + quad_lane<e / 2>(__builtin_bit_cast(int, e & 1 ? c.z : c.x)));
+    };
+    static_for(std::make_integer_sequence<int, kAhead>{}, gather);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+        constexpr int i = decltype(ic)::value, e = B + i;
+        if constexpr (i + kAhead < N) gather(std::integral_constant<int, i + kAhead>{});
+        fma_quad_lane<e / 2>(acc, e & 1 ? c.w : c.y, x[i]);
+        if constexpr (i + kAhead < N) __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+struct StripGrid {
+    int n_tiles, n_ranges, per;     // strips, ranges of sets, an eighth of the grid
+};
+__global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const SpmmArgs a, const StripGrid g)
+{
+    __shared__ float4 strip[kStripRows * kStripCols / 4 + kStripCols / 4];  // the block, then one row of zeros
+    // (neighbouring tiles share lines of the operand, all ranges of a tile its rows: a run of the list of both to an XCD)
+    const int at_block = static_cast<int>(blockIdx.x & 7) * g.per + static_cast<int>(blockIdx.x >> 3);
+    const int tile = at_block / g.n_ranges, range = at_block - tile * g.n_ranges;
+    if (tile >= g.n_tiles) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = wave_in_block();
+    const int lig = lane & 3, lig4 = lig * 4;
+    const bool col_on = tile * kStripCols + lig4 < a.batch;
+    const int col = four_columns(tile * kStripCols + lig4, a.batch);
+    const char *lds = reinterpret_cast<const char *>(strip) + lig * 16;
+    if (threadIdx.x < kStripCols / 4) strip[kStripRows * kStripCols / 4 + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);  // (visible after the first barrier)
+    constexpr auto all_j = std::make_integer_sequence<int, kStripJ>{};
+    // Set J of the wave (longest first, dealt there and back); lane J keeps its segment, block after block.
+    const int n_sets = (a.rows + kStripSet - 1) / kStripSet, round = kStripWaves * g.n_ranges, mine = wv * g.n_ranges + range, n_blocks = a.blocks.strip_blocks;
+    auto set_of = [&](int j) { return j * round + (j & 1 ? round - 1 - mine : mine); };
+    const int my_set = set_of(lane & (kStripJ - 1));
+    const int2 *my_segs = a.blocks.strip_segs + static_cast<int64_t>(my_set) * n_blocks;
+    auto segment = [&](int b) { return b < n_blocks && my_set < n_sets ? my_segs[b] : make_int2(0, 0); };
+    float4 acc[kStripJ];
+    static_for(all_j, [&](auto jc) { acc[decltype(jc)::value] = make_float4(0.f, 0.f, 0.f, 0.f); });
+    // the first two chunks of a segment are asked for a set ahead (of an empty one or a short one, others', which nothing is done with)
+    const float4 *stream = a.strip_stream + lane;
+    float4 held[2][2];
+    auto ask = [&](auto jc, const int2 &s) {
+        constexpr int j = decltype(jc)::value;
+        const float4 *p = stream + static_cast<int64_t>(__builtin_amdgcn_readlane(s.x, j)) * kWave;
+        held[j % 2][0] = p[0];
+        held[j % 2][1] = p[kWave];
+    };
+    // operand rows on their way to LDS: thread t holds four columns of rows t / 4, t / 4 + 256, ... of a block (see spmm_staged_kernel)
+    constexpr int kShare = kStripRows / 256;
+    float4 v[kShare];
+    const float *const my_x = a.X + static_cast<int64_t>(threadIdx.x >> 2) * a.ldx + col;
+    const int last_rows = a.x_rows - 256, last_i = (a.blocks.strip_block_rows >> 8) - 1;
+    auto ask_rows = [&](int i, int cb0, int last) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + min(i, last_i) * 256, last)) * a.ldx); };
+    auto put_rows = [&](int cb0) {
+#pragma unroll
+        for (int i = 0; i < kShare; ++i) strip[(min(cb0 + min(i, last_i) * 256, last_rows) - cb0) * 4 + static_cast<int>(threadIdx.x)] = v[i];
+    };
+    int2 now = segment(0), next = segment(1);
+#pragma unroll
+    for (int i = 0; i < kShare; ++i) ask_rows(i, 0, last_rows);
+    ask(std::integral_constant<int, 0>{}, now);
+    // the wave's segments of a block, the next block's rows asked for beside them; of the last block with what is done to a row once it is complete
+    auto serve = [&](int b, auto last_one) {
+        constexpr bool last = decltype(last_one)::value;
+        const int cb0 = strip_block_base(b, a.blocks.strip_block_rows, a.x_rows), cb_next = strip_block_base(b + 1, a.blocks.strip_block_rows, a.x_rows);
+        const int2 after = segment(b + 2);
+        int row[kStripJ / 4];     // lane k of a quad: of sets k, k + 4
+        float bias[kStripJ / 4];
+        lds_barrier();  // the previous block's gathers are done
+        put_rows(cb0);
+        if constexpr (last)
+#pragma unroll
+            for (int k = 0; k < kStripJ / 4; ++k) {
+                const int set = set_of(k * 4 + lig);
+                row[k] = set < n_sets ? a.blocks.strip_rows[set * kStripSet + (lane >> 2)] : -1;
+                bias[k] = a.bias ? a.bias[max(row[k], 0)] : 0.f;
+            }
+        lds_barrier();
+        static_for(all_j, [&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            if constexpr (!last && j < kShare / 2) {
+                ask_rows(2 * j, cb_next, last_rows);
+                ask_rows(2 * j + 1, cb_next, last_rows);
+            }
+            if constexpr (j + 1 < kStripJ) ask(std::integral_constant<int, j + 1>{}, now);
+            else if constexpr (!last) ask(std::integral_constant<int, 0>{}, next);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (j % 2 == 0) __builtin_amdgcn_s_setprio(3 - j / 2);   // (whoever is behind goes first)
+            int n = __builtin_amdgcn_readlane(now.y, j);
+            if (n > 0) {
+                float4 c = held[j % 2][0], d = held[j % 2][1];
+                const float4 *p = stream + static_cast<int64_t>(__builtin_amdgcn_readlane(now.x, j)) * kWave + 2 * kWave;
+                for (; n > 16; n -= 8, p += kWave) {
+                    const float4 e = *p;
+                    strip_steps<0, 8>(lds, c, acc[j]);
+                    c = d;
+                    d = e;
+                }
+                if (n > 8) {
+                    strip_steps<0, 8>(lds, c, acc[j]);
+                    c = d;
+                    n -= 8;
+                }
+                // (one if after the other: see staged_half)
+                int ways = n > 6 ? 1 : n > 4 ? 6 : n > 2 ? 2 : 8;
+                asm("" : "+s"(ways));
+                if (ways & 1) strip_steps<0, 8>(lds, c, acc[j]);
+                if (ways & 2) strip_steps<0, 4>(lds, c, acc[j]);
+                if (ways & 4) strip_steps<4, 2>(lds, c, acc[j]);
+                if (ways & 8) strip_steps<0, 2>(lds, c, acc[j]);
+            }
+            if constexpr (last) {
+                const int r = quad_lane<j % 4>(row[j / 4]);
+                const float bb = __builtin_bit_cast(float, quad_lane<j % 4>(__builtin_bit_cast(int, bias[j / 4])));   // (all lanes: moves read from active ones only)
+                if (r >= 0 && col_on) {
+                    float4 y = make_float4(acc[j].x + bb, acc[j].y + bb, acc[j].z + bb, acc[j].w + bb);
+                    if (a.relu) y = make_float4(y.x > 0.f ? y.x : 0.f, y.y > 0.f ? y.y : 0.f, y.z > 0.f ? y.z : 0.f, y.w > 0.f ? y.w : 0.f);
+                    if (a.YM) y = keep_where_positive(y, ld4(a.YM + static_cast<int64_t>(r) * a.ldym + col));
+                    st4(a.Y + static_cast<int64_t>(r) * a.ldy + col, y);
+                }
+            }
+        });
+        now = next;
+        next = after;
+    };
+    for (int b = 0; b + 1 < n_blocks; ++b) serve(b, std::false_type{});
+    serve(n_blocks - 1, std::true_type{});
+}
+
 // ---------------------------------------------------------------------------------------
 // SDDMM.  The row of dZ stays in registers; the wave is cut into 64/G groups of G lanes, each
 // group computing the dot product of one stored entry at a time (lanes along the batch, 4
@@ -2925,6 +3114,52 @@ int spmm_split_group(const SpmmArgs &a)
     return g;
 }
 
+bool spmm_staged_ok(const SpmmArgs &a);
+// The product in strips, us, with the ranges that make it shortest: rounds of 256 work-groups (one fits a compute unit), each the steps that its LDS serves, the sets that a wave takes one after the
+// other, and the copy of the operand's strip; before them the stream.  Root mean square 7 % from 330 uniform matrices of 512 to 16384 rows, 1024 to 16384 columns, 0.1 to 10 %, batch 193 to 1024.
+struct StripPlan {
+    StripGrid grid;
+    double us;
+};
+static StripPlan strip_plan(const SpmmArgs &a)
+{
+    StripPlan p{};
+    p.grid.n_tiles = (a.batch + kStripCols - 1) / kStripCols;
+    const int64_t sets = (static_cast<int64_t>(a.rows) + kStripSet - 1) / kStripSet, least = (sets + kStripWaves * kStripJ - 1) / (kStripWaves * kStripJ);
+    const double steps = a.blocks.strip_steps, per_set = steps / static_cast<double>(sets);
+    for (int64_t more = 0, first = (p.grid.n_tiles * least + 255) / 256; more < 4; ++more) {   // (of the ranges that a number of rounds holds the most)
+        const int64_t r = std::max(least, 256 * (first + more) / p.grid.n_tiles);
+        const double rounds = static_cast<double>((p.grid.n_tiles * r + 255) / 256), most = static_cast<double>((sets + kStripWaves * r - 1) / (kStripWaves * r));
+        const double us = rounds * (1.8 + 3.0e-3 * steps / static_cast<double>(r) + 12.7e-3 * most * per_set + 0.5e-3 * a.x_rows + 2.6 * a.blocks.strip_blocks);
+        if (p.grid.n_ranges == 0 || us < p.us) { p.us = us; p.grid.n_ranges = static_cast<int>(r); }
+    }
+    p.us += 6.3 + 0.64e-3 * a.blocks.strip_chunks;
+    p.grid.per = static_cast<int>((static_cast<int64_t>(p.grid.n_tiles) * p.grid.n_ranges + 7) / 8);
+    return p;
+}
+// Whether it pays: against an estimate of the kernel that would run otherwise (staged, in column tiles or over the whole batch; 5, 17 and 10 % root mean square from the same matrices).
+static bool strip_pays(const SpmmArgs &a)
+{
+    const double nnz = a.nnz * 1e-6, x_rows = a.x_rows * 1e-6, rows = a.rows * 1e-6, operand = 4. * x_rows * a.batch;   // (millions)
+    double other;
+    if (spmm_staged_ok(a)) {
+        other = 8.7 + (a.batch + kStageCols - 1) / kStageCols * (3.2 * nnz + 13. * rows * a.blocks.staged_cblocks + 18.7 * a.blocks.staged_ranges * x_rows);
+    } else {
+        if (a.rows < kPackMinRows) return false;   // (few sets, which the estimate is too kind to: 1223 x 4592 at 10 %, batch 466 46.8 -> 56.3)
+        int tg = spmm_tile_group(a);
+        if (tg == 0 && packed_tiles_pay(a)) tg = 16;
+        if (tg > 0) other = 6.2 + nnz * ((a.batch + tg * 4 - 1) / (tg * 4)) * tg * 16. * (0.036 + 0.015 * std::min(x_rows * tg * 16. / 4.194304, 2.)) + 0.2 * operand - 0.4 * rows * a.batch;
+        else other = 4.5 + 4. * nnz * a.batch * (0.031 + 0.09 * std::min(operand / 32., 1.)) + 0.15 * operand + 0.4 * rows * a.batch;
+    }
+    return strip_plan(a).us < 0.88 * other;
+}
+bool spmm_strip_ok(const SpmmArgs &a)
+{
+    if (!a.blocks.strip_segs || !a.strip_stream || a.XM || a.batch <= kStripFromBatch) return false;
+    const int64_t groups = (static_cast<int64_t>(a.rows) + kStripSet * kStripWaves * kStripJ - 1) / (kStripSet * kStripWaves * kStripJ) * ((a.batch + kStripCols - 1) / kStripCols);
+    return groups < (1 << 28) && (a.blocks.strip_preferred || strip_pays(a));
+}
+
 bool spmm_staged_ok(const SpmmArgs &a)
 {
     if (a.x_rows < 64 || a.nnz < 64) return false;  // (it brings 64 operand rows at a time, and reads entries up to 32 past the first)
@@ -3479,6 +3714,25 @@ static int spmv_rows_split(const SpmmArgs &a)
     return (a.blocks.staged_longest_row >> lg) <= 16 * 4 * kWave ? lg : -1;
 }
 
+bool spmm_takes_strip(const SpmmArgs &a)
+{
+    return a.rows > 0 && a.batch > 4 && a.blocks.n_blocks > 0 && !spmm_full_rows_ok(a) && !spmm_dense_rows_ok(a) && spmm_strip_ok(a);
+}
+
+hipError_t launch_strip_streams(const SpmmArgs *list, int n, hipStream_t s)
+{
+    StripStreams all{};
+    unsigned most = 0;
+    for (int k = 0; k < n; ++k) {
+        const SpmmArgs &a = list[k];
+        all.of[k] = StripStream{a.blocks.strip_segs, a.blocks.strip_cuts, a.indices, a.values, a.strip_stream, (a.rows + kStripSet - 1) / kStripSet,
+                                a.blocks.strip_blocks, a.blocks.strip_block_rows, a.x_rows, a.nnz};
+        most = std::max(most, static_cast<unsigned>((all.of[k].sets * all.of[k].blocks + kStripStreamWaves - 1) / kStripStreamWaves));
+    }
+    hipLaunchKernelGGL(strip_stream_kernel, dim3(most, n), dim3(kStripStreamWaves * kWave), 0, s, all);
+    return hipGetLastError();
+}
+
 hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
 {
     if (a.rows <= 0 || a.batch <= 0 || a.blocks.n_blocks <= 0) return hipSuccess;
@@ -3516,7 +3770,17 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         SpmmArgs others = a;
         others.blocks = a.split->others;
         others.split = nullptr;
+        others.blocks.strip_segs = nullptr;   // (its rows are all, the dense ones too)
         return launch_spmm(others, s);
+    }
+    if (spmm_strip_ok(a)) {
+        const StripGrid g = strip_plan(a).grid;
+        if (!a.strip_ready) {
+            const hipError_t e = launch_strip_streams(&a, 1, s);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(spmm_strip_kernel, dim3(8u * static_cast<unsigned>(g.per)), dim3(kStripWaves * kWave), 0, s, a, g);
+        return hipGetLastError();
     }
     if (spmm_staged_ok(a)) {
         const int n_tiles = (a.batch + kStageCols - 1) / kStageCols;
@@ -3539,6 +3803,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
                 }
             }
             rest.blocks.staged_rows = nullptr;
+            rest.blocks.strip_segs = nullptr;
             rest.blocks.n_short = 0;
             rest.blocks.waves = a.blocks.rest_waves;
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
@@ -3563,6 +3828,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
             rest.blocks.n_short = 0;
             rest.blocks.n_long_blocks = 0;   // (nothing left to split off)
             rest.blocks.staged_rows = nullptr;
+            rest.blocks.strip_segs = nullptr;
             const hipError_t e = launch_spmm(rest, s);
             if (e != hipSuccess) return e;
             switch (sg) {

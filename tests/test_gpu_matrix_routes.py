@@ -539,3 +539,103 @@ def test_one_to_four_examples_on_many_entries(nb, oracle, rows, cols, density, b
         check_layer(nb, oracle, layer_case(rows, cols, density, seed=rows, relu=relu), batch, ld=batch)
     finally:
         nb.nerva_set_dense_threshold(0.4)
+
+
+def strips_case(rows, cols, lens, seed):
+    """A layer whose row i has lens(i) entries, at most `cols`."""
+    rng = np.random.default_rng(seed)
+    per_row = [np.sort(rng.choice(cols, min(cols, int(lens(i))), replace=False)) for i in range(rows)]
+    indptr = np.concatenate([[0], np.cumsum([len(r) for r in per_row])]).astype(np.int32)
+    indices = np.concatenate(per_row).astype(np.int32)
+    return wl.SparseLayerData(rows, cols, indptr, indices, rng.standard_normal(len(indices)).astype(np.float32), rng.standard_normal(rows).astype(np.float32), bool(seed % 2))
+
+
+@pytest.fixture()
+def prefer_strips(nb):
+    nb.nerva_set_partition_mode(nb.NERVA_PARTITION_PREFER_STRIPS)
+    yield
+    nb.nerva_set_partition_mode(nb.NERVA_PARTITION_BALANCED)
+
+
+@pytest.mark.parametrize("rows,cols,lens,batch,ld", [
+    (1, 256, lambda i: 3, 193, None), (17, 257, lambda i: i, 194, 195), (16, 300, lambda i: 0 if i else 1, 200, None),     # the fewest; empty rows; one entry
+    (300, 2048, lambda i: i % 41, 208, None), (255, 2049, lambda i: i % 75, 207, 207),                                    # one block and two; every length of a chunk's rest
+    (2049, 4097, lambda i: 20 + i % 7, 193, 193), (700, 3072, lambda i: 40 if i % 3 else 90, 321, None),                  # three blocks; a set more than a range of a single one
+    (130, 9001, lambda i: 1200 - i, 195, 199), (4500, 700, lambda i: 12, 1023, None), (900, 1500, lambda i: 30, 1026, 1027),   # long segments; batches beyond 1024
+])
+def test_product_in_strips(nb, oracle, prefer_strips, rows, cols, lens, batch, ld):
+    check_layer(nb, oracle, strips_case(rows, cols, lens, rows + batch), batch, ld=ld, backward=False)
+
+
+def test_product_in_strips_where_the_rule_takes_it(nb, oracle):
+    """The layer sizes at which strips are the library's own choice, bound for a wider batch than it is called with; then another pattern, and the weights of that changed."""
+    rows, cols, batch = 6001, 2999, 811
+    lay = layer_case(rows, cols, 0.014, seed=3, relu=True)
+    check_layer(nb, oracle, lay, batch, ld=813, max_batch=1024, backward=False)
+    check_layer(nb, oracle, lay, 64, max_batch=1024, backward=False)
+
+
+def test_product_in_strips_keeps_a_non_finite_operand_row_to_the_rows_that_read_it(nb, oracle, prefer_strips):
+    """As of the staged product: lanes without an entry gather a row of zeros and not the first operand row of a block (0; 4608 - 1536, where the last block starts; 1536)."""
+    import torch
+    rows, cols, batch, bad = 500, 4600, 200, (0, 1536, 3064, 3072, 4599)
+    lay = strips_case(rows, cols, lambda i: i % 50, 8)
+    X = np.random.default_rng(5).standard_normal((cols, batch)).astype(np.float32)
+    X[list(bad)] = np.inf
+    L = nb.SparseLinear(lay, max_batch=batch)
+    Yd = nb.dense(rows, batch)
+    nb.sparse_linear_forward(L.handle, nb.to_dense(X), Yd, batch)
+    torch.cuda.synchronize()
+    Y = Yd.cpu().numpy()
+    touched = np.zeros(rows, dtype=bool)
+    touched[np.repeat(np.arange(rows), np.diff(lay.indptr))[np.isin(lay.indices, bad)]] = True
+    assert touched.any() and np.isfinite(Y[~touched]).all() and not np.isfinite(Y[touched]).all(axis=1).any()
+    X[list(bad)] = 0
+    Yr, S = oracle.spmm(rows, cols, lay.indptr, lay.indices, lay.values, lay.bias, X, False)
+    close(Y[~touched], Yr[~touched], S[~touched], what="rows that do not read them")
+    L.close()
+
+
+def test_training_step_in_strips_on_new_patterns(nb, oracle, prefer_strips):
+    """Both hidden layers in strips from one launch of streams, fused and apart, then on other patterns: steps of either pipeline stay close, and replays of a graph give what eager steps give."""
+    import torch
+    sizes, batch = [400, 600, 520, 10], 200
+    rng = np.random.default_rng(0)
+    labels = torch.from_numpy(rng.integers(0, 10, batch).astype(np.int32)).cuda()
+    X = nb.to_dense(rng.standard_normal((sizes[0], batch)).astype(np.float32))
+    data = wl.make_mlp(sizes, sparsity=0.7)
+    mlps = [nb.MLP(data, batch, f) for f in (nb.NERVA_MLP_DEFAULT, nb.NERVA_MLP_UNFUSED)]
+    for density in (None, 0.2):
+        if density:
+            for l in (0, 1):
+                new = strips_case(sizes[l + 1], sizes[l], lambda i: int(density * sizes[l]) + i % 9, l)
+                for m in mlps:
+                    L = m.layers[l]
+                    L.indptr, L.indices, L.values = (torch.from_numpy(np.array(a)).cuda() for a in (new.indptr, new.indices, new.values))
+                    L.velocity = torch.zeros_like(L.values)
+                    nb.sparse_linear_rebind(L.handle, L.values.numel(), L.indptr, L.indices, L.values)
+                    nb.mlp_rebind_velocity(m.handle, l, L.velocity)
+        for _ in range(3):
+            for m in mlps:
+                m.train_step(X, labels, batch, 0.01, 0.9)
+        torch.cuda.synchronize()
+        assert np.isclose(mlps[0].loss.item(), mlps[1].loss.item(), rtol=1e-5)
+        for a, b in zip(mlps[0].layers, mlps[1].layers):
+            close(a.values.cpu().numpy(), b.values.cpu().numpy(), np.full(b.values.numel(), 10 * b.values.abs().max().item()), what="weights")
+    m = mlps[0]
+    m.forward(X, batch)
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        m.forward(X, batch)
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            out = m.forward(X, batch)
+    for k in range(3):
+        m.layers[0].values.mul_(1.1)
+        want = m.forward(X, batch).clone()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, :batch], want[:, :batch]), k
+    m.close(); mlps[1].close()
