@@ -38,19 +38,41 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)); }
 __device__ __forceinline__ int lanes_below(uint64_t mask) { return __popcll(mask & ((1ull << lane_id()) - 1)); }
 
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v)
+// Sums, prefix sums and maxima over a wave, all lanes active.  Those of 32 bits by moves between lanes (DPP): a prefix sum through the LDS crossbar is six round trips of some 100 cycles, and the set-up
+// kernels are chains of them (8192^2 at 0.74 %: bin_place_kernel 20.7 -> 16.1 us, plan_kernel, whose first thread no longer writes all it reports alone either, 22.2 -> 18.1).
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int32_t lanes_moved(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }   // (0 where no lane is named)
+template <typename F>
+__device__ __forceinline__ int32_t wave_scan(int32_t v, F &&f)   // f(0, v) = v
+{
+    v = f(lanes_moved<0x111>(v), v);        // row_shr 1, 2, 4, 8: within rows of 16
+    v = f(lanes_moved<0x112>(v), v);
+    v = f(lanes_moved<0x114>(v), v);
+    v = f(lanes_moved<0x118>(v), v);
+    v = f(lanes_moved<0x142, 0xA>(v), v);   // the last lane of rows 0 and 2 into rows 1 and 3
+    return f(lanes_moved<0x143, 0xC>(v), v);   // that of row 1 into rows 2 and 3
+}
+__device__ __forceinline__ int32_t last_lane(int32_t v) { return __builtin_amdgcn_readlane(v, kWave - 1); }
+__device__ __forceinline__ int32_t wave_inclusive(int32_t v)
+{
+    return wave_scan(v, [](int32_t a, int32_t b) { return a + b; });
+}
+__device__ __forceinline__ int32_t wave_sum(int32_t v) { return last_lane(wave_inclusive(v)); }
+__device__ __forceinline__ int32_t wave_max(int32_t v)   // v >= 0
+{
+    return last_lane(wave_scan(v, [](int32_t a, int32_t b) { return max(a, b); }));
+}
+__device__ __forceinline__ int64_t wave_sum(int64_t v)
 {
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) v += __shfl_xor(v, d, kWave);
     return v;
 }
-template <typename T>
-__device__ __forceinline__ T wave_inclusive(T v)
+__device__ __forceinline__ int64_t wave_inclusive(int64_t v)
 {
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
-        const T y = __shfl_up(v, d, kWave);
+        const int64_t y = __shfl_up(v, d, kWave);
         if (lane_id() >= d) v += y;
     }
     return v;
@@ -181,7 +203,7 @@ __global__ __launch_bounds__(kSetupBlock) void bin_scan_kernel(const MirrorArgs 
         const int32_t v = t < m.tiles ? c[t] : 0;
         const int32_t incl = wave_inclusive(v);
         if (t < m.tiles) c[t] = run + incl - v;
-        run += __shfl(incl, kWave - 1, kWave);
+        run += last_lane(incl);
     }
     if (lane_id() == 0) m.bin_total[bin] = run;
 }
@@ -291,7 +313,7 @@ __global__ __launch_bounds__(kPlaceBlock) void bin_place_kernel(const MirrorArgs
                 col_first[c] = base + run + incl - v;
                 if (c0 + c < c_end) m.indptr_t[c0 + c] = base + run + incl - v;
             }
-            run += __shfl(incl, kWave - 1, kWave);
+            run += last_lane(incl);
         }
         if (lane == 0 && bin == m.bins - 1) {
             m.indptr_t[c_end] = base + n;
@@ -315,7 +337,7 @@ __global__ __launch_bounds__(kPlaceBlock) void bin_place_kernel(const MirrorArgs
                 const int32_t v = w < words ? __popc(bits[c * words + w]) : 0;
                 const int32_t incl = wave_inclusive(v);
                 if (w < words) before[c * words + w] = run + incl - v;
-                run += __shfl(incl, kWave - 1, kWave);
+                run += last_lane(incl);
             }
             if (lane == 0) col_run[c] = run;
         }
@@ -357,15 +379,15 @@ __device__ __forceinline__ int32_t blocks_of(const int32_t (&cls)[5])
 // One orientation per work-group.  The rows are dealt to the 16 waves in contiguous chunks; a wave walks its chunk
 // 64 rows at a time, so that prefix sums in row order need one exchange of the waves' totals.  What the walks read --
 // the row lengths, then the cuts and slots of the staged plan -- lies in LDS as far as it fits (kPlanLds): from memory
-// every step of every walk was a round trip (59 us for 8192 rows of 60 entries, 21 us from LDS).
+// every step of every walk was a round trip (59 us for 8192 rows of 60 entries, 22 us from LDS, 18 with the waves' totals by DPP and LDS atomics).
 __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) void plan_kernel(const PlanArgs A)
 {
     __shared__ int32_t hist[kWaves][256];
     __shared__ int32_t tot[256];
     __shared__ int64_t wtot[kWaves][8];
     extern __shared__ int32_t plan_lds[];
-    __shared__ int32_t cnt[16];
-    __shared__ int64_t cnt64;
+    __shared__ int32_t cnt[16], hot_cnt;
+    __shared__ PlanCounts C;   // (written by the first thread)
     __shared__ int32_t dense_cnt[3];   // rows, their entries, and the length from which the staged plan leaves rows out
     const PlanSide &S = A.side[blockIdx.x];
     const int32_t n = S.rows, nnz = A.nnz, tid = threadIdx.x;
@@ -379,12 +401,14 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const int64_t lds_arrays = kPlanLds / 4 / max(n, 1);
     int32_t *lens = lds_arrays >= 1 ? plan_lds : S.work.lens;
     int32_t *cut = lds_arrays >= 2 ? plan_lds + n : S.work.cut, *sl = lds_arrays >= 3 ? plan_lds + 2 * n : S.work.slots;
+    if (tid < 16) cnt[tid] = 0;
+    if (tid == 16) hot_cnt = 0;
     for (int32_t i = tid; i < n; i += kBig) lens[i] = indptr[i + 1] - indptr[i];
     __syncthreads();
 
     // classes, huge rows, totals
     int32_t long_cls[5] = {0, 0, 0, 0, 0}, rest_cls[5] = {0, 0, 0, 0, 0}, longest = 0, n_le = 0, n_huge = 0, parts = 0;
-    int64_t long_nnz = 0;
+    int32_t long_nnz = 0;
     for (int32_t i0 = k_lo; i0 < k_hi; i0 += kWave) {
         const int32_t i = i0 + lane;
         const bool ok = i < k_hi;
@@ -402,26 +426,17 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             rest_cls[k] += __popcll(__ballot(ok && !is_long && lg == k));
         }
     }
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) longest = max(longest, __shfl_xor(longest, d, kWave));
+    longest = wave_max(longest);
     long_nnz = wave_sum(long_nnz);
     parts = wave_sum(parts);
-    if (lane == 0) {
-        int32_t *h = hist[wv];
-        h[0] = longest; h[1] = n_le; h[2] = n_huge; h[3] = parts;
+    {
+        // lane k of a wave adds its k-th total
+        int32_t v = lane == 1 ? n_le : lane == 2 ? n_huge : lane == 3 ? parts : long_nnz;
 #pragma unroll
-        for (int k = 0; k < 5; ++k) { h[4 + k] = long_cls[k]; h[9 + k] = rest_cls[k]; }
-        wtot[wv][0] = long_nnz;
-    }
-    __syncthreads();
-    if (tid < 14) {
-        int32_t v = 0;
-        for (int w = 0; w < kWaves; ++w) v = tid == 0 ? max(v, hist[w][0]) : v + hist[w][tid];
-        cnt[tid] = v;
-    } else if (tid == 14) {
-        int64_t v = 0;
-        for (int w = 0; w < kWaves; ++w) v += wtot[w][0];
-        cnt64 = v;
+        for (int k = 0; k < 5; ++k) v = lane == 4 + k ? long_cls[k] : lane == 9 + k ? rest_cls[k] : v;
+        if (lane == 0) atomicMax(&cnt[0], longest);
+        else if (lane < 15) atomicAdd(&cnt[lane], v);
+        if (lane == 2 || lane == 3) hist[wv][lane] = v;
     }
     __syncthreads();
     auto total_of = [&](int k) { return __builtin_amdgcn_readfirstlane(cnt[k]); };
@@ -429,7 +444,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     n_le = total_of(1);
     n_huge = total_of(2);
     parts = total_of(3);
-    long_nnz = cnt64;
+    long_nnz = total_of(14);
     int32_t huge_before = 0, parts_before = 0;
     if (n_huge > 0)
         for (int w = 0; w < wv; ++w) {
@@ -448,7 +463,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             const uint64_t mask = __ballot(huge);
             if (huge) S.tables.huge_rows[huge_before + lanes_below(mask)] = make_int4(i, parts_before + incl - mine, mine, 0);
             huge_before += __popcll(mask);
-            parts_before += __shfl(incl, kWave - 1, kWave);
+            parts_before += last_lane(incl);
         }
 
     // rows long enough for the matrix instructions: listed where they hold enough of the entries
@@ -509,11 +524,13 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         for (int32_t k = k_lo + lane; k < k_hi; k += kWave) atomicAdd(&hist[wv][digit(item(k))], 1);
         __syncthreads();
         if (tid < 256) {
-            int32_t run = 0;
+            int32_t run = 0, v[kWaves];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) v[w] = hist[w][tid];
+#pragma unroll
             for (int w = 0; w < kWaves; ++w) {
-                const int32_t v = hist[w][tid];
                 hist[w][tid] = run;
-                run += v;
+                run += v[w];
             }
             tot[tid] = run;
         }
@@ -523,14 +540,17 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             for (int d0 = 0; d0 < 256; d0 += kWave) {
                 const int32_t v = tot[d0 + lane], incl = wave_inclusive(v);
                 tot[d0 + lane] = run + incl - v;
-                run += __shfl(incl, kWave - 1, kWave);
+                run += last_lane(incl);
             }
         }
         __syncthreads();
+        // (in the last pass the entries of the first rows, the most referenced ones of the other orientation's gathers, are counted as well)
+        const int32_t top = pass + 1 == passes ? min(n, kHotRows) : 0;
+        int32_t hot = 0;
         for (int32_t i0 = k_lo; i0 < k_hi; i0 += kWave) {
             const bool ok = i0 + lane < k_hi;
-            const int32_t r = ok ? item(i0 + lane) : 0;
-            const int d = ok ? digit(r) : 0;
+            const int32_t r = ok ? item(i0 + lane) : 0, len = ok ? lens[r] : 0;
+            const int d = ok ? ((longest - len) >> shift) & 255 : 0;
             uint64_t same = __ballot(ok);
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
@@ -539,29 +559,19 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
             if (ok) {
                 const int32_t at = hist[wv][d], rank = lanes_below(same);
-                to[tot[d] + at + rank] = r;
+                const int32_t place = tot[d] + at + rank;
+                to[place] = r;
+                if (place < top) hot += len;
                 if (rank == 0) hist[wv][d] = at + __popcll(same);   // (after every lane of the wave has read it)
             }
+        }
+        if (top > 0) {
+            hot = wave_sum(hot);
+            if (lane == 0) atomicAdd(&hot_cnt, hot);
         }
         __syncthreads();
         int32_t *x = from; from = to; to = x;
     }
-    const int32_t *order = S.work.order;
-
-    // entries of the most referenced rows (for the other orientation's gathers)
-    {
-        const int32_t top = min(n, kHotRows);
-        int64_t sum = 0;
-        for (int32_t k = tid; k < top; k += kBig) sum += lens[order[k]];
-        sum = wave_sum(sum);
-        if (lane == 0) wtot[wv][2] = sum;
-    }
-    __syncthreads();
-    int64_t hot = 0;
-    for (int w = 0; w < kWaves; ++w) hot += wtot[w][2];
-    __syncthreads();
-
-    PlanCounts &C = *S.work.counts;   // (written by the first thread)
     const int32_t n_short = n_le >= kPackMinRows && nnz > 0 && !row_split ? n_le : 0;
     if (tid == 0) {
         int32_t cls[3][5];
@@ -585,7 +595,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 #pragma unroll
             for (int k = 0; k < 5; ++k) C.cls[v][k] = cls[v][k];
         C.longest_row = longest;
-        C.hot_nnz = static_cast<int32_t>(hot);
+        C.hot_nnz = hot_cnt;
         C.n_dense = dense_cnt[0];
         C.dense_nnz = dense_cnt[1];
         C.long_nnz = static_cast<int32_t>(long_nnz);
@@ -647,11 +657,8 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             if (in) longest_in = max(longest_in, len);
         }
         slots = wave_sum(slots);
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            longest_single = max(longest_single, __shfl_xor(longest_single, d, kWave));
-            longest_in = max(longest_in, __shfl_xor(longest_in, d, kWave));
-        }
+        longest_single = wave_max(longest_single);
+        longest_in = wave_max(longest_in);
         if (lane == 0) { wtot[wv][4] = slots; wtot[wv][5] = longest_single; wtot[wv][7] = longest_in; }
         __syncthreads();
         slots = 0;
@@ -676,7 +683,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
             k_at += __popcll(mask);
             done += __shfl(c_incl, kWave - 1, kWave);
-            slots += __shfl(s_incl, kWave - 1, kWave);
+            slots += last_lane(s_incl);
         }
         __syncthreads();
         // a range begins where the cut does, and after every kStageRangeFill slots of it: a thread per cut finds its
@@ -716,8 +723,15 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         C.staged_rows = n_cov;
         C.staged_nnz = static_cast<int32_t>(want == 0 ? 0 : (min_len > 0 ? long_nnz : nnz) - dense_nnz);
         C.staged_longest_share = longest_share;
-        A.result->plan[blockIdx.x] = C;
         if (S.strip_blocks > 0) S.work.strip_count[0] = S.work.strip_count[1] = 0;
+    }
+    __syncthreads();
+    // (a word a thread: pinned memory is a long way off)
+    static_assert(sizeof(PlanCounts) / 4 <= kWave, "");
+    if (tid < sizeof(PlanCounts) / 4) {
+        const int32_t word = reinterpret_cast<const int32_t *>(&C)[tid];
+        reinterpret_cast<int32_t *>(S.work.counts)[tid] = word;
+        reinterpret_cast<int32_t *>(&A.result->plan[blockIdx.x])[tid] = word;
     }
 }
 
