@@ -101,6 +101,8 @@ struct PatternBuffers {
     size_t row_partial_floats = 0;
     int32_t *whole_staged = nullptr;   // staged plan of all rows beside that of the rows that are not dense
     size_t whole_staged_ints = 0;
+    int32_t *hot = nullptr;         // entry | at | count of RowBlocks::hot_*
+    size_t hot_ints = 0;
     DenseSplit split{};             // views into plan_mem and row_table
 };
 
@@ -601,6 +603,7 @@ void free_pattern_buffers(PatternBuffers &b)
     (void)hipFree(b.row_table);
     (void)hipFree(b.row_partial);
     (void)hipFree(b.whole_staged);
+    (void)hipFree(b.hot);
     b = PatternBuffers{};
 }
 
@@ -846,6 +849,8 @@ static bool use_dense(const nerva_layer *l, int32_t batch) { return l->dense_on 
 // tickets of the huge rows of W (side 0) or of its mirror (side 1): rows of the two alternate
 static int32_t *tickets_of(const nerva_layer *l, int side) { return l->tickets ? l->tickets + side * huge_row_tickets(l->scratch_ld) : nullptr; }
 
+static float *hot_values_of(const nerva_layer *l) { return l->plan_t.hot_entry ? reinterpret_cast<float *>(l->cur.hot) + 3 * static_cast<size_t>(round_up(l->nnz, 64)) : nullptr; }
+
 static const DenseSplit *split_of(const nerva_layer *l) { return l->cur.split.rows.n > 0 ? &l->cur.split : nullptr; }
 
 // Message for the status word of the device-side CSR check (bind_check_kernel).
@@ -1005,6 +1010,13 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         if (!thin_rows_pay_somewhere(B.split, cols) || !reserve_dense_rows(B, want)) B.split = DenseSplit{};
     }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
+    if (hot_order_wanted(rows, cols, nnz, max_batch, out->plan_t.hot_share) && asked == NERVA_PARTITION_BALANCED && reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
+        RowBlocks &v = out->plan_t;
+        HIP_TRY(launch_hot_order(out->plan.rows_by_length, rows, B.indptr_t, m.indices_t, cols, m.perm, W + work_at[0], B.hot, B.hot + n64, B.hot + 2 * n64, p.side[1].tables.rows_by_length,
+                                 reinterpret_cast<int4 *>(B.hot + 4 * n64), s));
+        v.hot_entry = B.hot; v.hot_at = B.hot + n64; v.hot_perm = B.hot + 2 * n64; v.hot_sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.hot_rows = out->plan.rows_by_length;
+        more_work = true;
+    }
 
     // scratch buffers of the products (they hold nothing between calls, the tickets zeros: grown in place, so that the old
     // pattern's products find them whatever fails from here on)
@@ -1013,6 +1025,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         // that they are not worth it), below which the kernels without them stay
         int32_t tiles = partial_tiles_wanted(out->plan, out->plan_t, rows, cols, nnz, max_batch);
         if ((out->plan.staged_rows || B.split.others.staged_rows) && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
+        if (out->plan_t.hot_entry) tiles = std::max(tiles, (max_batch + 63) / 64);
         out->partial_db_at = round_up(nnz, 64);
         out->partial_stride = out->partial_db_at + round_up(rows, 64);
         const size_t slice = static_cast<size_t>(out->partial_stride);
@@ -1268,6 +1281,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
         if (!form_dz) { a.values = layer->values; a.values_t = layer->values_t; }   // (where the mirror values are not up to date yet)
         if (layer->cur.has_table) { a.table = reinterpret_cast<const uint2 *>(layer->cur.table); a.table_words = table_words(layer); }
         a.split = split_of(layer);
+        a.hot_values = hot_values_of(layer);
         return a;
     };
     // (a small layer takes both gradients, and the mask, in one launch)
@@ -1626,6 +1640,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         g.partial_db_at = ly->partial_db_at; g.partial_tiles = ly->partial_tiles;
         if (ly->cur.has_table) { g.table = reinterpret_cast<const uint2 *>(ly->cur.table); g.table_words = table_words(ly); }
         g.split = split_of(ly);
+        g.hot_values = hot_values_of(ly);
         if ((head || ce_fused) && l == n - 1 && loss_out) { g.loss_cols = mlp->head_scratch; g.loss_out = loss_out; g.loss_n = batch; }
         if (fused) {
             g.fused = 1; g.nesterov = nesterov; g.lr = lr; g.momentum = momentum;

@@ -64,6 +64,13 @@ struct RowBlocks {
     int32_t strip_blocks, strip_block_rows;
     int32_t strip_chunks, strip_steps;   // of the stream; the sum of the longest segments
     int32_t strip_preferred;             // measurement aid: take it wherever it can run
+    // Of a mirror, where a few rows of the matrix hold most of its entries (backward_hot_kernel), or nullptr: the entries of a mirror row in another order, those of the
+    // kHotRowsLds longest rows of the matrix first.
+    const int32_t *hot_entry;      // [nnz] 256 times the row's place among the longest, for the hot ones of a mirror row; the row itself for the others
+    const int32_t *hot_at;         // [nnz] the entry's position in the mirror
+    const int4 *hot_sets;          // [mirror rows, padded as rows_by_length] {row or -1, first entry, entries, hot ones}: longest first, those of about one length by their hot entries
+    const int32_t *hot_perm;       // [nnz] CSR position
+    const int4 *hot_rows;          // the matrix's rows_by_length
 };
 
 // Strips: kStripRows operand rows of kStripCols columns lie in LDS at a time; the operand's blocks are of equal size, a multiple of 256 rows.
@@ -84,6 +91,7 @@ __host__ __device__ inline int32_t strip_block_base(int32_t b, int32_t block_row
     return b * block_rows < last ? b * block_rows : last;
 }
 
+constexpr int32_t kHotRowsLds = 512;
 constexpr int32_t kStageRows = 512;      // operand rows held in LDS at a time
 constexpr int32_t kStageCols = 64;       // columns of the operand (examples) per work-group
 constexpr int32_t kStageJ = 8;           // rows per row of 16 lanes
@@ -274,6 +282,7 @@ struct SddmmArgs {
     int32_t table_words;
     const DenseSplit *split;        // (for the launch) or nullptr
     const DenseSplit *split_done;   // (set by the launch) the dense rows are served already
+    float *hot_values;              // scratch [nnz] of backward_hot_kernel, or nullptr
     int32_t chain_lanes;            // 1: the sums of chain_kernel, for a step whose launches are kept apart
 };
 // Column-tile width (in columns) the products use when their gathered operand has x_rows rows and
@@ -309,6 +318,8 @@ struct BackwardArgs {
     float lr, momentum;
     float *w, *velocity, *w_t;   // values[], velocity[] (CSR order), mirror values
     float *bias, *bias_velocity;
+    const float *hot_values;     // mirror values in the order of RowBlocks::hot_*
+    const int32_t *hot_at;       // or nullptr
 };
 // alone: a single call, not part of a training step, where the two may share their launches with other layers' instead
 bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone);
@@ -531,6 +542,9 @@ struct PlanArgs {
     BindResult *result;
 };
 hipError_t launch_bind(const MirrorArgs &m, const PlanArgs &p, hipStream_t s);
+// place: scratch, [x_rows + rows]; sets: room for hot_sets_size(rows)
+hipError_t launch_hot_order(const int4 *rows_by_length, int32_t x_rows, const int32_t *indptr_t, const int32_t *indices_t, int32_t rows, const int32_t *perm, int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, const int4 *mirror_rows, int4 *sets,
+                            hipStream_t s);
 hipError_t launch_plan(const PlanArgs &p, int sides, hipStream_t s);   // its last part alone: the partitions of W, or of W and its mirror
 
 // Whether the product in strips can run (256 operand rows travel at a time), and whether a matrix is looked at for a plan: enough work, segments neither so short that a set's differ
@@ -545,6 +559,15 @@ __host__ __device__ inline bool strip_wanted(int32_t rows, int32_t cols, int64_t
     return strip_possible(rows, cols, nnz, max_batch) && rows >= 256 && cols >= 1024 && nnz * max_batch >= (96 << 20) && nnz >= 4 * segments && nnz <= 160 * segments;
 }
 __host__ __device__ inline bool strip_even(int32_t longest_row, int32_t rows, int64_t nnz) { return static_cast<int64_t>(longest_row) * rows <= 3 * nnz; }
+// Whether a mirror gets the order of RowBlocks::hot_*: the kHotRows longest rows hold half of the entries, and the layer's widest batch has the work (backward_hot_ok asks more closely).
+constexpr int32_t kHotFromBatch = 192;
+constexpr int64_t kHotTasks = 5000, kHotEntries = 45, kHotWork = 96ll << 20;
+inline int64_t hot_sets_size(int32_t rows) { return (static_cast<int64_t>(rows) + 255) / 256 * 256; }
+inline bool hot_order_wanted(int32_t rows, int32_t cols, int64_t nnz, int32_t max_batch, float hot_share)
+{
+    return rows >= 1024 && hot_share >= 0.5f && max_batch >= kHotFromBatch && nnz >= kHotEntries * cols && nnz < (1 << 30) && nnz * max_batch >= kHotWork &&
+           ((static_cast<int64_t>(cols) + 3) / 4) * ((static_cast<int64_t>(max_batch) + 63) / 64) >= kHotTasks;
+}
 // Ranges a staged plan over `rows` rows with `nnz` entries aims at, 0: such a plan would never be chosen.  (Host and
 // device; `cols`: operand rows.)
 __host__ __device__ inline int32_t staged_ranges_aim(int32_t rows, int32_t max_batch)

@@ -2151,22 +2151,19 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
         for_runs_of_xcds(a.nnz, n_entry_blocks, [&](int64_t q) {
             const int p = a.perm[q];
             float g = 0.f;
-            int t = 0;
-            for (; t + 8 <= n_tiles; t += 8) {  // eight loads in flight, added in tile order
+            for (int t = 0; t < n_tiles; t += 8) {  // eight loads in flight, added in pairs: sixteen slices are then no further off than eight one after the other (8.7e-8 and 9.2e-8; one after the other 1.0e-7)
                 float v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = a.partial[static_cast<int64_t>(t + u) * a.partial_stride + q];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) g += v[u];
+                for (int u = 0; u < 8; ++u) v[u] = t + u < n_tiles ? a.partial[static_cast<int64_t>(t + u) * a.partial_stride + q] : 0.f;   // (uniform)
+                g += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
             }
-            for (; t < n_tiles; ++t) g += a.partial[static_cast<int64_t>(t) * a.partial_stride + q];
             if (a.g) a.g[p] = g;
             if (a.fused) {
                 float w = a.w[p], v = a.velocity[p];
                 momentum_step(w, v, g, a.lr, a.momentum, a.nesterov);
                 a.w[p] = w;
                 a.velocity[p] = v;
-                a.w_t[q] = w;
+                a.w_t[a.hot_at ? a.hot_at[q] : q] = w;
             }
         });
         return;
@@ -2174,6 +2171,231 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
     if (!(a.db || (a.fused && a.bias))) return;
     backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_entry_blocks) * (kEwBlock / kWave) + wave_in_block(),
                       static_cast<int64_t>(gridDim.x - n_entry_blocks) * (kEwBlock / kWave));
+}
+
+// ---- both gradients where a few rows of dZ take most gathers ------------------------------------------
+// The backward pass on one gather stream (backward_fused_kernel) for matrices a few of whose rows hold most of the entries: the kHotRowsLds longest rows of W -- two thirds of the entries of 16384^2
+// power-law rows at 1 % -- are gathered from LDS, in which a work-group keeps its 64 columns of their dZ, the others from memory.  The entries of a mirror row are taken hot ones first
+// (RowBlocks::hot_*, made when the pattern is bound).  Sixteen lanes serve a mirror row, four of which run side by side in a wave; a gathered row goes into the row's result with the weight moved
+// between lanes in the multiply-add (fma_row_lane), and into the entry's product with the mirror row's X, sixteen products at a time added up across the lanes (row16_transpose_sum).
+// What bounds it: the vector ALUs (11.3 instructions a gather of four rows by 64 columns, 74 % busy at the 1.8 GHz that the card then holds; texture-address units 67 %, where the pass without LDS has
+// them 79 % busy).  16384^2 at 1 %, batch 1024: 490 -> 370 us; of it, weights and sums in the order of the walk (stored through the mirror's positions: 50 more), rows side by side of like
+// counts and half a chunk of cold rows on its way while hot ones are served 10, sets taken by whichever wave is free 10.  (Twice the slices of partial products: the second pass 38 -> 45.)
+constexpr int kHotWaves = kWavesPerBlock, kHotZeroRow = kHotRowsLds * 256;
+template <int N>
+__device__ __forceinline__ float hot_steps(const char *lds, int off, float w, const float4 &ax, float4 &acc, int lig)
+{
+    constexpr int kAhead = 4;
+    float4 x[N];
+    float d[16];
+    auto gather = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        x[i] = *reinterpret_cast<const float4 *>(lds + row_lane<i>(off));
+    };
+    static_for(std::make_integer_sequence<int, kAhead>{}, gather);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (i + kAhead < N) gather(std::integral_constant<int, i + kAhead>{});
+        fma_row_lane<i>(acc, w, x[i]);
+        d[i] = fmaf(x[i].w, ax.w, fmaf(x[i].z, ax.z, fmaf(x[i].y, ax.y, x[i].x * ax.x)));
+        if constexpr (i + kAhead < N) __builtin_amdgcn_sched_barrier(0);
+    });
+    return row16_transpose_sum<N>(d, lig);
+}
+// Entries B .. B + N - 1 of a cold chunk: asked for, and, when they have come, used.  (Lane i < N holds entry B + i's sum.)
+template <int B, int N>
+__device__ __forceinline__ void cold_ask(gmem_ptr Zg, int ro, uint32_t col_bytes, float4 (&x)[N])
+{
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        x[i] = gload4(Zg, static_cast<uint32_t>(row_lane<B + i>(ro)) + col_bytes);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <int B, int N, bool SPARE>
+__device__ __forceinline__ float cold_use(float4 (&x)[N], float w, const float4 &ax, const uint32_t (&own)[4], float4 &acc, int lig)
+{
+    float d[16];
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (SPARE) x[i] = make_float4(keep_bits(x[i].x, own[0]), keep_bits(x[i].y, own[1]), keep_bits(x[i].z, own[2]), keep_bits(x[i].w, own[3]));
+        fma_row_lane<B + i>(acc, w, x[i]);
+        d[i] = fmaf(x[i].w, ax.w, fmaf(x[i].z, ax.z, fmaf(x[i].y, ax.y, x[i].x * ax.x)));
+    });
+    const float sum = row16_transpose_sum<N>(d, lig);
+    __builtin_amdgcn_sched_barrier(0);
+    return sum;
+}
+
+// The mirror's values in the hot rows' order, out of the mirror, or, with perm (the CSR position of each), out of values[], from which the mirror's are brought up to date as well (gather_kernel's work).
+__global__ __launch_bounds__(kEwBlock) void hot_values_kernel(float *out, const float *values, float *values_t, const int32_t *at, const int32_t *perm, const int64_t n)
+{
+    for_runs_of_xcds(n, gridDim.x, [&](int64_t k) {
+        const int q = at[k];
+        const float v = perm ? values[perm[k]] : values[q];
+        out[k] = v;
+        if (perm) values_t[q] = v;
+    });
+}
+template <bool SPARE>
+__global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const BackwardArgs a, const StripGrid g)
+{
+    __shared__ float4 hot[kHotRowsLds * 16 + 16];   // the rows, then one of zeros
+    __shared__ int taken;
+    const int at_block = static_cast<int>(blockIdx.x & 7) * g.per + static_cast<int>(blockIdx.x >> 3);
+    const int tile = at_block / g.n_ranges, range = at_block - tile * g.n_ranges;
+    if (tile >= g.n_tiles) return;
+    const int lane = threadIdx.x & (kWave - 1), lrow = lane >> 4, lig = lane & 15;
+    const int own_col = tile * 64 + lig * 4;
+    const bool on = own_col < a.batch;
+    const int col = four_columns(own_col, a.batch);
+    uint32_t own[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) own[k] = on && col + k >= own_col ? ~0u : 0u;
+    auto owned = [&](const float4 &x) { return SPARE ? make_float4(keep_bits(x.x, own[0]), keep_bits(x.y, own[1]), keep_bits(x.z, own[2]), keep_bits(x.w, own[3])) : x; };
+    if (threadIdx.x == 0) taken = 0;
+    if (threadIdx.x < 16) hot[kHotRowsLds * 16 + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
+    {
+        float4 v[kHotRowsLds / 64];
+#pragma unroll
+        for (int i = 0; i < kHotRowsLds / 64; ++i)
+            v[i] = ld4(a.dZ + static_cast<int64_t>(a.blocks.hot_rows[i * 64 + static_cast<int>(threadIdx.x >> 4)].x) * a.lddz + col);
+#pragma unroll
+        for (int i = 0; i < kHotRowsLds / 64; ++i) hot[i * 1024 + static_cast<int>(threadIdx.x)] = owned(v[i]);
+    }
+    __syncthreads();
+    const char *lds = reinterpret_cast<const char *>(hot) + lig * 16;
+    const uint32_t col_bytes = static_cast<uint32_t>(col) * 4u, ldzb = static_cast<uint32_t>(a.lddz) * 4u;
+    const gmem_ptr Zg = as_gmem(a.dZ);
+    float *gp = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
+    const int n_sets = (a.rows + 3) >> 2;
+    auto take = [&] {   // the next of the range's sets
+        int k = 0;
+        if (lane == 0) k = atomicAdd(&taken, 1);
+        return __builtin_amdgcn_readfirstlane(k) * g.n_ranges + range;
+    };
+    // a mirror row of each lane row, and what the four take side by side: chunks of sixteen hot entries, then of cold ones
+    struct Set {
+        int row, s0, len, n_hot, most_hot, most_cold;
+    };
+    auto set_of = [&](const int4 &d) {
+        auto most_of = [&](int n) {
+            n = max(n, __shfl_xor(n, 16, kWave));
+            return __builtin_amdgcn_readfirstlane(max(n, __shfl_xor(n, 32, kWave)));
+        };
+        return Set{d.x, d.y, d.z, d.w, most_of(d.w), most_of(d.z - d.w)};
+    };
+    // sixteen entries from `first` on of the hot or the cold ones, a lane's one: {offset or row, weight}; on: there is one
+    struct Chunk {
+        int entry;
+        float w;
+    };
+    auto ask = [&](const Set &s, bool is_hot, int first) {
+        const int e = first + lig, n = is_hot ? s.n_hot : s.len - s.n_hot;
+        const uint32_t o = e < n ? static_cast<uint32_t>(s.s0 + (is_hot ? 0 : s.n_hot) + e) * 4u : 0u;
+        return Chunk{__builtin_bit_cast(int, gload1(as_gmem(a.blocks.hot_entry), o)), gload1(as_gmem(a.hot_values), o)};
+    };
+    auto record = [&](int set) { return set < n_sets ? a.blocks.hot_sets[set * 4 + lrow] : make_int4(-1, 0, 0, 0); };
+    auto input = [&](const Set &s) { return ld4(a.X + static_cast<int64_t>(max(s.row, 0)) * a.ldx + col); };
+    int set = take(), set_next = take();
+    Set now = set_of(record(set));
+    float4 mask = input(now);
+    Chunk hot_now = ask(now, true, 0), cold_now = ask(now, false, 0);
+    int4 d_next = record(set_next);
+    while (set < n_sets) {   // (every wave's tickets grow)
+        const int set_after = take();
+        const int4 d_after = record(set_after);
+        const Set next = set_of(d_next);
+        const float4 mask_next = input(next), ax = now.row >= 0 ? owned(mask) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const Chunk hot_first = ask(next, true, 0), cold_first = ask(next, false, 0);
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), acc_cold = acc;   // (apart, so that neither sum is long)
+        const int n_cold = now.len - now.n_hot;
+        int fill = 0;
+        if (now.most_cold > 0) {
+            // what a lane without a cold entry gathers, with weight 0: a row of dZ that the mirror row references anyway, its first cold one, or, without any, a hot one
+            // (an empty row: row 0, for a result that is not taken)
+            fill = row_lane<0>(cold_now.entry);
+            if (__any(n_cold == 0)) fill = n_cold > 0 ? fill : now.len > 0 ? a.blocks.hot_rows[a.blocks.hot_entry[now.s0] >> 8].x : 0;
+        }
+        auto hot_sums = [&](const Chunk &c, int e) {   // (a row of zeros for a lane without an entry)
+            const bool ok = e + lig < now.n_hot;
+            const int off = ok ? c.entry : kHotZeroRow, n = now.most_hot - e;
+            const float w = ok ? c.w : 0.f;
+            if (n > 12) return hot_steps<16>(lds, off, w, ax, acc, lig);
+            if (n > 8) return hot_steps<12>(lds, off, w, ax, acc, lig);
+            if (n > 4) return hot_steps<8>(lds, off, w, ax, acc, lig);
+            return hot_steps<4>(lds, off, w, ax, acc, lig);
+        };
+        const uint32_t gp_hot = static_cast<uint32_t>(now.s0 + lig) * 4u, gp_cold = static_cast<uint32_t>(now.s0 + now.n_hot + lig) * 4u;
+        int h = 0, c = 0;   // entries done
+        // two chunks of hot entries beside one of cold ones: half of the latter are on their way while a hot chunk is served from LDS
+        while (h + 16 < now.most_hot && c + 8 < now.most_cold) {
+            const bool ok = c + lig < n_cold;
+            const int ro = static_cast<int>(static_cast<uint32_t>(ok ? cold_now.entry : fill) * ldzb);
+            const float w = ok ? cold_now.w : 0.f;
+            const Chunk hot_next = ask(now, true, h + 16);
+            float4 x[8];
+            cold_ask<0, 8>(Zg, ro, col_bytes, x);
+            const bool ok_hot = h + lig < now.n_hot;
+            const float sum_hot = hot_steps<16>(lds, ok_hot ? hot_now.entry : kHotZeroRow, ok_hot ? hot_now.w : 0.f, ax, acc, lig);
+            __builtin_amdgcn_sched_barrier(0);
+            const float sum_0 = cold_use<0, 8, SPARE>(x, w, ax, own, acc_cold, lig);
+            hot_now = ask(now, true, h + 32);
+            cold_now = ask(now, false, c + 16);
+            cold_ask<8, 8>(Zg, ro, col_bytes, x);
+            if (ok_hot) gstore1(gp, gp_hot + static_cast<uint32_t>(h) * 4u, sum_hot);
+            if (lig < 8 && ok) gstore1(gp, gp_cold + static_cast<uint32_t>(c) * 4u, sum_0);
+            const float sum_hot2 = hot_sums(hot_next, h + 16);
+            __builtin_amdgcn_sched_barrier(0);
+            const float sum_1 = cold_use<8, 8, SPARE>(x, w, ax, own, acc_cold, lig);
+            if (h + 16 + lig < now.n_hot) gstore1(gp, gp_hot + static_cast<uint32_t>(h) * 4u + 64u, sum_hot2);
+            if (lig < 8 && c + 8 + lig < n_cold) gstore1(gp, gp_cold + static_cast<uint32_t>(c) * 4u + 32u, sum_1);
+            h += 32;
+            c += 16;
+        }
+        for (; h < now.most_hot; h += 16) {
+            const Chunk hot_next = ask(now, true, h + 16);
+            const float sum = hot_sums(hot_now, h);
+            if (h + lig < now.n_hot) gstore1(gp, gp_hot + static_cast<uint32_t>(h) * 4u, sum);
+            hot_now = hot_next;
+        }
+        for (; c < now.most_cold; c += 16) {
+            const bool ok = c + lig < n_cold;
+            const int ro = static_cast<int>(static_cast<uint32_t>(ok ? cold_now.entry : fill) * ldzb);
+            const float w = ok ? cold_now.w : 0.f;
+            cold_now = ask(now, false, c + 16);
+            float4 x[8];
+            cold_ask<0, 8>(Zg, ro, col_bytes, x);
+            const float sum_0 = cold_use<0, 8, SPARE>(x, w, ax, own, acc_cold, lig);
+            if (lig < 8 && ok) gstore1(gp, gp_cold + static_cast<uint32_t>(c) * 4u, sum_0);
+            if (c + 8 < now.most_cold) {
+                cold_ask<8, 8>(Zg, ro, col_bytes, x);
+                const float sum_1 = cold_use<8, 8, SPARE>(x, w, ax, own, acc_cold, lig);
+                if (lig < 8 && c + 8 + lig < n_cold) gstore1(gp, gp_cold + static_cast<uint32_t>(c) * 4u + 32u, sum_1);
+            }
+        }
+        const int row = now.row, len = now.len;
+        const float4 mask_now = mask;
+        set = set_next;
+        set_next = set_after;
+        now = next;
+        mask = mask_next;
+        hot_now = hot_first;
+        cold_now = cold_first;
+        d_next = d_after;
+        if (row < 0 || !on) continue;
+        float4 y = len > 0 ? make_float4(acc.x + acc_cold.x, acc.y + acc_cold.y, acc.z + acc_cold.z, acc.w + acc_cold.w) : make_float4(0.f, 0.f, 0.f, 0.f);   // (an empty row gathered, with weight 0, from row 0 of dZ)
+        if (a.mask) y = keep_where_positive(y, mask_now);
+        float *out = a.dX + static_cast<int64_t>(row) * a.lddx + col;
+        if (!SPARE || col == own_col) {
+            st4(out, y);
+        } else {   // (the lane's own columns of the batch's last four)
+            if (own_col <= col + 1) out[1] = y.y;
+            if (own_col <= col + 2) out[2] = y.z;
+            out[3] = y.w;
+        }
+    }
 }
 
 // ---- the end of a training step in one launch ----------------------------------------------------
@@ -3501,8 +3723,10 @@ bool chain_pays(const SpmmArgs &t, const SddmmArgs &g0)
 }
 
 // (reading values[] through the position map costs a scattered read per entry and tile, a launch of its own 3.5 us)
-bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &)
+bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g);
+bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g)
 {
+    if (backward_hot_ok(t, g)) return true;
     const int tiles = backward_tiles(t, backward_tile_group(t));
     return tiles == 1 || backward_looped(t) || static_cast<int64_t>(tiles) * t.nnz <= (1 << 20);
 }
@@ -3633,6 +3857,20 @@ static bool backward_gathers_apart(int gs, int64_t waves, const SpmmArgs &t, boo
     return gs == 64 || waves <= 3072 || waves >= 16384 || t.nnz <= 40ll * t.rows || (waves <= 4608 && t.nnz <= 192ll * t.rows);
 }
 
+// Whether the pass with hot rows in LDS runs: not where a tile's spare columns, few mirror rows (a wave for each four of them and tile) or short ones leave it waiting, shorter ones the less the more rows
+// of dZ there are beside the hot ones.  Power-law matrices, one gather stream from the L2s -> with the hot rows in LDS, us: 16384^2 at 1 / 3 %, batch 1024 524 -> 440, 1563 -> 1314; 8192^2 at 2 % 250 -> 190; 9784 x 8260 at
+// 4.2 %, batch 342 261 -> 217; 3269 x 9044 at 2.8 %, batch 782 135 -> 105; 4114 x 2469 at 3.2 %, batch 880 73.7 -> 59.3; 5197 x 6386 at 1.2 % (60 entries a mirror row), batch 632 57.3 -> 52.2; 12283 x 6279 at
+// 2.2 %, batch 315 145 -> 111; 13502 x 15851 at 0.6 % (86), batch 464 140 -> 128.  But 8068 x 4944 at 0.6 % (46), batch 762 46.4 -> 50.9; 14946 x 9731 at 0.5 % (68), batch 252 51.5 -> 54.8; 9338 x 11104 at 0.1 % (11),
+// batch 881 43 -> 51; few mirror rows: 12284 x 1987 at 5.4 %, batch 289 117 -> 133; spare columns: 5379 mirror rows, batch 116 101 -> 117.
+bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g)
+{
+    if (!t.blocks.hot_entry || !g.hot_values || t.XM || !g.partial) return false;
+    const int64_t tiles = (static_cast<int64_t>(t.batch) + 63) / 64, sets = (static_cast<int64_t>(t.rows) + 3) / 4;
+    if (tiles > g.partial_tiles || g.partial_stride < t.nnz) return false;
+    return t.batch >= kHotFromBatch && t.batch * 20ll >= tiles * 64 * 17 && sets * tiles >= kHotTasks && t.nnz >= (t.x_rows > 6144 ? 85ll : kHotEntries) * t.rows &&
+           static_cast<int64_t>(t.nnz) * t.batch >= kHotWork;
+}
+
 hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s)
 {
     BackwardArgs a{};
@@ -3651,6 +3889,22 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     const bool one = n_tiles == 1 || (alone && backward_looped(t));
     const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
+    if (backward_hot_ok(t, g)) {
+        StripGrid h;
+        h.n_tiles = (t.batch + 63) / 64;
+        // one round of work-groups, two tiles at a time on an XCD, where an L2 holds both (5001 x 9001 at 2 %, batch 999, in two: 133 -> 144 us), else two (16384^2 at 1 %, batch 1024, in one: 438 -> 474)
+        h.n_ranges = std::max(1, (t.x_rows * 512ll <= (3 << 20) ? 1 : 2) * 256 / h.n_tiles);
+        h.per = (h.n_tiles * h.n_ranges + 7) / 8;
+        a.hot_values = g.hot_values;
+        const bool refresh = alone && g.values;   // (backward_fused_refreshes: the call leaves it to this launch)
+        hipLaunchKernelGGL(hot_values_kernel, dim3(xcd_run_blocks(t.nnz)), dim3(kEwBlock), 0, s, g.hot_values, refresh ? g.values : t.values, g.values_t, t.blocks.hot_at,
+                           refresh ? t.blocks.hot_perm : nullptr, t.nnz);
+        hipLaunchKernelGGL(t.batch % 64 ? backward_hot_kernel<true> : backward_hot_kernel<false>, dim3(8u * h.per), dim3(kHotWaves * kWave), 0, s, a, h);
+        a.perm = t.blocks.hot_perm; a.hot_at = t.blocks.hot_at;
+        const int n_entry_blocks = xcd_run_blocks(t.nnz);
+        hipLaunchKernelGGL(backward_finish_kernel, dim3(n_entry_blocks + n_row_blocks), dim3(kEwBlock), 0, s, a, h.n_tiles, n_entry_blocks);
+        return hipGetLastError();
+    }
     const TileOrder order = tile_order(n_tiles, n_pack_blocks, tg, false, tiled_launch(t));
     const int64_t ids = one ? n_pack_blocks + n_row_blocks : tile_grid(order, n_tiles, n_pack_blocks);
     auto go = [&](auto group) {

@@ -967,7 +967,66 @@ __global__ __launch_bounds__(kBig) void plan_cuts_kernel(const PlanArgs A, const
     staged_ends(S, static_cast<int64_t>(e % kEndsBlocks) * kBig + threadIdx.x, static_cast<int64_t>(kEndsBlocks) * kBig);
 }
 
+// Entries of the mirror rows in the order of RowBlocks::hot_*: every row's place among the longest, or -1; then a wave per mirror row.
+__global__ __launch_bounds__(kSetupBlock) void hot_place_kernel(const int4 *rows_by_length, const int32_t n, int32_t *place)
+{
+    const int32_t e = blockIdx.x * kSetupBlock + threadIdx.x;
+    if (e < n) place[rows_by_length[e].x] = e < kHotRowsLds ? e : -1;
+}
+__global__ __launch_bounds__(kSetupBlock) void hot_order_kernel(const int32_t *indptr_t, const int32_t *indices_t, const int32_t rows, const int32_t *perm, const int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, int32_t *count)
+{
+    const int32_t row = blockIdx.x * (kSetupBlock / kWave) + wave_id();
+    if (row >= rows) return;
+    const int32_t p0 = indptr_t[row], p1 = indptr_t[row + 1], lane = lane_id();
+    int32_t hot = 0;
+    for (int32_t p = p0; p < p1; p += kWave) hot += __popcll(__ballot(p + lane < p1 && place[indices_t[min(p + lane, p1 - 1)]] >= 0));
+    if (lane == 0) count[row] = hot;
+    int32_t next_hot = p0, next_cold = p0 + hot;
+    for (int32_t p = p0; p < p1; p += kWave) {
+        const bool in = p + lane < p1;
+        const int32_t i = indices_t[min(p + lane, p1 - 1)], slot = place[i];
+        const uint64_t hots = __ballot(in && slot >= 0), colds = __ballot(in && slot < 0);
+        if (in) {
+            const int32_t to = slot >= 0 ? next_hot + lanes_below(hots) : next_cold + lanes_below(colds);
+            entry[to] = slot >= 0 ? slot * 256 : i;
+            at[to] = p + lane;
+            hot_perm[to] = perm[p + lane];
+        }
+        next_hot += __popcll(hots);
+        next_cold += __popcll(colds);
+    }
+}
+
+// Rows of about one length, kHotGroup at a time, by their hot entries: what runs side by side then has as many of either kind (16384^2 power-law at 1 %: 16 -> 6 % of the steps without an entry).
+constexpr int kHotGroup = 256;
+__global__ __launch_bounds__(kHotGroup) void hot_sets_kernel(const int4 *mirror_rows, const int32_t rows, const int32_t *count, int4 *sets)
+{
+    __shared__ int32_t key[kHotGroup];
+    const int32_t r = threadIdx.x, k = blockIdx.x * kHotGroup + r;
+    int4 d = make_int4(-1, 0, 0, 0);
+    if (k < rows) {
+        d = mirror_rows[k];
+        d.w = count[d.x];
+    }
+    key[r] = k < rows ? d.w : -1;
+    __syncthreads();
+    int32_t rank = 0;
+    const int32_t mine = key[r];
+    for (int u = 0; u < kHotGroup; ++u) rank += key[u] > mine || (key[u] == mine && u < r);
+    sets[blockIdx.x * kHotGroup + rank] = d;
+}
+
 }  // namespace
+
+hipError_t launch_hot_order(const int4 *rows_by_length, int32_t x_rows, const int32_t *indptr_t, const int32_t *indices_t, int32_t rows, const int32_t *perm, int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, const int4 *mirror_rows, int4 *sets,
+                            hipStream_t s)
+{
+    hipLaunchKernelGGL(hot_place_kernel, dim3((x_rows + kSetupBlock - 1) / kSetupBlock), dim3(kSetupBlock), 0, s, rows_by_length, x_rows, place);
+    int32_t *count = place + x_rows;
+    hipLaunchKernelGGL(hot_order_kernel, dim3((rows + kSetupBlock / kWave - 1) / (kSetupBlock / kWave)), dim3(kSetupBlock), 0, s, indptr_t, indices_t, rows, perm, place, entry, at, hot_perm, count);
+    hipLaunchKernelGGL(hot_sets_kernel, dim3((rows + kHotGroup - 1) / kHotGroup), dim3(kHotGroup), 0, s, mirror_rows, rows, count, sets);
+    return hipGetLastError();
+}
 
 MirrorGeometry mirror_geometry(int32_t rows, int32_t cols, int32_t nnz)
 {

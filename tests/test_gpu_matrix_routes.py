@@ -639,3 +639,77 @@ def test_training_step_in_strips_on_new_patterns(nb, oracle, prefer_strips):
         torch.cuda.synchronize()
         assert torch.equal(out[:, :batch], want[:, :batch]), k
     m.close(); mlps[1].close()
+
+
+def hot_rows_layer(rows, cols, n_long, long_share, short, seed, relu=False):
+    """`n_long` rows that store `long_share` of their columns among rows of `short` entries: the backward pass keeps dZ of the 512 longest in LDS.  Column 0 is only in rows of the
+    latter kind, column 1 only in the long ones, column 2 in none."""
+    rng = np.random.default_rng(seed)
+    long_rows = set(rng.choice(rows, n_long, replace=False).tolist())
+    per_row = []
+    for i in range(rows):
+        n = int(long_share * cols) if i in long_rows else short
+        j = rng.choice(np.arange(3, cols), n, replace=False)
+        if i in long_rows and i % 2 or i not in long_rows and i % 50 == 0:
+            j[0] = 1 if i in long_rows else 0
+        per_row.append(np.unique(j))
+    indptr = np.concatenate([[0], np.cumsum([len(r) for r in per_row])]).astype(np.int32)
+    indices = np.concatenate(per_row).astype(np.int32)
+    values = (rng.standard_normal(len(indices)) * 0.1).astype(np.float32)
+    return wl.SparseLayerData(rows, cols, indptr, indices, values, np.zeros(rows, dtype=np.float32), relu), sorted(long_rows)
+
+
+@pytest.mark.parametrize("rows,cols,n_long,batch,ld,relu", [
+    (1100, 2600, 400, 512, None, False),    # whole tiles; some of the 512 rows in LDS are short ones
+    (1531, 2599, 500, 509, 509, False),     # ragged columns, rows in sets of four with one left over
+    (1300, 2603, 600, 500, None, True),     # long rows outside LDS; a batch of a multiple of 4 that fills no tile
+    (6200, 2501, 512, 576, 577, False),     # more rows of dZ than an L2 holds two tiles of: two rounds of work-groups
+])
+def test_both_gradients_with_hot_rows_in_lds(nb, oracle, rows, cols, n_long, batch, ld, relu):
+    lay, _ = hot_rows_layer(rows, cols, n_long, 0.28 if rows < 6000 else 0.25, 20, rows + batch, relu)
+    check_layer(nb, oracle, lay, batch, ld=ld)
+
+
+def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
+    """A row of dZ of infinities, one of those in LDS and one that is not: they reach the gradients of the inputs that reference them, and their own entries' and biases', and nothing else."""
+    import torch
+    rows, cols, batch = 1100, 2600, 500
+    lay, long_rows = hot_rows_layer(rows, cols, 400, 0.28, 20, 11)
+    short_rows = [i for i in range(rows) if i not in set(long_rows)]
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal((cols, batch)).astype(np.float32); dY = rng.standard_normal((rows, batch)).astype(np.float32)
+    bad = [long_rows[7], short_rows[-3]]
+    dY[bad] = np.inf
+    L = nb.SparseLinear(lay, max_batch=batch)
+    dXd, g, db = nb.dense(cols, batch), torch.empty(lay.nnz, device="cuda"), torch.empty(rows, device="cuda")
+    nb.sparse_linear_backward(L.handle, nb.to_dense(X), None, nb.to_dense(dY), dXd, g, db, batch)
+    torch.cuda.synchronize()
+    row_of = np.repeat(np.arange(rows), np.diff(lay.indptr))
+    hit = np.zeros(cols, dtype=bool); hit[lay.indices[np.isin(row_of, bad)]] = True
+    dX, gh = dXd.cpu().numpy(), g.cpu().numpy()
+    assert np.isfinite(dX[~hit]).all() and not np.isfinite(dX[hit]).all(axis=1).any()
+    own = np.isin(row_of, bad)
+    assert np.isfinite(gh[~own]).all() and not np.isfinite(gh[own]).any()
+    assert np.array_equal(np.isfinite(db.cpu().numpy()), ~np.isin(np.arange(rows), bad))
+    dY[bad] = 0
+    ref, S = oracle.spmm_t(rows, cols, lay.indptr, lay.indices, lay.values, dY)
+    close(dX[~hit], ref[~hit], S[~hit], what="dX beside infinities")
+    L.close()
+
+
+@pytest.mark.parametrize("batch", [512, 449])
+def test_training_step_with_hot_rows_in_lds(nb, oracle, batch):
+    """The layer's update behind the same pass: every stage against the oracle, over steps whose weights each find changed."""
+    import torch
+    from test_gpu_mlp_step import snapshot, stage_parity
+    sizes = (60, 2600, 1100, 10)
+    mlp = wl.make_mlp(sizes, layer_nnz=(5200, 2600, 2000), pattern_seed=1, value_seed=2)
+    mlp.layers[1] = hot_rows_layer(1100, 2600, 400, 0.28, 20, 5, relu=True)[0]
+    Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 2, seed=3)
+    M = nb.MLP(mlp, batch)
+    for t in range(2):
+        before = snapshot(M)
+        M.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
+        torch.cuda.synchronize()
+        stage_parity(nb, torch, oracle, M, mlp, before, Xs[t], Ts[t], batch, 0.05, 0.9, False)
+    M.close()
