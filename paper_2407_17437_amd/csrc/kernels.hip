@@ -855,6 +855,9 @@ __global__ __launch_bounds__(kBlock) void full_rows_finish_softmax_kernel(const 
 // 1.5 times as fast), not either pipe.  Segments, masks and offsets worked out once per block and not per use, the rows brought ahead, no wait for memory among
 // the gathers, the weight's move in the multiply-add: 16384^2 power-law rows at 10 %, batch 1024, under the profiler 1087 -> 745 us (10.3 -> 6.5 vector instructions a gather; among other passes it takes 640 to 680);
 // forward products of uniform 8192^2 at 5 %, batch 1024, 374 -> 278, 16384^2 at 2 %, batch 512, 448 -> 334, 5000 x 7000 at 8 %, batch 511, 146 -> 115.
+// The waves of a SIMD take turns by age, so that the oldest were through a block while the youngest, alone, could not fill the LDS pipe: their priorities fall as they go through their slots, and who is behind
+// goes first.  Power-law 16384^2 at 10 %, batch 1024, dense rows included, 1311 -> 1243, uniform at 10 % 1780 -> 1650; 8192^2 at 5 % 291 -> 270; weight gradients of 16384^2 at 10 / 2 % 2571 -> 2483, 827 -> 798, 5000 x 7000 at 8 %,
+// batch 511, 153 -> 142.
 // (48 KB of code, the gradient's 56, the instruction cache 64.  Two registers are stored before the block loop and reloaded after it; with a mask four, two of them reloaded once a block.)
 // Slots dealt to the waves there and back change nothing, two runs of 8 gathers made one of 16 neither.  A row marked kStageQuad is
 // shared by the four lane rows of a wave, a quarter of each segment each, and their four results
@@ -1070,6 +1073,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
             if constexpr (j + kAheadJ < kStageJ) ask(std::integral_constant<int, j + kAheadJ>{}, now);
             else ask(std::integral_constant<int, j + kAheadJ - kStageJ>{}, next);
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (j % 2 == 0) __builtin_amdgcn_s_setprio(3 - j / 2);
             const int most = __builtin_amdgcn_readlane(now.most, j);
             if (most > 0) {
                 uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(now.at)) + lig * kUnit);
@@ -1705,6 +1709,7 @@ __global__ __launch_bounds__(kStageWaves * kWave) void sddmm_staged_kernel(const
             if constexpr (j + kAheadJ < kStageJ) ask(std::integral_constant<int, j + kAheadJ>{}, now);
             else ask(std::integral_constant<int, j + kAheadJ - kStageJ>{}, next);
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (j % 2 == 0) __builtin_amdgcn_s_setprio(3 - j / 2);
             int n = __builtin_amdgcn_readlane(now.most, j);
             if (n > 0) {
                 uint32_t at = static_cast<uint32_t>(row_lane<j>(static_cast<int>(now.at)) + lig4);
