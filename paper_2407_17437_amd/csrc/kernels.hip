@@ -1979,6 +1979,49 @@ __device__ __forceinline__ void bwd_pass(gmem_ptr Zg, gmem_ptr Mg, int src, int 
     }
 }
 
+// The same for one tile in groups of 16 or 32 lanes: a chunk is sixteen entries, one in each lane of every sixteen, n of them (or one more) used.  The weight is moved between lanes in
+// the multiply-add, and the products are added up across the lanes sixteen at a time: 11 vector instructions a gather where bwd_pass has 17 and three moves through the LDS crossbar.
+// Figures are at bwd_sixteens.
+template <int GS>
+__device__ __forceinline__ float bwd_chunk(gmem_ptr Zg, int n, int ro, float w, uint32_t off, const float4 &ax, float4 &acc, int lig)
+{
+    float d[16];
+    auto pass = [&](auto first, auto count) {
+        constexpr int B = decltype(first)::value, N = decltype(count)::value;
+        float4 x[N];
+        static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            x[i] = gload4(Zg, static_cast<uint32_t>(row_lane<B + i>(ro)) + off);
+        });
+        static_for(std::make_integer_sequence<int, N>{}, [&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if (i + 1 < N || n > B + i) fma_row_lane<B + i>(acc, w, x[i]);   // (uniform; the one more may hold an infinity)
+            float part = fmaf(x[i].w, ax.w, fmaf(x[i].z, ax.z, fmaf(x[i].y, ax.y, x[i].x * ax.x)));
+            d[B + i] = part;
+        });
+    };
+    using std::integral_constant;
+    auto half = [&](auto first, int m) {
+        constexpr int B = decltype(first)::value;
+        int ways = m > 6 ? 1 : m > 4 ? 6 : m > 2 ? 2 : 8;   // (one if after the other: see staged_half)
+        asm("" : "+s"(ways));
+        if (ways & 1) pass(first, integral_constant<int, 8>{});
+        if (ways & 2) pass(first, integral_constant<int, 4>{});
+        if (ways & 4) pass(integral_constant<int, B + 4>{}, integral_constant<int, 2>{});
+        if (ways & 8) pass(first, integral_constant<int, 2>{});
+    };
+    half(integral_constant<int, 0>{}, n);
+    float res;
+    if (n > 8) {
+        half(integral_constant<int, 8>{}, n - 8);
+        res = row16_transpose_sum<16>(d, lig);
+    } else {
+        res = row16_transpose_sum<8>(d, lig);
+    }
+    if constexpr (GS == 32) res += __shfl_xor(res, 16, kWave);
+    return res;
+}
+
 // Sums of the rows of dZ, a wave per row: the bias gradient, stored or applied.
 __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t wave, int64_t n_waves)
 {
@@ -2011,7 +2054,8 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // the lane groups and the matrix is small: then a wave takes its entries through all tiles.  XMASK: dZ is dY times
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
-template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE, bool APART>
+enum BackwardGathers { kGathersMixed, kGathersApart, kGathersSixteens };   // bwd_pass without and with APART; bwd_chunk
+template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE, BackwardGathers GATHERS>
 __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const TileOrder order,
                                                                           const int n_pack_blocks, const int lg_split)
 {
@@ -2034,6 +2078,9 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     const int wv = wave_in_block();
     const int grp = lane / GS;
     const int lig = lane % GS;
+    constexpr bool SIXTEENS = GATHERS == kGathersSixteens, APART = GATHERS == kGathersApart;
+    constexpr int CH = SIXTEENS ? 16 : GS;   // entries of a row in a chunk; lane lig % CH has its one
+    const int mine = lig % CH;
     const uint32_t ldzb = static_cast<uint32_t>(a.lddz) * 4u, ldmb = XMASK ? static_cast<uint32_t>(a.ldzm) * 4u : 0u;
     const gmem_ptr Zg = as_gmem(a.dZ), Mg = as_gmem(a.ZM);
     const int per_set = NE >> lg_split, part = grp & ((1 << lg_split) - 1);   // rows per wave; the group's share of its row
@@ -2045,14 +2092,14 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     float *gp = ONE ? nullptr : a.partial + static_cast<int64_t>(tile) * a.partial_stride;
 
     auto fetch = [&](int s0, int len, int base, int &j, float &w, int &at, float &v) {  // as in spmm_body_packed
-        const int e = base + part * GS + lig;
+        const int e = base + part * CH + mine;
         const bool ok = e < len;
         const int p = len > 0 ? s0 + (ok ? e : 0) : 0;
         j = a.indices[p];
         if (ONE || a.refresh) at = a.perm[p];
         if (a.refresh) {   // uniform
             w = a.refresh[at];
-            if (ok && (ONE || tile == 0)) a.w_t[p] = w;
+            if (ok && (ONE || tile == 0) && lig < CH) a.w_t[p] = w;
         } else {
             w = a.values[p];
         }
@@ -2081,32 +2128,37 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
 #pragma unroll
                 for (int k = 0; k < 4; ++k) own[k] = on && col + k >= own_col ? ~0u : 0u;
                 float acc[4] = {0.f, 0.f, 0.f, 0.f};
+                float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
                 int cur_j, cur_at = 0;
                 float cur_w, cur_v = 0.f;
                 fetch(s0, len, 0, cur_j, cur_w, cur_at, cur_v);
-                for (int base = 0; base < maxlen; base += GS << lg_split) {
+                for (int base = 0; base < maxlen; base += CH << lg_split) {
                     int next_j = 0, next_at = 0;
                     float next_w = 0.f, next_v = 0.f;
-                    if (base + (GS << lg_split) < maxlen)  // wave-uniform: one chunk ahead
-                        fetch(s0, len, base + (GS << lg_split), next_j, next_w, next_at, next_v);
+                    if (base + (CH << lg_split) < maxlen)  // wave-uniform: one chunk ahead
+                        fetch(s0, len, base + (CH << lg_split), next_j, next_w, next_at, next_v);
                     const int my_ro = static_cast<int>(static_cast<uint32_t>(cur_j) * ldzb);
                     const int my_mo = XMASK ? static_cast<int>(static_cast<uint32_t>(cur_j) * ldmb) : 0;
-                    const int steps = min(GS, maxlen - base);
                     float res = 0.f;
-                    int src = src0;
-                    int u0 = 0;
-                    for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
-                    if (u0 + 4 <= steps) {
-                        bwd_pass<4, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
-                        u0 += 4; src += 16;
+                    if constexpr (SIXTEENS) {
+                        res = bwd_chunk<GS>(Zg, min(CH, maxlen - base), my_ro, cur_w, off, ax, sum, lig & 15);
+                    } else {
+                        const int steps = min(GS, maxlen - base);
+                        int src = src0;
+                        int u0 = 0;
+                        for (; u0 + 8 <= steps; u0 += 8, src += 32) bwd_pass<8, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                        if (u0 + 4 <= steps) {
+                            bwd_pass<4, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                            u0 += 4; src += 16;
+                        }
+                        if (u0 + 2 <= steps) {
+                            bwd_pass<2, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
+                            u0 += 2; src += 8;
+                        }
+                        if (u0 < steps) bwd_pass<1, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
                     }
-                    if (u0 + 2 <= steps) {
-                        bwd_pass<2, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
-                        u0 += 2; src += 8;
-                    }
-                    if (u0 < steps) bwd_pass<1, GS, XMASK, SPARE, APART>(Zg, Mg, src, my_ro, my_mo, cur_w, off, ax, own, u0, lig, acc, res);
-                    const int e = base + part * GS + lig;
-                    if (row >= 0 && e < len) {
+                    const int e = base + part * CH + mine;
+                    if (row >= 0 && e < len && lig < CH) {
                         if constexpr (ONE) {
                             if constexpr (LOOPED) {   // (the row has one chunk)
                                 whole += res;
@@ -2129,6 +2181,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
                     cur_at = next_at;
                     cur_v = next_v;
                 }
+                if constexpr (SIXTEENS) { acc[0] = sum.x; acc[1] = sum.y; acc[2] = sum.z; acc[3] = sum.w; }
                 for (int d = GS; d < GS << lg_split; d <<= 1)   // the shares of a row, in one fixed order
 #pragma unroll
                     for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], d, kWave);
@@ -3862,6 +3915,13 @@ static bool backward_gathers_apart(int gs, int64_t waves, const SpmmArgs &t, boo
     return gs == 64 || waves <= 3072 || waves >= 16384 || t.nnz <= 40ll * t.rows || (waves <= 4608 && t.nnz <= 192ll * t.rows);
 }
 
+// Whether one tile in groups of 16 or 32 lanes, whose gathers would be apart, takes chunks of sixteen (80 registers, a third fewer instructions).  Uniform rows, us, batch 64 / 128: 1200 x 1100
+// at 2 % 5.4 -> 5.1, 5.8 -> 5.2, at 6 % 6.4 -> 6.4, 8.9 -> 7.7; 2048 x 3000 at 6 % 12.3 -> 12.0, 17.3 -> 16.1; 3000 x 4000 at 6 % 21.5 -> 20.8, 29.2 -> 27.5; 4000 x 3000 at 2 % 10.0 -> 9.6, 13.5 -> 12.6;
+// 8192^2 at 0.6 / 2 % 15.6 -> 15.2, 37.4 -> 37.5, 19.9 -> 19.7, 50.3 -> 49.0.  Not with rows of one chunk (3000 x 4000 at 0.3 %, 9 entries a row, batch 128 5.0 -> 5.4), nor with long ones, which lose
+// lines that the L1s would keep (2048 x 5500 at 25 % 67.7 -> 77.8, 98.5 -> 104; 9106 x 9383 at 6 %, batch 64 139 -> 158), nor with more waves than start at once (9106 x 9383 at 2 %, batch 128 65.0 -> 71.9,
+// at 0.3 % 16.1 -> 16.8; but 2048 x 5500 at 2 % 14.0 -> 12.1).
+static bool bwd_sixteens(int64_t waves, const SpmmArgs &t) { return waves <= 4096 && t.nnz > 20ll * t.rows && t.nnz <= 400ll * t.rows; }
+
 // Whether the pass with hot rows in LDS runs: not where a tile's spare columns, few mirror rows (a wave for each four of them and tile) or short ones leave it waiting, shorter ones the less the more rows
 // of dZ there are beside the hot ones.  Power-law matrices, one gather stream from the L2s -> with the hot rows in LDS, us: 16384^2 at 1 / 3 %, batch 1024 524 -> 440, 1563 -> 1314; 8192^2 at 2 % 250 -> 190; 9784 x 8260 at
 // 4.2 %, batch 342 261 -> 217; 3269 x 9044 at 2.8 %, batch 782 135 -> 105; 4114 x 2469 at 3.2 %, batch 880 73.7 -> 59.3; 5197 x 6386 at 1.2 % (60 entries a mirror row), batch 632 57.3 -> 52.2; 12283 x 6279 at
@@ -3918,10 +3978,18 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         auto launch = [&](auto pass, auto mask) {
             constexpr bool kOne = decltype(pass)::value == kBackwardOneTile && !decltype(mask)::value;
             auto with = [&](auto spare) {
-                auto kernel = backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value, kOne>;
-                if constexpr (kOne && (GS == 8 || decltype(spare)::value == kSpareNone))   // (else both variants take the same registers)
-                    if (!backward_gathers_apart(GS, static_cast<int64_t>(n_pack_blocks) * kBwdWaves, t, a.fused))
-                        kernel = backward_fused_kernel<GS, decltype(pass)::value, decltype(mask)::value, decltype(spare)::value, false>;
+                constexpr BackwardSpare SPARE = decltype(spare)::value;
+                constexpr BackwardPass P = decltype(pass)::value;
+                constexpr bool MASK = decltype(mask)::value;
+                const int64_t waves = static_cast<int64_t>(n_pack_blocks) * kBwdWaves;
+                auto kernel = backward_fused_kernel<GS, P, MASK, SPARE, kOne ? kGathersApart : kGathersMixed>;
+                if constexpr (kOne && (GS == 8 || SPARE == kSpareNone)) {   // (else both variants take the same registers)
+                    if (!backward_gathers_apart(GS, waves, t, a.fused)) {
+                        kernel = backward_fused_kernel<GS, P, MASK, SPARE, kGathersMixed>;
+                    } else if constexpr (GS == 16 || GS == 32) {
+                        if (bwd_sixteens(waves, t)) kernel = backward_fused_kernel<GS, P, MASK, SPARE, kGathersSixteens>;
+                    }
+                }
                 hipLaunchKernelGGL(kernel, grid, block, 0, s, a, n_tiles, order, n_pack_blocks, lg_split);
             };
             if (a.batch % (GS * 4) == 0) return with(std::integral_constant<BackwardSpare, kSpareNone>{});

@@ -276,6 +276,38 @@ def test_both_gradients_in_one_tile_of_more_waves_than_fit_at_once(nb, oracle, b
     check_layer(nb, oracle, layer_case(60, 17000, 0.01, seed=batch), batch)
 
 
+@pytest.mark.parametrize("batch", [64, 128])
+@pytest.mark.parametrize("rows,cols,lens", [(900, 301, range(3, 60)), (700, 640, [21]), (640, 1200, [33, 20, 31]), (2500, 77, [390, 400, 65]), (500, 2, [399, 401]), (5000, 8200, [21, 24]),
+                                            (1000, 900, [20]), (5000, 500, [401])])
+def test_both_gradients_in_chunks_of_sixteen(nb, oracle, rows, cols, lens, batch):
+    """One tile in groups of 16 or 32 lanes, mirror rows of 1 to 25 chunks and every remainder, alone in a wave and shared by groups; the last two and the longest matrix lie beyond the rule.
+    Infinities in dZ reach the entries that read them as infinities also where a row's number of entries is odd."""
+    import torch
+    lens = np.resize(np.asarray(list(lens)), cols)
+    tp, ti = wl.pattern_from_row_nnz(lens, rows, seed=cols)   # the mirror's rows
+    order = np.lexsort((np.repeat(np.arange(cols), lens), ti))
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(ti, minlength=rows))]).astype(tp.dtype)
+    lay = wl.SparseLayerData(rows, cols, indptr, np.repeat(np.arange(cols), lens)[order].astype(ti.dtype), wl.init_values(indptr, 5), np.zeros(rows, np.float32), False)
+    check_layer(nb, oracle, lay, batch)
+    rng = np.random.default_rng(1)
+    dY, X = (rng.standard_normal((n, batch)).astype(np.float32) for n in (rows, cols))
+    dY[np.argmax(np.diff(indptr)), 5] = np.inf
+    ref, S = oracle.spmm_t(rows, cols, lay.indptr, lay.indices, lay.values, np.where(np.isinf(dY), 0, dY))
+    L = nb.SparseLinear(lay, max_batch=batch)
+    dX, g, db = nb.dense(cols, batch), torch.empty(lay.nnz, device="cuda"), torch.empty(rows, device="cuda")
+    nb.sparse_linear_backward(L.handle, nb.to_dense(X), None, nb.to_dense(dY), dX, g, db, batch)
+    torch.cuda.synchronize()
+    hit = np.zeros(ref.shape, dtype=bool)
+    bad = np.nonzero(np.isinf(dY))[0][0]
+    hit[lay.indices[indptr[bad]:indptr[bad + 1]], 5] = True
+    got = dX.cpu().numpy()
+    assert not np.isfinite(got[hit]).any()
+    if len(set(lens.tolist())) == 1:   # (rows side by side in a wave are as long)
+        assert np.isinf(got[hit]).all()
+    close(np.where(hit, 0, got), np.where(hit, 0, ref), np.where(hit, 1, S), what="dX beside infinities")
+    L.close()
+
+
 def test_huge_rows_after_products_that_overlapped(nb, oracle):
     """Products of one layer on several streams at once may spoil one another (their results are not looked at), but no product
     that is ordered after them: the shares of its huge rows are counted from 0 again, in both orientations."""
