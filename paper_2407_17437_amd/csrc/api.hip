@@ -483,7 +483,7 @@ StagedPlan plan_staged(int32_t all_rows, int32_t cols, const int32_t *indptr, co
     return H;
 }
 
-// the segment bounds of a plan from host copies of the pattern (what staged_ends_kernel computes for a layer)
+// the segment bounds of a plan from host copies of the pattern (what plan_cuts_kernel computes for a layer)
 void fill_staged_ends_host(StagedPlan &H, const int32_t *indptr, const int32_t *indices)
 {
     H.ends.assign(H.ends_ints(), 0);

@@ -1929,7 +1929,7 @@ __global__ __launch_bounds__(kEwBlock) void sddmm_finish_kernel(const SddmmArgs 
 // backward_finish_kernel, which stores the gradient or applies the momentum step through perm (mirror -> CSR position) and
 // forms the bias gradient (row sums of dZ).  A single tile needs no second pass.  Where the mirror rows do not make enough
 // waves several groups share a row.  What bounds it is the gathers, half of what the two products apart take: backward call
-// on 16384^2 power-law rows at 1 %, batch 1024: 1088 -> 570 us; uniform 8192^2 at 0.5 % / 5 %: 146 -> 91, 982 -> 648; at batch
+// on 16384^2 power-law rows at 1 %, batch 1024: 1088 -> 570 us (452 with the longest rows of dZ in LDS, backward_hot_kernel); uniform 8192^2 at 0.5 % / 5 %: 146 -> 91, 982 -> 648; at batch
 // 32: 18.1 -> 10.8, 100 -> 68; 1000 x 1000 at 0.5 %, one launch instead of three: 13.5 -> 5.8.
 constexpr int kBwdWaves = 4;  // waves per work-group: no sums across waves, and smaller groups schedule finer (measured on the wide MLP:
                               // 134 / 138 / 142 us with 4 / 8 / 16 waves; gather depth 4 instead of 8 and a register cap of 64 change nothing)
@@ -2054,8 +2054,8 @@ __device__ __forceinline__ void backward_row_sums(const BackwardArgs &a, int64_t
 // the lane groups and the matrix is small: then a wave takes its entries through all tiles.  XMASK: dZ is dY times
 // [Y > 0], gathered from both.
 enum BackwardPass { kBackwardTiles, kBackwardOneTile, kBackwardLooped };
-enum BackwardGathers { kGathersMixed, kGathersApart, kGathersSixteens };   // bwd_pass without and with APART; bwd_chunk
-template <int GS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE, BackwardGathers GATHERS>
+// SIXTEENS: bwd_chunk instead of bwd_pass, where the gathers would be APART.
+template <int GS, bool SIXTEENS, BackwardPass PASS, bool XMASK, BackwardSpare SPARE, bool APART>
 __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const BackwardArgs a, const int n_tiles, const TileOrder order,
                                                                           const int n_pack_blocks, const int lg_split)
 {
@@ -2078,7 +2078,6 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
     const int wv = wave_in_block();
     const int grp = lane / GS;
     const int lig = lane % GS;
-    constexpr bool SIXTEENS = GATHERS == kGathersSixteens, APART = GATHERS == kGathersApart;
     constexpr int CH = SIXTEENS ? 16 : GS;   // entries of a row in a chunk; lane lig % CH has its one
     const int mine = lig % CH;
     const uint32_t ldzb = static_cast<uint32_t>(a.lddz) * 4u, ldmb = XMASK ? static_cast<uint32_t>(a.ldzm) * 4u : 0u;
@@ -3982,12 +3981,12 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
                 constexpr BackwardPass P = decltype(pass)::value;
                 constexpr bool MASK = decltype(mask)::value;
                 const int64_t waves = static_cast<int64_t>(n_pack_blocks) * kBwdWaves;
-                auto kernel = backward_fused_kernel<GS, P, MASK, SPARE, kOne ? kGathersApart : kGathersMixed>;
+                auto kernel = backward_fused_kernel<GS, false, P, MASK, SPARE, kOne>;
                 if constexpr (kOne && (GS == 8 || SPARE == kSpareNone)) {   // (else both variants take the same registers)
                     if (!backward_gathers_apart(GS, waves, t, a.fused)) {
-                        kernel = backward_fused_kernel<GS, P, MASK, SPARE, kGathersMixed>;
+                        kernel = backward_fused_kernel<GS, false, P, MASK, SPARE, false>;
                     } else if constexpr (GS == 16 || GS == 32) {
-                        if (bwd_sixteens(waves, t)) kernel = backward_fused_kernel<GS, P, MASK, SPARE, kGathersSixteens>;
+                        if (bwd_sixteens(waves, t)) kernel = backward_fused_kernel<GS, true, P, MASK, SPARE, true>;
                     }
                 }
                 hipLaunchKernelGGL(kernel, grid, block, 0, s, a, n_tiles, order, n_pack_blocks, lg_split);
