@@ -1718,11 +1718,15 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
             last_sampled = l;
             return apart ? flush_sampled() : static_cast<int>(NERVA_OK);
         };
+        BackwardFinish finish{};   // layer 1's, which S_0 does not wait for
         auto run_S_alone = [&](int l) -> int {
             const SddmmArgs g = make_S(l);
-            if (sddmm_sampled_ok(g)) return defer_S(l);
+            if (sddmm_sampled_ok(g)) {
+                HIP_TRY(launch_backward_finish(finish, s));
+                return defer_S(l);
+            }
             Timed tm(mlp->prof, s, "sddmm_update", l);
-            HIP_TRY(launch_sddmm(g, s));
+            HIP_TRY(launch_sddmm(g, s, &finish));
             return NERVA_OK;
         };
         if (head) pending = n - 1;  // the head launch has run T_{n-1}
@@ -1768,7 +1772,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 if (pending >= 0 && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
                 pending = -1;
                 Timed tm(mlp->prof, s, "backward_fused", l);
-                HIP_TRY(launch_backward_fused(t, g_same, false, s));
+                HIP_TRY(launch_backward_fused(t, g_same, false, s, l == 1 && !mlp->prof.on ? &finish : nullptr));   // (a profile's slots hold what their names say)
                 continue;
             }
             if (pending >= 0) {

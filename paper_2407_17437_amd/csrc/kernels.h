@@ -289,7 +289,9 @@ struct SddmmArgs {
 // does not fit an L2; 0: no tiling.  Shared by the kernels' dispatch and by the sizing of the
 // SDDMM partial buffer when a layer is created.
 int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, int32_t longest_row, float hot_share, bool masked, bool for_sddmm = false);
-hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s);
+struct BackwardFinish;
+// first: a finish pass of the layer above that waits, which runs before or in this launch
+hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s, BackwardFinish *first = nullptr);
 // Slices of partial products (SddmmArgs::partial) that the column-tiled SDDMM and the fused backward pass take at any batch up to max_batch
 int32_t partial_tiles_wanted(const RowBlocks &plan, const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch);
 
@@ -325,7 +327,14 @@ struct BackwardArgs {
 bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone);
 // whether such a call also brings the mirror values (g.values_t) up to date with g.values, so that the caller need not
 bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g);
-hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s);
+// The second pass over the partial products, where it is left to a launch that follows (later, which launch_sddmm or launch_backward_finish take).
+struct BackwardFinish {
+    BackwardArgs a;
+    int32_t n_tiles, n_entry_blocks, n_row_blocks;
+    bool waiting;
+};
+hipError_t launch_backward_finish(BackwardFinish &f, hipStream_t s);
+hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s, BackwardFinish *later = nullptr);
 bool full_backward_ok(const SpmmArgs &t, const SddmmArgs &g);
 hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream_t s);
 

@@ -71,16 +71,16 @@ struct XcdRun {
     int64_t first, end, step;   // the work-group's first item, its XCD's last, the way from one turn to the next
 };
 template <int EACH = 1>
-__device__ __forceinline__ XcdRun xcd_run(int64_t n, int n_blocks)
+__device__ __forceinline__ XcdRun xcd_run(int64_t n, int n_blocks, uint32_t block = blockIdx.x)
 {
     constexpr int kItems = kEwBlock * EACH;
-    const int64_t per = ((n + kItems - 1) / kItems + 7) / 8 * kItems, first = (blockIdx.x & 7) * per;
-    return XcdRun{first + static_cast<int64_t>(blockIdx.x >> 3) * kItems, min(n, first + per), static_cast<int64_t>(n_blocks >> 3) * kItems};
+    const int64_t per = ((n + kItems - 1) / kItems + 7) / 8 * kItems, first = (block & 7) * per;
+    return XcdRun{first + static_cast<int64_t>(block >> 3) * kItems, min(n, first + per), static_cast<int64_t>(n_blocks >> 3) * kItems};
 }
 template <typename F>
-__device__ __forceinline__ void for_runs_of_xcds(int64_t n, int n_blocks, F &&f)
+__device__ __forceinline__ void for_runs_of_xcds(int64_t n, int n_blocks, F &&f, uint32_t block = blockIdx.x)
 {
-    const XcdRun run = xcd_run(n, n_blocks);
+    const XcdRun run = xcd_run(n, n_blocks, block);
     for (int64_t i = run.first + threadIdx.x; i < run.end; i += run.step) f(i);
 }
 // dst[i] = src[perm[i]]: many in kGatherEach a thread, whose reads travel together, few in one
@@ -500,15 +500,15 @@ enum : int { kTilesOneByOne = 0, kTilesWhole = -1 };
 struct TileOrder {
     int per, stride;   // an eighth of the grid (an argument: the grid's size costs a load), or one of the above
 };
-__device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, TileOrder order, int &tile, int &block)
+__device__ __forceinline__ bool tile_of_block(int n_tiles, int n_blocks, TileOrder order, int &tile, int &block, uint32_t id = blockIdx.x)
 {
     const int stride = order.stride;
-    int at = blockIdx.x;
-    if (order.per > 0) at = (blockIdx.x & 7) * order.per + (blockIdx.x >> 3);
-    if (order.per < 0) at = blockIdx.x >> 3;
+    int at = id;
+    if (order.per > 0) at = (id & 7) * order.per + (id >> 3);
+    if (order.per < 0) at = id >> 3;
     tile = at / n_blocks;
     block = at - tile * n_blocks;
-    if (order.per < 0) tile = tile * 8 + (blockIdx.x & 7);
+    if (order.per < 0) tile = tile * 8 + (id & 7);
     if (stride > 1) block = static_cast<int>(static_cast<uint32_t>(block) * static_cast<uint32_t>(stride) % static_cast<uint32_t>(n_blocks));
     return tile < n_tiles;
 }
@@ -1520,17 +1520,22 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
 // batch 300 / 450 / 700 30.0 / 30.4, 52.5 / 47.3, 74.8 / 66.2 us; 5000^2 at 1.2 % 28.0 / 28.0, 40.1 / 37.0, 56.0 / 51.1; 8192 x 3072 at 1.3 %, batch 700 / 1024 56.7 / 53.8, 68.3 / 67.1.
 constexpr int kSddmmWaves = 4, kSddmmParts = kWavesPerBlock / kSddmmWaves;
 template <int G, int NV, bool SPARE>
-__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order)
+__device__ __forceinline__ void sddmm_tile(const SddmmArgs &a, int n_tiles, TileOrder order, uint32_t id)
 {
     const int nrb = a.blocks.n_blocks * kSddmmParts;
     int tile, rb;
-    if (!tile_of_block(n_tiles, nrb, order, tile, rb)) return;
+    if (!tile_of_block(n_tiles, nrb, order, tile, rb, id)) return;
     SddmmArgs t = a;
     t.fused = 0;
     t.g = a.partial + static_cast<int64_t>(tile) * a.partial_stride;
     t.db = t.g + a.partial_db_at;
     if (tile != 0) t.loss_cols = nullptr;
     sddmm_body<G, NV, SPARE, false, kSddmmWaves>(t, rb, tile * (G * 4 * NV));
+}
+template <int G, int NV, bool SPARE>
+__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void sddmm_tiled_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order)
+{
+    sddmm_tile<G, NV, SPARE>(a, n_tiles, order, blockIdx.x);
 }
 
 // ---- staged SDDMM --------------------------------------------------------------------------
@@ -2202,9 +2207,9 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
 // Second pass: work-groups [0, n_entry_blocks) add the tiles' partial products of mirror entry q in tile
 // order and apply the momentum step to the entry's CSR position perm[q] (or store the gradient there);
 // the remaining work-groups, a wave per row of W, sum the rows of dZ for the bias gradient.
-__global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const BackwardArgs a, const int n_tiles, const int n_entry_blocks)
+__device__ __forceinline__ void backward_finish(const BackwardArgs &a, int n_tiles, int n_entry_blocks, int n_blocks, int block)
 {
-    if (static_cast<int>(blockIdx.x) < n_entry_blocks) {
+    if (block < n_entry_blocks) {
         for_runs_of_xcds(a.nnz, n_entry_blocks, [&](int64_t q) {
             const int p = a.perm[q];
             float g = 0.f;
@@ -2222,12 +2227,33 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
                 a.velocity[p] = v;
                 a.w_t[a.hot_at ? a.hot_at[q] : q] = w;
             }
-        });
+        }, block);
         return;
     }
     if (!(a.db || (a.fused && a.bias))) return;
-    backward_row_sums(a, static_cast<int64_t>(blockIdx.x - n_entry_blocks) * (kEwBlock / kWave) + wave_in_block(),
-                      static_cast<int64_t>(gridDim.x - n_entry_blocks) * (kEwBlock / kWave));
+    backward_row_sums(a, static_cast<int64_t>(block - n_entry_blocks) * (kEwBlock / kWave) + wave_in_block(),
+                      static_cast<int64_t>(n_blocks - n_entry_blocks) * (kEwBlock / kWave));
+}
+__global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const BackwardArgs a, const int n_tiles, const int n_entry_blocks)
+{
+    backward_finish(a, n_tiles, n_entry_blocks, gridDim.x, blockIdx.x);
+}
+
+// The same among the work-groups of the column-tiled SDDMM of the layer below, which only needs the dZ that this layer's pass has formed: a launch and one drained chip less.  Every `every`-th eight
+// work-groups (one to an XCD) are the finish pass's.  Wide MLP 322 -> 318 us a step (21 + 64 in turn, 83 together: the second pass's scattered lines take the same L2 requests as the gathers;
+// at twice to eight times the rate, or first of all, 305-310 where this order gives 303).
+template <int NV, bool SPARE>
+__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void sddmm_tiled_finish_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order, const BackwardArgs f,
+                                                                                                                         const int f_tiles, const int n_entry_blocks, const int n_finish, const int every)
+{
+    static_assert(kSddmmWaves * kWave == kEwBlock, "");
+    const int eight = blockIdx.x >> 3, turn = eight / every, groups = (n_finish + 7) / 8;
+    if (turn < groups && eight - turn * every == every - 1) {
+        const int block = turn * 8 + (blockIdx.x & 7);
+        if (block < n_finish) backward_finish(f, f_tiles, n_entry_blocks, n_finish, block);
+        return;
+    }
+    sddmm_tile<16, NV, SPARE>(a, n_tiles, order, (eight - min(turn, groups)) * 8 + (blockIdx.x & 7));
 }
 
 // ---- both gradients where a few rows of dZ take most gathers ------------------------------------------
@@ -3487,7 +3513,7 @@ void sddmm_finish_go(const SddmmArgs &a, int n_tiles, hipStream_t s)
 }
 
 template <int G, int NV>
-hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
+hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s, BackwardFinish *first = nullptr)
 {
     const int W = G * 4 * NV;
     const int n_tiles = (a.batch + W - 1) / W;
@@ -3495,7 +3521,21 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s)
     const TileOrder order = tile_order(n_tiles, n_blocks, W / 4, false, tiled_launch(a));
     const int64_t ids = tile_grid(order, n_tiles, n_blocks);
     dim3 grid(static_cast<unsigned>(ids));
+    if (first && ids >= (1 << 23)) {   // (threads are counted in 32 bits)
+        const hipError_t e = launch_backward_finish(*first, s);
+        if (e != hipSuccess) return e;
+    }
     with_spare(a.batch, W, [&](auto spare) {
+        if constexpr (G == 16) {
+            if (first && first->waiting) {
+                const int n_finish = first->n_entry_blocks + first->n_row_blocks, groups = (n_finish + 7) / 8;
+                const int64_t eights = (ids + 7) / 8 + groups;
+                first->waiting = false;
+                hipLaunchKernelGGL((sddmm_tiled_finish_kernel<NV, decltype(spare)::value>), dim3(static_cast<unsigned>(eights * 8)), dim3(kSddmmWaves * kWave), 0, s, a, n_tiles, order, first->a,
+                                   first->n_tiles, first->n_entry_blocks, n_finish, static_cast<int>(eights / groups));
+                return;
+            }
+        }
         hipLaunchKernelGGL((sddmm_tiled_kernel<G, NV, decltype(spare)::value>), grid, dim3(kSddmmWaves * kWave), 0, s, a, n_tiles, order);
     });
     sddmm_finish_go(a, n_tiles, s);
@@ -3935,7 +3975,15 @@ bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g)
            static_cast<int64_t>(t.nnz) * t.batch >= kHotWork;
 }
 
-hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s)
+hipError_t launch_backward_finish(BackwardFinish &f, hipStream_t s)
+{
+    if (!f.waiting) return hipSuccess;
+    f.waiting = false;
+    hipLaunchKernelGGL(backward_finish_kernel, dim3(f.n_entry_blocks + f.n_row_blocks), dim3(kEwBlock), 0, s, f.a, f.n_tiles, f.n_entry_blocks);
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s, BackwardFinish *later)
 {
     BackwardArgs a{};
     a.blocks = t.blocks; a.indices = t.indices; a.values = t.values;
@@ -3953,6 +4001,13 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     const bool one = n_tiles == 1 || (alone && backward_looped(t));
     const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
+    auto finish = [&](int tiles) {
+        BackwardFinish f{a, tiles, xcd_run_blocks(t.nnz), n_row_blocks, true};
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !later) return e != hipSuccess ? e : launch_backward_finish(f, s);
+        *later = f;
+        return hipSuccess;
+    };
     if (backward_hot_ok(t, g)) {
         StripGrid h;
         h.n_tiles = (t.batch + 63) / 64;
@@ -3965,9 +4020,7 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
                            refresh ? t.blocks.hot_perm : nullptr, t.nnz);
         hipLaunchKernelGGL(t.batch % 64 ? backward_hot_kernel<true> : backward_hot_kernel<false>, dim3(8u * h.per), dim3(kHotWaves * kWave), 0, s, a, h);
         a.perm = t.blocks.hot_perm; a.hot_at = t.blocks.hot_at;
-        const int n_entry_blocks = xcd_run_blocks(t.nnz);
-        hipLaunchKernelGGL(backward_finish_kernel, dim3(n_entry_blocks + n_row_blocks), dim3(kEwBlock), 0, s, a, h.n_tiles, n_entry_blocks);
-        return hipGetLastError();
+        return finish(h.n_tiles);
     }
     const TileOrder order = tile_order(n_tiles, n_pack_blocks, tg, false, tiled_launch(t));
     const int64_t ids = one ? n_pack_blocks + n_row_blocks : tile_grid(order, n_tiles, n_pack_blocks);
@@ -4015,9 +4068,7 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         default: go(std::integral_constant<int, 8>{}); break;
     }
     if (one) return hipGetLastError();
-    const int n_entry_blocks = xcd_run_blocks(t.nnz);
-    hipLaunchKernelGGL(backward_finish_kernel, dim3(n_entry_blocks + n_row_blocks), dim3(kEwBlock), 0, s, a, n_tiles, n_entry_blocks);
-    return hipGetLastError();
+    return finish(n_tiles);
 }
 
 // whether launch_spmm serves `a` by streaming (full matrix of few rows), where the softmax epilogue can ride along
@@ -4197,8 +4248,19 @@ int sddmm_tile_columns(const SddmmArgs &a)
     return w;
 }
 
-hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
+// Whether launch_sddmm takes a finish pass that waits into its grid.
+static bool sddmm_takes_finish(const SddmmArgs &a)
 {
+    if (a.rows <= 0 || a.batch <= 0 || a.blocks.n_blocks <= 0 || sddmm_sampled_ok(a) || sddmm_dense_rows_ok(a) || sddmm_full_ok(a) || sddmm_staged_ok(a)) return false;
+    return sddmm_tile_columns(a) == 128 || sddmm_tile_columns(a) == 64;
+}
+
+hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s, BackwardFinish *first)
+{
+    if (first && first->waiting && !sddmm_takes_finish(a)) {
+        const hipError_t e = launch_backward_finish(*first, s);
+        if (e != hipSuccess) return e;
+    }
     if (a.rows <= 0 || a.batch <= 0 || a.blocks.n_blocks <= 0) return hipSuccess;
     if (sddmm_sampled_ok(a)) {
         SampledArgs one{};
@@ -4245,8 +4307,8 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s)
         return hipGetLastError();
     }
     switch (sddmm_tile_columns(a)) {
-        case 128: return sddmm_tiled_go<16, 2>(a, s);
-        case 64: return sddmm_tiled_go<16, 1>(a, s);
+        case 128: return sddmm_tiled_go<16, 2>(a, s, first);
+        case 64: return sddmm_tiled_go<16, 1>(a, s, first);
         case 32: return sddmm_tiled_go<8, 1>(a, s);
         default: break;
     }

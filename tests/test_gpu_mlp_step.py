@@ -142,6 +142,29 @@ def test_stage_parity_staged_products(nb, torch_mod, oracle):
     M.close()
 
 
+@pytest.mark.parametrize("sizes,batch", [((12000, 2600, 2500, 10), 300), ((12000, 2600, 2500, 10), 448), ((5000, 2600, 2600, 40), 501), ((3072, 4100, 4099, 10), 1024)])
+def test_stage_parity_second_pass_among_the_first_layers_gradient(nb, torch_mod, oracle, sizes, batch):
+    """The hidden layer's partial products are added up, and its update applied, in the launch of the first layer's column-tiled SDDMM: tiles of 64 and 128 columns, with and without spare columns, with the row
+    sums of the hidden layer's bias gradient in it and without; two steps, and a step of the same state in launches of their own (as they are while a profile is taken) gives the same bits."""
+    torch = torch_mod
+    mlp = wl.make_mlp(sizes, sparsity=0.986, bias_std=0.1, pattern_seed=105, value_seed=205)
+    Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 2, seed=305)
+    M, P = nb.MLP(mlp, batch), nb.MLP(mlp, batch)
+    nb.mlp_profile_enable(P.handle, 1)
+    for t in range(2):
+        before = snapshot(M)
+        for m in (M, P):
+            m.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
+        torch.cuda.synchronize()
+        stage_parity(nb, torch, oracle, M, mlp, before, Xs[t], Ts[t], batch, 0.05, 0.9, False)
+    names = [n for n, _ in nb.mlp_profile_read(P.handle)[1]]
+    assert "backward_fused[1]" in names and "sddmm_update[0]" in names, names
+    for a, b in zip(snapshot(M), snapshot(P)):
+        assert all(np.array_equal(a[k], b[k]) for k in a)
+    M.close()
+    P.close()
+
+
 @pytest.mark.parametrize("hidden,sparsity", [((2600, 2600), 0.855), ((1800, 1300), 0.72)])
 def test_stage_parity_staged_gradients(nb, torch_mod, oracle, hidden, sparsity):
     """A hidden layer in segments of 70 and 120 whose transposed product (with the ReLU mask of the layer below applied as it is stored) is staged, and
