@@ -2664,8 +2664,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     int block = blockIdx.x;
     if (block < a.blocks.n_blocks) return chain_body<G, NV, SPARE, true>(c, a, block);
     block -= a.blocks.n_blocks;
-    if (block < b.blocks.n_blocks) return sddmm_body<GB, NVB, SPARE || GB != G>(b, block);
-    chain_row_sums<G, NV>(c, a, block - b.blocks.n_blocks);
+    if (block < n_sum_blocks) return chain_row_sums<G, NV>(c, a, block);
+    sddmm_body<GB, NVB, SPARE || GB != G>(b, block - n_sum_blocks);
 }
 
 // Its first half alone, dZ_0: for a step whose launches are kept apart, so that both form the same sums.
