@@ -101,7 +101,7 @@ struct PatternBuffers {
     size_t row_partial_floats = 0;
     int32_t *whole_staged = nullptr;   // staged plan of all rows beside that of the rows that are not dense
     size_t whole_staged_ints = 0;
-    int32_t *hot = nullptr;         // entry | at | count of RowBlocks::hot_*
+    int32_t *hot = nullptr;         // entry | at | count of HotRows
     size_t hot_ints = 0;
     DenseSplit split{};             // views into plan_mem and row_table
 };
@@ -122,6 +122,8 @@ struct nerva_layer {
     int32_t *pos_t = nullptr;      // [nnz] CSR position -> mirror position
     // static work partitions of W (by rows) and of the mirror (by W's columns): views into cur.plan_mem
     RowBlocks plan{}, plan_t{};
+    Strips strips;                  // segs nullptr: none
+    HotRows hot;                    // entry nullptr: none
     // owned scratch of the set-up kernels, and what they report (pinned host memory)
     int32_t *build_work = nullptr;
     size_t build_work_ints = 0;
@@ -849,7 +851,7 @@ static bool use_dense(const nerva_layer *l, int32_t batch) { return l->dense_on 
 // tickets of the huge rows of W (side 0) or of its mirror (side 1): rows of the two alternate
 static int32_t *tickets_of(const nerva_layer *l, int side) { return l->tickets ? l->tickets + side * huge_row_tickets(l->scratch_ld) : nullptr; }
 
-static float *hot_values_of(const nerva_layer *l) { return l->plan_t.hot_entry ? reinterpret_cast<float *>(l->cur.hot) + 3 * static_cast<size_t>(round_up(l->nnz, 64)) : nullptr; }
+static float *hot_values_of(const nerva_layer *l) { return l->hot.entry ? reinterpret_cast<float *>(l->cur.hot) + 3 * static_cast<size_t>(round_up(l->nnz, 64)) : nullptr; }
 
 static const DenseSplit *split_of(const nerva_layer *l) { return l->cur.split.rows.n > 0 ? &l->cur.split : nullptr; }
 
@@ -876,6 +878,8 @@ static int csr_status_error(const int32_t *st)
 constexpr size_t kPartialMaxBytes = 4ull << 30, kDzMaxBytes = 1ull << 30, kStripMaxBytes = 1ull << 30;
 struct BuiltPattern {
     RowBlocks plan{}, plan_t{};
+    Strips strips;                  // segs nullptr: none
+    HotRows hot;                    // entry nullptr: none
     int64_t partial_stride = 0, partial_db_at = 0;
     int32_t partial_tiles = 0;
     int64_t scratch_ld = 0, full_scratch_ld = 0;
@@ -1011,10 +1015,10 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
     if (hot_order_wanted(rows, cols, nnz, max_batch, out->plan_t.hot_share) && asked == NERVA_PARTITION_BALANCED && reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
-        RowBlocks &v = out->plan_t;
+        HotRows &v = out->hot;
         HIP_TRY(launch_hot_order(out->plan.rows_by_length, rows, B.indptr_t, m.indices_t, cols, m.perm, W + work_at[0], B.hot, B.hot + n64, B.hot + 2 * n64, p.side[1].tables.rows_by_length,
                                  reinterpret_cast<int4 *>(B.hot + 4 * n64), s));
-        v.hot_entry = B.hot; v.hot_at = B.hot + n64; v.hot_perm = B.hot + 2 * n64; v.hot_sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.hot_rows = out->plan.rows_by_length;
+        v.entry = B.hot; v.at = B.hot + n64; v.perm = B.hot + 2 * n64; v.sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.rows = out->plan.rows_by_length;
         more_work = true;
     }
 
@@ -1025,7 +1029,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         // that they are not worth it), below which the kernels without them stay
         int32_t tiles = partial_tiles_wanted(out->plan, out->plan_t, rows, cols, nnz, max_batch);
         if ((out->plan.staged_rows || B.split.others.staged_rows) && (max_batch + kStageCols - 1) / kStageCols > tiles) tiles = (max_batch + kStageCols - 1) / kStageCols;
-        if (out->plan_t.hot_entry) tiles = std::max(tiles, (max_batch + 63) / 64);
+        if (out->hot.entry) tiles = std::max(tiles, (max_batch + 63) / 64);
         out->partial_db_at = round_up(nnz, 64);
         out->partial_stride = out->partial_db_at + round_up(rows, 64);
         const size_t slice = static_cast<size_t>(out->partial_stride);
@@ -1040,11 +1044,11 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         const int64_t slots = out->plan.n_huge_blocks > out->plan_t.n_huge_blocks ? out->plan.n_huge_blocks : out->plan_t.n_huge_blocks;
         if (const size_t chunks = static_cast<uint32_t>(R.strip), need = (chunks + 2) * kStripChunk * kStripSet * 2;
             chunks > 0 && need * 4 <= kStripMaxBytes && reserve_optional(&l->strip_stream, &l->strip_floats, need)) {
-            RowBlocks &v = out->plan;
-            v.strip_rows = p.side[0].tables.strip_rows; v.strip_segs = p.side[0].tables.strip_segs; v.strip_cuts = p.side[0].tables.strip_cuts;
-            v.strip_blocks = room.strip_blocks; v.strip_block_rows = strip_block_rows_of(cols);
-            v.strip_chunks = static_cast<int32_t>(chunks); v.strip_steps = static_cast<int32_t>(R.strip >> 32);
-            v.strip_preferred = p.prefer_strips;
+            Strips &v = out->strips;
+            v.rows = p.side[0].tables.strip_rows; v.segs = p.side[0].tables.strip_segs; v.cuts = p.side[0].tables.strip_cuts;
+            v.blocks = room.strip_blocks; v.block_rows = strip_block_rows_of(cols);
+            v.chunks = static_cast<int32_t>(chunks); v.steps = static_cast<int32_t>(R.strip >> 32);
+            v.preferred = p.prefer_strips;
         }
         out->scratch_ld = round_up(max_batch, 64);
         if (slots > 0) {
@@ -1074,7 +1078,7 @@ static void adopt_pattern(nerva_layer *l, int32_t nnz, const int32_t *indptr, co
     l->perm = l->cur.mirror_mem + n64;
     l->pos_t = l->cur.mirror_mem + 2 * n64;
     l->values_t = reinterpret_cast<float *>(l->cur.mirror_mem + 3 * n64);
-    l->plan = bp.plan; l->plan_t = bp.plan_t;
+    l->plan = bp.plan; l->plan_t = bp.plan_t; l->strips = bp.strips; l->hot = bp.hot;
     l->partial_stride = bp.partial_stride; l->partial_db_at = bp.partial_db_at; l->partial_tiles = bp.partial_tiles;
     l->scratch_ld = bp.scratch_ld;
     l->full_scratch_ld = bp.full_scratch_ld;
@@ -1232,7 +1236,7 @@ int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx,
     }
     SpmmArgs a{};
     a.blocks = layer->plan; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 0); a.scratch_ld = layer->scratch_ld;
-    a.strip_stream = reinterpret_cast<float4 *>(layer->strip_stream);
+    a.strips = layer->strips.segs ? &layer->strips : nullptr; a.strip_stream = reinterpret_cast<float4 *>(layer->strip_stream);
     a.indptr = layer->indptr; a.indices = layer->indices; a.values = layer->values; a.bias = layer->bias;
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
     a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.relu = layer->activation == NERVA_ACT_RELU;
@@ -1260,7 +1264,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
     bool form_dz = false, mask = relu;   // mask: dY still is the gradient of the output
     auto make_t = [&] {
         SpmmArgs a{};
-        a.blocks = layer->plan_t; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 1); a.scratch_ld = layer->scratch_ld;
+        a.blocks = layer->plan_t; a.hot = layer->hot.entry ? &layer->hot : nullptr; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 1); a.scratch_ld = layer->scratch_ld;
         a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
         a.X = dY; a.ldx = lddy;
         if (mask) { a.XM = Y; a.ldxm = ldy; }
@@ -1497,7 +1501,7 @@ static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldi
 {
     SpmmArgs a{};
     a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = tickets_of(ly, 0); a.scratch_ld = ly->scratch_ld;
-    a.strip_stream = reinterpret_cast<float4 *>(ly->strip_stream);
+    a.strips = ly->strips.segs ? &ly->strips : nullptr; a.strip_stream = reinterpret_cast<float4 *>(ly->strip_stream);
     a.indptr = ly->indptr; a.indices = ly->indices; a.values = ly->values; a.bias = ly->bias;
     a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
     a.rows = ly->rows; a.x_rows = ly->cols; a.batch = batch; a.relu = ly->activation == NERVA_ACT_RELU;
@@ -1621,7 +1625,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         // applied as the transposed product is stored
         nerva_layer *ly = mlp->layers[l];
         SpmmArgs t{};
-        t.blocks = ly->plan_t; t.nnz = ly->nnz; t.scratch = ly->scratch; t.tickets = tickets_of(ly, 1); t.scratch_ld = ly->scratch_ld;
+        t.blocks = ly->plan_t; t.hot = ly->hot.entry ? &ly->hot : nullptr; t.nnz = ly->nnz; t.scratch = ly->scratch; t.tickets = tickets_of(ly, 1); t.scratch_ld = ly->scratch_ld;
         t.indptr = ly->indptr_t; t.indices = ly->indices_t; t.values = ly->values_t;
         t.X = dZ(l); t.ldx = L.ld; t.Y = dZ(l - 1); t.ldy = L.ld;
         t.YM = A(l - 1); t.ldym = L.ld;

@@ -56,21 +56,26 @@ struct RowBlocks {
     int32_t staged_nnz;            // and their stored entries
     int32_t staged_preferred;      // measurement aid: take the staged kernels wherever they can run
     const int4 *rows_by_length;    // every row, as in short_rows (which is the end of this table)
-    // Optional fourth form, for the product in strips (spmm_strip_kernel; strip_segs != nullptr): sets of kStripSet rows, longer ones first,
-    // cut into segments at the multiples of strip_block_rows in the column indices.
-    const int32_t *strip_rows;     // [sets * kStripSet] row or -1
-    const int2 *strip_segs;        // [sets * strip_blocks] {first chunk of the stream, entries of the longest of the set's segments in that block}
-    const int32_t *strip_cuts;     // [sets * (strip_blocks + 1) * kStripSet] position of a row's first entry of a block, and one past its last
-    int32_t strip_blocks, strip_block_rows;
-    int32_t strip_chunks, strip_steps;   // of the stream; the sum of the longest segments
-    int32_t strip_preferred;             // measurement aid: take it wherever it can run
-    // Of a mirror, where a few rows of the matrix hold most of its entries (backward_hot_kernel), or nullptr: the entries of a mirror row in another order, those of the
-    // kHotRowsLds longest rows of the matrix first.
-    const int32_t *hot_entry;      // [nnz] 256 times the row's place among the longest, for the hot ones of a mirror row; the row itself for the others
-    const int32_t *hot_at;         // [nnz] the entry's position in the mirror
-    const int4 *hot_sets;          // [mirror rows, padded as rows_by_length] {row or -1, first entry, entries, hot ones}: longest first, those of about one length by their hot entries
-    const int32_t *hot_perm;       // [nnz] CSR position
-    const int4 *hot_rows;          // the matrix's rows_by_length
+};
+
+// What few kernels read of a pattern, apart from RowBlocks, which every launch carries (with these and the strips' in it calls of 4 to 12 us took 1 to 4 % longer).
+// The product in strips (spmm_strip_kernel): sets of kStripSet rows, longer ones first, cut into segments at the multiples of block_rows in the column indices.
+struct Strips {
+    const int32_t *rows = nullptr;    // [sets * kStripSet] row or -1
+    const int2 *segs = nullptr;       // [sets * blocks] {first chunk of the stream, entries of the longest of the set's segments in that block}
+    const int32_t *cuts = nullptr;    // [sets * (blocks + 1) * kStripSet] position of a row's first entry of a block, and one past its last
+    int32_t blocks = 0, block_rows = 0;
+    int32_t chunks = 0, steps = 0;    // of the stream; the sum of the longest segments
+    int32_t preferred = 0;            // measurement aid: take it wherever it can run
+};
+// Of a mirror, where a few rows of the matrix hold most of its entries (backward_hot_kernel): the entries of a mirror row in another order, those of the
+// kHotRowsLds longest rows of the matrix first.
+struct HotRows {
+    const int32_t *entry = nullptr;   // [nnz] 256 times the row's place among the longest, for the hot ones of a mirror row; the row itself for the others
+    const int32_t *at = nullptr;      // [nnz] the entry's position in the mirror
+    const int4 *sets = nullptr;       // [mirror rows, padded as rows_by_length] {row or -1, first entry, entries, hot ones}: longest first, those of about one length by their hot entries
+    const int32_t *perm = nullptr;    // [nnz] CSR position
+    const int4 *rows = nullptr;       // the matrix's rows_by_length
 };
 
 // Strips: kStripRows operand rows of kStripCols columns lie in LDS at a time; the operand's blocks are of equal size, a multiple of 256 rows.
@@ -201,6 +206,8 @@ struct SpmmArgs {
     int64_t ce_lddz;
     float *ce_loss_cols;       // [batch]
     const DenseSplit *split;   // (for the launch) or nullptr
+    const Strips *strips;      // the pattern's (host memory: the launch hands it on), or nullptr
+    const HotRows *hot;        // of a mirror, likewise
     float4 *strip_stream;      // room for the plan's chunks and two more, or nullptr
     int32_t strip_ready;       // (for the launch) launch_strip_streams has filled it
 };
@@ -320,7 +327,7 @@ struct BackwardArgs {
     float lr, momentum;
     float *w, *velocity, *w_t;   // values[], velocity[] (CSR order), mirror values
     float *bias, *bias_velocity;
-    const float *hot_values;     // mirror values in the order of RowBlocks::hot_*
+    const float *hot_values;     // mirror values in the order of HotRows
     const int32_t *hot_at;       // or nullptr
 };
 // alone: a single call, not part of a training step, where the two may share their launches with other layers' instead
@@ -568,7 +575,7 @@ __host__ __device__ inline bool strip_wanted(int32_t rows, int32_t cols, int64_t
     return strip_possible(rows, cols, nnz, max_batch) && rows >= 256 && cols >= 1024 && nnz * max_batch >= (96 << 20) && nnz >= 4 * segments && nnz <= 160 * segments;
 }
 __host__ __device__ inline bool strip_even(int32_t longest_row, int32_t rows, int64_t nnz) { return static_cast<int64_t>(longest_row) * rows <= 3 * nnz; }
-// Whether a mirror gets the order of RowBlocks::hot_*: the kHotRows longest rows hold half of the entries, and the layer's widest batch has the work (backward_hot_ok asks more closely).
+// Whether a mirror gets the order of HotRows: the kHotRows longest rows hold half of the entries, and the layer's widest batch has the work (backward_hot_ok asks more closely).
 constexpr int32_t kHotFromBatch = 192;
 constexpr int64_t kHotTasks = 5000, kHotEntries = 45, kHotWork = 96ll << 20;
 inline int64_t hot_sets_size(int32_t rows) { return (static_cast<int64_t>(rows) + 255) / 256 * 256; }

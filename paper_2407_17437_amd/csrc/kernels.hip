@@ -1202,7 +1202,7 @@ __device__ __forceinline__ void strip_steps(const char *lds, const float4 &c, fl
 struct StripGrid {
     int n_tiles, n_ranges, per;     // strips, ranges of sets, an eighth of the grid
 };
-__global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const SpmmArgs a, const StripGrid g)
+__global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const SpmmArgs a, const StripGrid g, const Strips f)
 {
     __shared__ float4 strip[kStripRows * kStripCols / 4 + kStripCols / 4];  // the block, then one row of zeros
     // (neighbouring tiles share lines of the operand, all ranges of a tile its rows: a run of the list of both to an XCD)
@@ -1218,10 +1218,10 @@ __global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const S
     if (threadIdx.x < kStripCols / 4) strip[kStripRows * kStripCols / 4 + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);  // (visible after the first barrier)
     constexpr auto all_j = std::make_integer_sequence<int, kStripJ>{};
     // Set J of the wave (longest first, dealt there and back); lane J keeps its segment, block after block.
-    const int n_sets = (a.rows + kStripSet - 1) / kStripSet, round = kStripWaves * g.n_ranges, mine = wv * g.n_ranges + range, n_blocks = a.blocks.strip_blocks;
+    const int n_sets = (a.rows + kStripSet - 1) / kStripSet, round = kStripWaves * g.n_ranges, mine = wv * g.n_ranges + range, n_blocks = f.blocks;
     auto set_of = [&](int j) { return j * round + (j & 1 ? round - 1 - mine : mine); };
     const int my_set = set_of(lane & (kStripJ - 1));
-    const int2 *my_segs = a.blocks.strip_segs + static_cast<int64_t>(my_set) * n_blocks;
+    const int2 *my_segs = f.segs + static_cast<int64_t>(my_set) * n_blocks;
     auto segment = [&](int b) { return b < n_blocks && my_set < n_sets ? my_segs[b] : make_int2(0, 0); };
     float4 acc[kStripJ];
     static_for(all_j, [&](auto jc) { acc[decltype(jc)::value] = make_float4(0.f, 0.f, 0.f, 0.f); });
@@ -1238,7 +1238,7 @@ __global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const S
     constexpr int kShare = kStripRows / 256;
     float4 v[kShare];
     const float *const my_x = a.X + static_cast<int64_t>(threadIdx.x >> 2) * a.ldx + col;
-    const int last_rows = a.x_rows - 256, last_i = (a.blocks.strip_block_rows >> 8) - 1;
+    const int last_rows = a.x_rows - 256, last_i = (f.block_rows >> 8) - 1;
     auto ask_rows = [&](int i, int cb0, int last) { v[i] = ld4(my_x + static_cast<int64_t>(min(cb0 + min(i, last_i) * 256, last)) * a.ldx); };
     auto put_rows = [&](int cb0) {
 #pragma unroll
@@ -1251,7 +1251,7 @@ __global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const S
     // the wave's segments of a block, the next block's rows asked for beside them; of the last block with what is done to a row once it is complete
     auto serve = [&](int b, auto last_one) {
         constexpr bool last = decltype(last_one)::value;
-        const int cb0 = strip_block_base(b, a.blocks.strip_block_rows, a.x_rows), cb_next = strip_block_base(b + 1, a.blocks.strip_block_rows, a.x_rows);
+        const int cb0 = strip_block_base(b, f.block_rows, a.x_rows), cb_next = strip_block_base(b + 1, f.block_rows, a.x_rows);
         const int2 after = segment(b + 2);
         int row[kStripJ / 4];     // lane k of a quad: of sets k, k + 4
         float bias[kStripJ / 4];
@@ -1261,7 +1261,7 @@ __global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const S
 #pragma unroll
             for (int k = 0; k < kStripJ / 4; ++k) {
                 const int set = set_of(k * 4 + lig);
-                row[k] = set < n_sets ? a.blocks.strip_rows[set * kStripSet + (lane >> 2)] : -1;
+                row[k] = set < n_sets ? f.rows[set * kStripSet + (lane >> 2)] : -1;
                 bias[k] = a.bias ? a.bias[max(row[k], 0)] : 0.f;
             }
         lds_barrier();
@@ -2259,7 +2259,7 @@ __global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_pe
 // ---- both gradients where a few rows of dZ take most gathers ------------------------------------------
 // The backward pass on one gather stream (backward_fused_kernel) for matrices a few of whose rows hold most of the entries: the kHotRowsLds longest rows of W -- two thirds of the entries of 16384^2
 // power-law rows at 1 % -- are gathered from LDS, in which a work-group keeps its 64 columns of their dZ, the others from memory.  The entries of a mirror row are taken hot ones first
-// (RowBlocks::hot_*, made when the pattern is bound).  Sixteen lanes serve a mirror row, four of which run side by side in a wave; a gathered row goes into the row's result with the weight moved
+// (HotRows, made when the pattern is bound).  Sixteen lanes serve a mirror row, four of which run side by side in a wave; a gathered row goes into the row's result with the weight moved
 // between lanes in the multiply-add (fma_row_lane), and into the entry's product with the mirror row's X, sixteen products at a time added up across the lanes (row16_transpose_sum).
 // What bounds it: the vector ALUs (11.3 instructions a gather of four rows by 64 columns, 74 % busy at the 1.8 GHz that the card then holds; texture-address units 67 %, where the pass without LDS has
 // them 79 % busy).  16384^2 at 1 %, batch 1024: 490 -> 370 us; of it, weights and sums in the order of the walk (stored through the mirror's positions: 50 more), rows side by side of like
@@ -2322,7 +2322,7 @@ __global__ __launch_bounds__(kEwBlock) void hot_values_kernel(float *out, const 
     });
 }
 template <bool SPARE>
-__global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const BackwardArgs a, const StripGrid g)
+__global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const BackwardArgs a, const StripGrid g, const HotRows f)
 {
     __shared__ float4 hot[kHotRowsLds * 16 + 16];   // the rows, then one of zeros
     __shared__ int taken;
@@ -2343,7 +2343,7 @@ __global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const B
         float4 v[kHotRowsLds / 64];
 #pragma unroll
         for (int i = 0; i < kHotRowsLds / 64; ++i)
-            v[i] = ld4(a.dZ + static_cast<int64_t>(a.blocks.hot_rows[i * 64 + static_cast<int>(threadIdx.x >> 4)].x) * a.lddz + col);
+            v[i] = ld4(a.dZ + static_cast<int64_t>(f.rows[i * 64 + static_cast<int>(threadIdx.x >> 4)].x) * a.lddz + col);
 #pragma unroll
         for (int i = 0; i < kHotRowsLds / 64; ++i) hot[i * 1024 + static_cast<int>(threadIdx.x)] = owned(v[i]);
     }
@@ -2377,9 +2377,9 @@ __global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const B
     auto ask = [&](const Set &s, bool is_hot, int first) {
         const int e = first + lig, n = is_hot ? s.n_hot : s.len - s.n_hot;
         const uint32_t o = e < n ? static_cast<uint32_t>(s.s0 + (is_hot ? 0 : s.n_hot) + e) * 4u : 0u;
-        return Chunk{__builtin_bit_cast(int, gload1(as_gmem(a.blocks.hot_entry), o)), gload1(as_gmem(a.hot_values), o)};
+        return Chunk{__builtin_bit_cast(int, gload1(as_gmem(f.entry), o)), gload1(as_gmem(a.hot_values), o)};
     };
-    auto record = [&](int set) { return set < n_sets ? a.blocks.hot_sets[set * 4 + lrow] : make_int4(-1, 0, 0, 0); };
+    auto record = [&](int set) { return set < n_sets ? f.sets[set * 4 + lrow] : make_int4(-1, 0, 0, 0); };
     auto input = [&](const Set &s) { return ld4(a.X + static_cast<int64_t>(max(s.row, 0)) * a.ldx + col); };
     int set = take(), set_next = take();
     Set now = set_of(record(set));
@@ -2399,7 +2399,7 @@ __global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const B
             // what a lane without a cold entry gathers, with weight 0: a row of dZ that the mirror row references anyway, its first cold one, or, without any, a hot one
             // (an empty row: row 0, for a result that is not taken)
             fill = row_lane<0>(cold_now.entry);
-            if (__any(n_cold == 0)) fill = n_cold > 0 ? fill : now.len > 0 ? a.blocks.hot_rows[a.blocks.hot_entry[now.s0] >> 8].x : 0;
+            if (__any(n_cold == 0)) fill = n_cold > 0 ? fill : now.len > 0 ? f.rows[f.entry[now.s0] >> 8].x : 0;
         }
         auto hot_sums = [&](const Chunk &c, int e) {   // (a row of zeros for a lane without an entry)
             const bool ok = e + lig < now.n_hot;
@@ -3431,14 +3431,14 @@ static StripPlan strip_plan(const SpmmArgs &a)
     StripPlan p{};
     p.grid.n_tiles = (a.batch + kStripCols - 1) / kStripCols;
     const int64_t sets = (static_cast<int64_t>(a.rows) + kStripSet - 1) / kStripSet, least = (sets + kStripWaves * kStripJ - 1) / (kStripWaves * kStripJ);
-    const double steps = a.blocks.strip_steps, per_set = steps / static_cast<double>(sets);
+    const double steps = a.strips->steps, per_set = steps / static_cast<double>(sets);
     for (int64_t more = 0, first = (p.grid.n_tiles * least + 255) / 256; more < 4; ++more) {   // (of the ranges that a number of rounds holds the most)
         const int64_t r = std::max(least, 256 * (first + more) / p.grid.n_tiles);
         const double rounds = static_cast<double>((p.grid.n_tiles * r + 255) / 256), most = static_cast<double>((sets + kStripWaves * r - 1) / (kStripWaves * r));
-        const double us = rounds * (1.8 + 3.0e-3 * steps / static_cast<double>(r) + 12.7e-3 * most * per_set + 0.5e-3 * a.x_rows + 2.6 * a.blocks.strip_blocks);
+        const double us = rounds * (1.8 + 3.0e-3 * steps / static_cast<double>(r) + 12.7e-3 * most * per_set + 0.5e-3 * a.x_rows + 2.6 * a.strips->blocks);
         if (p.grid.n_ranges == 0 || us < p.us) { p.us = us; p.grid.n_ranges = static_cast<int>(r); }
     }
-    p.us += 6.3 + 0.64e-3 * a.blocks.strip_chunks;
+    p.us += 6.3 + 0.64e-3 * a.strips->chunks;
     p.grid.per = static_cast<int>((static_cast<int64_t>(p.grid.n_tiles) * p.grid.n_ranges + 7) / 8);
     return p;
 }
@@ -3460,9 +3460,9 @@ static bool strip_pays(const SpmmArgs &a)
 }
 bool spmm_strip_ok(const SpmmArgs &a)
 {
-    if (!a.blocks.strip_segs || !a.strip_stream || a.XM || a.batch <= kStripFromBatch) return false;
+    if (!a.strips || !a.strip_stream || a.XM || a.batch <= kStripFromBatch) return false;
     const int64_t groups = (static_cast<int64_t>(a.rows) + kStripSet * kStripWaves * kStripJ - 1) / (kStripSet * kStripWaves * kStripJ) * ((a.batch + kStripCols - 1) / kStripCols);
-    return groups < (1 << 28) && (a.blocks.strip_preferred || strip_pays(a));
+    return groups < (1 << 28) && (a.strips->preferred || strip_pays(a));
 }
 
 bool spmm_staged_ok(const SpmmArgs &a)
@@ -3968,7 +3968,7 @@ static bool bwd_sixteens(int64_t waves, const SpmmArgs &t) { return waves <= 409
 // batch 881 43 -> 51; few mirror rows: 12284 x 1987 at 5.4 %, batch 289 117 -> 133; spare columns: 5379 mirror rows, batch 116 101 -> 117.
 bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g)
 {
-    if (!t.blocks.hot_entry || !g.hot_values || t.XM || !g.partial) return false;
+    if (!t.hot || !g.hot_values || t.XM || !g.partial) return false;
     const int64_t tiles = (static_cast<int64_t>(t.batch) + 63) / 64, sets = (static_cast<int64_t>(t.rows) + 3) / 4;
     if (tiles > g.partial_tiles || g.partial_stride < t.nnz) return false;
     return t.batch >= kHotFromBatch && t.batch * 20ll >= tiles * 64 * 17 && sets * tiles >= kHotTasks && t.nnz >= (t.x_rows > 6144 ? 85ll : kHotEntries) * t.rows &&
@@ -4016,10 +4016,10 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         h.per = (h.n_tiles * h.n_ranges + 7) / 8;
         a.hot_values = g.hot_values;
         const bool refresh = alone && g.values;   // (backward_fused_refreshes: the call leaves it to this launch)
-        hipLaunchKernelGGL(hot_values_kernel, dim3(xcd_run_blocks(t.nnz)), dim3(kEwBlock), 0, s, g.hot_values, refresh ? g.values : t.values, g.values_t, t.blocks.hot_at,
-                           refresh ? t.blocks.hot_perm : nullptr, t.nnz);
-        hipLaunchKernelGGL(t.batch % 64 ? backward_hot_kernel<true> : backward_hot_kernel<false>, dim3(8u * h.per), dim3(kHotWaves * kWave), 0, s, a, h);
-        a.perm = t.blocks.hot_perm; a.hot_at = t.blocks.hot_at;
+        hipLaunchKernelGGL(hot_values_kernel, dim3(xcd_run_blocks(t.nnz)), dim3(kEwBlock), 0, s, g.hot_values, refresh ? g.values : t.values, g.values_t, t.hot->at,
+                           refresh ? t.hot->perm : nullptr, t.nnz);
+        hipLaunchKernelGGL(t.batch % 64 ? backward_hot_kernel<true> : backward_hot_kernel<false>, dim3(8u * h.per), dim3(kHotWaves * kWave), 0, s, a, h, *t.hot);
+        a.perm = t.hot->perm; a.hot_at = t.hot->at;
         return finish(h.n_tiles);
     }
     const TileOrder order = tile_order(n_tiles, n_pack_blocks, tg, false, tiled_launch(t));
@@ -4102,8 +4102,8 @@ hipError_t launch_strip_streams(const SpmmArgs *list, int n, hipStream_t s)
     unsigned most = 0;
     for (int k = 0; k < n; ++k) {
         const SpmmArgs &a = list[k];
-        all.of[k] = StripStream{a.blocks.strip_segs, a.blocks.strip_cuts, a.indices, a.values, a.strip_stream, (a.rows + kStripSet - 1) / kStripSet,
-                                a.blocks.strip_blocks, a.blocks.strip_block_rows, a.x_rows, a.nnz};
+        all.of[k] = StripStream{a.strips->segs, a.strips->cuts, a.indices, a.values, a.strip_stream, (a.rows + kStripSet - 1) / kStripSet,
+                                a.strips->blocks, a.strips->block_rows, a.x_rows, a.nnz};
         most = std::max(most, static_cast<unsigned>((all.of[k].sets * all.of[k].blocks + kStripStreamWaves - 1) / kStripStreamWaves));
     }
     hipLaunchKernelGGL(strip_stream_kernel, dim3(most, n), dim3(kStripStreamWaves * kWave), 0, s, all);
@@ -4147,7 +4147,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         SpmmArgs others = a;
         others.blocks = a.split->others;
         others.split = nullptr;
-        others.blocks.strip_segs = nullptr;   // (its rows are all, the dense ones too)
+        others.strips = nullptr;   // (its rows are all, the dense ones too)
         return launch_spmm(others, s);
     }
     if (spmm_strip_ok(a)) {
@@ -4156,7 +4156,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
             const hipError_t e = launch_strip_streams(&a, 1, s);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(spmm_strip_kernel, dim3(8u * static_cast<unsigned>(g.per)), dim3(kStripWaves * kWave), 0, s, a, g);
+        hipLaunchKernelGGL(spmm_strip_kernel, dim3(8u * static_cast<unsigned>(g.per)), dim3(kStripWaves * kWave), 0, s, a, g, *a.strips);
         return hipGetLastError();
     }
     if (spmm_staged_ok(a)) {
@@ -4180,7 +4180,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
                 }
             }
             rest.blocks.staged_rows = nullptr;
-            rest.blocks.strip_segs = nullptr;
+            rest.strips = nullptr;
             rest.blocks.n_short = 0;
             rest.blocks.waves = a.blocks.rest_waves;
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
@@ -4205,7 +4205,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
             rest.blocks.n_short = 0;
             rest.blocks.n_long_blocks = 0;   // (nothing left to split off)
             rest.blocks.staged_rows = nullptr;
-            rest.blocks.strip_segs = nullptr;
+            rest.strips = nullptr;
             const hipError_t e = launch_spmm(rest, s);
             if (e != hipSuccess) return e;
             switch (sg) {

@@ -870,7 +870,7 @@ __device__ __forceinline__ void staged_ends(const PlanSide &S, int64_t thread, i
     }
 }
 
-// Plan of the product in strips (RowBlocks::strip_*), a work-group per kStripGroup rows of rows_by_length: where the blocks cut each row; which rows go together; the longest segment of every
+// Plan of the product in strips (Strips), a work-group per kStripGroup rows of rows_by_length: where the blocks cut each row; which rows go together; the longest segment of every
 // set and block, and its place in the stream.  Sixteen rows run side by side for as long as the longest of them has entries in a block, so rows of about one length are put together by
 // their entries in the first block, and 64 at a time of these by theirs in the second: of the steps 0.82 are entries of 8192^2 at 0.74 % (0.71 by length alone), 0.97 of
 // 8192 x 3072 at 1.4 % (0.79), 0.77 of 16384^2 at 1 % (0.73).  Product and stream 68 -> 58, 49 -> 41, 257 -> 245 us at batch 1024.
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(kBig) void plan_cuts_kernel(const PlanArgs A, const
     staged_ends(S, static_cast<int64_t>(e % kEndsBlocks) * kBig + threadIdx.x, static_cast<int64_t>(kEndsBlocks) * kBig);
 }
 
-// Entries of the mirror rows in the order of RowBlocks::hot_*: every row's place among the longest, or -1; then a wave per mirror row.
+// Entries of the mirror rows in the order of HotRows: every row's place among the longest, or -1; then a wave per mirror row.
 __global__ __launch_bounds__(kSetupBlock) void hot_place_kernel(const int4 *rows_by_length, const int32_t n, int32_t *place)
 {
     const int32_t e = blockIdx.x * kSetupBlock + threadIdx.x;
