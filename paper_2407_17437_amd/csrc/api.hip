@@ -1776,7 +1776,8 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 if (pending >= 0 && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
                 pending = -1;
                 Timed tm(mlp->prof, s, "backward_fused", l);
-                HIP_TRY(launch_backward_fused(t, g_same, false, s, l == 1 && !mlp->prof.on ? &finish : nullptr));   // (a profile's slots hold what their names say)
+                // (not while a profile is on, whose slots hold what their names say, nor where both layers are one handle: S_0 would write the partial products that the finish pass reads)
+                HIP_TRY(launch_backward_fused(t, g_same, false, s, l == 1 && !mlp->prof.on && mlp->layers[0] != mlp->layers[1] ? &finish : nullptr));
                 continue;
             }
             if (pending >= 0) {

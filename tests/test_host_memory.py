@@ -348,7 +348,33 @@ def products_of_very_many_entries_are_staged(L):
         L.destroy()
 
 
-CASES = [products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only(L):
+    """Layer 1's second pass rides in the launch of layer 0's column-tiled gradient, which writes partial products of its own: not where an MLP holds one handle twice."""
+    def layer(rows, cols, nnz, relu):
+        L.counts(0, n_blocks=600, longest_row=90, hot_nnz=nnz // 2 - 9)
+        L.counts(1, n_blocks=600, longest_row=90, hot_nnz=nnz // 2 - 9)
+        assert L.create(rows, cols, nnz, 700, relu=relu) == 0
+        handle, L.layer = L.layer, ctypes.c_void_p()
+        return handle
+
+    first, second, last = layer(2600, 2600, 94640, True), layer(2600, 2600, 94640, True), layer(40, 2600, 1456, False)
+    p = ctypes.addressof(L.host[3])
+    for handles, together in (((first, second, last), True), ((first, first, last), False)):
+        mlp, three = ctypes.c_void_p(), ctypes.c_void_p * 3
+        assert L.lib.mlp_create(ctypes.byref(mlp), 3, three(*handles), three(p, p, p), three(p, p, p), 700, 0) == 0
+        L.lib.mlp_workspace_bytes.restype = ctypes.c_size_t
+        room = L.lib.mlp_workspace_bytes(mlp, 700)
+        held = (ctypes.c_char * (room + 256))()
+        work = ctypes.c_void_p(ctypes.addressof(held) + -ctypes.addressof(held) % 256)
+        L.launched()
+        assert L.lib.mlp_train_step(mlp, ctypes.c_void_p(p), 700, ctypes.c_void_p(p), 700, ctypes.c_float(0.1), ctypes.c_float(0.9), work, ctypes.c_size_t(room), None, None) == 0, L.lib.nerva_last_error()
+        names = L.launched()
+        assert any("sddmm_tiled_finish_kernel" in k for k in names) == together and any("backward_finish_kernel" in k for k in names) != together, names
+        assert sum("sddmm_tiled" in k for k in names) == 1 and sum("backward_fused_kernel" in k for k in names) == 1, names
+        L.lib.mlp_destroy(mlp)
+
+
+CASES = [the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
