@@ -35,6 +35,12 @@ enum { NERVA_TABLE_WAVES = 0, NERVA_TABLE_HUGE_ROWS = 1, NERVA_TABLE_SHORT_ROWS 
        NERVA_TABLE_STAGED_ENDS = 5 };
 int sparse_linear_partition(const nerva_layer *layer, int32_t side, int32_t table, const int32_t **table_out, int64_t *ints_out);
 
+/* Inspection aid: of the ways that the library's rules choose between, those that calls on `batch` columns (rows of their operands less than 4 GiB apart) take; *routes_out receives an OR of
+ * NERVA_ROUTE_FORWARD_STRIPS: sparse_linear_forward and mlp_forward run this layer's product in strips;
+ * NERVA_ROUTE_BACKWARD_HOT_ROWS: sparse_linear_backward, asked for both gradients, keeps the longest rows of dZ in LDS. */
+enum { NERVA_ROUTE_FORWARD_STRIPS = 1, NERVA_ROUTE_BACKWARD_HOT_ROWS = 2 };
+int sparse_linear_routes(const nerva_layer *layer, int32_t batch, int32_t *routes_out);
+
 /* Measurement aid: the density from which sparse_linear_create / sparse_linear_rebind put a layer on the
  * dense route by themselves (process-wide; layers already bound keep their route).  Default 0.4; a value above
  * 1 keeps every later layer on the sparse route, 0 sends every layer of at least 64 x 64 down the dense one. */

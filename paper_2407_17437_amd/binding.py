@@ -27,6 +27,7 @@ NERVA_PARTITION_BALANCED, NERVA_PARTITION_ROW_SPLIT, NERVA_PARTITION_PREFER_STAG
 NERVA_MLP_DEFAULT, NERVA_MLP_UNFUSED, NERVA_MLP_NESTEROV, NERVA_MLP_SEPARATE_HEAD = 0, 1, 2, 4
 NERVA_WAVES_PER_BLOCK = 16
 (NERVA_TABLE_WAVES, NERVA_TABLE_HUGE_ROWS, NERVA_TABLE_SHORT_ROWS, NERVA_TABLE_LONG_WAVES, NERVA_TABLE_STAGED_ROWS, NERVA_TABLE_STAGED_ENDS) = range(6)
+NERVA_ROUTE_FORWARD_STRIPS, NERVA_ROUTE_BACKWARD_HOT_ROWS = 1, 2
 NERVA_STATIC_WORKSPACE_BYTES = 32 << 20
 NERVA_HUGE_FLAG = 0x40000000
 
@@ -36,7 +37,7 @@ EXPORTS = [
     "sparse_linear_forward", "sparse_linear_backward", "sgd_update_values", "sgd_update_values_nesterov",
     "softmax_cross_entropy", "mlp_create", "mlp_destroy", "mlp_rebind_velocity", "mlp_workspace_bytes",
     "mlp_workspace_layout", "mlp_train_step", "mlp_train_step_static", "mlp_forward", "nerva_copy_f32",
-    "mlp_profile_enable", "mlp_profile_read", "mlp_profile_slot_name", "sparse_linear_partition",
+    "mlp_profile_enable", "mlp_profile_read", "mlp_profile_slot_name", "sparse_linear_partition", "sparse_linear_routes",
 ]
 
 
@@ -83,6 +84,7 @@ def _load() -> ctypes.CDLL:
         "mlp_forward": (ctypes.c_int, [vp, vp, i32, i32, vp, sz, vp]),
         "nerva_copy_f32": (ctypes.c_int, [vp, vp, i64, vp]),
         "sparse_linear_partition": (ctypes.c_int, [vp, i32, i32, vp, vp]),
+        "sparse_linear_routes": (ctypes.c_int, [vp, i32, vp]),
         "mlp_profile_enable": (ctypes.c_int, [vp, i32]),
         "mlp_profile_read": (ctypes.c_int, [vp, i32, vp, vp, vp]),
         "mlp_profile_slot_name": (ctypes.c_char_p, [vp, i32]),
@@ -242,6 +244,13 @@ def sparse_linear_partition(layer: int, side: int, table: int):
     p, n = ctypes.c_void_p(), ctypes.c_int64()
     _check(lib.sparse_linear_partition(layer, side, table, ctypes.addressof(p), ctypes.addressof(n)))
     return p.value, n.value
+
+
+def sparse_linear_routes(layer: int, batch: int) -> int:
+    """An OR of NERVA_ROUTE_*: the ways that calls on `batch` columns take."""
+    out = ctypes.c_int32()
+    _check(lib.sparse_linear_routes(layer, batch, ctypes.addressof(out)))
+    return out.value
 
 
 def sparse_linear_forward(layer: int, X, Y, batch: int, stream=None) -> None:

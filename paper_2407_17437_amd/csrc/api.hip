@@ -1220,6 +1220,20 @@ int sparse_linear_partition(const nerva_layer *layer, int32_t side, int32_t tabl
     return NERVA_OK;
 }
 
+// Y = act(W X + b)
+static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldin, float *out, int64_t ldout, int32_t batch)
+{
+    SpmmArgs a{};
+    a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = tickets_of(ly, 0); a.scratch_ld = ly->scratch_ld;
+    a.strips = ly->strips.segs ? &ly->strips : nullptr; a.strip_stream = reinterpret_cast<float4 *>(ly->strip_stream);
+    a.indptr = ly->indptr; a.indices = ly->indices; a.values = ly->values; a.bias = ly->bias;
+    a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
+    a.rows = ly->rows; a.x_rows = ly->cols; a.batch = batch; a.relu = ly->activation == NERVA_ACT_RELU;
+    a.full_scratch = ly->full ? ly->full_scratch : nullptr; a.full_scratch_ld = ly->full_scratch_ld;
+    a.split = split_of(ly);
+    return a;
+}
+
 int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx, float *Y, int32_t ldy,
                           int32_t batch, void *stream)
 {
@@ -1234,16 +1248,66 @@ int sparse_linear_forward(const nerva_layer *layer, const float *X, int32_t ldx,
         HIP_TRY(dense_forward(layer, X, ldx, Y, ldy, batch, as_stream(stream)));
         return NERVA_OK;
     }
-    SpmmArgs a{};
-    a.blocks = layer->plan; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 0); a.scratch_ld = layer->scratch_ld;
-    a.strips = layer->strips.segs ? &layer->strips : nullptr; a.strip_stream = reinterpret_cast<float4 *>(layer->strip_stream);
-    a.indptr = layer->indptr; a.indices = layer->indices; a.values = layer->values; a.bias = layer->bias;
-    a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
-    a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.relu = layer->activation == NERVA_ACT_RELU;
-    a.full_scratch = layer->full ? layer->full_scratch : nullptr; a.full_scratch_ld = layer->full_scratch_ld;
-    a.split = split_of(layer);
-    HIP_TRY(launch_spmm(a, as_stream(stream)));
+    HIP_TRY(launch_spmm(forward_args(layer, X, ldx, Y, ldy, batch), as_stream(stream)));
     return NERVA_OK;
+}
+
+// A call of sparse_linear_backward as its launches see it.
+struct BackwardCall {
+    const nerva_layer *layer;
+    const float *X, *Y, *dY;
+    int32_t ldx, ldy, lddy;
+    float *dX;
+    int32_t lddx;
+    float *dvalues, *dbias;
+    int32_t batch;
+    bool form_dz, mask;   // dY is dZ, which a launch of this call has formed; dY still is the gradient of a ReLU's output
+};
+static SpmmArgs transposed_args(const BackwardCall &c)
+{
+    const nerva_layer *layer = c.layer;
+    SpmmArgs a{};
+    a.blocks = layer->plan_t; a.hot = layer->hot.entry ? &layer->hot : nullptr; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 1); a.scratch_ld = layer->scratch_ld;
+    a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
+    a.X = c.dY; a.ldx = c.lddy;
+    if (c.mask) { a.XM = c.Y; a.ldxm = c.ldy; }
+    a.Y = c.dX; a.ldy = c.lddx; a.rows = layer->cols; a.x_rows = layer->rows; a.batch = c.batch;
+    return a;
+}
+static SddmmArgs gradient_args(const BackwardCall &c)
+{
+    const nerva_layer *layer = c.layer;
+    SddmmArgs a{};
+    a.blocks = layer->plan;
+    a.indptr = layer->indptr; a.indices = layer->indices; a.perm = layer->perm;
+    a.dZ = c.dY; a.lddz = c.lddy;
+    if (c.mask) { a.ZM = c.Y; a.ldzm = c.ldy; }
+    a.X = c.X; a.ldx = c.ldx; a.g = c.dvalues; a.db = c.dbias;
+    a.rows = layer->rows; a.x_rows = layer->cols; a.batch = c.batch; a.nnz = layer->nnz;
+    a.partial = layer->partial; a.partial_stride = layer->partial_stride;
+    a.partial_db_at = layer->partial_db_at; a.partial_tiles = layer->partial_tiles;
+    a.skip_products = c.dvalues ? 0 : 1;  // only the bias gradient is wanted
+    if (!c.form_dz) { a.values = layer->values; a.values_t = layer->values_t; }   // (where the mirror values are not up to date yet)
+    if (layer->cur.has_table) { a.table = reinterpret_cast<const uint2 *>(layer->cur.table); a.table_words = table_words(layer); }
+    a.split = split_of(layer);
+    a.hot_values = hot_values_of(layer);
+    return a;
+}
+// (a small layer takes both gradients, and the mask, in one launch)
+static bool backward_in_one(const BackwardCall &c)
+{
+    return c.mask && c.dX && c.dvalues && !use_dense(c.layer, c.batch) && backward_fused_ok(transposed_args(c), gradient_args(c), true);
+}
+// dZ of a ReLU layer: formed once where a transposed product would gather its rows from two operands, unless the
+// matrix is so sparse that the pass over dY and Y costs more than the gathers it saves
+static bool backward_forms_dz(const BackwardCall &c)
+{
+    return c.mask && c.dX && c.layer->dz && c.batch > 4 && c.layer->nnz >= 4 * static_cast<int64_t>(c.layer->rows);
+}
+static void take_formed_dz(BackwardCall &c)
+{
+    c.form_dz = true; c.mask = false;
+    c.dY = c.layer->dz; c.lddy = static_cast<int32_t>(c.layer->dz_ld);
 }
 
 int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, const float *Y, int32_t ldy,
@@ -1261,62 +1325,47 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
     if (rc == NERVA_OK && batch > layer->max_batch) rc = fail(NERVA_ERR_SHAPE, "batch %d exceeds the layer's max_batch %d", batch, layer->max_batch);
     if (rc != NERVA_OK) return rc;
     hipStream_t s = as_stream(stream);
-    bool form_dz = false, mask = relu;   // mask: dY still is the gradient of the output
-    auto make_t = [&] {
-        SpmmArgs a{};
-        a.blocks = layer->plan_t; a.hot = layer->hot.entry ? &layer->hot : nullptr; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 1); a.scratch_ld = layer->scratch_ld;
-        a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
-        a.X = dY; a.ldx = lddy;
-        if (mask) { a.XM = Y; a.ldxm = ldy; }
-        a.Y = dX; a.ldy = lddx; a.rows = layer->cols; a.x_rows = layer->rows; a.batch = batch;
-        return a;
-    };
-    auto make_g = [&] {
-        SddmmArgs a{};
-        a.blocks = layer->plan;
-        a.indptr = layer->indptr; a.indices = layer->indices; a.perm = layer->perm;
-        a.dZ = dY; a.lddz = lddy;
-        if (mask) { a.ZM = Y; a.ldzm = ldy; }
-        a.X = X; a.ldx = ldx; a.g = dvalues; a.db = dbias;
-        a.rows = layer->rows; a.x_rows = layer->cols; a.batch = batch; a.nnz = layer->nnz;
-        a.partial = layer->partial; a.partial_stride = layer->partial_stride;
-        a.partial_db_at = layer->partial_db_at; a.partial_tiles = layer->partial_tiles;
-        a.skip_products = dvalues ? 0 : 1;  // only the bias gradient is wanted
-        if (!form_dz) { a.values = layer->values; a.values_t = layer->values_t; }   // (where the mirror values are not up to date yet)
-        if (layer->cur.has_table) { a.table = reinterpret_cast<const uint2 *>(layer->cur.table); a.table_words = table_words(layer); }
-        a.split = split_of(layer);
-        a.hot_values = hot_values_of(layer);
-        return a;
-    };
-    // (a small layer takes both gradients, and the mask, in one launch)
-    const bool in_one = relu && dX && dvalues && !use_dense(layer, batch) && backward_fused_ok(make_t(), make_g(), true);
-    // dZ of a ReLU layer: formed once where a transposed product would gather its rows from two operands, unless the
-    // matrix is so sparse that the pass over dY and Y costs more than the gathers it saves
-    form_dz = !in_one && dX && relu && layer->dz && batch > 4 && layer->nnz >= 4 * static_cast<int64_t>(layer->rows);
-    if (form_dz) {
+    BackwardCall c{layer, X, Y, dY, ldx, ldy, lddy, dX, lddx, dvalues, dbias, batch, false, relu};
+    const bool in_one = backward_in_one(c);
+    if (!in_one && backward_forms_dz(c)) {
         HIP_TRY(launch_backward_prep(layer->values_t, layer->values, layer->perm, layer->nnz, dY, lddy, Y, ldy, layer->dz, layer->dz_ld,
                                      layer->rows, batch, s));
         layer->mirror_stale = false;
-        dY = layer->dz;
-        lddy = static_cast<int32_t>(layer->dz_ld);
+        take_formed_dz(c);
     }
-    mask = relu && !form_dz;
-    if (dX && use_dense(layer, batch) && !mask) {
+    if (dX && use_dense(layer, batch) && !c.mask) {
         HIP_TRY(refresh_dense_copies(layer, s));
-        HIP_TRY(dense_transposed(layer, dY, lddy, dX, lddx, nullptr, 0, batch, s));
-    } else if (dX && dvalues && (in_one || (!mask && backward_fused_ok(make_t(), make_g(), true)))) {
-        if (!form_dz && !backward_fused_refreshes(make_t(), make_g())) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
+        HIP_TRY(dense_transposed(layer, c.dY, c.lddy, dX, lddx, nullptr, 0, batch, s));
+    } else if (dX && dvalues && (in_one || (!c.mask && backward_fused_ok(transposed_args(c), gradient_args(c), true)))) {
+        if (!c.form_dz && !backward_fused_refreshes(transposed_args(c), gradient_args(c))) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
         layer->mirror_stale = false;
-        HIP_TRY(launch_backward_fused(make_t(), make_g(), true, s));
+        HIP_TRY(launch_backward_fused(transposed_args(c), gradient_args(c), true, s));
         return NERVA_OK;
     } else if (dX) {
-        if (!form_dz) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
+        if (!c.form_dz) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
         layer->mirror_stale = false;
-        HIP_TRY(launch_spmm(make_t(), s));
+        HIP_TRY(launch_spmm(transposed_args(c), s));
     }
     if (dvalues || dbias) {
-        HIP_TRY(launch_sddmm(make_g(), s));
+        HIP_TRY(launch_sddmm(gradient_args(c), s));
     }
+    return NERVA_OK;
+}
+
+int sparse_linear_routes(const nerva_layer *layer, int32_t batch, int32_t *routes_out)
+{
+    if (!layer || !routes_out) return fail(NERVA_ERR_ARGUMENT, "null argument");
+    int rc = check_batch(batch, batch, "ld");
+    if (rc == NERVA_OK && batch > layer->max_batch) rc = fail(NERVA_ERR_SHAPE, "batch %d exceeds the layer's max_batch %d", batch, layer->max_batch);
+    if (rc != NERVA_OK) return rc;
+    *routes_out = 0;
+    if (use_dense(layer, batch)) return NERVA_OK;
+    float *any = layer->values;   // (nothing is launched)
+    if (spmm_takes_strip(forward_args(layer, any, batch, any, batch, batch))) *routes_out |= NERVA_ROUTE_FORWARD_STRIPS;
+    BackwardCall c{layer, any, any, any, batch, batch, batch, any, batch, any, any, batch, false, layer->activation == NERVA_ACT_RELU};
+    if (backward_in_one(c)) return NERVA_OK;
+    if (backward_forms_dz(c)) take_formed_dz(c);
+    if (!c.mask && backward_fused_ok(transposed_args(c), gradient_args(c), true) && backward_hot_ok(transposed_args(c), gradient_args(c))) *routes_out |= NERVA_ROUTE_BACKWARD_HOT_ROWS;
     return NERVA_OK;
 }
 
@@ -1494,20 +1543,6 @@ static int check_step_args(const nerva_mlp *mlp, const float *X, int32_t ldx, in
     if (workspace_bytes < static_cast<size_t>(L.bytes))
         return fail(NERVA_ERR_WORKSPACE, "workspace has %zu bytes, %lld needed", workspace_bytes, (long long)L.bytes);
     return NERVA_OK;
-}
-
-// Y = act(W X + b) of one layer of a step
-static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldin, float *out, int64_t ldout, int32_t batch)
-{
-    SpmmArgs a{};
-    a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = tickets_of(ly, 0); a.scratch_ld = ly->scratch_ld;
-    a.strips = ly->strips.segs ? &ly->strips : nullptr; a.strip_stream = reinterpret_cast<float4 *>(ly->strip_stream);
-    a.indptr = ly->indptr; a.indices = ly->indices; a.values = ly->values; a.bias = ly->bias;
-    a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
-    a.rows = ly->rows; a.x_rows = ly->cols; a.batch = batch; a.relu = ly->activation == NERVA_ACT_RELU;
-    a.full_scratch = ly->full ? ly->full_scratch : nullptr; a.full_scratch_ld = ly->full_scratch_ld;
-    a.split = split_of(ly);
-    return a;
 }
 
 static int forward_chain(nerva_mlp *mlp, const float *X, int32_t ldx, int32_t batch, char *ws, const Layout &L,

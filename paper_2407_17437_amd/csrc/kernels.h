@@ -334,6 +334,8 @@ struct BackwardArgs {
 bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone);
 // whether such a call also brings the mirror values (g.values_t) up to date with g.values, so that the caller need not
 bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g);
+// whether it takes the hot rows of dZ out of LDS
+bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g);
 // The second pass over the partial products, where it is left to a launch that follows (later, which launch_sddmm or launch_backward_finish take).
 struct BackwardFinish {
     BackwardArgs a;

@@ -3820,7 +3820,6 @@ bool chain_pays(const SpmmArgs &t, const SddmmArgs &g0)
 }
 
 // (reading values[] through the position map costs a scattered read per entry and tile, a launch of its own 3.5 us)
-bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g);
 bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g)
 {
     if (backward_hot_ok(t, g)) return true;

@@ -17,11 +17,13 @@ def nb():
     return binding
 
 
-def check_layer(nb, oracle, lay, batch, ld=None, max_batch=None, seed=1, backward=True):
+def check_layer(nb, oracle, lay, batch, ld=None, max_batch=None, seed=1, backward=True, routes=None):
+    """routes: what sparse_linear_routes has to say of the calls, where it matters."""
     import torch
     rng = np.random.default_rng(seed)
     X = rng.standard_normal((lay.cols, batch)).astype(np.float32); dY = rng.standard_normal((lay.rows, batch)).astype(np.float32)
     L = nb.SparseLinear(lay, max_batch=max_batch or batch)
+    assert routes is None or nb.sparse_linear_routes(L.handle, batch) == routes
     Xd, dYd = nb.to_dense(X, ld=ld), nb.to_dense(dY, ld=ld)
     Yd, dXd = nb.dense(lay.rows, batch, ld=ld), nb.dense(lay.cols, batch, ld=ld)
     g, db = torch.full((lay.nnz,), float("nan"), device="cuda"), torch.full((lay.rows,), float("nan"), device="cuda")
@@ -596,15 +598,42 @@ def prefer_strips(nb):
     (130, 9001, lambda i: 1200 - i, 195, 199), (4500, 700, lambda i: 12, 1023, None), (900, 1500, lambda i: 30, 1026, 1027),   # long segments; batches beyond 1024
 ])
 def test_product_in_strips(nb, oracle, prefer_strips, rows, cols, lens, batch, ld):
-    check_layer(nb, oracle, strips_case(rows, cols, lens, rows + batch), batch, ld=ld, backward=False)
+    check_layer(nb, oracle, strips_case(rows, cols, lens, rows + batch), batch, ld=ld, backward=False, routes=nb.NERVA_ROUTE_FORWARD_STRIPS)
 
 
 def test_product_in_strips_where_the_rule_takes_it(nb, oracle):
-    """The layer sizes at which strips are the library's own choice, bound for a wider batch than it is called with; then another pattern, and the weights of that changed."""
-    rows, cols, batch = 6001, 2999, 811
+    """The layer sizes at which strips are the library's own choice, bound for a wider batch than it is called with: one handle through weights that change in place, a pattern of more entries, whose
+    stream is longer, one of fewer, and one of so few that the product goes another way; and narrower batches between."""
+    import torch
+    rows, cols, ld = 6001, 2999, 813
+    X = np.random.default_rng(2).standard_normal((cols, 811)).astype(np.float32)
+    Xd = nb.to_dense(X, ld=ld)
     lay = layer_case(rows, cols, 0.014, seed=3, relu=True)
-    check_layer(nb, oracle, lay, batch, ld=813, max_batch=1024, backward=False)
-    check_layer(nb, oracle, lay, 64, max_batch=1024, backward=False)
+    L = nb.SparseLinear(lay, max_batch=1024)
+
+    def check(indptr, indices, what, strips=True):
+        values = L.values.cpu().numpy()
+        for batch in (811, 64):
+            assert nb.sparse_linear_routes(L.handle, batch) & nb.NERVA_ROUTE_FORWARD_STRIPS == (strips and batch == 811), what
+            Yd = nb.dense(rows, batch, ld=ld)
+            Yd.fill_(float("nan"))
+            nb.sparse_linear_forward(L.handle, Xd, Yd, batch)
+            torch.cuda.synchronize()
+            Y, S = oracle.spmm(rows, cols, indptr, indices, values, lay.bias, np.ascontiguousarray(X[:, :batch]), True)
+            close(Yd[:, :batch].cpu().numpy(), Y, S, what=f"{what}, batch {batch}")
+
+    check(lay.indptr, lay.indices, "as created")
+    L.values.mul_(-0.5)
+    check(lay.indptr, lay.indices, "weights changed in place")
+    for density in (0.022, 0.012, 0.002):
+        new = layer_case(rows, cols, density, seed=int(1000 * density))
+        L.rebind(new.indptr, new.indices, new.values)
+        check(new.indptr, new.indices, f"rebound at {density}", strips=density > 0.002)
+    L.values.add_(0.25)
+    check(new.indptr, new.indices, "weights of the last pattern changed", strips=False)
+    L.rebind(lay.indptr, lay.indices, lay.values)
+    check(lay.indptr, lay.indices, "rebound as created")
+    L.close()
 
 
 def test_product_in_strips_keeps_a_non_finite_operand_row_to_the_rows_that_read_it(nb, oracle, prefer_strips):
@@ -615,6 +644,7 @@ def test_product_in_strips_keeps_a_non_finite_operand_row_to_the_rows_that_read_
     X = np.random.default_rng(5).standard_normal((cols, batch)).astype(np.float32)
     X[list(bad)] = np.inf
     L = nb.SparseLinear(lay, max_batch=batch)
+    assert nb.sparse_linear_routes(L.handle, batch) & nb.NERVA_ROUTE_FORWARD_STRIPS
     Yd = nb.dense(rows, batch)
     nb.sparse_linear_forward(L.handle, nb.to_dense(X), Yd, batch)
     torch.cuda.synchronize()
@@ -647,6 +677,7 @@ def test_training_step_in_strips_on_new_patterns(nb, oracle, prefer_strips):
                     L.velocity = torch.zeros_like(L.values)
                     nb.sparse_linear_rebind(L.handle, L.values.numel(), L.indptr, L.indices, L.values)
                     nb.mlp_rebind_velocity(m.handle, l, L.velocity)
+        assert all(nb.sparse_linear_routes(m.layers[l].handle, batch) & nb.NERVA_ROUTE_FORWARD_STRIPS for m in mlps for l in (0, 1))
         for _ in range(3):
             for m in mlps:
                 m.train_step(X, labels, batch, 0.01, 0.9)
@@ -699,7 +730,7 @@ def hot_rows_layer(rows, cols, n_long, long_share, short, seed, relu=False):
 ])
 def test_both_gradients_with_hot_rows_in_lds(nb, oracle, rows, cols, n_long, batch, ld, relu):
     lay, _ = hot_rows_layer(rows, cols, n_long, 0.28 if rows < 6000 else 0.25, 20, rows + batch, relu)
-    check_layer(nb, oracle, lay, batch, ld=ld)
+    check_layer(nb, oracle, lay, batch, ld=ld, routes=nb.NERVA_ROUTE_BACKWARD_HOT_ROWS)
 
 
 def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
@@ -713,6 +744,7 @@ def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
     bad = [long_rows[7], short_rows[-3]]
     dY[bad] = np.inf
     L = nb.SparseLinear(lay, max_batch=batch)
+    assert nb.sparse_linear_routes(L.handle, batch) == nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
     dXd, g, db = nb.dense(cols, batch), torch.empty(lay.nnz, device="cuda"), torch.empty(rows, device="cuda")
     nb.sparse_linear_backward(L.handle, nb.to_dense(X), None, nb.to_dense(dY), dXd, g, db, batch)
     torch.cuda.synchronize()
@@ -733,15 +765,17 @@ def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
 def test_training_step_with_hot_rows_in_lds(nb, oracle, batch):
     """The layer's update behind the same pass: every stage against the oracle, over steps whose weights each find changed."""
     import torch
-    from test_gpu_mlp_step import snapshot, stage_parity
+    from test_gpu_mlp_step import _launch_names, snapshot, stage_parity
     sizes = (60, 2600, 1100, 10)
     mlp = wl.make_mlp(sizes, layer_nnz=(5200, 2600, 2000), pattern_seed=1, value_seed=2)
     mlp.layers[1] = hot_rows_layer(1100, 2600, 400, 0.28, 20, 5, relu=True)[0]
     Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 2, seed=3)
     M = nb.MLP(mlp, batch)
+    assert nb.sparse_linear_routes(M.layers[1].handle, batch) == nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
     for t in range(2):
         before = snapshot(M)
         M.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
         torch.cuda.synchronize()
         stage_parity(nb, torch, oracle, M, mlp, before, Xs[t], Ts[t], batch, 0.05, 0.9, False)
+    assert "backward_fused[1]" in _launch_names(nb, torch, M, Xs[0], Ts[0], batch)   # (whose kernels the route says)
     M.close()
