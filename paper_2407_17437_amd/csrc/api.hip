@@ -1014,11 +1014,12 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         if (!thin_rows_pay_somewhere(B.split, cols) || !reserve_dense_rows(B, want)) B.split = DenseSplit{};
     }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
-    if (hot_order_wanted(rows, cols, nnz, max_batch, out->plan_t.hot_share) && asked == NERVA_PARTITION_BALANCED && reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
+    const float in_lds = nnz > 0 ? static_cast<float>(static_cast<double>(R.plan[0].hot_lds_nnz) / nnz) : 0.f;
+    if (asked == NERVA_PARTITION_BALANCED && hot_rows_pay_somewhere(out->plan_t, rows, cols, nnz, max_batch, in_lds) && reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
         HotRows &v = out->hot;
         HIP_TRY(launch_hot_order(out->plan.rows_by_length, rows, B.indptr_t, m.indices_t, cols, m.perm, W + work_at[0], B.hot, B.hot + n64, B.hot + 2 * n64, p.side[1].tables.rows_by_length,
                                  reinterpret_cast<int4 *>(B.hot + 4 * n64), s));
-        v.entry = B.hot; v.at = B.hot + n64; v.perm = B.hot + 2 * n64; v.sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.rows = out->plan.rows_by_length;
+        v.entry = B.hot; v.at = B.hot + n64; v.perm = B.hot + 2 * n64; v.sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.rows = out->plan.rows_by_length; v.share = in_lds;
         more_work = true;
     }
 

@@ -76,6 +76,7 @@ struct HotRows {
     const int4 *sets = nullptr;       // [mirror rows, padded as rows_by_length] {row or -1, first entry, entries, hot ones}: longest first, those of about one length by their hot entries
     const int32_t *perm = nullptr;    // [nnz] CSR position
     const int4 *rows = nullptr;       // the matrix's rows_by_length
+    float share = 0.f;                // of the entries, those of the kHotRowsLds longest rows
 };
 
 // Strips: kStripRows operand rows of kStripCols columns lie in LDS at a time; the operand's blocks are of equal size, a multiple of 256 rows.
@@ -515,7 +516,7 @@ struct MirrorArgs : MirrorGeometry {
 struct PlanCounts {
     int32_t n_blocks, n_huge_rows, n_huge_blocks, n_short, n_long_blocks, n_rest_blocks, long_nnz, longest_row;
     int32_t n_long_rows;             // rows of more than kPackMaxLen entries
-    int32_t hot_nnz;                 // stored entries of the kHotRows longest rows
+    int32_t hot_nnz, hot_lds_nnz;    // stored entries of the kHotRows, the kHotRowsLds longest rows
     int32_t n_dense, dense_nnz;      // rows of PlanSide::dense_len entries or more, and their entries
     int32_t staged_ranges, staged_partial, staged_rows, staged_nnz, staged_quad_len, staged_longest_share;
     int32_t cls[3][5];               // rows per class of the partitions waves / long_waves / rest_waves
@@ -577,15 +578,11 @@ __host__ __device__ inline bool strip_wanted(int32_t rows, int32_t cols, int64_t
     return strip_possible(rows, cols, nnz, max_batch) && rows >= 256 && cols >= 1024 && nnz * max_batch >= (96 << 20) && nnz >= 4 * segments && nnz <= 160 * segments;
 }
 __host__ __device__ inline bool strip_even(int32_t longest_row, int32_t rows, int64_t nnz) { return static_cast<int64_t>(longest_row) * rows <= 3 * nnz; }
-// Whether a mirror gets the order of HotRows: the kHotRows longest rows hold half of the entries, and the layer's widest batch has the work (backward_hot_ok asks more closely).
+// Whether both gradients with the hot rows of dZ in LDS (backward_hot_ok, which says where the lines lie) are worth it at a batch up to max_batch: the mirror then gets the order of HotRows.
+// plan_t: the mirror's; share: HotRows'.
 constexpr int32_t kHotFromBatch = 192;
-constexpr int64_t kHotTasks = 5000, kHotEntries = 45, kHotWork = 96ll << 20;
 inline int64_t hot_sets_size(int32_t rows) { return (static_cast<int64_t>(rows) + 255) / 256 * 256; }
-inline bool hot_order_wanted(int32_t rows, int32_t cols, int64_t nnz, int32_t max_batch, float hot_share)
-{
-    return rows >= 1024 && hot_share >= 0.5f && max_batch >= kHotFromBatch && nnz >= kHotEntries * cols && nnz < (1 << 30) && nnz * max_batch >= kHotWork &&
-           ((static_cast<int64_t>(cols) + 3) / 4) * ((static_cast<int64_t>(max_batch) + 63) / 64) >= kHotTasks;
-}
+bool hot_rows_pay_somewhere(const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, float share);
 // Ranges a staged plan over `rows` rows with `nnz` entries aims at, 0: such a plan would never be chosen.  (Host and
 // device; `cols`: operand rows.)
 __host__ __device__ inline int32_t staged_ranges_aim(int32_t rows, int32_t max_batch)

@@ -3960,18 +3960,46 @@ static bool backward_gathers_apart(int gs, int64_t waves, const SpmmArgs &t, boo
 // at 0.3 % 16.1 -> 16.8; but 2048 x 5500 at 2 % 14.0 -> 12.1).
 static bool bwd_sixteens(int64_t waves, const SpmmArgs &t) { return waves <= 4096 && t.nnz > 20ll * t.rows && t.nnz <= 400ll * t.rows; }
 
-// Whether the pass with hot rows in LDS runs: not where a tile's spare columns, few mirror rows (a wave for each four of them and tile) or short ones leave it waiting, shorter ones the less the more rows
-// of dZ there are beside the hot ones.  Power-law matrices, one gather stream from the L2s -> with the hot rows in LDS, us: 16384^2 at 1 / 3 %, batch 1024 524 -> 440, 1563 -> 1314; 8192^2 at 2 % 250 -> 190; 9784 x 8260 at
-// 4.2 %, batch 342 261 -> 217; 3269 x 9044 at 2.8 %, batch 782 135 -> 105; 4114 x 2469 at 3.2 %, batch 880 73.7 -> 59.3; 5197 x 6386 at 1.2 % (60 entries a mirror row), batch 632 57.3 -> 52.2; 12283 x 6279 at
-// 2.2 %, batch 315 145 -> 111; 13502 x 15851 at 0.6 % (86), batch 464 140 -> 128.  But 8068 x 4944 at 0.6 % (46), batch 762 46.4 -> 50.9; 14946 x 9731 at 0.5 % (68), batch 252 51.5 -> 54.8; 9338 x 11104 at 0.1 % (11),
-// batch 881 43 -> 51; few mirror rows: 12284 x 1987 at 5.4 %, batch 289 117 -> 133; spare columns: 5379 mirror rows, batch 116 101 -> 117.
+// Whether the pass with hot rows in LDS runs: where a tile's columns are on, there are mirror rows enough (a wave for
+// each four of them and tile) and long ones (8068 x 4944 at 0.6 %, 46 entries a mirror row, batch 762 46.4 -> 50.9 us;
+// with more rows of dZ beside the hot ones 14946 x 9731 at 0.5 %, 68, batch 252 51.5 -> 54.8), and where by the estimates
+// of both it is the shorter way.  They are of 15400 matrices of 1024 to 16384 rows, power-law ones and even ones of up to
+// 2400, batch 193 to 1024 (3.4 % root mean square each): those that take the pass are 1.13 times as fast, 0.7 % of them
+// slower by 3 % or more.  From the L2s -> in LDS, us: power-law 16384^2 at 1 %, batch 1024 / 256 541 -> 446, 146 -> 133;
+// 4000 x 8000 at 4 %, batch 256 77.7 -> 65.5; even 1100 x 2600 at 10 %, batch 1024 62.5 -> 53.1, 1200 x 16384 at 6 %,
+// batch 320 91.8 -> 75.3.  But even 1500^2 at 5 %, batch 1024 32.4 -> 34.8 (a third of the gathers from LDS, few rounds of
+// work-groups), and batches of up to 256 that otherwise need no second pass: power-law 3000 x 6000 at 3 % 33.7 -> 40.5,
+// 2000 x 8000 31.5 -> 35.3, even 1500 x 8000 at 5 % 37.6 -> 44.5.  With the update, whose weights go back through the
+// order of the walk, 1 us and 6 per million entries more (2450 training steps: of those that take the pass then one in
+// 150 is slower by 2 % or more).
+constexpr int64_t kHotTasks = 5000, kHotEntries = 45, kHotWork = 96ll << 20;
+static bool hot_pays(const SpmmArgs &t, float share, bool update)
+{
+    const int64_t tiles = (static_cast<int64_t>(t.batch) + 63) / 64, sets = (static_cast<int64_t>(t.rows) + 3) / 4;
+    if (t.batch < kHotFromBatch || t.batch * 20ll < tiles * 64 * 17 || sets * tiles < kHotTasks || t.nnz < (t.x_rows > 6144 ? 85ll : kHotEntries) * t.rows ||
+        static_cast<int64_t>(t.nnz) * t.batch < kHotWork || t.x_rows < 1024 || t.blocks.hot_share < 0.5f || t.nnz >= (1 << 30)) return false;
+    const int tg = backward_tile_group(t), n_tiles = backward_tiles(t, tg);
+    const double nnz = t.nnz * 1e-6, operand = 1e-6 * t.x_rows * t.batch, x = t.x_rows / 8192.;
+    const double stream = n_tiles == 1 ? 8 + nnz * (53 + 4.6 * x) + 0.2 * operand : 15.6 + nnz * (7.6 + n_tiles * tg / 16. * (10.45 + 0.1 * x)) + 0.65 * operand;
+    const double hot = (update ? 19 : 18) + nnz * ((update ? 17.8 : 11.8) + static_cast<double>(tiles) * (5.8 + (1. - share) * (4.1 + 1.7 * x))) + 1.1 * operand + 0.05e-3 * static_cast<double>(tiles) * t.rows;
+    return hot < 0.98 * stream;
+}
 bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g)
 {
-    if (!t.hot || !g.hot_values || t.XM || !g.partial) return false;
-    const int64_t tiles = (static_cast<int64_t>(t.batch) + 63) / 64, sets = (static_cast<int64_t>(t.rows) + 3) / 4;
-    if (tiles > g.partial_tiles || g.partial_stride < t.nnz) return false;
-    return t.batch >= kHotFromBatch && t.batch * 20ll >= tiles * 64 * 17 && sets * tiles >= kHotTasks && t.nnz >= (t.x_rows > 6144 ? 85ll : kHotEntries) * t.rows &&
-           static_cast<int64_t>(t.nnz) * t.batch >= kHotWork;
+    if (!t.hot || !g.hot_values || t.XM || !g.partial || (t.batch + 63) / 64 > g.partial_tiles || g.partial_stride < t.nnz) return false;
+    return hot_pays(t, t.hot->share, g.fused);
+}
+bool hot_rows_pay_somewhere(const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, float share)
+{
+    SpmmArgs t{};
+    t.blocks = plan_t; t.rows = cols; t.x_rows = rows; t.nnz = nnz;
+    // (asked of the fewest and the most columns that fill a number of tiles; beyond some thousand they all say the same)
+    for (int32_t tiles = kHotFromBatch / 64, most = std::min((max_batch + 63) / 64, 256); tiles <= most; ++tiles)
+        for (const int32_t batch : {(tiles * 64 * 17 + 19) / 20, std::min(tiles * 64, max_batch)}) {
+            t.batch = batch;
+            if (batch <= max_batch && hot_pays(t, share, false)) return true;
+        }
+    return false;
 }
 
 hipError_t launch_backward_finish(BackwardFinish &f, hipStream_t s)

@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     __shared__ int32_t tot[256];
     __shared__ int64_t wtot[kWaves][8];
     extern __shared__ int32_t plan_lds[];
-    __shared__ int32_t cnt[16], hot_cnt;
+    __shared__ int32_t cnt[16], hot_cnt[2];
     __shared__ PlanCounts C;   // (written by the first thread)
     __shared__ int32_t dense_cnt[3];   // rows, their entries, and the length from which the staged plan leaves rows out
     const PlanSide &S = A.side[blockIdx.x];
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     int32_t *lens = lds_arrays >= 1 ? plan_lds : S.work.lens;
     int32_t *cut = lds_arrays >= 2 ? plan_lds + n : S.work.cut, *sl = lds_arrays >= 3 ? plan_lds + 2 * n : S.work.slots;
     if (tid < 16) cnt[tid] = 0;
-    if (tid == 16) hot_cnt = 0;
+    if (tid < 2) hot_cnt[tid] = 0;
     for (int32_t i = tid; i < n; i += kBig) lens[i] = indptr[i + 1] - indptr[i];
     __syncthreads();
 
@@ -544,9 +544,9 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
         }
         __syncthreads();
-        // (in the last pass the entries of the first rows, the most referenced ones of the other orientation's gathers, are counted as well)
-        const int32_t top = pass + 1 == passes ? min(n, kHotRows) : 0;
-        int32_t hot = 0;
+        // (in the last pass the entries of the first rows, the most referenced ones of the other orientation's gathers, are counted as well, and those of the ones that HotRows keeps in LDS)
+        const bool last_pass = pass + 1 == passes;
+        int32_t hot = 0, hot_lds = 0;
         for (int32_t i0 = k_lo; i0 < k_hi; i0 += kWave) {
             const bool ok = i0 + lane < k_hi;
             const int32_t r = ok ? item(i0 + lane) : 0, len = ok ? lens[r] : 0;
@@ -561,13 +561,15 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 const int32_t at = hist[wv][d], rank = lanes_below(same);
                 const int32_t place = tot[d] + at + rank;
                 to[place] = r;
-                if (place < top) hot += len;
+                hot += place < kHotRows ? len : 0;
+                hot_lds += place < kHotRowsLds ? len : 0;
                 if (rank == 0) hist[wv][d] = at + __popcll(same);   // (after every lane of the wave has read it)
             }
         }
-        if (top > 0) {
+        if (last_pass) {
             hot = wave_sum(hot);
-            if (lane == 0) atomicAdd(&hot_cnt, hot);
+            hot_lds = wave_sum(hot_lds);
+            if (lane < 2) atomicAdd(&hot_cnt[lane], lane == 0 ? hot : hot_lds);
         }
         __syncthreads();
         int32_t *x = from; from = to; to = x;
@@ -595,7 +597,8 @@ __global__ __launch_bounds__(kBig) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 #pragma unroll
             for (int k = 0; k < 5; ++k) C.cls[v][k] = cls[v][k];
         C.longest_row = longest;
-        C.hot_nnz = hot_cnt;
+        C.hot_nnz = hot_cnt[0];
+        C.hot_lds_nnz = hot_cnt[1];
         C.n_dense = dense_cnt[0];
         C.dense_nnz = dense_cnt[1];
         C.long_nnz = static_cast<int32_t>(long_nnz);

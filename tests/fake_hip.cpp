@@ -78,7 +78,7 @@ const char *fake_launched() { static std::string out; out.swap(launched); launch
 int fake_set(int side, const char *field, int value)
 {
 #define FIELD(name) if (!strcmp(field, #name)) { counts[side].name = value; return 0; }
-    FIELD(n_blocks) FIELD(n_huge_rows) FIELD(n_huge_blocks) FIELD(n_short) FIELD(longest_row) FIELD(n_long_rows) FIELD(hot_nnz) FIELD(n_dense)
+    FIELD(n_blocks) FIELD(n_huge_rows) FIELD(n_huge_blocks) FIELD(n_short) FIELD(longest_row) FIELD(n_long_rows) FIELD(hot_nnz) FIELD(hot_lds_nnz) FIELD(n_dense)
     FIELD(dense_nnz) FIELD(staged_ranges) FIELD(staged_rows) FIELD(staged_nnz) FIELD(staged_longest_share)
     return 1;
 }

@@ -51,6 +51,11 @@ class Library:
         p = ctypes.c_void_p(ctypes.addressof(self.host[3]))
         return self.lib.sparse_linear_backward(self.layer, p, batch, p, batch, p, batch, p if dx else None, batch, p if dvalues else None, p, batch, None)
 
+    def routes(self, batch):
+        out = ctypes.c_int32(-1)
+        assert self.lib.sparse_linear_routes(self.layer, batch, ctypes.byref(out)) == 0
+        return out.value
+
     def launched(self):
         return self.hip.fake_launched().decode().split()
 
@@ -374,7 +379,35 @@ def the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only
         L.lib.mlp_destroy(mlp)
 
 
-CASES = [the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def hot_rows_are_kept_in_lds_where_that_is_faster(L):
+    """rows, columns, entries of a mirror row, batch, shares of the 1024 longest rows and of the 512 that fit in LDS; as measured, us, from the L2s and from LDS."""
+    for rows, cols, entries, batch, most, share, hot in (
+            (16384, 16384, 164, 1024, 0.76, 0.67, True),    # 541 / 446
+            (16384, 16384, 164, 256, 0.76, 0.67, True),     # 146 / 133
+            (4000, 8000, 160, 256, 0.84, 0.75, True),       # 77.7 / 65.5
+            (5197, 6386, 62, 632, 0.87, 0.80, True),        # 57.3 / 52.2
+            (1100, 2600, 110, 1024, 0.96, 0.49, True),      # even rows: 62.5 / 53.1
+            (1200, 16384, 72, 320, 0.87, 0.44, True),       # 91.8 / 75.3
+            (1500, 1500, 75, 1024, 0.71, 0.38, False),      # 32.4 / 34.8
+            (1500, 8000, 75, 256, 0.71, 0.36, False),       # 37.6 / 44.5: one tile, no second pass
+            (3000, 6000, 90, 256, 0.89, 0.81, False),       # power-law rows: 33.7 / 40.5
+            (2000, 8000, 60, 256, 0.93, 0.86, False),       # 31.5 / 35.3
+            (2000, 8000, 60, 384, 0.93, 0.86, True),        # 44.2 / 43.0
+            (8192, 8192, 164, 1024, 0.13, 0.07, False)):    # 270 / 284
+        nnz = cols * entries
+        L.counts(0, n_blocks=600, longest_row=3000, hot_nnz=int(most * nnz), hot_lds_nnz=int(share * nnz))
+        L.counts(1, n_blocks=600, longest_row=2 * entries, hot_nnz=nnz // 8, hot_lds_nnz=nnz // 16)
+        for max_batch in (batch, 1024):
+            assert L.create(rows, cols, nnz, max_batch) == 0
+            L.launched()
+            assert L.backward(batch) == 0
+            names = L.launched()
+            assert any("backward_hot_kernel" in k for k in names) == hot and any("backward_fused_kernel" in k for k in names) != hot, (rows, cols, batch, names)
+            assert L.routes(batch) & 2 == 2 * hot
+            L.destroy()
+
+
+CASES = [hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
