@@ -3421,48 +3421,55 @@ int spmm_split_group(const SpmmArgs &a)
 
 bool spmm_staged_ok(const SpmmArgs &a);
 // The product in strips, us, with the ranges that make it shortest: rounds of 256 work-groups (one fits a compute unit), each the steps that its LDS serves, the sets that a wave takes one after the
-// other, and the copy of the operand's strip; before them the stream.  Root mean square 7 % from 330 uniform matrices of 512 to 16384 rows, 1024 to 16384 columns, 0.1 to 10 %, batch 193 to 1024.
+// other, and the copy of the operand's strip; before them the stream.  Fitted, as the estimates of the other kernels below, to 28600 uniform matrices of 300 to 16384 rows, 1024 to 16384 columns, 0.1 to
+// 10 %, batch 193 to 1024, and to the next best number of ranges: root mean square 6.6 %, 1 % off at any number of blocks.
 struct StripPlan {
     StripGrid grid;
     double us;
 };
-static StripPlan strip_plan(const SpmmArgs &a)
+static StripPlan strip_plan(int32_t rows, int32_t x_rows, int32_t batch, int32_t blocks, double steps, double chunks)
 {
     StripPlan p{};
-    p.grid.n_tiles = (a.batch + kStripCols - 1) / kStripCols;
-    const int64_t sets = (static_cast<int64_t>(a.rows) + kStripSet - 1) / kStripSet, least = (sets + kStripWaves * kStripJ - 1) / (kStripWaves * kStripJ);
-    const double steps = a.strips->steps, per_set = steps / static_cast<double>(sets);
+    p.grid.n_tiles = (batch + kStripCols - 1) / kStripCols;
+    const int64_t sets = (static_cast<int64_t>(rows) + kStripSet - 1) / kStripSet, least = (sets + kStripWaves * kStripJ - 1) / (kStripWaves * kStripJ);
+    const double per_set = steps / static_cast<double>(sets);
     for (int64_t more = 0, first = (p.grid.n_tiles * least + 255) / 256; more < 4; ++more) {   // (of the ranges that a number of rounds holds the most)
         const int64_t r = std::max(least, 256 * (first + more) / p.grid.n_tiles);
         const double rounds = static_cast<double>((p.grid.n_tiles * r + 255) / 256), most = static_cast<double>((sets + kStripWaves * r - 1) / (kStripWaves * r));
-        const double us = rounds * (1.8 + 3.0e-3 * steps / static_cast<double>(r) + 12.7e-3 * most * per_set + 0.5e-3 * a.x_rows + 2.6 * a.strips->blocks);
+        const double us = rounds * (6.8 + 2.06e-3 * steps / static_cast<double>(r) + 20.7e-3 * most * per_set + 0.46e-3 * x_rows + 2.07 * blocks);
         if (p.grid.n_ranges == 0 || us < p.us) { p.us = us; p.grid.n_ranges = static_cast<int>(r); }
     }
-    p.us += 6.3 + 0.64e-3 * a.strips->chunks;
+    p.us += 6.6 + 0.62e-3 * chunks;
     p.grid.per = static_cast<int>((static_cast<int64_t>(p.grid.n_tiles) * p.grid.n_ranges + 7) / 8);
     return p;
 }
-// Whether it pays: against an estimate of the kernel that would run otherwise (staged, in column tiles or over the whole batch; 5, 17 and 10 % root mean square from the same matrices).
-static bool strip_pays(const SpmmArgs &a)
+static StripPlan strip_plan(const SpmmArgs &a) { return strip_plan(a.rows, a.x_rows, a.batch, a.strips->blocks, a.strips->steps, a.strips->chunks); }
+// The kernel that would run otherwise, us: staged, in column tiles (of 128, or of 64 and fewer) or over the whole batch; 3.5, 8.8, 17 (3 to 16 too short in the mean) and 10 % root mean square.  0: not known
+// well enough for a comparison.
+static double other_product_us(const SpmmArgs &a)
 {
     const double nnz = a.nnz * 1e-6, x_rows = a.x_rows * 1e-6, rows = a.rows * 1e-6, operand = 4. * x_rows * a.batch;   // (millions)
-    double other;
     if (spmm_staged_ok(a)) {
-        other = 8.7 + (a.batch + kStageCols - 1) / kStageCols * (3.2 * nnz + 13. * rows * a.blocks.staged_cblocks + 18.7 * a.blocks.staged_ranges * x_rows);
-    } else {
-        if (a.rows < kPackMinRows) return false;   // (few sets, which the estimate is too kind to: 1223 x 4592 at 10 %, batch 466 46.8 -> 56.3)
-        int tg = spmm_tile_group(a);
-        if (tg == 0 && packed_tiles_pay(a)) tg = 16;
-        if (tg > 0) other = 6.2 + nnz * ((a.batch + tg * 4 - 1) / (tg * 4)) * tg * 16. * (0.036 + 0.015 * std::min(x_rows * tg * 16. / 4.194304, 2.)) + 0.2 * operand - 0.4 * rows * a.batch;
-        else other = 4.5 + 4. * nnz * a.batch * (0.031 + 0.09 * std::min(operand / 32., 1.)) + 0.15 * operand + 0.4 * rows * a.batch;
+        const int tiles = (a.batch + kStageCols - 1) / kStageCols, ranges = a.blocks.staged_ranges;
+        const double rounds = static_cast<double>((static_cast<int64_t>(tiles) * ranges + kStageTargetGroups - 1) / kStageTargetGroups);
+        return 2.1 + tiles * (0.36 * nnz + 9.5 * rows * a.blocks.staged_cblocks) + rounds * (7.2 + 652. * nnz / ranges + 4600. * x_rows);
     }
-    return strip_plan(a).us < 0.88 * other;
+    if (a.rows < kPackMinRows) return 0.;   // (few sets, which the strips' estimate is too kind to: 1223 x 4592 at 10 %, batch 466 46.8 -> 56.3)
+    int tg = spmm_tile_group(a);
+    if (tg == 0 && packed_tiles_pay(a)) tg = 16;
+    if (tg == 0) return 6. + 4. * nnz * a.batch * (0.0228 + 0.0262 * std::max(operand - 4., 0.) / 8.) + 10.9 * nnz * ((a.batch + 255) / 256) + 0.3 * operand + 0.033 * rows * a.batch;
+    const double gathers = nnz * ((a.batch + tg * 4 - 1) / (tg * 4)) * tg * 16., tile = x_rows * tg * 16. / 4.194304;
+    if (tg == 32) return 7.4 + gathers * (0.0294 + 0.0118 * tile) + 0.36 * rows * a.batch;
+    return 6.2 + gathers * (0.036 + 0.015 * std::min(tile, 2.)) + 0.2 * operand - 0.4 * rows * a.batch;
 }
+// Where strips pay: of the matrices above that take them 0.75 % are slower by 3 % or more, the worst by 14 %; all in all they are 1.32 times as fast.  (A line that asks less of the strips, 0.98: 1.27 times, but
+// 3 % of the matrices slower.)
+static bool strip_pays(double strips, double other) { return strips < 0.94 * other; }
 bool spmm_strip_ok(const SpmmArgs &a)
 {
     if (!a.strips || !a.strip_stream || a.XM || a.batch <= kStripFromBatch) return false;
     const int64_t groups = (static_cast<int64_t>(a.rows) + kStripSet * kStripWaves * kStripJ - 1) / (kStripSet * kStripWaves * kStripJ) * ((a.batch + kStripCols - 1) / kStripCols);
-    return groups < (1 << 28) && (a.strips->preferred || strip_pays(a));
+    return groups < (1 << 28) && (a.strips->preferred || strip_pays(strip_plan(a).us, other_product_us(a)));
 }
 
 bool spmm_staged_ok(const SpmmArgs &a)

@@ -407,7 +407,35 @@ def hot_rows_are_kept_in_lds_where_that_is_faster(L):
             L.destroy()
 
 
-CASES = [hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+def strips_run_where_they_are_faster(L):
+    """rows, columns, entries, share of the steps that carry an entry; widest batch; batches, and whether they take strips.  As measured, us, by the other kernel and in strips."""
+    for rows, cols, nnz, full, max_batch, batches in (
+            (8192, 3072, 342893, 0.97, 300, ((300, False),)),                       # 20 / 25
+            (8192, 8192, 498753, 0.82, 300, ((300, False),)),
+            (8192, 3072, 342893, 0.97, 1024, ((208, False), (1024, True))),         # 59 / 41
+            (8192, 8192, 498753, 0.82, 1024, ((208, False), (1024, True))),         # 93 / 58
+            (3101, 2026, 381630, 0.99, 329, ((329, False),)),                       # 24.9 / 31.4: staged
+            (2622, 4783, 128466, 0.93, 1020, ((1020, False),)),                     # 23.8 / 29.3
+            (16384, 16384, 2684355, 0.77, 1024, ((1024, True),)),                   # 456 / 245
+            (8192, 8192, 498753, 0.3, 1024, ((1024, False),))):                     # segments of many lengths
+        blocks = (cols + 2047) // 2048
+        steps = int(nnz / 16 / full)
+        L.counts(0, n_blocks=600, longest_row=int(1.6 * nnz / rows), hot_nnz=nnz // 8, n_short=rows if nnz < 100 * rows else 0)
+        L.counts(1, n_blocks=600, longest_row=int(1.6 * nnz / cols), hot_nnz=nnz * 1024 // cols)
+        ranges = {16384: 48, 3101: 42}.get(rows, 0)
+        L.counts(0, staged_ranges=ranges, staged_rows=rows * (ranges > 0), staged_nnz=nnz * (ranges > 0))
+        L.hip.fake_set_strips(int(steps / 8 + rows / 16 * blocks / 2), steps)
+        assert L.create(rows, cols, nnz, max_batch) == 0
+        for batch, strips in batches:
+            L.launched()
+            assert L.forward(batch) == 0
+            names = L.launched()
+            assert any("spmm_strip_kernel" in k for k in names) == any("strip_stream_kernel" in k for k in names) == strips, (rows, cols, batch, names)
+            assert L.routes(batch) & 1 == strips
+        L.destroy()
+
+
+CASES = [strips_run_where_they_are_faster, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
