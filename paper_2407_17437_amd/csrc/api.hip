@@ -916,7 +916,11 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     const bool seek_dense = mode == NERVA_PARTITION_BALANCED && asked != NERVA_PARTITION_PREFER_STRIPS && cols >= kDenseRowsMinCols && max_batch >= kDenseRowsMinBatch && nnz < (1 << 30) &&
                             !takes_dense_route(l, nnz);
     const int32_t dense_len = seek_dense ? dense_row_length(cols) : INT32_MAX;
-    const bool strips = !takes_dense_route(l, nnz) && (asked == NERVA_PARTITION_PREFER_STRIPS ? strip_possible(rows, cols, nnz, max_batch) : mode == NERVA_PARTITION_BALANCED && strip_wanted(rows, cols, nnz, max_batch));
+    const bool strips = !takes_dense_route(l, nnz) &&
+                        (asked == NERVA_PARTITION_PREFER_STRIPS
+                             ? strip_possible(rows, cols, nnz, max_batch)
+                             : mode == NERVA_PARTITION_BALANCED &&
+                                   strip_wanted(rows, cols, nnz, max_batch, staged_ranges_wanted(rows, nnz, cols, max_batch, mode, staged_range_bound(rows, cols, max_batch))));
     const PlanRoom room(rows, cols, nnz, max_batch, strips, dense_len), room_t(cols, rows, nnz, max_batch);
     const size_t plan_ints = static_cast<size_t>(round_up(static_cast<int64_t>(room.ints()), 64));
     HIP_TRY(reserve(&B.plan_mem, &B.plan_ints, plan_ints + room_t.ints()));
@@ -1043,12 +1047,14 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         if (l->activation == NERVA_ACT_RELU && max_batch > 4 && nnz >= 4 * static_cast<int64_t>(rows) && dz * 4 <= kDzMaxBytes)
             (void)reserve_optional(&l->dz, &l->dz_floats, dz, false);
         const int64_t slots = out->plan.n_huge_blocks > out->plan_t.n_huge_blocks ? out->plan.n_huge_blocks : out->plan_t.n_huge_blocks;
-        if (const size_t chunks = static_cast<uint32_t>(R.strip), need = (chunks + 2) * kStripChunk * kStripSet * 2;
-            chunks > 0 && need * 4 <= kStripMaxBytes && reserve_optional(&l->strip_stream, &l->strip_floats, need)) {
+        const size_t chunks = static_cast<uint32_t>(R.strip), need = (chunks + 2) * kStripChunk * kStripSet * 2;
+        const int32_t steps = static_cast<int32_t>(R.strip >> 32);
+        if (chunks > 0 && need * 4 <= kStripMaxBytes && (p.prefer_strips || strips_pay_somewhere(out->plan, rows, cols, nnz, max_batch, steps, static_cast<double>(chunks))) &&
+            reserve_optional(&l->strip_stream, &l->strip_floats, need)) {
             Strips &v = out->strips;
             v.rows = p.side[0].tables.strip_rows; v.segs = p.side[0].tables.strip_segs; v.cuts = p.side[0].tables.strip_cuts;
             v.blocks = room.strip_blocks; v.block_rows = strip_block_rows_of(cols);
-            v.chunks = static_cast<int32_t>(chunks); v.steps = static_cast<int32_t>(R.strip >> 32);
+            v.chunks = static_cast<int32_t>(chunks); v.steps = steps;
             v.preferred = p.prefer_strips;
         }
         out->scratch_ld = round_up(max_batch, 64);

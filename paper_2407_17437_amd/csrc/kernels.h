@@ -566,16 +566,20 @@ hipError_t launch_hot_order(const int4 *rows_by_length, int32_t x_rows, const in
                             hipStream_t s);
 hipError_t launch_plan(const PlanArgs &p, int sides, hipStream_t s);   // its last part alone: the partitions of W, or of W and its mirror
 
-// Whether the product in strips can run (256 operand rows travel at a time), and whether a matrix is looked at for a plan: enough work, segments neither so short that a set's differ
-// too much nor so long that the staged product, whose gathers are wider, is as fast (spmm_strip_ok asks more closely).  Rows of different lengths have no use for it: a wave would run as long as the longest.
+// Whether the product in strips can run (256 operand rows travel at a time), and whether a matrix is looked at for a plan: some work, segments neither so short that a set's differ
+// too much nor so long that the staged product, whose gathers are wider, is as fast; and by the estimates that calls ask (spmm_strip_ok) strips may be the shorter way at a batch up to max_batch.  Before the plan is made
+// these are of the best that it can come to (strips_may_pay), and of what has come out before its stream gets room.  Rows of different lengths have no use for it: a wave would run as long as the longest.
 __host__ __device__ inline bool strip_possible(int32_t rows, int32_t cols, int64_t nnz, int32_t max_batch)
 {
     return max_batch > kStripFromBatch && cols >= 256 && strip_blocks_of(cols) <= kStripMaxBlocks && nnz > 0 && nnz < (1 << 30) && static_cast<int64_t>(rows) * strip_blocks_of(cols) <= (1 << 28);
 }
-__host__ __device__ inline bool strip_wanted(int32_t rows, int32_t cols, int64_t nnz, int32_t max_batch)
+bool strips_pay_somewhere(const RowBlocks &plan, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, double steps, double chunks);
+bool strips_may_pay(int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, int32_t staged_ranges);   // staged_ranges: that a staged plan would aim at, 0: none
+inline bool strip_wanted(int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, int32_t staged_ranges)
 {
     const int64_t segments = static_cast<int64_t>(rows) * strip_blocks_of(cols);
-    return strip_possible(rows, cols, nnz, max_batch) && rows >= 256 && cols >= 1024 && nnz * max_batch >= (96 << 20) && nnz >= 4 * segments && nnz <= 160 * segments;
+    return strip_possible(rows, cols, nnz, max_batch) && rows >= 256 && cols >= 1024 && static_cast<int64_t>(nnz) * max_batch >= (96 << 20) && nnz >= 4 * segments && nnz <= 160 * segments &&
+           strips_may_pay(rows, cols, nnz, max_batch, staged_ranges);
 }
 __host__ __device__ inline bool strip_even(int32_t longest_row, int32_t rows, int64_t nnz) { return static_cast<int64_t>(longest_row) * rows <= 3 * nnz; }
 // Whether both gradients with the hot rows of dZ in LDS (backward_hot_ok, which says where the lines lie) are worth it at a batch up to max_batch: the mirror then gets the order of HotRows.

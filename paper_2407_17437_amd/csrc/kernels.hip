@@ -3903,6 +3903,40 @@ bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
     return ((n_tiles + 7) / 8) * 8 * ((sets + kBwdWaves - 1) / kBwdWaves) + 2048 <= kMaxGridIds;
 }
 
+bool strips_pay_somewhere(const RowBlocks &plan, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, double steps, double chunks)
+{
+    SpmmArgs a{};
+    a.blocks = plan; a.rows = rows; a.x_rows = cols; a.ldx = max_batch; a.nnz = nnz;
+    // (asked at a quarter and at all of every 64 columns; beyond some thousand they all say the same)
+    for (int32_t most = std::min(max_batch, 4096), hi = most; hi > kStripFromBatch; hi = (hi - 1) / 64 * 64)
+        for (const int32_t batch : {hi, (hi - 1) / 64 * 64 + 16}) {
+            if (batch > hi) continue;
+            a.batch = batch;
+            if (strip_pays(strip_plan(rows, cols, batch, strip_blocks_of(cols), steps, chunks).us, other_product_us(a))) return true;
+        }
+    return false;
+}
+bool strips_may_pay(int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, int32_t staged_ranges)
+{
+    // at the best: every set's segments of one length, and whichever of the other kernels is the slowest
+    const double steps = nnz / static_cast<double>(kStripSet), chunks = steps / kStripChunk;
+    RowBlocks plan{};
+    static constexpr int32_t some = 0;
+    plan.n_short = nnz <= static_cast<int64_t>(kPackMaxLen) * rows ? rows : 0;
+    plan.staged_longest_row = nnz / rows;
+    for (const float hot : {0.f, 1.f}) {
+        plan.hot_share = hot;
+        plan.staged_rows = nullptr;
+        if (strips_pay_somewhere(plan, rows, cols, nnz, max_batch, steps, chunks)) return true;
+        if (staged_ranges == 0) continue;
+        plan.staged_rows = &some;   // (asked whether it is there, never read)
+        plan.staged_ranges = staged_ranges; plan.staged_cblocks = (cols + kStageRows - 1) / kStageRows;
+        plan.staged_row_count = rows; plan.staged_nnz = nnz;
+        if (strips_pay_somewhere(plan, rows, cols, nnz, max_batch, steps, chunks)) return true;
+    }
+    return false;
+}
+
 int32_t partial_tiles_wanted(const RowBlocks &plan, const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch)
 {
     SpmmArgs t{};

@@ -19,6 +19,7 @@ std::map<const void *, std::string> kernels;
 std::string launched;
 PlanCounts counts[2];
 unsigned long long strip_counts = 0;   // as BindResult::strip, of plans that have room for strips
+int strip_blocks = -1;   // that the last bind asked for
 long calls_until_failure = -1;   // of the calls that allocate, fill or wait
 int bad_pointers = 0, bad_grids = 0, dirty_tickets = 0, mixed_tickets = 0;
 std::map<const int32_t *, int> ticket_ends;   // what each ticket of a shared tile counts up to
@@ -75,6 +76,7 @@ int fake_bad_grids() { return bad_grids; }
 int fake_dirty_tickets() { return dirty_tickets; }
 int fake_mixed_tickets() { return mixed_tickets; }
 size_t fake_live_bytes() { return live_bytes; }
+int fake_strip_blocks() { return strip_blocks; }
 void fake_set_strips(int chunks, int steps) { strip_counts = static_cast<unsigned>(chunks) | static_cast<unsigned long long>(steps) << 32; }
 const char *fake_launched() { static std::string out; out.swap(launched); launched.clear(); return out.c_str(); }
 int fake_set(int side, const char *field, int value)
@@ -164,7 +166,8 @@ hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3, void **args, siz
         const PlanArgs &p = *static_cast<const PlanArgs *>(args[0]);
         memset(p.result, 0, sizeof(BindResult));
         memcpy(p.result->plan, counts, sizeof counts);
-        p.result->strip = p.side[0].strip_blocks > 0 ? strip_counts : 0;
+        strip_blocks = p.side[0].strip_blocks;
+        p.result->strip = strip_blocks > 0 ? strip_counts : 0;
     }
     return hipSuccess;
 }
