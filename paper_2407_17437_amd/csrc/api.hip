@@ -135,7 +135,7 @@ struct nerva_layer {
     // owned: tickets of the huge rows (SpmmArgs::tickets), 0 but while a product runs
     int32_t *tickets = nullptr;
     size_t ticket_ints = 0;
-    // owned: stream of a forward product in strips (SpmmArgs::strip_stream), or nullptr
+    // owned: stream of a forward product in strips (SpmmCall::strip_stream), or nullptr
     float *strip_stream = nullptr;
     size_t strip_floats = 0;
     // owned: per-tile partial products of the SDDMM and of the backward pass on one gather stream, as many tiles as
@@ -1228,9 +1228,9 @@ int sparse_linear_partition(const nerva_layer *layer, int32_t side, int32_t tabl
 }
 
 // Y = act(W X + b)
-static SpmmArgs forward_args(const nerva_layer *ly, const float *in, int64_t ldin, float *out, int64_t ldout, int32_t batch)
+static SpmmCall forward_args(const nerva_layer *ly, const float *in, int64_t ldin, float *out, int64_t ldout, int32_t batch)
 {
-    SpmmArgs a{};
+    SpmmCall a{};
     a.blocks = ly->plan; a.nnz = ly->nnz; a.scratch = ly->scratch; a.tickets = tickets_of(ly, 0); a.scratch_ld = ly->scratch_ld;
     a.strips = ly->strips.segs ? &ly->strips : nullptr; a.strip_stream = reinterpret_cast<float4 *>(ly->strip_stream);
     a.indptr = ly->indptr; a.indices = ly->indices; a.values = ly->values; a.bias = ly->bias;
@@ -1270,10 +1270,10 @@ struct BackwardCall {
     int32_t batch;
     bool form_dz, mask;   // dY is dZ, which a launch of this call has formed; dY still is the gradient of a ReLU's output
 };
-static SpmmArgs transposed_args(const BackwardCall &c)
+static SpmmCall transposed_args(const BackwardCall &c)
 {
     const nerva_layer *layer = c.layer;
-    SpmmArgs a{};
+    SpmmCall a{};
     a.blocks = layer->plan_t; a.hot = layer->hot.entry ? &layer->hot : nullptr; a.nnz = layer->nnz; a.scratch = layer->scratch; a.tickets = tickets_of(layer, 1); a.scratch_ld = layer->scratch_ld;
     a.indptr = layer->indptr_t; a.indices = layer->indices_t; a.values = layer->values_t;
     a.X = c.dY; a.ldx = c.lddy;
@@ -1281,10 +1281,10 @@ static SpmmArgs transposed_args(const BackwardCall &c)
     a.Y = c.dX; a.ldy = c.lddx; a.rows = layer->cols; a.x_rows = layer->rows; a.batch = c.batch;
     return a;
 }
-static SddmmArgs gradient_args(const BackwardCall &c)
+static SddmmCall gradient_args(const BackwardCall &c)
 {
     const nerva_layer *layer = c.layer;
-    SddmmArgs a{};
+    SddmmCall a{};
     a.blocks = layer->plan;
     a.indptr = layer->indptr; a.indices = layer->indices; a.perm = layer->perm;
     a.dZ = c.dY; a.lddz = c.lddy;
@@ -1560,7 +1560,7 @@ static int forward_chain(nerva_mlp *mlp, const float *X, int32_t ldx, int32_t ba
     // the streams of products in strips, which depend on the weights alone, in one launch at the start
     size_t ready = 0;   // layers below this one have theirs
     if (batch > kStripFromBatch) {
-        SpmmArgs strips[kStripStreams];
+        SpmmCall strips[kStripStreams];
         int n = 0;
         for (; ready < n_layers && n < kStripStreams; ++ready)
             if (!use_dense(mlp->layers[ready], batch)) {
@@ -1577,7 +1577,7 @@ static int forward_chain(nerva_mlp *mlp, const float *X, int32_t ldx, int32_t ba
     for (size_t l = 0; l < n_layers; ++l) {
         const nerva_layer *ly = mlp->layers[l];
         float *A = A_of(l);
-        SpmmArgs a = args_of(l);
+        SpmmCall a = args_of(l);
         a.strip_ready = l < ready;
         if (use_dense(ly, batch)) {
             Timed tm(mlp->prof, s, "dense_forward", static_cast<int>(l));
@@ -1666,7 +1666,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         // dZ_{l-1} = (W_l^T dZ_l) * [A_{l-1} > 0]: the ReLU derivative of the layer below is
         // applied as the transposed product is stored
         nerva_layer *ly = mlp->layers[l];
-        SpmmArgs t{};
+        SpmmCall t{};
         t.blocks = ly->plan_t; t.hot = ly->hot.entry ? &ly->hot : nullptr; t.nnz = ly->nnz; t.scratch = ly->scratch; t.tickets = tickets_of(ly, 1); t.scratch_ld = ly->scratch_ld;
         t.indptr = ly->indptr_t; t.indices = ly->indices_t; t.values = ly->values_t;
         t.X = dZ(l); t.ldx = L.ld; t.Y = dZ(l - 1); t.ldy = L.ld;
@@ -1676,7 +1676,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
     };
     auto make_S = [&](int l) {
         nerva_layer *ly = mlp->layers[l];
-        SddmmArgs g{};
+        SddmmCall g{};
         g.blocks = ly->plan;
         g.indptr = ly->indptr; g.indices = ly->indices;
         g.dZ = dZ(l); g.lddz = L.ld;
@@ -1704,7 +1704,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
     // A saturated output layer too large for the head: its forward product streams the operand, and the finish pass of
     // that product can form the loss gradient as it stores the logits, when the layer's backward pass (one streaming
     // launch as well) is there to take the mean of the per-column losses.
-    SpmmArgs last_F{};
+    SpmmCall last_F{};
     if (!head && fused && n >= 2 && mlp->head_scratch && !use_dense(last, batch)) {
         last_F = forward_args(last, A(n - 2), L.ld, A(n - 1), L.ld, batch);
         last_F.ce_labels = labels; last_F.ce_dZ = dZ(n - 1); last_F.ce_lddz = L.ld; last_F.ce_loss_cols = mlp->head_scratch;
@@ -1766,7 +1766,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         };
         BackwardFinish finish{};   // layer 1's, which S_0 does not wait for
         auto run_S_alone = [&](int l) -> int {
-            const SddmmArgs g = make_S(l);
+            const SddmmCall g = make_S(l);
             if (sddmm_sampled_ok(g)) {
                 HIP_TRY(launch_backward_finish(finish, s));
                 return defer_S(l);
@@ -1779,7 +1779,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         bool chained = false;       // S_0 has run
         for (int l = head ? n - 2 : n - 1; l >= 1; --l) {
             // dZ_l is ready: T_l (which hands dZ_{l-1} down) and S_l
-            const SpmmArgs t = make_T(l);
+            const SpmmCall t = make_T(l);
             if (use_dense(mlp->layers[l], batch)) {
                 // (no grid to share with a dense product: a small output layer joins the sampled ones where it has a table)
                 if (pending >= 0 && (rc = sddmm_sampled_possible(make_S(pending)) ? defer_S(pending) : run_S_alone(pending)) != NERVA_OK) return rc;
@@ -1787,11 +1787,11 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 pending = l;
                 continue;
             }
-            const SddmmArgs g_same = make_S(l);
+            const SddmmCall g_same = make_S(l);
             if (l == 1 && !use_dense(mlp->layers[0], batch) && chain_ok(t, g_same, make_S(0))) {
                 // the rest of the step in one launch
-                const SddmmArgs g0 = make_S(0);
-                SddmmArgs waiting{};
+                const SddmmCall g0 = make_S(0);
+                SddmmCall waiting{};
                 if (pending >= 0) waiting = make_S(pending);
                 const bool along = pending >= 0 && can_pair(g0, waiting);
                 if (pending >= 0 && !along && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
@@ -1804,7 +1804,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
             if (full_backward_ok(t, g_same)) {
                 if (pending >= 0 && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
                 pending = -1;
-                SddmmArgs g_full = g_same;
+                SddmmCall g_full = g_same;
                 if (bias_done < 0 && mlp->layers[l - 1]->bias) {
                     // dZ_{l-1} is formed a whole row per wave: the bias gradient of layer l-1 is that row's sum
                     g_full.below_bias = mlp->layers[l - 1]->bias; g_full.below_bias_velocity = mlp->bias_vel[l - 1];
@@ -1823,7 +1823,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 continue;
             }
             if (pending >= 0) {
-                const SddmmArgs g = make_S(pending);
+                const SddmmCall g = make_S(pending);
                 if (can_pair(t, g)) {
                     Timed tm(mlp->prof, s, "spmm_transposed+sddmm_update", l);
                     HIP_TRY(launch_pair(t, g, s));
@@ -1839,7 +1839,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
         }
         // the first layer has no transposed product: its S, with the one still pending if any
         if (!chained && pending >= 0) {
-            const SddmmArgs gp = make_S(pending), g0 = make_S(0);
+            const SddmmCall gp = make_S(pending), g0 = make_S(0);
             if (pending == 1 && can_pair(g0, gp)) {
                 Timed tm(mlp->prof, s, "sddmm_update+sddmm_update", 0);
                 HIP_TRY(launch_pair(g0, gp, s));  // the larger layer's work-groups start first
@@ -1867,7 +1867,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                         HIP_TRY(launch_spmm(make_T(l), s));
                 }
             }
-            SddmmArgs g = make_S(l);
+            SddmmCall g = make_S(l);
             g.chain_lanes = as_chain && l <= 1;
             {
                 Timed tm(mlp->prof, s, "sddmm", l);

@@ -844,16 +844,16 @@ hipError_t launch_dense_product(const DenseArgs &a, hipStream_t s)
 }
 
 // what the sampled kernel asks of a layer's arrays: 32-bit byte offsets
-bool sampled_operands_ok(const SddmmArgs &a)
+bool sampled_operands_ok(const SddmmCall &a)
 {
     return a.nnz > 0 && a.nnz < (1 << 30) && a.batch >= kSampledMinBatch && !a.ZM && !a.skip_products &&
            static_cast<int64_t>(a.rows) * a.lddz < (1 << 30) && static_cast<int64_t>(a.x_rows) * a.ldx < (1 << 30) &&
            (!a.dense || static_cast<int64_t>(a.rows) * a.dense_ld < (1 << 30));
 }
 
-bool sddmm_sampled_possible(const SddmmArgs &a) { return a.table && sampled_operands_ok(a); }
+bool sddmm_sampled_possible(const SddmmCall &a) { return a.table && sampled_operands_ok(a); }
 
-bool sddmm_sampled_ok(const SddmmArgs &a)
+bool sddmm_sampled_ok(const SddmmCall &a)
 {
     if (!sddmm_sampled_possible(a) || a.rows < 64 || a.x_rows < 64) return false;
     // Measured against the gathering SDDMM, uniform patterns: 4096 x 3072 at batch 100 / 1024, 15 %: 42.6 / 242 us against 43.8 /
@@ -972,7 +972,7 @@ DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch, bool t
     return room;
 }
 
-hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s)
+hipError_t launch_dense_rows(const SpmmCall &a, hipStream_t s)
 {
     const DenseRows &D = a.split->rows;
     const DenseRowsCut fp32 = dense_rows_fp32_cut(D.n, a.x_rows, a.batch);
@@ -997,7 +997,7 @@ hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-void add_sampled_rows(SampledArgs &list, const SddmmArgs &a)
+void add_sampled_rows(SampledArgs &list, const SddmmCall &a)
 {
     add_sampled(list, a);
     SampledLayer &L = list.layer[list.n - 1];
@@ -1006,7 +1006,7 @@ void add_sampled_rows(SampledArgs &list, const SddmmArgs &a)
     if (D.n < a.rows) list.loss_cols = nullptr;   // (the other rows' launch takes the mean of the losses)
 }
 
-void add_sampled(SampledArgs &list, const SddmmArgs &a)
+void add_sampled(SampledArgs &list, const SddmmCall &a)
 {
     SampledLayer &L = list.layer[list.n++];
     L.table = a.table; L.words = a.table_words; L.rows = a.rows; L.cols = a.x_rows; L.nnz = a.nnz; L.fused = a.fused;

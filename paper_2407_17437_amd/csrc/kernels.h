@@ -206,12 +206,17 @@ struct SpmmArgs {
     float *ce_dZ;              // (rows, ce_lddz)
     int64_t ce_lddz;
     float *ce_loss_cols;       // [batch]
-    const DenseSplit *split;   // (for the launch) or nullptr
-    const Strips *strips;      // the pattern's (host memory: the launch hands it on), or nullptr
-    const HotRows *hot;        // of a mirror, likewise
-    float4 *strip_stream;      // room for the plan's chunks and two more, or nullptr
-    int32_t strip_ready;       // (for the launch) launch_strip_streams has filled it
 };
+// A call: what its kernels are given, and what chooses among them and is no kernel's of the others (in host memory).  Every launch carries all of its
+// kernel's arguments, so that what one kernel reads is handed to that one: with 88 bytes more in them calls of 4 to 12 us take 1 to 4 % longer.
+struct SpmmCall : SpmmArgs {
+    const DenseSplit *split;   // or nullptr
+    const Strips *strips;      // the pattern's, or nullptr
+    const HotRows *hot;        // of a mirror, or nullptr
+    float4 *strip_stream;      // (device memory) room for the plan's chunks and two more, or nullptr
+    int32_t strip_ready;       // launch_strip_streams has filled it
+};
+static_assert(sizeof(SpmmArgs) <= 336, "every product's launch carries them");
 // What the product in strips is given in place of the matrix, for up to kStripStreams products in one launch.
 constexpr int kStripStreams = 4;
 struct StripStream {
@@ -224,14 +229,14 @@ struct StripStream {
 struct StripStreams {
     StripStream of[kStripStreams];
 };
-bool spmm_takes_strip(const SpmmArgs &a);
-hipError_t launch_strip_streams(const SpmmArgs *list, int n, hipStream_t s);
+bool spmm_takes_strip(const SpmmCall &a);
+hipError_t launch_strip_streams(const SpmmCall *list, int n, hipStream_t s);
 // tickets per huge row, one per 32 columns
 __host__ __device__ inline int64_t huge_row_tickets(int64_t scratch_ld) { return scratch_ld / 32; }
-bool spmm_softmax_epilogue_ok(const SpmmArgs &a);
+bool spmm_softmax_epilogue_ok(const SpmmCall &a);
 constexpr int32_t kFullMaxRows = 16;
 constexpr int32_t kFullSlice = 128;   // columns of W (rows of the operand) per work-group
-hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s);
+hipError_t launch_spmm(const SpmmCall &a, hipStream_t s);
 
 // g[p] = <dZ[row(p),:], X[indices[p],:]>, db[i] = sum_c dZ[i,c]; optionally followed, inside
 // the same kernel, by the momentum step on values/velocity (and bias/bias_velocity).
@@ -288,18 +293,21 @@ struct SddmmArgs {
     // pattern table of a layer dense enough for the sampled gradient (or nullptr): [rows * table_words]
     const uint2 *table;
     int32_t table_words;
-    const DenseSplit *split;        // (for the launch) or nullptr
-    const DenseSplit *split_done;   // (set by the launch) the dense rows are served already
-    float *hot_values;              // scratch [nnz] of backward_hot_kernel, or nullptr
     int32_t chain_lanes;            // 1: the sums of chain_kernel, for a step whose launches are kept apart
 };
+struct SddmmCall : SddmmArgs {      // (see SpmmCall)
+    const DenseSplit *split;        // or nullptr
+    const DenseSplit *split_done;   // (set by the launch) the dense rows are served already
+    float *hot_values;              // (device memory) scratch [nnz] of backward_hot_kernel, or nullptr
+};
+static_assert(sizeof(SddmmArgs) <= 424, "every launch of a gradient carries them");
 // Column-tile width (in columns) the products use when their gathered operand has x_rows rows and
 // does not fit an L2; 0: no tiling.  Shared by the kernels' dispatch and by the sizing of the
 // SDDMM partial buffer when a layer is created.
 int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, int32_t longest_row, float hot_share, bool masked, bool for_sddmm = false);
 struct BackwardFinish;
 // first: a finish pass of the layer above that waits, which runs before or in this launch
-hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s, BackwardFinish *first = nullptr);
+hipError_t launch_sddmm(const SddmmCall &a, hipStream_t s, BackwardFinish *first = nullptr);
 // Slices of partial products (SddmmArgs::partial) that the column-tiled SDDMM and the fused backward pass take at any batch up to max_batch
 int32_t partial_tiles_wanted(const RowBlocks &plan, const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch);
 
@@ -328,30 +336,30 @@ struct BackwardArgs {
     float lr, momentum;
     float *w, *velocity, *w_t;   // values[], velocity[] (CSR order), mirror values
     float *bias, *bias_velocity;
-    const float *hot_values;     // mirror values in the order of HotRows
-    const int32_t *hot_at;       // or nullptr
 };
+static_assert(sizeof(BackwardArgs) <= 352, "every launch of a backward pass carries them");
 // alone: a single call, not part of a training step, where the two may share their launches with other layers' instead
-bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone);
+bool backward_fused_ok(const SpmmCall &t, const SddmmCall &g, bool alone);
 // whether such a call also brings the mirror values (g.values_t) up to date with g.values, so that the caller need not
-bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g);
+bool backward_fused_refreshes(const SpmmCall &t, const SddmmCall &g);
 // whether it takes the hot rows of dZ out of LDS
-bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g);
+bool backward_hot_ok(const SpmmCall &t, const SddmmCall &g);
 // The second pass over the partial products, where it is left to a launch that follows (later, which launch_sddmm or launch_backward_finish take).
 struct BackwardFinish {
     BackwardArgs a;
+    const int32_t *hot_at;       // of an order of HotRows, in which the products are then: the entries' positions in the mirror; else nullptr
     int32_t n_tiles, n_entry_blocks, n_row_blocks;
     bool waiting;
 };
 hipError_t launch_backward_finish(BackwardFinish &f, hipStream_t s);
-hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s, BackwardFinish *later = nullptr);
-bool full_backward_ok(const SpmmArgs &t, const SddmmArgs &g);
-hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream_t s);
+hipError_t launch_backward_fused(const SpmmCall &t, const SddmmCall &g, bool alone, hipStream_t s, BackwardFinish *later = nullptr);
+bool full_backward_ok(const SpmmCall &t, const SddmmCall &g);
+hipError_t launch_full_backward(const SpmmCall &t, const SddmmCall &g, hipStream_t s);
 
 // Two independent launches in one grid (both on the 16-byte path, batch <= 1024, one column tile).
-bool can_pair(const SpmmArgs &a, const SddmmArgs &b);
-bool can_pair(const SddmmArgs &a, const SddmmArgs &b);
-hipError_t launch_pair(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s);
+bool can_pair(const SpmmCall &a, const SddmmCall &b);
+bool can_pair(const SddmmCall &a, const SddmmCall &b);
+hipError_t launch_pair(const SpmmCall &a, const SddmmCall &b, hipStream_t s);
 // The end of a training step in one launch (chain_kernel): T_1, S_1 and S_0, and the SDDMM of a layer above that waits for its update (or nullptr;
 // can_pair(g0, it)).
 struct ChainArgs {
@@ -365,11 +373,11 @@ struct ChainArgs {
 };
 constexpr int32_t kChainMinRows = 256, kChainMaxBatch = 192;
 // chain_shape_ok: the part that does not depend on whether the updates are fused; then a step that keeps its launches apart forms dZ_0 in the same order.
-bool chain_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0);
-bool chain_shape_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0);
-hipError_t launch_chain_transposed(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, hipStream_t s);
-hipError_t launch_chain(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, const SddmmArgs *waiting, hipStream_t s);
-hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s);
+bool chain_ok(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0);
+bool chain_shape_ok(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0);
+hipError_t launch_chain_transposed(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0, hipStream_t s);
+hipError_t launch_chain(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0, const SddmmCall *waiting, hipStream_t s);
+hipError_t launch_pair(const SddmmCall &a, const SddmmCall &b, hipStream_t s);
 
 hipError_t launch_momentum(float *w, float *v, const float *g, int64_t n, float lr, float mu, int nesterov,
                            hipStream_t s);
@@ -449,16 +457,16 @@ struct SampledArgs {
     int32_t loss_n;
 };
 // whether launch_sddmm takes that route for `a`, and whether it could be served by it beside layers that do
-bool sddmm_sampled_ok(const SddmmArgs &a);
-bool sddmm_sampled_possible(const SddmmArgs &a);
-void add_sampled(SampledArgs &list, const SddmmArgs &a);
+bool sddmm_sampled_ok(const SddmmCall &a);
+bool sddmm_sampled_possible(const SddmmCall &a);
+void add_sampled(SampledArgs &list, const SddmmCall &a);
 hipError_t launch_sampled(SampledArgs &a, hipStream_t s);
 // Y = act(W X + b) of a matrix's dense rows, and the room in DenseRows that takes at up to max_batch columns
 bool dense_rows_product_ok(const DenseSplit *d, int32_t cols, int32_t batch);
 bool dense_rows_sddmm_ok(const DenseSplit *d, int32_t batch);
 bool thin_rows_pay_somewhere(const DenseSplit &d, int32_t cols);
-bool sampled_operands_ok(const SddmmArgs &a);
-hipError_t launch_dense_rows(const SpmmArgs &a, hipStream_t s);
+bool sampled_operands_ok(const SddmmCall &a);
+hipError_t launch_dense_rows(const SpmmCall &a, hipStream_t s);
 __host__ __device__ inline int64_t dense_rows_ld(int32_t batch) { return (batch + 31) / 32 * 32; }
 // The same on the bf16 matrix units, every fp32 number as three bf16 ones (split.hip): work-groups, most chunks of 32 columns of the matrix in one
 // of them, and the operand's parts: 12 ints per 8 rows and column, columns rounded up to whole work-groups, and a flag per 32 rows
@@ -476,7 +484,7 @@ struct DenseRowsRoom {
     int64_t partial_floats, parts_ints;
 };
 DenseRowsRoom dense_rows_room(int32_t n, int32_t cols, int32_t max_batch, bool thin);
-void add_sampled_rows(SampledArgs &list, const SddmmArgs &a);
+void add_sampled_rows(SampledArgs &list, const SddmmCall &a);
 // status: result of the pattern check (the launch does nothing where it is not 0), or nullptr
 // list: the rows (or nullptr: 0 .. rows - 1)
 hipError_t launch_pattern_table(const int32_t *indptr, const int32_t *indices, const int32_t *list, int32_t rows, int32_t words, uint2 *table,

@@ -1202,7 +1202,7 @@ __device__ __forceinline__ void strip_steps(const char *lds, const float4 &c, fl
 struct StripGrid {
     int n_tiles, n_ranges, per;     // strips, ranges of sets, an eighth of the grid
 };
-__global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const SpmmArgs a, const StripGrid g, const Strips f)
+__global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const SpmmArgs a, const StripGrid g, const Strips f, const float4 *const strip_stream)
 {
     __shared__ float4 strip[kStripRows * kStripCols / 4 + kStripCols / 4];  // the block, then one row of zeros
     // (neighbouring tiles share lines of the operand, all ranges of a tile its rows: a run of the list of both to an XCD)
@@ -1226,7 +1226,7 @@ __global__ __launch_bounds__(kStripWaves * kWave) void spmm_strip_kernel(const S
     float4 acc[kStripJ];
     static_for(all_j, [&](auto jc) { acc[decltype(jc)::value] = make_float4(0.f, 0.f, 0.f, 0.f); });
     // the first two chunks of a segment are asked for a set ahead (of an empty one or a short one, others', which nothing is done with)
-    const float4 *stream = a.strip_stream + lane;
+    const float4 *stream = strip_stream + lane;
     float4 held[2][2];
     auto ask = [&](auto jc, const int2 &s) {
         constexpr int j = decltype(jc)::value;
@@ -2207,7 +2207,7 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void backward_fused_kernel(const
 // Second pass: work-groups [0, n_entry_blocks) add the tiles' partial products of mirror entry q in tile
 // order and apply the momentum step to the entry's CSR position perm[q] (or store the gradient there);
 // the remaining work-groups, a wave per row of W, sum the rows of dZ for the bias gradient.
-__device__ __forceinline__ void backward_finish(const BackwardArgs &a, int n_tiles, int n_entry_blocks, int n_blocks, int block)
+__device__ __forceinline__ void backward_finish(const BackwardArgs &a, const int32_t *hot_at, int n_tiles, int n_entry_blocks, int n_blocks, int block)
 {
     if (block < n_entry_blocks) {
         for_runs_of_xcds(a.nnz, n_entry_blocks, [&](int64_t q) {
@@ -2225,7 +2225,7 @@ __device__ __forceinline__ void backward_finish(const BackwardArgs &a, int n_til
                 momentum_step(w, v, g, a.lr, a.momentum, a.nesterov);
                 a.w[p] = w;
                 a.velocity[p] = v;
-                a.w_t[a.hot_at ? a.hot_at[q] : q] = w;
+                a.w_t[hot_at ? hot_at[q] : q] = w;
             }
         }, block);
         return;
@@ -2234,23 +2234,23 @@ __device__ __forceinline__ void backward_finish(const BackwardArgs &a, int n_til
     backward_row_sums(a, static_cast<int64_t>(block - n_entry_blocks) * (kEwBlock / kWave) + wave_in_block(),
                       static_cast<int64_t>(n_blocks - n_entry_blocks) * (kEwBlock / kWave));
 }
-__global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const BackwardArgs a, const int n_tiles, const int n_entry_blocks)
+__global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const BackwardArgs a, const int32_t *const hot_at, const int n_tiles, const int n_entry_blocks)
 {
-    backward_finish(a, n_tiles, n_entry_blocks, gridDim.x, blockIdx.x);
+    backward_finish(a, hot_at, n_tiles, n_entry_blocks, gridDim.x, blockIdx.x);
 }
 
 // The same among the work-groups of the column-tiled SDDMM of the layer below, which only needs the dZ that this layer's pass has formed: a launch and one drained chip less.  Every `every`-th eight
 // work-groups (one to an XCD) are the finish pass's.  Wide MLP 322 -> 318 us a step (21 + 64 in turn, 83 together: the second pass's scattered lines take the same L2 requests as the gathers;
 // at twice to eight times the rate, or first of all, 305-310 where this order gives 303).
 template <int NV, bool SPARE>
-__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void sddmm_tiled_finish_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order, const BackwardArgs f,
+__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void sddmm_tiled_finish_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order, const BackwardArgs f, const int32_t *const hot_at,
                                                                                                                          const int f_tiles, const int n_entry_blocks, const int n_finish, const int every)
 {
     static_assert(kSddmmWaves * kWave == kEwBlock, "");
     const int eight = blockIdx.x >> 3, turn = eight / every, groups = (n_finish + 7) / 8;
     if (turn < groups && eight - turn * every == every - 1) {
         const int block = turn * 8 + (blockIdx.x & 7);
-        if (block < n_finish) backward_finish(f, f_tiles, n_entry_blocks, n_finish, block);
+        if (block < n_finish) backward_finish(f, hot_at, f_tiles, n_entry_blocks, n_finish, block);
         return;
     }
     sddmm_tile<16, NV, SPARE>(a, n_tiles, order, (eight - min(turn, groups)) * 8 + (blockIdx.x & 7));
@@ -2322,7 +2322,7 @@ __global__ __launch_bounds__(kEwBlock) void hot_values_kernel(float *out, const 
     });
 }
 template <bool SPARE>
-__global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const BackwardArgs a, const StripGrid g, const HotRows f)
+__global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const BackwardArgs a, const StripGrid g, const HotRows f, const float *const hot_values)
 {
     __shared__ float4 hot[kHotRowsLds * 16 + 16];   // the rows, then one of zeros
     __shared__ int taken;
@@ -2377,7 +2377,7 @@ __global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const B
     auto ask = [&](const Set &s, bool is_hot, int first) {
         const int e = first + lig, n = is_hot ? s.n_hot : s.len - s.n_hot;
         const uint32_t o = e < n ? static_cast<uint32_t>(s.s0 + (is_hot ? 0 : s.n_hot) + e) * 4u : 0u;
-        return Chunk{__builtin_bit_cast(int, gload1(as_gmem(f.entry), o)), gload1(as_gmem(a.hot_values), o)};
+        return Chunk{__builtin_bit_cast(int, gload1(as_gmem(f.entry), o)), gload1(as_gmem(hot_values), o)};
     };
     auto record = [&](int set) { return set < n_sets ? f.sets[set * 4 + lrow] : make_int4(-1, 0, 0, 0); };
     auto input = [&](const Set &s) { return ld4(a.X + static_cast<int64_t>(max(s.row, 0)) * a.ldx + col); };
@@ -3172,9 +3172,9 @@ inline int xcd_run_blocks(int64_t work_items, int each = 1)
 }
 inline int gather_blocks(int64_t n) { return xcd_run_blocks(n, n < kGatherMany ? 1 : kGatherEach); }
 
-bool spmm_offsets_ok(const SpmmArgs &a);
+bool spmm_offsets_ok(const SpmmCall &a);
 
-hipError_t spmm_go(SpmmArgs a, hipStream_t s)
+hipError_t spmm_go(SpmmCall a, hipStream_t s)
 {
     a.wide_offsets = !spmm_offsets_ok(a);
     dim3 grid(a.blocks.n_blocks, (a.batch + 255) / 256);
@@ -3186,7 +3186,7 @@ hipError_t spmm_go(SpmmArgs a, hipStream_t s)
 }
 
 template <int GS>
-hipError_t spmm_grouped_go(const SpmmArgs &a, hipStream_t s)
+hipError_t spmm_grouped_go(const SpmmCall &a, hipStream_t s)
 {
     dim3 grid(a.blocks.n_blocks);
     if (a.XM)
@@ -3199,7 +3199,7 @@ hipError_t spmm_grouped_go(const SpmmArgs &a, hipStream_t s)
 // The gathered operand (and its mask) should stay in one 4 MiB L2 while it is being gathered
 // from: if the whole operand is too large for that, the batch is walked in column tiles of
 // 4 * (return value) columns.  0: no tiling.
-int spmm_tile_group(const SpmmArgs &a)
+int spmm_tile_group(const SpmmCall &a)
 {
     if (static_cast<int64_t>(a.blocks.n_blocks) * ((a.batch + 31) / 32 + 8) >= (1ll << 31)) return 0;
     return tile_columns(a.x_rows, a.batch, a.nnz, a.rows, a.blocks.staged_longest_row, a.blocks.hot_share, a.XM != nullptr) / 4;
@@ -3250,7 +3250,7 @@ template <typename Args>
 inline TiledLaunch tiled_launch(const Args &a) { return TiledLaunch{a.x_rows, a.rows, a.blocks.staged_longest_row, a.nnz, a.blocks.hot_share}; }
 
 template <int GS>
-hipError_t spmm_tiled_go(const SpmmArgs &a, hipStream_t s)
+hipError_t spmm_tiled_go(const SpmmCall &a, hipStream_t s)
 {
     const int n_tiles = (a.batch + GS * 4 - 1) / (GS * 4);
     const TileOrder order = tile_order(n_tiles, a.blocks.n_blocks, GS, true, tiled_launch(a));
@@ -3271,7 +3271,7 @@ struct PackedGrid {
     int64_t ids;
     bool long_rows;   // (else spmm_packed_only_kernel)
 };
-PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
+PackedGrid packed_grid(const SpmmCall &a, int gs, bool with_long_rows)
 {
     PackedGrid g;
     const int ne = kWave / gs;
@@ -3286,7 +3286,7 @@ PackedGrid packed_grid(const SpmmArgs &a, int gs, bool with_long_rows)
     return g;
 }
 template <int GS>
-hipError_t spmm_packed_go(const SpmmArgs &a, hipStream_t s)
+hipError_t spmm_packed_go(const SpmmCall &a, hipStream_t s)
 {
     const PackedGrid pg = packed_grid(a, GS, true);
     const int n_tiles = pg.n_tiles, n_pack_blocks = pg.n_pack_blocks;
@@ -3312,7 +3312,7 @@ void with_spare(int batch, int columns, F &&go)
 }
 
 template <int G, int NV>
-hipError_t sddmm_go(const SddmmArgs &a, hipStream_t s)
+hipError_t sddmm_go(const SddmmCall &a, hipStream_t s)
 {
     dim3 grid(a.blocks.n_blocks);
     with_spare(a.batch, G * 4 * NV, [&](auto spare) { hipLaunchKernelGGL((sddmm_kernel<G, NV, decltype(spare)::value>), grid, dim3(kBlock), 0, s, a); });
@@ -3328,11 +3328,11 @@ inline bool spans_below_4gib(int64_t rows, int64_t ld) { return rows * ld * 4 < 
 // L2 and evenly used (the gathers of the other kernels then go to memory); and where no single lane row's share,
 // served at about one entry per 60 ns, outlasts the rest of the matrix, which
 // the chip's 256 LDS serve at about one entry and tile per 3.3 ns each.
-bool spmm_dense_rows_ok(const SpmmArgs &a)
+bool spmm_dense_rows_ok(const SpmmCall &a)
 {
     return dense_rows_product_ok(a.split, a.x_rows, a.batch) && !a.XM && spmm_offsets_ok(a);
 }
-bool sddmm_dense_rows_ok(const SddmmArgs &a)
+bool sddmm_dense_rows_ok(const SddmmCall &a)
 {
     return dense_rows_sddmm_ok(a.split, a.batch) && sampled_operands_ok(a);
 }
@@ -3385,7 +3385,7 @@ constexpr int64_t kFusedMinWork = 16 << 20;        // (backward_fused_ok)
 constexpr int64_t kPackTilesOperand = 21ll << 18;  // operand bytes
 constexpr int64_t kPackTilesGathers = 13;          // entries per operand row
 static_assert(kPackTilesOperand / 4 * kPackTilesGathers >= kFusedMinWork, "");
-static bool packed_tiles_pay(const SpmmArgs &a)
+static bool packed_tiles_pay(const SpmmCall &a)
 {
     if (a.batch <= 128 || a.XM || a.blocks.n_short != a.rows || a.blocks.hot_share >= 0.5f) return false;
     if (static_cast<int64_t>(a.blocks.staged_longest_row) * a.rows > 4ll * a.nnz || (a.batch + 63) / 64 * 320 > 6 * a.batch) return false;
@@ -3394,13 +3394,13 @@ static bool packed_tiles_pay(const SpmmArgs &a)
            packed_grid(a, 16, true).ids <= kMaxGridIds;
 }
 
-int spmm_tile_group(const SpmmArgs &a);
+int spmm_tile_group(const SpmmCall &a);
 constexpr int64_t kSplitMinOperand = 48ll << 20;  // operand bytes from which long rows go into column tiles of their own: beyond the eight L2s
 
 // Lanes per row (4 columns each) of the column tiles in which the LONG rows of a matrix run while its short rows run
 // untiled: for an operand that the L2s together cannot hold, gathered about evenly, on a matrix whose long rows
 // (beyond kPackMaxLen entries; they have a partition of their own) hold most of the stored entries.  0: no split.
-int spmm_split_group(const SpmmArgs &a)
+int spmm_split_group(const SpmmCall &a)
 {
     if (a.blocks.n_long_blocks <= 0 || a.blocks.n_rest_blocks <= 0 || a.batch < 128) return 0;
     if (static_cast<int64_t>(a.x_rows) * a.batch * 4 < kSplitMinOperand || a.blocks.hot_share >= 0.5f) return 0;
@@ -3419,7 +3419,7 @@ int spmm_split_group(const SpmmArgs &a)
     return g;
 }
 
-bool spmm_staged_ok(const SpmmArgs &a);
+bool spmm_staged_ok(const SpmmCall &a);
 // The product in strips, us, with the ranges that make it shortest: rounds of 256 work-groups (one fits a compute unit), each the steps that its LDS serves, the sets that a wave takes one after the
 // other, and the copy of the operand's strip; before them the stream.  Fitted, as the estimates of the other kernels below, to 28600 uniform matrices of 300 to 16384 rows, 1024 to 16384 columns, 0.1 to
 // 10 %, batch 193 to 1024, and to the next best number of ranges: root mean square 6.6 %, 1 % off at any number of blocks.
@@ -3443,10 +3443,10 @@ static StripPlan strip_plan(int32_t rows, int32_t x_rows, int32_t batch, int32_t
     p.grid.per = static_cast<int>((static_cast<int64_t>(p.grid.n_tiles) * p.grid.n_ranges + 7) / 8);
     return p;
 }
-static StripPlan strip_plan(const SpmmArgs &a) { return strip_plan(a.rows, a.x_rows, a.batch, a.strips->blocks, a.strips->steps, a.strips->chunks); }
+static StripPlan strip_plan(const SpmmCall &a) { return strip_plan(a.rows, a.x_rows, a.batch, a.strips->blocks, a.strips->steps, a.strips->chunks); }
 // The kernel that would run otherwise, us: staged, in column tiles (of 128, or of 64 and fewer) or over the whole batch; 3.5, 8.8, 17 (3 to 16 too short in the mean) and 10 % root mean square.  0: not known
 // well enough for a comparison.
-static double other_product_us(const SpmmArgs &a)
+static double other_product_us(const SpmmCall &a)
 {
     const double nnz = a.nnz * 1e-6, x_rows = a.x_rows * 1e-6, rows = a.rows * 1e-6, operand = 4. * x_rows * a.batch;   // (millions)
     if (spmm_staged_ok(a)) {
@@ -3465,14 +3465,14 @@ static double other_product_us(const SpmmArgs &a)
 // Where strips pay: of the matrices above that take them 0.75 % are slower by 3 % or more, the worst by 14 %; all in all they are 1.32 times as fast.  (A line that asks less of the strips, 0.98: 1.27 times, but
 // 3 % of the matrices slower.)
 static bool strip_pays(double strips, double other) { return strips < 0.94 * other; }
-bool spmm_strip_ok(const SpmmArgs &a)
+bool spmm_strip_ok(const SpmmCall &a)
 {
     if (!a.strips || !a.strip_stream || a.XM || a.batch <= kStripFromBatch) return false;
     const int64_t groups = (static_cast<int64_t>(a.rows) + kStripSet * kStripWaves * kStripJ - 1) / (kStripSet * kStripWaves * kStripJ) * ((a.batch + kStripCols - 1) / kStripCols);
     return groups < (1 << 28) && (a.strips->preferred || strip_pays(strip_plan(a).us, other_product_us(a)));
 }
 
-bool spmm_staged_ok(const SpmmArgs &a)
+bool spmm_staged_ok(const SpmmCall &a)
 {
     if (a.x_rows < 64 || a.nnz < 64) return false;  // (it brings 64 operand rows at a time, and reads entries up to 32 past the first)
     if (!staged_pays(a.blocks, a.x_rows, a.batch, staged_work(a.blocks, a.x_rows, a.batch) >= kStageSomeWork ? kStageSegmentSomeWork : kStageLongSegment)) return false;
@@ -3480,15 +3480,15 @@ bool spmm_staged_ok(const SpmmArgs &a)
 }
 
 // whether the rows a partial plan leaves out take the packed kernel, which runs inside column tiles only
-bool staged_rest_packed(const SpmmArgs &a, int tg)
+bool staged_rest_packed(const SpmmCall &a, int tg)
 {
     return a.blocks.n_short > 0 && tg != 0 && spmm_offsets_ok(a) && packed_grid(a, tg, false).ids <= kMaxGridIds;
 }
 
-bool sddmm_offsets_ok(const SddmmArgs &a);
+bool sddmm_offsets_ok(const SddmmCall &a);
 
 // a full matrix of few rows whose dZ fits in 64 KiB of LDS
-bool sddmm_full_ok(const SddmmArgs &a)
+bool sddmm_full_ok(const SddmmCall &a)
 {
     if (a.rows > kFullMaxRows || a.x_rows < 256 || static_cast<int64_t>(a.nnz) != static_cast<int64_t>(a.rows) * a.x_rows) return false;
     if (a.batch < 64 || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
@@ -3496,7 +3496,7 @@ bool sddmm_full_ok(const SddmmArgs &a)
 }
 
 // the staged SDDMM needs room for one slice of partial products per 64-column tile
-bool sddmm_staged_ok(const SddmmArgs &a)
+bool sddmm_staged_ok(const SddmmCall &a)
 {
     if (!a.partial || a.skip_products || a.dense || a.loss_cols || !sddmm_offsets_ok(a)) return false;
     if ((a.batch + kStageCols - 1) / kStageCols > a.partial_tiles) return false;
@@ -3507,12 +3507,12 @@ bool sddmm_staged_ok(const SddmmArgs &a)
     return staged_pays(a.blocks, a.x_rows, a.batch, segment);
 }
 
-bool spmm_offsets_ok(const SpmmArgs &a)
+bool spmm_offsets_ok(const SpmmCall &a)
 {
     return spans_below_4gib(a.x_rows, a.ldx) && (!a.XM || spans_below_4gib(a.x_rows, a.ldxm));
 }
 
-void sddmm_finish_go(const SddmmArgs &a, int n_tiles, hipStream_t s)
+void sddmm_finish_go(const SddmmCall &a, int n_tiles, hipStream_t s)
 {
     const int64_t work = a.nnz > a.rows ? a.nnz : a.rows;
     hipLaunchKernelGGL(sddmm_finish_kernel, dim3(a.fused && a.values_t ? xcd_run_blocks(work) : elementwise_blocks(work)), dim3(kEwBlock), 0, s, a, n_tiles,
@@ -3520,7 +3520,7 @@ void sddmm_finish_go(const SddmmArgs &a, int n_tiles, hipStream_t s)
 }
 
 template <int G, int NV>
-hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s, BackwardFinish *first = nullptr)
+hipError_t sddmm_tiled_go(const SddmmCall &a, hipStream_t s, BackwardFinish *first = nullptr)
 {
     const int W = G * 4 * NV;
     const int n_tiles = (a.batch + W - 1) / W;
@@ -3538,7 +3538,7 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s, BackwardFinish *fir
                 const int n_finish = first->n_entry_blocks + first->n_row_blocks, groups = (n_finish + 7) / 8;
                 const int64_t eights = (ids + 7) / 8 + groups;
                 first->waiting = false;
-                hipLaunchKernelGGL((sddmm_tiled_finish_kernel<NV, decltype(spare)::value>), dim3(static_cast<unsigned>(eights * 8)), dim3(kSddmmWaves * kWave), 0, s, a, n_tiles, order, first->a,
+                hipLaunchKernelGGL((sddmm_tiled_finish_kernel<NV, decltype(spare)::value>), dim3(static_cast<unsigned>(eights * 8)), dim3(kSddmmWaves * kWave), 0, s, a, n_tiles, order, first->a, first->hot_at,
                                    first->n_tiles, first->n_entry_blocks, n_finish, static_cast<int>(eights / groups));
                 return;
             }
@@ -3550,13 +3550,13 @@ hipError_t sddmm_tiled_go(const SddmmArgs &a, hipStream_t s, BackwardFinish *fir
 }
 
 // what the SDDMM kernels but the generic one ask for: four columns, 32-bit offsets into X
-bool sddmm_offsets_ok(const SddmmArgs &a)
+bool sddmm_offsets_ok(const SddmmCall &a)
 {
     return a.batch >= 4 && (a.skip_products || spans_below_4gib(a.x_rows, a.ldx));
 }
 
 template <int GS_S, int G, int NV_D>
-hipError_t pair_go(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
+hipError_t pair_go(const SpmmCall &a, const SddmmCall &b, hipStream_t s)
 {
     const int na = a.blocks.n_blocks * (GS_S == kWave ? (a.batch + 255) / 256 : 1);
     dim3 grid(na + b.blocks.n_blocks);
@@ -3567,7 +3567,7 @@ hipError_t pair_go(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
 }
 
 template <int G, int NV_D>
-hipError_t sddmm_pair_go(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
+hipError_t sddmm_pair_go(const SddmmCall &a, const SddmmCall &b, hipStream_t s)
 {
     const int na = a.blocks.n_blocks;
     dim3 grid(na + b.blocks.n_blocks);
@@ -3599,7 +3599,7 @@ hipError_t with_sddmm_lanes(int batch, F &&go)
 
 }  // namespace
 
-int sddmm_tile_columns(const SddmmArgs &a);
+int sddmm_tile_columns(const SddmmCall &a);
 
 static int tile_columns_wanted(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, bool skewed, float hot_share, bool masked, bool for_sddmm)
 {
@@ -3675,13 +3675,13 @@ int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, int32
 
 // Few tiles of an operand whose rows are gathered rarely are for the product alone, with a gradient they lose: 9000 x 4000 at 0.3 %, batch 400, both
 // gradients 30.2 -> 33.6 us in them; 9106 x 9383 at 0.1 % 28.9 -> 29.8.
-static bool few_rare_tiles(const SpmmArgs &a)
+static bool few_rare_tiles(const SpmmCall &a)
 {
     const int columns = 4 * spmm_tile_group(a);
     return columns > 0 && (a.batch + columns - 1) / columns < 8 && a.nnz < 24ll * a.x_rows && static_cast<int64_t>(a.blocks.staged_longest_row) * a.rows <= 16 * a.nnz;
 }
 
-bool can_pair(const SpmmArgs &a, const SddmmArgs &b)
+bool can_pair(const SpmmCall &a, const SddmmCall &b)
 {
     return !sddmm_sampled_ok(b) && !sddmm_dense_rows_ok(b) && a.batch == b.batch && a.batch > 4 && a.batch <= 1024 && !a.XM && a.rows > 0 && b.rows > 0 &&
            a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && spmm_offsets_ok(a) &&
@@ -3689,7 +3689,7 @@ bool can_pair(const SpmmArgs &a, const SddmmArgs &b)
            !sddmm_staged_ok(b) && !sddmm_full_ok(b);
 }
 
-bool can_pair(const SddmmArgs &a, const SddmmArgs &b)
+bool can_pair(const SddmmCall &a, const SddmmCall &b)
 {
     return !sddmm_sampled_ok(a) && !sddmm_sampled_ok(b) && !sddmm_dense_rows_ok(a) && !sddmm_dense_rows_ok(b) && a.batch == b.batch && a.batch > 0 && a.batch <= 1024 && a.rows > 0 && b.rows > 0 &&
            a.blocks.n_blocks > 0 && b.blocks.n_blocks > 0 && sddmm_offsets_ok(a) && sddmm_offsets_ok(b) &&
@@ -3697,7 +3697,7 @@ bool can_pair(const SddmmArgs &a, const SddmmArgs &b)
            !sddmm_full_ok(a) && !sddmm_full_ok(b);
 }
 
-hipError_t launch_pair(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
+hipError_t launch_pair(const SpmmCall &a, const SddmmCall &b, hipStream_t s)
 {
     return with_sddmm_lanes(a.batch, [&](auto g, auto nv) {
         // (the product's own lane groups for that many columns, as launch_spmm has them)
@@ -3706,7 +3706,7 @@ hipError_t launch_pair(const SpmmArgs &a, const SddmmArgs &b, hipStream_t s)
     });
 }
 
-hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
+hipError_t launch_pair(const SddmmCall &a, const SddmmCall &b, hipStream_t s)
 {
     return with_sddmm_lanes(a.batch, [&](auto g, auto nv) { return sddmm_pair_go<decltype(g)::value, decltype(nv)::value>(a, b, s); });
 }
@@ -3716,20 +3716,20 @@ hipError_t launch_pair(const SddmmArgs &a, const SddmmArgs &b, hipStream_t s)
 // two or have long rows.  Steps at batch 100 apart / in one, us: 500-1000-1000-10 at 10 % (twice W_0's entries) 34.3 / 29.8, 300-1000-1000-10 (three times)
 // 33.6 / 29.2.  Up to 192 columns: 2000-1500-400-10 at 5 %, batch 180 / 256: 37.2 / 34.4, 41.3 / 43.6.  Networks of a small hidden layer keep their two
 // launches, which a profile of the step shows one by one (256-128-64-10 at 20 %: 20.9 / 18.6).
-bool chain_pays(const SpmmArgs &t, const SddmmArgs &g0);
-bool chain_shape_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
+bool chain_pays(const SpmmCall &t, const SddmmCall &g0);
+bool chain_shape_ok(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0)
 {
     if (t.batch != g1.batch || t.batch > kChainMaxBatch || t.X != g1.dZ || t.ldx != g1.lddz || !t.YM || t.YM != g1.X || t.ldym != g1.ldx || t.Y != g0.dZ || t.ldy != g0.lddz) return false;
     if (!can_pair(t, g0) || !can_pair(t, g1) || t.nnz <= 0 || t.nnz != g1.nnz || t.rows != g0.rows) return false;
     if (g1.dense || g0.dense || g1.loss_cols || g0.loss_cols || g0.values_t || g0.ZM || g1.ZM) return false;
     return g0.blocks.n_huge_rows == 0 && t.rows >= kChainMinRows && t.blocks.staged_longest_row <= 2 * kPackMaxLen && t.nnz / 4 <= g0.nnz && chain_pays(t, g0);
 }
-bool chain_ok(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0)
+bool chain_ok(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0)
 {
     return g0.fused && g1.fused && g1.perm && g1.values_t && chain_shape_ok(t, g1, g0);
 }
 
-static ChainArgs chain_args(const SpmmArgs &t, const SddmmArgs &g1)
+static ChainArgs chain_args(const SpmmCall &t, const SddmmCall &g1)
 {
     ChainArgs c{};
     c.indptr_t = t.indptr; c.indices_t = t.indices; c.values_t = const_cast<float *>(t.values); c.perm = g1.perm; c.w = g1.values; c.velocity = g1.velocity;
@@ -3752,10 +3752,10 @@ hipError_t with_chain_lanes(int batch, F &&go)
     });
 }
 
-hipError_t launch_chain(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, const SddmmArgs *waiting, hipStream_t s)
+hipError_t launch_chain(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0, const SddmmCall *waiting, hipStream_t s)
 {
     const ChainArgs c = chain_args(t, g1);
-    SddmmArgs b{};
+    SddmmCall b{};
     if (waiting) b = *waiting;
     return with_chain_lanes(t.batch, [&](auto g, auto nv, auto gb, auto nvb) {
         constexpr int G = decltype(g)::value, NV = decltype(nv)::value, kRows = kWavesPerBlock * (kWave / G);
@@ -3768,7 +3768,7 @@ hipError_t launch_chain(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs 
     });
 }
 
-hipError_t launch_chain_transposed(const SpmmArgs &t, const SddmmArgs &g1, const SddmmArgs &g0, hipStream_t s)
+hipError_t launch_chain_transposed(const SpmmCall &t, const SddmmCall &g1, const SddmmCall &g0, hipStream_t s)
 {
     return with_chain_lanes(t.batch, [&](auto g, auto nv, auto, auto) {
         hipLaunchKernelGGL((chain_transposed_kernel<decltype(g)::value, decltype(nv)::value>), dim3(g0.blocks.n_blocks), dim3(kBlock), 0, s, chain_args(t, g1), g0);
@@ -3782,7 +3782,7 @@ hipError_t launch_chain_transposed(const SpmmArgs &t, const SddmmArgs &g1, const
 // Small work on short rows, two column tiles: a wave takes its entries through both, which leaves no second launch (546 x 2764 at
 // 0.12 %, batch 300: 16.3 -> 6.4 us; through four tiles it is the longer way, 2592 x 702 at batch 933: 18).
 constexpr int64_t kBackwardSmallWork = 8 << 20;   // entries times columns: a few us of gathers, a launch costs 3.5
-static bool backward_looped(const SpmmArgs &t)
+static bool backward_looped(const SpmmCall &t)
 {
     return t.batch > 128 && t.batch <= 512 && t.blocks.staged_longest_row <= kWave && static_cast<int64_t>(t.nnz) * t.batch <= kBackwardSmallWork;
 }
@@ -3791,7 +3791,7 @@ static bool backward_looped(const SpmmArgs &t)
 // 12000^2 at 0.1 %: 27 and 24), and tiles of 128 beyond; its own tiles are widened to 128 columns
 // while a tile of dZ still fills no more than an L2 -- half as many tiles halve the partial products that go
 // out and come back (wide MLP, 8192 x 8192 layer: 128.6 -> 122.6 us; the product alone loses 7 % with them).
-static int backward_tile_group(const SpmmArgs &t)
+static int backward_tile_group(const SpmmCall &t)
 {
     if (backward_looped(t)) return 64;
     const int tg = few_rare_tiles(t) ? 0 : spmm_tile_group(t);
@@ -3802,13 +3802,13 @@ static int backward_tile_group(const SpmmArgs &t)
 }
 // log2 of the lane groups that share a mirror row: more of them where the rows alone do not make 4096 waves, as long as the
 // shares are not shorter than a pass
-static int backward_split(const SpmmArgs &t, int tg, int n_tiles)
+static int backward_split(const SpmmCall &t, int tg, int n_tiles)
 {
     int lg = 0;
     while ((tg << lg) < kWave && (static_cast<int64_t>(t.rows) * tg << lg) / kWave * n_tiles < 4096 && static_cast<int64_t>(t.rows) * (16 << lg) <= t.nnz) ++lg;
     return lg;
 }
-static int backward_tiles(const SpmmArgs &t, int tg) { return (t.batch + tg * 4 - 1) / (tg * 4); }
+static int backward_tiles(const SpmmCall &t, int tg) { return (t.batch + tg * 4 - 1) / (tg * 4); }
 
 // What the end of a step in one launch saves is 3 to 5 us whatever the work, and where there is much of it the launches apart are the faster ones, with more registers.  W_1: the entries of
 // a mirror row lie a row of W_1 apart in its values and velocity.  Steps, us, apart -> in one (thousand entries of W_1 x thousand rows): 1000-2000-2000-10 at 5 / 10 % (200 x 2, 400 x 2), batch 64 39.8 ->
@@ -3817,7 +3817,7 @@ static int backward_tiles(const SpmmArgs &t, int tg) { return (t.batch + tg * 4 
 // 0.5 / 1 / 1.7 % (29, 58 and 98 entries a mirror row), batch 64 47.4 -> 42.1, 62.8 -> 56.9, 80.9 -> 76.0, at 2.5 % 107 -> 112, batch 16 at 1 / 1.7 % 50.6 -> 51.6, 59.5 -> 68.6; where its backward pass
 // alone takes two tiles, batch 150: 1.7 % 138 -> 122.  W_0's gradient beside a small W_1: 2500-700-64-10 at 30 % (525 and 13), batch 38 / 100: 34.0 -> 35.0, 42.9 -> 45.2, at 12 % 27.1 -> 25.0,
 // 31.1 -> 30.2; 4000-6000-300-10 at 2.5 / 4 % (960 and 72), batch 80: 48.2 -> 45.5, 64.9 -> 68.7.
-bool chain_pays(const SpmmArgs &t, const SddmmArgs &g0)
+bool chain_pays(const SpmmCall &t, const SddmmCall &g0)
 {
     const int64_t n = t.nnz, spread = n * t.x_rows, below = static_cast<int64_t>(g0.nnz) * t.batch;
     if ((n * 16 < g0.nnz && below > (24 << 20)) || (n * 8 < g0.nnz && below > (64 << 20))) return false;
@@ -3827,7 +3827,7 @@ bool chain_pays(const SpmmArgs &t, const SddmmArgs &g0)
 }
 
 // (reading values[] through the position map costs a scattered read per entry and tile, a launch of its own 3.5 us)
-bool backward_fused_refreshes(const SpmmArgs &t, const SddmmArgs &g)
+bool backward_fused_refreshes(const SpmmCall &t, const SddmmCall &g)
 {
     if (backward_hot_ok(t, g)) return true;
     const int tiles = backward_tiles(t, backward_tile_group(t));
@@ -3855,11 +3855,11 @@ static double staged_launch_time(const RowBlocks &blocks, int64_t nnz, int32_t x
     const double rounds = static_cast<double>((groups + kStageTargetGroups - 1) / kStageTargetGroups);
     return rounds * (1.12e-3 * static_cast<double>(nnz) / blocks.staged_ranges + 5.9e-3 * x_rows);
 }
-static bool backward_apart_pays(const SpmmArgs &t, const SddmmArgs &g, bool alone)
+static bool backward_apart_pays(const SpmmCall &t, const SddmmCall &g, bool alone)
 {
     if (!spmm_staged_ok(t)) return false;
     const bool sampled = sddmm_sampled_ok(g), split = !sampled && sddmm_dense_rows_ok(g);
-    SddmmArgs others = g;
+    SddmmCall others = g;
     if (split) {
         if (!alone) return true;
         others.blocks = g.split->others; others.split = nullptr; others.split_done = g.split;
@@ -3882,7 +3882,7 @@ static bool backward_apart_pays(const SpmmArgs &t, const SddmmArgs &g, bool alon
     }
     return apart < (!alone ? (sampled ? 1.03 : 0.96) : split ? 0.98 : t.rows < 2048 ? 0.93 : sampled ? 1.03 : 1.) * stream;
 }
-bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
+bool backward_fused_ok(const SpmmCall &t, const SddmmCall &g, bool alone)
 {
     if (t.batch != g.batch || t.batch < 4 || t.X != g.dZ || t.ldx != g.lddz || t.XM != g.ZM || t.ldxm != g.ldzm) return false;
     if (t.YM && (t.YM != g.X || t.ldym != g.ldx)) return false;
@@ -3905,7 +3905,7 @@ bool backward_fused_ok(const SpmmArgs &t, const SddmmArgs &g, bool alone)
 
 bool strips_pay_somewhere(const RowBlocks &plan, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, double steps, double chunks)
 {
-    SpmmArgs a{};
+    SpmmCall a{};
     a.blocks = plan; a.rows = rows; a.x_rows = cols; a.ldx = max_batch; a.nnz = nnz;
     // (asked at a quarter and at all of every 64 columns; beyond some thousand they all say the same)
     for (int32_t most = std::min(max_batch, 4096), hi = most; hi > kStripFromBatch; hi = (hi - 1) / 64 * 64)
@@ -3939,7 +3939,7 @@ bool strips_may_pay(int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, 
 
 int32_t partial_tiles_wanted(const RowBlocks &plan, const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch)
 {
-    SpmmArgs t{};
+    SpmmCall t{};
     t.blocks = plan_t; t.rows = cols; t.x_rows = rows; t.nnz = nnz;
     if (nnz <= 0) return 0;
     // The rules are asked at either end of every 64 columns, and tiles counted to the far end: none is narrower than 32 columns.
@@ -3961,16 +3961,16 @@ int32_t partial_tiles_wanted(const RowBlocks &plan, const RowBlocks &plan_t, int
 
 // The same sharing for a full matrix of few rows (a saturated output layer): its SDDMM streams the layer's
 // input once, a wave per input row, and that row is also the mask of the transposed product's result row.
-bool full_backward_ok(const SpmmArgs &t, const SddmmArgs &g)
+bool full_backward_ok(const SpmmCall &t, const SddmmCall &g)
 {
-    SddmmArgs plain = g;
+    SddmmCall plain = g;
     plain.loss_cols = nullptr;  // (this launch can carry the mean of the losses, the plain one is not asked to)
     if (g.batch % 4 != 0 || !sddmm_full_ok(plain) || !g.fused || g.ZM || !g.values || !g.velocity) return false;
     if (t.batch != g.batch || t.XM || t.bias || t.relu || !t.YM || t.YM != g.X || t.ldym != g.ldx || t.X != g.dZ || t.ldx != g.lddz) return false;
     return t.rows == g.x_rows && t.x_rows == g.rows && t.nnz == g.nnz && t.Y;
 }
 
-hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream_t s)
+hipError_t launch_full_backward(const SpmmCall &t, const SddmmCall &g, hipStream_t s)
 {
     const int n_chunks = (g.batch + 255) / 256;
     const int groups = (g.x_rows + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -3986,7 +3986,7 @@ hipError_t launch_full_backward(const SpmmArgs &t, const SddmmArgs &g, hipStream
 // 3000 x 16384 at 12 % 208 -> 200,
 // 8192^2 at 0.3 / 0.6 / 2 / 7 % 14.3 -> 13.5, 20.9 -> 19.6, 51 -> 49.3, 151 -> 162, 9106 x 9383 at 0.3 / 0.6 / 2 % 16.7 -> 15.8, 24.4 -> 25.3, 65 -> 71.6; batch 256 not slower up to 25 %.  With the update, which loads more: steps of 3000-3000-3000-10, batch 64, at 15 / 25 % 121 -> 122, 185 -> 197, of
 // 2000-2000-2000-10 at 25 % 97 -> 90.
-static bool backward_gathers_apart(int gs, int64_t waves, const SpmmArgs &t, bool update)
+static bool backward_gathers_apart(int gs, int64_t waves, const SpmmCall &t, bool update)
 {
     if (update && gs < 64 && waves > 2048 && t.nnz > 400ll * t.rows) return false;
     if (gs == 8) return waves <= 2048;
@@ -3999,7 +3999,7 @@ static bool backward_gathers_apart(int gs, int64_t waves, const SpmmArgs &t, boo
 // 8192^2 at 0.6 / 2 % 15.6 -> 15.2, 37.4 -> 37.5, 19.9 -> 19.7, 50.3 -> 49.0.  Not with rows of one chunk (3000 x 4000 at 0.3 %, 9 entries a row, batch 128 5.0 -> 5.4), nor with long ones, which lose
 // lines that the L1s would keep (2048 x 5500 at 25 % 67.7 -> 77.8, 98.5 -> 104; 9106 x 9383 at 6 %, batch 64 139 -> 158), nor with more waves than start at once (9106 x 9383 at 2 %, batch 128 65.0 -> 71.9,
 // at 0.3 % 16.1 -> 16.8; but 2048 x 5500 at 2 % 14.0 -> 12.1).
-static bool bwd_sixteens(int64_t waves, const SpmmArgs &t) { return waves <= 4096 && t.nnz > 20ll * t.rows && t.nnz <= 400ll * t.rows; }
+static bool bwd_sixteens(int64_t waves, const SpmmCall &t) { return waves <= 4096 && t.nnz > 20ll * t.rows && t.nnz <= 400ll * t.rows; }
 
 // Whether the pass with hot rows in LDS runs: where a tile's columns are on, there are mirror rows enough (a wave for
 // each four of them and tile) and long ones (8068 x 4944 at 0.6 %, 46 entries a mirror row, batch 762 46.4 -> 50.9 us;
@@ -4014,7 +4014,7 @@ static bool bwd_sixteens(int64_t waves, const SpmmArgs &t) { return waves <= 409
 // order of the walk, 1 us and 6 per million entries more (2450 training steps: of those that take the pass then one in
 // 150 is slower by 2 % or more).
 constexpr int64_t kHotTasks = 5000, kHotEntries = 45, kHotWork = 96ll << 20;
-static bool hot_pays(const SpmmArgs &t, float share, bool update)
+static bool hot_pays(const SpmmCall &t, float share, bool update)
 {
     const int64_t tiles = (static_cast<int64_t>(t.batch) + 63) / 64, sets = (static_cast<int64_t>(t.rows) + 3) / 4;
     if (t.batch < kHotFromBatch || t.batch * 20ll < tiles * 64 * 17 || sets * tiles < kHotTasks || t.nnz < (t.x_rows > 6144 ? 85ll : kHotEntries) * t.rows ||
@@ -4025,14 +4025,14 @@ static bool hot_pays(const SpmmArgs &t, float share, bool update)
     const double hot = (update ? 19 : 18) + nnz * ((update ? 17.8 : 11.8) + static_cast<double>(tiles) * (5.8 + (1. - share) * (4.1 + 1.7 * x))) + 1.1 * operand + 0.05e-3 * static_cast<double>(tiles) * t.rows;
     return hot < 0.98 * stream;
 }
-bool backward_hot_ok(const SpmmArgs &t, const SddmmArgs &g)
+bool backward_hot_ok(const SpmmCall &t, const SddmmCall &g)
 {
     if (!t.hot || !g.hot_values || t.XM || !g.partial || (t.batch + 63) / 64 > g.partial_tiles || g.partial_stride < t.nnz) return false;
     return hot_pays(t, t.hot->share, g.fused);
 }
 bool hot_rows_pay_somewhere(const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, float share)
 {
-    SpmmArgs t{};
+    SpmmCall t{};
     t.blocks = plan_t; t.rows = cols; t.x_rows = rows; t.nnz = nnz;
     // (asked of the fewest and the most columns that fill a number of tiles; beyond some thousand they all say the same)
     for (int32_t tiles = kHotFromBatch / 64, most = std::min((max_batch + 63) / 64, 256); tiles <= most; ++tiles)
@@ -4047,11 +4047,11 @@ hipError_t launch_backward_finish(BackwardFinish &f, hipStream_t s)
 {
     if (!f.waiting) return hipSuccess;
     f.waiting = false;
-    hipLaunchKernelGGL(backward_finish_kernel, dim3(f.n_entry_blocks + f.n_row_blocks), dim3(kEwBlock), 0, s, f.a, f.n_tiles, f.n_entry_blocks);
+    hipLaunchKernelGGL(backward_finish_kernel, dim3(f.n_entry_blocks + f.n_row_blocks), dim3(kEwBlock), 0, s, f.a, f.hot_at, f.n_tiles, f.n_entry_blocks);
     return hipGetLastError();
 }
 
-hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alone, hipStream_t s, BackwardFinish *later)
+hipError_t launch_backward_fused(const SpmmCall &t, const SddmmCall &g, bool alone, hipStream_t s, BackwardFinish *later)
 {
     BackwardArgs a{};
     a.blocks = t.blocks; a.indices = t.indices; a.values = t.values;
@@ -4069,8 +4069,8 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
     const bool one = n_tiles == 1 || (alone && backward_looped(t));
     const int64_t row_blocks = (static_cast<int64_t>(a.x_rows) + kBwdWaves - 1) / kBwdWaves;
     const int n_row_blocks = (a.db || (a.fused && a.bias)) ? static_cast<int>(row_blocks < 2048 ? row_blocks : 2048) : 0;
-    auto finish = [&](int tiles) {
-        BackwardFinish f{a, tiles, xcd_run_blocks(t.nnz), n_row_blocks, true};
+    auto finish = [&](int tiles, const int32_t *hot_at) {
+        BackwardFinish f{a, hot_at, tiles, xcd_run_blocks(t.nnz), n_row_blocks, true};
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || !later) return e != hipSuccess ? e : launch_backward_finish(f, s);
         *later = f;
@@ -4082,13 +4082,12 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         // one round of work-groups, two tiles at a time on an XCD, where an L2 holds both (5001 x 9001 at 2 %, batch 999, in two: 133 -> 144 us), else two (16384^2 at 1 %, batch 1024, in one: 438 -> 474)
         h.n_ranges = std::max(1, (t.x_rows * 512ll <= (3 << 20) ? 1 : 2) * 256 / h.n_tiles);
         h.per = (h.n_tiles * h.n_ranges + 7) / 8;
-        a.hot_values = g.hot_values;
         const bool refresh = alone && g.values;   // (backward_fused_refreshes: the call leaves it to this launch)
         hipLaunchKernelGGL(hot_values_kernel, dim3(xcd_run_blocks(t.nnz)), dim3(kEwBlock), 0, s, g.hot_values, refresh ? g.values : t.values, g.values_t, t.hot->at,
                            refresh ? t.hot->perm : nullptr, t.nnz);
-        hipLaunchKernelGGL(t.batch % 64 ? backward_hot_kernel<true> : backward_hot_kernel<false>, dim3(8u * h.per), dim3(kHotWaves * kWave), 0, s, a, h, *t.hot);
-        a.perm = t.hot->perm; a.hot_at = t.hot->at;
-        return finish(h.n_tiles);
+        hipLaunchKernelGGL(t.batch % 64 ? backward_hot_kernel<true> : backward_hot_kernel<false>, dim3(8u * h.per), dim3(kHotWaves * kWave), 0, s, a, h, *t.hot, g.hot_values);
+        a.perm = t.hot->perm;
+        return finish(h.n_tiles, t.hot->at);
     }
     const TileOrder order = tile_order(n_tiles, n_pack_blocks, tg, false, tiled_launch(t));
     const int64_t ids = one ? n_pack_blocks + n_row_blocks : tile_grid(order, n_tiles, n_pack_blocks);
@@ -4136,22 +4135,22 @@ hipError_t launch_backward_fused(const SpmmArgs &t, const SddmmArgs &g, bool alo
         default: go(std::integral_constant<int, 8>{}); break;
     }
     if (one) return hipGetLastError();
-    return finish(n_tiles);
+    return finish(n_tiles, nullptr);
 }
 
 // whether launch_spmm serves `a` by streaming (full matrix of few rows), where the softmax epilogue can ride along
-static bool spmm_full_rows_ok(const SpmmArgs &a)
+static bool spmm_full_rows_ok(const SpmmCall &a)
 {
     return a.batch > 4 && a.full_scratch && !a.XM && a.batch >= 64 && a.rows <= kFullMaxRows;
 }
-bool spmm_softmax_epilogue_ok(const SpmmArgs &a)
+bool spmm_softmax_epilogue_ok(const SpmmCall &a)
 {
     return a.rows > 0 && a.blocks.n_blocks > 0 && spmm_full_rows_ok(a) && !a.relu && !a.YM && a.ce_labels && a.ce_dZ && a.ce_loss_cols;
 }
 
 // log2 of the waves per row of spmv_rows_kernel, -1: not for this matrix.  It needs more entries than 8192 waves hold at 64
 // each, and no row that keeps its waves busy for more than 16 rounds.
-static int spmv_rows_split(const SpmmArgs &a)
+static int spmv_rows_split(const SpmmCall &a)
 {
     if (a.nnz < 8192 * kWave || !spmm_offsets_ok(a)) return -1;
     int lg = 0;
@@ -4159,17 +4158,17 @@ static int spmv_rows_split(const SpmmArgs &a)
     return (a.blocks.staged_longest_row >> lg) <= 16 * 4 * kWave ? lg : -1;
 }
 
-bool spmm_takes_strip(const SpmmArgs &a)
+bool spmm_takes_strip(const SpmmCall &a)
 {
     return a.rows > 0 && a.batch > 4 && a.blocks.n_blocks > 0 && !spmm_full_rows_ok(a) && !spmm_dense_rows_ok(a) && spmm_strip_ok(a);
 }
 
-hipError_t launch_strip_streams(const SpmmArgs *list, int n, hipStream_t s)
+hipError_t launch_strip_streams(const SpmmCall *list, int n, hipStream_t s)
 {
     StripStreams all{};
     unsigned most = 0;
     for (int k = 0; k < n; ++k) {
-        const SpmmArgs &a = list[k];
+        const SpmmCall &a = list[k];
         all.of[k] = StripStream{a.strips->segs, a.strips->cuts, a.indices, a.values, a.strip_stream, (a.rows + kStripSet - 1) / kStripSet,
                                 a.strips->blocks, a.strips->block_rows, a.x_rows, a.nnz};
         most = std::max(most, static_cast<unsigned>((all.of[k].sets * all.of[k].blocks + kStripStreamWaves - 1) / kStripStreamWaves));
@@ -4178,7 +4177,7 @@ hipError_t launch_strip_streams(const SpmmArgs *list, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
+hipError_t launch_spmm(const SpmmCall &a, hipStream_t s)
 {
     if (a.rows <= 0 || a.batch <= 0 || a.blocks.n_blocks <= 0) return hipSuccess;
     if (a.batch <= 4) {
@@ -4212,7 +4211,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         // the dense rows by matrix instructions, then the others as ever, told to leave these out
         const hipError_t e = launch_dense_rows(a, s);
         if (e != hipSuccess || a.split->rows.n == a.rows) return e;
-        SpmmArgs others = a;
+        SpmmCall others = a;
         others.blocks = a.split->others;
         others.split = nullptr;
         others.strips = nullptr;   // (its rows are all, the dense ones too)
@@ -4224,7 +4223,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
             const hipError_t e = launch_strip_streams(&a, 1, s);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(spmm_strip_kernel, dim3(8u * static_cast<unsigned>(g.per)), dim3(kStripWaves * kWave), 0, s, a, g, *a.strips);
+        hipLaunchKernelGGL(spmm_strip_kernel, dim3(8u * static_cast<unsigned>(g.per)), dim3(kStripWaves * kWave), 0, s, a, g, *a.strips, a.strip_stream);
         return hipGetLastError();
     }
     if (spmm_staged_ok(a)) {
@@ -4236,7 +4235,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         if (a.blocks.staged_partial) {
             // the short rows: packed where that path runs (inside column tiles), and nothing else in that grid;
             // otherwise whatever kernel the batch asks for, on the short rows' own partition
-            SpmmArgs rest = a;
+            SpmmCall rest = a;
             rest.blocks.n_huge_rows = 0;
             const int tg = spmm_tile_group(a);
             if (staged_rest_packed(a, tg)) {
@@ -4263,7 +4262,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
         if (sg != 0) {
             // Long rows inside column tiles (their gathers are most of the traffic and then hit in the L2s),
             // short rows outside (a pass over them per tile would cost more than their gathers): two launches.
-            SpmmArgs longs = a, rest = a;
+            SpmmCall longs = a, rest = a;
             longs.blocks.waves = a.blocks.long_waves;
             longs.blocks.n_blocks = a.blocks.n_long_blocks;
             longs.blocks.n_short = 0;
@@ -4303,7 +4302,7 @@ hipError_t launch_spmm(const SpmmArgs &a, hipStream_t s)
 }
 
 // Columns per tile of the column-tiled SDDMM, 0: one pass over the whole batch.
-int sddmm_tile_columns(const SddmmArgs &a)
+int sddmm_tile_columns(const SddmmCall &a)
 {
     if (!a.partial || a.skip_products || a.dense || !sddmm_offsets_ok(a)) return 0;  // (the finish pass does not know an entry's row)
     // the operand rows an entry gathers are named by its column index: the matrix's own partition
@@ -4320,14 +4319,14 @@ int sddmm_tile_columns(const SddmmArgs &a)
 // are many: not beyond 4096 rows (1 MiB in an L2) unless there are few entries, or half again as many as the gradient's at the most among eight tiles or more, whose last round has room.  Steps of 5400 networks of
 // two hidden layers, apart -> in one launch: where it is taken 1.012 times as fast, else 0.999 in the mean: 1108-1879-8144-10 at 3 %, batch 1024 230 -> 241 us, 5871-5373-4349-10, batch 492 274 -> 288,
 // 1134-7260-7945-10 at 1.2 %, batch 902 304 -> 320.
-static bool sddmm_takes_finish(const SddmmArgs &a, const BackwardArgs &f)
+static bool sddmm_takes_finish(const SddmmCall &a, const BackwardArgs &f)
 {
     if (a.rows <= 0 || a.batch <= 0 || a.blocks.n_blocks <= 0 || sddmm_sampled_ok(a) || sddmm_dense_rows_ok(a) || sddmm_full_ok(a) || sddmm_staged_ok(a)) return false;
     const int w = sddmm_tile_columns(a);
     return (w == 128 || w == 64) && (f.x_rows <= 4096 || f.nnz < 100'000 || (w == 128 && a.batch > 7 * 128 && f.nnz <= a.nnz + a.nnz / 2));
 }
 
-hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s, BackwardFinish *first)
+hipError_t launch_sddmm(const SddmmCall &a, hipStream_t s, BackwardFinish *first)
 {
     if (first && first->waiting && !sddmm_takes_finish(a, first->a)) {
         const hipError_t e = launch_backward_finish(*first, s);
@@ -4344,7 +4343,7 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s, BackwardFinish *first
         add_sampled_rows(rows, a);
         const hipError_t e = launch_sampled(rows, s);
         if (e != hipSuccess || a.split->rows.n == a.rows) return e;
-        SddmmArgs others = a;
+        SddmmCall others = a;
         others.blocks = a.split->others;
         others.split = nullptr;
         others.split_done = a.split;
@@ -4362,7 +4361,7 @@ hipError_t launch_sddmm(const SddmmArgs &a, hipStream_t s, BackwardFinish *first
         hipLaunchKernelGGL(sddmm_staged_kernel, dim3(n_tiles * a.blocks.staged_ranges), dim3(kStageWaves * kWave), 0, s, a, n_tiles);
         if (a.blocks.staged_partial) {
             // the rows the plan leaves out: the column-tiled SDDMM on their own partition, same tiles, same partial buffer
-            SddmmArgs rest = a;
+            SddmmCall rest = a;
             rest.blocks.waves = a.blocks.rest_waves;
             rest.blocks.n_blocks = a.blocks.n_rest_blocks;
             TiledLaunch like = tiled_launch(a);
