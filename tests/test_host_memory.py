@@ -327,6 +327,30 @@ def both_gradients_go_apart_where_that_is_faster(L):
         L.destroy()
 
 
+def both_gradients_go_apart_where_that_beats_hot_rows_in_lds(L):
+    """rows, columns, entries, batch, ranges of W's plan and of its mirror's; dense rows, their entries, rows and entries of the plan beside them; shares of the 1024 and of the 512 longest rows.  Power-law
+    matrices as measured, us, apart and with hot rows in LDS (one stream from the L2s takes longer than either)."""
+    for rows, cols, nnz, batch, ranges, dense, most, share, hot in (
+            (12085, 6193, 9677122, 656, (23, 23), (2602, 7015440, 9483, 2661682), 0.51, 0.33, False),     # 951 / 1329
+            (8782, 15534, 13505539, 768, (21, 42), (1384, 9356951, 7398, 4148588), 0.63, 0.47, False),    # 1449 / 1837
+            (8164, 11068, 10400338, 666, (23, 46), (1533, 7386461, 6631, 3013877), 0.62, 0.46, False),    # 1066 / 1255
+            (8119, 5813, 5177373, 450, (32, 32), (1443, 3648530, 6676, 1528843), 0.63, 0.47, False),      # 445 / 488
+            (4089, 5120, 2018199, 856, (18, 18), (625, 1392036, 3464, 626163), 0.78, 0.65, True),         # 304 / 273
+            (9349, 10144, 4580591, 1024, (32, 32), (651, 2874377, 8698, 1706214), 0.71, 0.58, True),      # 835 / 733
+            (9341, 4974, 2169781, 967, (32, 16), (628, 1357123, 8713, 812658), 0.71, 0.59, True),         # 423 / 354
+            (2128, 4636, 1253893, 901, (17, 17), (450, 906259, 1678, 347634), 0.88, 0.75, True)):         # 228 / 181
+        n_dense, dense_nnz, plan_rows, plan_nnz = dense
+        L.counts(0, n_blocks=600, n_dense=n_dense, dense_nnz=dense_nnz, longest_row=int(0.9 * cols), hot_nnz=int(most * nnz), hot_lds_nnz=int(share * nnz),
+                 staged_ranges=ranges[0], staged_rows=plan_rows, staged_nnz=plan_nnz)
+        L.counts(1, n_blocks=600, longest_row=2 * nnz // cols, hot_nnz=nnz // 8, staged_ranges=ranges[1], staged_rows=cols, staged_nnz=nnz)
+        assert L.create(rows, cols, nnz, batch) == 0
+        L.launched()
+        assert L.backward(batch) == 0
+        names = L.launched()
+        assert any("backward_hot_kernel" in k for k in names) == hot and any("spmm_staged_kernel" in k for k in names) != hot, (rows, cols, batch, names)
+        L.destroy()
+
+
 def a_grid_has_no_more_work_groups_than_a_launch_can(L):
     """The gradient in column tiles comes in quarters of the partition's work-groups: where these are too many for a grid, the rows go through all columns at once."""
     for n_blocks, tiled in ((30_000_000, True), (60_000_000, False)):
@@ -445,7 +469,7 @@ def strips_are_planned_where_a_batch_takes_them(L):
         L.destroy()
 
 
-CASES = [strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [both_gradients_go_apart_where_that_beats_hot_rows_in_lds, strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
