@@ -1019,7 +1019,21 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     }
     out->plan_t = plan_view(p.side[1].tables, R.plan[1], rows, nnz, R.plan[0].hot_nnz, mode);
     const float in_lds = nnz > 0 ? static_cast<float>(static_cast<double>(R.plan[0].hot_lds_nnz) / nnz) : 0.f;
-    if (asked == NERVA_PARTITION_BALANCED && hot_rows_pay_somewhere(out->plan_t, rows, cols, nnz, max_batch, in_lds) && reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
+    auto takes_hot_rows = [&] {
+        HotRows order;
+        order.share = in_lds;
+        SpmmCall t{};
+        t.blocks = out->plan_t; t.hot = &order; t.rows = cols; t.x_rows = rows; t.nnz = nnz;
+        SddmmCall g{};
+        g.blocks = out->plan; g.perm = m.perm; g.rows = rows; g.x_rows = cols; g.nnz = nnz;
+        g.partial_stride = round_up(nnz, 64) + round_up(rows, 64);
+        g.partial_tiles = static_cast<int32_t>(std::min<int64_t>(INT32_MAX, static_cast<int64_t>(kPartialMaxBytes / 4) / g.partial_stride));
+        if (B.has_table) g.table = reinterpret_cast<const uint2 *>(B.table);
+        g.split = B.split.rows.n > 0 ? &B.split : nullptr;
+        return hot_rows_pay_somewhere(t, g, max_batch);
+    };
+    // (the dense route has no use for it)
+    if (asked == NERVA_PARTITION_BALANCED && nnz > 0 && !takes_dense_route(l, nnz) && takes_hot_rows() && reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
         HotRows &v = out->hot;
         HIP_TRY(launch_hot_order(out->plan.rows_by_length, rows, B.indptr_t, m.indices_t, cols, m.perm, W + work_at[0], B.hot, B.hot + n64, B.hot + 2 * n64, p.side[1].tables.rows_by_length,
                                  reinterpret_cast<int4 *>(B.hot + 4 * n64), s));

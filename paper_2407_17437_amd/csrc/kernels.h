@@ -590,11 +590,11 @@ inline bool strip_wanted(int32_t rows, int32_t cols, int32_t nnz, int32_t max_ba
            strips_may_pay(rows, cols, nnz, max_batch, staged_ranges);
 }
 __host__ __device__ inline bool strip_even(int32_t longest_row, int32_t rows, int64_t nnz) { return static_cast<int64_t>(longest_row) * rows <= 3 * nnz; }
-// Whether both gradients with the hot rows of dZ in LDS (backward_hot_ok, which says where the lines lie) are worth it at a batch up to max_batch: the mirror then gets the order of HotRows.
-// plan_t: the mirror's; share: HotRows'.
+// Whether a call or a training step on up to max_batch columns takes the hot rows of dZ out of LDS (backward_hot_ok): the
+// mirror then gets the order of HotRows.  t, g: as these have them, but for batch, operands and room, with HotRows' share.
 constexpr int32_t kHotFromBatch = 192;
 inline int64_t hot_sets_size(int32_t rows) { return (static_cast<int64_t>(rows) + 255) / 256 * 256; }
-bool hot_rows_pay_somewhere(const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, float share);
+bool hot_rows_pay_somewhere(SpmmCall t, SddmmCall g, int32_t max_batch);
 // Ranges a staged plan over `rows` rows with `nnz` entries aims at, 0: such a plan would never be chosen.  (Host and
 // device; `cols`: operand rows.)
 __host__ __device__ inline int32_t staged_ranges_aim(int32_t rows, int32_t max_batch)

@@ -4041,16 +4041,20 @@ bool backward_hot_ok(const SpmmCall &t, const SddmmCall &g)
     if (!t.hot || !g.hot_values || t.XM || !g.partial || (t.batch + 63) / 64 > g.partial_tiles || g.partial_stride < t.nnz) return false;
     return hot_pays(t, t.hot->share, g.fused);
 }
-bool hot_rows_pay_somewhere(const RowBlocks &plan_t, int32_t rows, int32_t cols, int32_t nnz, int32_t max_batch, float share)
+bool hot_rows_pay_somewhere(SpmmCall t, SddmmCall g, int32_t max_batch)
 {
-    SpmmCall t{};
-    t.blocks = plan_t; t.rows = cols; t.x_rows = rows; t.nnz = nnz;
+    static float some;
+    t.X = g.dZ = g.partial = g.hot_values = &some;   // (asked whether they are there)
     // (asked of the fewest and the most columns that fill a number of tiles; beyond some thousand they all say the same)
     for (int32_t tiles = kHotFromBatch / 64, most = std::min((max_batch + 63) / 64, 256); tiles <= most; ++tiles)
-        for (const int32_t batch : {(tiles * 64 * 17 + 19) / 20, std::min(tiles * 64, max_batch)}) {
-            t.batch = batch;
-            if (batch <= max_batch && hot_pays(t, share, false)) return true;
-        }
+        for (const int32_t batch : {(tiles * 64 * 17 + 19) / 20, std::min(tiles * 64, max_batch)})
+            for (const bool alone : {true, false}) {
+                if (batch > max_batch) continue;
+                t.batch = g.batch = batch;
+                t.ldx = g.lddz = g.ldx = batch;
+                g.fused = !alone;
+                if (backward_hot_ok(t, g) && backward_fused_ok(t, g, alone)) return true;
+            }
     return false;
 }
 
