@@ -133,6 +133,18 @@ hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3, void **args, siz
     launched += name + "\n";
     if (grid.x == 0 || grid.x > 0x7FFFFFFFu) ++bad_grids;
     auto takes = [&](const char *type) { return name.find(type) != std::string::npos; };
+    // (what a kernel is given beside the arguments that many share)
+    if (takes("spmm_strip_kernel")) {
+        check(args[2], sizeof(Strips));
+        check(args[3], 8);
+    } else if (takes("strip_stream_kernel")) {
+        check(args[0], sizeof(StripStreams));
+    } else if (takes("backward_hot_kernel")) {
+        check(args[2], sizeof(HotRows));
+        check(args[3], 8);
+    } else if (takes("backward_finish_kernel")) {
+        check(args[1], 8);
+    }
     if (takes("8SpmmArgs")) {
         const SpmmArgs &a = *static_cast<const SpmmArgs *>(args[0]);
         check(&a, sizeof a);

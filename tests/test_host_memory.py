@@ -369,6 +369,40 @@ def an_order_of_hot_rows_is_made_where_a_call_takes_it(L):
         L.destroy()
 
 
+def a_failed_rebind_leaves_strips_and_hot_rows_in_place(L):
+    """As above, of patterns whose forward product runs in strips, or whose gradients keep hot rows in LDS, and which grow or shrink."""
+    def strips(nnz):
+        L.counts(0, n_blocks=600, longest_row=2 * nnz // 8192, hot_nnz=nnz // 8, hot_lds_nnz=nnz // 16, n_short=8192)
+        L.counts(1, n_blocks=600, longest_row=2 * nnz // 3072, hot_nnz=nnz // 3)
+        L.hip.fake_set_strips(int(nnz / 16 / 8 / 0.9) + 600, int(nnz / 16 / 0.9))
+
+    def hot(nnz):
+        L.counts(0, n_blocks=600, longest_row=3000, hot_nnz=int(0.76 * nnz), hot_lds_nnz=int(0.67 * nnz))
+        L.counts(1, n_blocks=600, longest_row=600, hot_nnz=nnz // 8)
+        L.hip.fake_set_strips(0, 0)
+
+    for rows, cols, counts, old, new, route in ((8192, 3072, strips, 342893, 500000, 1), (8192, 3072, strips, 500000, 342893, 1), (16384, 16384, hot, 2000000, 2684354, 2), (16384, 16384, hot, 2684354, 2000000, 2)):
+        for k in range(100):
+            counts(old)
+            assert L.create(rows, cols, old, 1024, relu=True) == 0
+            assert L.routes(1024) & route == route
+            counts(new)
+            L.hip.fake_fail_after(k)
+            rc = L.rebind(new)
+            L.hip.fake_fail_after(-1)
+            L.launched()
+            assert L.forward(1024) == 0 and L.backward(1024) == 0, L.lib.nerva_last_error()
+            assert L.hip.fake_bad_pointers() == 0, k
+            names = L.launched()
+            if rc != 0:   # (else it may have gone on without what there was no room for)
+                assert any(("spmm_strip_kernel", "backward_hot_kernel")[route - 1] in n for n in names), (k, names)
+            L.destroy()
+            assert rc in (0, -5)
+            if rc == 0 and k > 30:
+                break
+        assert 3 < k < 99
+
+
 def a_grid_has_no_more_work_groups_than_a_launch_can(L):
     """The gradient in column tiles comes in quarters of the partition's work-groups: where these are too many for a grid, the rows go through all columns at once."""
     for n_blocks, tiled in ((30_000_000, True), (60_000_000, False)):
@@ -487,7 +521,7 @@ def strips_are_planned_where_a_batch_takes_them(L):
         L.destroy()
 
 
-CASES = [an_order_of_hot_rows_is_made_where_a_call_takes_it, both_gradients_go_apart_where_that_beats_hot_rows_in_lds, strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [a_failed_rebind_leaves_strips_and_hot_rows_in_place, an_order_of_hot_rows_is_made_where_a_call_takes_it, both_gradients_go_apart_where_that_beats_hot_rows_in_lds, strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
