@@ -1033,7 +1033,8 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         return hot_rows_pay_somewhere(t, g, max_batch);
     };
     // (the dense route has no use for it)
-    if (asked == NERVA_PARTITION_BALANCED && nnz > 0 && !takes_dense_route(l, nnz) && takes_hot_rows() && reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
+    if (asked == NERVA_PARTITION_BALANCED && nnz > 0 && !takes_dense_route(l, nnz) && takes_hot_rows() &&
+        reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
         HotRows &v = out->hot;
         HIP_TRY(launch_hot_order(out->plan.rows_by_length, rows, B.indptr_t, m.indices_t, cols, m.perm, W + work_at[0], B.hot, B.hot + n64, B.hot + 2 * n64, p.side[1].tables.rows_by_length,
                                  reinterpret_cast<int4 *>(B.hot + 4 * n64), s));

@@ -107,14 +107,19 @@ constexpr int32_t kStageRangeFill = kStageRangeRows - 4;  // slots after which a
 constexpr int32_t kStageMinBatch = 128;  // narrower batches never take the staged product
 constexpr int32_t kStageTargetGroups = 256;  // work-groups wanted at max_batch (one per compute unit)
 constexpr float kStageMinReuse = 2.f;    // stored entries per staged operand row and work-group, at least
-constexpr int32_t kStageLongSegment = 10;       // mean entries per segment from which staging pays whatever the operand's size: products,
-constexpr int32_t kStageSegmentSomeWork = 8;    // products of so many of the plan's entries times columns (8.7 and 10 entries, in column tiles / staged, us: 8192^2 at 1.7 / 1.95 %, batch 256 / 512 / 1024
-constexpr int64_t kStageSomeWork = 324 << 20;   // 77 / 76, 136 / 99, 267 / 192 and 84 / 77, 152 / 104, 295 / 198; 4500^2 and 6000^2 at 1.75 %, batch 512 43 / 47, 61 / 64, batch 1024 65 / 59, 119 / 92; of 44 more
-                                                // staged takes 0.59 to 1.01 of the time above the line and 0.81 to 1.52 below it, by shape and not by work; below 8 no plan is made but for operands of 48 MiB),
-constexpr int32_t kStageLongSegmentSddmm = 20;  // ... the SDDMM, which has its second pass to pay for as well,
-constexpr int32_t kStageSegmentMuchWork = 10;   // ... and the SDDMM of so many (8192^2 at 1.95 / 2.5 / 3.5 %, batch 256 76 / 91 / 135 -> 86 / 97 / 116, batch 512
-constexpr int64_t kStageMuchWork = 420 << 20;   // 143 / 173 / 254 -> 128 / 147 / 177, batch 1024 271 / 328 / 477 -> 251 / 288 / 338; 5000^2, batch 512 54 / 69 / 90 -> 61 / 68 / 81; 12000^2 at 2.5 %, batch 256 / 1024 233 / 853 -> 177 / 529;
-                                                // of 58 more 0.67 to 1.04 above the line, 0.81 to 1.53 below)
+// Mean entries per segment from which staging pays whatever the operand's size.  Products: kStageLongSegment, kStageSegmentSomeWork from so much work
+// (the plan's entries times columns) on: 8.7 and 10 entries, in column tiles / staged, us: 8192^2 at 1.7 / 1.95 %, batch 256 / 512 / 1024 77 / 76, 136 / 99,
+// 267 / 192 and 84 / 77, 152 / 104, 295 / 198; 4500^2 and 6000^2 at 1.75 %, batch 512 43 / 47, 61 / 64, batch 1024 65 / 59, 119 / 92; of 44 more staged takes 0.59
+// to 1.01 of the time above the line and 0.81 to 1.52 below it, by shape and not by work; below 8 no plan is made but for operands of 48 MiB.
+constexpr int32_t kStageLongSegment = 10;
+constexpr int32_t kStageSegmentSomeWork = 8;
+constexpr int64_t kStageSomeWork = 324 << 20;
+// The SDDMM, which has its second pass to pay for as well, and from so much work on: 8192^2 at 1.95 / 2.5 / 3.5 %, batch 256 76 / 91 / 135 -> 86 / 97 / 116, batch
+// 512 143 / 173 / 254 -> 128 / 147 / 177, batch 1024 271 / 328 / 477 -> 251 / 288 / 338; 5000^2, batch 512 54 / 69 / 90 -> 61 / 68 / 81; 12000^2 at 2.5 %, batch 256 /
+// 1024 233 / 853 -> 177 / 529; of 58 more 0.67 to 1.04 above the line, 0.81 to 1.53 below.
+constexpr int32_t kStageLongSegmentSddmm = 20;
+constexpr int32_t kStageSegmentMuchWork = 10;
+constexpr int64_t kStageMuchWork = 420 << 20;
 constexpr int32_t kStageSegmentBesideDense = 8;   // ... and the SDDMM of the rows beside dense ones (DenseSplit), from batch 512 on: power-law 16384^2 at 3 / 10 %,
                                                   // batch 1024: 1249 -> 932 and 3405 -> 2265 us; at batch 256 4096^2 loses (55 -> 84)
 constexpr int64_t kStageBigOperand = 48ll << 20;  // operand bytes no set of L2s holds: staging pays for shorter segments,
@@ -570,13 +575,15 @@ struct PlanArgs {
 };
 hipError_t launch_bind(const MirrorArgs &m, const PlanArgs &p, hipStream_t s);
 // place: scratch, [x_rows + rows]; sets: room for hot_sets_size(rows)
-hipError_t launch_hot_order(const int4 *rows_by_length, int32_t x_rows, const int32_t *indptr_t, const int32_t *indices_t, int32_t rows, const int32_t *perm, int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, const int4 *mirror_rows, int4 *sets,
-                            hipStream_t s);
+hipError_t launch_hot_order(const int4 *rows_by_length, int32_t x_rows, const int32_t *indptr_t, const int32_t *indices_t, int32_t rows, const int32_t *perm,
+                            int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, const int4 *mirror_rows, int4 *sets, hipStream_t s);
 hipError_t launch_plan(const PlanArgs &p, int sides, hipStream_t s);   // its last part alone: the partitions of W, or of W and its mirror
 
-// Whether the product in strips can run (256 operand rows travel at a time), and whether a matrix is looked at for a plan: some work, segments neither so short that a set's differ
-// too much nor so long that the staged product, whose gathers are wider, is as fast; and by the estimates that calls ask (spmm_strip_ok) strips may be the shorter way at a batch up to max_batch.  Before the plan is made
-// these are of the best that it can come to (strips_may_pay), and of what has come out before its stream gets room.  Rows of different lengths have no use for it: a wave would run as long as the longest.
+// Whether the product in strips can run (256 operand rows travel at a time), and whether a matrix is looked at for a plan: some work, segments
+// neither so short that a set's differ too much nor so long that the staged product, whose gathers are wider, is as fast; and by the estimates that
+// calls ask (spmm_strip_ok) strips may be the shorter way at a batch up to max_batch.  Before the plan is made these are of the best that it can come
+// to (strips_may_pay), and of what has come out before its stream gets room.  Rows of different lengths have no use for it: a wave would run as long
+// as the longest.
 __host__ __device__ inline bool strip_possible(int32_t rows, int32_t cols, int64_t nnz, int32_t max_batch)
 {
     return max_batch > kStripFromBatch && cols >= 256 && strip_blocks_of(cols) <= kStripMaxBlocks && nnz > 0 && nnz < (1 << 30) && static_cast<int64_t>(rows) * strip_blocks_of(cols) <= (1 << 28);
@@ -636,9 +643,10 @@ __host__ __device__ inline int32_t staged_range_bound(int32_t rows, int32_t cols
     const int64_t bound = want + (rows + 96 * want) / kStageRangeFill + 2;
     return bound * ((cols + kStageRows - 1) / kStageRows + 1) * kStageRangeRows > (1ll << 28) ? 0 : static_cast<int32_t>(bound);
 }
-// Whether the listed rows are worth a route of their own at max_batch columns (calls ask again: dense_rows_product_ok).  Without -> with it on the fp32 units, forward product: power-law 4096^2 at 5 % (297 rows,
-// 0.53 M entries) at batch 256 / 512 / 1024: 48 -> 50, 81 -> 77, 129 -> 120 us; 8192 x 1024 at 10 %: 35 -> 36, 87 -> 51, 109 -> 82.
-// Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even with the fp32 units at 30 % (324 us; 20 %: 235 -> 326).
+// Whether the listed rows are worth a route of their own at max_batch columns (calls ask again: dense_rows_product_ok).  Without -> with it on the
+// fp32 units, forward product: power-law 4096^2 at 5 % (297 rows, 0.53 M entries) at batch 256 / 512 / 1024: 48 -> 50, 81 -> 77, 129 -> 120 us; 8192
+// x 1024 at 10 %: 35 -> 36, 87 -> 51, 109 -> 82.  Rows of like length are cheaper to gather for: uniform 4096^2 at batch 1024 breaks even with the
+// fp32 units at 30 % (324 us; 20 %: 235 -> 326).
 __host__ __device__ inline bool dense_rows_pay(int32_t n_dense, int64_t dense_nnz, int64_t nnz, int32_t cols, int32_t max_batch)
 {
     return n_dense >= kDenseRowsMin && dense_nnz * 8 >= nnz && dense_nnz * 10 >= static_cast<int64_t>(n_dense) * cols * 3 &&

@@ -840,30 +840,25 @@ __global__ __launch_bounds__(kBlock) void full_rows_finish_softmax_kernel(const 
 }
 
 // ---- staged product ----------------------------------------------------------------------
-// For wide batches and matrices with many entries per operand row the gathers are served from
-// LDS instead of the L2, and the results stay in registers until they are complete.  A
-// work-group of 16 waves owns a range of at most kStageRangeRows rows and kStageCols columns of
-// the batch; a row of 16 lanes owns up to kStageJ of those rows, a float4 of the batch per lane
-// and row.  The work-group walks the column blocks of the matrix in order: it copies the
-// block's kStageRows operand rows (128 KiB) into LDS, then every lane row serves, out of that
-// copy, the segment (row, block) of each of its rows.  A segment's (column, weight) pairs are
-// loaded one per lane, two segments ahead, and reach the other lanes of the row through DPP row
-// broadcasts, so the only LDS traffic is the gather itself.  The next block's operand rows travel to registers
-// while a block is served.  Bias, ReLU and the output mask are
-// applied when the rows are stored, once, after the last block.
-// What bounds it: the latency of short runs of LDS gathers at four waves a SIMD (vector ALUs 65 % busy, LDS 45 %; a loop of nothing but whole chunks runs
-// 1.5 times as fast), not either pipe.  Segments, masks and offsets worked out once per block and not per use, the rows brought ahead, no wait for memory among
-// the gathers, the weight's move in the multiply-add: 16384^2 power-law rows at 10 %, batch 1024, under the profiler 1087 -> 745 us (10.3 -> 6.5 vector instructions a gather; among other passes it takes 640 to 680);
-// forward products of uniform 8192^2 at 5 %, batch 1024, 374 -> 278, 16384^2 at 2 %, batch 512, 448 -> 334, 5000 x 7000 at 8 %, batch 511, 146 -> 115.
-// The waves of a SIMD take turns by age, so that the oldest were through a block while the youngest, alone, could not fill the LDS pipe: their priorities fall as they go through their slots, and who is behind
-// goes first.  Power-law 16384^2 at 10 %, batch 1024, dense rows included, 1311 -> 1243, uniform at 10 % 1780 -> 1650; 8192^2 at 5 % 291 -> 270; weight gradients of 16384^2 at 10 / 2 % 2571 -> 2483, 827 -> 798, 5000 x 7000 at 8 %,
-// batch 511, 153 -> 142.
-// (48 KB of code, the gradient's 56, the instruction cache 64.  Two registers are stored before the block loop and reloaded after it; with a mask four, two of them reloaded once a block.)
-// Slots dealt to the waves there and back change nothing, two runs of 8 gathers made one of 16 neither.  A row marked kStageQuad is
-// shared by the four lane rows of a wave, a quarter of each segment each, and their four results
-// are added in a fixed order before the store.  Every output element is summed in one order.
-// With a partial plan (RowBlocks::staged_partial) the kernel serves the long rows only and a
-// second launch, the packed kernel, the others.
+// For wide batches and matrices with many entries per operand row the gathers are served from LDS instead of the L2, and the results stay in
+// registers until they are complete.  A work-group of 16 waves owns a range of at most kStageRangeRows rows and kStageCols columns of the batch; a
+// row of 16 lanes owns up to kStageJ of those rows, a float4 of the batch per lane and row.  The work-group walks the column blocks of the matrix in
+// order: it copies the block's kStageRows operand rows (128 KiB) into LDS, then every lane row serves, out of that copy, the segment (row, block) of
+// each of its rows.  A segment's (column, weight) pairs are loaded one per lane, two segments ahead, and reach the other lanes of the row through DPP
+// row broadcasts, so the only LDS traffic is the gather itself.  The next block's operand rows travel to registers while a block is served.  Bias,
+// ReLU and the output mask are applied when the rows are stored, once, after the last block.  What bounds it: the latency of short runs of LDS
+// gathers at four waves a SIMD (vector ALUs 65 % busy, LDS 45 %; a loop of nothing but whole chunks runs 1.5 times as fast), not either pipe.
+// Segments, masks and offsets worked out once per block and not per use, the rows brought ahead, no wait for memory among the gathers, the weight's
+// move in the multiply-add: 16384^2 power-law rows at 10 %, batch 1024, under the profiler 1087 -> 745 us (10.3 -> 6.5 vector instructions a gather;
+// among other passes it takes 640 to 680); forward products of uniform 8192^2 at 5 %, batch 1024, 374 -> 278, 16384^2 at 2 %, batch 512, 448 -> 334,
+// 5000 x 7000 at 8 %, batch 511, 146 -> 115.  The waves of a SIMD take turns by age, so that the oldest were through a block while the youngest,
+// alone, could not fill the LDS pipe: their priorities fall as they go through their slots, and who is behind goes first.  Power-law 16384^2 at 10 %,
+// batch 1024, dense rows included, 1311 -> 1243, uniform at 10 % 1780 -> 1650; 8192^2 at 5 % 291 -> 270; weight gradients of 16384^2 at 10 / 2 % 2571
+// -> 2483, 827 -> 798, 5000 x 7000 at 8 %, batch 511, 153 -> 142.  (48 KB of code, the gradient's 56, the instruction cache 64.  Two registers are
+// stored before the block loop and reloaded after it; with a mask four, two of them reloaded once a block.) Slots dealt to the waves there and back
+// change nothing, two runs of 8 gathers made one of 16 neither.  A row marked kStageQuad is shared by the four lane rows of a wave, a quarter of each
+// segment each, and their four results are added in a fixed order before the store.  Every output element is summed in one order.  With a partial
+// plan (RowBlocks::staged_partial) the kernel serves the long rows only and a second launch, the packed kernel, the others.
 constexpr int kStageWaves = kWavesPerBlock;
 // LDS byte offset of a zero-filled row behind the staged block: where a lane with no entry of its own
 // gathers from, so that it multiplies its weight 0 with 0 and not with an operand row that the
@@ -974,7 +969,8 @@ __device__ __forceinline__ StagedSegments staged_segments(int e_lo, int e_hi, bo
     return StagedSegments{static_cast<uint32_t>(p0) * UNIT, len * 4, most};
 }
 
-// MANY: 2^30 entries or more, which 32-bit byte offsets do not reach; they are counted instead.  (65536 x 131072 at 12.5 %, batch 128, forward / transposed, with the mirror's values: 8.5 / 29 ms, gathered from memory 70 / 72.)
+// MANY: 2^30 entries or more, which 32-bit byte offsets do not reach; they are counted instead.  (65536 x 131072 at 12.5 %, batch 128, forward /
+// transposed, with the mirror's values: 8.5 / 29 ms, gathered from memory 70 / 72.)
 template <bool XMASK, bool MANY>
 __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const SpmmArgs a, const int n_tiles)
 {
@@ -1128,15 +1124,18 @@ __global__ __launch_bounds__(kStageWaves * kWave) void spmm_staged_kernel(const 
 }
 
 // ---- product out of LDS in strips of 16 columns ------------------------------------------------------
-// The staged product in narrower tiles, for even rows of some 20 to some hundred entries a block at wide batches: a strip of kStripCols columns leaves room for kStripRows operand rows at a time
-// (128 KiB), four times as many as there, so that segments are four times as long and the operand is copied by a quarter of the work-groups.  A quad of lanes serves a row (four columns a lane),
-// a wave a set of sixteen rows, and an entry reaches the lanes of its quad by DPP quad_perm.  What all strips of a product have in common is done once, by strip_stream_kernel: it writes every entry
-// as the LDS offset of its operand row and its weight, in the order in which the waves take them, segments as long as the longest of the set, so that the product has nothing
-// to look up and nothing to mask (with its entries as they are stored, masked by every strip, 80 vector instructions a chunk: 371 us for the first matrix below, 92 for the second).
-// What bounds it: LDS and vector ALUs together, 4.2 ns a gather (62 TB/s; rows of 64 bytes meet in a bank group one time in four), of which 0.7 to 0.97 carry an entry (strip_plan in structure.hip);
-// around them a launch, 4.4 us until the first block is there, and 1 to 3 us a block for the last wave of it: the waves' priorities fall as they go through their sets, so that who is behind goes first (270 -> 257,
-// 62 -> 58).  Results are stored as the last block completes them, under the gathers of the sets that follow (49 -> 47).  Forward products at batch 1024, stream included, gathered from the L2s (staged: *) -> in
-// strips: 16384^2 at 1 % 456* -> 245, at 0.3 % 198 -> 133; 8192^2 at 0.74 % 93 -> 58; 8192 x 3072 at 1.4 % 59 -> 41; 5818 x 7889 at 1.6 %, batch 806 131* -> 63.
+// The staged product in narrower tiles, for even rows of some 20 to some hundred entries a block at wide batches: a strip of kStripCols columns
+// leaves room for kStripRows operand rows at a time (128 KiB), four times as many as there, so that segments are four times as long and the operand
+// is copied by a quarter of the work-groups.  A quad of lanes serves a row (four columns a lane), a wave a set of sixteen rows, and an entry reaches
+// the lanes of its quad by DPP quad_perm.  What all strips of a product have in common is done once, by strip_stream_kernel: it writes every entry as
+// the LDS offset of its operand row and its weight, in the order in which the waves take them, segments as long as the longest of the set, so that
+// the product has nothing to look up and nothing to mask (with its entries as they are stored, masked by every strip, 80 vector instructions a chunk:
+// 371 us for the first matrix below, 92 for the second).  What bounds it: LDS and vector ALUs together, 4.2 ns a gather (62 TB/s; rows of 64 bytes
+// meet in a bank group one time in four), of which 0.7 to 0.97 carry an entry (strip_plan in structure.hip); around them a launch, 4.4 us until the
+// first block is there, and 1 to 3 us a block for the last wave of it: the waves' priorities fall as they go through their sets, so that who is
+// behind goes first (270 -> 257, 62 -> 58).  Results are stored as the last block completes them, under the gathers of the sets that follow (49 ->
+// 47).  Forward products at batch 1024, stream included, gathered from the L2s (staged: *) -> in strips: 16384^2 at 1 % 456* -> 245, at 0.3 % 198 ->
+// 133; 8192^2 at 0.74 % 93 -> 58; 8192 x 3072 at 1.4 % 59 -> 41; 5818 x 7889 at 1.6 %, batch 806 131* -> 63.
 constexpr int kStripJ = 8, kStripWaves = kWavesPerBlock;
 constexpr int kStripZeroRow = kStripRows * kStripCols * 4;   // as kStageZeroRow
 static_assert(kStripCols * 4 == 1 << 6 && kStripSet * 4 == kWave && kStripChunk == 8, "");
@@ -1512,12 +1511,12 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a)
     sddmm_body<G, NV, SPARE>(a, blockIdx.x);
 }
 
-// Column-tiled SDDMM for operands X that no L2 holds: tile t covers columns [t*W, t*W + W), W =
-// G*4*NV; a work-group computes the partial products of its rows over one tile and stores them (and the partial row
-// sums of dZ) in the tile's slice of the partial buffer.  Tiles go to the XCDs as in spmm_tiled_kernel, so that an operand
-// tile stays in one L2 while every entry gathers from it.
-// In work-groups of four waves, a quarter of one of the partition's (nothing is shared among them; see spmm_packed_only_kernel): of 16 / of 4 waves, weight gradients of 12000 x 5000 power-law at 0.5 %,
-// batch 300 / 450 / 700 30.0 / 30.4, 52.5 / 47.3, 74.8 / 66.2 us; 5000^2 at 1.2 % 28.0 / 28.0, 40.1 / 37.0, 56.0 / 51.1; 8192 x 3072 at 1.3 %, batch 700 / 1024 56.7 / 53.8, 68.3 / 67.1.
+// Column-tiled SDDMM for operands X that no L2 holds: tile t covers columns [t*W, t*W + W), W = G*4*NV; a work-group computes the partial products of
+// its rows over one tile and stores them (and the partial row sums of dZ) in the tile's slice of the partial buffer.  Tiles go to the XCDs as in
+// spmm_tiled_kernel, so that an operand tile stays in one L2 while every entry gathers from it.  In work-groups of four waves, a quarter of one of
+// the partition's (nothing is shared among them; see spmm_packed_only_kernel): of 16 / of 4 waves, weight gradients of 12000 x 5000 power-law at 0.5
+// %, batch 300 / 450 / 700 30.0 / 30.4, 52.5 / 47.3, 74.8 / 66.2 us; 5000^2 at 1.2 % 28.0 / 28.0, 40.1 / 37.0, 56.0 / 51.1; 8192 x 3072 at 1.3 %,
+// batch 700 / 1024 56.7 / 53.8, 68.3 / 67.1.
 constexpr int kSddmmWaves = 4, kSddmmParts = kWavesPerBlock / kSddmmWaves;
 template <int G, int NV, bool SPARE>
 __device__ __forceinline__ void sddmm_tile(const SddmmArgs &a, int n_tiles, TileOrder order, uint32_t id)
@@ -2213,7 +2212,8 @@ __device__ __forceinline__ void backward_finish(const BackwardArgs &a, const int
         for_runs_of_xcds(a.nnz, n_entry_blocks, [&](int64_t q) {
             const int p = a.perm[q];
             float g = 0.f;
-            for (int t = 0; t < n_tiles; t += 8) {  // eight loads in flight, added in pairs: sixteen slices are then no further off than eight one after the other (8.7e-8 and 9.2e-8; one after the other 1.0e-7)
+            // (eight loads in flight, added in pairs: sixteen slices are then no further off than eight one after the other, 8.7e-8 and 9.2e-8; one after the other 1.0e-7)
+            for (int t = 0; t < n_tiles; t += 8) {
                 float v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = t + u < n_tiles ? a.partial[static_cast<int64_t>(t + u) * a.partial_stride + q] : 0.f;   // (uniform)
@@ -2243,8 +2243,9 @@ __global__ __launch_bounds__(kEwBlock) void backward_finish_kernel(const Backwar
 // work-groups (one to an XCD) are the finish pass's.  Wide MLP 322 -> 318 us a step (21 + 64 in turn, 83 together: the second pass's scattered lines take the same L2 requests as the gathers;
 // at twice to eight times the rate, or first of all, 305-310 where this order gives 303).
 template <int NV, bool SPARE>
-__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void sddmm_tiled_finish_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order, const BackwardArgs f, const int32_t *const hot_at,
-                                                                                                                         const int f_tiles, const int n_entry_blocks, const int n_finish, const int every)
+__global__ __launch_bounds__(kSddmmWaves * kWave) __attribute__((amdgpu_waves_per_eu(8)))
+void sddmm_tiled_finish_kernel(const SddmmArgs a, const int n_tiles, const TileOrder order, const BackwardArgs f, const int32_t *const hot_at, const int f_tiles,
+                               const int n_entry_blocks, const int n_finish, const int every)
 {
     static_assert(kSddmmWaves * kWave == kEwBlock, "");
     const int eight = blockIdx.x >> 3, turn = eight / every, groups = (n_finish + 7) / 8;
@@ -2311,7 +2312,8 @@ __device__ __forceinline__ float cold_use(float4 (&x)[N], float w, const float4 
     return sum;
 }
 
-// The mirror's values in the hot rows' order, out of the mirror, or, with perm (the CSR position of each), out of values[], from which the mirror's are brought up to date as well (gather_kernel's work).
+// The mirror's values in the hot rows' order, out of the mirror, or, with perm (the CSR position of each), out of values[], from which the mirror's
+// are brought up to date as well (gather_kernel's work).
 __global__ __launch_bounds__(kEwBlock) void hot_values_kernel(float *out, const float *values, float *values_t, const int32_t *at, const int32_t *perm, const int64_t n)
 {
     for_runs_of_xcds(n, gridDim.x, [&](int64_t k) {
@@ -2468,7 +2470,8 @@ __global__ __launch_bounds__(kHotWaves * kWave) void backward_hot_kernel(const B
         cold_now = cold_first;
         d_next = d_after;
         if (row < 0 || !on) continue;
-        float4 y = len > 0 ? make_float4(acc.x + acc_cold.x, acc.y + acc_cold.y, acc.z + acc_cold.z, acc.w + acc_cold.w) : make_float4(0.f, 0.f, 0.f, 0.f);   // (an empty row gathered, with weight 0, from row 0 of dZ)
+        // (an empty row gathered, with weight 0, from row 0 of dZ)
+        float4 y = len > 0 ? make_float4(acc.x + acc_cold.x, acc.y + acc_cold.y, acc.z + acc_cold.z, acc.w + acc_cold.w) : make_float4(0.f, 0.f, 0.f, 0.f);
         if (a.mask) y = keep_where_positive(y, mask_now);
         float *out = a.dX + static_cast<int64_t>(row) * a.lddx + col;
         if (!SPARE || col == own_col) {
@@ -3353,34 +3356,36 @@ bool staged_pays(const RowBlocks &blocks, int32_t x_rows, int32_t batch, int32_t
     if (groups < (blocks.staged_partial ? kStageTargetGroups / 2 : kStageTargetGroups * 3 / 4)) return false;
     if (static_cast<double>(nnz) < static_cast<double>(kStageMinReuse) * blocks.staged_ranges * x_rows) return false;
     if (static_cast<int64_t>(blocks.staged_longest_share) * 4096 > nnz * n_tiles) return false;
-    // An operand beyond the L2s, evenly used, on rows of similar length: shorter segments already pay, because the other
-    // kernels' gathers partly go to memory there (a few hot operand rows that take most gathers would stay cached on
-    // the other paths; on a power-law matrix most (row, block) pairs hold one entry or none and cost a visit all the
-    // same).  16384^2 uniform matrices at batch 1024, column-tiled -> staged, us: products at 0.6 / 0.7 / 0.79 / 1 / 2 % (3.1, 3.6, 4.0, 5.1 and 10.2 entries per segment)
-    // 345 -> 424, 414 -> 429, 525 -> 437, 662 -> 458, 1331 -> 598, SDDMM 512 -> 500, 594 -> 521, 666 -> 572, 834 -> 680, 1656 -> 805; 44 others of 12300 columns and more, batch 768 and more: 0.88 to 1.06
-    // below 4 entries, 0.50 to 0.92 from there on.
+    // An operand beyond the L2s, evenly used, on rows of similar length: shorter segments already pay, because the other kernels' gathers partly go
+    // to memory there (a few hot operand rows that take most gathers would stay cached on the other paths; on a power-law matrix most (row, block)
+    // pairs hold one entry or none and cost a visit all the same).  16384^2 uniform matrices at batch 1024, column-tiled -> staged, us: products at
+    // 0.6 / 0.7 / 0.79 / 1 / 2 % (3.1, 3.6, 4.0, 5.1 and 10.2 entries per segment) 345 -> 424, 414 -> 429, 525 -> 437, 662 -> 458, 1331 -> 598, SDDMM
+    // 512 -> 500, 594 -> 521, 666 -> 572, 834 -> 680, 1656 -> 805; 44 others of 12300 columns and more, batch 768 and more: 0.88 to 1.06 below 4
+    // entries, 0.50 to 0.92 from there on.
     const bool big_operand = static_cast<int64_t>(x_rows) * batch * 4 >= kStageBigOperand && blocks.hot_share < 0.5f &&
                              static_cast<int64_t>(blocks.staged_longest_row) * rows <= 4 * nnz;
     const int64_t segment = big_operand ? std::min(long_segment, kStageSegmentBigOperand) : long_segment;
     return nnz >= segment * rows * blocks.staged_cblocks;
 }
 
-// Entries times columns for the rules of shorter segments: of the rows that the plan covers, which beside dense rows (DenseSplit) or in a plan of the long rows are a part of the matrix
-// (weight gradient of 5000^2 power-law at 10 %, batch 256, 640 M in all, 186 M staged: 78 us in column tiles, 103 staged), and none where copying the operand weighs
-// too much beside them (column tiles / staged, entries per copied row: products of 7278 x 12626 and 8772 x 13004, batch 256 97 / 102 us (2.2), 101 / 106 (2.3), 6024 x 14996, batch 384 171 / 125 (2.6);
-// gradients of 5901 x 11786, batch 192 93 / 104 (2.3), 4665 x 10700, batch 320 100 / 97 (2.6)).
+// Entries times columns for the rules of shorter segments: of the rows that the plan covers, which beside dense rows (DenseSplit) or in a plan of the
+// long rows are a part of the matrix (weight gradient of 5000^2 power-law at 10 %, batch 256, 640 M in all, 186 M staged: 78 us in column tiles, 103
+// staged), and none where copying the operand weighs too much beside them (column tiles / staged, entries per copied row: products of 7278 x 12626
+// and 8772 x 13004, batch 256 97 / 102 us (2.2), 101 / 106 (2.3), 6024 x 14996, batch 384 171 / 125 (2.6); gradients of 5901 x 11786, batch 192 93 /
+// 104 (2.3), 4665 x 10700, batch 320 100 / 97 (2.6)).
 static int64_t staged_work(const RowBlocks &blocks, int32_t x_rows, int32_t batch)
 {
     return blocks.staged_nnz * 2ll >= 5ll * blocks.staged_ranges * x_rows ? static_cast<int64_t>(blocks.staged_nnz) * batch : 0;
 }
 
-// Short even rows in 64-column tiles for the sake of the packed kernel and its small work-groups, where the rule of the tiles (tile_columns) leaves the operand whole: one beyond an
-// L2 whose rows are gathered a dozen times or more (and not so often that it stays in cache), tiles hardly empty.  Uniform rows, whole -> in tiles, us: 15997 x 15191 at 0.35 %, batch 372 126 -> 79;
-// 3894 x 6816 at 0.6 %, batch 227 15.9 -> 11.8; 16384^2 at 0.3 %, batch 300 103 -> 61; 10442 x 13851 at 0.37 %, batch 164 38.8 -> 27.9.  But tiles a fifth empty or more: 10681 x 8704 at 0.8 %, batch 134
-// 36.5 -> 42.3, 11466 x 5888 at 0.5 %, batch 263 30.2 -> 34.0; operands near an L2: 4545 x 5628 at 0.7 %, batch 189 13.1 -> 14.1; often gathered: 16000 x 5000 at 0.8 %, batch 200 29.0 -> 31.2,
-// 3182 x 2692 at 1.9 %, batch 580 25.7 -> 28.3; rarely: 3428 x 12999 at 0.33 %, batch 290 25.3 -> 26.7.
-// (More work than kFusedMinWork whatever the shape: in a training step such a transposed product shares its gathers, or both pipelines follow the chain's order (chain_shape_ok), and it is never
-// in another launch's grid, which would add in another order.)
+// Short even rows in 64-column tiles for the sake of the packed kernel and its small work-groups, where the rule of the tiles (tile_columns) leaves
+// the operand whole: one beyond an L2 whose rows are gathered a dozen times or more (and not so often that it stays in cache), tiles hardly empty.
+// Uniform rows, whole -> in tiles, us: 15997 x 15191 at 0.35 %, batch 372 126 -> 79; 3894 x 6816 at 0.6 %, batch 227 15.9 -> 11.8; 16384^2 at 0.3 %,
+// batch 300 103 -> 61; 10442 x 13851 at 0.37 %, batch 164 38.8 -> 27.9.  But tiles a fifth empty or more: 10681 x 8704 at 0.8 %, batch 134 36.5 ->
+// 42.3, 11466 x 5888 at 0.5 %, batch 263 30.2 -> 34.0; operands near an L2: 4545 x 5628 at 0.7 %, batch 189 13.1 -> 14.1; often gathered: 16000 x
+// 5000 at 0.8 %, batch 200 29.0 -> 31.2, 3182 x 2692 at 1.9 %, batch 580 25.7 -> 28.3; rarely: 3428 x 12999 at 0.33 %, batch 290 25.3 -> 26.7.  (More
+// work than kFusedMinWork whatever the shape: in a training step such a transposed product shares its gathers, or both pipelines follow the chain's
+// order (chain_shape_ok), and it is never in another launch's grid, which would add in another order.)
 constexpr int64_t kFusedMinWork = 16 << 20;        // (backward_fused_ok)
 constexpr int64_t kPackTilesOperand = 21ll << 18;  // operand bytes
 constexpr int64_t kPackTilesGathers = 13;          // entries per operand row
@@ -3420,9 +3425,10 @@ int spmm_split_group(const SpmmCall &a)
 }
 
 bool spmm_staged_ok(const SpmmCall &a);
-// The product in strips, us, with the ranges that make it shortest: rounds of 256 work-groups (one fits a compute unit), each the steps that its LDS serves, the sets that a wave takes one after the
-// other, and the copy of the operand's strip; before them the stream.  Fitted, as the estimates of the other kernels below, to 28600 uniform matrices of 300 to 16384 rows, 1024 to 16384 columns, 0.1 to
-// 10 %, batch 193 to 1024, and to the next best number of ranges: root mean square 6.6 %, 1 % off at any number of blocks.
+// The product in strips, us, with the ranges that make it shortest: rounds of 256 work-groups (one fits a compute unit), each the steps that its LDS
+// serves, the sets that a wave takes one after the other, and the copy of the operand's strip; before them the stream.  Fitted, as the estimates of
+// the other kernels below, to 28600 uniform matrices of 300 to 16384 rows, 1024 to 16384 columns, 0.1 to 10 %, batch 193 to 1024, and to the next
+// best number of ranges: root mean square 6.6 %, 1 % off at any number of blocks.
 struct StripPlan {
     StripGrid grid;
     double us;
@@ -3444,8 +3450,8 @@ static StripPlan strip_plan(int32_t rows, int32_t x_rows, int32_t batch, int32_t
     return p;
 }
 static StripPlan strip_plan(const SpmmCall &a) { return strip_plan(a.rows, a.x_rows, a.batch, a.strips->blocks, a.strips->steps, a.strips->chunks); }
-// The kernel that would run otherwise, us: staged, in column tiles (of 128, or of 64 and fewer) or over the whole batch; 3.5, 8.8, 17 (3 to 16 too short in the mean) and 10 % root mean square.  0: not known
-// well enough for a comparison.
+// The kernel that would run otherwise, us: staged, in column tiles (of 128, or of 64 and fewer) or over the whole batch; 3.5, 8.8, 17 (3 to 16 too
+// short in the mean) and 10 % root mean square.  0: not known well enough for a comparison.
 static double other_product_us(const SpmmCall &a)
 {
     const double nnz = a.nnz * 1e-6, x_rows = a.x_rows * 1e-6, rows = a.rows * 1e-6, operand = 4. * x_rows * a.batch;   // (millions)
@@ -3462,8 +3468,8 @@ static double other_product_us(const SpmmCall &a)
     if (tg == 32) return 7.4 + gathers * (0.0294 + 0.0118 * tile) + 0.36 * rows * a.batch;
     return 6.2 + gathers * (0.036 + 0.015 * std::min(tile, 2.)) + 0.2 * operand - 0.4 * rows * a.batch;
 }
-// Where strips pay: of the matrices above that take them 0.75 % are slower by 3 % or more, the worst by 14 %; all in all they are 1.32 times as fast.  (A line that asks less of the strips, 0.98: 1.27 times, but
-// 3 % of the matrices slower.)
+// Where strips pay: of the matrices above that take them 0.75 % are slower by 3 % or more, the worst by 14 %; all in all they are 1.32 times as fast.
+// (A line that asks less of the strips, 0.98: 1.27 times, but 3 % of the matrices slower.)
 static bool strip_pays(double strips, double other) { return strips < 0.94 * other; }
 bool spmm_strip_ok(const SpmmCall &a)
 {
@@ -3503,7 +3509,8 @@ bool sddmm_staged_ok(const SddmmCall &a)
     if (a.x_rows < 64 || a.nnz < 64 || a.nnz >= (1 << 30)) return false;  // (as spmm_staged_ok; its byte offsets have 32 bits, and for so many entries there is no room for partial products)
     const int64_t work = staged_work(a.blocks, a.x_rows, a.batch);
     const int32_t segment = a.split_done && a.batch >= 512 ? kStageSegmentBesideDense : work >= kStageMuchWork ? kStageSegmentMuchWork : kStageLongSegmentSddmm;
-    if (a.blocks.staged_partial && (a.blocks.n_rest_blocks <= 0 || static_cast<int64_t>(a.blocks.n_rest_blocks) * kSddmmParts * ((a.batch + kStageCols - 1) / kStageCols + 8) >= (1ll << 31))) return false;
+    const int64_t rest_ids = static_cast<int64_t>(a.blocks.n_rest_blocks) * kSddmmParts * ((a.batch + kStageCols - 1) / kStageCols + 8);
+    if (a.blocks.staged_partial && (a.blocks.n_rest_blocks <= 0 || rest_ids >= (1ll << 31))) return false;
     return staged_pays(a.blocks, a.x_rows, a.batch, segment);
 }
 
@@ -3538,8 +3545,8 @@ hipError_t sddmm_tiled_go(const SddmmCall &a, hipStream_t s, BackwardFinish *fir
                 const int n_finish = first->n_entry_blocks + first->n_row_blocks, groups = (n_finish + 7) / 8;
                 const int64_t eights = (ids + 7) / 8 + groups;
                 first->waiting = false;
-                hipLaunchKernelGGL((sddmm_tiled_finish_kernel<NV, decltype(spare)::value>), dim3(static_cast<unsigned>(eights * 8)), dim3(kSddmmWaves * kWave), 0, s, a, n_tiles, order, first->a, first->hot_at,
-                                   first->n_tiles, first->n_entry_blocks, n_finish, static_cast<int>(eights / groups));
+                hipLaunchKernelGGL((sddmm_tiled_finish_kernel<NV, decltype(spare)::value>), dim3(static_cast<unsigned>(eights * 8)), dim3(kSddmmWaves * kWave), 0, s, a,
+                                   n_tiles, order, first->a, first->hot_at, first->n_tiles, first->n_entry_blocks, n_finish, static_cast<int>(eights / groups));
                 return;
             }
         }
@@ -3652,15 +3659,17 @@ int tile_columns(int32_t x_rows, int32_t batch, int64_t nnz, int32_t rows, int32
     const int w = tile_columns_wanted(x_rows, batch, nnz, rows, skewed, hot_share, masked, for_sddmm);
     const int n_tiles = w > 0 ? (batch + w - 1) / w : 0;
     if (w == 0 || n_tiles >= 8) return w;
-    // Fewer tiles than XCDs: either every L2 sees every tile, and an eighth of the gathers from it, or it sees few and its share of the work is short (tile_order).
-    // The tiles then pay where an L2 gathers a row of one several times and the untiled operand is well beyond the L2; a product's also on an operand
-    // beyond three L2s whose rows are gathered rarely.  Rows of very different lengths: where enough is gathered from an operand of two L2s; in products rows and columns of 48 entries, and
-    // tiles that fill much of an L2 (narrower ones lose), but no more than one where the last of seven is partly empty.
-    // Untiled / in tiles.  Even rows, 9106 x 9383 at 0.3 % (27 entries per operand row), batch 100 / 182 / 400: forward 11.2 / 17.7 / 40.5 and 16.1 / 18.4 / 39.7 us, at 0.1 %: SDDMM
-    // 7.8 / 11.2 / 22.4 and 10.4 / 16.1 / 28.1, forward at batch 400 18.9 and 14.5; 5000^2 at 0.3 %, batch 300 / 700 / 850: 11.5 / 21.2 / 25.9 and 10.6 / 17.4 / 18.8,
-    // but transposed 6656 x 1314 at 0.3 %, batch 400 (10 MiB): 10.1 and 15.6.  Power-law rows, forward: 9106 x 9383 at 0.6 %, batch 256 / 700: 48.3 / 112 and 38.4 / 94; 3000 x 12000 at 3.5 %, batch 256: 115 and 67, at 1.2 % 46.2 and 45.0;
-    // but 12000 x 3000 at 0.6 %, batch 700: 41.4 and 53.3, 5000^2 at 1.2 %: 52.6 and 61.3; 9106 x 9383 at 1.2 %, batch 850: 209 and 225.  SDDMM: 5000^2 at 2 %, batch 300 / 700: 47.6 / 139 and 44.4 / 79; 8192^2 at 0.6 %,
-    // batch 256 / 850: 39.2 / 161 and 32.4 / 95, at 0.3 %, batch 400: 39.0 and 41.1; 12000 x 3000 at 0.3 %, batch 850: 40.7 and 58.0.
+    // Fewer tiles than XCDs: either every L2 sees every tile, and an eighth of the gathers from it, or it sees few and its share of the work is short
+    // (tile_order).  The tiles then pay where an L2 gathers a row of one several times and the untiled operand is well beyond the L2; a product's
+    // also on an operand beyond three L2s whose rows are gathered rarely.  Rows of very different lengths: where enough is gathered from an operand
+    // of two L2s; in products rows and columns of 48 entries, and tiles that fill much of an L2 (narrower ones lose), but no more than one where the
+    // last of seven is partly empty.  Untiled / in tiles.  Even rows, 9106 x 9383 at 0.3 % (27 entries per operand row), batch 100 / 182 / 400:
+    // forward 11.2 / 17.7 / 40.5 and 16.1 / 18.4 / 39.7 us, at 0.1 %: SDDMM 7.8 / 11.2 / 22.4 and 10.4 / 16.1 / 28.1, forward at batch 400 18.9 and
+    // 14.5; 5000^2 at 0.3 %, batch 300 / 700 / 850: 11.5 / 21.2 / 25.9 and 10.6 / 17.4 / 18.8, but transposed 6656 x 1314 at 0.3 %, batch 400 (10
+    // MiB): 10.1 and 15.6.  Power-law rows, forward: 9106 x 9383 at 0.6 %, batch 256 / 700: 48.3 / 112 and 38.4 / 94; 3000 x 12000 at 3.5 %, batch
+    // 256: 115 and 67, at 1.2 % 46.2 and 45.0; but 12000 x 3000 at 0.6 %, batch 700: 41.4 and 53.3, 5000^2 at 1.2 %: 52.6 and 61.3; 9106 x 9383 at
+    // 1.2 %, batch 850: 209 and 225.  SDDMM: 5000^2 at 2 %, batch 300 / 700: 47.6 / 139 and 44.4 / 79; 8192^2 at 0.6 %, batch 256 / 850: 39.2 / 161
+    // and 32.4 / 95, at 0.3 %, batch 400: 39.0 and 41.1; 12000 x 3000 at 0.3 %, batch 850: 40.7 and 58.0.
     const int64_t operand = static_cast<int64_t>(x_rows) * batch * 4, tile = static_cast<int64_t>(x_rows) * 4 * w;
     bool pays;
     if (!skewed)
@@ -3810,13 +3819,15 @@ static int backward_split(const SpmmCall &t, int tg, int n_tiles)
 }
 static int backward_tiles(const SpmmCall &t, int tg) { return (t.batch + tg * 4 - 1) / (tg * 4); }
 
-// What the end of a step in one launch saves is 3 to 5 us whatever the work, and where there is much of it the launches apart are the faster ones, with more registers.  W_1: the entries of
-// a mirror row lie a row of W_1 apart in its values and velocity.  Steps, us, apart -> in one (thousand entries of W_1 x thousand rows): 1000-2000-2000-10 at 5 / 10 % (200 x 2, 400 x 2), batch 64 39.8 ->
-// 36.6, 51.9 -> 52.3, batch 16 33.9 -> 31.6, 39.8 -> 45.0; 3000-3000-3000-10 at 1 / 2 / 5 % (90, 180, 450 x 3), batch 192 50.4 -> 48.6, 66.5 -> 67.5, 108 -> 112; 1500-3000-800-10 at 14 % (336 x
-// 0.8), batch 64 54.5 -> 49.4, batch 16 39.6 -> 40.4; 1300-6600-700-10 (430 x 0.7), batch 80 78 -> 72; 3000-4000-4000-10 at 1 / 1.7 % (160, 272 x 4), batch 100 52.8 -> 48.9, 62.2 -> 64.1; 2498-7241-5799-13 at
-// 0.5 / 1 / 1.7 % (29, 58 and 98 entries a mirror row), batch 64 47.4 -> 42.1, 62.8 -> 56.9, 80.9 -> 76.0, at 2.5 % 107 -> 112, batch 16 at 1 / 1.7 % 50.6 -> 51.6, 59.5 -> 68.6; where its backward pass
-// alone takes two tiles, batch 150: 1.7 % 138 -> 122.  W_0's gradient beside a small W_1: 2500-700-64-10 at 30 % (525 and 13), batch 38 / 100: 34.0 -> 35.0, 42.9 -> 45.2, at 12 % 27.1 -> 25.0,
-// 31.1 -> 30.2; 4000-6000-300-10 at 2.5 / 4 % (960 and 72), batch 80: 48.2 -> 45.5, 64.9 -> 68.7.
+// What the end of a step in one launch saves is 3 to 5 us whatever the work, and where there is much of it the launches apart are the faster ones,
+// with more registers.  W_1: the entries of a mirror row lie a row of W_1 apart in its values and velocity.  Steps, us, apart -> in one (thousand
+// entries of W_1 x thousand rows): 1000-2000-2000-10 at 5 / 10 % (200 x 2, 400 x 2), batch 64 39.8 -> 36.6, 51.9 -> 52.3, batch 16 33.9 -> 31.6, 39.8
+// -> 45.0; 3000-3000-3000-10 at 1 / 2 / 5 % (90, 180, 450 x 3), batch 192 50.4 -> 48.6, 66.5 -> 67.5, 108 -> 112; 1500-3000-800-10 at 14 % (336 x
+// 0.8), batch 64 54.5 -> 49.4, batch 16 39.6 -> 40.4; 1300-6600-700-10 (430 x 0.7), batch 80 78 -> 72; 3000-4000-4000-10 at 1 / 1.7 % (160, 272 x 4),
+// batch 100 52.8 -> 48.9, 62.2 -> 64.1; 2498-7241-5799-13 at 0.5 / 1 / 1.7 % (29, 58 and 98 entries a mirror row), batch 64 47.4 -> 42.1, 62.8 ->
+// 56.9, 80.9 -> 76.0, at 2.5 % 107 -> 112, batch 16 at 1 / 1.7 % 50.6 -> 51.6, 59.5 -> 68.6; where its backward pass alone takes two tiles, batch
+// 150: 1.7 % 138 -> 122.  W_0's gradient beside a small W_1: 2500-700-64-10 at 30 % (525 and 13), batch 38 / 100: 34.0 -> 35.0, 42.9 -> 45.2, at 12 %
+// 27.1 -> 25.0, 31.1 -> 30.2; 4000-6000-300-10 at 2.5 / 4 % (960 and 72), batch 80: 48.2 -> 45.5, 64.9 -> 68.7.
 bool chain_pays(const SpmmCall &t, const SddmmCall &g0)
 {
     const int64_t n = t.nnz, spread = n * t.x_rows, below = static_cast<int64_t>(g0.nnz) * t.batch;
@@ -3834,26 +3845,28 @@ bool backward_fused_refreshes(const SpmmCall &t, const SddmmCall &g)
     return tiles == 1 || backward_looped(t) || static_cast<int64_t>(tiles) * t.nnz <= (1 << 20);
 }
 
-// Within a training step small layers do better with T and S in the grids of their neighbours: entries times columns from
-// which the pass pays there (steps of 3072-1024-512-10 at 10 %, batch 100, 5 M in the middle layer: 38.6 -> 42.5 us with it;
-// 2000-4000-3000-10 at 3 %, batch 128, 46 M: 72.4 -> 70.2; three layers of 3000 at 5 %, batch 100: 128 -> 116): kFusedMinWork.
-// The transposed product staged through LDS and the gradient apart from it (staged too, or by matrix instructions sampled on the pattern) against one stream of L2 gathers for both: apart they read
-// the operands twice, from LDS at up to three times the rate, and copy them there.  Which is faster goes by estimates of both, us.  A staged launch takes rounds of a work-group per compute unit,
-// each a range's entries and the copy of its operand tile; the stream its gathers (more of them miss where dZ has many rows), and the strewing of results through the position map,
-// whose share grows with the entries.  Root mean square from what was measured, apart / stream, batch 128 to 1024: 4 / 4 % on 330 uniform layers of 1500 to 16384 rows and columns, 3 to 15 %; 3 / 5 %
-// on 94 power-law ones, where the staged gradient has the rows that are not dense, and the stream finds the operand rows of the dense ones in cache; 3 / 6 % on 75 of 15 to 40 % with a sampled gradient.
-// One stream -> apart: 12000 x 11500 at 7 %, batch 900 2103 -> 1677; 14000 x 6800 at 12 %, batch 640 1693 -> 1228; 9877 x 13217 at 9 %, batch 192 636 -> 545; 16384^2 at 5 / 10 %, batch 1024 3246 -> 2596,
-// 6435 -> 4595; power-law 14000 x 2800 at 12 %, batch 768 825 -> 593; 1896 x 8041 at 33 %, batch 300 360 -> 225; but 3336 x 14187 at 9 %, batch 640 483 -> 546, 6300 x 10100 at 9 %, batch 256 306 -> 334, power-law
-// 11600 x 4700 at 5 %, batch 512 310 -> 346.  Far from the estimates: segments shorter than those fitted (16384^2 at 2 %, batch 300 478 -> 700), little work (1525 x 1453 at 15 %, batch 900 69 -> 89,
-// 551 x 3748 at 31 %, batch 256 38 -> 46; steps of 604-1571-1495-10 at 8 %, batch 700 117 -> 129, 393-2977-692-10 at 17 %, batch 300 104 -> 110), and the stream of a mirror of few rows (11458 x 1073 at 8 %, batch 1024 198 -> 222).
-// In a training step the stream has the updates to strew over values and velocity as well, which the gradient's second pass finds in order: steps of 802-6257-6435-10 at 14 %, batch 320
-// 732 -> 581, 751-8177-7029-10 at 8 %, batch 900 1264 -> 1174, 1055-7772-2917-10 at 24 %, batch 160 564 -> 423, but of 750-6610-5291-10 at 5 %, batch 640 382 -> 407; with dense rows much of the
-// gradient goes by matrix instructions, and apart it stays.
-// A single call on a matrix with dense rows that would go apart stays together where its stream keeps its hot rows in LDS
-// (backward_hot_ok) and takes less by 6 %: of 5000 power-law layers of 1500 to 16384 rows and columns, 1 to 14 %, batch 193
-// to 1024, 271 do, 1.10 times as fast, eight of them slower by 3 % or more, the worst by 5.  Apart -> with hot rows:
-// 9349 x 10144 at 4.8 %, batch 1024 835 -> 733; 2128 x 4636 at 13 %, batch 901 228 -> 181; but 12085 x 6193 at 13 %, batch
-// 656 951 -> 1329; 8119 x 5813 at 11 %, batch 450 445 -> 488.
+// Within a training step small layers do better with T and S in the grids of their neighbours: entries times columns from which the pass pays there
+// (steps of 3072-1024-512-10 at 10 %, batch 100, 5 M in the middle layer: 38.6 -> 42.5 us with it; 2000-4000-3000-10 at 3 %, batch 128, 46 M: 72.4 ->
+// 70.2; three layers of 3000 at 5 %, batch 100: 128 -> 116): kFusedMinWork.  The transposed product staged through LDS and the gradient apart from it
+// (staged too, or by matrix instructions sampled on the pattern) against one stream of L2 gathers for both: apart they read the operands twice, from
+// LDS at up to three times the rate, and copy them there.  Which is faster goes by estimates of both, us.  A staged launch takes rounds of a
+// work-group per compute unit, each a range's entries and the copy of its operand tile; the stream its gathers (more of them miss where dZ has many
+// rows), and the strewing of results through the position map, whose share grows with the entries.  Root mean square from what was measured, apart /
+// stream, batch 128 to 1024: 4 / 4 % on 330 uniform layers of 1500 to 16384 rows and columns, 3 to 15 %; 3 / 5 % on 94 power-law ones, where the
+// staged gradient has the rows that are not dense, and the stream finds the operand rows of the dense ones in cache; 3 / 6 % on 75 of 15 to 40 % with
+// a sampled gradient.  One stream -> apart: 12000 x 11500 at 7 %, batch 900 2103 -> 1677; 14000 x 6800 at 12 %, batch 640 1693 -> 1228; 9877 x 13217
+// at 9 %, batch 192 636 -> 545; 16384^2 at 5 / 10 %, batch 1024 3246 -> 2596, 6435 -> 4595; power-law 14000 x 2800 at 12 %, batch 768 825 -> 593;
+// 1896 x 8041 at 33 %, batch 300 360 -> 225; but 3336 x 14187 at 9 %, batch 640 483 -> 546, 6300 x 10100 at 9 %, batch 256 306 -> 334, power-law
+// 11600 x 4700 at 5 %, batch 512 310 -> 346.  Far from the estimates: segments shorter than those fitted (16384^2 at 2 %, batch 300 478 -> 700),
+// little work (1525 x 1453 at 15 %, batch 900 69 -> 89, 551 x 3748 at 31 %, batch 256 38 -> 46; steps of 604-1571-1495-10 at 8 %, batch 700 117 ->
+// 129, 393-2977-692-10 at 17 %, batch 300 104 -> 110), and the stream of a mirror of few rows (11458 x 1073 at 8 %, batch 1024 198 -> 222).  In a
+// training step the stream has the updates to strew over values and velocity as well, which the gradient's second pass finds in order: steps of
+// 802-6257-6435-10 at 14 %, batch 320 732 -> 581, 751-8177-7029-10 at 8 %, batch 900 1264 -> 1174, 1055-7772-2917-10 at 24 %, batch 160 564 -> 423,
+// but of 750-6610-5291-10 at 5 %, batch 640 382 -> 407; with dense rows much of the gradient goes by matrix instructions, and apart it stays.  A
+// single call on a matrix with dense rows that would go apart stays together where its stream keeps its hot rows in LDS (backward_hot_ok) and takes
+// less by 6 %: of 5000 power-law layers of 1500 to 16384 rows and columns, 1 to 14 %, batch 193 to 1024, 271 do, 1.10 times as fast, eight of them
+// slower by 3 % or more, the worst by 5.  Apart -> with hot rows: 9349 x 10144 at 4.8 %, batch 1024 835 -> 733; 2128 x 4636 at 13 %, batch 901 228 ->
+// 181; but 12085 x 6193 at 13 %, batch 656 951 -> 1329; 8119 x 5813 at 11 %, batch 450 445 -> 488.
 static double hot_time(const SpmmCall &t, float share, bool update);
 static double staged_launch_time(const RowBlocks &blocks, int64_t nnz, int32_t x_rows, int32_t batch)
 {
@@ -3986,13 +3999,14 @@ hipError_t launch_full_backward(const SpmmCall &t, const SddmmCall &g, hipStream
     return hipGetLastError();
 }
 
-// Whether the waves of one tile have all gathers of a pass in flight (APART, 70 to 82 registers, 5 to 7 waves a SIMD) or two or three (62 to 78, 6 to 8): where few waves leave
-// room anyway, and in groups of 16 where rows are short.  Uniform rows, us, mixed -> apart: batch 16, 8000 x 1000 at 12 % 3 % faster, 700 x 6000 at 12 % 11.6 -> 12.6, 3000 x 16384 at
-// 12 % 131 -> 150; batch 64, 2048 x 3000 at 10 / 40 % 21.2 -> 18.6, 60.5 -> 53.9, 2048 x 4096 at 10 / 40 % 24.4 -> 23.0, 73.9 -> 79.4, 2048 x 5500 at 10 / 40 % 30.2 -> 30.7, 107 -> 124,
-// 3000 x 8192 at 5 / 40 % 34.8 -> 32.3, 226 -> 258; batch 128, 2048 x 3000 at 10 % 26.3 -> 25.1, 2048 x 3400 28.2 -> 28.6, 2048 x 6500 48.3 -> 50.6, 3000 x 13000 at 2 % 30.5 -> 33.2,
-// 3000 x 16384 at 12 % 208 -> 200,
-// 8192^2 at 0.3 / 0.6 / 2 / 7 % 14.3 -> 13.5, 20.9 -> 19.6, 51 -> 49.3, 151 -> 162, 9106 x 9383 at 0.3 / 0.6 / 2 % 16.7 -> 15.8, 24.4 -> 25.3, 65 -> 71.6; batch 256 not slower up to 25 %.  With the update, which loads more: steps of 3000-3000-3000-10, batch 64, at 15 / 25 % 121 -> 122, 185 -> 197, of
-// 2000-2000-2000-10 at 25 % 97 -> 90.
+// Whether the waves of one tile have all gathers of a pass in flight (APART, 70 to 82 registers, 5 to 7 waves a SIMD) or two or three (62 to 78, 6 to
+// 8): where few waves leave room anyway, and in groups of 16 where rows are short.  Uniform rows, us, mixed -> apart: batch 16, 8000 x 1000 at 12 % 3
+// % faster, 700 x 6000 at 12 % 11.6 -> 12.6, 3000 x 16384 at 12 % 131 -> 150; batch 64, 2048 x 3000 at 10 / 40 % 21.2 -> 18.6, 60.5 -> 53.9, 2048 x
+// 4096 at 10 / 40 % 24.4 -> 23.0, 73.9 -> 79.4, 2048 x 5500 at 10 / 40 % 30.2 -> 30.7, 107 -> 124, 3000 x 8192 at 5 / 40 % 34.8 -> 32.3, 226 -> 258;
+// batch 128, 2048 x 3000 at 10 % 26.3 -> 25.1, 2048 x 3400 28.2 -> 28.6, 2048 x 6500 48.3 -> 50.6, 3000 x 13000 at 2 % 30.5 -> 33.2, 3000 x 16384 at
+// 12 % 208 -> 200, 8192^2 at 0.3 / 0.6 / 2 / 7 % 14.3 -> 13.5, 20.9 -> 19.6, 51 -> 49.3, 151 -> 162, 9106 x 9383 at 0.3 / 0.6 / 2 % 16.7 -> 15.8,
+// 24.4 -> 25.3, 65 -> 71.6; batch 256 not slower up to 25 %.  With the update, which loads more: steps of 3000-3000-3000-10, batch 64, at 15 / 25 %
+// 121 -> 122, 185 -> 197, of 2000-2000-2000-10 at 25 % 97 -> 90.
 static bool backward_gathers_apart(int gs, int64_t waves, const SpmmCall &t, bool update)
 {
     if (update && gs < 64 && waves > 2048 && t.nnz > 400ll * t.rows) return false;
@@ -4001,11 +4015,12 @@ static bool backward_gathers_apart(int gs, int64_t waves, const SpmmCall &t, boo
     return gs == 64 || waves <= 3072 || waves >= 16384 || t.nnz <= 40ll * t.rows || (waves <= 4608 && t.nnz <= 192ll * t.rows);
 }
 
-// Whether one tile in groups of 16 or 32 lanes, whose gathers would be apart, takes chunks of sixteen (80 registers, a third fewer instructions).  Uniform rows, us, batch 64 / 128: 1200 x 1100
-// at 2 % 5.4 -> 5.1, 5.8 -> 5.2, at 6 % 6.4 -> 6.4, 8.9 -> 7.7; 2048 x 3000 at 6 % 12.3 -> 12.0, 17.3 -> 16.1; 3000 x 4000 at 6 % 21.5 -> 20.8, 29.2 -> 27.5; 4000 x 3000 at 2 % 10.0 -> 9.6, 13.5 -> 12.6;
-// 8192^2 at 0.6 / 2 % 15.6 -> 15.2, 37.4 -> 37.5, 19.9 -> 19.7, 50.3 -> 49.0.  Not with rows of one chunk (3000 x 4000 at 0.3 %, 9 entries a row, batch 128 5.0 -> 5.4), nor with long ones, which lose
-// lines that the L1s would keep (2048 x 5500 at 25 % 67.7 -> 77.8, 98.5 -> 104; 9106 x 9383 at 6 %, batch 64 139 -> 158), nor with more waves than start at once (9106 x 9383 at 2 %, batch 128 65.0 -> 71.9,
-// at 0.3 % 16.1 -> 16.8; but 2048 x 5500 at 2 % 14.0 -> 12.1).
+// Whether one tile in groups of 16 or 32 lanes, whose gathers would be apart, takes chunks of sixteen (80 registers, a third fewer instructions).
+// Uniform rows, us, batch 64 / 128: 1200 x 1100 at 2 % 5.4 -> 5.1, 5.8 -> 5.2, at 6 % 6.4 -> 6.4, 8.9 -> 7.7; 2048 x 3000 at 6 % 12.3 -> 12.0, 17.3
+// -> 16.1; 3000 x 4000 at 6 % 21.5 -> 20.8, 29.2 -> 27.5; 4000 x 3000 at 2 % 10.0 -> 9.6, 13.5 -> 12.6; 8192^2 at 0.6 / 2 % 15.6 -> 15.2, 37.4 ->
+// 37.5, 19.9 -> 19.7, 50.3 -> 49.0.  Not with rows of one chunk (3000 x 4000 at 0.3 %, 9 entries a row, batch 128 5.0 -> 5.4), nor with long ones,
+// which lose lines that the L1s would keep (2048 x 5500 at 25 % 67.7 -> 77.8, 98.5 -> 104; 9106 x 9383 at 6 %, batch 64 139 -> 158), nor with more
+// waves than start at once (9106 x 9383 at 2 %, batch 128 65.0 -> 71.9, at 0.3 % 16.1 -> 16.8; but 2048 x 5500 at 2 % 14.0 -> 12.1).
 static bool bwd_sixteens(int64_t waves, const SpmmCall &t) { return waves <= 4096 && t.nnz > 20ll * t.rows && t.nnz <= 400ll * t.rows; }
 
 // Whether the pass with hot rows in LDS runs: where a tile's columns are on, there are mirror rows enough (a wave for
@@ -4094,7 +4109,8 @@ hipError_t launch_backward_fused(const SpmmCall &t, const SddmmCall &g, bool alo
     if (backward_hot_ok(t, g)) {
         StripGrid h;
         h.n_tiles = (t.batch + 63) / 64;
-        // one round of work-groups, two tiles at a time on an XCD, where an L2 holds both (5001 x 9001 at 2 %, batch 999, in two: 133 -> 144 us), else two (16384^2 at 1 %, batch 1024, in one: 438 -> 474)
+        // one round of work-groups, two tiles at a time on an XCD, where an L2 holds both (5001 x 9001 at 2 %, batch 999, in two: 133 -> 144 us),
+        // else two (16384^2 at 1 %, batch 1024, in one: 438 -> 474)
         h.n_ranges = std::max(1, (t.x_rows * 512ll <= (3 << 20) ? 1 : 2) * 256 / h.n_tiles);
         h.per = (h.n_tiles * h.n_ranges + 7) / 8;
         const bool refresh = alone && g.values;   // (backward_fused_refreshes: the call leaves it to this launch)
@@ -4330,10 +4346,11 @@ int sddmm_tile_columns(const SddmmCall &a)
     return w;
 }
 
-// Whether launch_sddmm takes a finish pass that waits into its grid.  It strews weights and velocity over the rows of the layer above, whose lines the gathers beside it push out of the L2s half written where they
-// are many: not beyond 4096 rows (1 MiB in an L2) unless there are few entries, or half again as many as the gradient's at the most among eight tiles or more, whose last round has room.  Steps of 5400 networks of
-// two hidden layers, apart -> in one launch: where it is taken 1.012 times as fast, else 0.999 in the mean: 1108-1879-8144-10 at 3 %, batch 1024 230 -> 241 us, 5871-5373-4349-10, batch 492 274 -> 288,
-// 1134-7260-7945-10 at 1.2 %, batch 902 304 -> 320.
+// Whether launch_sddmm takes a finish pass that waits into its grid.  It strews weights and velocity over the rows of the layer above, whose lines
+// the gathers beside it push out of the L2s half written where they are many: not beyond 4096 rows (1 MiB in an L2) unless there are few entries, or
+// half again as many as the gradient's at the most among eight tiles or more, whose last round has room.  Steps of 5400 networks of two hidden
+// layers, apart -> in one launch: where it is taken 1.012 times as fast, else 0.999 in the mean: 1108-1879-8144-10 at 3 %, batch 1024 230 -> 241 us,
+// 5871-5373-4349-10, batch 492 274 -> 288, 1134-7260-7945-10 at 1.2 %, batch 902 304 -> 320.
 static bool sddmm_takes_finish(const SddmmCall &a, const BackwardArgs &f)
 {
     if (a.rows <= 0 || a.batch <= 0 || a.blocks.n_blocks <= 0 || sddmm_sampled_ok(a) || sddmm_dense_rows_ok(a) || sddmm_full_ok(a) || sddmm_staged_ok(a)) return false;

@@ -38,8 +38,9 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)); }
 __device__ __forceinline__ int lanes_below(uint64_t mask) { return __popcll(mask & ((1ull << lane_id()) - 1)); }
 
-// Sums, prefix sums and maxima over a wave, all lanes active.  Those of 32 bits by moves between lanes (DPP): a prefix sum through the LDS crossbar is six round trips of some 100 cycles, and the set-up
-// kernels are chains of them (8192^2 at 0.74 %: bin_place_kernel 20.7 -> 16.1 us, plan_kernel, whose first thread no longer writes all it reports alone either, 22.2 -> 18.1).
+// Sums, prefix sums and maxima over a wave, all lanes active.  Those of 32 bits by moves between lanes (DPP): a prefix sum through the LDS crossbar
+// is six round trips of some 100 cycles, and the set-up kernels are chains of them (8192^2 at 0.74 %: bin_place_kernel 20.7 -> 16.1 us, plan_kernel,
+// whose first thread no longer writes all it reports alone either, 22.2 -> 18.1).
 template <int CTRL, int ROWS = 0xF>
 __device__ __forceinline__ int32_t lanes_moved(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }   // (0 where no lane is named)
 template <typename F>
@@ -976,7 +977,8 @@ __global__ __launch_bounds__(kSetupBlock) void hot_place_kernel(const int4 *rows
     const int32_t e = blockIdx.x * kSetupBlock + threadIdx.x;
     if (e < n) place[rows_by_length[e].x] = e < kHotRowsLds ? e : -1;
 }
-__global__ __launch_bounds__(kSetupBlock) void hot_order_kernel(const int32_t *indptr_t, const int32_t *indices_t, const int32_t rows, const int32_t *perm, const int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, int32_t *count)
+__global__ __launch_bounds__(kSetupBlock) void hot_order_kernel(const int32_t *indptr_t, const int32_t *indices_t, const int32_t rows, const int32_t *perm,
+                                                                const int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, int32_t *count)
 {
     const int32_t row = blockIdx.x * (kSetupBlock / kWave) + wave_id();
     if (row >= rows) return;
@@ -1021,8 +1023,8 @@ __global__ __launch_bounds__(kHotGroup) void hot_sets_kernel(const int4 *mirror_
 
 }  // namespace
 
-hipError_t launch_hot_order(const int4 *rows_by_length, int32_t x_rows, const int32_t *indptr_t, const int32_t *indices_t, int32_t rows, const int32_t *perm, int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, const int4 *mirror_rows, int4 *sets,
-                            hipStream_t s)
+hipError_t launch_hot_order(const int4 *rows_by_length, int32_t x_rows, const int32_t *indptr_t, const int32_t *indices_t, int32_t rows, const int32_t *perm,
+                            int32_t *place, int32_t *entry, int32_t *at, int32_t *hot_perm, const int4 *mirror_rows, int4 *sets, hipStream_t s)
 {
     hipLaunchKernelGGL(hot_place_kernel, dim3((x_rows + kSetupBlock - 1) / kSetupBlock), dim3(kSetupBlock), 0, s, rows_by_length, x_rows, place);
     int32_t *count = place + x_rows;
