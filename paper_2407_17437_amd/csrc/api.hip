@@ -101,7 +101,7 @@ struct PatternBuffers {
     size_t row_partial_floats = 0;
     int32_t *whole_staged = nullptr;   // staged plan of all rows beside that of the rows that are not dense
     size_t whole_staged_ints = 0;
-    int32_t *hot = nullptr;         // entry | at | count of HotRows
+    int32_t *hot = nullptr;         // entry | at | perm of HotRows | mirror values in that order | sets | scratch of launch_hot_order
     size_t hot_ints = 0;
     DenseSplit split{};             // views into plan_mem and row_table
 };
@@ -124,6 +124,8 @@ struct nerva_layer {
     RowBlocks plan{}, plan_t{};
     Strips strips;                  // segs nullptr: none
     HotRows hot;                    // entry nullptr: none
+    bool hot_ordered = false;       // the entries are in that order (order_hot_rows)
+    bool hot_taken = false;         // by a call, of this pattern or one before
     // owned scratch of the set-up kernels, and what they report (pinned host memory)
     int32_t *build_work = nullptr;
     size_t build_work_ints = 0;
@@ -851,6 +853,28 @@ static bool use_dense(const nerva_layer *l, int32_t batch) { return l->dense_on 
 // tickets of the huge rows of W (side 0) or of its mirror (side 1): rows of the two alternate
 static int32_t *tickets_of(const nerva_layer *l, int side) { return l->tickets ? l->tickets + side * huge_row_tickets(l->scratch_ld) : nullptr; }
 
+// The mirror's entries in the order of `v`, in b.hot (views of b's own arrays).
+static hipError_t make_hot_order(const PatternBuffers &b, const HotRows &v, int32_t rows, int32_t cols, int32_t nnz, const RowBlocks &plan_t, hipStream_t s)
+{
+    const size_t n64 = static_cast<size_t>(round_up(nnz, 64));
+    int32_t *sets = b.hot + 4 * n64;
+    return launch_hot_order(v.rows, rows, b.indptr_t, b.mirror_mem, cols, b.mirror_mem + n64, sets + 4 * hot_sets_size(cols), b.hot, b.hot + n64, b.hot + 2 * n64,
+                            plan_t.rows_by_length, reinterpret_cast<int4 *>(sets), s);
+}
+// For a call that takes it.  One that is recorded into a graph has not run: the next one makes the order again.
+static hipError_t order_hot_rows(nerva_layer *l, hipStream_t s)
+{
+    if (l->hot_ordered) return hipSuccess;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
+    const hipError_t e = make_hot_order(l->cur, l->hot, l->rows, l->cols, l->nnz, l->plan_t, s);
+    if (e == hipSuccess && capture == hipStreamCaptureStatusNone) l->hot_ordered = l->hot_taken = true;
+    return e;
+}
+
 static float *hot_values_of(const nerva_layer *l) { return l->hot.entry ? reinterpret_cast<float *>(l->cur.hot) + 3 * static_cast<size_t>(round_up(l->nnz, 64)) : nullptr; }
 
 static const DenseSplit *split_of(const nerva_layer *l) { return l->cur.split.rows.n > 0 ? &l->cur.split : nullptr; }
@@ -1032,14 +1056,16 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         g.split = B.split.rows.n > 0 ? &B.split : nullptr;
         return hot_rows_pay_somewhere(t, g, max_batch);
     };
-    // (the dense route has no use for it)
+    // (the dense route has no use for it; a layer none of whose calls has taken it, as the first one of a network, waits for one that does: making it takes 28 us of
+    // the 117 that binding 1100 x 2600 at 10 % does)
     if (asked == NERVA_PARTITION_BALANCED && nnz > 0 && !takes_dense_route(l, nnz) && takes_hot_rows() &&
-        reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)))) {
+        reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)) + static_cast<size_t>(rows) + cols)) {
         HotRows &v = out->hot;
-        HIP_TRY(launch_hot_order(out->plan.rows_by_length, rows, B.indptr_t, m.indices_t, cols, m.perm, W + work_at[0], B.hot, B.hot + n64, B.hot + 2 * n64, p.side[1].tables.rows_by_length,
-                                 reinterpret_cast<int4 *>(B.hot + 4 * n64), s));
         v.entry = B.hot; v.at = B.hot + n64; v.perm = B.hot + 2 * n64; v.sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.rows = out->plan.rows_by_length; v.share = in_lds;
-        more_work = true;
+        if (l->hot_taken) {
+            HIP_TRY(make_hot_order(B, v, rows, cols, nnz, out->plan_t, s));
+            more_work = true;
+        }
     }
 
     // scratch buffers of the products (they hold nothing between calls, the tickets zeros: grown in place, so that the old
@@ -1100,7 +1126,7 @@ static void adopt_pattern(nerva_layer *l, int32_t nnz, const int32_t *indptr, co
     l->perm = l->cur.mirror_mem + n64;
     l->pos_t = l->cur.mirror_mem + 2 * n64;
     l->values_t = reinterpret_cast<float *>(l->cur.mirror_mem + 3 * n64);
-    l->plan = bp.plan; l->plan_t = bp.plan_t; l->strips = bp.strips; l->hot = bp.hot;
+    l->plan = bp.plan; l->plan_t = bp.plan_t; l->strips = bp.strips; l->hot = bp.hot; l->hot_ordered = l->hot_taken;
     l->partial_stride = bp.partial_stride; l->partial_db_at = bp.partial_db_at; l->partial_tiles = bp.partial_tiles;
     l->scratch_ld = bp.scratch_ld;
     l->full_scratch_ld = bp.full_scratch_ld;
@@ -1361,6 +1387,7 @@ int sparse_linear_backward(nerva_layer *layer, const float *X, int32_t ldx, cons
     } else if (dX && dvalues && (in_one || (!c.mask && backward_fused_ok(transposed_args(c), gradient_args(c), true)))) {
         if (!c.form_dz && !backward_fused_refreshes(transposed_args(c), gradient_args(c))) HIP_TRY(launch_gather(layer->values_t, layer->values, layer->perm, layer->nnz, s));
         layer->mirror_stale = false;
+        if (backward_hot_ok(transposed_args(c), gradient_args(c))) HIP_TRY(order_hot_rows(layer, s));
         HIP_TRY(launch_backward_fused(transposed_args(c), gradient_args(c), true, s));
         return NERVA_OK;
     } else if (dX) {
@@ -1833,6 +1860,7 @@ static int train_step(nerva_mlp *mlp, const float *X, int32_t ldx, const int32_t
                 if (pending >= 0 && (rc = run_S_alone(pending)) != NERVA_OK) return rc;
                 pending = -1;
                 Timed tm(mlp->prof, s, "backward_fused", l);
+                if (backward_hot_ok(t, g_same)) HIP_TRY(order_hot_rows(mlp->layers[l], s));
                 // (not while a profile is on, whose slots hold what their names say, nor where both layers are one handle: S_0 would write the partial products that the finish pass reads)
                 HIP_TRY(launch_backward_fused(t, g_same, false, s, l == 1 && !mlp->prof.on && mlp->layers[0] != mlp->layers[1] ? &finish : nullptr));
                 continue;

@@ -20,6 +20,7 @@ std::string launched;
 PlanCounts counts[2];
 unsigned long long strip_counts = 0;   // as BindResult::strip, of plans that have room for strips
 int strip_blocks = -1;   // that the last bind asked for
+bool capturing = false;
 long calls_until_failure = -1;   // of the calls that allocate, fill or wait
 int bad_pointers = 0, bad_grids = 0, dirty_tickets = 0, mixed_tickets = 0;
 std::map<const int32_t *, int> ticket_ends;   // what each ticket of a shared tile counts up to
@@ -77,6 +78,7 @@ int fake_dirty_tickets() { return dirty_tickets; }
 int fake_mixed_tickets() { return mixed_tickets; }
 size_t fake_live_bytes() { return live_bytes; }
 int fake_strip_blocks() { return strip_blocks; }
+void fake_set_capturing(int on) { capturing = on; }
 void fake_set_strips(int chunks, int steps) { strip_counts = static_cast<unsigned>(chunks) | static_cast<unsigned long long>(steps) << 32; }
 const char *fake_launched() { static std::string out; out.swap(launched); launched.clear(); return out.c_str(); }
 int fake_set(int side, const char *field, int value)
@@ -100,6 +102,7 @@ hipError_t hipMemset(void *p, int v, size_t n)
 }
 hipError_t hipMemsetAsync(void *p, int v, size_t n, hipStream_t) { return hipMemset(p, v, n); }
 hipError_t hipStreamSynchronize(hipStream_t) { return fails(hipErrorUnknown) ? hipErrorUnknown : hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { static char symbol[256]; *p = symbol; return hipSuccess; }
 hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }   // (also of calls before the last one)

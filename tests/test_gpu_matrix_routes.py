@@ -769,6 +769,57 @@ def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
     L.close()
 
 
+def test_order_of_hot_rows_is_made_by_the_call_that_takes_it(nb, oracle):
+    """The first such call may be one that is recorded into a graph, which has not run when an eager one follows; then a new pattern, for whose binding the order is made at once."""
+    import torch
+    rows, cols, batch = 1100, 2600, 500
+    lay = hot_rows_layer(rows, cols, 400, 0.28, 20, 11)[0]
+    other = hot_rows_layer(rows, cols, 380, 0.29, 21, 12)[0]
+    rng = np.random.default_rng(7)
+    X = rng.standard_normal((cols, batch)).astype(np.float32); dY = rng.standard_normal((rows, batch)).astype(np.float32)
+    Xd, dYd, dXd = nb.to_dense(X), nb.to_dense(dY), nb.dense(cols, batch)
+    db = torch.empty(rows, device="cuda")
+
+    def call(L, g):
+        nb.sparse_linear_backward(L.handle, Xd, None, dYd, dXd, g, db, batch)
+
+    def check(L, pattern, g, what):
+        torch.cuda.synchronize()
+        values = L.values.cpu().numpy()
+        dX, S = oracle.spmm_t(rows, cols, pattern.indptr, pattern.indices, values, dY)
+        close(dXd.cpu().numpy(), dX, S, what=f"dX, {what}")
+        gr, Sg, dbr, Sdb = oracle.sddmm(rows, cols, pattern.indptr, pattern.indices, dY, X)
+        close(g.cpu().numpy(), gr, Sg, what=f"g, {what}")
+        close(db.cpu().numpy(), dbr, Sdb, what=f"db, {what}")
+
+    warm, g = nb.SparseLinear(lay, max_batch=batch), torch.empty(lay.nnz, device="cuda")
+    call(warm, g)   # (the kernels are loaded)
+    torch.cuda.synchronize()
+    warm.close()
+    L = nb.SparseLinear(lay, max_batch=batch)
+    assert nb.sparse_linear_routes(L.handle, batch) & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        call(L, g)
+    for k in range(3):
+        L.values.mul_(-1.1)
+        dXd.fill_(float("nan")); g.fill_(float("nan"))
+        if k == 1:
+            call(L, g)
+            check(L, lay, g, "eager")
+            dXd.fill_(float("nan")); g.fill_(float("nan"))
+        graph.replay()
+        check(L, lay, g, f"replay {k}")
+    del graph
+    L.rebind(other.indptr, other.indices, other.values)
+    g = torch.full((other.nnz,), float("nan"), device="cuda")
+    dXd.fill_(float("nan"))
+    call(L, g)
+    check(L, other, g, "rebound")
+    L.close()
+
+
 @pytest.mark.parametrize("batch", [512, 449])
 def test_training_step_with_hot_rows_in_lds(nb, oracle, batch):
     """The layer's update behind the same pass: every stage against the oracle, over steps whose weights each find changed."""

@@ -351,8 +351,8 @@ def both_gradients_go_apart_where_that_beats_hot_rows_in_lds(L):
         L.destroy()
 
 
-def an_order_of_hot_rows_is_made_where_a_call_takes_it(L):
-    """Not where the layer's wide batches go by its dense copy, nor where at every batch the hot rows would be slower than both gradients apart."""
+def an_order_of_hot_rows_is_made_when_a_call_takes_it(L):
+    """By the first that does; not where the layer's wide batches go by its dense copy, nor where at every batch the hot rows would be slower than both gradients apart."""
     for rows, cols, nnz, max_batch, dense, ranges, most, share, made in (
             (2000, 4000, 4000000, 1024, None, 0, 0.52, 0.26, False),         # half of its entries stored: the dense route
             (2000, 4000, 1000000, 1024, None, 0, 0.52, 0.26, True),
@@ -363,10 +363,29 @@ def an_order_of_hot_rows_is_made_where_a_call_takes_it(L):
                  staged_ranges=ranges, staged_rows=plan_rows, staged_nnz=plan_nnz)
         L.counts(1, n_blocks=600, longest_row=2 * nnz // cols, hot_nnz=nnz // 8, staged_ranges=ranges, staged_rows=cols if ranges else 0, staged_nnz=nnz if ranges else 0)
         L.launched()
+        before = L.hip.fake_live_bytes()
         assert L.create(rows, cols, nnz, max_batch) == 0
-        assert any("hot_order_kernel" in k for k in L.launched()) == made, (rows, cols, nnz)
-        assert any(L.routes(batch) & 2 for batch in range(1, max_batch + 1)) == made
+        took = [batch for batch in range(1, max_batch + 1) if L.routes(batch) & 2]
+        assert bool(took) == made, (rows, cols, nnz)
+
+        def ordered():
+            return sum("hot_order_kernel" in k for k in L.launched())
+
+        # made by the first call that takes it: nothing else of the layer pays for it
+        assert L.forward(max_batch) == 0 and L.backward(max_batch, dx=False) == 0 and L.backward(64) == 0 and L.rebind(nnz) == 0
+        assert ordered() == 0
+        if made:
+            # (a call that is recorded into a graph has not run)
+            L.hip.fake_set_capturing(1)
+            assert L.backward(took[-1]) == 0 and L.backward(took[0]) == 0 and ordered() == 2
+            L.hip.fake_set_capturing(0)
+            assert L.backward(took[-1]) == 0 and ordered() == 1
+            assert L.backward(took[-1]) == 0 and L.backward(took[0]) == 0 and ordered() == 0
+            # a layer that has taken it has it made as a pattern is bound
+            assert L.rebind(nnz) == 0 and ordered() == 1
+            assert L.backward(took[-1]) == 0 and ordered() == 0
         L.destroy()
+        assert L.hip.fake_live_bytes() == before and L.hip.fake_bad_pointers() == 0
 
 
 def a_failed_rebind_leaves_strips_and_hot_rows_in_place(L):
@@ -521,7 +540,7 @@ def strips_are_planned_where_a_batch_takes_them(L):
         L.destroy()
 
 
-CASES = [a_failed_rebind_leaves_strips_and_hot_rows_in_place, an_order_of_hot_rows_is_made_where_a_call_takes_it, both_gradients_go_apart_where_that_beats_hot_rows_in_lds, strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [a_failed_rebind_leaves_strips_and_hot_rows_in_place, an_order_of_hot_rows_is_made_when_a_call_takes_it, both_gradients_go_apart_where_that_beats_hot_rows_in_lds, strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
