@@ -106,6 +106,8 @@ struct PatternBuffers {
     DenseSplit split{};             // views into plan_mem and row_table
 };
 
+enum HotState { kHotUnordered, kHotOnItsWay, kHotOrdered };   // the entries in the order of HotRows
+
 struct nerva_layer {
     int32_t rows = 0, cols = 0, nnz = 0, activation = 0, max_batch = 0;
     // caller-owned
@@ -124,7 +126,8 @@ struct nerva_layer {
     RowBlocks plan{}, plan_t{};
     Strips strips;                  // segs nullptr: none
     HotRows hot;                    // entry nullptr: none
-    bool hot_ordered = false;       // the entries are in that order (order_hot_rows)
+    HotState hot_state = kHotUnordered;
+    hipEvent_t hot_event = nullptr; // after the launches that put the entries in that order (order_hot_rows)
     bool hot_taken = false;         // by a call, of this pattern or one before
     // owned scratch of the set-up kernels, and what they report (pinned host memory)
     int32_t *build_work = nullptr;
@@ -617,6 +620,7 @@ void free_layer_buffers(nerva_layer *l)
     free_pattern_buffers(l->spare);
     (void)hipFree(l->build_work);
     if (l->bind_result) (void)hipHostFree(l->bind_result);
+    if (l->hot_event) (void)hipEventDestroy(l->hot_event);
     (void)hipFree(l->scratch);
     (void)hipFree(l->tickets);
     (void)hipFree(l->strip_stream);
@@ -861,17 +865,28 @@ static hipError_t make_hot_order(const PatternBuffers &b, const HotRows &v, int3
     return launch_hot_order(v.rows, rows, b.indptr_t, b.mirror_mem, cols, b.mirror_mem + n64, sets + 4 * hot_sets_size(cols), b.hot, b.hot + n64, b.hot + 2 * n64,
                             plan_t.rows_by_length, reinterpret_cast<int4 *>(sets), s);
 }
-// For a call that takes it.  One that is recorded into a graph has not run: the next one makes the order again.
+// For a call that takes it: made by the first, which the others, on whatever stream, wait for.  (One that is recorded into a graph has not run: it makes the order in
+// the graph, the same again.)
 static hipError_t order_hot_rows(nerva_layer *l, hipStream_t s)
 {
-    if (l->hot_ordered) return hipSuccess;
+    if (l->hot_state == kHotOrdered) return hipSuccess;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
         (void)hipGetLastError();
         capture = hipStreamCaptureStatusActive;
     }
-    const hipError_t e = make_hot_order(l->cur, l->hot, l->rows, l->cols, l->nnz, l->plan_t, s);
-    if (e == hipSuccess && capture == hipStreamCaptureStatusNone) l->hot_ordered = l->hot_taken = true;
+    if (capture == hipStreamCaptureStatusNone && l->hot_state == kHotOnItsWay) {
+        if (hipEventQuery(l->hot_event) == hipSuccess) {
+            l->hot_state = kHotOrdered;
+            return hipSuccess;
+        }
+        (void)hipGetLastError();   // (not ready)
+        return hipStreamWaitEvent(s, l->hot_event, 0);
+    }
+    hipError_t e = make_hot_order(l->cur, l->hot, l->rows, l->cols, l->nnz, l->plan_t, s);
+    if (e != hipSuccess || capture != hipStreamCaptureStatusNone) return e;
+    e = hipEventRecord(l->hot_event, s);
+    if (e == hipSuccess) { l->hot_state = kHotOnItsWay; l->hot_taken = true; }
     return e;
 }
 
@@ -1059,6 +1074,7 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
     // (the dense route has no use for it; a layer none of whose calls has taken it, as the first one of a network, waits for one that does: making it takes 28 us of
     // the 117 that binding 1100 x 2600 at 10 % does)
     if (asked == NERVA_PARTITION_BALANCED && nnz > 0 && !takes_dense_route(l, nnz) && takes_hot_rows() &&
+        (l->hot_event || hipEventCreateWithFlags(&l->hot_event, hipEventDisableTiming) == hipSuccess) &&
         reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)) + static_cast<size_t>(rows) + cols)) {
         HotRows &v = out->hot;
         v.entry = B.hot; v.at = B.hot + n64; v.perm = B.hot + 2 * n64; v.sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.rows = out->plan.rows_by_length; v.share = in_lds;
@@ -1126,7 +1142,7 @@ static void adopt_pattern(nerva_layer *l, int32_t nnz, const int32_t *indptr, co
     l->perm = l->cur.mirror_mem + n64;
     l->pos_t = l->cur.mirror_mem + 2 * n64;
     l->values_t = reinterpret_cast<float *>(l->cur.mirror_mem + 3 * n64);
-    l->plan = bp.plan; l->plan_t = bp.plan_t; l->strips = bp.strips; l->hot = bp.hot; l->hot_ordered = l->hot_taken;
+    l->plan = bp.plan; l->plan_t = bp.plan_t; l->strips = bp.strips; l->hot = bp.hot; l->hot_state = l->hot_taken ? kHotOrdered : kHotUnordered;
     l->partial_stride = bp.partial_stride; l->partial_db_at = bp.partial_db_at; l->partial_tiles = bp.partial_tiles;
     l->scratch_ld = bp.scratch_ld;
     l->full_scratch_ld = bp.full_scratch_ld;

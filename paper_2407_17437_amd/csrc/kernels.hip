@@ -2260,7 +2260,7 @@ void sddmm_tiled_finish_kernel(const SddmmArgs a, const int n_tiles, const TileO
 // ---- both gradients where a few rows of dZ take most gathers ------------------------------------------
 // The backward pass on one gather stream (backward_fused_kernel) for matrices a few of whose rows hold most of the entries: the kHotRowsLds longest rows of W -- two thirds of the entries of 16384^2
 // power-law rows at 1 % -- are gathered from LDS, in which a work-group keeps its 64 columns of their dZ, the others from memory.  The entries of a mirror row are taken hot ones first
-// (HotRows, made when the pattern is bound).  Sixteen lanes serve a mirror row, four of which run side by side in a wave; a gathered row goes into the row's result with the weight moved
+// (HotRows, launch_hot_order).  Sixteen lanes serve a mirror row, four of which run side by side in a wave; a gathered row goes into the row's result with the weight moved
 // between lanes in the multiply-add (fma_row_lane), and into the entry's product with the mirror row's X, sixteen products at a time added up across the lanes (row16_transpose_sum).
 // What bounds it: the vector ALUs (11.3 instructions a gather of four rows by 64 columns, 74 % busy at the 1.8 GHz that the card then holds; texture-address units 67 %, where the pass without LDS has
 // them 79 % busy).  16384^2 at 1 %, batch 1024: 490 -> 370 us; of it, weights and sums in the order of the walk (stored through the mirror's positions: 50 more), rows side by side of like

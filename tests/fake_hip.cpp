@@ -20,7 +20,8 @@ std::string launched;
 PlanCounts counts[2];
 unsigned long long strip_counts = 0;   // as BindResult::strip, of plans that have room for strips
 int strip_blocks = -1;   // that the last bind asked for
-bool capturing = false;
+bool capturing = false, pending = false;
+int events = 0, waits = 0;
 long calls_until_failure = -1;   // of the calls that allocate, fill or wait
 int bad_pointers = 0, bad_grids = 0, dirty_tickets = 0, mixed_tickets = 0;
 std::map<const int32_t *, int> ticket_ends;   // what each ticket of a shared tile counts up to
@@ -79,6 +80,9 @@ int fake_mixed_tickets() { return mixed_tickets; }
 size_t fake_live_bytes() { return live_bytes; }
 int fake_strip_blocks() { return strip_blocks; }
 void fake_set_capturing(int on) { capturing = on; }
+void fake_set_pending(int on) { pending = on; }   // events that are recorded
+int fake_waits() { return waits; }
+int fake_events() { return events; }
 void fake_set_strips(int chunks, int steps) { strip_counts = static_cast<unsigned>(chunks) | static_cast<unsigned long long>(steps) << 32; }
 const char *fake_launched() { static std::string out; out.swap(launched); launched.clear(); return out.c_str(); }
 int fake_set(int side, const char *field, int value)
@@ -108,7 +112,10 @@ hipError_t hipGetSymbolAddress(void **p, const void *) { static char symbol[256]
 hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }   // (also of calls before the last one)
 const char *hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
 hipError_t hipEventCreate(hipEvent_t *) { return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = reinterpret_cast<hipEvent_t>(&events); ++events; return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return pending ? last = hipErrorNotReady : hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { ++waits; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { events -= e == reinterpret_cast<hipEvent_t>(&events); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }

@@ -379,13 +379,21 @@ def an_order_of_hot_rows_is_made_when_a_call_takes_it(L):
             L.hip.fake_set_capturing(1)
             assert L.backward(took[-1]) == 0 and L.backward(took[0]) == 0 and ordered() == 2
             L.hip.fake_set_capturing(0)
+            waits = L.hip.fake_waits()
+            L.hip.fake_set_pending(1)
             assert L.backward(took[-1]) == 0 and ordered() == 1
-            assert L.backward(took[-1]) == 0 and L.backward(took[0]) == 0 and ordered() == 0
+            # (while it has not come through, calls that may be on other streams wait for it, recorded ones make their own)
+            assert L.backward(took[-1]) == 0 and L.backward(took[0]) == 0 and ordered() == 0 and L.hip.fake_waits() == waits + 2
+            L.hip.fake_set_capturing(1)
+            assert L.backward(took[-1]) == 0 and ordered() == 1
+            L.hip.fake_set_capturing(0)
+            L.hip.fake_set_pending(0)
+            assert L.backward(took[-1]) == 0 and L.backward(took[0]) == 0 and ordered() == 0 and L.hip.fake_waits() == waits + 2
             # a layer that has taken it has it made as a pattern is bound
             assert L.rebind(nnz) == 0 and ordered() == 1
             assert L.backward(took[-1]) == 0 and ordered() == 0
         L.destroy()
-        assert L.hip.fake_live_bytes() == before and L.hip.fake_bad_pointers() == 0
+        assert L.hip.fake_live_bytes() == before and L.hip.fake_events() == 0 and L.hip.fake_bad_pointers() == 0
 
 
 def a_failed_rebind_leaves_strips_and_hot_rows_in_place(L):
