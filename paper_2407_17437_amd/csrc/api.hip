@@ -128,7 +128,7 @@ struct nerva_layer {
     HotRows hot;                    // entry nullptr: none
     HotState hot_state = kHotUnordered;
     hipEvent_t hot_event = nullptr; // after the launches that put the entries in that order (order_hot_rows)
-    bool hot_taken = false;         // by a call, of this pattern or one before
+    bool hot_at_bind = true;        // made as a pattern is bound: the first one, and the next after a call that has taken it
     // owned scratch of the set-up kernels, and what they report (pinned host memory)
     int32_t *build_work = nullptr;
     size_t build_work_ints = 0;
@@ -865,10 +865,11 @@ static hipError_t make_hot_order(const PatternBuffers &b, const HotRows &v, int3
     return launch_hot_order(v.rows, rows, b.indptr_t, b.mirror_mem, cols, b.mirror_mem + n64, sets + 4 * hot_sets_size(cols), b.hot, b.hot + n64, b.hot + 2 * n64,
                             plan_t.rows_by_length, reinterpret_cast<int4 *>(sets), s);
 }
-// For a call that takes it: made by the first, which the others, on whatever stream, wait for.  (One that is recorded into a graph has not run: it makes the order in
+// For a call that takes it: where it is not made yet by the first, which the others, on whatever stream, wait for.  (One that is recorded into a graph has not run: it makes the order in
 // the graph, the same again.)
 static hipError_t order_hot_rows(nerva_layer *l, hipStream_t s)
 {
+    l->hot_at_bind = true;
     if (l->hot_state == kHotOrdered) return hipSuccess;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
@@ -886,7 +887,7 @@ static hipError_t order_hot_rows(nerva_layer *l, hipStream_t s)
     hipError_t e = make_hot_order(l->cur, l->hot, l->rows, l->cols, l->nnz, l->plan_t, s);
     if (e != hipSuccess || capture != hipStreamCaptureStatusNone) return e;
     e = hipEventRecord(l->hot_event, s);
-    if (e == hipSuccess) { l->hot_state = kHotOnItsWay; l->hot_taken = true; }
+    if (e == hipSuccess) l->hot_state = kHotOnItsWay;
     return e;
 }
 
@@ -1071,14 +1072,14 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         g.split = B.split.rows.n > 0 ? &B.split : nullptr;
         return hot_rows_pay_somewhere(t, g, max_batch);
     };
-    // (the dense route has no use for it; a layer none of whose calls has taken it, as the first one of a network, waits for one that does: making it takes 28 us of
-    // the 117 that binding 1100 x 2600 at 10 % does)
+    // (The dense route has no use for it.  A new pattern of a layer whose calls have not taken it, as the first one of a network, waits for a call that does: making it
+    // takes 28 us of the 117 that binding 1100 x 2600 at 10 % does; a step of 2667-1317-8 at 6.7 %, batch 1016, with new patterns for both layers 217 -> 179.)
     if (asked == NERVA_PARTITION_BALANCED && nnz > 0 && !takes_dense_route(l, nnz) && takes_hot_rows() &&
         (l->hot_event || hipEventCreateWithFlags(&l->hot_event, hipEventDisableTiming) == hipSuccess) &&
         reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)) + static_cast<size_t>(rows) + cols)) {
         HotRows &v = out->hot;
         v.entry = B.hot; v.at = B.hot + n64; v.perm = B.hot + 2 * n64; v.sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.rows = out->plan.rows_by_length; v.share = in_lds;
-        if (l->hot_taken) {
+        if (l->hot_at_bind) {
             HIP_TRY(make_hot_order(B, v, rows, cols, nnz, out->plan_t, s));
             more_work = true;
         }
@@ -1142,7 +1143,7 @@ static void adopt_pattern(nerva_layer *l, int32_t nnz, const int32_t *indptr, co
     l->perm = l->cur.mirror_mem + n64;
     l->pos_t = l->cur.mirror_mem + 2 * n64;
     l->values_t = reinterpret_cast<float *>(l->cur.mirror_mem + 3 * n64);
-    l->plan = bp.plan; l->plan_t = bp.plan_t; l->strips = bp.strips; l->hot = bp.hot; l->hot_state = l->hot_taken ? kHotOrdered : kHotUnordered;
+    l->plan = bp.plan; l->plan_t = bp.plan_t; l->strips = bp.strips; l->hot = bp.hot; l->hot_state = l->hot_at_bind ? kHotOrdered : kHotUnordered; l->hot_at_bind = false;
     l->partial_stride = bp.partial_stride; l->partial_db_at = bp.partial_db_at; l->partial_tiles = bp.partial_tiles;
     l->scratch_ld = bp.scratch_ld;
     l->full_scratch_ld = bp.full_scratch_ld;

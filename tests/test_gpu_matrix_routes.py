@@ -770,7 +770,8 @@ def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
 
 
 def test_order_of_hot_rows_is_made_by_the_call_that_takes_it(nb, oracle):
-    """The first such call may be one that is recorded into a graph, which has not run when an eager one follows; then a new pattern, for whose binding the order is made at once."""
+    """Of a pattern bound to a layer that has not taken it: the first such call may be one that is recorded into a graph, which has not run when an eager one follows.  Then a new pattern, with
+    which the order is made as it is bound, and one more without a call between."""
     import torch
     rows, cols, batch = 1100, 2600, 500
     lay = hot_rows_layer(rows, cols, 400, 0.28, 20, 11)[0]
@@ -798,6 +799,7 @@ def test_order_of_hot_rows_is_made_by_the_call_that_takes_it(nb, oracle):
     warm.close()
     L = nb.SparseLinear(lay, max_batch=batch)
     assert nb.sparse_linear_routes(L.handle, batch) & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
+    L.rebind(lay.indptr, lay.indices, lay.values)
     side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
     with torch.cuda.graph(graph, stream=side):
@@ -817,6 +819,12 @@ def test_order_of_hot_rows_is_made_by_the_call_that_takes_it(nb, oracle):
     dXd.fill_(float("nan"))
     call(L, g)
     check(L, other, g, "rebound")
+    for pattern in (other, lay):
+        L.rebind(pattern.indptr, pattern.indices, pattern.values)
+    g = torch.full((lay.nnz,), float("nan"), device="cuda")
+    dXd.fill_(float("nan"))
+    call(L, g)
+    check(L, lay, g, "rebound twice")
     L.close()
 
 

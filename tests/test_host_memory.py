@@ -352,7 +352,7 @@ def both_gradients_go_apart_where_that_beats_hot_rows_in_lds(L):
 
 
 def an_order_of_hot_rows_is_made_when_a_call_takes_it(L):
-    """By the first that does; not where the layer's wide batches go by its dense copy, nor where at every batch the hot rows would be slower than both gradients apart."""
+    """As a layer is created, and for a new pattern by the first that does or where one has; not where the layer's wide batches go by its dense copy, nor where at every batch the hot rows would be slower than both gradients apart."""
     for rows, cols, nnz, max_batch, dense, ranges, most, share, made in (
             (2000, 4000, 4000000, 1024, None, 0, 0.52, 0.26, False),         # half of its entries stored: the dense route
             (2000, 4000, 1000000, 1024, None, 0, 0.52, 0.26, True),
@@ -367,11 +367,12 @@ def an_order_of_hot_rows_is_made_when_a_call_takes_it(L):
         assert L.create(rows, cols, nnz, max_batch) == 0
         took = [batch for batch in range(1, max_batch + 1) if L.routes(batch) & 2]
         assert bool(took) == made, (rows, cols, nnz)
+        assert any("hot_order_kernel" in k for k in L.launched()) == made, (rows, cols, nnz)
 
         def ordered():
             return sum("hot_order_kernel" in k for k in L.launched())
 
-        # made by the first call that takes it: nothing else of the layer pays for it
+        # for a new pattern by the first call that takes it, where none has: nothing else of the layer pays for it
         assert L.forward(max_batch) == 0 and L.backward(max_batch, dx=False) == 0 and L.backward(64) == 0 and L.rebind(nnz) == 0
         assert ordered() == 0
         if made:
@@ -390,8 +391,11 @@ def an_order_of_hot_rows_is_made_when_a_call_takes_it(L):
             L.hip.fake_set_pending(0)
             assert L.backward(took[-1]) == 0 and L.backward(took[0]) == 0 and ordered() == 0 and L.hip.fake_waits() == waits + 2
             # a layer that has taken it has it made as a pattern is bound
-            assert L.rebind(nnz) == 0 and ordered() == 1
-            assert L.backward(took[-1]) == 0 and ordered() == 0
+            for _ in range(2):
+                assert L.rebind(nnz) == 0 and ordered() == 1
+                assert L.backward(took[-1]) == 0 and ordered() == 0
+            assert L.rebind(nnz) == 0 and ordered() == 1 and L.rebind(nnz) == 0 and ordered() == 0
+            assert L.backward(took[0]) == 0 and ordered() == 1
         L.destroy()
         assert L.hip.fake_live_bytes() == before and L.hip.fake_events() == 0 and L.hip.fake_bad_pointers() == 0
 
