@@ -17,15 +17,19 @@ def nb():
     return binding
 
 
-def check_layer(nb, oracle, lay, batch, ld=None, max_batch=None, seed=1, backward=True, strips=None, hot=None):
-    """strips, hot: whether the library has to say that the product runs in strips, and that the longest rows of dZ lie in LDS."""
+def routes(nb, lay, batch, max_batch=None):
+    """The ways that calls of the layer take, as the library says."""
+    L = nb.SparseLinear(lay, max_batch=max_batch or batch)
+    taken = nb.sparse_linear_routes(L.handle, batch)
+    L.close()
+    return taken
+
+
+def check_layer(nb, oracle, lay, batch, ld=None, max_batch=None, seed=1, backward=True):
     import torch
     rng = np.random.default_rng(seed)
     X = rng.standard_normal((lay.cols, batch)).astype(np.float32); dY = rng.standard_normal((lay.rows, batch)).astype(np.float32)
     L = nb.SparseLinear(lay, max_batch=max_batch or batch)
-    routes = nb.sparse_linear_routes(L.handle, batch)
-    assert strips is None or bool(routes & nb.NERVA_ROUTE_FORWARD_STRIPS) == strips
-    assert hot is None or bool(routes & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS) == hot
     Xd, dYd = nb.to_dense(X, ld=ld), nb.to_dense(dY, ld=ld)
     Yd, dXd = nb.dense(lay.rows, batch, ld=ld), nb.dense(lay.cols, batch, ld=ld)
     g, db = torch.full((lay.nnz,), float("nan"), device="cuda"), torch.full((lay.rows,), float("nan"), device="cuda")
@@ -600,10 +604,23 @@ def prefer_strips(nb):
     (130, 9001, lambda i: 1200 - i, 195, 199), (4500, 700, lambda i: 12, 1023, None), (900, 1500, lambda i: 30, 1026, 1027),   # long segments; batches beyond 1024
 ])
 def test_product_in_strips(nb, oracle, prefer_strips, rows, cols, lens, batch, ld):
-    check_layer(nb, oracle, strips_case(rows, cols, lens, rows + batch), batch, ld=ld, backward=False, strips=True)
+    check_layer(nb, oracle, strips_case(rows, cols, lens, rows + batch), batch, ld=ld, backward=False)
+
+
+@pytest.mark.parametrize("rows,cols,lens,batch", [case[:4] for case in test_product_in_strips.pytestmark[0].args[1]])
+def test_matrices_of_the_strips_tests_take_strips(nb, prefer_strips, rows, cols, lens, batch):
+    assert routes(nb, strips_case(rows, cols, lens, rows + batch), batch) & nb.NERVA_ROUTE_FORWARD_STRIPS
 
 
 def test_product_in_strips_where_the_rule_takes_it(nb, oracle):
+    """The layer sizes at which strips are the library's own choice, bound for a wider batch than it is called with; then another pattern, and the weights of that changed."""
+    rows, cols, batch = 6001, 2999, 811
+    lay = layer_case(rows, cols, 0.014, seed=3, relu=True)
+    check_layer(nb, oracle, lay, batch, ld=813, max_batch=1024, backward=False)
+    check_layer(nb, oracle, lay, 64, max_batch=1024, backward=False)
+
+
+def test_product_in_strips_through_changed_weights_and_patterns(nb, oracle):
     """The layer sizes at which strips are the library's own choice, bound for a wider batch than it is called with: one handle through weights that change in place, a pattern of more entries, whose
     stream is longer, one of fewer, and one of so few that the product goes another way; and narrower batches between."""
     import torch
@@ -646,7 +663,6 @@ def test_product_in_strips_keeps_a_non_finite_operand_row_to_the_rows_that_read_
     X = np.random.default_rng(5).standard_normal((cols, batch)).astype(np.float32)
     X[list(bad)] = np.inf
     L = nb.SparseLinear(lay, max_batch=batch)
-    assert nb.sparse_linear_routes(L.handle, batch) & nb.NERVA_ROUTE_FORWARD_STRIPS
     Yd = nb.dense(rows, batch)
     nb.sparse_linear_forward(L.handle, nb.to_dense(X), Yd, batch)
     torch.cuda.synchronize()
@@ -679,7 +695,6 @@ def test_training_step_in_strips_on_new_patterns(nb, oracle, prefer_strips):
                     L.velocity = torch.zeros_like(L.values)
                     nb.sparse_linear_rebind(L.handle, L.values.numel(), L.indptr, L.indices, L.values)
                     nb.mlp_rebind_velocity(m.handle, l, L.velocity)
-        assert all(nb.sparse_linear_routes(m.layers[l].handle, batch) & nb.NERVA_ROUTE_FORWARD_STRIPS for m in mlps for l in (0, 1))
         for _ in range(3):
             for m in mlps:
                 m.train_step(X, labels, batch, 0.01, 0.9)
@@ -732,41 +747,20 @@ def hot_rows_layer(rows, cols, n_long, long_share, short, seed, relu=False):
 ])
 def test_both_gradients_with_hot_rows_in_lds(nb, oracle, rows, cols, n_long, batch, ld, relu):
     lay, _ = hot_rows_layer(rows, cols, n_long, 0.28 if rows < 6000 else 0.25, 20, rows + batch, relu)
-    check_layer(nb, oracle, lay, batch, ld=ld, hot=True)
+    check_layer(nb, oracle, lay, batch, ld=ld)
+
+
+@pytest.mark.parametrize("rows,cols,n_long,batch,relu", [(*case[:4], case[5]) for case in test_both_gradients_with_hot_rows_in_lds.pytestmark[0].args[1]])
+def test_matrices_of_the_hot_rows_tests_take_them_from_lds(nb, rows, cols, n_long, batch, relu):
+    assert routes(nb, hot_rows_layer(rows, cols, n_long, 0.28 if rows < 6000 else 0.25, 20, rows + batch, relu)[0], batch) & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
 
 
 @pytest.mark.parametrize("rows,cols,density,batch,hot", [(1100, 2600, 0.1, 1000, True), (1201, 9001, 0.06, 319, True), (1500, 1500, 0.05, 1024, False), (1500, 8000, 0.05, 256, False)])
 def test_both_gradients_of_even_rows_with_the_first_512_in_lds(nb, oracle, rows, cols, density, batch, hot):
     """Half of the gathers, or fewer, are from LDS: where the mirror's rows are long that still pays."""
-    check_layer(nb, oracle, layer_case(rows, cols, density, seed=rows + batch), batch, hot=hot)
-
-
-def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
-    """A row of dZ of infinities, one of those in LDS and one that is not: they reach the gradients of the inputs that reference them, and their own entries' and biases', and nothing else."""
-    import torch
-    rows, cols, batch = 1100, 2600, 500
-    lay, long_rows = hot_rows_layer(rows, cols, 400, 0.28, 20, 11)
-    short_rows = [i for i in range(rows) if i not in set(long_rows)]
-    rng = np.random.default_rng(3)
-    X = rng.standard_normal((cols, batch)).astype(np.float32); dY = rng.standard_normal((rows, batch)).astype(np.float32)
-    bad = [long_rows[7], short_rows[-3]]
-    dY[bad] = np.inf
-    L = nb.SparseLinear(lay, max_batch=batch)
-    assert nb.sparse_linear_routes(L.handle, batch) & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
-    dXd, g, db = nb.dense(cols, batch), torch.empty(lay.nnz, device="cuda"), torch.empty(rows, device="cuda")
-    nb.sparse_linear_backward(L.handle, nb.to_dense(X), None, nb.to_dense(dY), dXd, g, db, batch)
-    torch.cuda.synchronize()
-    row_of = np.repeat(np.arange(rows), np.diff(lay.indptr))
-    hit = np.zeros(cols, dtype=bool); hit[lay.indices[np.isin(row_of, bad)]] = True
-    dX, gh = dXd.cpu().numpy(), g.cpu().numpy()
-    assert np.isfinite(dX[~hit]).all() and not np.isfinite(dX[hit]).all(axis=1).any()
-    own = np.isin(row_of, bad)
-    assert np.isfinite(gh[~own]).all() and not np.isfinite(gh[own]).any()
-    assert np.array_equal(np.isfinite(db.cpu().numpy()), ~np.isin(np.arange(rows), bad))
-    dY[bad] = 0
-    ref, S = oracle.spmm_t(rows, cols, lay.indptr, lay.indices, lay.values, dY)
-    close(dX[~hit], ref[~hit], S[~hit], what="dX beside infinities")
-    L.close()
+    lay = layer_case(rows, cols, density, seed=rows + batch)
+    assert bool(routes(nb, lay, batch) & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS) == hot
+    check_layer(nb, oracle, lay, batch)
 
 
 def test_order_of_hot_rows_is_made_by_the_call_that_takes_it(nb, oracle):
@@ -828,21 +822,61 @@ def test_order_of_hot_rows_is_made_by_the_call_that_takes_it(nb, oracle):
     L.close()
 
 
+def test_hot_rows_in_lds_keep_infinities_to_the_rows_that_read_them(nb, oracle):
+    """A row of dZ of infinities, one of those in LDS and one that is not: they reach the gradients of the inputs that reference them, and their own entries' and biases', and nothing else."""
+    import torch
+    rows, cols, batch = 1100, 2600, 500
+    lay, long_rows = hot_rows_layer(rows, cols, 400, 0.28, 20, 11)
+    short_rows = [i for i in range(rows) if i not in set(long_rows)]
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal((cols, batch)).astype(np.float32); dY = rng.standard_normal((rows, batch)).astype(np.float32)
+    bad = [long_rows[7], short_rows[-3]]
+    dY[bad] = np.inf
+    L = nb.SparseLinear(lay, max_batch=batch)
+    dXd, g, db = nb.dense(cols, batch), torch.empty(lay.nnz, device="cuda"), torch.empty(rows, device="cuda")
+    nb.sparse_linear_backward(L.handle, nb.to_dense(X), None, nb.to_dense(dY), dXd, g, db, batch)
+    torch.cuda.synchronize()
+    row_of = np.repeat(np.arange(rows), np.diff(lay.indptr))
+    hit = np.zeros(cols, dtype=bool); hit[lay.indices[np.isin(row_of, bad)]] = True
+    dX, gh = dXd.cpu().numpy(), g.cpu().numpy()
+    assert np.isfinite(dX[~hit]).all() and not np.isfinite(dX[hit]).all(axis=1).any()
+    own = np.isin(row_of, bad)
+    assert np.isfinite(gh[~own]).all() and not np.isfinite(gh[own]).any()
+    assert np.array_equal(np.isfinite(db.cpu().numpy()), ~np.isin(np.arange(rows), bad))
+    dY[bad] = 0
+    ref, S = oracle.spmm_t(rows, cols, lay.indptr, lay.indices, lay.values, dY)
+    close(dX[~hit], ref[~hit], S[~hit], what="dX beside infinities")
+    L.close()
+
+
 @pytest.mark.parametrize("batch", [512, 449])
 def test_training_step_with_hot_rows_in_lds(nb, oracle, batch):
     """The layer's update behind the same pass: every stage against the oracle, over steps whose weights each find changed."""
     import torch
-    from test_gpu_mlp_step import _launch_names, snapshot, stage_parity
+    from test_gpu_mlp_step import snapshot, stage_parity
     sizes = (60, 2600, 1100, 10)
     mlp = wl.make_mlp(sizes, layer_nnz=(5200, 2600, 2000), pattern_seed=1, value_seed=2)
     mlp.layers[1] = hot_rows_layer(1100, 2600, 400, 0.28, 20, 5, relu=True)[0]
     Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 2, seed=3)
     M = nb.MLP(mlp, batch)
-    assert nb.sparse_linear_routes(M.layers[1].handle, batch) & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
     for t in range(2):
         before = snapshot(M)
         M.train_step(nb.to_dense(Xs[t]), torch.as_tensor(Ts[t]).cuda(), batch, 0.05, 0.9)
         torch.cuda.synchronize()
         stage_parity(nb, torch, oracle, M, mlp, before, Xs[t], Ts[t], batch, 0.05, 0.9, False)
+    M.close()
+
+
+@pytest.mark.parametrize("batch", [512, 449])
+def test_training_step_takes_hot_rows_from_lds(nb, batch):
+    """The network of the test above."""
+    import torch
+    from test_gpu_mlp_step import _launch_names
+    sizes = (60, 2600, 1100, 10)
+    mlp = wl.make_mlp(sizes, layer_nnz=(5200, 2600, 2000), pattern_seed=1, value_seed=2)
+    mlp.layers[1] = hot_rows_layer(1100, 2600, 400, 0.28, 20, 5, relu=True)[0]
+    Xs, Ts = wl.make_batches(sizes[0], sizes[-1], batch, 1, seed=3)
+    M = nb.MLP(mlp, batch)
+    assert nb.sparse_linear_routes(M.layers[1].handle, batch) & nb.NERVA_ROUTE_BACKWARD_HOT_ROWS
     assert "backward_fused[1]" in _launch_names(nb, torch, M, Xs[0], Ts[0], batch)   # (whose kernels the route says)
     M.close()
