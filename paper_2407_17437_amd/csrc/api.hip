@@ -1072,10 +1072,16 @@ static int build_structures(nerva_layer *l, int32_t nnz, const int32_t *indptr, 
         g.split = B.split.rows.n > 0 ? &B.split : nullptr;
         return hot_rows_pay_somewhere(t, g, max_batch);
     };
+    auto has_event = [&] {
+        if (l->hot_event || hipEventCreateWithFlags(&l->hot_event, hipEventDisableTiming) == hipSuccess) return true;
+        (void)hipGetLastError();
+        l->hot_event = nullptr;
+        return false;
+    };
     // (The dense route has no use for it.  A new pattern of a layer whose calls have not taken it, as the first one of a network, waits for a call that does: making it
     // takes 28 us of the 117 that binding 1100 x 2600 at 10 % does; a step of 2667-1317-8 at 6.7 %, batch 1016, with new patterns for both layers 217 -> 179.)
     if (asked == NERVA_PARTITION_BALANCED && nnz > 0 && !takes_dense_route(l, nnz) && takes_hot_rows() &&
-        (l->hot_event || hipEventCreateWithFlags(&l->hot_event, hipEventDisableTiming) == hipSuccess) &&
+        has_event() &&
         reserve_optional(&B.hot, &B.hot_ints, 4 * n64 + 4 * static_cast<size_t>(hot_sets_size(cols)) + static_cast<size_t>(rows) + cols)) {
         HotRows &v = out->hot;
         v.entry = B.hot; v.at = B.hot + n64; v.perm = B.hot + 2 * n64; v.sets = reinterpret_cast<const int4 *>(B.hot + 4 * n64); v.rows = out->plan.rows_by_length; v.share = in_lds;

@@ -112,7 +112,7 @@ hipError_t hipGetSymbolAddress(void **p, const void *) { static char symbol[256]
 hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }   // (also of calls before the last one)
 const char *hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
 hipError_t hipEventCreate(hipEvent_t *) { return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = reinterpret_cast<hipEvent_t>(&events); ++events; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { if (fails(hipErrorOutOfMemory)) return hipErrorOutOfMemory; *e = reinterpret_cast<hipEvent_t>(&events); ++events; return hipSuccess; }
 hipError_t hipEventQuery(hipEvent_t) { return pending ? last = hipErrorNotReady : hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { ++waits; return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { events -= e == reinterpret_cast<hipEvent_t>(&events); return hipSuccess; }

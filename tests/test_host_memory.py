@@ -434,6 +434,27 @@ def a_failed_rebind_leaves_strips_and_hot_rows_in_place(L):
         assert 3 < k < 99
 
 
+def hot_rows_are_done_without_where_something_for_them_fails(L):
+    """Whichever of a layer's allocations fails: it is not created, or its calls are in order, and their first launches report nothing that went before."""
+    L.counts(0, n_blocks=600, longest_row=3000, hot_nnz=int(0.76 * 2684354), hot_lds_nnz=int(0.67 * 2684354))
+    L.counts(1, n_blocks=600, longest_row=600, hot_nnz=300000)
+    took = set()
+    for k in range(60):
+        L.hip.fake_fail_after(k)
+        rc = L.create(16384, 16384, 2684354, 1024)
+        left = L.hip.fake_fail_after_left()
+        L.hip.fake_fail_after(-1)
+        assert rc in (0, -5), k
+        if rc == 0:
+            took.add(L.routes(1024) & 2)
+            assert L.backward(1024) == 0 and L.forward(1024) == 0, (k, L.lib.nerva_last_error())
+            L.destroy()
+        assert L.hip.fake_events() == 0 and L.hip.fake_bad_pointers() == 0, k
+        if left >= 0:
+            break
+    assert took == {0, 2} and 3 < k < 59
+
+
 def a_grid_has_no_more_work_groups_than_a_launch_can(L):
     """The gradient in column tiles comes in quarters of the partition's work-groups: where these are too many for a grid, the rows go through all columns at once."""
     for n_blocks, tiled in ((30_000_000, True), (60_000_000, False)):
@@ -552,7 +573,7 @@ def strips_are_planned_where_a_batch_takes_them(L):
         L.destroy()
 
 
-CASES = [a_failed_rebind_leaves_strips_and_hot_rows_in_place, an_order_of_hot_rows_is_made_when_a_call_takes_it, both_gradients_go_apart_where_that_beats_hot_rows_in_lds, strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
+CASES = [hot_rows_are_done_without_where_something_for_them_fails, a_failed_rebind_leaves_strips_and_hot_rows_in_place, an_order_of_hot_rows_is_made_when_a_call_takes_it, both_gradients_go_apart_where_that_beats_hot_rows_in_lds, strips_are_planned_where_a_batch_takes_them, hot_rows_are_kept_in_lds_where_that_is_faster, the_first_layers_gradient_takes_a_second_pass_of_other_partial_products_only, products_of_very_many_entries_are_staged, a_grid_has_no_more_work_groups_than_a_launch_can, both_gradients_go_apart_where_that_is_faster, short_segments_are_staged_by_the_work_of_the_plan, few_column_tiles_serve_where_they_pay, gathers_of_a_backward_tile_are_all_in_flight_where_its_waves_fit, a_thin_matrix_takes_the_bf16_units_where_they_pay, slices_of_dense_rows_stay_where_their_parts_have_no_room, a_ticket_of_a_shared_tile_counts_to_one_number, wide_products_of_dense_rows_take_the_bf16_units, a_layer_is_created_without_what_it_can_do_without, a_single_tile_needs_no_partial_products, a_failed_call_is_reported_once, a_failed_rebind_leaves_nothing_freed_in_use, dense_rows_go_apart_by_the_batch_of_the_call]
 
 
 @pytest.fixture(scope="module")
